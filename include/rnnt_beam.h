@@ -87,8 +87,14 @@ typedef struct {
                                 (Sec. 2.2, "a maximum of s expansions per frame") */
   float prune_margin;        /* AES++ only: a token whose log-probability is more than this below
                                 the best one of its hypothesis is not expanded; INFINITY = off */
-  int32_t use_graph;         /* 1: replay the per-step kernels as a captured HIP graph (Sec. 2.1,
-                                "CUDA Graphs"); 0: launch them one by one */
+  int32_t use_graph;         /* 1: no launch per step.  LSTM decoders whose weights fit the chip (H, P multiples of 64 up to 640,
+                                V <= 1024, no tdt_all_pairs) run the step loop as one launch whose blocks keep the weights
+                                on chip ("resident loop"; batches of up to 48 hypotheses per 32 compute units); all others
+                                replay the per-step kernels as a captured HIP graph (Sec. 2.1, "CUDA Graphs").  0: the
+                                per-step kernels are launched one by one.  The results are the same bit for bit up to 256
+                                hypotheses.  The resident loop needs every one of its blocks on the chip at once: where they
+                                do not find room within 50 ms, or another thread's decode holds the device, the per-step
+                                launches decode the batch */
   int32_t joint_path;        /* rnnt_joint_path_t; create fails if MATERIALIZED is asked for a decoder
                                 that cannot take it */
   int32_t lm_rule;           /* how the LM enters a candidate's score (Sec. 2.3): 0 or 4 = Eq. (4), tokens get
@@ -265,7 +271,8 @@ int rnnt_beam_debug_block_map(int32_t a_tiles, int32_t a_m, int32_t b_begin, int
 
 /* Test hook for the error path of the single-launch step loop: the number of polls after which a wait between its
  * blocks gives up (default 2^22).  With a limit of a few polls the first wait fails, every block returns, and
- * rnnt_beam_results reports RNNT_E_HIP; no kernel is left waiting. */
+ * rnnt_beam_results reports RNNT_E_HIP; no kernel is left waiting.  The resident loop (use_graph) gives up at its start
+ * and the batch is decoded with per-step launches. */
 int rnnt_beam_debug_set_spin_limit(rnnt_beam_t *h, int32_t polls);
 
 /* Time, in milliseconds, between the first and the last kernel of the last decode (HIP events on

@@ -290,4 +290,17 @@ __device__ __forceinline__ void wave_best(double &v, int &i) {
   i = bi;
 }
 
+// ---- arithmetic of the LSTM cell
+__device__ __forceinline__ float sigmoid_f(float x) { return 1.f / (1.f + __expf(-x)); }
+__device__ __forceinline__ float tanh_f(float x) {
+  const float e = __expf(-2.f * fabsf(x));
+  const float r = (1.f - e) / (1.f + e);
+  return x < 0.f ? -r : r;
+}
+// gates (i, f, g, o) = recurrent part r4 + token part g4; c: the unit's old cell state in, the new one out; returns h
+__device__ __forceinline__ float lstm_unit(float4 r4, float4 g4, float &c) {
+  c = sigmoid_f(r4.y + g4.y) * c + sigmoid_f(r4.x + g4.x) * tanh_f(r4.z + g4.z);
+  return sigmoid_f(r4.w + g4.w) * tanh_f(c);
+}
+
 }  // namespace rb

@@ -1,0 +1,1163 @@
+// The whole step loop of an LSTM decoder in one launch whose blocks keep the weights on chip from the first step to the
+// last ("resident" loop).
+//
+// What bounds the per-step launches is not their work but their boundaries: three dependent kernels of 4 to 14 us per
+// step of which each pays 2 to 3 us of launch head and tail, fetches the weights anew (the caches do not survive a
+// kernel boundary) and hands its results over through memory.  Here the utterances are dealt out to groups of blocks
+// (at most one group per 32 compute units) that decode them independently of each other.  A group holds every weight of
+// the three contractions once, in registers and LDS: a block owns some 16-row tiles of W_hh (at most 6, with the LSTM
+// cells of their four units each), of the output layer and of the prediction projection.  One step of a group:
+//   cell    words of the last step -> the owners of W_hh tiles update the cells of their units        -> h
+//   P       h    -> the owners of projection tiles: pre = f_proj[frame] + W_pred h + b_pred           -> pre
+//   J       pre  -> the owners of output-layer tiles: z = W_out ReLU(pre) + b_out                     -> logits
+//   select  z    -> one block per utterance (a wave per hypothesis): top Beam, tree, recombination    -> words
+//   R       h    -> the owners of W_hh tiles: W_hh h for the next cell update, under the selection
+// Hand-over between blocks: an array that one phase writes and another reads is pre-filled with a bit pattern that no
+// result has (a NaN with all bits set); the reader loads the data itself, device-coherently, until none of it holds the
+// pattern.  No barrier, no flag and no acknowledged store lies between the two (one hop costs 0.6 us; stores, their
+// acknowledgement, a counter and then the loads 2.0 us).  The words of the selection carry the step's number instead.
+// A writer puts the pattern back once a word of a later phase proves that every reader is through (see the clear_
+// functions), two to four steps before the array is used again.
+//
+// Every sum is formed in the order of the per-step kernels (K slices of 1/8 of the contraction, one chain of fused
+// multiply-adds each, in the order in which the 32x32x2 matrix instructions take their k; slices added first to last), so the
+// results are the same bit for bit: a 16x16x4 fp32 matrix instruction rounds like four fused multiply-adds in a row.
+//
+// Every wait is bounded: a wave that waits too long raises the abort word and ends, every other wave sees the word (or
+// its own limit) and ends too, and the host decodes the batch with the per-step launches instead.
+#pragma once
+#include "lm_device.h"
+#include "select.h"
+
+namespace rb {
+
+constexpr int kResWaves = 8, kResThreads = 64 * kResWaves;
+constexpr int kResSlot = 16;         // slots per tile
+constexpr int kResMaxNT = 3;         // slot tiles per group
+constexpr int kResMaxR = 6;          // W_hh tiles per block
+constexpr int kResMaxLdsTiles = 2;   // tiles that wait in LDS: projection tiles and the output-layer tile beyond those in registers
+constexpr int kResMaxP = 2;
+constexpr int kResMaxSel = 4;        // utterances per selecting block
+constexpr int kResMaxRounds = 10;    // rounds of 8 k per wave slice: H, P <= 640
+constexpr int kResMaxV = 1024;
+constexpr int kResStepRing = 4;      // ring of h and of the words; pre and logits alternate
+constexpr uint32_t kResEmpty = 0xffffffffu;
+constexpr int kResSurvivors = 128;
+constexpr int kResRedBlock = 2048;   // floats of one 16-row tile's partial sums: 8 waves x 64 lanes x 4
+
+// What one block of a group owns (the same table for every group).
+struct ResTab {
+  int8_t nR, nJ, nP, pad;
+  int16_t R[kResMaxR], J[3], P[kResMaxP];
+};
+// output-layer tiles a block keeps in registers (a tile is 16 rows; 32 with the bf16 matrix instructions)
+template <bool BF16>
+constexpr int kResRegJ = BF16 ? 1 : 2;
+// 16-row tiles whose partial sums one half of the buffer holds
+template <bool BF16>
+constexpr int kResRedBlocks = BF16 ? 4 : 3;
+
+// Fragment order of an activation vector set: round (8 k), k-quad kq, slot, 2 floats; element 0 is k = 8 round +
+// {0, 4, 1, 5}[kq], element 1 is two further.  A lane (slot, kq) of a wave reads its two matrix operands of a round with one
+// 8-byte load.  Unit order within a W_hh tile follows: tile t holds units 8 (t / 2) + t % 2 + {0, 2, 4, 6}, whose 16
+// slots are 256 contiguous bytes.
+__host__ __device__ inline int res_k_of(int round, int kq, int e) { return 8 * round + (kq & 1) * 4 + (kq >> 1) + 2 * e; }
+
+struct ResArgs {
+  const float *WR, *WJ, *WP;         // [tile][round][64 lanes][2] (bf16 models: WR only)
+  const uint64_t *WJb, *WPb;         // bf16 models: [32-row tile][round][64 lanes] four bf16 (k of the lane's half)
+  const float *b_out, *b_pred, *G, *f_proj;
+  const int *lengths;
+  float *hb, *pb, *zb;               // rings of the hand-over arrays, all groups
+  uint64_t *words;
+  const ResTab *tab;                 // of the group's blocks behind the selecting ones
+  int *ctl;                          // [0] blocks that have started, [1] abort
+  volatile int *h_abort;             // pinned host word
+  SelectArgs sel;
+  LmView lm;
+  int B, K, T, V, N, Npad, H, P;
+  int n_groups, n_sel, upc;          // groups; per group: selecting blocks, utterances of each
+  int NT, halves, has_lm;            // slot tiles per group
+  int rounds_h, rounds_p;            // rounds of 8 k per wave slice over H and over P
+  int poll_limit, start_limit;       // polls of a data wait; ticks (10 ns) of the wait for all blocks
+  int start_blocks;                  // how many those are
+};
+
+// The kernel's arguments, read from the argument segment anew at the begin of every phase: kept in scalar registers over
+// the whole loop they would push the weights out of the vector registers (a thousand spills).
+__device__ __forceinline__ const ResArgs &res_args() {
+  typedef const __attribute__((address_space(4))) ResArgs ConstArgs;
+  ConstArgs *p = (ConstArgs *)__builtin_amdgcn_kernarg_segment_ptr();
+  asm volatile("" : "+s"(p));
+  return *(const ResArgs *)p;
+}
+
+__device__ __forceinline__ floatx4 mfma16(float a, float b, floatx4 acc) {
+  return __builtin_amdgcn_mfma_f32_16x16x4f32(a, b, acc, 0, 0, 0);
+}
+__device__ __forceinline__ float lo_f(uint64_t x) { return __uint_as_float((uint32_t)x); }
+__device__ __forceinline__ float hi_f(uint64_t x) { return __uint_as_float((uint32_t)(x >> 32)); }
+// whether any of a lane's words still holds the pattern in one of its halves: the pattern is the largest 32-bit number
+template <int N>
+__device__ __forceinline__ bool res_any_empty(const uint64_t (&x)[N]) {
+  uint32_t m = 0;
+#pragma unroll
+  for (int i = 0; i < N; ++i) m = max(m, max((uint32_t)x[i], (uint32_t)(x[i] >> 32)));
+  return m == kResEmpty;
+}
+__device__ __forceinline__ uint64_t pack2(float lo, float hi) {
+  return (uint64_t)__float_as_uint(hi) << 32 | __float_as_uint(lo);
+}
+
+// bounded waiting: true while another poll may follow
+struct ResWait {
+  int n = 0;
+  __device__ __forceinline__ bool again() {
+    if ((++n & 255) == 0) return more();
+    return true;
+  }
+  __device__ __forceinline__ bool more() const {
+    const ResArgs &a = res_args();
+    if (n < a.poll_limit && !load_agent(a.ctl + 1)) return true;
+    store_agent(a.ctl + 1, 1);
+    *a.h_abort = 1;
+    return false;
+  }
+};
+
+// Waits until one 8-byte word of every lane is there.  (One load per poll: all blocks of a group poll at once, and with all
+// words of a lane in every poll, 5 KB per wave, the polls alone filled the L2's bandwidth.)
+__device__ __forceinline__ bool res_probe(const uint64_t *p, ResWait &w) {
+  for (;;) {
+    const uint64_t x[1] = {load_agent(p)};
+    if (__ballot(res_any_empty(x)) == 0ull) return true;
+    if (!w.again()) return false;
+  }
+}
+// N 8-byte words of a lane as soon as all are there (in every lane of the wave), the last one first.  at(i): address of
+// word i; the first n are used (FULL: all N).
+template <bool FULL, int N, class AT>
+__device__ __forceinline__ bool res_gather(AT at, int n, uint64_t (&x)[N]) {
+  ResWait w;
+  for (;;) {
+    if (!res_probe(at(FULL ? N - 1 : n - 1), w)) return false;
+#pragma unroll
+    for (int i = 0; i < N; ++i) {
+      x[i] = 0;
+      if (FULL || i < n) x[i] = load_agent(at(i));
+    }
+    if (__ballot(res_any_empty(x)) == 0ull) return true;
+    if (!w.again()) return false;
+  }
+}
+
+// x[i] for an index that is the same in all lanes but not known at compile time
+__device__ __forceinline__ uint64_t res_pick(const uint64_t (&x)[kResMaxRounds], int i) {
+  uint64_t v = x[0];
+#pragma unroll
+  for (int q = 1; q < kResMaxRounds; ++q) v = i == q ? x[q] : v;
+  return v;
+}
+
+// ---- addresses of the hand-over arrays
+struct ResAddr {
+  float *hb, *pb, *zb;
+  uint64_t *words;
+  size_t h_ring, p_ring, z_ring, w_ring, h_tile, p_tile;
+  int Npad;
+  __device__ __forceinline__ float *h(int step, int nt) const { return hb + (step & (kResStepRing - 1)) * h_ring + nt * h_tile; }
+  __device__ __forceinline__ float *p(int step, int nt) const { return pb + (step & 1) * p_ring + nt * p_tile; }
+  __device__ __forceinline__ float *z(int step, int slot) const { return zb + (step & 1) * z_ring + (size_t)slot * Npad; }
+  __device__ __forceinline__ uint64_t *w(int step) const { return words + (step & (kResStepRing - 1)) * w_ring; }
+};
+__host__ __device__ inline size_t res_h_floats(const ResArgs &a) { return (size_t)kResStepRing * a.n_groups * a.NT * a.P * kResSlot; }
+__host__ __device__ inline size_t res_p_floats(const ResArgs &a) { return (size_t)2 * a.n_groups * a.NT * a.H * kResSlot; }
+__host__ __device__ inline size_t res_z_floats(const ResArgs &a) { return (size_t)2 * a.n_groups * a.NT * kResSlot * a.Npad; }
+__host__ __device__ inline size_t res_words(const ResArgs &a) { return (size_t)kResStepRing * a.n_groups * a.NT * kResSlot; }
+__device__ __forceinline__ ResAddr res_addr(const ResArgs &a, int g) {
+  ResAddr r;
+  r.Npad = a.Npad;
+  r.h_tile = (size_t)a.P * kResSlot;
+  r.p_tile = (size_t)a.H * kResSlot;
+  r.h_ring = (size_t)a.n_groups * a.NT * r.h_tile;
+  r.p_ring = (size_t)a.n_groups * a.NT * r.p_tile;
+  r.z_ring = (size_t)a.n_groups * a.NT * kResSlot * a.Npad;
+  r.w_ring = (size_t)a.n_groups * a.NT * kResSlot;
+  r.hb = a.hb + (size_t)g * a.NT * r.h_tile;
+  r.pb = a.pb + (size_t)g * a.NT * r.p_tile;
+  r.zb = a.zb + (size_t)g * a.NT * kResSlot * a.Npad;
+  r.words = a.words + (size_t)g * a.NT * kResSlot;
+  return r;
+}
+
+// what a wave knows about itself and its block
+struct ResBlock {
+  int g, nu, nslots;                 // group, utterances and slots of the group
+  int nR, nJ, nP;
+  int wave;
+  int ptile, jtile[2];               // the tile of 16 outputs / columns whose sums this wave finishes (-1: none)
+  float *red;                        // LDS: partial sums (two halves that alternate)
+  const uint64_t *tiles;             // LDS: weights of up to kResMaxLdsTiles tiles
+  const int2 *info;                  // LDS: frames of the slot's utterance, its first row of f_proj
+  uint64_t *word;                    // LDS: this wave's copy of the last step's words, [slot tile][16]
+  int phase;                         // which half of the partial sums
+};
+// A lane's place in the wave.  (Computed anew where it is needed rather than kept: the weights leave no registers to
+// spare.)  sl: slot of the tile, kq: k-quad, also the group of four rows of a result tile.
+struct ResLane {
+  int lane, kq, sl;
+};
+__device__ __forceinline__ ResLane res_lane() {
+  int l;
+  asm volatile("v_mbcnt_lo_u32_b32 %0, -1, 0\n\tv_mbcnt_hi_u32_b32 %0, -1, %0" : "=&v"(l));
+  return ResLane{l, l >> 4, l & 15};
+}
+__device__ __forceinline__ int res_uniform(int x) { return __builtin_amdgcn_readfirstlane(x); }
+// index of utterance u of the group in the batch
+__device__ __forceinline__ int res_utt(const ResArgs &a, int g, int u) { return g + a.n_groups * u; }
+
+// partial sums of a 16-row tile: wave's lane (row group, slot) holds four rows
+template <bool BF16>
+__device__ __forceinline__ float *res_red(const ResBlock &k, int block) {
+  return k.red + ((k.phase & 1) * kResRedBlocks<BF16> + block) * kResRedBlock;
+}
+template <bool BF16>
+__device__ __forceinline__ void res_put(const ResBlock &k, const ResLane &l, int block, floatx4 v) {
+  *reinterpret_cast<floatx4 *>(res_red<BF16>(k, block) + (k.wave * 64 + l.lane) * 4) = v;
+}
+template <bool BF16>
+__device__ __forceinline__ floatx4 res_sum(const ResBlock &k, const ResLane &l, int block) {
+  const float *r = res_red<BF16>(k, block) + l.lane * 4;
+  floatx4 v[kResWaves];
+#pragma unroll
+  for (int w = 0; w < kResWaves; ++w) v[w] = *reinterpret_cast<const floatx4 *>(r + w * 256);
+  floatx4 s = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+  for (int w = 0; w < kResWaves; ++w) s += v[w];
+  return s;
+}
+
+// Waits for the words of step `step` and leaves them in the wave's LDS copy; slots beyond the group's are idle (finished).
+// 1: every utterance of the group has finished, 0: not yet, -1: the wait gave up.
+__device__ __forceinline__ int res_words(const ResBlock &k, int step) {
+  const ResArgs &a = res_args();
+  const ResLane l = res_lane();
+  const uint64_t *p = res_addr(a, k.g).w(step) + l.sl;
+  const int tag = (step + 1) & 0xffff;
+  bool open = false;
+#pragma unroll 1
+  for (int nt = 0; nt < a.NT; ++nt) {
+    const int slot = nt * kResSlot + l.sl;
+    uint64_t w = slot_word(step, 1, slot, -1, 0);
+    ResWait wait;
+    for (;;) {
+      bool missing = false;
+      if (slot < k.nslots) {
+        w = load_agent(p + nt * kResSlot);
+        missing = word_tag(w) != tag;
+      }
+      if (__ballot(missing) == 0ull) break;
+      if (!wait.again()) return -1;
+    }
+    open |= !word_finished(w);
+    if (l.kq == 0) k.word[slot] = w;
+  }
+  wave_sync();
+  return __ballot(open) == 0ull ? 1 : 0;
+}
+// before the first step: hypothesis 0 of every utterance reads the start symbol
+__device__ __forceinline__ int res_first_words(const ResArgs &a, const ResBlock &k) {
+  const ResLane l = res_lane();
+  bool open = false;
+  for (int nt = 0; nt < a.NT; ++nt) {
+    const int slot = nt * kResSlot + l.sl;
+    const bool used = slot < k.nslots;
+    const bool empty = !used || a.lengths[res_utt(a, k.g, used ? slot / a.K : 0)] == 0;
+    open |= !empty;
+    if (l.kq == 0) k.word[slot] = slot_word(-1, empty ? 1 : 0, slot, (used && slot % a.K == 0) ? a.V : -1, 0);
+  }
+  wave_sync();
+  return __ballot(open) == 0ull ? 1 : 0;
+}
+
+// ---- P: pre[step] = f_proj[frame] + W_pred h[step] + b_pred for the block's tiles of 16 outputs
+// output row i of tile t: o = 16 t + 8 (i / 8) + (i / 4) % 2 + 2 (i % 4), so that a lane's four rows are two 8-byte words
+// of the fragment order.
+__host__ __device__ inline int res_p_row(int tile, int i) { return 16 * tile + 8 * (i >> 3) + ((i >> 2) & 1) + 2 * (i & 3); }
+__device__ __forceinline__ float *res_p_dst(float *p, int tile, int g, int sl) {  // two words, 32 floats apart
+  return p + ((size_t)((2 * tile + (g >> 1)) * 4 + 2 * (g & 1)) * kResSlot + sl) * 2;
+}
+// every second one of eight floats, from the first or the second on: the four rows of a lane
+__device__ __forceinline__ floatx4 res_p_pick(const ResLane &l, const float *p) {
+  const floatx4 f0 = *reinterpret_cast<const floatx4 *>(p), f1 = *reinterpret_cast<const floatx4 *>(p + 4);
+  return (l.kq & 1) ? floatx4{f0[1], f0[3], f1[1], f1[3]} : floatx4{f0[0], f0[2], f1[0], f1[2]};
+}
+// The frame's projection of the four outputs that the wave finishes: requested before the activations are waited for.
+__device__ __forceinline__ floatx4 res_p_frame(const ResArgs &a, const ResBlock &k, const ResLane &l, int nt) {
+  const int2 in = k.info[nt * kResSlot + l.sl];
+  int tt = word_frame(k.word[nt * kResSlot + l.sl]);
+  tt = tt < in.x ? tt : in.x - 1;
+  tt = tt < 0 ? 0 : tt;
+  return res_p_pick(l, a.f_proj + ((size_t)in.y + tt) * a.H + 16 * k.ptile + 8 * (l.kq >> 1));
+}
+__device__ __forceinline__ floatx4 res_p_bias(const ResArgs &a, const ResBlock &k, const ResLane &l) {
+  return res_p_pick(l, a.b_pred + 16 * k.ptile + 8 * (l.kq >> 1));
+}
+// sums of the wave's tile -> pre.  first / second: the blocks of its partial sums of the two halves of k (halves: the
+// per-step launches add the bias and the frame's projection to the first half's sum, then the second half's).
+template <bool BF16>
+__device__ __forceinline__ void res_p_finish(const ResArgs &a, const ResBlock &k, const ResLane &l, const ResAddr &ad, int step, int nt, int first,
+                                             int second, floatx4 bias, floatx4 f) {
+  floatx4 v = (res_sum<BF16>(k, l, first) + bias) + f;
+  if (a.halves) v += res_sum<BF16>(k, l, second);
+  float *dst = res_p_dst(ad.p(step, nt), k.ptile, l.kq, l.sl);
+  wait_stores_acknowledged();  // (of the pattern that this wave put back into places of the array meanwhile)
+  store_agent(reinterpret_cast<uint64_t *>(dst), pack2(v[0], v[1]));
+  store_agent(reinterpret_cast<uint64_t *>(dst + 2 * kResSlot), pack2(v[2], v[3]));
+}
+__device__ __forceinline__ void clear_p(const ResBlock &k, const ResLane &l, const ResAddr &ad, int step, int nt) {
+  float *dst = res_p_dst(ad.p(step, nt), k.ptile, l.kq, l.sl);
+  store_agent(reinterpret_cast<uint64_t *>(dst), (uint64_t)~0ull);
+  store_agent(reinterpret_cast<uint64_t *>(dst + 2 * kResSlot), (uint64_t)~0ull);
+}
+// the wave that finishes a tile of the projection: from the last one down, which own no cells
+__device__ __forceinline__ int res_p_wave(int tile_no) { return kResWaves - 1 - tile_no; }
+
+// Operand of a bf16 matrix instruction (32 x 32 x 16) from two rounds of activations: lane (slot column, half of k)
+__device__ __forceinline__ floatx16 mfma_pair_bf16(uint64_t w0, uint64_t w1, const uint64_t *x0, const uint64_t *x1, bool two,
+                                                   bool relu, floatx16 acc) {
+  const uintx4_t w = {(uint32_t)w0, (uint32_t)(w0 >> 32), two ? (uint32_t)w1 : 0u, two ? (uint32_t)(w1 >> 32) : 0u};
+  float v[8] = {lo_f(x0[0]), lo_f(x0[1]), hi_f(x0[0]), hi_f(x0[1]), 0.f, 0.f, 0.f, 0.f};
+  if (two) {
+    v[4] = lo_f(x1[0]); v[5] = lo_f(x1[1]); v[6] = hi_f(x1[0]); v[7] = hi_f(x1[1]);
+  }
+  if (relu) {
+#pragma unroll
+    for (int i = 0; i < 8; ++i) v[i] = fmaxf(v[i], 0.f);
+  }
+  const uintx4_t b = {pack_bf16_rne(v[0], v[1]), pack_bf16_rne(v[2], v[3]), pack_bf16_rne(v[4], v[5]), pack_bf16_rne(v[6], v[7])};
+  return __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8_t, w), __builtin_bit_cast(bf16x8_t, b), acc, 0, 0, 0);
+}
+// lane (column c, half): the two words of a round; columns 16..31 are the next slot tile (or a repeat)
+__device__ __forceinline__ const uint64_t *bf16_src(const ResLane &l, const float *tile0, size_t tile_floats, bool second,
+                                                    int round0) {
+  const int half = l.lane >> 5, c = l.lane & 31;
+  const float *t = tile0 + ((c >> 4) && second ? tile_floats : 0);
+  return reinterpret_cast<const uint64_t *>(t) + (size_t)(round0 * 4 + half) * kResSlot + (c & 15);
+}
+// words of a round: quads half and half + 2, i.e. two words 2 * 16 apart; rounds 4 * 16 apart: one even stride
+template <bool FULL, int ROUNDS>
+__device__ __forceinline__ bool bf16_gather(const uint64_t *p, int n, uint64_t (&x)[2 * ROUNDS]) {
+  return res_gather<FULL, 2 * ROUNDS>([p](int i) { return p + i * 2 * kResSlot; }, 2 * n, x);
+}
+// 32-row tile's accumulators -> partial sums of its two 16-row tiles (blocks b0, b0 + 1) for columns 16 nt2 .. + 15
+__device__ __forceinline__ void bf16_put(const ResBlock &k, const ResLane &l, int b0, int nt2, const floatx16 &acc) {
+  const int half = l.lane >> 5, c = l.lane & 31;
+  if ((c >> 4) == nt2) {
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+      const int g = (q & 1) * 2 + half;
+      *reinterpret_cast<floatx4 *>(res_red<true>(k, b0 + (q >> 1)) + (k.wave * 64 + g * 16 + (c & 15)) * 4) =
+          floatx4{acc[4 * q], acc[4 * q + 1], acc[4 * q + 2], acc[4 * q + 3]};
+    }
+  }
+}
+
+template <bool FULL, bool BF16>
+__device__ __forceinline__ bool res_p_phase(ResBlock &k, int step) {
+  if (k.nP == 0) return true;
+  const ResArgs &a = res_args();
+  const ResLane l = res_lane();
+  const ResAddr ad = res_addr(a, k.g);
+  const int nr = FULL ? kResMaxRounds : a.rounds_p;
+  const bool halves = a.halves != 0;
+  const int nh = halves ? nr / 2 : nr;  // rounds of a slice: the wave has one in either half of k, or one of the whole
+  if constexpr (BF16) {  // one tile of 32 outputs: two waves finish 16 each
+#pragma unroll 1
+    for (int nt = 0; nt < a.NT; nt += 2) {
+      const bool second = nt + 1 < a.NT;
+      floatx4 f[2] = {floatx4{0.f, 0.f, 0.f, 0.f}, floatx4{0.f, 0.f, 0.f, 0.f}}, bias = f[0];
+      if (k.ptile >= 0) {
+        bias = res_p_bias(a, k, l);
+        f[0] = res_p_frame(a, k, l, nt);
+        if (second) f[1] = res_p_frame(a, k, l, nt + 1);
+      }
+      const uint64_t *w = k.tiles + l.lane;
+      if (second) __syncthreads();  // (both halves of the buffer are written below; one of them has just been read)
+      for (int hf = 0; hf < (halves ? 2 : 1); ++hf) {
+        const int r0 = halves ? hf * (4 * nr) + k.wave * nh : k.wave * nr;
+        uint64_t x[2 * kResMaxRounds];
+        if (!bf16_gather<false, kResMaxRounds>(bf16_src(l, ad.h(step, nt), ad.h_tile, second, r0), nh, x)) return false;
+        floatx16 acc = {0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0};
+#pragma unroll
+        for (int i = 0; i < kResMaxRounds / 2; ++i)
+          if (2 * i < nh) {
+            const bool two = 2 * i + 1 < nh;
+            acc = mfma_pair_bf16(w[(r0 + 2 * i) * 64], w[(r0 + 2 * i + (two ? 1 : 0)) * 64], x + 4 * i, x + 4 * i + 2, two, false, acc);
+          }
+        bf16_put(k, l, 2 * hf, 0, acc);
+        if (second) {  // the other slot tile's sums go to the other half of the buffer
+          ++k.phase;
+          bf16_put(k, l, 2 * hf, 1, acc);
+          --k.phase;
+        }
+      }
+      __syncthreads();
+      if (k.ptile >= 0) res_p_finish<true>(a, k, l, ad, step, nt, k.ptile & 1, 2 + (k.ptile & 1), bias, f[0]);
+      ++k.phase;
+      if (second) {
+        if (k.ptile >= 0) res_p_finish<true>(a, k, l, ad, step, nt + 1, k.ptile & 1, 2 + (k.ptile & 1), bias, f[1]);
+        ++k.phase;
+        __syncthreads();  // (both halves of the buffer have just been read)
+      }
+    }
+  } else {
+#pragma unroll 1
+    for (int nt = 0; nt < a.NT; ++nt) {
+      floatx4 f = {0.f, 0.f, 0.f, 0.f}, bias = f;
+      if (k.ptile >= 0) {
+        bias = res_p_bias(a, k, l);
+        f = res_p_frame(a, k, l, nt);
+      }
+      uint64_t x[kResMaxRounds];
+      // rounds i < nr / 2 from the wave's slice of the first half of k, the others from its slice of the second half (or
+      // all of one slice)
+      const uint64_t *src = reinterpret_cast<const uint64_t *>(ad.h(step, nt)) + (size_t)k.wave * nh * 64 + l.lane;
+      const int n1 = FULL ? kResMaxRounds / 2 : nr / 2, jump = halves ? (4 * nr - n1) * 64 : 0;
+      auto at = [&](int i) { return src + i * 64 + (i >= n1 ? jump : 0); };
+      if (!res_gather<FULL, kResMaxRounds>(at, nr, x)) return false;
+      for (int tp = 0; tp < k.nP; ++tp) {
+        const uint64_t *w = k.tiles + (size_t)tp * (a.P * kResSlot / 2) + (size_t)k.wave * nh * 64 + l.lane;
+        if (halves) {
+          floatx4 acc0 = {0.f, 0.f, 0.f, 0.f}, acc1 = acc0;
+#pragma unroll
+          for (int i = 0; i < kResMaxRounds / 2; ++i)
+            if (FULL || i < n1) {
+              const uint64_t u = w[i * 64], v = w[(4 * nr + i) * 64];
+              const uint64_t y = FULL ? x[kResMaxRounds / 2 + i] : res_pick(x, n1 + i);
+              acc0 = mfma16(lo_f(u), lo_f(x[i]), acc0);
+              acc1 = mfma16(lo_f(v), lo_f(y), acc1);
+              acc0 = mfma16(hi_f(u), hi_f(x[i]), acc0);
+              acc1 = mfma16(hi_f(v), hi_f(y), acc1);
+            }
+          res_put<false>(k, l, 0, acc0);
+          res_put<false>(k, l, 1, acc1);
+        } else {
+          floatx4 acc = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+          for (int i = 0; i < kResMaxRounds; ++i)
+            if (FULL || i < nr) {
+              const uint64_t u = w[i * 64];
+              acc = mfma16(lo_f(u), lo_f(x[i]), acc);
+              acc = mfma16(hi_f(u), hi_f(x[i]), acc);
+            }
+          res_put<false>(k, l, 0, acc);
+        }
+        __syncthreads();
+        if (k.wave == res_p_wave(tp)) res_p_finish<false>(a, k, l, ad, step, nt, 0, 1, bias, f);
+        ++k.phase;
+      }
+    }
+  }
+  return true;
+}
+
+// ---- J: z[step] = W_out ReLU(pre[step]) + b_out for the block's tiles
+template <bool BF16>
+__device__ __forceinline__ void res_j_finish(const ResBlock &k, const ResLane &l, const ResAddr &ad, int step, int nt, int tile, floatx4 bias, int block) {
+  const int slot = nt * kResSlot + l.sl, n0 = 16 * tile + 4 * l.kq;
+  const floatx4 v = res_sum<BF16>(k, l, block) + bias;
+  wait_stores_acknowledged();
+  if (slot < k.nslots) store16_through(ad.z(step, slot) + n0, v);
+}
+__device__ __forceinline__ void clear_z(const ResBlock &k, const ResLane &l, const ResAddr &ad, int step, int nt, int tile) {
+  const int slot = nt * kResSlot + l.sl;
+  const float e = __uint_as_float(kResEmpty);
+  if (slot < k.nslots) store16_through(ad.z(step, slot) + 16 * tile + 4 * l.kq, floatx4{e, e, e, e});
+}
+
+// wj: the tiles that the block keeps in registers; one more may lie in LDS behind the projection's
+template <bool FULL, bool BF16>
+__device__ __forceinline__ bool res_j_phase(ResBlock &k, int step, const float (&wj)[kResRegJ<BF16>][2 * kResMaxRounds]) {
+  if (k.nJ == 0) return true;
+  constexpr int NJ = kResRegJ<BF16>;
+  const ResArgs &a = res_args();
+  const ResLane l = res_lane();
+  const ResAddr ad = res_addr(a, k.g);
+  const int nr = FULL ? kResMaxRounds : a.rounds_h;
+  floatx4 bias[2];
+#pragma unroll
+  for (int t = 0; t < 2; ++t) {
+    bias[t] = floatx4{0.f, 0.f, 0.f, 0.f};
+    if ((BF16 || t == 0) && k.jtile[t] >= 0) bias[t] = *reinterpret_cast<const floatx4 *>(a.b_out + 16 * k.jtile[t] + 4 * l.kq);
+  }
+  const uint64_t *wx = k.tiles + (size_t)k.nP * (a.P * kResSlot / 2) + (size_t)k.wave * nr * 64 + l.lane;
+  if constexpr (BF16) {
+#pragma unroll 1
+    for (int nt = 0; nt < a.NT; nt += 2) {
+      const bool second = nt + 1 < a.NT;
+      uint64_t x[2 * kResMaxRounds];
+      if (!bf16_gather<FULL, kResMaxRounds>(bf16_src(l, ad.p(step, nt), ad.p_tile, second, k.wave * nr), nr, x)) return false;
+#pragma unroll
+      for (int t = 0; t < NJ + 1; ++t) {
+        if (t >= k.nJ) break;
+        floatx16 acc = {0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0};
+#pragma unroll
+        for (int i = 0; i < kResMaxRounds / 2; ++i)
+          if (FULL || 2 * i < nr) {
+            const bool two = FULL || 2 * i + 1 < nr;
+            uint64_t w0, w1;
+            if (t < NJ) {
+              w0 = pack2(wj[t < NJ ? t : 0][4 * i], wj[t < NJ ? t : 0][4 * i + 1]);
+              w1 = pack2(wj[t < NJ ? t : 0][4 * i + 2], wj[t < NJ ? t : 0][4 * i + 3]);
+            } else {
+              w0 = wx[2 * i * 64];
+              w1 = wx[(2 * i + (two ? 1 : 0)) * 64];
+            }
+            acc = mfma_pair_bf16(w0, w1, x + 4 * i, x + 4 * i + 2, two, true, acc);
+          }
+        bf16_put(k, l, 0, 0, acc);
+        if (second) bf16_put(k, l, 2, 1, acc);
+        __syncthreads();
+        if (k.wave < (second ? 4 : 2)) res_j_finish<true>(k, l, ad, step, nt + (k.wave >> 1), k.jtile[t], bias[t], k.wave);
+        ++k.phase;
+      }
+    }
+  } else {
+#pragma unroll 1
+    for (int nt = 0; nt < a.NT; ++nt) {
+      uint64_t x[kResMaxRounds];
+      const uint64_t *src = reinterpret_cast<const uint64_t *>(ad.p(step, nt)) + (size_t)k.wave * nr * 64 + l.lane;
+      if (!res_gather<FULL, kResMaxRounds>([src](int i) { return src + i * 64; }, nr, x)) return false;
+#pragma unroll
+      for (int i = 0; i < kResMaxRounds; ++i) x[i] = pack2(fmaxf(lo_f(x[i]), 0.f), fmaxf(hi_f(x[i]), 0.f));
+      floatx4 acc[NJ];
+#pragma unroll
+      for (int t = 0; t < NJ; ++t) acc[t] = floatx4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+      for (int i = 0; i < kResMaxRounds; ++i)
+        if (FULL || i < nr) {
+#pragma unroll
+          for (int t = 0; t < NJ; ++t) acc[t] = mfma16(wj[t][2 * i], lo_f(x[i]), acc[t]);
+#pragma unroll
+          for (int t = 0; t < NJ; ++t) acc[t] = mfma16(wj[t][2 * i + 1], hi_f(x[i]), acc[t]);
+        }
+#pragma unroll
+      for (int t = 0; t < NJ; ++t)
+        if (t < k.nJ) res_put<false>(k, l, t, acc[t]);
+      if (k.nJ > NJ) {
+        floatx4 c = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+        for (int i = 0; i < kResMaxRounds; ++i)
+          if (FULL || i < nr) {
+            const uint64_t u = wx[i * 64];
+            c = mfma16(lo_f(u), lo_f(x[i]), c);
+            c = mfma16(hi_f(u), hi_f(x[i]), c);
+          }
+        res_put<false>(k, l, NJ, c);
+      }
+      __syncthreads();
+      if (k.jtile[0] >= 0) res_j_finish<false>(k, l, ad, step, nt, k.jtile[0], bias[0], k.wave);
+      ++k.phase;
+    }
+  }
+  return true;
+}
+
+// the block's own pieces of pre[step] and of the logits of `step`: every word of `step` has been seen, i.e. every selecting
+// block has read its logits, which needed every piece of pre
+// (the wave that writes a place next is the one that clears it, with a wait for its stores in between)
+template <bool BF16>
+__device__ __forceinline__ void res_clear_pz(const ResArgs &a, const ResBlock &k, const ResAddr &ad, int step) {
+  const ResLane l = res_lane();
+  for (int nt = 0; nt < a.NT; ++nt) {
+    if (k.ptile >= 0) clear_p(k, l, ad, step, nt);
+    if constexpr (BF16) {
+      if (k.wave >> 1 == (nt & 1)) {
+        if (k.jtile[0] >= 0) clear_z(k, l, ad, step, nt, k.jtile[0]);
+        if (k.jtile[1] >= 0) clear_z(k, l, ad, step, nt, k.jtile[1]);
+      }
+    } else {
+      if (k.jtile[0] >= 0) clear_z(k, l, ad, step, nt, k.jtile[0]);
+    }
+  }
+}
+
+// ---------------------------------------------------------------------------
+// blocks that own tiles
+// ---------------------------------------------------------------------------
+template <bool FULL, bool BF16>
+__device__ __forceinline__ void res_worker(ResBlock k, const ResTab &tab, float *lds) {
+  constexpr int NJ = kResRegJ<BF16>;
+  const ResArgs &a0 = res_args();
+  k.nR = res_uniform(tab.nR);
+  k.nJ = res_uniform(tab.nJ);
+  k.nP = res_uniform(tab.nP);
+  // which tile's sums this wave finishes, and the tile whose cells it updates
+  int pt = -1, jt0 = -1, jt1 = -1;
+  if constexpr (BF16) {  // two waves per 32-row tile (output layer: two more for the second slot tile)
+    if (k.nP > 0 && k.wave >= kResWaves - 2) pt = 2 * tab.P[0] + (kResWaves - 1 - k.wave);
+    if (k.wave < 4) {
+      if (k.nJ > 0) jt0 = 2 * tab.J[0] + (k.wave & 1);
+      if (k.nJ > 1) jt1 = 2 * tab.J[1] + (k.wave & 1);
+    }
+  } else {
+    if (kResWaves - 1 - k.wave < k.nP) pt = tab.P[kResWaves - 1 - k.wave];
+    if (k.wave < k.nJ) jt0 = tab.J[k.wave];
+  }
+  k.ptile = res_uniform(pt);
+  k.jtile[0] = res_uniform(jt0);
+  k.jtile[1] = res_uniform(jt1);
+  const int mytile = res_uniform(k.wave < k.nR ? tab.R[k.wave] : 0);
+  const ResLane l0 = res_lane();
+  // weights: projection tiles (and the output-layer tile that finds no registers) to LDS, the others to registers
+  {
+    const int n4 = a0.P * kResSlot / 4, h4 = a0.H * kResSlot / 4;
+    uintx4_t *dst = reinterpret_cast<uintx4_t *>(lds);
+    k.tiles = reinterpret_cast<const uint64_t *>(lds);
+    for (int tp = 0; tp < k.nP; ++tp) {
+      const uintx4_t *src = (BF16 ? reinterpret_cast<const uintx4_t *>(a0.WPb) : reinterpret_cast<const uintx4_t *>(a0.WP)) +
+                            (size_t)tab.P[tp] * n4;
+      for (int i = threadIdx.x; i < n4; i += kResThreads) dst[i] = src[i];
+      dst += n4;
+    }
+    if (k.nJ > NJ) {
+      const uintx4_t *src = (BF16 ? reinterpret_cast<const uintx4_t *>(a0.WJb) : reinterpret_cast<const uintx4_t *>(a0.WJ)) +
+                            (size_t)tab.J[NJ] * h4;
+      for (int i = threadIdx.x; i < h4; i += kResThreads) dst[i] = src[i];
+      dst += h4;
+    }
+    k.red = reinterpret_cast<float *>(dst);
+  }
+  // LDS of the cells: sums W_hh h of the block's tiles, cell state and hidden state of their units, [tile][slot tile][64]
+  float *Rl = k.red + 2 * kResRedBlocks<BF16> * kResRedBlock, *cl = Rl + kResMaxR * a0.NT * 256, *hl = cl + kResMaxR * a0.NT * 64;
+  int2 *info = reinterpret_cast<int2 *>(hl + kResMaxR * a0.NT * 64);
+  for (int i = threadIdx.x; i < kResMaxR * a0.NT * (256 + 128); i += kResThreads) Rl[i] = 0.f;
+  if (threadIdx.x < a0.NT * kResSlot) {
+    const int b = res_utt(a0, k.g, (int)threadIdx.x < k.nslots ? threadIdx.x / a0.K : 0);
+    info[threadIdx.x] = make_int2(a0.lengths[b], b * a0.T);
+  }
+  k.info = info;
+  k.word = reinterpret_cast<uint64_t *>(info + a0.NT * kResSlot) + k.wave * a0.NT * kResSlot;
+  float wj[NJ][2 * kResMaxRounds], wr[kResMaxR][2 * kResMaxRounds];
+  {
+    const int nrh = FULL ? kResMaxRounds : a0.rounds_h, nrp = FULL ? kResMaxRounds : a0.rounds_p;
+#pragma unroll
+    for (int t = 0; t < NJ; ++t)
+#pragma unroll
+      for (int i = 0; i < kResMaxRounds; ++i) {
+        wj[t][2 * i] = wj[t][2 * i + 1] = 0.f;
+        if (t < k.nJ && (FULL || i < nrh)) {
+          const uint64_t v = ((BF16 ? a0.WJb : reinterpret_cast<const uint64_t *>(a0.WJ)) +
+                              ((size_t)tab.J[t] * (a0.H / 8) + k.wave * nrh) * 64 + l0.lane)[i * 64];
+          wj[t][2 * i] = lo_f(v);
+          wj[t][2 * i + 1] = hi_f(v);
+        }
+      }
+#pragma unroll
+    for (int t = 0; t < kResMaxR; ++t)
+#pragma unroll
+      for (int i = 0; i < kResMaxRounds; ++i) {
+        wr[t][2 * i] = wr[t][2 * i + 1] = 0.f;
+        if (t < k.nR && (FULL || i < nrp)) {
+          const uint64_t v = reinterpret_cast<const uint64_t *>(a0.WR)[((size_t)tab.R[t] * (a0.P / 8) + k.wave * nrp + i) * 64 + l0.lane];
+          wr[t][2 * i] = lo_f(v);
+          wr[t][2 * i + 1] = hi_f(v);
+        }
+      }
+    // (loaded once; without this the compiler would rather load them again in every step)
+#pragma unroll
+    for (int i = 0; i < 2 * kResMaxRounds; ++i) {
+#pragma unroll
+      for (int t = 0; t < NJ; ++t) asm volatile("" : "+v"(wj[t][i]));
+#pragma unroll
+      for (int t = 0; t < kResMaxR; ++t) asm volatile("" : "+v"(wr[t][i]));
+    }
+  }
+  __syncthreads();
+  int over = res_first_words(a0, k);
+  for (int step = 0; over == 0; ++step) {
+    // ---- cells
+    if (k.wave < k.nR) {
+      const ResArgs &a = res_args();
+      const ResLane l = res_lane();
+      const ResAddr ad = res_addr(a, k.g);
+      const int unit = 8 * (mytile >> 1) + 2 * l.kq + (mytile & 1);
+      const int hofs = ((mytile >> 1) * 4 + (mytile & 1) * 2 + (l.kq >> 1)) * (2 * kResSlot) + l.sl * 2 + (l.kq & 1);
+      float4 g4[kResMaxNT];
+#pragma unroll
+      for (int nt = 0; nt < kResMaxNT; ++nt)
+        if (nt < a.NT) {
+          const int tok = word_tok(k.word[nt * kResSlot + l.sl]);
+          g4[nt] = *reinterpret_cast<const float4 *>(a.G + (size_t)(tok < 0 ? a.V : tok) * 4 * a.P + 4 * unit);
+        }
+      // h of three steps ago may be cleared: the words of the last step needed h of the last step from every owner of
+      // W_hh tiles, who had multiplied h of two steps ago (and the one before) by then
+      if (step > 2)
+        for (int nt = 0; nt < a.NT; ++nt) store_agent(reinterpret_cast<uint32_t *>(ad.h(step - 3, nt) + hofs), kResEmpty);
+      float cn[kResMaxNT], hn[kResMaxNT];
+#pragma unroll
+      for (int nt = 0; nt < kResMaxNT; ++nt)
+        if (nt < a.NT) {
+          const uint64_t w = k.word[nt * kResSlot + l.sl];
+          const int src = word_src(w), at = (k.wave * a.NT + (src >> 4)) * 64 + l.kq * 16 + (src & 15);
+          cn[nt] = cl[at];
+          hn[nt] = hl[at];
+          if (word_tok(w) >= 0) hn[nt] = lstm_unit(*reinterpret_cast<const float4 *>(Rl + at * 4), g4[nt], cn[nt]);
+          if (nt == 0) wait_stores_acknowledged();
+          store_agent(ad.h(step, nt) + hofs, hn[nt]);
+        }
+      wave_sync();
+#pragma unroll
+      for (int nt = 0; nt < kResMaxNT; ++nt)
+        if (nt < a.NT) {
+          const int at = (k.wave * a.NT + nt) * 64 + l.lane;
+          cl[at] = cn[nt];
+          hl[at] = hn[nt];
+        }
+    }
+    if (step > 0) {
+      const ResArgs &a = res_args();
+      res_clear_pz<BF16>(a, k, res_addr(a, k.g), step - 1);
+    }
+    if (!res_p_phase<FULL, BF16>(k, step)) return;
+    if (!res_j_phase<FULL, BF16>(k, step, wj)) return;
+    // ---- R
+    if (k.nR > 0) {
+      const ResArgs &a = res_args();
+      const ResLane l = res_lane();
+      const ResAddr ad = res_addr(a, k.g);
+      const int nrp = FULL ? kResMaxRounds : a.rounds_p;
+#pragma unroll 1
+      for (int nt = 0; nt < a.NT; ++nt) {
+        uint64_t x[kResMaxRounds];
+        const uint64_t *src = reinterpret_cast<const uint64_t *>(ad.h(step, nt)) + (size_t)k.wave * nrp * 64 + l.lane;
+        if (!res_gather<FULL, kResMaxRounds>([src](int i) { return src + i * 64; }, nrp, x)) return;
+#pragma unroll
+        for (int t0 = 0; t0 < kResMaxR; t0 += 3) {
+          if (t0 >= k.nR) break;
+          floatx4 acc[3];
+#pragma unroll
+          for (int t = 0; t < 3; ++t) acc[t] = floatx4{0.f, 0.f, 0.f, 0.f};
+          // (tiles that the block does not own have zero weights; fewer branches are worth more than their instructions)
+#pragma unroll
+          for (int i = 0; i < kResMaxRounds; ++i)
+            if (FULL || i < nrp) {
+#pragma unroll
+              for (int t = 0; t < 3; ++t) acc[t] = mfma16(wr[t0 + t][2 * i], lo_f(x[i]), acc[t]);
+#pragma unroll
+              for (int t = 0; t < 3; ++t) acc[t] = mfma16(wr[t0 + t][2 * i + 1], hi_f(x[i]), acc[t]);
+            }
+#pragma unroll
+          for (int t = 0; t < 3; ++t)
+            if (t0 + t < k.nR) res_put<BF16>(k, l, t, acc[t]);
+          __syncthreads();
+          if (k.wave >= t0 && k.wave < t0 + 3 && k.wave < k.nR)
+            *reinterpret_cast<floatx4 *>(Rl + ((k.wave * a.NT + nt) * 64 + l.lane) * 4) = res_sum<BF16>(k, l, k.wave - t0);
+          ++k.phase;
+        }
+      }
+    }
+    over = res_words(k, step);
+  }
+}
+
+// ---------------------------------------------------------------------------
+// selecting blocks
+// ---------------------------------------------------------------------------
+constexpr int kResMaxHyps = 24;  // hypotheses of a selecting block
+struct ResSelLds {  // LDS of the selection beside the scratch of its utterances
+  uint64_t cand[512];                                   // K lists of K per utterance (upc * K * K <= 512)
+  float smax[kResMaxHyps], ssum[kResMaxHyps], zs[kResMaxHyps * 9];
+  uint64_t surv[kResMaxHyps][kResSurvivors];
+  float2 cst[kResMaxHyps][32];                          // (maximum, sum of exponentials) of every chunk of 32 columns
+  int n_surv[kResMaxHyps][2];
+  LmCtxRec rec[kResWaves][kCtxMax + 1];
+};
+
+// x[i] = max (or sum) of x[i] and the lane that CTRL names, for N values at once: one instruction each plus the wait
+// states of the first (the compiler's form takes five per value)
+#define RB_RES_DPP(NAME, OP)                                                                                       \
+  template <int CTRL, int N>                                                                                       \
+  __device__ __forceinline__ void NAME(float (&x)[N]) {                                                            \
+    _Pragma("unroll") for (int i = 0; i < N; ++i) {                                                                \
+      float y;                                                                                                     \
+      if constexpr (CTRL == kDppXor1) asm("s_nop 1\n\t" OP " %0, %1, %1 quad_perm:[1,0,3,2] row_mask:0xf bank_mask:0xf" : "=v"(y) : "v"(x[i])); \
+      else if constexpr (CTRL == kDppXor2) asm("s_nop 1\n\t" OP " %0, %1, %1 quad_perm:[2,3,0,1] row_mask:0xf bank_mask:0xf" : "=v"(y) : "v"(x[i])); \
+      else if constexpr (CTRL == kDppHalfMirror) asm("s_nop 1\n\t" OP " %0, %1, %1 row_half_mirror row_mask:0xf bank_mask:0xf" : "=v"(y) : "v"(x[i])); \
+      else asm("s_nop 1\n\t" OP " %0, %1, %1 row_mirror row_mask:0xf bank_mask:0xf" : "=v"(y) : "v"(x[i]));      \
+      x[i] = y;                                                                                                    \
+    }                                                                                                              \
+  }
+RB_RES_DPP(dpp_max_n, "v_max_f32_dpp")
+RB_RES_DPP(dpp_min_n, "v_min_f32_dpp")
+RB_RES_DPP(dpp_add_n, "v_add_f32_dpp")
+#undef RB_RES_DPP
+template <int LANES, int N>
+__device__ __forceinline__ void group_max_n(float (&x)[N]) {
+  dpp_max_n<kDppXor1>(x);
+  dpp_max_n<kDppXor2>(x);
+  if constexpr (LANES >= 8) dpp_max_n<kDppHalfMirror>(x);
+  if constexpr (LANES >= 16) dpp_max_n<kDppMirror>(x);
+}
+template <int LANES, int N>
+__device__ __forceinline__ void group_sum_n(float (&x)[N]) {
+  dpp_add_n<kDppXor1>(x);
+  dpp_add_n<kDppXor2>(x);
+  if constexpr (LANES >= 8) dpp_add_n<kDppHalfMirror>(x);
+  if constexpr (LANES >= 16) dpp_add_n<kDppMirror>(x);
+}
+
+// A hypothesis' row of logits, columns 128 (q0 .. q0 + NQ - 1), by one wave: chunk statistics as the per-step kernels form
+// them, the blank and duration logits, and the keys that can be among the K best.  A lane holds columns 128 q + 2 lane +
+// {0, 1}; 16 lanes are a chunk of 32.  part / parts: the waves of the row, each of which collects keys of its own columns.
+// (Every load is unconditional, from a clamped address, and nothing branches before the keys are compared: the wave's
+// time is the latency of this chain.)
+template <int NQ, int KC, int PLAIN>
+__device__ __forceinline__ bool res_row(int g, int step, int slot, const float *lmrow, int hyp, int part, int parts, ResSelLds &L) {
+  const ResArgs &a = res_args();
+  const int lane = threadIdx.x & 63, V = a.V, nz = a.N - V;
+  const int q0 = part * NQ;
+  const float *zrow = res_addr(a, g).z(step, slot);
+  const int v_last = (V - 1) & ~1;
+  uint64_t zz[NQ + 1];  // the last: blank and duration logits, one per lane
+  const uint32_t *ps = reinterpret_cast<const uint32_t *>(zrow) + V + (lane < nz ? lane : 0);
+  ResWait w;
+  if (!res_probe(reinterpret_cast<const uint64_t *>(zrow + min(128 * q0 + 2 * lane, v_last)), w)) return false;
+  for (;;) {
+#pragma unroll
+    for (int q = 0; q < NQ; ++q) zz[q] = load_agent(reinterpret_cast<const uint64_t *>(zrow + min(128 * (q0 + q) + 2 * lane, v_last)));
+    zz[NQ] = load_agent(ps);
+    if (__ballot(res_any_empty(zz)) == 0ull) break;
+    if (!w.again()) return false;
+  }
+  if (part == 0 && lane < nz) L.zs[hyp * nz + lane] = lo_f(zz[NQ]);
+  // a place without a token: -inf
+  float z[2 * NQ];
+#pragma unroll
+  for (int q = 0; q < NQ; ++q) {
+    const int n = 128 * (q0 + q) + 2 * lane;
+    z[2 * q] = n < V ? lo_f(zz[q]) : -INFINITY;
+    z[2 * q + 1] = n + 1 < V ? hi_f(zz[q]) : -INFINITY;
+  }
+  // chunk statistics
+  float mx[NQ], sum[NQ];
+#pragma unroll
+  for (int q = 0; q < NQ; ++q) mx[q] = fmaxf(z[2 * q], z[2 * q + 1]);
+  float km = mx[0];
+#pragma unroll
+  for (int q = 1; q < NQ; ++q) km = fmaxf(km, mx[q]);
+  group_max_n<16>(mx);
+#pragma unroll
+  for (int q = 0; q < NQ; ++q) {
+    sum[q] = z[2 * q] > -INFINITY ? __expf(z[2 * q] - mx[q]) : 0.f;
+    sum[q] += z[2 * q + 1] > -INFINITY ? __expf(z[2 * q + 1] - mx[q]) : 0.f;
+  }
+  group_sum_n<16>(sum);
+  {  // lane q of every group of 16 writes the statistics of the group's q-th chunk
+    float m = mx[0], e = sum[0];
+#pragma unroll
+    for (int q = 1; q < NQ; ++q) {
+      m = (lane & 15) == q ? mx[q] : m;
+      e = (lane & 15) == q ? sum[q] : e;
+    }
+    if ((lane & 15) < NQ) L.cst[hyp][4 * (q0 + (lane & 15)) + (lane >> 4)] = make_float2(m, e);
+  }
+  // keys
+  if (PLAIN == 0 && lmrow) {
+    km = -INFINITY;
+#pragma unroll
+    for (int q = 0; q < NQ; ++q) {
+      const int n = min(128 * (q0 + q) + 2 * lane, v_last);
+      const float l0 = lmrow[n] * kLn10, l1 = lmrow[min(n + 1, V - 1)] * kLn10;
+      z[2 * q] = z[2 * q] + a.sel.lambda * l0;
+      z[2 * q + 1] = z[2 * q + 1] + a.sel.lambda * l1;
+      km = fmaxf(km, fmaxf(z[2 * q], z[2 * q + 1]));
+    }
+  }
+  // a lower bound of the K-th largest key: the smallest of the maxima of at least K disjoint sets of columns
+  float tau[1] = {km};
+  if constexpr (KC == 4) group_max_n<16>(tau);
+  else if constexpr (KC == 8) {
+    group_max_n<8>(tau);
+    dpp_min_n<kDppMirror>(tau);
+  } else {
+    group_max_n<4>(tau);
+    dpp_min_n<kDppHalfMirror>(tau);
+    dpp_min_n<kDppMirror>(tau);
+  }
+  const float t = fmaxf(fminf(fminf(readlane_f(tau[0], 0), readlane_f(tau[0], 16)), fminf(readlane_f(tau[0], 32), readlane_f(tau[0], 48))),
+                        -3.4028235e38f);  // (no token at -inf is a candidate)
+  // the keys at or above it (a dozen or two)
+  const int cap = kResSurvivors / parts;
+  uint64_t *surv = L.surv[hyp] + part * cap;
+  int total = 0;
+#pragma unroll
+  for (int i = 0; i < 2 * NQ; ++i) {
+    const bool in = z[i] >= t;
+    const unsigned long long mask = __ballot(in);
+    const int pos = total + __builtin_amdgcn_mbcnt_hi((uint32_t)(mask >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)mask, 0));
+    if (in && pos < cap) surv[pos] = pack_cand(z[i], 128 * (q0 + i / 2) + 2 * lane + (i & 1));
+    total += __popcll(mask);
+  }
+  if (lane < 8 && total + lane < cap) surv[total + lane] = 0;  // (below every key: the ranking reads in eights)
+  if (lane == 0) L.n_surv[hyp][part] = total;
+  return true;
+}
+
+// The row's soft-max statistics from those of its chunks, added up in the order of the per-step kernels (which depends on
+// the beam), and its K best keys from the collected ones.
+template <int KC, int PLAIN>
+__device__ __forceinline__ void res_row_finish(int g, int step, int slot, const float *lmrow, int hyp, int parts, ResSelLds &L) {
+  const ResArgs &a = res_args();
+  const int lane = threadIdx.x & 63, K = a.K, n_cst = 4 * ((a.V + 127) / 128);
+  const float2 *cst = L.cst[hyp];
+  const int cap = kResSurvivors / parts;
+  const int n0 = L.n_surv[hyp][0], n1 = parts > 1 ? L.n_surv[hyp][1] : 0, total = n0 + n1;
+  const uint64_t *surv = L.surv[hyp];
+  const int first = lane < total ? lane : 0;
+  const uint64_t mine0 = surv[min(first < n0 ? first : cap + first - n0, kResSurvivors - 1)];
+  // lanes of a group of LPR take chunks e, e + LPR, ..
+  constexpr int LPR = KC == 4 ? 16 : KC == 8 ? 8 : 64, NC = LPR == 64 ? 1 : 32 / LPR;
+  const int e = lane & (LPR - 1);
+  float2 c[NC];
+#pragma unroll
+  for (int q = 0; q < NC; ++q) {
+    const int i = e + LPR * q;
+    const float2 v = cst[i & 31];
+    c[q] = i < n_cst ? v : make_float2(-INFINITY, 0.f);
+  }
+  float m[1] = {c[0].x}, st_sum[1] = {0.f};
+#pragma unroll
+  for (int q = 1; q < NC; ++q) m[0] = fmaxf(m[0], c[q].x);
+  group_max_n<(LPR < 16 ? LPR : 16)>(m);
+  float st_mx = m[0];
+  if constexpr (LPR == 64) st_mx = fmaxf(fmaxf(readlane_f(st_mx, 0), readlane_f(st_mx, 16)), fmaxf(readlane_f(st_mx, 32), readlane_f(st_mx, 48)));
+#pragma unroll
+  for (int q = 0; q < NC; ++q)
+    st_sum[0] = c[q].x > -INFINITY ? st_sum[0] + c[q].y * __expf(c[q].x - st_mx) : st_sum[0];
+  group_sum_n<(LPR < 16 ? LPR : 16)>(st_sum);
+  float sum = st_sum[0];
+  if constexpr (LPR == 64) sum = (readlane_f(sum, 0) + readlane_f(sum, 16)) + (readlane_f(sum, 32) + readlane_f(sum, 48));
+  if (lane == 0) {
+    L.smax[hyp] = st_mx;
+    L.ssum[hyp] = sum;
+  }
+  uint64_t *out = L.cand + hyp * K;
+  if (n0 <= cap && n1 <= cap) {
+    if (lane < K && lane >= total) out[lane] = no_cand();
+    for (int i = lane; i < total; i += 64) {
+      const uint64_t mine = i < 64 ? mine0 : surv[i < n0 ? i : cap + i - n0];
+      int rank = 0;
+      auto count = [&](const uint64_t *list, int n) {
+        for (int j = 0; j < n; j += 8) {
+          uint64_t v[8];
+#pragma unroll
+          for (int q = 0; q < 8; ++q) v[q] = list[j + q];
+#pragma unroll
+          for (int q = 0; q < 8; ++q) rank += v[q] > mine;
+        }
+      };
+      count(surv, n0);
+      if (parts > 1) count(surv + cap, n1);
+      if (rank < K) out[rank] = mine;
+    }
+  } else {  // (many equal keys) K rounds of "best remaining key" over the row
+    const float *zrow = res_addr(a, g).z(step, slot);
+    uint64_t last = ~0ull;
+    for (int j = 0; j < K; ++j) {
+      uint64_t best = no_cand();
+      for (int n = lane; n < a.V; n += 64) {
+        float key = load_agent(zrow + n);
+        if (PLAIN == 0 && lmrow) key = key + a.sel.lambda * (lmrow[n] * kLn10);
+        const uint64_t x = key > -INFINITY ? pack_cand(key, n) : no_cand();
+        if (x < last && x > best) best = x;
+      }
+      best = wave_max_u64(best);
+      if (lane == 0) out[j] = best;
+      last = best > no_cand() ? best : no_cand() + 1;
+    }
+  }
+}
+
+// LM scores (log10) of every token after a hypothesis, by one wave, into an LDS row: see lm_row_block
+__device__ __forceinline__ void res_lm_row(const LmView &lm, const int *hist, int len, float *row, LmCtxRec *rec) {
+  const int lane = threadIdx.x & 63, nj = lm.order - 1;
+  int toks[kCtxMax], have = 0;
+#pragma unroll
+  for (int i = 0; i < kCtxMax; ++i) {
+    toks[i] = hist[i];
+    if (toks[i] >= 0 && have == i) have = i + 1;
+  }
+  int jmax = nj < have ? nj : have;
+  jmax = len < jmax ? len : jmax;
+  constexpr int NU = kResMaxV / 64;
+  float uni[NU];
+#pragma unroll
+  for (int q = 0; q < NU; ++q) {
+    const int v = lane + 64 * q;
+    uni[q] = lm.uni[v < lm.V ? v : 0];
+  }
+  if (lane >= 1 && lane <= kCtxMax) rec[lane] = lm_probe(lm, toks, lane, jmax);
+  wave_sync();
+  double bo[kCtxMax + 1];
+  {
+    double acc = 0.0;
+#pragma unroll
+    for (int j = kCtxMax; j >= 1; --j) {
+      bo[j] = acc;
+      if (j <= nj) acc += (double)rec[j].backoff;
+    }
+    bo[0] = acc;
+  }
+  const float base = (float)bo[0];
+#pragma unroll
+  for (int q = 0; q < NU; ++q) {
+    const int v = lane + 64 * q;
+    if (v < lm.V) row[v] = uni[q] + base;
+  }
+#pragma unroll
+  for (int j = 1; j <= kCtxMax; ++j) {
+    if (j > nj) break;
+    wave_sync();
+    const float add = (float)bo[j];
+    const int beg = rec[j].begin, cnt = rec[j].count;
+    for (int i0 = lane; i0 < cnt; i0 += 4 * 64) {  // four successors of a lane in flight at once
+      int st[4];
+      float sp[4];
+#pragma unroll
+      for (int q = 0; q < 4; ++q) {
+        const int i = i0 + 64 * q;
+        st[q] = lm.succ_tok[beg + (i < cnt ? i : 0)];
+        sp[q] = lm.succ_p[beg + (i < cnt ? i : 0)];
+      }
+#pragma unroll
+      for (int q = 0; q < 4; ++q)
+        if (i0 + 64 * q < cnt) row[st[q]] = sp[q] + add;
+    }
+  }
+  wave_sync();
+}
+
+template <int KC, int PLAIN>
+__device__ __forceinline__ void res_selector(ResBlock k, int sel, float *lds) {
+  const ResArgs &a0 = res_args();
+  const int K = a0.K, V = a0.V, lane = threadIdx.x & 63, upc = a0.upc;
+  const bool has_lm = a0.has_lm != 0, late_lm = has_lm && !a0.sel.lm_early;
+  ResSelLds &L = *reinterpret_cast<ResSelLds *>(lds);
+  SelectScratchWide *scratch = reinterpret_cast<SelectScratchWide *>(lds + (sizeof(ResSelLds) + 15) / 16 * 4);
+  k.word = reinterpret_cast<uint64_t *>(scratch + upc) + k.wave * a0.NT * kResSlot;
+  float *lm_rows = reinterpret_cast<float *>(reinterpret_cast<uint64_t *>(scratch + upc) + kResWaves * a0.NT * kResSlot);
+  const int u0 = sel * upc, nu = min(upc, k.nu - u0);  // the block's utterances of the group (none: nu <= 0)
+  const int n_hyp = nu * K;
+  const int parts = n_hyp <= kResWaves / 2 && V > kResMaxV / 2 ? 2 : 1;  // waves per row
+  ResidentSelect rs{};
+  if (k.wave < nu) {  // the wave that selects for utterance u0 + wave
+    const int u = u0 + k.wave;
+    SelectScratchWide &s = scratch[k.wave];
+    if (lane < K) {
+      s.score[lane] = lane == 0 ? 0.0 : -INFINITY;
+      s.t[lane] = s.sym[lane] = s.len[lane] = 0;
+      s.last[lane] = -1;
+      s.hash[lane] = 0;
+      for (int i = 0; i < kCtxMax; ++i) s.ctx[lane][i] = -1;
+    }
+    rs.slot0 = u * K;
+    rs.T_b = a0.lengths[res_utt(a0, k.g, u)];
+    rs.lm = lm_rows + (size_t)k.wave * K * V;
+    rs.finished = rs.T_b == 0;
+  }
+  __syncthreads();
+  int over = res_first_words(a0, k);
+  for (int step = 0; over == 0; ++step) {
+    if (has_lm)  // rows of the hypotheses as the last step left them (their histories: behind its last barrier)
+      for (int q = k.wave; q < n_hyp; q += kResWaves)
+        res_lm_row(res_args().lm, scratch[q / K].ctx[q % K], scratch[q / K].len[q % K], lm_rows + (size_t)q * V, L.rec[k.wave]);
+    // (every row is waited for, also those of finished utterances: a word of this step tells the group's other blocks that
+    // all logits of the step were there)
+    if (parts == 2) {
+      const int q = k.wave >> 1;
+      if (q < n_hyp && !res_row<kResMaxV / 256, KC, PLAIN>(k.g, step, u0 * K + q, late_lm ? lm_rows + (size_t)q * V : nullptr, q, k.wave & 1, 2, L)) return;
+    } else {
+      for (int q = k.wave; q < n_hyp; q += kResWaves)
+        if (!res_row<kResMaxV / 128, KC, PLAIN>(k.g, step, u0 * K + q, late_lm ? lm_rows + (size_t)q * V : nullptr, q, 0, 1, L)) return;
+    }
+    __syncthreads();
+    for (int q = k.wave; q < n_hyp; q += kResWaves)
+      res_row_finish<KC, PLAIN>(k.g, step, u0 * K + q, late_lm ? lm_rows + (size_t)q * V : nullptr, q, parts, L);
+    __syncthreads();
+    if (k.wave < nu) {
+      const ResArgs &a = res_args();
+      const int u = u0 + k.wave, b = res_utt(a, k.g, u);
+      rs.words = res_addr(a, k.g).w(step) + u * K;
+      rs.step = step;
+      if (rs.finished) {
+        if (lane < K) store_agent(rs.words + lane, slot_word(step, 1, u * K + lane, -1, 0));
+      } else {
+        const CandView cv{L.cand + k.wave * K * K, L.smax + k.wave * K, L.ssum + k.wave * K, L.zs + k.wave * K * (1 + a.sel.ND), b * K};
+        if constexpr (KC == 4) select_utterance<16, 1, 4, false, false, SelectScratchWide, true, PLAIN, false, true>(a.sel, b, scratch[k.wave], cv, &rs);
+        else if constexpr (KC == 8) select_utterance<8, 1, 8, false, false, SelectScratchWide, true, PLAIN, false, true>(a.sel, b, scratch[k.wave], cv, &rs);
+        else select_utterance<4, 1, 16, false, false, SelectScratchWide, true, PLAIN, false, true>(a.sel, b, scratch[k.wave], cv, &rs);
+        rs.finished = __builtin_amdgcn_readfirstlane(rs.finished);
+      }
+    }
+    if (has_lm) __syncthreads();
+    over = res_words(k, step);
+  }
+}
+
+// FULL: H = P = 640 (loops of known length).  KC: beams up to 4, 8, 16.  PLAIN: 1 = ALSD++ on a plain RNN-T (see
+// select_utterance), 0 = any.  One block of 8 waves per compute unit (the LDS it asks for is more than half of a unit's).
+// The first n_sel blocks of a group select, the others own the tiles.
+template <bool FULL, bool BF16, int KC, int PLAIN>
+__global__ __launch_bounds__(kResThreads, 2) void k_decode_resident(ResArgs) {
+  extern __shared__ __align__(16) float smem[];
+  __shared__ int s_ok;
+  const ResArgs &a = res_args();
+  if (*reinterpret_cast<const volatile int *>(a.sel.done)) return;
+  // every block of the launch must be on the chip before any of them waits for another's data
+  if (threadIdx.x == 0) {
+    __hip_atomic_fetch_add(a.ctl, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    const long long t0 = wall_clock64();
+    int ok = 0;
+    for (;;) {
+      if (load_agent(a.ctl + 1)) break;
+      if (load_agent(a.ctl) >= a.start_blocks) {
+        ok = 1;
+        break;
+      }
+      if (wall_clock64() - t0 > a.start_limit) {
+        store_agent(a.ctl + 1, 1);
+        *a.h_abort = 1;
+        break;
+      }
+      __builtin_amdgcn_s_sleep(4);
+    }
+    s_ok = ok;
+  }
+  __syncthreads();
+  if (!s_ok) return;
+  ResBlock k;
+  // (workgroup i runs on XCD i % 8: the blocks of a group share as few L2s as they can)
+  k.g = (int)blockIdx.x % a.n_groups;
+  const int rank = (int)blockIdx.x / a.n_groups;
+  k.nu = (a.B - k.g + a.n_groups - 1) / a.n_groups;
+  k.nslots = k.nu * a.K;
+  k.wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  k.phase = 0;
+  if (rank < a.n_sel) {
+    res_selector<KC, PLAIN>(k, rank, smem);
+  } else {
+    const ResTab &tab = a.tab[rank - a.n_sel];
+    if (tab.nR + tab.nJ + tab.nP > 0) res_worker<FULL, BF16>(k, tab, smem);
+  }
+}
+
+typedef void (*ResKernel)(ResArgs);
+// each in a translation unit of its own (resident_kernels.hip), so that they build at once
+ResKernel resident_kernel_640_f32(int K, bool plain);
+ResKernel resident_kernel_640_bf16(int K, bool plain);
+ResKernel resident_kernel_any_f32(int K, bool plain);
+ResKernel resident_kernel_any_bf16(int K, bool plain);
+
+}  // namespace rb

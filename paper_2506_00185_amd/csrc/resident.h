@@ -1,0 +1,57 @@
+// Host side of the resident step loop (kernels_resident.h): weights in its layout, plan per batch shape, launch.
+#pragma once
+#include <hip/hip_runtime.h>
+
+#include <cstddef>
+#include <string>
+#include <vector>
+
+#include "../../include/rnnt_beam.h"
+#include "lm_device.h"
+#include "select.h"
+
+namespace rb {
+
+struct ResTab;
+
+// Per-handle state: owned by the handle, everything on the device it was created on.
+struct Resident {
+  bool usable = false;
+  int n_cus = 0, max_lds = 0;
+  int misses = 0;                 // launches that gave up; after kResidentMaxMisses the handle stays with the per-step launches
+  float *WR = nullptr, *WJ = nullptr, *WP = nullptr;
+  uint64_t *WJb = nullptr, *WPb = nullptr;
+  float *hb = nullptr, *pb = nullptr, *zb = nullptr;
+  uint64_t *words = nullptr;
+  int *ctl = nullptr;
+  ResTab *tab = nullptr;          // who owns what in a group, as uploaded for the last launch:
+  int tab_blocks = 0, tab_sel = 0, tab_lm = -1;
+  int *h_abort = nullptr, *h_abort_dev = nullptr;  // pinned
+  std::vector<void *> allocs;
+};
+constexpr int kResidentMaxMisses = 3;
+
+// What the packing reads: the handle's k4-major weights (see kernels.h, k4_index)
+struct ResidentWeights {
+  const float *W_hh, *W_out, *W_pred;
+  int out_rows;  // padded rows of W_out
+};
+
+int resident_create(Resident &r, const rnnt_config_t &c, const ResidentWeights &w, std::string &err);
+void resident_destroy(Resident &r);
+
+struct ResidentBatch {
+  int B, T, K, algo, spin_limit;
+  bool halves;      // the per-step launches would split the projection along k at this size
+  const float *b_out, *b_pred, *G, *f_proj;
+  const int *lengths;
+  int Npad;
+  bool has_lm;
+  LmView lm;
+  SelectArgs sel;   // n_chunks = 1
+};
+// whether a batch of this shape can run as one resident launch
+bool resident_fits(const Resident &r, const rnnt_config_t &c, int B, int K, int T, int max_steps, bool has_lm);
+hipError_t resident_launch(Resident &r, const rnnt_config_t &c, const ResidentBatch &b, hipStream_t s);
+
+}  // namespace rb

@@ -23,6 +23,7 @@
 #include "kernels_big.h"
 #include "kernels_persistent.h"
 #include "lm.h"
+#include "resident.h"
 
 using namespace rb;
 
@@ -182,6 +183,7 @@ struct rnnt_beam {
   int n_cus = 0, spin_limit = kSpinLimit;
   int max_lds = 64 * 1024;  // LDS a block may ask for on this device
   bool last_persistent = false;
+  Resident res;         // the step loop as one launch with the weights on chip
   char *h_out = nullptr;          // pinned: the last decode's control words and packed results (see out_pack)
   size_t h_out_bytes = 0;
   OutPack last_out{};
@@ -905,7 +907,51 @@ int launch_persistent(rnnt_beam *h, hipStream_t s, const StepPlan &p, int max_st
   return RNNT_OK;
 }
 
-int run_decode(rnnt_beam *h, const float *enc, const int32_t *lengths, const StepPlan &p, hipStream_t s) {
+// The resident loop (one launch that keeps the weights on chip, kernels_resident.h) takes the decodes that would replay a
+// graph, where the batch fits it.  Its blocks wait for each other, so there is one such launch at a time on a device:
+// a decode that finds the device taken by another thread's uses the per-step launches.
+struct DeviceSlot {
+  std::mutex *m = nullptr;
+  bool take(int dev) {
+    static std::mutex slots[kMaxDevices];
+    if (dev < 0 || dev >= kMaxDevices || !slots[dev].try_lock()) return false;
+    m = &slots[dev];
+    return true;
+  }
+  ~DeviceSlot() {
+    if (m) m->unlock();
+  }
+};
+
+int decode_max_steps(const rnnt_config_t &c, const Workspace &w, int T) {
+  // every utterance has finished after at most T (s + 1) steps (the selection enforces it)
+  return T * (c.max_symbols + 1) < w.S_max ? T * (c.max_symbols + 1) : w.S_max;
+}
+
+bool use_resident(const rnnt_beam *h, const StepPlan &p) {
+  const rnnt_config_t &c = h->cfg;
+  if (!c.use_graph || c.persistent_kernel || h->profiling || p.inj_tok || p.plain || p.ahead || p.big) return false;
+  return resident_fits(h->res, c, p.B, p.K, p.T, decode_max_steps(c, *p.ws, p.T), p.lm != nullptr);
+}
+
+int launch_resident(rnnt_beam *h, hipStream_t s, const StepPlan &p) {
+  const Workspace &w = *p.ws;
+  const rnnt_config_t &c = h->cfg;
+  ResidentBatch b{};
+  b.B = p.B; b.T = p.T; b.K = p.K; b.algo = p.algo;
+  b.spin_limit = h->spin_limit;
+  b.halves = proj_split(c, p.M);
+  b.b_out = h->b_out; b.b_pred = h->b_pred; b.G = h->G; b.f_proj = w.f_proj;
+  b.lengths = w.lengths;
+  b.Npad = h->n_chunks * 32;
+  b.has_lm = p.lm != nullptr;
+  if (p.lm) b.lm = lm_view(p.lm);
+  fill_select_args(h, p, 0, 1, b.sel);
+  RB_HIP(h, resident_launch(h->res, c, b, s));
+  return RNNT_OK;
+}
+
+int run_decode(rnnt_beam *h, const float *enc, const int32_t *lengths, const StepPlan &p, hipStream_t s, bool resident = true) {
   const Workspace &w = *p.ws;
   const rnnt_config_t &c = h->cfg;
   int *n_finished = w.ctrl, *done = w.ctrl + 1, *step_base = w.ctrl + 2, *bad_arg = w.ctrl + 3,
@@ -916,6 +962,11 @@ int run_decode(rnnt_beam *h, const float *enc, const int32_t *lengths, const Ste
   for (int i = 0; i < KT_COUNT; ++i) h->timers[i] = KernelTimer{kKernelNames[i], 0.f, 0};
   h->prof_used = 0;
   h->prof_launches.clear();
+  DeviceSlot slot;
+  if (resident) {
+    int dev = -1;
+    resident = use_resident(h, p) && hipGetDevice(&dev) == hipSuccess && slot.take(dev);
+  }
   RB_HIP(h, hipEventRecord(h->ev_begin, s));
   {
     InitArgs a;
@@ -930,7 +981,8 @@ int run_decode(rnnt_beam *h, const float *enc, const int32_t *lengths, const Ste
     a.n_state = (size_t)c.P * w.Mp;
     a.R = lstm ? w.Rgates : nullptr;
     a.n_R = (size_t)p.M * 4 * c.P;
-    const bool halves = lstm && proj_split(c, p.M);
+    if (resident) a.h0 = a.c0 = a.R = nullptr;  // (that loop's state is its own)
+    const bool halves = lstm && !resident && proj_split(c, p.M);
     a.pre0 = halves ? w.pre : nullptr;
     a.pre1 = halves ? w.pre2 : nullptr;
     a.n_pre = (size_t)c.H * w.Mp;
@@ -956,11 +1008,12 @@ int run_decode(rnnt_beam *h, const float *enc, const int32_t *lengths, const Ste
                          c.prec == RNNT_BF16_JOINT ? 1 : 0, nonfinite, lengths, p.T);
     if (rc) return rc;
   }
-  // every utterance has finished after at most T (s + 1) steps (the selection enforces it)
-  const int max_steps = p.T * (c.max_symbols + 1) < w.S_max ? p.T * (c.max_symbols + 1) : w.S_max;
+  const int max_steps = decode_max_steps(c, w, p.T);
   int rc = RNNT_OK;
-  h->last_persistent = use_persistent(h, p);
-  if (h->last_persistent) {
+  h->last_persistent = !resident && use_persistent(h, p);
+  if (resident) {
+    if ((rc = launch_resident(h, s, p))) return rc;
+  } else if (h->last_persistent) {
     // one launch walks all steps (it starts with the prediction network on the start symbol itself)
     if ((rc = launch_persistent(h, s, p, max_steps))) return rc;
   } else {
@@ -1103,6 +1156,27 @@ int run_decode(rnnt_beam *h, const float *enc, const int32_t *lengths, const Ste
   h->last_K = p.K;
   h->last_T = p.T;
   h->last_stream = s;
+  if (resident) {
+    // until the device reports that every utterance has finished, or that the launch gave up (its blocks did not all find
+    // a compute unit in time); then the batch is decoded once more with the per-step launches
+    volatile int *host_done = h->h_done, *gave_up = h->res.h_abort;
+    for (int i = 1; !*host_done && !*gave_up; ++i)
+      if ((i & 0xffff) == 0) {  // (an error on the stream ends the wait)
+        const hipError_t e = hipStreamQuery(s);
+        if (e != hipErrorNotReady) {
+          RB_HIP(h, e);
+          break;
+        }
+      }
+    if (*gave_up || !*host_done) {
+      RB_HIP(h, hipStreamSynchronize(s));
+      if (*gave_up || !*host_done) {
+        ++h->res.misses;
+        if (h->trace_pacing) fprintf(stderr, "rnnt_beam: resident loop gave up, decoding with per-step launches\n");
+        return run_decode(h, enc, lengths, p, s, false);
+      }
+    }
+  }
   return RNNT_OK;
 }
 
@@ -1222,6 +1296,10 @@ int rnnt_beam_create(const rnnt_config_t *cfg, const rnnt_weights_t *w, rnnt_bea
   if (!rc) {
     hipError_t e = hipHostMalloc(reinterpret_cast<void **>(&h->h_done), 128, hipHostMallocMapped);
     if (e == hipSuccess) e = hipHostGetDevicePointer(reinterpret_cast<void **>(&h->h_done_dev), h->h_done, 0);
+    if (e == hipSuccess) {
+      const ResidentWeights rw{h->W_hh, h->W_out, h->W_pred, h->n_chunks * 32};
+      rc = c.use_graph && !c.persistent_kernel && !c.async_enqueue ? resident_create(h->res, c, rw, h->err) : RNNT_OK;
+    }
     h->h_out_bytes = out_pack(c.max_B, c.max_beam, h->ws.cap).bytes;
     if (e == hipSuccess) e = hipHostMalloc(reinterpret_cast<void **>(&h->h_out), h->h_out_bytes, hipHostMallocDefault);
     if (e == hipSuccess) e = hipEventCreate(&h->ev_begin);
@@ -1250,7 +1328,7 @@ int rnnt_beam_create(const rnnt_config_t *cfg, const rnnt_weights_t *w, rnnt_bea
         h->pctl = static_cast<PersistCtl *>(q);
       }
     }
-    if (e != hipSuccess) {
+    if (e != hipSuccess && !rc) {
       h->err = std::string("create: ") + hipGetErrorString(e);
       rc = RNNT_E_HIP;
     }
@@ -1496,6 +1574,7 @@ void rnnt_beam_destroy(rnnt_beam_t *h) {
   hipDeviceSynchronize();
   for (auto &kv : h->graphs) hipGraphExecDestroy(kv.second.first);
   for (void *p : h->allocs) hipFree(p);
+  resident_destroy(h->res);
   if (h->h_done) hipHostFree(h->h_done);
   if (h->h_out) hipHostFree(h->h_out);
   hipEvent_t evs[] = {h->ev_begin, h->ev_end};

@@ -1,0 +1,251 @@
+// Host side of the resident step loop: see resident.h and kernels_resident.h.
+#include "resident.h"
+
+#include <algorithm>
+#include <cmath>
+#include <cstring>
+
+#include "kernels_resident.h"
+
+namespace rb {
+
+namespace {
+
+__device__ __forceinline__ size_t k4_at(int k, int row, int rows) { return ((size_t)(k >> 2) * rows + row) * 4 + (k & 3); }
+
+// W (k4-major, `rows` rows) -> [tile of 16 rows][round][64 lanes][2].  MAP 0: rows as they are; 1: tiles of four LSTM units;
+// 2: tiles of projection outputs (res_p_row)
+template <int MAP>
+__global__ void k_pack_f32(const float *W, int rows, int K, int n_tiles, float *out) {
+  const int n_rounds = K / 8;
+  const size_t n = (size_t)n_tiles * n_rounds * 128;
+  for (size_t i = (size_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += (size_t)gridDim.x * blockDim.x) {
+    const int e = (int)(i & 1), lane = (int)(i >> 1) & 63;
+    const int round = (int)((i >> 7) % n_rounds), tile = (int)((i >> 7) / n_rounds);
+    const int r = lane & 15, kq = lane >> 4;
+    int row;
+    if (MAP == 0) row = 16 * tile + r;
+    else if (MAP == 1) row = 4 * (8 * (tile >> 1) + 2 * (r >> 2) + (tile & 1)) + (r & 3);
+    else row = res_p_row(tile, r);
+    out[i] = row < rows ? W[k4_at(res_k_of(round, kq, e), row, rows)] : 0.f;
+  }
+}
+// the same for the bf16 matrix instructions: [tile of 32 rows][round][64 lanes] four bf16 (values are bf16 already)
+template <int MAP>
+__global__ void k_pack_bf16(const float *W, int rows, int K, int n_tiles, uint64_t *out) {
+  const int n_rounds = K / 8;
+  const size_t n = (size_t)n_tiles * n_rounds * 64;
+  for (size_t i = (size_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += (size_t)gridDim.x * blockDim.x) {
+    const int lane = (int)(i & 63), r = lane & 31, half = lane >> 5;
+    const int round = (int)((i >> 6) % n_rounds), tile = (int)((i >> 6) / n_rounds);
+    const int row = MAP == 0 ? 32 * tile + r : res_p_row(2 * tile + (r >> 4), r & 15);
+    float v[4];
+    for (int q = 0; q < 4; ++q) v[q] = row < rows ? W[k4_at(8 * round + 4 * half + q, row, rows)] : 0.f;
+    out[i] = (uint64_t)pack_bf16_rne(v[2], v[3]) << 32 | pack_bf16_rne(v[0], v[1]);
+  }
+}
+
+// pre-fill of the hand-over arrays, zero words and counters
+__global__ void k_resident_init(ResArgs a) {
+  const size_t gid = (size_t)blockIdx.x * blockDim.x + threadIdx.x, n = (size_t)gridDim.x * blockDim.x;
+  const uintx4_t e = {kResEmpty, kResEmpty, kResEmpty, kResEmpty};
+  for (size_t i = gid; i < res_h_floats(a) / 4; i += n) reinterpret_cast<uintx4_t *>(a.hb)[i] = e;
+  for (size_t i = gid; i < res_p_floats(a) / 4; i += n) reinterpret_cast<uintx4_t *>(a.pb)[i] = e;
+  for (size_t i = gid; i < res_z_floats(a) / 4; i += n) reinterpret_cast<uintx4_t *>(a.zb)[i] = e;
+  for (size_t i = gid; i < res_words(a); i += n) a.words[i] = 0;
+  if (gid < 2) a.ctl[gid] = 0;
+}
+
+constexpr int kResShortSpin = 1000;  // a test's limit: the launch waits, for a microsecond, for one block more than it has
+
+struct Plan {
+  bool ok = false;
+  int n_groups = 0, n_blocks = 0, nu = 0, n_sel = 0, upc = 0, NT = 0;
+  size_t lds = 0;
+  std::vector<ResTab> tab;
+};
+
+// Who owns what among the n_blocks blocks of a group that do not select.  Every tile goes to the block that has least of
+// its kind (the phases of a step follow each other, so what counts is the largest number per block and kind), then least of
+// all.  False: they do not fit.
+bool assign_tiles(const rnnt_config_t &c, int n_blocks, std::vector<ResTab> &tab) {
+  const bool bf = c.prec == RNNT_BF16_JOINT;
+  const int N = c.V + 1 + c.n_durations;
+  const int nR = 4 * c.P / 16, nJ = bf ? (N + 31) / 32 : (N + 15) / 16, nP = bf ? c.H / 32 : c.H / 16;
+  const int reg_j = bf ? kResRegJ<true> : kResRegJ<false>, max_p = bf ? 1 : kResMaxP;
+  tab.assign(n_blocks, ResTab{});
+  auto total = [&](const ResTab &t) { return t.nR + t.nJ + t.nP; };
+  auto put = [&](int tile, auto count, auto room, auto store) {
+    int best = -1;
+    for (int i = 0; i < n_blocks; ++i) {
+      if (!room(tab[i])) continue;
+      if (best < 0 || count(tab[i]) < count(tab[best]) || (count(tab[i]) == count(tab[best]) && total(tab[i]) < total(tab[best])))
+        best = i;
+    }
+    if (best < 0) return false;
+    store(tab[best], tile);
+    return true;
+  };
+  for (int t = 0; t < nR; ++t)
+    if (!put(t, [](const ResTab &x) { return (int)x.nR; }, [](const ResTab &x) { return x.nR < kResMaxR; },
+             [](ResTab &x, int tile) { x.R[x.nR++] = (int16_t)tile; }))
+      return false;
+  for (int t = 0; t < nJ; ++t)
+    if (!put(t, [](const ResTab &x) { return (int)x.nJ; }, [&](const ResTab &x) { return x.nJ < reg_j + 1; },
+             [](ResTab &x, int tile) { x.J[x.nJ++] = (int16_t)tile; }))
+      return false;
+  for (int t = 0; t < nP; ++t)
+    if (!put(t, [](const ResTab &x) { return (int)x.nP; },
+             [&](const ResTab &x) { return x.nP < max_p && x.nP + std::max(0, x.nJ - reg_j) < kResMaxLdsTiles; },
+             [](ResTab &x, int tile) { x.P[x.nP++] = (int16_t)tile; }))
+      return false;
+  return true;
+}
+
+Plan make_plan(const Resident &r, const rnnt_config_t &c, int B, int K, bool has_lm) {
+  Plan p;
+  // one group per 32 compute units at most (a group of 32 holds the weights of a 640-wide decoder), never more groups
+  // than utterances: few utterances get more blocks each
+  int G = 1;
+  while (2 * G <= B && 2 * G * 32 <= r.n_cus) G *= 2;
+  p.n_groups = G;
+  p.n_blocks = r.n_cus / G;
+  p.nu = (B + G - 1) / G;
+  const int slots = p.nu * K;
+  p.NT = (slots + kResSlot - 1) / kResSlot;
+  if (p.NT > kResMaxNT) return p;
+  const int most_sel = std::max(1, p.n_blocks / 8);
+  p.upc = (p.nu + most_sel - 1) / most_sel;
+  if (p.upc > kResMaxSel || p.upc * K * K > 512 || p.upc * K > kResMaxHyps) return p;
+  p.n_sel = (p.nu + p.upc - 1) / p.upc;
+  if (!assign_tiles(c, p.n_blocks - p.n_sel, p.tab)) return p;
+  const bool bf = c.prec == RNNT_BF16_JOINT;
+  int lds_tiles = 0;
+  for (const ResTab &t : p.tab) lds_tiles = std::max(lds_tiles, t.nP + std::max(0, t.nJ - (bf ? kResRegJ<true> : kResRegJ<false>)));
+  const size_t worker = (size_t)lds_tiles * std::max(c.P, c.H) * kResSlot * 4 +
+                        (size_t)2 * (bf ? kResRedBlocks<true> : kResRedBlocks<false>) * kResRedBlock * 4 +
+                        (size_t)kResMaxR * p.NT * (256 + 128) * 4 + (size_t)p.NT * kResSlot * (sizeof(int2) + kResWaves * 8);
+  const size_t sel = (sizeof(ResSelLds) + 15) / 16 * 16 + p.upc * sizeof(SelectScratchWide) +
+                     (size_t)p.NT * kResSlot * kResWaves * 8 + (has_lm ? (size_t)p.upc * K * c.V * 4 : 0);
+  p.lds = std::max(worker, sel);
+  p.lds = std::max<size_t>(p.lds, 84 * 1024);  // more than half of a compute unit's: two blocks never share one
+  if (p.lds + 64 > (size_t)r.max_lds) return p;
+  p.ok = true;
+  return p;
+}
+
+ResKernel pick_kernel(const rnnt_config_t &c, int K, bool plain) {
+  const bool full = c.H == 640 && c.P == 640, bf = c.prec == RNNT_BF16_JOINT;
+  if (full) return bf ? resident_kernel_640_bf16(K, plain) : resident_kernel_640_f32(K, plain);
+  return bf ? resident_kernel_any_bf16(K, plain) : resident_kernel_any_f32(K, plain);
+}
+
+}  // namespace
+
+void resident_destroy(Resident &r) {
+  for (void *p : r.allocs) hipFree(p);
+  if (r.h_abort) hipHostFree(r.h_abort);
+  r = Resident{};
+}
+
+int resident_create(Resident &r, const rnnt_config_t &c, const ResidentWeights &w, std::string &err) {
+  r.usable = false;
+  // LSTM decoders whose contractions split into eight slices of whole rounds and fit the registers; vocabularies that one
+  // wave holds in registers
+  if (c.pred != RNNT_PRED_LSTM || c.tdt_all_pairs || c.H % 64 || c.P % 64 || c.H > 8 * 8 * kResMaxRounds ||
+      c.P > 8 * 8 * kResMaxRounds || c.V > kResMaxV)
+    return RNNT_OK;
+  hipError_t e;
+  auto fail = [&](const char *what) {
+    err = std::string(what) + ": " + hipGetErrorString(e);
+    resident_destroy(r);
+    return e == hipErrorOutOfMemory ? RNNT_E_NOMEM : RNNT_E_HIP;
+  };
+  int dev = 0;
+  if ((e = hipGetDevice(&dev)) != hipSuccess) return fail("hipGetDevice");
+  if ((e = hipDeviceGetAttribute(&r.n_cus, hipDeviceAttributeMultiprocessorCount, dev)) != hipSuccess) return fail("CU count");
+  if ((e = hipDeviceGetAttribute(&r.max_lds, hipDeviceAttributeMaxSharedMemoryPerBlock, dev)) != hipSuccess) return fail("LDS size");
+  if (r.n_cus < 32) return RNNT_OK;
+  const bool bf = c.prec == RNNT_BF16_JOINT;
+  const int N = c.V + 1 + c.n_durations, G = r.n_cus / 32;
+  const size_t rows = (size_t)G * kResMaxNT * kResSlot;
+  auto alloc = [&](auto **p, size_t n) {
+    void *q = nullptr;
+    e = hipMalloc(&q, n * sizeof(**p));
+    if (e == hipSuccess) {
+      r.allocs.push_back(q);
+      *p = static_cast<std::remove_reference_t<decltype(*p)>>(q);
+    }
+    return e == hipSuccess;
+  };
+  const int nR = 4 * c.P / 16, nJ = bf ? (N + 31) / 32 : (N + 15) / 16, nP = bf ? c.H / 32 : c.H / 16;
+  bool ok = alloc(&r.WR, (size_t)nR * 16 * c.P);
+  if (bf) ok = ok && alloc(&r.WJb, (size_t)nJ * (c.H / 8) * 64) && alloc(&r.WPb, (size_t)nP * (c.P / 8) * 64);
+  else ok = ok && alloc(&r.WJ, (size_t)nJ * 16 * c.H) && alloc(&r.WP, (size_t)nP * 16 * c.P);
+  ok = ok && alloc(&r.hb, kResStepRing * rows * c.P) && alloc(&r.pb, 2 * rows * c.H) && alloc(&r.zb, 2 * rows * w.out_rows) &&
+       alloc(&r.words, kResStepRing * rows) && alloc(&r.ctl, 64) && alloc(&r.tab, r.n_cus);
+  if (!ok) return fail("resident loop: hipMalloc");
+  if ((e = hipHostMalloc(reinterpret_cast<void **>(&r.h_abort), 128, hipHostMallocMapped)) != hipSuccess) return fail("hipHostMalloc");
+  if ((e = hipHostGetDevicePointer(reinterpret_cast<void **>(&r.h_abort_dev), r.h_abort, 0)) != hipSuccess) return fail("pinned word");
+  const dim3 grid(512), block(256);
+  hipLaunchKernelGGL(k_pack_f32<1>, grid, block, 0, nullptr, w.W_hh, 4 * c.P, c.P, nR, r.WR);
+  if (bf) {
+    hipLaunchKernelGGL(k_pack_bf16<0>, grid, block, 0, nullptr, w.W_out, w.out_rows, c.H, nJ, r.WJb);
+    hipLaunchKernelGGL(k_pack_bf16<2>, grid, block, 0, nullptr, w.W_pred, c.H, c.P, nP, r.WPb);
+  } else {
+    hipLaunchKernelGGL(k_pack_f32<0>, grid, block, 0, nullptr, w.W_out, w.out_rows, c.H, nJ, r.WJ);
+    hipLaunchKernelGGL(k_pack_f32<2>, grid, block, 0, nullptr, w.W_pred, c.H, c.P, nP, r.WP);
+  }
+  if ((e = hipGetLastError()) != hipSuccess || (e = hipDeviceSynchronize()) != hipSuccess) return fail("resident loop: packing");
+  r.usable = true;
+  return RNNT_OK;
+}
+
+bool resident_fits(const Resident &r, const rnnt_config_t &c, int B, int K, int T, int max_steps, bool has_lm) {
+  if (!r.usable || r.misses >= kResidentMaxMisses) return false;
+  if (T >= kWordMaxFrames || max_steps > 60000) return false;  // fields of the words
+  return make_plan(r, c, B, K, has_lm).ok;
+}
+
+hipError_t resident_launch(Resident &r, const rnnt_config_t &c, const ResidentBatch &b, hipStream_t s) {
+  Plan p = make_plan(r, c, b.B, b.K, b.has_lm);
+  if (!p.ok) return hipErrorInvalidValue;
+  ResArgs a{};
+  a.WR = r.WR; a.WJ = r.WJ; a.WP = r.WP; a.WJb = r.WJb; a.WPb = r.WPb;
+  a.b_out = b.b_out; a.b_pred = b.b_pred; a.G = b.G; a.f_proj = b.f_proj;
+  a.lengths = b.lengths;
+  a.hb = r.hb; a.pb = r.pb; a.zb = r.zb; a.words = r.words;
+  a.tab = r.tab;
+  a.ctl = r.ctl;
+  a.h_abort = r.h_abort_dev;
+  a.sel = b.sel;
+  a.lm = b.lm;
+  a.B = b.B; a.K = b.K; a.T = b.T; a.V = c.V; a.N = c.V + 1 + c.n_durations; a.Npad = b.Npad; a.H = c.H; a.P = c.P;
+  a.n_groups = p.n_groups; a.n_sel = p.n_sel; a.upc = p.upc;
+  a.NT = p.NT; a.halves = b.halves ? 1 : 0; a.has_lm = b.has_lm ? 1 : 0;
+  a.rounds_h = c.H / 64; a.rounds_p = c.P / 64;
+  a.poll_limit = std::min(1 << 19, b.spin_limit);
+  const bool short_spin = b.spin_limit < kResShortSpin;
+  a.start_blocks = p.n_groups * p.n_blocks + (short_spin ? 1 : 0);
+  a.start_limit = short_spin ? 100 : 5000000;  // 50 ms
+  *reinterpret_cast<volatile int *>(r.h_abort) = 0;
+  hipError_t e = hipSuccess;
+  if (r.tab_blocks != p.n_blocks || r.tab_sel != p.n_sel || r.tab_lm != a.has_lm) {
+    // (pageable memory: the call returns when it has been read; the last launch that read the table is over, as its
+    // decode waited for it)
+    e = hipMemcpyAsync(r.tab, p.tab.data(), sizeof(ResTab) * p.tab.size(), hipMemcpyHostToDevice, s);
+    if (e != hipSuccess) return e;
+    r.tab_blocks = p.n_blocks;
+    r.tab_sel = p.n_sel;
+    r.tab_lm = a.has_lm;
+  }
+  hipLaunchKernelGGL(k_resident_init, dim3(512), dim3(256), 0, s, a);
+  const bool plain = c.n_durations == 0 && !b.has_lm && b.algo == RNNT_ALSD;
+  ResKernel k = pick_kernel(c, b.K, plain);
+  e = hipFuncSetAttribute(reinterpret_cast<const void *>(k), hipFuncAttributeMaxDynamicSharedMemorySize, (int)p.lds);
+  if (e != hipSuccess) return e;
+  hipLaunchKernelGGL(k, dim3(p.n_groups * p.n_blocks), dim3(kResThreads), p.lds, s, a);
+  return hipGetLastError();
+}
+
+}  // namespace rb

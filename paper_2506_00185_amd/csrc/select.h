@@ -1,0 +1,962 @@
+// Selection of a beam-search step (top Beam of an utterance's candidates, tree write, hypothesis state, recombination,
+// end-of-utterance detection) as device functions, for the kernels of the per-step launches and for the resident loop.
+#pragma once
+#include "device_utils.h"
+
+namespace rb {
+
+// ---------------------------------------------------------------------------
+// Selection, tree write, state update and recombination: one block per utterance.
+// ---------------------------------------------------------------------------
+struct SelectArgs {
+  // hypothesis state, [M] each (ctx: [M][kCtxMax])
+  double *score;
+  int *t, *sym, *len, *last;
+  uint32_t *hash;
+  int *ctx;
+  const int *lengths;
+  // candidate lists from the joint (k_step_main, k_row_select) or k_inject
+  const float *p_max, *p_sum;
+  const uint64_t *p_cand;  // [M, K, n_chunks] packed (key, token): entry j of every chunk's list (best first) side by
+                           // side, so that lanes that take neighbouring chunks read neighbouring words
+  const float *zs;
+  int n_chunks;
+  int use_ctx;     // 1: the token history of each hypothesis is kept (stateless prediction network, LM)
+  int normalized;  // 1: keys are log-probabilities already (injected mode)
+  // configuration
+  int B, K, V, ND;
+  int dur[8];
+  uint64_t dur_bytes;   // the same, one byte each (durations are at most 255): one scalar register pair instead of eight
+  int algo, max_sym;
+  float gamma;
+  int has_lm;
+  int lm_rule3;         // 1: Eq. (3) (LM on tokens only, blank as it is); 0: Eq. (4)
+  int lm_early;         // 1: early pruning: keys carry no LM term; the kept candidates are charged it here
+  int prefix;           // 1: AES++ maximum-length prefix search (ranking credit, see select_utterance)
+  const float *lm_rows; // [M, V] natural-log LM scores (read for the kept candidates under early pruning)
+  float lambda;
+  // what the prediction step has to do for each new slot
+  int *src_row, *tok;
+  // tree [B][S_max][K]
+  int *tree_parent, *tree_token, *tree_merged;
+  int S_max;
+  // loop control
+  const int *step_base;
+  int step_off;
+  int *finished, *utt_steps, *n_finished, *done;
+  volatile int *h_done;  // pinned host word, set when every utterance has finished
+};
+
+// Where the selection finds the candidate lists of its utterance: the arrays of SelectArgs (rows indexed by
+// hypothesis), or arrays in LDS that hold the rows of this utterance only (row0 = its first hypothesis).
+struct CandView {
+  const uint64_t *cand;
+  const float *pmax, *psum, *zs;
+  int row0;
+};
+__device__ __forceinline__ CandView cand_view(const SelectArgs &a) { return CandView{a.p_cand, a.p_max, a.p_sum, a.zs, 0}; }
+
+__device__ __forceinline__ float logaddexp_f(float a, float b) {
+  const float m = fmaxf(a, b), d = fminf(a, b) - m;  // d <= 0
+  return d > -INFINITY ? m + log1pf(expf(d)) : m;
+}
+
+// LDS scratch of one wave while it handles one utterance
+template <int CAND, int STAIR = 64>
+struct SelectScratchT {
+  static constexpr int kStair = STAIR;  // candidates the staircase form of the ranking can hold (64 per lane pass)
+  double score[kMaxBeam];
+  double rc_val[CAND];
+  double rc_key[CAND];  // early pruning only: what the candidates are ranked by
+  double sel_val[kMaxBeam];
+  double n_score[kMaxBeam];
+  double delta[kMaxBeam];  // prefix search: what the ranking adds to every candidate of the hypothesis
+  int t[kMaxBeam], sym[kMaxBeam], len[kMaxBeam], last[kMaxBeam], kind[kMaxBeam];
+  uint32_t hash[kMaxBeam];
+  int ctx[kMaxBeam][kCtxMax];
+  int advt[kMaxBeam], advb[kMaxBeam];
+  int rc_flat[CAND];
+  int sel_flat[kMaxBeam];
+  // staircase form of the ranking (beams 8 .. 10): per hypothesis the place of blank in its sorted list, its head,
+  // the order of the lists by their heads; then the K (K + 1) / 2 candidates that can still be among the Beam best
+  double head_val[kMaxBeam], st_key[STAIR + 8];
+  int head_flat[kMaxBeam], pos_blank[kMaxBeam], ord[kMaxBeam], st_flat[STAIR + 8], st_src[STAIR];
+  int n_t[kMaxBeam], n_sym[kMaxBeam], n_len[kMaxBeam], n_last[kMaxBeam], n_live[kMaxBeam];
+  uint32_t n_hash[kMaxBeam];
+};
+// K (K + 1) candidates per utterance: K tokens and blank / stay of every hypothesis
+typedef SelectScratchT<kMaxBeam * (kMaxBeam + 1)> SelectScratch;
+// the same with room for the staircase of beams up to 16 (16 * 17 / 2 = 136 candidates, three per lane)
+typedef SelectScratchT<kMaxBeam * (kMaxBeam + 1), 192> SelectScratchWide;
+// TDT with every (symbol, duration) pair as a candidate: K (K + 1) ND of them, for beams up to 8
+constexpr int kPairsMaxBeam = 8;
+typedef SelectScratchT<kPairsMaxBeam * (kPairsMaxBeam + 1) * 8> SelectScratchPairs;
+
+// the lanes of one wave see each other's LDS writes after this (they run in lockstep; this
+// only stops the compiler and the memory pipeline from re-ordering)
+__device__ __forceinline__ void wave_sync() {
+  __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+  __builtin_amdgcn_wave_barrier();
+}
+
+// candidate order inside an utterance: (hypothesis k, token v) -> k * 2^20 + v, the same order as
+// k * (V + 1) + v for V < 2^20, without a division on the way back
+constexpr int kFlatShift = 20;
+
+// x mod (2^31 - 1) for x < 2^62
+__device__ __forceinline__ uint32_t mod_mersenne31(uint64_t x) {
+  uint64_t y = (x & kHashMod) + (x >> 31);
+  y = (y & kHashMod) + (y >> 31);
+  return (uint32_t)(y >= kHashMod ? y - kHashMod : y);
+}
+
+// Rank of the calling lane's candidate (value mv, index mf) among the cnt candidates in LDS: the number of those that
+// come before it.  Every lane reads all candidates (the same address in all lanes: broadcasts, many in flight), eight
+// at a time; the arrays hold eight entries beyond cnt that come before nothing.  First on the values alone (one
+// comparison per candidate): when no two finite values are equal, which the sum of the counts tells, that is the
+// rank; otherwise once more in the full order (value, then index).
+__device__ __forceinline__ int rank_by_counting(const double *keys, const int *flats, int cnt, double mv, int mf) {
+  int ge = 0;  // candidates not below mine, myself included
+  for (int c0 = 0; c0 < cnt; c0 += 8) {
+    double cv[8];
+#pragma unroll
+    for (int q = 0; q < 8; ++q) cv[q] = keys[c0 + q];
+#pragma unroll
+    for (int q = 0; q < 8; ++q) ge += (int)(cv[q] >= mv);
+  }
+  const bool finite = mv > -INFINITY;
+  const int F = __popcll(__ballot(finite));
+  if (wave_sum_i(finite ? ge : 0) == F * (F + 1) / 2) return ge - 1;
+  int rank = 0;
+  for (int c0 = 0; c0 < cnt; c0 += 8) {
+    double cv[8];
+    int cf[8];
+#pragma unroll
+    for (int q = 0; q < 8; ++q) {
+      cv[q] = keys[c0 + q];
+      cf[q] = flats[c0 + q];
+    }
+#pragma unroll
+    for (int q = 0; q < 8; ++q) rank += comes_before_count(cv[q], cf[q], mv, mf);
+  }
+  return rank;
+}
+
+// The same for OWN candidates per lane (lane, lane + 64, ..): one pass over the candidates serves them all.
+template <int OWN>
+__device__ __forceinline__ void rank_by_counting_n(const double *keys, const int *flats, int cnt, const double (&mv)[OWN],
+                                                   const int (&mf)[OWN], int (&rank)[OWN]) {
+  int ge[OWN];
+#pragma unroll
+  for (int o = 0; o < OWN; ++o) ge[o] = 0;
+  for (int c0 = 0; c0 < cnt; c0 += 8) {
+    double cv[8];
+#pragma unroll
+    for (int q = 0; q < 8; ++q) cv[q] = keys[c0 + q];
+#pragma unroll
+    for (int q = 0; q < 8; ++q)
+#pragma unroll
+      for (int o = 0; o < OWN; ++o) ge[o] += (int)(cv[q] >= mv[o]);
+  }
+  int F = 0, tot = 0;
+#pragma unroll
+  for (int o = 0; o < OWN; ++o) {
+    const bool finite = mv[o] > -INFINITY;
+    F += __popcll(__ballot(finite));
+    tot += finite ? ge[o] : 0;
+  }
+  if (wave_sum_i(tot) == F * (F + 1) / 2) {
+#pragma unroll
+    for (int o = 0; o < OWN; ++o) rank[o] = ge[o] - 1;
+    return;
+  }
+#pragma unroll
+  for (int o = 0; o < OWN; ++o) rank[o] = 0;
+  for (int c0 = 0; c0 < cnt; c0 += 8) {
+    double cv[8];
+    int cf[8];
+#pragma unroll
+    for (int q = 0; q < 8; ++q) {
+      cv[q] = keys[c0 + q];
+      cf[q] = flats[c0 + q];
+    }
+#pragma unroll
+    for (int q = 0; q < 8; ++q)
+#pragma unroll
+      for (int o = 0; o < OWN; ++o) rank[o] += comes_before_count(cv[q], cf[q], mv[o], mf[o]);
+  }
+}
+
+// How the resident loop (kernels_resident.h) calls the selection: the hypotheses' state stays in the scratch from one step
+// to the next (score .. hash, ctx), and what the step decided for each slot leaves as one word (slot_word) that every
+// block of the group waits for.
+struct ResidentSelect {
+  uint64_t *words;      // of the utterance's K slots, written with device-coherent stores
+  int slot0;            // the utterance's first slot in its group
+  int step, T_b;
+  const float *lm;      // [K][V] LM scores (log10) of the slots in LDS (early pruning)
+  int finished;         // out: the utterance's last step is done
+};
+// step tag (16 bits, step + 1) | utterance finished (1) | parent slot in the group (6) | token + 1 (21) | frame (20)
+constexpr int kWordMaxFrames = 1 << 20;
+__device__ __forceinline__ uint64_t slot_word(int step, int fin, int src, int tok, int t) {
+  return (uint64_t)((step + 1) & 0xffff) | (uint64_t)fin << 16 | (uint64_t)src << 17 | (uint64_t)(tok + 1) << 23 |
+         (uint64_t)t << 44;
+}
+__device__ __forceinline__ int word_tag(uint64_t w) { return (int)(w & 0xffff); }
+__device__ __forceinline__ int word_finished(uint64_t w) { return (int)(w >> 16) & 1; }
+__device__ __forceinline__ int word_src(uint64_t w) { return (int)(w >> 17) & 63; }
+__device__ __forceinline__ int word_tok(uint64_t w) { return ((int)(w >> 23) & 0x1fffff) - 1; }
+__device__ __forceinline__ int word_frame(uint64_t w) { return (int)(w >> 44); }
+constexpr float kLn10 = 2.302585092994046f;
+
+// One beam-search step of utterance b by one wave: the K best tokens and blank of every
+// hypothesis (LPR lanes per hypothesis, all hypotheses at once), the Beam best of those,
+// expansion, tree write, recombination, end-of-utterance detection.
+// NCH > 0: a lane keeps the lists of NCH chunks in registers (n_chunks <= LPR * NCH, K <= KMAX) and
+// the K best of the hypothesis come out of a K-way merge of list heads; NCH == 0: the lists are
+// scanned in memory at every round instead (any size).
+// MULTI: the beam may be wider than the 64 / LPR hypotheses handled at once; the per-hypothesis part then
+// runs in several passes.
+// PAIRS (TDT): every (symbol, duration) pair of a hypothesis is a candidate of its own (blank only with
+// durations >= 1) instead of one duration per symbol; candidate (k, j, d) sits at ((k (K + 1) + j) ND + d.
+// ONE: every hypothesis comes with exactly one list (n_chunks == 1, NCH == 1), known at compile time: the merge
+// of list heads and its registers drop out.
+// RES: called by the resident loop (see ResidentSelect).
+template <int LPR, int NCH, int KMAX, bool MULTI = false, bool PAIRS = false, class Scratch = SelectScratch,
+          bool ONE = false, int PLAIN = 0, bool DYNDUR = false, bool RES = false>
+__device__ __forceinline__ void select_utterance(const SelectArgs &a, int b, Scratch &s, const CandView cv,
+                                                 ResidentSelect *rs = nullptr) {
+  const int K = a.K, V = a.V, lane = threadIdx.x & 63;
+  // PLAIN (the caller has checked): 1 = ALSD++, 2 = AES++ without prune margin and prefix search, both without
+  // durations and LM: the code of the other cases drops out
+  const int a_ND = PLAIN ? 0 : a.ND;
+  const int a_has_lm = PLAIN ? 0 : a.has_lm, a_lm_early = PLAIN ? 0 : a.lm_early, a_lm_rule3 = PLAIN ? 0 : a.lm_rule3;
+  const int a_prefix = PLAIN ? 0 : a.prefix;
+  const float a_gamma = PLAIN ? INFINITY : a.gamma;
+  const int a_algo = PLAIN ? PLAIN - 1 : a.algo;
+  const int m_base = b * K;
+  const int nz = 1 + a_ND;
+  // ---- every load of the prologue is requested before anything waits on one of them
+  const int fin = RES ? 0 : load_agent(a.finished + b);  // (a wave-uniform word that changes: never through the scalar cache)
+  const int S = RES ? rs->step : *a.step_base + a.step_off;
+  const int T_b = RES ? rs->T_b : a.lengths[b];
+  double my_score = -INFINITY;
+  int my_t = 0, my_sym = 0, my_len = 0, my_last = -1;
+  uint32_t my_hash = 0;
+  if (lane < K) {
+    if constexpr (RES) {
+      my_score = s.score[lane];
+      my_t = s.t[lane];
+    } else {
+      const int m = m_base + lane;
+      my_score = a.score[m];
+      my_t = a.t[m];
+      my_sym = a.sym[m];
+      my_len = a.len[m];
+      my_last = a.last[m];
+      my_hash = a.hash[m];
+    }
+  }
+  // LPR lanes per hypothesis, 64 / LPR hypotheses at once; a beam wider than that takes several passes
+  // over the per-hypothesis part (lists -> K best tokens -> candidate scores in LDS)
+  constexpr int kRowsPerPass = 64 / LPR;
+  const int e = lane % LPR;  // position inside the lane group
+  const int ncand = a.n_chunks * K;
+  int rk = 0;                // hypothesis of this lane in the current pass
+  bool row_ok = false;
+  const uint64_t *cands = nullptr;
+  const float *pmax = nullptr, *psum = nullptr;
+  uint64_t list[NCH > 0 ? NCH : 1][KMAX];
+  float pm[NCH > 0 ? NCH : 1], ps[NCH > 0 ? NCH : 1];
+  float zb = 0.f;
+  float dl[8];
+  // a single chunk's list IS the K best of the hypothesis: lane e takes entries e, e + LPR, .. as they are
+  constexpr int kMine = (KMAX + LPR - 1) / LPR;
+  const bool one_list = ONE || (NCH == 1 && a.n_chunks == 1);
+  uint64_t direct[kMine];
+  auto load_rows = [&](int r0) {
+    rk = r0 + lane / LPR;
+    row_ok = rk < K;
+    const int krow = row_ok ? rk : 0;
+    const int crow = m_base - cv.row0 + krow;
+    cands = cv.cand + (size_t)crow * ncand;
+    pmax = cv.pmax + (size_t)crow * a.n_chunks;
+    psum = cv.psum + (size_t)crow * a.n_chunks;
+    const float *zsr = cv.zs + (size_t)crow * nz;
+    // (every load is unconditional, from a clamped address, and what does not apply is replaced afterwards: a load
+    // under a condition of its own costs a branch each)
+    if constexpr (NCH > 0) {
+#pragma unroll
+      for (int q = 0; q < NCH; ++q) {
+        const int ch = e + LPR * q;
+        const bool ok = row_ok && ch < a.n_chunks;
+        const int chs = min(ch, a.n_chunks - 1);  // (lanes without a chunk repeat their group's last address: no extra line)
+        if constexpr (!ONE) {
+          if (!one_list) {
+#pragma unroll
+            for (int j = 0; j < KMAX; ++j) {
+              const uint64_t x = load_agent(cands + (j < K ? j : 0) * a.n_chunks + chs);
+              list[q][j] = (ok && j < K) ? x : no_cand();
+            }
+          }
+        }
+        const float xm = load_agent(pmax + chs), xs = load_agent(psum + chs);
+        pm[q] = (ok && !a.normalized) ? xm : -INFINITY;
+        ps[q] = (ok && !a.normalized) ? xs : 0.f;
+      }
+      if (one_list) {
+#pragma unroll
+        for (int i = 0; i < kMine; ++i) {
+          const int j = e + LPR * i;
+          const uint64_t x = load_agent(cands + (j < K ? j : 0));
+          direct[i] = (row_ok && j < K) ? x : no_cand();
+        }
+      }
+    }
+    zb = load_agent(zsr);
+    if (a_ND > 0) {
+#pragma unroll
+      for (int d = 0; d < 8; ++d) dl[d] = load_agent(zsr + 1 + (d < a_ND ? d : 0));
+    }
+  };
+  auto process_rows = [&]() {
+    // ---- K rounds of "best remaining candidate" in every lane group at once.
+    // Lane e keeps the winners of rounds e, e + LPR, ... (at most KMAX / LPR + 1 of them).
+    uint64_t mine[kMine];
+#pragma unroll
+    for (int i = 0; i < kMine; ++i) mine[i] = no_cand();
+    if (one_list) {
+#pragma unroll
+      for (int i = 0; i < kMine; ++i) mine[i] = direct[i];
+    } else if constexpr (ONE) {
+    } else if constexpr (NCH > 0) {
+#pragma unroll
+      for (int j = 0; j < KMAX; ++j) {
+        if (j < K) {
+          uint64_t best = list[0][0];
+#pragma unroll
+          for (int q = 1; q < NCH; ++q) best = list[q][0] > best ? list[q][0] : best;
+          best = group_max_u64<LPR>(best);
+#pragma unroll
+          for (int q = 0; q < NCH; ++q)
+            if (list[q][0] == best) {  // the winner's list moves up (real candidates are unique)
+#pragma unroll
+              for (int x = 0; x + 1 < KMAX; ++x) list[q][x] = list[q][x + 1];
+              list[q][KMAX - 1] = no_cand();
+            }
+          if (e == j % LPR) mine[j / LPR] = best;
+        }
+      }
+    } else {
+      uint64_t last = ~0ull;
+      for (int j = 0; j < K; ++j) {
+        uint64_t best = no_cand();
+        if (row_ok)
+          for (int c = e; c < ncand; c += LPR) {
+            const uint64_t v = load_agent(cands + c);
+            if (v < last && v > best) best = v;
+          }
+        best = group_max_u64<LPR>(best);
+#pragma unroll
+        for (int i = 0; i < kMine; ++i)
+          if (e == j % LPR && i == j / LPR) mine[i] = best;
+        last = best > no_cand() ? best : no_cand() + 1;  // nothing below "no candidate" is eligible again
+      }
+    }
+    // ---- soft-max statistics of the hypothesis (float transcendental math, scores accumulate in double)
+    float lse_all = 0.f, lse_nb = 0.f, max_nb = -INFINITY;
+    if (!a.normalized) {
+      float st_mx = -INFINITY, st_sum = 0.f;
+      if constexpr (NCH > 0) {
+#pragma unroll
+        for (int q = 0; q < NCH; ++q) st_mx = fmaxf(st_mx, pm[q]);
+        st_mx = group_max<LPR>(st_mx);
+#pragma unroll
+        for (int q = 0; q < NCH; ++q)
+          if (pm[q] > -INFINITY) st_sum += ps[q] * __expf(pm[q] - st_mx);
+      } else {
+        if (row_ok)
+          for (int c = e; c < a.n_chunks; c += LPR) st_mx = fmaxf(st_mx, load_agent(pmax + c));
+        st_mx = group_max<LPR>(st_mx);
+        if (row_ok)
+          for (int c = e; c < a.n_chunks; c += LPR) {
+            const float p = load_agent(pmax + c);
+            if (p > -INFINITY) st_sum += load_agent(psum + c) * __expf(p - st_mx);
+          }
+      }
+      st_sum = group_sum<LPR>(st_sum);
+      lse_nb = st_mx + __logf(st_sum);
+      const float hi = fmaxf(lse_nb, zb), lo = fminf(lse_nb, zb);
+      lse_all = hi + __logf(1.f + __expf(lo - hi));
+      max_nb = st_mx;
+    } else {
+      // keys are log-probabilities already; the best token of the row is round 0's winner, the largest
+      // of the winners spread over the group's lanes
+      max_nb = cand_key(group_max_u64<LPR>(mine[0]));
+    }
+    const double logp_b = (double)zb - (double)lse_all;
+    const double nb = (double)lse_nb - (double)lse_all;
+    const double maxlogp = (double)fmaxf(max_nb, zb) - (double)lse_all;
+    // TDT durations
+    double x_tok = 0.0, x_blank = 0.0;
+    int adv_tok = 0, adv_blank = 1;
+    if (a_ND > 0) {
+      if constexpr (DYNDUR) {
+        // The form with indices computed at run time (every access a dependent load: 2.4 us at five durations).  Kept
+        // for the main kernel's instantiation for 256 slots and more, where the selection is not what the launch
+        // waits for and the kernel as a whole came out 0.9 us SLOWER with the form below (its joint blocks end 0.8 us
+        // later: the compiler's placement of the whole kernel, not this block's own time).
+        if (!a.normalized) {
+          float dmx = -INFINITY, sm = 0.f;
+          for (int d = 0; d < a_ND; ++d) dmx = fmaxf(dmx, dl[d]);
+          for (int d = 0; d < a_ND; ++d) sm += __expf(dl[d] - dmx);
+          const float l = dmx + __logf(sm);
+          for (int d = 0; d < a_ND; ++d) dl[d] -= l;
+        }
+        int best = -1, best_b = -1;
+        for (int d = 0; d < a_ND; ++d) {
+          if (best < 0 || dl[d] > dl[best]) best = d;
+          if (a.dur[d] >= 1 && (best_b < 0 || dl[d] > dl[best_b])) best_b = d;
+        }
+        if constexpr (!PAIRS) {
+          x_tok = (double)dl[best];
+          x_blank = (double)dl[best_b];
+          adv_tok = a.dur[best];
+          adv_blank = a.dur[best_b];
+        }
+      } else {
+        // (every index into dl and a.dur below is a compile-time constant: an index computed at run time turns each
+        // access into a dependent load from memory, 2.4 us for this block at five durations)
+        if (!a.normalized) {
+          float dmx = -INFINITY, sm = 0.f;
+#pragma unroll
+          for (int d = 0; d < 8; ++d)
+            if (d < a_ND) dmx = fmaxf(dmx, dl[d]);
+#pragma unroll
+          for (int d = 0; d < 8; ++d)
+            if (d < a_ND) sm += __expf(dl[d] - dmx);
+          const float l = dmx + __logf(sm);
+#pragma unroll
+          for (int d = 0; d < 8; ++d)
+            if (d < a_ND) dl[d] -= l;
+        }
+        // the most likely duration (the first of equal ones), and the most likely one that advances
+        bool have = false, have_b = false;
+        float best_v = 0.f, best_bv = 0.f;
+        int best_adv = 0, best_badv = 1;
+#pragma unroll
+        for (int d = 0; d < 8; ++d)
+          if (d < a_ND) {
+            const int du = (int)((a.dur_bytes >> (8 * d)) & 0xff);
+            if (!have || dl[d] > best_v) {
+              have = true;
+              best_v = dl[d];
+              best_adv = du;
+            }
+            if (du >= 1 && (!have_b || dl[d] > best_bv)) {
+              have_b = true;
+              best_bv = dl[d];
+              best_badv = du;
+            }
+          }
+        if constexpr (!PAIRS) {  // one duration per candidate: the most likely one (for blank: that advances)
+          x_tok = (double)best_v;
+          x_blank = (double)best_bv;
+          adv_tok = best_adv;
+          adv_blank = best_badv;
+        }
+      }
+    }
+    wave_sync();  // s.kind / s.score / s.sym are needed per row from here on
+    // candidate c of the utterance is rc[k * (K + 1) + j]: j < K tokens, j == K blank / stay
+    if (row_ok) {
+      const int kind = s.kind[rk];
+      const bool forced = s.sym[rk] >= a.max_sym;
+      const bool use_gamma = a_algo == 1 && a_gamma < INFINITY;
+      const double thr = maxlogp - (double)a_gamma;
+      const double sc = s.score[rk];
+      const int flat0 = rk << kFlatShift;
+      // Eq. (4): tokens get lambda (ln(1 - p_blank) + lm), blank (1 + lambda) ln p_blank; Eq. (3): tokens lambda lm,
+      // blank unchanged.  Late pruning: lambda * lm is in the key already; early: added here, after the ranking value.
+      const double lm_const = (a_has_lm && !a_lm_rule3) ? (double)a.lambda * nb : 0.0;
+      const double tok_base = x_tok - (double)lse_all;
+      const bool early = a_lm_early != 0;
+      // where candidate (hypothesis rk, j-th symbol[, duration d]) goes and how it is numbered for the tie-break
+      const int nd = PAIRS ? a_ND : 1;
+      auto put = [&](int j, int token, double key, double val) {
+        if constexpr (PAIRS) {
+          for (int d = 0; d < nd; ++d) {
+            // blank must advance by at least one frame; a waiting hypothesis is the single candidate d = 0
+            const bool ok = key > -INFINITY && (kind == 1 ? d == 0 : (token < V || a.dur[d] >= 1));
+            const double x = kind == 1 ? 0.0 : (double)dl[d];
+            const int c = (rk * (K + 1) + j) * nd + d;
+            s.rc_val[c] = ok ? val + x : -INFINITY;
+            if (early) s.rc_key[c] = ok ? key + x : -INFINITY;
+            s.rc_flat[c] = ((flat0 + token) << 3) | d;
+          }
+        } else {
+          const int c = rk * (K + 1) + j;
+          s.rc_val[c] = val;
+          if (early) s.rc_key[c] = key;
+          s.rc_flat[c] = flat0 + token;
+        }
+      };
+#pragma unroll
+      for (int i = 0; i < kMine; ++i) {
+        const int j = e + LPR * i;
+        if (j < K) {
+          const float wk = cand_key(mine[i]);
+          const int wi = cand_idx(mine[i]);
+          double val = -INFINITY, key = -INFINITY;
+          if (kind == 2 && wk > -INFINITY && !forced) {
+            const double lp = (double)wk - (double)lse_all;  // pre-LM log-probability when no LM is in the key
+            if (!(use_gamma && lp < thr)) {
+              key = sc + (double)wk + tok_base;
+              val = key + lm_const;
+              if (early)
+                val += (double)a.lambda * (double)(RES ? rs->lm[rk * V + wi] * kLn10 : a.lm_rows[(size_t)(m_base + rk) * V + wi]);
+            }
+          }
+          put(j, wi < V ? wi : V - 1, key, val);
+        }
+      }
+      if (e == LPR - 1) {  // blank / stay: the group's last lane (least loaded with winners)
+        double val = -INFINITY, key = -INFINITY;
+        if (kind == 2) {
+          double bl = logp_b;
+          if (use_gamma && logp_b < thr && !forced) bl = -INFINITY;
+          key = sc + bl + x_blank;
+          val = (a_has_lm && !a_lm_rule3 && bl > -INFINITY) ? key + (double)a.lambda * bl : key;
+          s.advt[rk] = adv_tok;
+          s.advb[rk] = adv_blank;
+        } else if (kind == 1) {
+          val = key = sc;  // a waiting or finished hypothesis stays as it is
+        }
+        put(K, V, key, val);
+      }
+    }
+    wave_sync();
+  };
+  auto per_utterance = [&]() -> bool {  // false: the utterance had finished before this step
+    if (!RES && a.use_ctx)
+      for (int i = lane; i < K * kCtxMax; i += 64) s.ctx[i / kCtxMax][i % kCtxMax] = a.ctx[m_base * kCtxMax + i];
+    if (fin) {  // a finished utterance is frozen; its slots tell the prediction step to copy
+      if (lane < K) {
+        store_through(a.src_row + m_base + lane, m_base + lane);
+        store_through(a.tok + m_base + lane, -1);
+      }
+      return false;
+    }
+    if (lane < K) {
+      if constexpr (!RES) {
+        s.score[lane] = my_score;
+        s.t[lane] = my_t;
+        s.sym[lane] = my_sym;
+        s.len[lane] = my_len;
+        s.last[lane] = my_last;
+        s.hash[lane] = my_hash;
+      }
+      s.sel_val[lane] = -INFINITY;
+      s.sel_flat[lane] = -1;
+    }
+    // frame of the earliest unfinished hypothesis (lanes >= K hold neutral values)
+    const bool my_live = my_score > -INFINITY;
+    int t_cur = group_min_i<16>((my_live && my_t < T_b) ? my_t : T_b);
+    t_cur = __builtin_amdgcn_readlane(t_cur, 0);
+    if (lane < K) s.kind[lane] = my_live ? ((my_t < T_b && (a_algo == 0 || my_t == t_cur)) ? 2 : 1) : 0;
+    return true;
+  };
+  if constexpr (MULTI) {
+    for (int r0 = 0; r0 < K; r0 += kRowsPerPass) {
+      load_rows(r0);
+      if (r0 == 0 && !per_utterance()) return;
+      process_rows();
+    }
+  } else {
+    load_rows(0);
+    if (!per_utterance()) return;
+    process_rows();
+  }
+
+  const int n = K * (K + 1) * (PAIRS ? a_ND : 1);
+  // ---- AES++, maximum-length prefix search (Sec. 2.2, "AES").  Hypotheses i and j expanded at this step in the
+  // same frame with transcript(i) = transcript(j) + v: the step's own expansion (j, v), if it is among j's Beam best
+  // tokens and stays in the frame, is credited to i for the RANKING of i's candidates; the new scores stay as they
+  // are (the expansion competes on its own and meets i in the recombination; adding it to i's score too would count
+  // that alignment twice).  Pairs are found through Eq. (1), like equal transcripts in the recombination.
+  const bool prefix = !PAIRS && a_prefix && a_algo == 1 && !a_lm_early;
+  if constexpr (!PAIRS) {
+    if (prefix) {
+      if (lane < K) {
+        const int i = lane;
+        double add = -INFINITY;
+        if (s.kind[i] == 2 && s.len[i] >= 1) {
+          const uint32_t hi = s.hash[i];
+          const int li = s.len[i], la = s.last[i], ti = s.t[i];
+          for (int j = 0; j < K; ++j) {
+            if (j == i || s.kind[j] != 2 || s.t[j] != ti || s.len[j] + 1 != li) continue;
+            if (s.advt[j] != 0) continue;
+            if (mod_mersenne31((uint64_t)s.hash[j] * kHashBase + (uint64_t)(la + 1)) != hi) continue;
+            for (int c = 0; c < K; ++c) {  // j's Beam best tokens: is v among them, with a finite score?
+              const int idx = j * (K + 1) + c;
+              if (s.rc_flat[idx] == (j << kFlatShift) + la && s.rc_val[idx] > -INFINITY) add = logaddexp_d(add, s.rc_val[idx]);
+            }
+          }
+        }
+        s.delta[i] = add > -INFINITY ? logaddexp_d(s.score[i], add) - s.score[i] : 0.0;
+      }
+      wave_sync();
+      for (int c = lane; c < n; c += 64) s.rc_key[c] = s.rc_val[c] + s.delta[c / (K + 1)];
+      wave_sync();
+    }
+  }
+  // ---- the Beam best of all K * (K + 1) candidates, by (ranking value desc, (k, v) asc); the ranking
+  // value is the new score itself except under early pruning and with a prefix credit
+  double *rank_of = (a_lm_early || prefix) ? s.rc_key : s.rc_val;
+  // candidates a lane may own in the counting form below
+  constexpr int kOwn = 1;  // (measured: from 65 candidates up the rounds below are faster than two owned candidates)
+  if (n <= 64 * kOwn) {
+    // Each lane counts, for each candidate it owns (lane, lane + 64, ..), how many candidates come before it; that
+    // count is the candidate's new slot.  (Every lane reads all n candidates back from LDS, the same address in all
+    // lanes: such reads are broadcasts and, unlike lane reads into scalar registers, can be requested many at a time.)
+    double mv[kOwn];
+    int mf[kOwn], rank[kOwn];
+#pragma unroll
+    for (int q = 0; q < kOwn; ++q) {
+      const int c = lane + 64 * q;
+      mv[q] = c < n ? rank_of[c] : -INFINITY;
+      mf[q] = c < n ? s.rc_flat[c] : 0x7fffffff;
+      rank[q] = 0;
+    }
+    // the loop below reads in eights: the (up to seven) places after the last candidate hold one that comes before
+    // nothing, so that no comparison needs a bound check (the arrays have room beyond n; nothing else uses it)
+    if (lane < 8) {
+      rank_of[n + lane] = -INFINITY;
+      s.rc_flat[n + lane] = 0x7fffffff;
+    }
+    wave_sync();
+    rank[0] = rank_by_counting(rank_of, s.rc_flat, n, mv[0], mf[0]);
+#pragma unroll
+    for (int q = 0; q < kOwn; ++q)
+      if (mv[q] > -INFINITY && rank[q] < K) {
+        s.sel_val[rank[q]] = s.rc_val[lane + 64 * q];
+        s.sel_flat[rank[q]] = mf[q];
+      }
+  } else if (!PAIRS && KMAX > 7 && K * (K + 1) / 2 <= Scratch::kStair) {
+    // More than 64 candidates.  The candidates of one hypothesis are a sorted list: its tokens come
+    // best first (the ranking value grows with the key) and blank / stay has its place among them.  With the lists
+    // ordered by their heads, the entry at place p of the list of order o has at least p + o candidates ahead of it,
+    // so only the K (K + 1) / 2 entries with p + o < K can be among the Beam best, and an entry's rank among those
+    // is its rank among all whenever that is below K.  One to three per lane, and the counting form applies.
+    if (lane < K) {
+      const int base = lane * (K + 1);
+      const double bv = rank_of[base + K];
+      int pos = 0;
+#pragma unroll
+      for (int j = 0; j < KMAX; ++j) {  // (reads past the K tokens stay inside the array and are not counted)
+        const double tv = rank_of[base + j];
+        pos += (int)(j < K) & (int)(tv > -INFINITY) & (int)(tv >= bv);  // (equal values: the token comes first)
+      }
+      s.pos_blank[lane] = pos;
+      s.head_val[lane] = pos == 0 ? bv : rank_of[base];
+      s.head_flat[lane] = pos == 0 ? s.rc_flat[base + K] : s.rc_flat[base];
+    }
+    wave_sync();
+    if (lane < K) {
+      const double hv = s.head_val[lane];
+      const int hf = s.head_flat[lane];
+      int o = 0;
+#pragma unroll
+      for (int r = 0; r < KMAX; ++r) o += (int)(r < K) & comes_before_count(s.head_val[r], s.head_flat[r], hv, hf);
+      s.ord[lane] = o;
+    }
+    wave_sync();
+    const unsigned inv = 65536u / (unsigned)(K + 1) + 1u;  // c / (K + 1) for c < 272 without a division per lane
+    for (int c = lane; c < n; c += 64) {
+      const int r = (int)(((unsigned)c * inv) >> 16), j = c - r * (K + 1);
+      const int pb = s.pos_blank[r], o = s.ord[r];
+      const int p = j == K ? pb : (j < pb ? j : j + 1);
+      if (p + o < K) {
+        const int slot = o * K - o * (o - 1) / 2 + p;
+        s.st_key[slot] = rank_of[c];
+        s.st_flat[slot] = s.rc_flat[c];
+        s.st_src[slot] = c;
+      }
+    }
+    const int nn = K * (K + 1) / 2;
+    if (lane < 8) {  // (as above: the counting loop reads in eights)
+      s.st_key[nn + lane] = -INFINITY;
+      s.st_flat[nn + lane] = 0x7fffffff;
+    }
+    wave_sync();
+    // (candidates a lane owns: as many as the form's widest beam needs and the scratch holds)
+    constexpr int kNeed = (KMAX * (KMAX + 1) / 2 + 63) / 64, kHave = Scratch::kStair / 64;
+    constexpr int OWN = kNeed < kHave ? kNeed : kHave;
+    double mv[OWN];
+    int mf[OWN], rank[OWN];
+#pragma unroll
+    for (int o = 0; o < OWN; ++o) {
+      const int slot = lane + 64 * o;
+      mv[o] = slot < nn ? s.st_key[slot] : -INFINITY;
+      mf[o] = slot < nn ? s.st_flat[slot] : 0x7fffffff;
+      rank[o] = K;
+    }
+    if (OWN == 1 || nn <= 64) rank[0] = rank_by_counting(s.st_key, s.st_flat, nn, mv[0], mf[0]);
+    else rank_by_counting_n<OWN>(s.st_key, s.st_flat, nn, mv, mf, rank);
+#pragma unroll
+    for (int o = 0; o < OWN; ++o)
+      if (mv[o] > -INFINITY && rank[o] < K) {
+        s.sel_val[rank[o]] = s.rc_val[s.st_src[lane + 64 * o]];
+        s.sel_flat[rank[o]] = mf[o];
+      }
+  } else {
+    double last_v = INFINITY;
+    int last_i = -1;
+    for (int j = 0; j < K; ++j) {
+      double bv = -INFINITY;
+      int bi = 0x7fffffff;
+      for (int c = lane; c < n; c += 64) {
+        const double v = rank_of[c];
+        const int i = s.rc_flat[c];
+        const bool eligible = v > -INFINITY && (v < last_v || (v == last_v && i > last_i));
+        if (eligible && comes_before(v, i, bv, bi)) {
+          bv = v;
+          bi = i;
+        }
+      }
+      wave_best(bv, bi);
+      if (!(bv > -INFINITY)) break;
+      for (int c = lane; c < n; c += 64)  // the candidate's own lane hands over its score ((k, v) is unique)
+        if (s.rc_flat[c] == bi && rank_of[c] == bv) {
+          s.sel_val[j] = s.rc_val[c];
+          s.sel_flat[j] = bi;
+        }
+      last_v = bv;
+      last_i = bi;
+    }
+  }
+  wave_sync();
+
+  // ---- expansion into the new slots
+  int code = -3, parent = -1, appended = -1;
+  int ctx_new[kCtxMax];
+  if (lane < K) {
+    const int j = lane;
+    const double val = s.sel_val[j];
+#pragma unroll
+    for (int i = 0; i < kCtxMax; ++i) ctx_new[i] = -1;
+    if (!(val > -INFINITY)) {
+      s.n_live[j] = 0;
+      s.n_score[j] = -INFINITY;
+      s.n_t[j] = 0;
+      s.n_sym[j] = 0;
+      s.n_len[j] = 0;
+      s.n_last[j] = -1;
+      s.n_hash[j] = 0;
+    } else {
+      const int kv = PAIRS ? s.sel_flat[j] >> 3 : s.sel_flat[j];
+      const int k = kv >> kFlatShift, v = kv & ((1 << kFlatShift) - 1);
+      const int adv_b = PAIRS ? a.dur[s.sel_flat[j] & 7] : s.advb[k];  // frames the step advances: the pair's own
+      const int adv_t = PAIRS ? a.dur[s.sel_flat[j] & 7] : s.advt[k];  // duration, or the hypothesis' chosen one
+      parent = k;
+      int t = s.t[k], sym = s.sym[k], len = s.len[k], last = s.last[k];
+      uint32_t hash = s.hash[k];
+      if (a.use_ctx) {
+#pragma unroll
+        for (int i = 0; i < kCtxMax; ++i) ctx_new[i] = s.ctx[k][i];
+      }
+      if (s.kind[k] == 1) {
+        code = -2;
+      } else if (v == V) {
+        code = -1;
+        t += adv_b;
+        sym = 0;
+      } else {
+        code = v;
+        appended = v;
+        len += 1;
+        last = v;
+        hash = mod_mersenne31((uint64_t)hash * kHashBase + (uint64_t)(v + 1));
+        t += adv_t;
+        sym = adv_t == 0 ? sym + 1 : 0;
+#pragma unroll
+        for (int i = kCtxMax - 1; i > 0; --i) ctx_new[i] = ctx_new[i - 1];
+        ctx_new[0] = v;
+      }
+      if (t > T_b) t = T_b;
+      s.n_live[j] = 1;
+      s.n_score[j] = val;
+      s.n_t[j] = t;
+      s.n_sym[j] = sym;
+      s.n_len[j] = len;
+      s.n_last[j] = last;
+      s.n_hash[j] = hash;
+    }
+  }
+  wave_sync();
+
+  // ---- recombination: equal (hash, length, last token, frame, symbols in frame)
+  if (lane < K) {
+    const int j = lane;
+    int merged = -1;
+    double score = s.n_score[j];
+    bool live = s.n_live[j] != 0;
+    if (live) {
+      // which slots hold the same (hash, length, last token, frame, symbols in frame): all keys are read without
+      // branches in between, so that the LDS reads go out together
+      const uint32_t mh = s.n_hash[j];
+      const int ml = s.n_len[j], mla = s.n_last[j], mt = s.n_t[j], ms = s.n_sym[j];
+      // (the hashes first, read without branches in between; the other fields only of the few slots whose hash is equal)
+      uint32_t same_hash = 0;
+#pragma unroll
+      for (int i = 0; i < KMAX; ++i) {
+        const bool e = (i < K) & (s.n_live[i] != 0) & (s.n_hash[i] == mh);
+        same_hash |= (uint32_t)e << i;
+      }
+      uint32_t same = 1u << j;
+      for (uint32_t r = same_hash & ~(1u << j); r; r &= r - 1u) {
+        const int i = __builtin_ctz(r);
+        const bool e = (s.n_len[i] == ml) & (s.n_last[i] == mla) & (s.n_t[i] == mt) & (s.n_sym[i] == ms);
+        same |= (uint32_t)e << i;
+      }
+      const uint32_t lower = same & ((1u << j) - 1u);
+      if (lower == 0) {  // the lowest slot of its class keeps the log-sum, added up in slot order
+        merged = j;
+        for (uint32_t higher = same & ~((2u << j) - 1u); higher; higher &= higher - 1u)
+          score = logaddexp_d(score, s.n_score[__builtin_ctz(higher)]);
+      } else {
+        merged = __builtin_ctz(lower);
+        live = false;
+        score = -INFINITY;
+      }
+    }
+    const int m = m_base + j;
+    // finished when no surviving slot has frames left
+    const bool open = live && s.n_t[j] < T_b;
+    const unsigned long long any_open = __ballot(open);
+    const bool last_step = any_open == 0ull || S + 1 >= T_b * (a.max_sym + 1);
+    if constexpr (RES) {
+      store_agent(rs->words + j, slot_word(S, last_step ? 1 : 0, rs->slot0 + (parent >= 0 ? parent : j), appended, s.n_t[j]));
+      // (every read of the old state lies before the last wave_sync; the same words are re-read by this wave only)
+      s.score[j] = score;
+      s.t[j] = s.n_t[j];
+      s.sym[j] = s.n_sym[j];
+      s.len[j] = s.n_len[j];
+      s.last[j] = s.n_last[j];
+      s.hash[j] = s.n_hash[j];
+      if (a.use_ctx) {
+#pragma unroll
+        for (int i = 0; i < kCtxMax; ++i) s.ctx[j][i] = ctx_new[i];
+      }
+      if (last_step) {  // what the back-trace ranks and sizes the transcripts by
+        store_through(a.score + m, score);
+        store_through(a.len + m, s.n_len[j]);
+      }
+      rs->finished = last_step;
+    } else {
+    // written through (see store_through): nothing of a step's results waits in an L2 for the kernel's end
+    store_through(a.score + m, score);
+    store_through(a.t + m, s.n_t[j]);
+    store_through(a.sym + m, s.n_sym[j]);
+    store_through(a.len + m, s.n_len[j]);
+    store_through(a.last + m, s.n_last[j]);
+    store_through(a.hash + m, s.n_hash[j]);
+    if (a.use_ctx) {
+#pragma unroll
+      for (int i = 0; i < kCtxMax; ++i) {
+        store_through(a.ctx + m * kCtxMax + i, ctx_new[i]);
+        s.ctx[j][i] = ctx_new[i];  // (every read of the parents' histories lies before the last wave_sync)
+      }
+    }
+    store_through(a.src_row + m, parent >= 0 ? m_base + parent : m);
+    store_through(a.tok + m, appended);
+    }
+    if (S < a.S_max) {
+      const size_t ti = ((size_t)b * a.S_max + S) * K + j;
+      store_through(a.tree_parent + ti, parent);
+      store_through(a.tree_token + ti, code);
+      store_through(a.tree_merged + ti, merged);
+    }
+    if (j == 0 && last_step) {
+      store_through(a.finished + b, 1);
+      store_through(a.utt_steps + b, S + 1);
+      __threadfence();
+      const int old = atomicAdd(a.n_finished, 1);
+      if (old + 1 == a.B) {
+        *reinterpret_cast<volatile int *>(a.done) = 1;
+        __threadfence_system();
+        *a.h_done = 1;
+      }
+    }
+  }
+  wave_sync();
+}
+
+// picks the lane-group width and register budget for the beam and list sizes at hand.
+// FORMS: 4 = one list per hypothesis, known at compile time (tail of the row kernel of the materialised-logits path);
+// 0 = beams up to 8 (what the main kernel of a step runs in its tail); 1 = those plus wider beams
+// whose hypotheses come with a single list; 2 = wider beams with many lists (several passes, many
+// registers).  The heavy forms are kept out of the kernels that do not need them.
+template <int FORMS, class Scratch = SelectScratch>
+__device__ __forceinline__ void select_dispatch(const SelectArgs &a, int b, Scratch &s, const CandView cv) {
+  if constexpr (FORMS == 12 || FORMS == 16) {  // FORMS == 4 on a plain RNN-T (no durations, no LM): 12 for AES++
+    constexpr int P = FORMS == 12 ? 2 : 1;      // without prune margin and prefix search, 16 for ALSD++
+    if (a.K <= 4) select_utterance<16, 1, 4, false, false, Scratch, true, P>(a, b, s, cv);
+    else if (a.K <= 8) select_utterance<8, 1, 8, false, false, Scratch, true, P>(a, b, s, cv);
+    else if (a.K <= 12) select_utterance<4, 1, 12, false, false, Scratch, true, P>(a, b, s, cv);
+    else select_utterance<4, 1, 16, false, false, Scratch, true, P>(a, b, s, cv);
+  } else if constexpr (FORMS == 4) {  // one list per hypothesis (the materialised-logits path), any beam
+    if (a.K <= 4) select_utterance<16, 1, 4, false, false, Scratch, true>(a, b, s, cv);
+    else if (a.K <= 8) select_utterance<8, 1, 8, false, false, Scratch, true>(a, b, s, cv);
+    else if (a.K <= 12) select_utterance<4, 1, 12, false, false, Scratch, true>(a, b, s, cv);
+    else select_utterance<4, 1, 16, false, false, Scratch, true>(a, b, s, cv);
+  } else if constexpr (FORMS == 3) {  // TDT, every (symbol, duration) pair a candidate, beams up to 8
+    if (a.K <= 4) {
+      if (a.n_chunks <= 16 * 3) select_utterance<16, 3, 4, false, true, Scratch>(a, b, s, cv);
+      else select_utterance<16, 0, 4, false, true, Scratch>(a, b, s, cv);
+    } else {
+      if (a.n_chunks <= 8 * 5) select_utterance<8, 5, 8, false, true, Scratch>(a, b, s, cv);
+      else select_utterance<8, 0, 8, false, true, Scratch>(a, b, s, cv);
+    }
+  } else if constexpr (FORMS == 17) {  // forms 5 and 6 with the durations' older code (see select_utterance)
+    select_utterance<16, 3, 4, false, false, Scratch, false, 0, true>(a, b, s, cv);
+  } else if constexpr (FORMS == 18) {
+    select_utterance<8, 5, 8, false, false, Scratch, false, 0, true>(a, b, s, cv);
+  } else if constexpr (FORMS == 5) {  // one form alone (the caller has checked 2 < K <= 4, n_chunks <= 48) ...
+    select_utterance<16, 3, 4>(a, b, s, cv);
+  } else if constexpr (FORMS == 11) {  // ... the same for ALSD++ on a plain RNN-T (no durations, no LM): beams 3, 4,
+    select_utterance<16, 3, 4, false, false, Scratch, false, 1>(a, b, s, cv);
+  } else if constexpr (FORMS == 13) {  // ... 1, 2 (n_chunks <= 48),
+    select_utterance<16, 3, 2, false, false, Scratch, false, 1>(a, b, s, cv);
+  } else if constexpr (FORMS == 14) {  // ... 5 to 8 (n_chunks <= 40);
+    select_utterance<8, 5, 8, false, false, Scratch, false, 1>(a, b, s, cv);
+  } else if constexpr (FORMS == 15) {  // AES++ without prune margin and prefix search on a plain RNN-T, beams 3, 4
+    select_utterance<16, 3, 4, false, false, Scratch, false, 2>(a, b, s, cv);
+  } else if constexpr (FORMS == 6) {  // ... (4 < K <= 8, n_chunks <= 40): a kernel a third the size
+    select_utterance<8, 5, 8>(a, b, s, cv);
+  } else if constexpr (FORMS == 2) {
+    if (a.n_chunks <= 16 * 3) select_utterance<16, 3, 16, true>(a, b, s, cv);  // four hypotheses per pass
+    else select_utterance<4, 0, 16>(a, b, s, cv);
+  } else {
+    if (a.K <= 2 && a.n_chunks <= 16 * 3) {  // (a form of its own: the lists are loaded and merged KMAX entries wide)
+      select_utterance<16, 3, 2>(a, b, s, cv);
+    } else if (a.K <= 4) {
+      if (a.n_chunks <= 16 * 3) select_utterance<16, 3, 4>(a, b, s, cv);
+      else select_utterance<16, 0, 4>(a, b, s, cv);
+    } else if (a.K <= 8) {
+      if (a.n_chunks <= 8 * 5) select_utterance<8, 5, 8>(a, b, s, cv);
+      else select_utterance<8, 0, 8>(a, b, s, cv);
+    } else if constexpr (FORMS == 1) {
+      select_utterance<4, 1, 16>(a, b, s, cv);
+    }
+  }
+}
+template <int FORMS, class Scratch = SelectScratch>
+__device__ __forceinline__ void select_dispatch(const SelectArgs &a, int b, Scratch &s) {
+  select_dispatch<FORMS, Scratch>(a, b, s, cand_view(a));
+}
+// which stand-alone selection kernel takes a beam of K with n_chunks lists per hypothesis
+__host__ __device__ inline bool select_needs_wide_forms(int K, int n_chunks) { return K > 8 && n_chunks > 4; }
+
+}  // namespace rb

@@ -1,0 +1,85 @@
+"""The resident step loop (one launch that keeps the weights on chip, what a default LSTM decoder runs) against the per-step
+launches (use_graph=False), bit for bit: both form every sum in the same order.  Shapes at the edges of its tiles: beams
+of every selection form, one to three tiles of 16 slots per group, one to eight groups, widths of 64 to 640 with W_hh and
+output-layer tiles that do not divide evenly, vocabularies of one column pair to the largest that fits, utterances
+without frames."""
+from __future__ import annotations
+
+import numpy as np
+import pytest
+
+import synth_inputs as S
+from gpu_common import gpu_decode
+
+pytestmark = pytest.mark.gpu
+
+W640 = dict(H=640, P=640, E=640, D=64)
+TDT = dict(model="tdt", durations=(0, 1, 2, 3, 4))
+CASES = [
+    dict(B=1, beam=1, V=2, H=64, P=64, E=32, D=32),
+    dict(B=1, beam=16, V=1024, s=2, **W640),
+    dict(B=2, beam=5, V=1023, algo="aes", **W640),
+    dict(B=3, beam=4, V=33, H=64, P=192, E=64, D=32, **TDT),
+    dict(B=5, beam=8, V=700, H=576, P=128, E=64, D=32, algo="aes", gamma=2.3),
+    dict(B=8, beam=2, V=513, H=320, P=320, E=64, D=32, algo="aes", aes_prefix=True),
+    dict(B=13, beam=3, V=129, H=448, P=640, E=64, D=32, prec="bf16"),
+    dict(B=19, beam=4, V=1024, prec="bf16", algo="aes", gamma=2.3, **W640, **TDT),
+    dict(B=11, beam=9, V=512, prec="bf16", H=256, P=256, E=64, D=32),
+    dict(B=20, beam=12, V=1000, s=1, **W640),
+    dict(B=40, beam=1, V=1024, **W640),
+    dict(B=50, beam=4, V=90, **W640),
+]
+
+
+@pytest.mark.parametrize("kw", CASES, ids=lambda kw: f"b{kw['B']}_k{kw['beam']}_v{kw['V']}_h{kw['H']}_p{kw['P']}_{kw.get('prec', 'f32')}")
+def test_resident_loop_equals_the_per_step_launches(kw, monkeypatch, capfd):
+    import paper_2506_00185_amd as A
+    monkeypatch.setenv("RNNT_BEAM_TRACE_PACING", "1")  # (reports a launch that gave up)
+    c = S.custom_config(**dict(dict(T=17, T_min=3, s=3, blank_bias=3.0), **kw))
+    w = S.perturb_biases(S.make_weights(c, 5), 6)
+    L = S.make_lengths(c, 7)
+    if c["B"] > 2:
+        L[1] = 0
+    enc = S.make_enc(c, L, 8)
+    ref = gpu_decode(A.BeamDecoder(c, w, use_graph=False), enc, L)
+    dec = A.BeamDecoder(c, w)
+    for _ in range(2):
+        r = gpu_decode(dec, enc, L)
+        for key in ("tokens", "lens", "scores", "n_steps", "parent", "token", "merged"):
+            np.testing.assert_array_equal(r[key], ref[key])
+    assert "gave up" not in capfd.readouterr().err
+
+
+@pytest.mark.parametrize("prune,rule,beam,B", [("late", 4, 8, 9), ("early", 3, 4, 17), ("late", 3, 11, 4)])
+def test_resident_loop_with_an_lm(prune, rule, beam, B):
+    import paper_2506_00185_amd as A
+    c = S.custom_config(B=B, T=15, T_min=4, s=3, beam=beam, V=300, blank_bias=3.0, **W640)
+    w = S.perturb_biases(S.make_weights(c, 15), 16)
+    L = S.make_lengths(c, 17)
+    enc = S.make_enc(c, L, 18)
+    lm = A.NGramLM(S.make_lm(V=c["V"], order=4, n_target=20000, zipf_s=1.1, seed=19))
+    kw = dict(lm_rule=rule, lm_prune=prune)
+    ref = gpu_decode(A.BeamDecoder(c, w, use_graph=False, **kw), enc, L, lm=lm, lm_weight=0.3)
+    r = gpu_decode(A.BeamDecoder(c, w, **kw), enc, L, lm=lm, lm_weight=0.3)
+    for key in ("tokens", "lens", "scores", "n_steps", "parent", "token", "merged"):
+        np.testing.assert_array_equal(r[key], ref[key])
+
+
+def test_resident_loop_that_gives_up_is_replaced_by_the_per_step_launches(monkeypatch, capfd):
+    import paper_2506_00185_amd as A
+    monkeypatch.setenv("RNNT_BEAM_TRACE_PACING", "1")
+    c = S.custom_config(B=9, T=12, T_min=4, s=3, beam=4, V=300, blank_bias=3.0, **W640)
+    w = S.make_weights(c, 25)
+    L = S.make_lengths(c, 27)
+    enc = S.make_enc(c, L, 28)
+    ref = gpu_decode(A.BeamDecoder(c, w, use_graph=False), enc, L)
+    dec = A.BeamDecoder(c, w)
+    dec.debug_set_spin_limit(1)  # (its blocks then wait in vain for one more)
+    for _ in range(2):
+        r = gpu_decode(dec, enc, L)
+        for key in ("tokens", "lens", "scores", "n_steps"):
+            np.testing.assert_array_equal(r[key], ref[key])
+    assert "gave up" in capfd.readouterr().err
+    dec.debug_set_spin_limit(1 << 22)
+    r = gpu_decode(dec, enc, L)
+    np.testing.assert_array_equal(r["tokens"], ref["tokens"])
