@@ -1,4 +1,4 @@
-// The whole step loop of an LSTM decoder in one launch whose blocks keep the weights on chip from the first step to the
+// The whole step loop of a decoder in one launch whose blocks keep the weights on chip from the first step to the
 // last ("resident" loop).
 //
 // What bounds the per-step launches is not their work but their boundaries: three dependent kernels of 4 to 14 us per
@@ -22,6 +22,11 @@
 // Every sum is formed in the order of the per-step kernels (K slices of 1/8 of the contraction, one chain of fused
 // multiply-adds each, in the order in which the 32x32x2 matrix instructions take their k; slices added first to last), so the
 // results are the same bit for bit: a 16x16x4 fp32 matrix instruction rounds like four fused multiply-adds in a row.
+//
+// Stateless decoders (ST) have no cells and no projection: pre is a sum of table rows, f_proj[frame] + tab_0[last token] +
+// tab_1[the one before] + .., and every owner of output-layer tiles forms its own slice of it from the words (see
+// res_stateless_pre), so that a step is two hops (words -> z -> words).  The owners keep the slots' last tokens themselves.
+// (batch 8, beam 4, bf16 joint, 640 wide, V = 1024: 5.46 ms per decode with the per-step launches, 3.62 here.)
 //
 // Every wait is bounded: a wave that waits too long raises the abort word and ends, every other wave sees the word (or
 // its own limit) and ends too, and the host decodes the batch with the per-step launches instead.
@@ -67,6 +72,8 @@ struct ResArgs {
   const float *WR, *WJ, *WP;         // [tile][round][64 lanes][2] (bf16 models: WR only)
   const uint64_t *WJb, *WPb;         // bf16 models: [32-row tile][round][64 lanes] four bf16 (k of the lane's half)
   const float *b_out, *b_pred, *G, *f_proj;
+  const float *emb_tab;              // stateless decoders: [n_ctx][V + 1][H], else null
+  int n_ctx;
   const int *lengths;
   float *hb, *pb, *zb;               // rings of the hand-over arrays, all groups
   uint64_t *words;
@@ -170,8 +177,8 @@ struct ResAddr {
   __device__ __forceinline__ float *z(int step, int slot) const { return zb + (step & 1) * z_ring + (size_t)slot * Npad; }
   __device__ __forceinline__ uint64_t *w(int step) const { return words + (step & (kResStepRing - 1)) * w_ring; }
 };
-__host__ __device__ inline size_t res_h_floats(const ResArgs &a) { return (size_t)kResStepRing * a.n_groups * a.NT * a.P * kResSlot; }
-__host__ __device__ inline size_t res_p_floats(const ResArgs &a) { return (size_t)2 * a.n_groups * a.NT * a.H * kResSlot; }
+__host__ __device__ inline size_t res_h_floats(const ResArgs &a) { return a.emb_tab ? 0 : (size_t)kResStepRing * a.n_groups * a.NT * a.P * kResSlot; }
+__host__ __device__ inline size_t res_p_floats(const ResArgs &a) { return a.emb_tab ? 0 : (size_t)2 * a.n_groups * a.NT * a.H * kResSlot; }
 __host__ __device__ inline size_t res_z_floats(const ResArgs &a) { return (size_t)2 * a.n_groups * a.NT * kResSlot * a.Npad; }
 __host__ __device__ inline size_t res_words(const ResArgs &a) { return (size_t)kResStepRing * a.n_groups * a.NT * kResSlot; }
 __device__ __forceinline__ ResAddr res_addr(const ResArgs &a, int g) {
@@ -200,6 +207,7 @@ struct ResBlock {
   const uint64_t *tiles;             // LDS: weights of up to kResMaxLdsTiles tiles
   const int2 *info;                  // LDS: frames of the slot's utterance, its first row of f_proj
   uint64_t *word;                    // LDS: this wave's copy of the last step's words, [slot tile][16]
+  int4 *ctx;                         // LDS, stateless decoders: this wave's copy of the slots' last tokens (-1: none)
   int phase;                         // which half of the partial sums
 };
 // A lane's place in the wave.  (Computed anew where it is needed rather than kept: the weights leave no registers to
@@ -476,8 +484,74 @@ __device__ __forceinline__ void clear_z(const ResBlock &k, const ResLane &l, con
   if (slot < k.nslots) store16_through(ad.z(step, slot) + 16 * tile + 4 * l.kq, floatx4{e, e, e, e});
 }
 
-// wj: the tiles that the block keeps in registers; one more may lie in LDS behind the projection's
+// Stateless decoders: the wave's slice of pre of its lanes' slots, as res_gather / bf16_gather would have read it, summed up
+// in the order of k_stateless_pre.  All rows of a pair of tables are requested before the first is needed: the time is that
+// of one trip to the L2 (each block of a group reads all of the group's rows, at most 48 x (1 + n_ctx) x 2.5 KB; a
+// hand-over of sums formed once would cost a hop more, and the same trip before it).
 template <bool FULL, bool BF16>
+__device__ __forceinline__ void res_stateless_pre(const ResArgs &a, const ResBlock &k, const ResLane &l, int nt, bool second, int nr,
+                                                  uint64_t (&x)[(BF16 ? 2 : 1) * kResMaxRounds]) {
+  int slot = (nt + (BF16 && second ? (l.lane >> 4) & 1 : 0)) * kResSlot + l.sl;
+  slot = slot < k.nslots ? slot : 0;  // (places without a slot repeat the first one's rows)
+  const int2 in = k.info[slot];
+  const int4 c = k.ctx[slot];
+  int tt = word_frame(k.word[slot]);
+  tt = tt < in.x ? tt : in.x - 1;
+  tt = tt < 0 ? 0 : tt;
+  const int k0 = 8 * k.wave * nr + 4 * (BF16 ? l.lane >> 5 : l.kq & 1);
+  float4 v[kResMaxRounds];
+  auto row = [&](float4 (&d)[kResMaxRounds], const float *p) {
+#pragma unroll
+    for (int i = 0; i < kResMaxRounds; ++i) d[i] = *reinterpret_cast<const float4 *>(p + k0 + 8 * (FULL || i < nr ? i : 0));
+  };
+  auto add = [&](const float4 (&d)[kResMaxRounds]) {
+#pragma unroll
+    for (int i = 0; i < kResMaxRounds; ++i) {
+      v[i].x += d[i].x; v[i].y += d[i].y; v[i].z += d[i].z; v[i].w += d[i].w;
+    }
+  };
+  row(v, a.f_proj + ((size_t)in.y + tt) * a.H);
+#pragma unroll 1
+  for (int j = 0; j < a.n_ctx; j += 2) {
+    const int j1 = j + 1 < a.n_ctx ? j + 1 : j;
+    const int t0 = j == 0 ? c.x : c.z, t1 = j1 == j ? t0 : j == 0 ? c.y : c.w;
+    float4 d0[kResMaxRounds], d1[kResMaxRounds];
+    row(d0, a.emb_tab + ((size_t)j * (a.V + 1) + (t0 < 0 ? a.V : t0)) * a.H);
+    row(d1, a.emb_tab + ((size_t)j1 * (a.V + 1) + (t1 < 0 ? a.V : t1)) * a.H);
+    add(d0);
+    if (j1 > j) add(d1);
+  }
+#pragma unroll
+  for (int i = 0; i < kResMaxRounds; ++i) {
+    if constexpr (BF16) {
+      x[2 * i] = pack2(v[i].x, v[i].z);
+      x[2 * i + 1] = pack2(v[i].y, v[i].w);
+    } else {
+      x[i] = l.kq >> 1 ? pack2(v[i].y, v[i].w) : pack2(v[i].x, v[i].z);
+    }
+  }
+}
+// the slots' last tokens behind the words that the wave holds
+__device__ __forceinline__ void res_update_ctx(const ResArgs &a, const ResBlock &k) {
+  const ResLane l = res_lane();
+  int4 c[kResMaxNT];
+#pragma unroll
+  for (int nt = 0; nt < kResMaxNT; ++nt)
+    if (nt < a.NT) {
+      const uint64_t w = k.word[nt * kResSlot + l.sl];
+      const int tok = word_tok(w);
+      c[nt] = k.ctx[word_src(w)];
+      if (tok >= 0) c[nt] = make_int4(tok, c[nt].x, c[nt].y, c[nt].z);
+    }
+  wave_sync();
+#pragma unroll
+  for (int nt = 0; nt < kResMaxNT; ++nt)
+    if (nt < a.NT && l.kq == 0) k.ctx[nt * kResSlot + l.sl] = c[nt];
+  wave_sync();
+}
+
+// wj: the tiles that the block keeps in registers; one more may lie in LDS behind the projection's
+template <bool FULL, bool BF16, bool ST>
 __device__ __forceinline__ bool res_j_phase(ResBlock &k, int step, const float (&wj)[kResRegJ<BF16>][2 * kResMaxRounds]) {
   if (k.nJ == 0) return true;
   constexpr int NJ = kResRegJ<BF16>;
@@ -497,7 +571,8 @@ __device__ __forceinline__ bool res_j_phase(ResBlock &k, int step, const float (
     for (int nt = 0; nt < a.NT; nt += 2) {
       const bool second = nt + 1 < a.NT;
       uint64_t x[2 * kResMaxRounds];
-      if (!bf16_gather<FULL, kResMaxRounds>(bf16_src(l, ad.p(step, nt), ad.p_tile, second, k.wave * nr), nr, x)) return false;
+      if constexpr (ST) res_stateless_pre<FULL, true>(a, k, l, nt, second, nr, x);
+      else if (!bf16_gather<FULL, kResMaxRounds>(bf16_src(l, ad.p(step, nt), ad.p_tile, second, k.wave * nr), nr, x)) return false;
 #pragma unroll
       for (int t = 0; t < NJ + 1; ++t) {
         if (t >= k.nJ) break;
@@ -528,7 +603,8 @@ __device__ __forceinline__ bool res_j_phase(ResBlock &k, int step, const float (
     for (int nt = 0; nt < a.NT; ++nt) {
       uint64_t x[kResMaxRounds];
       const uint64_t *src = reinterpret_cast<const uint64_t *>(ad.p(step, nt)) + (size_t)k.wave * nr * 64 + l.lane;
-      if (!res_gather<FULL, kResMaxRounds>([src](int i) { return src + i * 64; }, nr, x)) return false;
+      if constexpr (ST) res_stateless_pre<FULL, false>(a, k, l, nt, false, nr, x);
+      else if (!res_gather<FULL, kResMaxRounds>([src](int i) { return src + i * 64; }, nr, x)) return false;
 #pragma unroll
       for (int i = 0; i < kResMaxRounds; ++i) x[i] = pack2(fmaxf(lo_f(x[i]), 0.f), fmaxf(hi_f(x[i]), 0.f));
       floatx4 acc[NJ];
@@ -586,9 +662,9 @@ __device__ __forceinline__ void res_clear_pz(const ResArgs &a, const ResBlock &k
 // ---------------------------------------------------------------------------
 // blocks that own tiles
 // ---------------------------------------------------------------------------
-template <bool FULL, bool BF16>
+template <bool FULL, bool BF16, bool ST>
 __device__ __forceinline__ void res_worker(ResBlock k, const ResTab &tab, float *lds) {
-  constexpr int NJ = kResRegJ<BF16>;
+  constexpr int NJ = kResRegJ<BF16>, NR = ST ? 0 : kResMaxR;
   const ResArgs &a0 = res_args();
   k.nR = res_uniform(tab.nR);
   k.nJ = res_uniform(tab.nJ);
@@ -632,14 +708,19 @@ __device__ __forceinline__ void res_worker(ResBlock k, const ResTab &tab, float 
   // LDS of the cells: sums W_hh h of the block's tiles, cell state and hidden state of their units, [tile][slot tile][64]
   float *Rl = k.red + 2 * kResRedBlocks<BF16> * kResRedBlock, *cl = Rl + kResMaxR * a0.NT * 256, *hl = cl + kResMaxR * a0.NT * 64;
   int2 *info = reinterpret_cast<int2 *>(hl + kResMaxR * a0.NT * 64);
-  for (int i = threadIdx.x; i < kResMaxR * a0.NT * (256 + 128); i += kResThreads) Rl[i] = 0.f;
+  if constexpr (!ST)
+    for (int i = threadIdx.x; i < kResMaxR * a0.NT * (256 + 128); i += kResThreads) Rl[i] = 0.f;
   if (threadIdx.x < a0.NT * kResSlot) {
     const int b = res_utt(a0, k.g, (int)threadIdx.x < k.nslots ? threadIdx.x / a0.K : 0);
     info[threadIdx.x] = make_int2(a0.lengths[b], b * a0.T);
   }
   k.info = info;
   k.word = reinterpret_cast<uint64_t *>(info + a0.NT * kResSlot) + k.wave * a0.NT * kResSlot;
-  float wj[NJ][2 * kResMaxRounds], wr[kResMaxR][2 * kResMaxRounds];
+  if constexpr (ST) {  // (in the place of the cells' LDS: 8 waves x NT x 16 x 16 bytes of 6 x NT x 1536)
+    k.ctx = reinterpret_cast<int4 *>(Rl) + k.wave * a0.NT * kResSlot;
+    for (int i = l0.lane; i < a0.NT * kResSlot; i += 64) k.ctx[i] = make_int4(-1, -1, -1, -1);
+  }
+  float wj[NJ][2 * kResMaxRounds], wr[ST ? 1 : kResMaxR][2 * kResMaxRounds];
   {
     const int nrh = FULL ? kResMaxRounds : a0.rounds_h, nrp = FULL ? kResMaxRounds : a0.rounds_p;
 #pragma unroll
@@ -655,7 +736,7 @@ __device__ __forceinline__ void res_worker(ResBlock k, const ResTab &tab, float 
         }
       }
 #pragma unroll
-    for (int t = 0; t < kResMaxR; ++t)
+    for (int t = 0; t < NR; ++t)
 #pragma unroll
       for (int i = 0; i < kResMaxRounds; ++i) {
         wr[t][2 * i] = wr[t][2 * i + 1] = 0.f;
@@ -671,14 +752,14 @@ __device__ __forceinline__ void res_worker(ResBlock k, const ResTab &tab, float 
 #pragma unroll
       for (int t = 0; t < NJ; ++t) asm volatile("" : "+v"(wj[t][i]));
 #pragma unroll
-      for (int t = 0; t < kResMaxR; ++t) asm volatile("" : "+v"(wr[t][i]));
+      for (int t = 0; t < NR; ++t) asm volatile("" : "+v"(wr[t][i]));
     }
   }
   __syncthreads();
   int over = res_first_words(a0, k);
   for (int step = 0; over == 0; ++step) {
     // ---- cells
-    if (k.wave < k.nR) {
+    if (!ST && k.wave < k.nR) {
       const ResArgs &a = res_args();
       const ResLane l = res_lane();
       const ResAddr ad = res_addr(a, k.g);
@@ -720,10 +801,11 @@ __device__ __forceinline__ void res_worker(ResBlock k, const ResTab &tab, float 
       const ResArgs &a = res_args();
       res_clear_pz<BF16>(a, k, res_addr(a, k.g), step - 1);
     }
-    if (!res_p_phase<FULL, BF16>(k, step)) return;
-    if (!res_j_phase<FULL, BF16>(k, step, wj)) return;
+    if constexpr (!ST)
+      if (!res_p_phase<FULL, BF16>(k, step)) return;
+    if (!res_j_phase<FULL, BF16, ST>(k, step, wj)) return;
     // ---- R
-    if (k.nR > 0) {
+    if constexpr (!ST) if (k.nR > 0) {
       const ResArgs &a = res_args();
       const ResLane l = res_lane();
       const ResAddr ad = res_addr(a, k.g);
@@ -759,6 +841,9 @@ __device__ __forceinline__ void res_worker(ResBlock k, const ResTab &tab, float 
       }
     }
     over = res_words(k, step);
+    if constexpr (ST) {
+      if (over == 0) res_update_ctx(res_args(), k);
+    }
   }
 }
 
@@ -1106,10 +1191,10 @@ __device__ __forceinline__ void res_selector(ResBlock k, int sel, float *lds) {
   }
 }
 
-// FULL: H = P = 640 (loops of known length).  KC: beams up to 4, 8, 16.  PLAIN: 1 = ALSD++ on a plain RNN-T (see
+// FULL: H = P = 640 (loops of known length).  ST: stateless decoder (P does not count).  KC: beams up to 4, 8, 16.  PLAIN: 1 = ALSD++ on a plain RNN-T (see
 // select_utterance), 0 = any.  One block of 8 waves per compute unit (the LDS it asks for is more than half of a unit's).
 // The first n_sel blocks of a group select, the others own the tiles.
-template <bool FULL, bool BF16, int KC, int PLAIN>
+template <bool FULL, bool BF16, bool ST, int KC, int PLAIN>
 __global__ __launch_bounds__(kResThreads, 2) void k_decode_resident(ResArgs) {
   extern __shared__ __align__(16) float smem[];
   __shared__ int s_ok;
@@ -1149,15 +1234,13 @@ __global__ __launch_bounds__(kResThreads, 2) void k_decode_resident(ResArgs) {
     res_selector<KC, PLAIN>(k, rank, smem);
   } else {
     const ResTab &tab = a.tab[rank - a.n_sel];
-    if (tab.nR + tab.nJ + tab.nP > 0) res_worker<FULL, BF16>(k, tab, smem);
+    if (tab.nR + tab.nJ + tab.nP > 0) res_worker<FULL, BF16, ST>(k, tab, smem);
   }
 }
 
 typedef void (*ResKernel)(ResArgs);
 // each in a translation unit of its own (resident_kernels.hip), so that they build at once
-ResKernel resident_kernel_640_f32(int K, bool plain);
-ResKernel resident_kernel_640_bf16(int K, bool plain);
-ResKernel resident_kernel_any_f32(int K, bool plain);
-ResKernel resident_kernel_any_bf16(int K, bool plain);
+template <bool FULL, bool BF16, bool ST>
+ResKernel resident_kernel(int K, bool plain);
 
 }  // namespace rb

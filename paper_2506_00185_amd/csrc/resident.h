@@ -44,6 +44,8 @@ struct ResidentBatch {
   int B, T, K, algo, spin_limit;
   bool halves;      // the per-step launches would split the projection along k at this size
   const float *b_out, *b_pred, *G, *f_proj;
+  const float *emb_tab;  // stateless decoders (see ResArgs), else null
+  int n_ctx;
   const int *lengths;
   int Npad;
   bool has_lm;

@@ -940,8 +940,12 @@ int launch_resident(rnnt_beam *h, hipStream_t s, const StepPlan &p) {
   ResidentBatch b{};
   b.B = p.B; b.T = p.T; b.K = p.K; b.algo = p.algo;
   b.spin_limit = h->spin_limit;
-  b.halves = proj_split(c, p.M);
+  b.halves = c.pred == RNNT_PRED_LSTM && proj_split(c, p.M);
   b.b_out = h->b_out; b.b_pred = h->b_pred; b.G = h->G; b.f_proj = w.f_proj;
+  if (c.pred == RNNT_PRED_STATELESS) {
+    b.emb_tab = h->tab;
+    b.n_ctx = c.stateless_context;
+  }
   b.lengths = w.lengths;
   b.Npad = h->n_chunks * 32;
   b.has_lm = p.lm != nullptr;

@@ -71,7 +71,8 @@ struct Plan {
 bool assign_tiles(const rnnt_config_t &c, int n_blocks, std::vector<ResTab> &tab) {
   const bool bf = c.prec == RNNT_BF16_JOINT;
   const int N = c.V + 1 + c.n_durations;
-  const int nR = 4 * c.P / 16, nJ = bf ? (N + 31) / 32 : (N + 15) / 16, nP = bf ? c.H / 32 : c.H / 16;
+  const bool lstm = c.pred == RNNT_PRED_LSTM;
+  const int nR = lstm ? 4 * c.P / 16 : 0, nJ = bf ? (N + 31) / 32 : (N + 15) / 16, nP = !lstm ? 0 : bf ? c.H / 32 : c.H / 16;
   const int reg_j = bf ? kResRegJ<true> : kResRegJ<false>, max_p = bf ? 1 : kResMaxP;
   tab.assign(n_blocks, ResTab{});
   auto total = [&](const ResTab &t) { return t.nR + t.nJ + t.nP; };
@@ -122,7 +123,7 @@ Plan make_plan(const Resident &r, const rnnt_config_t &c, int B, int K, bool has
   const bool bf = c.prec == RNNT_BF16_JOINT;
   int lds_tiles = 0;
   for (const ResTab &t : p.tab) lds_tiles = std::max(lds_tiles, t.nP + std::max(0, t.nJ - (bf ? kResRegJ<true> : kResRegJ<false>)));
-  const size_t worker = (size_t)lds_tiles * std::max(c.P, c.H) * kResSlot * 4 +
+  const size_t worker = (size_t)lds_tiles * std::max(c.pred == RNNT_PRED_LSTM ? c.P : 0, c.H) * kResSlot * 4 +
                         (size_t)2 * (bf ? kResRedBlocks<true> : kResRedBlocks<false>) * kResRedBlock * 4 +
                         (size_t)kResMaxR * p.NT * (256 + 128) * 4 + (size_t)p.NT * kResSlot * (sizeof(int2) + kResWaves * 8);
   const size_t sel = (sizeof(ResSelLds) + 15) / 16 * 16 + p.upc * sizeof(SelectScratchWide) +
@@ -134,10 +135,11 @@ Plan make_plan(const Resident &r, const rnnt_config_t &c, int B, int K, bool has
   return p;
 }
 
+template <bool ST>
 ResKernel pick_kernel(const rnnt_config_t &c, int K, bool plain) {
-  const bool full = c.H == 640 && c.P == 640, bf = c.prec == RNNT_BF16_JOINT;
-  if (full) return bf ? resident_kernel_640_bf16(K, plain) : resident_kernel_640_f32(K, plain);
-  return bf ? resident_kernel_any_bf16(K, plain) : resident_kernel_any_f32(K, plain);
+  const bool full = c.H == 640 && (ST || c.P == 640), bf = c.prec == RNNT_BF16_JOINT;
+  if (full) return bf ? resident_kernel<true, true, ST>(K, plain) : resident_kernel<true, false, ST>(K, plain);
+  return bf ? resident_kernel<false, true, ST>(K, plain) : resident_kernel<false, false, ST>(K, plain);
 }
 
 }  // namespace
@@ -150,11 +152,11 @@ void resident_destroy(Resident &r) {
 
 int resident_create(Resident &r, const rnnt_config_t &c, const ResidentWeights &w, std::string &err) {
   r.usable = false;
-  // LSTM decoders whose contractions split into eight slices of whole rounds and fit the registers; vocabularies that one
-  // wave holds in registers
-  if (c.pred != RNNT_PRED_LSTM || c.tdt_all_pairs || c.H % 64 || c.P % 64 || c.H > 8 * 8 * kResMaxRounds ||
-      c.P > 8 * 8 * kResMaxRounds || c.V > kResMaxV)
-    return RNNT_OK;
+  // decoders whose contractions split into eight slices of whole rounds and fit the registers (stateless ones: P is not
+  // that of a contraction); vocabularies that one wave holds in registers
+  const bool lstm = c.pred == RNNT_PRED_LSTM;
+  const int most = 8 * 8 * kResMaxRounds;
+  if (c.tdt_all_pairs || c.H % 64 || c.H > most || (lstm && (c.P % 64 || c.P > most)) || c.V > kResMaxV) return RNNT_OK;
   hipError_t e;
   auto fail = [&](const char *what) {
     err = std::string(what) + ": " + hipGetErrorString(e);
@@ -179,22 +181,23 @@ int resident_create(Resident &r, const rnnt_config_t &c, const ResidentWeights &
     return e == hipSuccess;
   };
   const int nR = 4 * c.P / 16, nJ = bf ? (N + 31) / 32 : (N + 15) / 16, nP = bf ? c.H / 32 : c.H / 16;
-  bool ok = alloc(&r.WR, (size_t)nR * 16 * c.P);
-  if (bf) ok = ok && alloc(&r.WJb, (size_t)nJ * (c.H / 8) * 64) && alloc(&r.WPb, (size_t)nP * (c.P / 8) * 64);
-  else ok = ok && alloc(&r.WJ, (size_t)nJ * 16 * c.H) && alloc(&r.WP, (size_t)nP * 16 * c.P);
-  ok = ok && alloc(&r.hb, kResStepRing * rows * c.P) && alloc(&r.pb, 2 * rows * c.H) && alloc(&r.zb, 2 * rows * w.out_rows) &&
+  bool ok = bf ? alloc(&r.WJb, (size_t)nJ * (c.H / 8) * 64) : alloc(&r.WJ, (size_t)nJ * 16 * c.H);
+  if (lstm) {
+    ok = ok && alloc(&r.WR, (size_t)nR * 16 * c.P) && alloc(&r.hb, kResStepRing * rows * c.P) && alloc(&r.pb, 2 * rows * c.H);
+    ok = ok && (bf ? alloc(&r.WPb, (size_t)nP * (c.P / 8) * 64) : alloc(&r.WP, (size_t)nP * 16 * c.P));
+  }
+  ok = ok && alloc(&r.zb, 2 * rows * w.out_rows) &&
        alloc(&r.words, kResStepRing * rows) && alloc(&r.ctl, 64) && alloc(&r.tab, r.n_cus);
   if (!ok) return fail("resident loop: hipMalloc");
   if ((e = hipHostMalloc(reinterpret_cast<void **>(&r.h_abort), 128, hipHostMallocMapped)) != hipSuccess) return fail("hipHostMalloc");
   if ((e = hipHostGetDevicePointer(reinterpret_cast<void **>(&r.h_abort_dev), r.h_abort, 0)) != hipSuccess) return fail("pinned word");
   const dim3 grid(512), block(256);
-  hipLaunchKernelGGL(k_pack_f32<1>, grid, block, 0, nullptr, w.W_hh, 4 * c.P, c.P, nR, r.WR);
-  if (bf) {
-    hipLaunchKernelGGL(k_pack_bf16<0>, grid, block, 0, nullptr, w.W_out, w.out_rows, c.H, nJ, r.WJb);
-    hipLaunchKernelGGL(k_pack_bf16<2>, grid, block, 0, nullptr, w.W_pred, c.H, c.P, nP, r.WPb);
-  } else {
-    hipLaunchKernelGGL(k_pack_f32<0>, grid, block, 0, nullptr, w.W_out, w.out_rows, c.H, nJ, r.WJ);
-    hipLaunchKernelGGL(k_pack_f32<2>, grid, block, 0, nullptr, w.W_pred, c.H, c.P, nP, r.WP);
+  if (bf) hipLaunchKernelGGL(k_pack_bf16<0>, grid, block, 0, nullptr, w.W_out, w.out_rows, c.H, nJ, r.WJb);
+  else hipLaunchKernelGGL(k_pack_f32<0>, grid, block, 0, nullptr, w.W_out, w.out_rows, c.H, nJ, r.WJ);
+  if (lstm) {
+    hipLaunchKernelGGL(k_pack_f32<1>, grid, block, 0, nullptr, w.W_hh, 4 * c.P, c.P, nR, r.WR);
+    if (bf) hipLaunchKernelGGL(k_pack_bf16<2>, grid, block, 0, nullptr, w.W_pred, c.H, c.P, nP, r.WPb);
+    else hipLaunchKernelGGL(k_pack_f32<2>, grid, block, 0, nullptr, w.W_pred, c.H, c.P, nP, r.WP);
   }
   if ((e = hipGetLastError()) != hipSuccess || (e = hipDeviceSynchronize()) != hipSuccess) return fail("resident loop: packing");
   r.usable = true;
@@ -212,6 +215,7 @@ hipError_t resident_launch(Resident &r, const rnnt_config_t &c, const ResidentBa
   if (!p.ok) return hipErrorInvalidValue;
   ResArgs a{};
   a.WR = r.WR; a.WJ = r.WJ; a.WP = r.WP; a.WJb = r.WJb; a.WPb = r.WPb;
+  a.emb_tab = b.emb_tab; a.n_ctx = b.n_ctx;
   a.b_out = b.b_out; a.b_pred = b.b_pred; a.G = b.G; a.f_proj = b.f_proj;
   a.lengths = b.lengths;
   a.hb = r.hb; a.pb = r.pb; a.zb = r.zb; a.words = r.words;
@@ -241,7 +245,7 @@ hipError_t resident_launch(Resident &r, const rnnt_config_t &c, const ResidentBa
   }
   hipLaunchKernelGGL(k_resident_init, dim3(512), dim3(256), 0, s, a);
   const bool plain = c.n_durations == 0 && !b.has_lm && b.algo == RNNT_ALSD;
-  ResKernel k = pick_kernel(c, b.K, plain);
+  ResKernel k = b.emb_tab ? pick_kernel<true>(c, b.K, plain) : pick_kernel<false>(c, b.K, plain);
   e = hipFuncSetAttribute(reinterpret_cast<const void *>(k), hipFuncAttributeMaxDynamicSharedMemorySize, (int)p.lds);
   if (e != hipSuccess) return e;
   hipLaunchKernelGGL(k, dim3(p.n_groups * p.n_blocks), dim3(kResThreads), p.lds, s, a);

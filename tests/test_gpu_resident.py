@@ -1,4 +1,4 @@
-"""The resident step loop (one launch that keeps the weights on chip, what a default LSTM decoder runs) against the per-step
+"""The resident step loop (one launch that keeps the weights on chip, what a default decoder runs) against the per-step
 launches (use_graph=False), bit for bit: both form every sum in the same order.  Shapes at the edges of its tiles: beams
 of every selection form, one to three tiles of 16 slots per group, one to eight groups, widths of 64 to 640 with W_hh and
 output-layer tiles that do not divide evenly, vocabularies of one column pair to the largest that fits, utterances
@@ -14,6 +14,7 @@ from gpu_common import gpu_decode
 pytestmark = pytest.mark.gpu
 
 W640 = dict(H=640, P=640, E=640, D=64)
+ST = dict(pred="stateless")
 TDT = dict(model="tdt", durations=(0, 1, 2, 3, 4))
 CASES = [
     dict(B=1, beam=1, V=2, H=64, P=64, E=32, D=32),
@@ -28,10 +29,17 @@ CASES = [
     dict(B=20, beam=12, V=1000, s=1, **W640),
     dict(B=40, beam=1, V=1024, **W640),
     dict(B=50, beam=4, V=90, **W640),
+    # stateless decoders: every context length, both precisions, one to three tiles of slots
+    dict(B=1, beam=3, V=2, H=64, P=64, E=64, D=32, **ST, ctx=1),
+    dict(B=8, beam=4, V=1024, prec="bf16", algo="aes", s=2, **W640, **ST, ctx=2),
+    dict(B=9, beam=13, V=1000, prec="bf16", **W640, **ST, ctx=3),
+    dict(B=25, beam=8, V=257, H=448, P=64, E=64, D=32, **ST, ctx=4),
+    dict(B=40, beam=5, V=1023, **W640, **ST, ctx=2),
+    dict(B=30, beam=4, V=129, prec="bf16", H=192, P=192, E=192, D=32, algo="aes", gamma=2.3, **ST, ctx=4, **TDT),
 ]
 
 
-@pytest.mark.parametrize("kw", CASES, ids=lambda kw: f"b{kw['B']}_k{kw['beam']}_v{kw['V']}_h{kw['H']}_p{kw['P']}_{kw.get('prec', 'f32')}")
+@pytest.mark.parametrize("kw", CASES, ids=lambda kw: f"b{kw['B']}_k{kw['beam']}_v{kw['V']}_h{kw['H']}_p{kw['P']}_{kw.get('prec', 'f32')}_ctx{kw.get('ctx', 0)}")
 def test_resident_loop_equals_the_per_step_launches(kw, monkeypatch, capfd):
     import paper_2506_00185_amd as A
     monkeypatch.setenv("RNNT_BEAM_TRACE_PACING", "1")  # (reports a launch that gave up)
@@ -50,10 +58,11 @@ def test_resident_loop_equals_the_per_step_launches(kw, monkeypatch, capfd):
     assert "gave up" not in capfd.readouterr().err
 
 
-@pytest.mark.parametrize("prune,rule,beam,B", [("late", 4, 8, 9), ("early", 3, 4, 17), ("late", 3, 11, 4)])
-def test_resident_loop_with_an_lm(prune, rule, beam, B):
+@pytest.mark.parametrize("prune,rule,beam,B,more", [("late", 4, 8, 9, {}), ("early", 3, 4, 17, {}), ("late", 3, 11, 4, {}),
+                                                    ("late", 4, 6, 10, dict(ST, ctx=2))])
+def test_resident_loop_with_an_lm(prune, rule, beam, B, more):
     import paper_2506_00185_amd as A
-    c = S.custom_config(B=B, T=15, T_min=4, s=3, beam=beam, V=300, blank_bias=3.0, **W640)
+    c = S.custom_config(B=B, T=15, T_min=4, s=3, beam=beam, V=300, blank_bias=3.0, **W640, **more)
     w = S.perturb_biases(S.make_weights(c, 15), 16)
     L = S.make_lengths(c, 17)
     enc = S.make_enc(c, L, 18)
