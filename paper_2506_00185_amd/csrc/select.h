@@ -741,6 +741,8 @@ __device__ __forceinline__ void select_utterance(const SelectArgs &a, int b, Scr
   // ---- expansion into the new slots
   int code = -3, parent = -1, appended = -1;
   int ctx_new[kCtxMax];
+  int t_new = 0;
+  bool live_new = false;
   if (lane < K) {
     const int j = lane;
     const double val = s.sel_val[j];
@@ -785,6 +787,8 @@ __device__ __forceinline__ void select_utterance(const SelectArgs &a, int b, Scr
         ctx_new[0] = v;
       }
       if (t > T_b) t = T_b;
+      t_new = t;
+      live_new = true;
       s.n_live[j] = 1;
       s.n_score[j] = val;
       s.n_t[j] = t;
@@ -793,6 +797,16 @@ __device__ __forceinline__ void select_utterance(const SelectArgs &a, int b, Scr
       s.n_last[j] = last;
       s.n_hash[j] = hash;
     }
+  }
+  // Resident loop: the words leave here, ahead of the recombination, which changes none of their fields: the slots of a
+  // class stand in the same frame and one of them stays live, so whether any slot is open is known already.  The group's
+  // other blocks go on while this wave merges and writes the tree (batch 32 / beam 4: 10.79
+  // -> 10.50 ms per decode, one utterance 9.53 -> 9.33).
+  bool last_step = false;
+  if constexpr (RES) {
+    last_step = __ballot(live_new && t_new < T_b) == 0ull || S + 1 >= T_b * (a.max_sym + 1);
+    if (lane < K)
+      store_agent(rs->words + lane, slot_word(S, last_step ? 1 : 0, rs->slot0 + (parent >= 0 ? parent : lane), appended, t_new));
   }
   wave_sync();
 
@@ -833,11 +847,8 @@ __device__ __forceinline__ void select_utterance(const SelectArgs &a, int b, Scr
     }
     const int m = m_base + j;
     // finished when no surviving slot has frames left
-    const bool open = live && s.n_t[j] < T_b;
-    const unsigned long long any_open = __ballot(open);
-    const bool last_step = any_open == 0ull || S + 1 >= T_b * (a.max_sym + 1);
+    if constexpr (!RES) last_step = __ballot(live && s.n_t[j] < T_b) == 0ull || S + 1 >= T_b * (a.max_sym + 1);
     if constexpr (RES) {
-      store_agent(rs->words + j, slot_word(S, last_step ? 1 : 0, rs->slot0 + (parent >= 0 ? parent : j), appended, s.n_t[j]));
       // (every read of the old state lies before the last wave_sync; the same words are re-read by this wave only)
       s.score[j] = score;
       s.t[j] = s.n_t[j];
