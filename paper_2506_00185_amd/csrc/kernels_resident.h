@@ -17,7 +17,7 @@
 // pattern.  No barrier, no flag and no acknowledged store lies between the two (one hop costs 0.6 us; stores, their
 // acknowledgement, a counter and then the loads 2.0 us).  The words of the selection carry the step's number instead.
 // A writer puts the pattern back once a word of a later phase proves that every reader is through (see the clear_
-// functions), two to four steps before the array is used again.
+// functions), one or two steps before the place is used again.
 //
 // Every sum is formed in the order of the per-step kernels (K slices of 1/8 of the contraction, one chain of fused
 // multiply-adds each, in the order in which the 32x32x2 matrix instructions take their k; slices added first to last), so the
@@ -200,6 +200,8 @@ __device__ __forceinline__ ResAddr res_addr(const ResArgs &a, int g) {
 // what a wave knows about itself and its block
 struct ResBlock {
   int g, nu, nslots;                 // group, utterances and slots of the group
+  int nt;                            // slot tiles up to the last one with an unfinished utterance: the others are left out
+  const int16_t *order;              // LDS: the group's utterances (indices in the batch), longest first
   int nR, nJ, nP;
   int wave;
   int ptile, jtile[2];               // the tile of 16 outputs / columns whose sums this wave finishes (-1: none)
@@ -222,7 +224,7 @@ __device__ __forceinline__ ResLane res_lane() {
 }
 __device__ __forceinline__ int res_uniform(int x) { return __builtin_amdgcn_readfirstlane(x); }
 // index of utterance u of the group in the batch
-__device__ __forceinline__ int res_utt(const ResArgs &a, int g, int u) { return g + a.n_groups * u; }
+__device__ __forceinline__ int res_utt(const ResBlock &k, int u) { return k.order[u]; }
 
 // partial sums of a 16-row tile: wave's lane (row group, slot) holds four rows
 template <bool BF16>
@@ -247,12 +249,12 @@ __device__ __forceinline__ floatx4 res_sum(const ResBlock &k, const ResLane &l, 
 
 // Waits for the words of step `step` and leaves them in the wave's LDS copy; slots beyond the group's are idle (finished).
 // 1: every utterance of the group has finished, 0: not yet, -1: the wait gave up.
-__device__ __forceinline__ int res_words(const ResBlock &k, int step) {
+__device__ __forceinline__ int res_words(ResBlock &k, int step) {
   const ResArgs &a = res_args();
   const ResLane l = res_lane();
   const uint64_t *p = res_addr(a, k.g).w(step) + l.sl;
   const int tag = (step + 1) & 0xffff;
-  bool open = false;
+  int top = 0;
 #pragma unroll 1
   for (int nt = 0; nt < a.NT; ++nt) {
     const int slot = nt * kResSlot + l.sl;
@@ -267,25 +269,27 @@ __device__ __forceinline__ int res_words(const ResBlock &k, int step) {
       if (__ballot(missing) == 0ull) break;
       if (!wait.again()) return -1;
     }
-    open |= !word_finished(w);
+    if (__ballot(!word_finished(w))) top = nt + 1;
     if (l.kq == 0) k.word[slot] = w;
   }
   wave_sync();
-  return __ballot(open) == 0ull ? 1 : 0;
+  k.nt = top;
+  return top == 0 ? 1 : 0;
 }
 // before the first step: hypothesis 0 of every utterance reads the start symbol
-__device__ __forceinline__ int res_first_words(const ResArgs &a, const ResBlock &k) {
+__device__ __forceinline__ int res_first_words(const ResArgs &a, ResBlock &k) {
   const ResLane l = res_lane();
-  bool open = false;
+  int top = 0;
   for (int nt = 0; nt < a.NT; ++nt) {
     const int slot = nt * kResSlot + l.sl;
     const bool used = slot < k.nslots;
-    const bool empty = !used || a.lengths[res_utt(a, k.g, used ? slot / a.K : 0)] == 0;
-    open |= !empty;
+    const bool empty = !used || a.lengths[res_utt(k, used ? slot / a.K : 0)] == 0;
+    if (__ballot(!empty)) top = nt + 1;
     if (l.kq == 0) k.word[slot] = slot_word(-1, empty ? 1 : 0, slot, (used && slot % a.K == 0) ? a.V : -1, 0);
   }
   wave_sync();
-  return __ballot(open) == 0ull ? 1 : 0;
+  k.nt = top;
+  return top == 0 ? 1 : 0;
 }
 
 // ---- P: pre[step] = f_proj[frame] + W_pred h[step] + b_pred for the block's tiles of 16 outputs
@@ -382,8 +386,8 @@ __device__ __forceinline__ bool res_p_phase(ResBlock &k, int step) {
   const int nh = halves ? nr / 2 : nr;  // rounds of a slice: the wave has one in either half of k, or one of the whole
   if constexpr (BF16) {  // one tile of 32 outputs: two waves finish 16 each
 #pragma unroll 1
-    for (int nt = 0; nt < a.NT; nt += 2) {
-      const bool second = nt + 1 < a.NT;
+    for (int nt = 0; nt < k.nt; nt += 2) {
+      const bool second = nt + 1 < k.nt;
       floatx4 f[2] = {floatx4{0.f, 0.f, 0.f, 0.f}, floatx4{0.f, 0.f, 0.f, 0.f}}, bias = f[0];
       if (k.ptile >= 0) {
         bias = res_p_bias(a, k, l);
@@ -421,7 +425,7 @@ __device__ __forceinline__ bool res_p_phase(ResBlock &k, int step) {
     }
   } else {
 #pragma unroll 1
-    for (int nt = 0; nt < a.NT; ++nt) {
+    for (int nt = 0; nt < k.nt; ++nt) {
       floatx4 f = {0.f, 0.f, 0.f, 0.f}, bias = f;
       if (k.ptile >= 0) {
         bias = res_p_bias(a, k, l);
@@ -486,13 +490,12 @@ __device__ __forceinline__ void clear_z(const ResBlock &k, const ResLane &l, con
 
 // Stateless decoders: the wave's slice of pre of its lanes' slots, as res_gather / bf16_gather would have read it, summed up
 // in the order of k_stateless_pre.  All rows of a pair of tables are requested before the first is needed: the time is that
-// of one trip to the L2 (each block of a group reads all of the group's rows, at most 48 x (1 + n_ctx) x 2.5 KB; a
+// of one trip to the L2 (each block of a group reads all of the group's rows, at most 16 x (1 + n_ctx) x 2.5 KB; a
 // hand-over of sums formed once would cost a hop more, and the same trip before it).
 template <bool FULL, bool BF16>
-__device__ __forceinline__ void res_stateless_pre(const ResArgs &a, const ResBlock &k, const ResLane &l, int nt, bool second, int nr,
+__device__ __forceinline__ void res_stateless_pre(const ResArgs &a, const ResBlock &k, const ResLane &l, int nr,
                                                   uint64_t (&x)[(BF16 ? 2 : 1) * kResMaxRounds]) {
-  int slot = (nt + (BF16 && second ? (l.lane >> 4) & 1 : 0)) * kResSlot + l.sl;
-  slot = slot < k.nslots ? slot : 0;  // (places without a slot repeat the first one's rows)
+  const int slot = l.sl < k.nslots ? l.sl : 0;  // (places without a slot repeat the first one's rows)
   const int2 in = k.info[slot];
   const int4 c = k.ctx[slot];
   int tt = word_frame(k.word[slot]);
@@ -531,22 +534,15 @@ __device__ __forceinline__ void res_stateless_pre(const ResArgs &a, const ResBlo
     }
   }
 }
-// the slots' last tokens behind the words that the wave holds
-__device__ __forceinline__ void res_update_ctx(const ResArgs &a, const ResBlock &k) {
+// the slots' last tokens behind the words that the wave holds (a group of a stateless decoder has one tile of slots)
+__device__ __forceinline__ void res_update_ctx(const ResBlock &k) {
   const ResLane l = res_lane();
-  int4 c[kResMaxNT];
-#pragma unroll
-  for (int nt = 0; nt < kResMaxNT; ++nt)
-    if (nt < a.NT) {
-      const uint64_t w = k.word[nt * kResSlot + l.sl];
-      const int tok = word_tok(w);
-      c[nt] = k.ctx[word_src(w)];
-      if (tok >= 0) c[nt] = make_int4(tok, c[nt].x, c[nt].y, c[nt].z);
-    }
+  const uint64_t w = k.word[l.sl];
+  const int tok = word_tok(w);
+  int4 c = k.ctx[word_src(w)];
+  if (tok >= 0) c = make_int4(tok, c.x, c.y, c.z);
   wave_sync();
-#pragma unroll
-  for (int nt = 0; nt < kResMaxNT; ++nt)
-    if (nt < a.NT && l.kq == 0) k.ctx[nt * kResSlot + l.sl] = c[nt];
+  if (l.kq == 0) k.ctx[l.sl] = c;
   wave_sync();
 }
 
@@ -568,10 +564,10 @@ __device__ __forceinline__ bool res_j_phase(ResBlock &k, int step, const float (
   const uint64_t *wx = k.tiles + (size_t)k.nP * (a.P * kResSlot / 2) + (size_t)k.wave * nr * 64 + l.lane;
   if constexpr (BF16) {
 #pragma unroll 1
-    for (int nt = 0; nt < a.NT; nt += 2) {
-      const bool second = nt + 1 < a.NT;
+    for (int nt = 0; nt < k.nt; nt += 2) {
+      const bool second = nt + 1 < k.nt;
       uint64_t x[2 * kResMaxRounds];
-      if constexpr (ST) res_stateless_pre<FULL, true>(a, k, l, nt, second, nr, x);
+      if constexpr (ST) res_stateless_pre<FULL, true>(a, k, l, nr, x);
       else if (!bf16_gather<FULL, kResMaxRounds>(bf16_src(l, ad.p(step, nt), ad.p_tile, second, k.wave * nr), nr, x)) return false;
 #pragma unroll
       for (int t = 0; t < NJ + 1; ++t) {
@@ -600,10 +596,10 @@ __device__ __forceinline__ bool res_j_phase(ResBlock &k, int step, const float (
     }
   } else {
 #pragma unroll 1
-    for (int nt = 0; nt < a.NT; ++nt) {
+    for (int nt = 0; nt < k.nt; ++nt) {
       uint64_t x[kResMaxRounds];
       const uint64_t *src = reinterpret_cast<const uint64_t *>(ad.p(step, nt)) + (size_t)k.wave * nr * 64 + l.lane;
-      if constexpr (ST) res_stateless_pre<FULL, false>(a, k, l, nt, false, nr, x);
+      if constexpr (ST) res_stateless_pre<FULL, false>(a, k, l, nr, x);
       else if (!res_gather<FULL, kResMaxRounds>([src](int i) { return src + i * 64; }, nr, x)) return false;
 #pragma unroll
       for (int i = 0; i < kResMaxRounds; ++i) x[i] = pack2(fmaxf(lo_f(x[i]), 0.f), fmaxf(hi_f(x[i]), 0.f));
@@ -646,7 +642,7 @@ __device__ __forceinline__ bool res_j_phase(ResBlock &k, int step, const float (
 template <bool BF16>
 __device__ __forceinline__ void res_clear_pz(const ResArgs &a, const ResBlock &k, const ResAddr &ad, int step) {
   const ResLane l = res_lane();
-  for (int nt = 0; nt < a.NT; ++nt) {
+  for (int nt = 0; nt < k.nt; ++nt) {
     if (k.ptile >= 0) clear_p(k, l, ad, step, nt);
     if constexpr (BF16) {
       if (k.wave >> 1 == (nt & 1)) {
@@ -662,6 +658,11 @@ __device__ __forceinline__ void res_clear_pz(const ResArgs &a, const ResBlock &k
 // ---------------------------------------------------------------------------
 // blocks that own tiles
 // ---------------------------------------------------------------------------
+// place of the lane's unit of W_hh tile t in the fragment order of h
+__device__ __forceinline__ int res_h_ofs(const ResLane &l, int t) {
+  return ((t >> 1) * 4 + (t & 1) * 2 + (l.kq >> 1)) * (2 * kResSlot) + l.sl * 2 + (l.kq & 1);
+}
+
 template <bool FULL, bool BF16, bool ST>
 __device__ __forceinline__ void res_worker(ResBlock k, const ResTab &tab, float *lds) {
   constexpr int NJ = kResRegJ<BF16>, NR = ST ? 0 : kResMaxR;
@@ -711,7 +712,7 @@ __device__ __forceinline__ void res_worker(ResBlock k, const ResTab &tab, float 
   if constexpr (!ST)
     for (int i = threadIdx.x; i < kResMaxR * a0.NT * (256 + 128); i += kResThreads) Rl[i] = 0.f;
   if (threadIdx.x < a0.NT * kResSlot) {
-    const int b = res_utt(a0, k.g, (int)threadIdx.x < k.nslots ? threadIdx.x / a0.K : 0);
+    const int b = res_utt(k, (int)threadIdx.x < k.nslots ? threadIdx.x / a0.K : 0);
     info[threadIdx.x] = make_int2(a0.lengths[b], b * a0.T);
   }
   k.info = info;
@@ -764,22 +765,18 @@ __device__ __forceinline__ void res_worker(ResBlock k, const ResTab &tab, float 
       const ResLane l = res_lane();
       const ResAddr ad = res_addr(a, k.g);
       const int unit = 8 * (mytile >> 1) + 2 * l.kq + (mytile & 1);
-      const int hofs = ((mytile >> 1) * 4 + (mytile & 1) * 2 + (l.kq >> 1)) * (2 * kResSlot) + l.sl * 2 + (l.kq & 1);
+      const int hofs = res_h_ofs(l, mytile);
       float4 g4[kResMaxNT];
 #pragma unroll
       for (int nt = 0; nt < kResMaxNT; ++nt)
-        if (nt < a.NT) {
+        if (nt < k.nt) {
           const int tok = word_tok(k.word[nt * kResSlot + l.sl]);
           g4[nt] = *reinterpret_cast<const float4 *>(a.G + (size_t)(tok < 0 ? a.V : tok) * 4 * a.P + 4 * unit);
         }
-      // h of three steps ago may be cleared: the words of the last step needed h of the last step from every owner of
-      // W_hh tiles, who had multiplied h of two steps ago (and the one before) by then
-      if (step > 2)
-        for (int nt = 0; nt < a.NT; ++nt) store_agent(reinterpret_cast<uint32_t *>(ad.h(step - 3, nt) + hofs), kResEmpty);
       float cn[kResMaxNT], hn[kResMaxNT];
 #pragma unroll
       for (int nt = 0; nt < kResMaxNT; ++nt)
-        if (nt < a.NT) {
+        if (nt < k.nt) {
           const uint64_t w = k.word[nt * kResSlot + l.sl];
           const int src = word_src(w), at = (k.wave * a.NT + (src >> 4)) * 64 + l.kq * 16 + (src & 15);
           cn[nt] = cl[at];
@@ -791,7 +788,7 @@ __device__ __forceinline__ void res_worker(ResBlock k, const ResTab &tab, float 
       wave_sync();
 #pragma unroll
       for (int nt = 0; nt < kResMaxNT; ++nt)
-        if (nt < a.NT) {
+        if (nt < k.nt) {
           const int at = (k.wave * a.NT + nt) * 64 + l.lane;
           cl[at] = cn[nt];
           hl[at] = hn[nt];
@@ -810,8 +807,17 @@ __device__ __forceinline__ void res_worker(ResBlock k, const ResTab &tab, float 
       const ResLane l = res_lane();
       const ResAddr ad = res_addr(a, k.g);
       const int nrp = FULL ? kResMaxRounds : a.rounds_p;
+      // h of two steps ago is cleared under the selection: the words of the last step needed h of the last step from every
+      // owner of W_hh tiles, who had multiplied h of two steps ago by then.  Who reads the place next (h of two steps on)
+      // has seen words that needed this wave's h of the next step, which it stores behind the acknowledgement of these.
+      // (Cleared ahead of the cell update, the acknowledgement was waited for on the critical path: one utterance 9.19 -> 9.03
+      // ms.  Behind the products below, the clear delays the next step where they outlast the selection: batch 32 / beam 8
+      // 1.3 % slower.)
+      if (step > 1 && k.wave < k.nR)
+        for (int nt = 0; nt < k.nt; ++nt)
+          store_agent(reinterpret_cast<uint32_t *>(ad.h(step - 2, nt) + res_h_ofs(l, mytile)), kResEmpty);
 #pragma unroll 1
-      for (int nt = 0; nt < a.NT; ++nt) {
+      for (int nt = 0; nt < k.nt; ++nt) {
         uint64_t x[kResMaxRounds];
         const uint64_t *src = reinterpret_cast<const uint64_t *>(ad.h(step, nt)) + (size_t)k.wave * nrp * 64 + l.lane;
         if (!res_gather<FULL, kResMaxRounds>([src](int i) { return src + i * 64; }, nrp, x)) return;
@@ -842,7 +848,7 @@ __device__ __forceinline__ void res_worker(ResBlock k, const ResTab &tab, float 
     }
     over = res_words(k, step);
     if constexpr (ST) {
-      if (over == 0) res_update_ctx(res_args(), k);
+      if (over == 0) res_update_ctx(k);
     }
   }
 }
@@ -1148,32 +1154,34 @@ __device__ __forceinline__ void res_selector(ResBlock k, int sel, float *lds) {
       for (int i = 0; i < kCtxMax; ++i) s.ctx[lane][i] = -1;
     }
     rs.slot0 = u * K;
-    rs.T_b = a0.lengths[res_utt(a0, k.g, u)];
+    rs.T_b = a0.lengths[res_utt(k, u)];
     rs.lm = lm_rows + (size_t)k.wave * K * V;
     rs.finished = rs.T_b == 0;
   }
   __syncthreads();
   int over = res_first_words(a0, k);
   for (int step = 0; over == 0; ++step) {
+    // rows in the tiles that are left out (their utterances have finished) do not come
+    const int n_rows = min(n_hyp, k.nt * kResSlot - u0 * K);
     if (has_lm)  // rows of the hypotheses as the last step left them (their histories: behind its last barrier)
-      for (int q = k.wave; q < n_hyp; q += kResWaves)
+      for (int q = k.wave; q < n_rows; q += kResWaves)
         res_lm_row(res_args().lm, scratch[q / K].ctx[q % K], scratch[q / K].len[q % K], lm_rows + (size_t)q * V, L.rec[k.wave]);
-    // (every row is waited for, also those of finished utterances: a word of this step tells the group's other blocks that
+    // (every other row is waited for, also those of finished utterances: a word of this step tells the group's other blocks that
     // all logits of the step were there)
     if (parts == 2) {
       const int q = k.wave >> 1;
-      if (q < n_hyp && !res_row<kResMaxV / 256, KC, PLAIN>(k.g, step, u0 * K + q, late_lm ? lm_rows + (size_t)q * V : nullptr, q, k.wave & 1, 2, L)) return;
+      if (q < n_rows && !res_row<kResMaxV / 256, KC, PLAIN>(k.g, step, u0 * K + q, late_lm ? lm_rows + (size_t)q * V : nullptr, q, k.wave & 1, 2, L)) return;
     } else {
-      for (int q = k.wave; q < n_hyp; q += kResWaves)
+      for (int q = k.wave; q < n_rows; q += kResWaves)
         if (!res_row<kResMaxV / 128, KC, PLAIN>(k.g, step, u0 * K + q, late_lm ? lm_rows + (size_t)q * V : nullptr, q, 0, 1, L)) return;
     }
     __syncthreads();
-    for (int q = k.wave; q < n_hyp; q += kResWaves)
+    for (int q = k.wave; q < n_rows; q += kResWaves)
       res_row_finish<KC, PLAIN>(k.g, step, u0 * K + q, late_lm ? lm_rows + (size_t)q * V : nullptr, q, parts, L);
     __syncthreads();
     if (k.wave < nu) {
       const ResArgs &a = res_args();
-      const int u = u0 + k.wave, b = res_utt(a, k.g, u);
+      const int u = u0 + k.wave, b = res_utt(k, u);
       rs.words = res_addr(a, k.g).w(step) + u * K;
       rs.step = step;
       if (rs.finished) {
@@ -1198,6 +1206,7 @@ template <bool FULL, bool BF16, bool ST, int KC, int PLAIN>
 __global__ __launch_bounds__(kResThreads, 2) void k_decode_resident(ResArgs) {
   extern __shared__ __align__(16) float smem[];
   __shared__ int s_ok;
+  __shared__ int16_t s_order[kResMaxNT * kResSlot];
   const ResArgs &a = res_args();
   if (*reinterpret_cast<const volatile int *>(a.sel.done)) return;
   // every block of the launch must be on the chip before any of them waits for another's data
@@ -1220,13 +1229,27 @@ __global__ __launch_bounds__(kResThreads, 2) void k_decode_resident(ResArgs) {
     }
     s_ok = ok;
   }
-  __syncthreads();
-  if (!s_ok) return;
   ResBlock k;
   // (workgroup i runs on XCD i % 8: the blocks of a group share as few L2s as they can)
   k.g = (int)blockIdx.x % a.n_groups;
   const int rank = (int)blockIdx.x / a.n_groups;
   k.nu = (a.B - k.g + a.n_groups - 1) / a.n_groups;
+  // utterances of the group, g + n_groups i, the longest first: the ends of the slots run empty first, and tiles behind
+  // the last unfinished utterance are left out of every phase (TDT, 64 utterances of 4 to 20 s, beam 4: 5.90 -> 5.22 ms;
+  // 16 utterances of 3 to 10 s, beam 12: 19.70 -> 18.53)
+  if ((int)threadIdx.x < k.nu) {
+    const int mine = a.lengths[k.g + a.n_groups * threadIdx.x];
+    int at = 0;
+    for (int i = 0; i < k.nu; ++i) {
+      const int other = a.lengths[k.g + a.n_groups * i];
+      at += other > mine || (other == mine && i < (int)threadIdx.x);
+    }
+    s_order[at] = (int16_t)(k.g + a.n_groups * threadIdx.x);
+  }
+  k.order = s_order;
+  k.nt = a.NT;
+  __syncthreads();
+  if (!s_ok) return;
   k.nslots = k.nu * a.K;
   k.wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   k.phase = 0;

@@ -29,12 +29,15 @@ CASES = [
     dict(B=20, beam=12, V=1000, s=1, **W640),
     dict(B=40, beam=1, V=1024, **W640),
     dict(B=50, beam=4, V=90, **W640),
-    # stateless decoders: every context length, both precisions, one to three tiles of slots
+    # lengths that let later slot tiles run empty well before the first
+    dict(B=40, beam=8, V=300, T=40, T_min=1, **W640),
+    dict(B=17, beam=13, V=300, T=40, T_min=1, prec="bf16", **W640),
+    # stateless decoders: every context length, both precisions, up to a full tile of slots per group
     dict(B=1, beam=3, V=2, H=64, P=64, E=64, D=32, **ST, ctx=1),
     dict(B=8, beam=4, V=1024, prec="bf16", algo="aes", s=2, **W640, **ST, ctx=2),
-    dict(B=9, beam=13, V=1000, prec="bf16", **W640, **ST, ctx=3),
-    dict(B=25, beam=8, V=257, H=448, P=64, E=64, D=32, **ST, ctx=4),
-    dict(B=40, beam=5, V=1023, **W640, **ST, ctx=2),
+    dict(B=7, beam=13, V=1000, prec="bf16", **W640, **ST, ctx=3),
+    dict(B=16, beam=8, V=257, H=448, P=64, E=64, D=32, **ST, ctx=4),
+    dict(B=23, beam=5, V=1023, **W640, **ST, ctx=2),
     dict(B=30, beam=4, V=129, prec="bf16", H=192, P=192, E=192, D=32, algo="aes", gamma=2.3, **ST, ctx=4, **TDT),
 ]
 
