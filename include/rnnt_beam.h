@@ -89,7 +89,8 @@ typedef struct {
                                 the best one of its hypothesis is not expanded; INFINITY = off */
   int32_t use_graph;         /* 1: no launch per step.  Decoders whose weights fit the chip (H, for LSTM models also P, multiples of
                                 64 up to 640; V <= 1024; no tdt_all_pairs; fused joint) run the step loop as one launch whose blocks keep the weights
-                                on chip ("resident loop"; batches of up to 48 hypotheses per 32 compute units); all others
+                                on chip ("resident loop"; batches of up to 48 hypotheses per 32 compute units,
+                                stateless ones 16); all others
                                 replay the per-step kernels as a captured HIP graph (Sec. 2.1, "CUDA Graphs").  0: the
                                 per-step kernels are launched one by one.  The results are the same bit for bit up to 256
                                 hypotheses.  The resident loop needs every one of its blocks on the chip at once: where they
