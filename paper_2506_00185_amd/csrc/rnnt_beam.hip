@@ -182,7 +182,7 @@ struct rnnt_beam {
   PersistCtl *pctl = nullptr;  // counters of the single-launch step loop
   int n_cus = 0, spin_limit = kSpinLimit;
   int max_lds = 64 * 1024;  // LDS a block may ask for on this device
-  bool last_persistent = false;
+  int last_loop = RNNT_LOOP_LAUNCHES;  // rnnt_step_loop_t of the last decode
   Resident res;         // the step loop as one launch with the weights on chip
   char *h_out = nullptr;          // pinned: the last decode's control words and packed results (see out_pack)
   size_t h_out_bytes = 0;
@@ -1014,17 +1014,18 @@ int run_decode(rnnt_beam *h, const float *enc, const int32_t *lengths, const Ste
   }
   const int max_steps = decode_max_steps(c, w, p.T);
   int rc = RNNT_OK;
-  h->last_persistent = !resident && use_persistent(h, p);
+  const bool use_graph = c.use_graph && !h->profiling && !p.inj_tok && !p.plain;
+  h->last_loop = resident ? RNNT_LOOP_RESIDENT
+                 : use_persistent(h, p) ? RNNT_LOOP_SINGLE_LAUNCH : use_graph ? RNNT_LOOP_GRAPH : RNNT_LOOP_LAUNCHES;
   if (resident) {
     if ((rc = launch_resident(h, s, p))) return rc;
-  } else if (h->last_persistent) {
+  } else if (h->last_loop == RNNT_LOOP_SINGLE_LAUNCH) {
     // one launch walks all steps (it starts with the prediction network on the start symbol itself)
     if ((rc = launch_persistent(h, s, p, max_steps))) return rc;
   } else {
   // prediction network on the start symbol (reads parity 1, writes parity 0), LM on the empty context
   if ((rc = launch_pred(h, s, p, 1, 0))) return rc;
   if ((rc = launch_lm(h, s, p))) return rc;
-  const bool use_graph = c.use_graph && !h->profiling && !p.inj_tok && !p.plain;
   hipGraphExec_t exec = nullptr;
   if (use_graph) {
     // The captured kernel arguments hold the LM's device tables: the key carries the LM's unique id, not its
@@ -1459,7 +1460,7 @@ int rnnt_beam_results(rnnt_beam_t *h, int32_t *tokens, int32_t cap, int32_t *len
       if (n > 0) memcpy(tokens + i * cap, buf + i * w.cap, sizeof(int) * n);
     }
   }
-  if (h->last_persistent) {
+  if (h->last_loop == RNNT_LOOP_SINGLE_LAUNCH) {
     int ab = 0;
     RB_HIP(h, hipMemcpy(&ab, &h->pctl->abort, sizeof(int), hipMemcpyDeviceToHost));
     if (ab == 1) return fail(h, RNNT_E_HIP, "single-launch step loop: a wait between blocks ran into its limit (results invalid)");
@@ -1526,6 +1527,11 @@ int rnnt_beam_debug_block_map(int32_t a_tiles, int32_t a_m, int32_t b_begin, int
     if (mtile) mtile[bid] = r < 0 ? -1 : mt;
   }
   return grid;
+}
+
+int rnnt_beam_last_step_loop(const rnnt_beam_t *h) {
+  if (!h) return RNNT_E_ARG;
+  return h->have_result ? h->last_loop : RNNT_E_NORESULT;
 }
 
 float rnnt_beam_last_decode_ms(rnnt_beam_t *h) {

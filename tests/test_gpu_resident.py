@@ -13,6 +13,7 @@ from gpu_common import gpu_decode
 
 pytestmark = pytest.mark.gpu
 
+KEYS = ("tokens", "lens", "scores", "n_steps", "parent", "token", "merged")
 W640 = dict(H=640, P=640, E=640, D=64)
 ST = dict(pred="stateless")
 TDT = dict(model="tdt", durations=(0, 1, 2, 3, 4))
@@ -35,7 +36,9 @@ CASES = [
     # stateless decoders: every context length, both precisions, up to a full tile of slots per group
     dict(B=1, beam=3, V=2, H=64, P=64, E=64, D=32, **ST, ctx=1),
     dict(B=8, beam=4, V=1024, prec="bf16", algo="aes", s=2, **W640, **ST, ctx=2),
-    dict(B=7, beam=13, V=1000, prec="bf16", **W640, **ST, ctx=3),
+    dict(B=8, beam=13, V=1000, prec="bf16", **W640, **ST, ctx=3),
+    dict(B=1, beam=16, V=1024, **W640, **ST, ctx=3),
+    dict(B=8, beam=10, V=700, algo="aes", **W640, **ST, ctx=1),
     dict(B=16, beam=8, V=257, H=448, P=64, E=64, D=32, **ST, ctx=4),
     dict(B=23, beam=5, V=1023, **W640, **ST, ctx=2),
     dict(B=30, beam=4, V=129, prec="bf16", H=192, P=192, E=192, D=32, algo="aes", gamma=2.3, **ST, ctx=4, **TDT),
@@ -43,22 +46,23 @@ CASES = [
 
 
 @pytest.mark.parametrize("kw", CASES, ids=lambda kw: f"b{kw['B']}_k{kw['beam']}_v{kw['V']}_h{kw['H']}_p{kw['P']}_{kw.get('prec', 'f32')}_ctx{kw.get('ctx', 0)}")
-def test_resident_loop_equals_the_per_step_launches(kw, monkeypatch, capfd):
+def test_resident_loop_equals_the_per_step_launches(kw):
     import paper_2506_00185_amd as A
-    monkeypatch.setenv("RNNT_BEAM_TRACE_PACING", "1")  # (reports a launch that gave up)
     c = S.custom_config(**dict(dict(T=17, T_min=3, s=3, blank_bias=3.0), **kw))
     w = S.perturb_biases(S.make_weights(c, 5), 6)
     L = S.make_lengths(c, 7)
     if c["B"] > 2:
         L[1] = 0
     enc = S.make_enc(c, L, 8)
-    ref = gpu_decode(A.BeamDecoder(c, w, use_graph=False), enc, L)
+    plain = A.BeamDecoder(c, w, use_graph=False)
+    ref = gpu_decode(plain, enc, L)
+    assert plain.last_step_loop() == "launches"
     dec = A.BeamDecoder(c, w)
     for _ in range(2):
         r = gpu_decode(dec, enc, L)
-        for key in ("tokens", "lens", "scores", "n_steps", "parent", "token", "merged"):
+        assert dec.last_step_loop() == "resident"
+        for key in KEYS:
             np.testing.assert_array_equal(r[key], ref[key])
-    assert "gave up" not in capfd.readouterr().err
 
 
 @pytest.mark.parametrize("prune,rule,beam,B,more", [("late", 4, 8, 9, {}), ("early", 3, 4, 17, {}), ("late", 3, 11, 4, {}),
@@ -72,14 +76,15 @@ def test_resident_loop_with_an_lm(prune, rule, beam, B, more):
     lm = A.NGramLM(S.make_lm(V=c["V"], order=4, n_target=20000, zipf_s=1.1, seed=19))
     kw = dict(lm_rule=rule, lm_prune=prune)
     ref = gpu_decode(A.BeamDecoder(c, w, use_graph=False, **kw), enc, L, lm=lm, lm_weight=0.3)
-    r = gpu_decode(A.BeamDecoder(c, w, **kw), enc, L, lm=lm, lm_weight=0.3)
-    for key in ("tokens", "lens", "scores", "n_steps", "parent", "token", "merged"):
+    dec = A.BeamDecoder(c, w, **kw)
+    r = gpu_decode(dec, enc, L, lm=lm, lm_weight=0.3)
+    assert dec.last_step_loop() == "resident"
+    for key in KEYS:
         np.testing.assert_array_equal(r[key], ref[key])
 
 
-def test_resident_loop_that_gives_up_is_replaced_by_the_per_step_launches(monkeypatch, capfd):
+def test_resident_loop_that_gives_up_is_replaced_by_the_per_step_launches():
     import paper_2506_00185_amd as A
-    monkeypatch.setenv("RNNT_BEAM_TRACE_PACING", "1")
     c = S.custom_config(B=9, T=12, T_min=4, s=3, beam=4, V=300, blank_bias=3.0, **W640)
     w = S.make_weights(c, 25)
     L = S.make_lengths(c, 27)
@@ -89,9 +94,9 @@ def test_resident_loop_that_gives_up_is_replaced_by_the_per_step_launches(monkey
     dec.debug_set_spin_limit(1)  # (its blocks then wait in vain for one more)
     for _ in range(2):
         r = gpu_decode(dec, enc, L)
-        for key in ("tokens", "lens", "scores", "n_steps"):
+        assert dec.last_step_loop() == "graph"
+        for key in KEYS:
             np.testing.assert_array_equal(r[key], ref[key])
-    assert "gave up" in capfd.readouterr().err
     dec.debug_set_spin_limit(1 << 22)
     r = gpu_decode(dec, enc, L)
     np.testing.assert_array_equal(r["tokens"], ref["tokens"])
