@@ -1166,6 +1166,8 @@ __device__ __forceinline__ void res_selector(ResBlock k, int sel, float *lds) {
     if (has_lm)  // rows of the hypotheses as the last step left them (their histories: behind its last barrier)
       for (int q = k.wave; q < n_rows; q += kResWaves)
         res_lm_row(res_args().lm, scratch[q / K].ctx[q % K], scratch[q / K].len[q % K], lm_rows + (size_t)q * V, L.rec[k.wave]);
+    // (with two waves per row of logits a wave reads an LM row that another one has written)
+    if (late_lm && parts == 2) __syncthreads();
     // (every other row is waited for, also those of finished utterances: a word of this step tells the group's other blocks that
     // all logits of the step were there)
     if (parts == 2) {

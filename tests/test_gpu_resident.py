@@ -66,10 +66,13 @@ def test_resident_loop_equals_the_per_step_launches(kw):
 
 
 @pytest.mark.parametrize("prune,rule,beam,B,more", [("late", 4, 8, 9, {}), ("early", 3, 4, 17, {}), ("late", 3, 11, 4, {}),
-                                                    ("late", 4, 6, 10, dict(ST, ctx=2))])
+                                                    ("late", 4, 6, 10, dict(ST, ctx=2)),
+                                                    # up to four hypotheses of more than 512 tokens: two waves per row
+                                                    ("late", 4, 4, 1, dict(V=1024)), ("late", 3, 2, 9, dict(V=515)),
+                                                    ("early", 4, 3, 2, dict(V=777))])
 def test_resident_loop_with_an_lm(prune, rule, beam, B, more):
     import paper_2506_00185_amd as A
-    c = S.custom_config(B=B, T=15, T_min=4, s=3, beam=beam, V=300, blank_bias=3.0, **W640, **more)
+    c = S.custom_config(**dict(dict(B=B, T=15, T_min=4, s=3, beam=beam, V=300, blank_bias=3.0, **W640), **more))
     w = S.perturb_biases(S.make_weights(c, 15), 16)
     L = S.make_lengths(c, 17)
     enc = S.make_enc(c, L, 18)
