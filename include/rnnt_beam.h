@@ -276,6 +276,11 @@ int rnnt_beam_debug_block_map(int32_t a_tiles, int32_t a_m, int32_t b_begin, int
  * and the batch is decoded with per-step launches. */
 int rnnt_beam_debug_set_spin_limit(rnnt_beam_t *h, int32_t polls);
 
+/* Test hook for the waits inside the resident loop (use_graph): at step `step` the owners of the output layer publish no
+ * logits for the last tile of 16 hypotheses that they hold and end; the other blocks' waits give up (after 4096 polls
+ * instead of 2^19) and the batch is decoded with per-step launches.  -1 (default): off. */
+int rnnt_beam_debug_stall_resident(rnnt_beam_t *h, int32_t step);
+
 /* Which step loop the last rnnt_beam_decode / rnnt_beam_decode_injected of the handle used (rnnt_step_loop_t; see the
  * config fields use_graph and persistent_kernel), RNNT_E_NORESULT before the first one.  Does not wait for the device. */
 typedef enum { RNNT_LOOP_LAUNCHES = 0, RNNT_LOOP_GRAPH = 1, RNNT_LOOP_SINGLE_LAUNCH = 2, RNNT_LOOP_RESIDENT = 3 } rnnt_step_loop_t;

@@ -88,6 +88,7 @@ struct ResArgs {
   int rounds_h, rounds_p;            // rounds of 8 k per wave slice over H and over P
   int poll_limit, start_limit;       // polls of a data wait; ticks (10 ns) of the wait for all blocks
   int start_blocks;                  // how many those are
+  int stall_step;                    // a test's: from this step on the last tile of slots gets no logits (-1: never)
 };
 
 // The kernel's arguments, read from the argument segment anew at the begin of every phase: kept in scalar registers over
@@ -116,6 +117,14 @@ __device__ __forceinline__ uint64_t pack2(float lo, float hi) {
   return (uint64_t)__float_as_uint(hi) << 32 | __float_as_uint(lo);
 }
 
+// Giving up is a matter of the whole block: a wave whose wait fails leaves a flag in LDS and ends (the barriers no longer
+// count it), and every wave looks at the flag behind each barrier that follows a wait, before it uses or publishes what
+// the others should have left in LDS.
+__device__ __forceinline__ volatile int &res_gave_up_word() {
+  __shared__ int word;
+  return word;
+}
+__device__ __forceinline__ bool res_gave_up() { return __builtin_amdgcn_readfirstlane(res_gave_up_word()) != 0; }
 // bounded waiting: true while another poll may follow
 struct ResWait {
   int n = 0;
@@ -128,6 +137,8 @@ struct ResWait {
     if (n < a.poll_limit && !load_agent(a.ctl + 1)) return true;
     store_agent(a.ctl + 1, 1);
     *a.h_abort = 1;
+    res_gave_up_word() = 1;
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");  // (ahead of the wave's end)
     return false;
   }
 };
@@ -415,6 +426,7 @@ __device__ __forceinline__ bool res_p_phase(ResBlock &k, int step) {
         }
       }
       __syncthreads();
+      if (res_gave_up()) return false;
       if (k.ptile >= 0) res_p_finish<true>(a, k, l, ad, step, nt, k.ptile & 1, 2 + (k.ptile & 1), bias, f[0]);
       ++k.phase;
       if (second) {
@@ -466,6 +478,7 @@ __device__ __forceinline__ bool res_p_phase(ResBlock &k, int step) {
           res_put<false>(k, l, 0, acc);
         }
         __syncthreads();
+        if (res_gave_up()) return false;
         if (k.wave == res_p_wave(tp)) res_p_finish<false>(a, k, l, ad, step, nt, 0, 1, bias, f);
         ++k.phase;
       }
@@ -566,6 +579,7 @@ __device__ __forceinline__ bool res_j_phase(ResBlock &k, int step, const float (
 #pragma unroll 1
     for (int nt = 0; nt < k.nt; nt += 2) {
       const bool second = nt + 1 < k.nt;
+      if (step == a.stall_step && nt + 2 >= k.nt) return false;
       uint64_t x[2 * kResMaxRounds];
       if constexpr (ST) res_stateless_pre<FULL, true>(a, k, l, nr, x);
       else if (!bf16_gather<FULL, kResMaxRounds>(bf16_src(l, ad.p(step, nt), ad.p_tile, second, k.wave * nr), nr, x)) return false;
@@ -590,6 +604,7 @@ __device__ __forceinline__ bool res_j_phase(ResBlock &k, int step, const float (
         bf16_put(k, l, 0, 0, acc);
         if (second) bf16_put(k, l, 2, 1, acc);
         __syncthreads();
+        if (res_gave_up()) return false;
         if (k.wave < (second ? 4 : 2)) res_j_finish<true>(k, l, ad, step, nt + (k.wave >> 1), k.jtile[t], bias[t], k.wave);
         ++k.phase;
       }
@@ -597,6 +612,7 @@ __device__ __forceinline__ bool res_j_phase(ResBlock &k, int step, const float (
   } else {
 #pragma unroll 1
     for (int nt = 0; nt < k.nt; ++nt) {
+      if (step == a.stall_step && nt + 1 == k.nt) return false;
       uint64_t x[kResMaxRounds];
       const uint64_t *src = reinterpret_cast<const uint64_t *>(ad.p(step, nt)) + (size_t)k.wave * nr * 64 + l.lane;
       if constexpr (ST) res_stateless_pre<FULL, false>(a, k, l, nr, x);
@@ -629,6 +645,7 @@ __device__ __forceinline__ bool res_j_phase(ResBlock &k, int step, const float (
         res_put<false>(k, l, NJ, c);
       }
       __syncthreads();
+      if (res_gave_up()) return false;
       if (k.jtile[0] >= 0) res_j_finish<false>(k, l, ad, step, nt, k.jtile[0], bias[0], k.wave);
       ++k.phase;
     }
@@ -840,6 +857,7 @@ __device__ __forceinline__ void res_worker(ResBlock k, const ResTab &tab, float 
           for (int t = 0; t < 3; ++t)
             if (t0 + t < k.nR) res_put<BF16>(k, l, t, acc[t]);
           __syncthreads();
+          if (res_gave_up()) return;
           if (k.wave >= t0 && k.wave < t0 + 3 && k.wave < k.nR)
             *reinterpret_cast<floatx4 *>(Rl + ((k.wave * a.NT + nt) * 64 + l.lane) * 4) = res_sum<BF16>(k, l, k.wave - t0);
           ++k.phase;
@@ -1178,6 +1196,7 @@ __device__ __forceinline__ void res_selector(ResBlock k, int sel, float *lds) {
         if (!res_row<kResMaxV / 128, KC, PLAIN>(k.g, step, u0 * K + q, late_lm ? lm_rows + (size_t)q * V : nullptr, q, 0, 1, L)) return;
     }
     __syncthreads();
+    if (res_gave_up()) return;
     for (int q = k.wave; q < n_rows; q += kResWaves)
       res_row_finish<KC, PLAIN>(k.g, step, u0 * K + q, late_lm ? lm_rows + (size_t)q * V : nullptr, q, parts, L);
     __syncthreads();
@@ -1248,6 +1267,7 @@ __global__ __launch_bounds__(kResThreads, 2) void k_decode_resident(ResArgs) {
     }
     s_order[at] = (int16_t)(k.g + a.n_groups * threadIdx.x);
   }
+  if (threadIdx.x == 0) res_gave_up_word() = 0;
   k.order = s_order;
   k.nt = a.NT;
   __syncthreads();

@@ -42,6 +42,7 @@ void resident_destroy(Resident &r);
 
 struct ResidentBatch {
   int B, T, K, algo, spin_limit;
+  int stall_step;   // see ResArgs
   bool halves;      // the per-step launches would split the projection along k at this size
   const float *b_out, *b_pred, *G, *f_proj;
   const float *emb_tab;  // stateless decoders (see ResArgs), else null

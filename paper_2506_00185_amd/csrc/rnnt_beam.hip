@@ -180,7 +180,7 @@ struct rnnt_beam {
   float *Wspec = nullptr, *bias_spec = nullptr, *b_big = nullptr;
   Workspace ws;         // the handle's own workspace, laid out for max_B / max_T / max_beam in one allocation
   PersistCtl *pctl = nullptr;  // counters of the single-launch step loop
-  int n_cus = 0, spin_limit = kSpinLimit;
+  int n_cus = 0, spin_limit = kSpinLimit, stall_step = -1;
   int max_lds = 64 * 1024;  // LDS a block may ask for on this device
   int last_loop = RNNT_LOOP_LAUNCHES;  // rnnt_step_loop_t of the last decode
   Resident res;         // the step loop as one launch with the weights on chip
@@ -940,6 +940,7 @@ int launch_resident(rnnt_beam *h, hipStream_t s, const StepPlan &p) {
   ResidentBatch b{};
   b.B = p.B; b.T = p.T; b.K = p.K; b.algo = p.algo;
   b.spin_limit = h->spin_limit;
+  b.stall_step = h->stall_step;
   b.halves = c.pred == RNNT_PRED_LSTM && proj_split(c, p.M);
   b.b_out = h->b_out; b.b_pred = h->b_pred; b.G = h->G; b.f_proj = w.f_proj;
   if (c.pred == RNNT_PRED_STATELESS) {
@@ -1545,6 +1546,12 @@ float rnnt_beam_last_decode_ms(rnnt_beam_t *h) {
 int rnnt_beam_debug_set_spin_limit(rnnt_beam_t *h, int32_t polls) {
   if (!h || polls < 1) return RNNT_E_ARG;
   h->spin_limit = polls;
+  return RNNT_OK;
+}
+
+int rnnt_beam_debug_stall_resident(rnnt_beam_t *h, int32_t step) {
+  if (!h || step < -1) return RNNT_E_ARG;
+  h->stall_step = step;
   return RNNT_OK;
 }
 

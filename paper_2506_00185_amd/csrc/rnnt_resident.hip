@@ -58,6 +58,8 @@ __global__ void k_resident_init(ResArgs a) {
 
 constexpr int kResShortSpin = 1000;  // a test's limit: the launch waits, for a microsecond, for one block more than it has
 
+constexpr int kResStallPolls = 4096;  // a test's wait for data that does not come
+
 struct Plan {
   bool ok = false;
   int n_groups = 0, n_blocks = 0, nu = 0, n_sel = 0, upc = 0, NT = 0;
@@ -232,7 +234,8 @@ hipError_t resident_launch(Resident &r, const rnnt_config_t &c, const ResidentBa
   a.n_groups = p.n_groups; a.n_sel = p.n_sel; a.upc = p.upc;
   a.NT = p.NT; a.halves = b.halves ? 1 : 0; a.has_lm = b.has_lm ? 1 : 0;
   a.rounds_h = c.H / 64; a.rounds_p = c.P / 64;
-  a.poll_limit = std::min(1 << 19, b.spin_limit);
+  a.stall_step = b.stall_step;
+  a.poll_limit = std::min(b.stall_step < 0 ? 1 << 19 : kResStallPolls, b.spin_limit);
   const bool short_spin = b.spin_limit < kResShortSpin;
   a.start_blocks = p.n_groups * p.n_blocks + (short_spin ? 1 : 0);
   a.start_limit = short_spin ? 100 : 5000000;  // 50 ms

@@ -103,3 +103,28 @@ def test_resident_loop_that_gives_up_is_replaced_by_the_per_step_launches():
     dec.debug_set_spin_limit(1 << 22)
     r = gpu_decode(dec, enc, L)
     np.testing.assert_array_equal(r["tokens"], ref["tokens"])
+
+
+@pytest.mark.parametrize("kw", [dict(beam=12), dict(beam=12, prec="bf16", B=24), dict(beam=4, B=8), dict(beam=4, B=8, **ST, ctx=2)],
+                         ids=["straddles_two_tiles", "bf16", "one_tile", "stateless"])
+@pytest.mark.parametrize("step", [0, 1, 5])
+def test_logits_that_do_not_come_end_the_resident_loop_as_a_whole(kw, step):
+    """The hypotheses of an utterance lie in two tiles of slots and the logits of the second never come: the block that selects
+    for it has some rows and not others.  Every wave of it ends, and what the per-step launches then decode is the result."""
+    import paper_2506_00185_amd as A
+    c = S.custom_config(**dict(dict(B=16, T=12, T_min=8, s=3, V=300, blank_bias=3.0, **W640), **kw))
+    w = S.make_weights(c, 35)
+    L = S.make_lengths(c, 37)
+    enc = S.make_enc(c, L, 38)
+    ref = gpu_decode(A.BeamDecoder(c, w, use_graph=False), enc, L)
+    dec = A.BeamDecoder(c, w)
+    dec.debug_stall_resident(step)
+    r = gpu_decode(dec, enc, L)
+    assert dec.last_step_loop() == "graph"
+    for key in KEYS:
+        np.testing.assert_array_equal(r[key], ref[key])
+    dec.debug_stall_resident(-1)
+    for _ in range(2):
+        r = gpu_decode(dec, enc, L)
+        for key in KEYS:
+            np.testing.assert_array_equal(r[key], ref[key])
