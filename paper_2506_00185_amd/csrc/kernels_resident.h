@@ -70,6 +70,7 @@ __host__ __device__ inline int res_k_of(int round, int kq, int e) { return 8 * r
 
 struct ResArgs {
   const float *WR, *WJ, *WP;         // [tile][round][64 lanes][2] (bf16 models: WR only)
+  const float *WJs;                  // the tile that begins with the blank column, for res_fold_mma: see k_pack_fold
   const uint64_t *WJb, *WPb;         // bf16 models: [32-row tile][round][64 lanes] four bf16 (k of the lane's half)
   const float *b_out, *b_pred, *G, *f_proj;
   const float *emb_tab;              // stateless decoders: [n_ctx][V + 1][H], else null
@@ -88,6 +89,7 @@ struct ResArgs {
   int rounds_h, rounds_p;            // rounds of 8 k per wave slice over H and over P
   int poll_limit, start_limit;       // polls of a data wait; ticks (10 ns) of the wait for all blocks
   int start_blocks;                  // how many those are
+  int fold;                          // the per-step launches would fold the blank and duration columns (see res_fold_mma)
   int stall_step;                    // a test's: from this step on the last tile of slots gets no logits (-1: never)
 };
 
@@ -119,7 +121,7 @@ __device__ __forceinline__ uint64_t pack2(float lo, float hi) {
 
 // Giving up is a matter of the whole block: a wave whose wait fails leaves a flag in LDS and ends (the barriers no longer
 // count it), and every wave looks at the flag behind each barrier that follows a wait, before it uses or publishes what
-// the others should have left in LDS.
+// the others should have left in LDS.  (Reading the flag along with that and looking at it last: 1 to 3 % slower.)
 __device__ __forceinline__ volatile int &res_gave_up_word() {
   __shared__ int word;
   return word;
@@ -215,8 +217,10 @@ struct ResBlock {
   const int16_t *order;              // LDS: the group's utterances (indices in the batch), longest first
   int nR, nJ, nP;
   int wave;
+  int fold;                          // the first output-layer tile holds the blank and duration columns, and they are folded
   int ptile, jtile[2];               // the tile of 16 outputs / columns whose sums this wave finishes (-1: none)
   float *red;                        // LDS: partial sums (two halves that alternate)
+  const uint64_t *spec;              // LDS: see res_fold_bf16
   const uint64_t *tiles;             // LDS: weights of up to kResMaxLdsTiles tiles
   const int2 *info;                  // LDS: frames of the slot's utterance, its first row of f_proj
   uint64_t *word;                    // LDS: this wave's copy of the last step's words, [slot tile][16]
@@ -346,19 +350,20 @@ __device__ __forceinline__ void clear_p(const ResBlock &k, const ResLane &l, con
 // the wave that finishes a tile of the projection: from the last one down, which own no cells
 __device__ __forceinline__ int res_p_wave(int tile_no) { return kResWaves - 1 - tile_no; }
 
-// Operand of a bf16 matrix instruction (32 x 32 x 16) from two rounds of activations: lane (slot column, half of k)
-__device__ __forceinline__ floatx16 mfma_pair_bf16(uint64_t w0, uint64_t w1, const uint64_t *x0, const uint64_t *x1, bool two,
-                                                   bool relu, floatx16 acc) {
-  const uintx4_t w = {(uint32_t)w0, (uint32_t)(w0 >> 32), two ? (uint32_t)w1 : 0u, two ? (uint32_t)(w1 >> 32) : 0u};
-  float v[8] = {lo_f(x0[0]), lo_f(x0[1]), hi_f(x0[0]), hi_f(x0[1]), 0.f, 0.f, 0.f, 0.f};
-  if (two) {
-    v[4] = lo_f(x1[0]); v[5] = lo_f(x1[1]); v[6] = hi_f(x1[0]); v[7] = hi_f(x1[1]);
-  }
-  if (relu) {
+// A round of activations (lane: slot column, half of k) rounded to bf16, the four k in order
+template <bool RELU>
+__device__ __forceinline__ uint64_t round_bf16(const uint64_t *x) {
+  float v[4] = {lo_f(x[0]), lo_f(x[1]), hi_f(x[0]), hi_f(x[1])};
+  if constexpr (RELU) {
 #pragma unroll
-    for (int i = 0; i < 8; ++i) v[i] = fmaxf(v[i], 0.f);
+    for (int i = 0; i < 4; ++i) v[i] = fmaxf(v[i], 0.f);
   }
-  const uintx4_t b = {pack_bf16_rne(v[0], v[1]), pack_bf16_rne(v[2], v[3]), pack_bf16_rne(v[4], v[5]), pack_bf16_rne(v[6], v[7])};
+  return (uint64_t)pack_bf16_rne(v[2], v[3]) << 32 | pack_bf16_rne(v[0], v[1]);
+}
+// bf16 matrix instruction (32 x 32 x 16) on two rounds
+__device__ __forceinline__ floatx16 mfma_pair_bf16(uint64_t w0, uint64_t w1, uint64_t x0, uint64_t x1, bool two, floatx16 acc) {
+  const uintx4_t w = {(uint32_t)w0, (uint32_t)(w0 >> 32), two ? (uint32_t)w1 : 0u, two ? (uint32_t)(w1 >> 32) : 0u};
+  const uintx4_t b = {(uint32_t)x0, (uint32_t)(x0 >> 32), two ? (uint32_t)x1 : 0u, two ? (uint32_t)(x1 >> 32) : 0u};
   return __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8_t, w), __builtin_bit_cast(bf16x8_t, b), acc, 0, 0, 0);
 }
 // lane (column c, half): the two words of a round; columns 16..31 are the next slot tile (or a repeat)
@@ -416,7 +421,8 @@ __device__ __forceinline__ bool res_p_phase(ResBlock &k, int step) {
         for (int i = 0; i < kResMaxRounds / 2; ++i)
           if (2 * i < nh) {
             const bool two = 2 * i + 1 < nh;
-            acc = mfma_pair_bf16(w[(r0 + 2 * i) * 64], w[(r0 + 2 * i + (two ? 1 : 0)) * 64], x + 4 * i, x + 4 * i + 2, two, false, acc);
+            acc = mfma_pair_bf16(w[(r0 + 2 * i) * 64], w[(r0 + 2 * i + (two ? 1 : 0)) * 64], round_bf16<false>(x + 4 * i),
+                                 round_bf16<false>(x + 4 * i + 2), two, acc);
           }
         bf16_put(k, l, 2 * hf, 0, acc);
         if (second) {  // the other slot tile's sums go to the other half of the buffer
@@ -547,6 +553,50 @@ __device__ __forceinline__ void res_stateless_pre(const ResArgs &a, const ResBlo
     }
   }
 }
+// The blank and duration columns where the per-step launches fold them into the token columns' blocks (see joint_tile): per
+// wave slice and half of every eight k a chain of its own, then the halves' sum, then the slices'.
+// Float32: one matrix instruction takes the four k of a half.  x: two k of a round, {0, 4, 1, 5}[kq] and two further; the
+// swaps (rows 2, 3 of the first with rows 0, 1 of the second, then odd rows with even ones) leave k = kq and 4 + kq.  The
+// weights lie that way (k_pack_fold).  other: the block's second tile, in the usual order, between the two chains.
+__device__ __forceinline__ floatx4 res_fold_mma(const float (&w)[2 * kResMaxRounds], const uint64_t (&x)[kResMaxRounds],
+                                                const float (&w_other)[2 * kResMaxRounds], floatx4 &other) {
+  floatx4 lo = {0.f, 0.f, 0.f, 0.f}, hi = lo;
+#pragma unroll
+  for (int i = 0; i < kResMaxRounds; ++i) {
+    const auto s32 = __builtin_amdgcn_permlane32_swap((uint32_t)x[i], (uint32_t)(x[i] >> 32), false, false);
+    const auto s16 = __builtin_amdgcn_permlane16_swap(s32[0], s32[1], false, false);
+    other = mfma16(w_other[2 * i], lo_f(x[i]), other);
+    lo = mfma16(w[2 * i], __uint_as_float(s16[0]), lo);
+    other = mfma16(w_other[2 * i + 1], hi_f(x[i]), other);
+    hi = mfma16(w[2 * i + 1], __uint_as_float(s16[1]), hi);
+  }
+  return lo + hi;
+}
+// bf16 operands: the lane (column, half) has the half's k in order, and the chain is one of fused multiply-adds.  The weights
+// lie in LDS (k.spec), [column][round of all slices][half] four bf16.  (The other columns of the tile are beyond the last one.)
+__device__ __forceinline__ void res_fold_bf16(const ResBlock &k, const ResLane &l, int n_cols, bool second,
+                                              const uint64_t (&xb)[kResMaxRounds]) {
+  const int half = l.lane >> 5, c = l.lane & 31;
+  auto up = [](uint32_t lo16) { return __uint_as_float(lo16 << 16); };
+#pragma unroll 1
+  for (int n = 0; n < n_cols; ++n) {
+    const uint64_t *w = k.spec + (n * (8 * kResMaxRounds) + k.wave * kResMaxRounds) * 2 + half;
+    float part = 0.f;
+#pragma unroll
+    for (int i = 0; i < kResMaxRounds; ++i) {
+      const uint64_t u = w[2 * i];
+      const uint32_t b0 = (uint32_t)xb[i], b1 = (uint32_t)(xb[i] >> 32);
+      part = fmaf(up((uint32_t)u & 0xffffu), up(b0 & 0xffffu), part);
+      part = fmaf(up((uint32_t)u >> 16), up(b0 >> 16), part);
+      part = fmaf(up((uint32_t)(u >> 32) & 0xffffu), up(b1 & 0xffffu), part);
+      part = fmaf(up((uint32_t)(u >> 48)), up(b1 >> 16), part);
+    }
+    const auto s = __builtin_amdgcn_permlane32_swap(__float_as_uint(part), __float_as_uint(part), false, false);
+    part = __uint_as_float(s[0]) + __uint_as_float(s[1]);
+    if (half == 0 && (c < kResSlot || second))
+      res_red<true>(k, (c >> 4) * 2)[(k.wave * 64 + (n >> 2) * 16 + (c & 15)) * 4 + (n & 3)] = part;
+  }
+}
 // the slots' last tokens behind the words that the wave holds (a group of a stateless decoder has one tile of slots)
 __device__ __forceinline__ void res_update_ctx(const ResBlock &k) {
   const ResLane l = res_lane();
@@ -583,9 +633,25 @@ __device__ __forceinline__ bool res_j_phase(ResBlock &k, int step, const float (
       uint64_t x[2 * kResMaxRounds];
       if constexpr (ST) res_stateless_pre<FULL, true>(a, k, l, nr, x);
       else if (!bf16_gather<FULL, kResMaxRounds>(bf16_src(l, ad.p(step, nt), ad.p_tile, second, k.wave * nr), nr, x)) return false;
+      uint64_t xb[kResMaxRounds];
+#pragma unroll
+      for (int i = 0; i < kResMaxRounds; ++i) xb[i] = round_bf16<true>(x + 2 * i);
+      auto put_out = [&](int t) {
+        __syncthreads();
+        if (res_gave_up()) return false;
+        if (k.wave < (second ? 4 : 2)) res_j_finish<true>(k, l, ad, step, nt + (k.wave >> 1), k.jtile[t], bias[t], k.wave);
+        ++k.phase;
+        return true;
+      };
 #pragma unroll
       for (int t = 0; t < NJ + 1; ++t) {
         if (t >= k.nJ) break;
+        if constexpr (FULL)
+          if (t == 0 && k.fold) {
+            res_fold_bf16(k, l, a.N - a.V, second, xb);
+            if (!put_out(t)) return false;
+            continue;
+          }
         floatx16 acc = {0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0};
 #pragma unroll
         for (int i = 0; i < kResMaxRounds / 2; ++i)
@@ -599,14 +665,11 @@ __device__ __forceinline__ bool res_j_phase(ResBlock &k, int step, const float (
               w0 = wx[2 * i * 64];
               w1 = wx[(2 * i + (two ? 1 : 0)) * 64];
             }
-            acc = mfma_pair_bf16(w0, w1, x + 4 * i, x + 4 * i + 2, two, true, acc);
+            acc = mfma_pair_bf16(w0, w1, xb[2 * i], xb[2 * i + 1], two, acc);
           }
         bf16_put(k, l, 0, 0, acc);
         if (second) bf16_put(k, l, 2, 1, acc);
-        __syncthreads();
-        if (res_gave_up()) return false;
-        if (k.wave < (second ? 4 : 2)) res_j_finish<true>(k, l, ad, step, nt + (k.wave >> 1), k.jtile[t], bias[t], k.wave);
-        ++k.phase;
+        if (!put_out(t)) return false;
       }
     }
   } else {
@@ -622,14 +685,19 @@ __device__ __forceinline__ bool res_j_phase(ResBlock &k, int step, const float (
       floatx4 acc[NJ];
 #pragma unroll
       for (int t = 0; t < NJ; ++t) acc[t] = floatx4{0.f, 0.f, 0.f, 0.f};
+      if (FULL && k.fold) {
+        static_assert(NJ == 2);
+        acc[0] = res_fold_mma(wj[0], x, wj[1], acc[1]);
+      } else {
 #pragma unroll
-      for (int i = 0; i < kResMaxRounds; ++i)
-        if (FULL || i < nr) {
+        for (int i = 0; i < kResMaxRounds; ++i)
+          if (FULL || i < nr) {
 #pragma unroll
-          for (int t = 0; t < NJ; ++t) acc[t] = mfma16(wj[t][2 * i], lo_f(x[i]), acc[t]);
+            for (int t = 0; t < NJ; ++t) acc[t] = mfma16(wj[t][2 * i], lo_f(x[i]), acc[t]);
 #pragma unroll
-          for (int t = 0; t < NJ; ++t) acc[t] = mfma16(wj[t][2 * i + 1], hi_f(x[i]), acc[t]);
-        }
+            for (int t = 0; t < NJ; ++t) acc[t] = mfma16(wj[t][2 * i + 1], hi_f(x[i]), acc[t]);
+          }
+      }
 #pragma unroll
       for (int t = 0; t < NJ; ++t)
         if (t < k.nJ) res_put<false>(k, l, t, acc[t]);
@@ -687,6 +755,7 @@ __device__ __forceinline__ void res_worker(ResBlock k, const ResTab &tab, float 
   k.nR = res_uniform(tab.nR);
   k.nJ = res_uniform(tab.nJ);
   k.nP = res_uniform(tab.nP);
+  k.fold = res_uniform(FULL && a0.fold && k.nJ > 0 && tab.J[0] == a0.V / (BF16 ? 32 : 16));
   // which tile's sums this wave finishes, and the tile whose cells it updates
   int pt = -1, jt0 = -1, jt1 = -1;
   if constexpr (BF16) {  // two waves per 32-row tile (output layer: two more for the second slot tile)
@@ -721,6 +790,16 @@ __device__ __forceinline__ void res_worker(ResBlock k, const ResTab &tab, float 
       for (int i = threadIdx.x; i < h4; i += kResThreads) dst[i] = src[i];
       dst += h4;
     }
+    if (BF16 && k.fold) {  // the weights of the blank and duration columns: the words of their lanes, round by round
+      uint64_t *spec = reinterpret_cast<uint64_t *>(dst);
+      const int n = (a0.N - a0.V) * (a0.H / 8) * 2;
+      for (int i = threadIdx.x; i < n; i += kResThreads) {
+        const int col = i / (a0.H / 4), at = i % (a0.H / 4);
+        spec[i] = a0.WJb[((size_t)tab.J[0] * (a0.H / 8) + (at >> 1)) * 64 + col + 32 * (at & 1)];
+      }
+      k.spec = spec;
+      dst += n / 2;
+    }
     k.red = reinterpret_cast<float *>(dst);
   }
   // LDS of the cells: sums W_hh h of the block's tiles, cell state and hidden state of their units, [tile][slot tile][64]
@@ -747,8 +826,9 @@ __device__ __forceinline__ void res_worker(ResBlock k, const ResTab &tab, float 
       for (int i = 0; i < kResMaxRounds; ++i) {
         wj[t][2 * i] = wj[t][2 * i + 1] = 0.f;
         if (t < k.nJ && (FULL || i < nrh)) {
-          const uint64_t v = ((BF16 ? a0.WJb : reinterpret_cast<const uint64_t *>(a0.WJ)) +
-                              ((size_t)tab.J[t] * (a0.H / 8) + k.wave * nrh) * 64 + l0.lane)[i * 64];
+          const bool fold = !BF16 && t == 0 && k.fold;
+          const uint64_t v = ((BF16 ? a0.WJb : reinterpret_cast<const uint64_t *>(fold ? a0.WJs : a0.WJ)) +
+                              ((size_t)(fold ? 0 : tab.J[t]) * (a0.H / 8) + k.wave * nrh) * 64 + l0.lane)[i * 64];
           wj[t][2 * i] = lo_f(v);
           wj[t][2 * i + 1] = hi_f(v);
         }

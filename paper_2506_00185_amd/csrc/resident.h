@@ -19,7 +19,7 @@ struct Resident {
   bool usable = false;
   int n_cus = 0, max_lds = 0;
   int misses = 0;                 // launches that gave up; after kResidentMaxMisses the handle stays with the per-step launches
-  float *WR = nullptr, *WJ = nullptr, *WP = nullptr;
+  float *WR = nullptr, *WJ = nullptr, *WJs = nullptr, *WP = nullptr;
   uint64_t *WJb = nullptr, *WPb = nullptr;
   float *hb = nullptr, *pb = nullptr, *zb = nullptr;
   uint64_t *words = nullptr;
@@ -44,6 +44,7 @@ struct ResidentBatch {
   int B, T, K, algo, spin_limit;
   int stall_step;   // see ResArgs
   bool halves;      // the per-step launches would split the projection along k at this size
+  bool fold;        // they would fold the blank and duration columns into the token columns' blocks
   const float *b_out, *b_pred, *G, *f_proj;
   const float *emb_tab;  // stateless decoders (see ResArgs), else null
   int n_ctx;
@@ -54,7 +55,7 @@ struct ResidentBatch {
   SelectArgs sel;   // n_chunks = 1
 };
 // whether a batch of this shape can run as one resident launch
-bool resident_fits(const Resident &r, const rnnt_config_t &c, int B, int K, int T, int max_steps, bool has_lm);
+bool resident_fits(const Resident &r, const rnnt_config_t &c, int B, int K, int T, int max_steps, bool has_lm, bool fold);
 hipError_t resident_launch(Resident &r, const rnnt_config_t &c, const ResidentBatch &b, hipStream_t s);
 
 }  // namespace rb

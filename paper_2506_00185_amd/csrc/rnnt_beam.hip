@@ -260,6 +260,19 @@ bool proj_split(const rnnt_config_t &c, int M) {
   return c.P % 128 == 0 && M >= 8 && (c.H / 32) * ((M + 31) / 32) * 2 <= 200;
 }
 
+// utterances per joint tile: one wave of the completing block each
+int joint_upt(int K) { return 32 / K < 8 ? 32 / K : 8; }
+
+// More joint blocks than compute units, and the blank / duration columns alone in the last chunk: its blocks would start
+// when the first ones end, and the selection would wait for them.  The token chunks' blocks take those columns instead
+// (one each), as dot products on the operands that they hold in registers.  (The resident loop forms those columns' sums in
+// the same order then: which of the two decodes a batch is not to be seen in the result.)
+bool fold_specials(const rnnt_config_t &c, int n_chunks, int B, int K) {
+  const int n_jtiles = (B + joint_upt(K) - 1) / joint_upt(K);
+  return c.V % 32 == 0 && c.H == 640 && (c.pred != RNNT_PRED_LSTM || c.P == 640) && n_chunks - 1 >= 1 + c.n_durations &&
+         n_chunks * n_jtiles > 256;
+}
+
 // Gate tiles of the recurrent product computed in the prediction-projection launch (the rest ride in the
 // main launch): as many as fit beside the projection's own blocks, one block per compute unit, on every XCD
 // (32 compute units each).
@@ -768,7 +781,7 @@ int launch_step(rnnt_beam *h, hipStream_t s, const StepPlan &p, int step_off, in
     a.M = p.M; a.Mp = w.Mp; a.K = p.K; a.H = c.H; a.V = c.V; a.ND = c.n_durations;
     a.n_chunks = h->n_chunks;
     a.round_ops = c.prec == RNNT_BF16_JOINT ? 1 : 0;
-    a.upt = 32 / p.K < 8 ? 32 / p.K : 8;  // one wave of the completing block per utterance
+    a.upt = joint_upt(p.K);
     a.rpt = a.upt * p.K;
     a.n_jtiles = (p.B + a.upt - 1) / a.upt;
     a.p_max = w.p_max; a.p_sum = w.p_sum; a.p_cand = w.p_cand; a.zs = w.zs;
@@ -777,11 +790,7 @@ int launch_step(rnnt_beam *h, hipStream_t s, const StepPlan &p, int step_off, in
     if (lstm && proj_split(c, p.M) && cur) a.pre = w.pre2;  // (see launch_pred: the buffers alternate with the steps)
     a.rec.Whh = h->W_hh; a.rec.h = w.h[cur]; a.rec.R = w.Rgates;
     a.rec.P = c.P; a.rec.M = p.M; a.rec.Mp = w.Mp; a.rec.group = recurrent_group(c, p.M);
-    // More joint blocks than compute units, and the blank / duration columns alone in the last chunk: its blocks
-    // would start when the first ones end, and the selection would wait for them.  The token chunks' blocks take
-    // those columns instead (one each), as dot products on the operands that they hold in registers.
-    const bool fold = c.V % 32 == 0 && c.H == 640 && (!lstm || c.P == 640) && a.n_chunks - 1 >= 1 + c.n_durations &&
-                      a.n_chunks * a.n_jtiles > 256;
+    const bool fold = fold_specials(c, a.n_chunks, p.B, p.K);
     a.n_jchunks = fold ? a.n_chunks - 1 : a.n_chunks;
     a.map.a_tiles = a.n_jchunks; a.map.a_m = a.n_jtiles;
     a.map.b_begin = lstm ? recurrent_split(c, p.M) : 0;
@@ -931,7 +940,8 @@ int decode_max_steps(const rnnt_config_t &c, const Workspace &w, int T) {
 bool use_resident(const rnnt_beam *h, const StepPlan &p) {
   const rnnt_config_t &c = h->cfg;
   if (!c.use_graph || c.persistent_kernel || h->profiling || p.inj_tok || p.plain || p.ahead || p.big) return false;
-  return resident_fits(h->res, c, p.B, p.K, p.T, decode_max_steps(c, *p.ws, p.T), p.lm != nullptr);
+  return resident_fits(h->res, c, p.B, p.K, p.T, decode_max_steps(c, *p.ws, p.T), p.lm != nullptr,
+                       fold_specials(c, h->n_chunks, p.B, p.K));
 }
 
 int launch_resident(rnnt_beam *h, hipStream_t s, const StepPlan &p) {
@@ -942,6 +952,7 @@ int launch_resident(rnnt_beam *h, hipStream_t s, const StepPlan &p) {
   b.spin_limit = h->spin_limit;
   b.stall_step = h->stall_step;
   b.halves = c.pred == RNNT_PRED_LSTM && proj_split(c, p.M);
+  b.fold = fold_specials(c, h->n_chunks, p.B, p.K);
   b.b_out = h->b_out; b.b_pred = h->b_pred; b.G = h->G; b.f_proj = w.f_proj;
   if (c.pred == RNNT_PRED_STATELESS) {
     b.emb_tab = h->tab;

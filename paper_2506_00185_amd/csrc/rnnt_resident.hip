@@ -30,7 +30,15 @@ __global__ void k_pack_f32(const float *W, int rows, int K, int n_tiles, float *
     out[i] = row < rows ? W[k4_at(res_k_of(round, kq, e), row, rows)] : 0.f;
   }
 }
-// the same for the bf16 matrix instructions: [tile of 32 rows][round][64 lanes] four bf16 (values are bf16 already)
+// rows row0 .. + 15 as res_fold_mma reads them: [round][64 lanes][2], k = 8 round + lane / 16 and four further
+__global__ void k_pack_fold(const float *W, int rows, int row0, int K, float *out) {
+  const int n = K / 8 * 128;
+  for (int i = blockIdx.x * blockDim.x + threadIdx.x; i < n; i += gridDim.x * blockDim.x) {
+    const int e = i & 1, lane = (i >> 1) & 63, row = row0 + (lane & 15);
+    out[i] = row < rows ? W[k4_at(8 * (i >> 7) + 4 * e + (lane >> 4), row, rows)] : 0.f;
+  }
+}
+// k_pack_f32 for the bf16 matrix instructions: [tile of 32 rows][round][64 lanes] four bf16 (values are bf16 already)
 template <int MAP>
 __global__ void k_pack_bf16(const float *W, int rows, int K, int n_tiles, uint64_t *out) {
   const int n_rounds = K / 8;
@@ -93,10 +101,15 @@ bool assign_tiles(const rnnt_config_t &c, int n_blocks, std::vector<ResTab> &tab
     if (!put(t, [](const ResTab &x) { return (int)x.nR; }, [](const ResTab &x) { return x.nR < kResMaxR; },
              [](ResTab &x, int tile) { x.R[x.nR++] = (int16_t)tile; }))
       return false;
-  for (int t = 0; t < nJ; ++t)
-    if (!put(t, [](const ResTab &x) { return (int)x.nJ; }, [&](const ResTab &x) { return x.nJ < reg_j + 1; },
+  // (the tile with the blank column is dealt first, as its block reads it from its first place where it is folded, and counts
+  // as two: it has two chains of sums then)
+  const int blank_tile = c.V / (bf ? 32 : 16);
+  for (int i = 0; i < nJ; ++i) {
+    const int t = i == 0 ? blank_tile : i <= blank_tile ? i - 1 : i;
+    if (!put(t, [&](const ResTab &x) { return x.nJ + (x.nJ > 0 && x.J[0] == blank_tile); }, [&](const ResTab &x) { return x.nJ < reg_j + 1; },
              [](ResTab &x, int tile) { x.J[x.nJ++] = (int16_t)tile; }))
       return false;
+  }
   for (int t = 0; t < nP; ++t)
     if (!put(t, [](const ResTab &x) { return (int)x.nP; },
              [&](const ResTab &x) { return x.nP < max_p && x.nP + std::max(0, x.nJ - reg_j) < kResMaxLdsTiles; },
@@ -105,7 +118,7 @@ bool assign_tiles(const rnnt_config_t &c, int n_blocks, std::vector<ResTab> &tab
   return true;
 }
 
-Plan make_plan(const Resident &r, const rnnt_config_t &c, int B, int K, bool has_lm) {
+Plan make_plan(const Resident &r, const rnnt_config_t &c, int B, int K, bool has_lm, bool fold) {
   Plan p;
   // one group per 32 compute units at most (a group of 32 holds the weights of a 640-wide decoder), never more groups
   // than utterances: few utterances get more blocks each
@@ -130,7 +143,7 @@ Plan make_plan(const Resident &r, const rnnt_config_t &c, int B, int K, bool has
   int lds_tiles = 0;
   for (const ResTab &t : p.tab) lds_tiles = std::max(lds_tiles, t.nP + std::max(0, t.nJ - (bf ? kResRegJ<true> : kResRegJ<false>)));
   const size_t worker = (size_t)lds_tiles * std::max(c.pred == RNNT_PRED_LSTM ? c.P : 0, c.H) * kResSlot * 4 +
-                        (size_t)2 * (bf ? kResRedBlocks<true> : kResRedBlocks<false>) * kResRedBlock * 4 +
+                        (bf && fold ? (size_t)(1 + c.n_durations) * c.H * 2 : 0) + (size_t)2 * (bf ? kResRedBlocks<true> : kResRedBlocks<false>) * kResRedBlock * 4 +
                         (size_t)kResMaxR * p.NT * (256 + 128) * 4 + (size_t)p.NT * kResSlot * (sizeof(int2) + kResWaves * 8);
   const size_t sel = (sizeof(ResSelLds) + 15) / 16 * 16 + p.upc * sizeof(SelectScratchWide) +
                      (size_t)p.NT * kResSlot * kResWaves * 8 + (has_lm ? (size_t)p.upc * K * c.V * 4 : 0);
@@ -187,7 +200,7 @@ int resident_create(Resident &r, const rnnt_config_t &c, const ResidentWeights &
     return e == hipSuccess;
   };
   const int nR = 4 * c.P / 16, nJ = bf ? (N + 31) / 32 : (N + 15) / 16, nP = bf ? c.H / 32 : c.H / 16;
-  bool ok = bf ? alloc(&r.WJb, (size_t)nJ * (c.H / 8) * 64) : alloc(&r.WJ, (size_t)nJ * 16 * c.H);
+  bool ok = bf ? alloc(&r.WJb, (size_t)nJ * (c.H / 8) * 64) : alloc(&r.WJ, (size_t)nJ * 16 * c.H) && alloc(&r.WJs, (size_t)16 * c.H);
   if (lstm) {
     ok = ok && alloc(&r.WR, (size_t)nR * 16 * c.P) && alloc(&r.hb, kResStepRing * rows * c.P) && alloc(&r.pb, 2 * rows * c.H);
     ok = ok && (bf ? alloc(&r.WPb, (size_t)nP * (c.P / 8) * 64) : alloc(&r.WP, (size_t)nP * 16 * c.P));
@@ -199,7 +212,10 @@ int resident_create(Resident &r, const rnnt_config_t &c, const ResidentWeights &
   if ((e = hipHostGetDevicePointer(reinterpret_cast<void **>(&r.h_abort_dev), r.h_abort, 0)) != hipSuccess) return fail("pinned word");
   const dim3 grid(512), block(256);
   if (bf) hipLaunchKernelGGL(k_pack_bf16<0>, grid, block, 0, nullptr, w.W_out, w.out_rows, c.H, nJ, r.WJb);
-  else hipLaunchKernelGGL(k_pack_f32<0>, grid, block, 0, nullptr, w.W_out, w.out_rows, c.H, nJ, r.WJ);
+  else {
+    hipLaunchKernelGGL(k_pack_f32<0>, grid, block, 0, nullptr, w.W_out, w.out_rows, c.H, nJ, r.WJ);
+    hipLaunchKernelGGL(k_pack_fold, grid, block, 0, nullptr, w.W_out, w.out_rows, c.V / 16 * 16, c.H, r.WJs);
+  }
   if (lstm) {
     hipLaunchKernelGGL(k_pack_f32<1>, grid, block, 0, nullptr, w.W_hh, 4 * c.P, c.P, nR, r.WR);
     if (bf) hipLaunchKernelGGL(k_pack_bf16<2>, grid, block, 0, nullptr, w.W_pred, c.H, c.P, nP, r.WPb);
@@ -210,17 +226,17 @@ int resident_create(Resident &r, const rnnt_config_t &c, const ResidentWeights &
   return RNNT_OK;
 }
 
-bool resident_fits(const Resident &r, const rnnt_config_t &c, int B, int K, int T, int max_steps, bool has_lm) {
+bool resident_fits(const Resident &r, const rnnt_config_t &c, int B, int K, int T, int max_steps, bool has_lm, bool fold) {
   if (!r.usable || r.misses >= kResidentMaxMisses) return false;
   if (T >= kWordMaxFrames || max_steps > 60000) return false;  // fields of the words
-  return make_plan(r, c, B, K, has_lm).ok;
+  return make_plan(r, c, B, K, has_lm, fold).ok;
 }
 
 hipError_t resident_launch(Resident &r, const rnnt_config_t &c, const ResidentBatch &b, hipStream_t s) {
-  Plan p = make_plan(r, c, b.B, b.K, b.has_lm);
+  Plan p = make_plan(r, c, b.B, b.K, b.has_lm, b.fold);
   if (!p.ok) return hipErrorInvalidValue;
   ResArgs a{};
-  a.WR = r.WR; a.WJ = r.WJ; a.WP = r.WP; a.WJb = r.WJb; a.WPb = r.WPb;
+  a.WR = r.WR; a.WJ = r.WJ; a.WJs = r.WJs; a.WP = r.WP; a.WJb = r.WJb; a.WPb = r.WPb;
   a.emb_tab = b.emb_tab; a.n_ctx = b.n_ctx;
   a.b_out = b.b_out; a.b_pred = b.b_pred; a.G = b.G; a.f_proj = b.f_proj;
   a.lengths = b.lengths;
@@ -234,6 +250,7 @@ hipError_t resident_launch(Resident &r, const rnnt_config_t &c, const ResidentBa
   a.n_groups = p.n_groups; a.n_sel = p.n_sel; a.upc = p.upc;
   a.NT = p.NT; a.halves = b.halves ? 1 : 0; a.has_lm = b.has_lm ? 1 : 0;
   a.rounds_h = c.H / 64; a.rounds_p = c.P / 64;
+  a.fold = b.fold ? 1 : 0;
   a.stall_step = b.stall_step;
   a.poll_limit = std::min(b.stall_step < 0 ? 1 << 19 : kResStallPolls, b.spin_limit);
   const bool short_spin = b.spin_limit < kResShortSpin;

@@ -42,6 +42,15 @@ CASES = [
     dict(B=16, beam=8, V=257, H=448, P=64, E=64, D=32, **ST, ctx=4),
     dict(B=23, beam=5, V=1023, **W640, **ST, ctx=2),
     dict(B=30, beam=4, V=129, prec="bf16", H=192, P=192, E=192, D=32, algo="aes", gamma=2.3, **ST, ctx=4, **TDT),
+    # the per-step launches fold the blank and duration columns into the token columns' blocks (V % 32 == 0, 640 wide, more than
+    # 256 blocks): the same sums in the same order, one to three tiles of slots, every precision and network
+    dict(B=15, beam=12, V=1024, **W640),
+    dict(B=29, beam=8, V=1024, algo="aes", **W640, **TDT),
+    dict(B=128, beam=2, V=512, s=2, **W640),
+    dict(B=15, beam=12, V=1024, prec="bf16", **W640),
+    dict(B=57, beam=4, V=1024, prec="bf16", **W640, **TDT),
+    dict(B=64, beam=2, V=1024, **W640, **ST, ctx=2),
+    dict(B=57, beam=1, V=1024, prec="bf16", **W640, **ST, ctx=1, **TDT),
 ]
 
 
