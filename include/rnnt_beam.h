@@ -95,7 +95,8 @@ typedef struct {
                                 per-step kernels are launched one by one.  The results are the same bit for bit up to 256
                                 hypotheses.  The resident loop needs every one of its blocks on the chip at once: where they
                                 do not find room within 50 ms, or another thread's decode holds the device, the per-step
-                                launches decode the batch */
+                                launches decode the batch (after a launch that gave up, the next 4 decodes of the handle
+                                as well; 8, 16, .. 256 after further ones in a row) */
   int32_t joint_path;        /* rnnt_joint_path_t; create fails if MATERIALIZED is asked for a decoder
                                 that cannot take it */
   int32_t lm_rule;           /* how the LM enters a candidate's score (Sec. 2.3): 0 or 4 = Eq. (4), tokens get

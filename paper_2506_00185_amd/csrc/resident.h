@@ -18,7 +18,7 @@ struct ResTab;
 struct Resident {
   bool usable = false;
   int n_cus = 0, max_lds = 0;
-  int misses = 0;                 // launches that gave up; after kResidentMaxMisses the handle stays with the per-step launches
+  int misses = 0, skip = 0;       // launches in a row that gave up; decodes left to the per-step launches before the next try
   float *WR = nullptr, *WJ = nullptr, *WJs = nullptr, *WP = nullptr;
   uint64_t *WJb = nullptr, *WPb = nullptr;
   float *hb = nullptr, *pb = nullptr, *zb = nullptr;
@@ -29,7 +29,14 @@ struct Resident {
   int *h_abort = nullptr, *h_abort_dev = nullptr;  // pinned
   std::vector<void *> allocs;
 };
-constexpr int kResidentMaxMisses = 3;
+// A launch that gives up costs the decode up to 50 ms, several decodes' time: after the n-th in a row the next 4, 8, 16, ..
+// 256 decodes of the handle use the per-step launches.  One that succeeds starts the count anew.
+constexpr int kResidentSkip = 4, kResidentMaxSkip = 256;
+inline void resident_missed(Resident &r) {
+  r.skip = kResidentSkip << r.misses;
+  if (r.skip >= kResidentMaxSkip) r.skip = kResidentMaxSkip;
+  else ++r.misses;
+}
 
 // What the packing reads: the handle's k4-major weights (see kernels.h, k4_index)
 struct ResidentWeights {

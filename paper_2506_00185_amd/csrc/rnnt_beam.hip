@@ -937,11 +937,17 @@ int decode_max_steps(const rnnt_config_t &c, const Workspace &w, int T) {
   return T * (c.max_symbols + 1) < w.S_max ? T * (c.max_symbols + 1) : w.S_max;
 }
 
-bool use_resident(const rnnt_beam *h, const StepPlan &p) {
+bool use_resident(rnnt_beam *h, const StepPlan &p) {
   const rnnt_config_t &c = h->cfg;
   if (!c.use_graph || c.persistent_kernel || h->profiling || p.inj_tok || p.plain || p.ahead || p.big) return false;
-  return resident_fits(h->res, c, p.B, p.K, p.T, decode_max_steps(c, *p.ws, p.T), p.lm != nullptr,
-                       fold_specials(c, h->n_chunks, p.B, p.K));
+  if (!resident_fits(h->res, c, p.B, p.K, p.T, decode_max_steps(c, *p.ws, p.T), p.lm != nullptr,
+                     fold_specials(c, h->n_chunks, p.B, p.K)))
+    return false;
+  if (h->res.skip > 0) {
+    --h->res.skip;
+    return false;
+  }
+  return true;
 }
 
 int launch_resident(rnnt_beam *h, hipStream_t s, const StepPlan &p) {
@@ -1188,11 +1194,12 @@ int run_decode(rnnt_beam *h, const float *enc, const int32_t *lengths, const Ste
     if (*gave_up || !*host_done) {
       RB_HIP(h, hipStreamSynchronize(s));
       if (*gave_up || !*host_done) {
-        ++h->res.misses;
+        resident_missed(h->res);
         if (h->trace_pacing) fprintf(stderr, "rnnt_beam: resident loop gave up, decoding with per-step launches\n");
         return run_decode(h, enc, lengths, p, s, false);
       }
     }
+    h->res.misses = 0;
   }
   return RNNT_OK;
 }

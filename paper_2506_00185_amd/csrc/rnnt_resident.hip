@@ -227,7 +227,7 @@ int resident_create(Resident &r, const rnnt_config_t &c, const ResidentWeights &
 }
 
 bool resident_fits(const Resident &r, const rnnt_config_t &c, int B, int K, int T, int max_steps, bool has_lm, bool fold) {
-  if (!r.usable || r.misses >= kResidentMaxMisses) return false;
+  if (!r.usable) return false;
   if (T >= kWordMaxFrames || max_steps > 60000) return false;  // fields of the words
   return make_plan(r, c, B, K, has_lm, fold).ok;
 }

@@ -114,6 +114,32 @@ def test_resident_loop_that_gives_up_is_replaced_by_the_per_step_launches():
     np.testing.assert_array_equal(r["tokens"], ref["tokens"])
 
 
+def test_resident_loop_is_tried_again_after_launches_that_gave_up():
+    import paper_2506_00185_amd as A
+    c = S.custom_config(B=2, T=5, D=32, H=64, P=64, E=64, V=30, beam=2, s=2)
+    w = S.make_weights(c, 25)
+    L = S.make_lengths(c, 27)
+    enc = S.make_enc(c, L, 28)
+    dec = A.BeamDecoder(c, w)
+
+    def loops(n):
+        out = []
+        for _ in range(n):
+            gpu_decode(dec, enc, L)
+            out.append(dec.last_step_loop())
+        return out
+
+    assert loops(1) == ["resident"]
+    dec.debug_set_spin_limit(1)
+    assert loops(1 + 4 + 1 + 8 + 1) == ["graph"] * 15  # three launches give up
+    dec.debug_set_spin_limit(1 << 22)
+    assert loops(16 + 2) == ["graph"] * 16 + ["resident"] * 2
+    dec.debug_set_spin_limit(1)
+    assert loops(1) == ["graph"]
+    dec.debug_set_spin_limit(1 << 22)
+    assert loops(4 + 1) == ["graph"] * 4 + ["resident"]  # the count had started anew
+
+
 @pytest.mark.parametrize("kw", [dict(beam=12), dict(beam=12, prec="bf16", B=24), dict(beam=4, B=8), dict(beam=4, B=8, **ST, ctx=2)],
                          ids=["straddles_two_tiles", "bf16", "one_tile", "stateless"])
 @pytest.mark.parametrize("step", [0, 1, 5])
