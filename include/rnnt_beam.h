@@ -93,7 +93,8 @@ typedef struct {
                                 stateless ones 16); all others
                                 replay the per-step kernels as a captured HIP graph (Sec. 2.1, "CUDA Graphs").  0: the
                                 per-step kernels are launched one by one.  The results are the same bit for bit up to 256
-                                hypotheses.  The resident loop needs every one of its blocks on the chip at once: where they
+                                hypotheses.  The resident loop needs memory for a second copy of
+                                the weights (without it the per-step launches are replayed) and every one of its blocks on the chip at once: where they
                                 do not find room within 50 ms, or another thread's decode holds the device, the per-step
                                 launches decode the batch (after a launch that gave up, the next 4 decodes of the handle
                                 as well; 8, 16, .. 256 after further ones in a row) */
@@ -281,6 +282,11 @@ int rnnt_beam_debug_set_spin_limit(rnnt_beam_t *h, int32_t polls);
  * logits for the last tile of 16 hypotheses that they hold and end; the other blocks' waits give up (after 4096 polls
  * instead of 2^19) and the batch is decoded with per-step launches.  -1 (default): off. */
 int rnnt_beam_debug_stall_resident(rnnt_beam_t *h, int32_t step);
+
+/* Test hook for the resident loop's memory: its second copy of the weights, hand-over arrays and tables are given back and laid
+ * out anew, with allocation number `fail_alloc` (0, 1, ..) taken to fail.  The handle then decodes without that loop, as it
+ * does where create finds no memory for them.  -1: none fails. */
+int rnnt_beam_debug_rebuild_resident(rnnt_beam_t *h, int32_t fail_alloc);
 
 /* Which step loop the last rnnt_beam_decode / rnnt_beam_decode_injected of the handle used (rnnt_step_loop_t; see the
  * config fields use_graph and persistent_kernel), RNNT_E_NORESULT before the first one.  Does not wait for the device. */

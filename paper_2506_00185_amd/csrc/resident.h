@@ -44,7 +44,9 @@ struct ResidentWeights {
   int out_rows;  // padded rows of W_out
 };
 
-int resident_create(Resident &r, const rnnt_config_t &c, const ResidentWeights &w, std::string &err);
+// RNNT_OK with r.usable == false: the decoder does not fit the loop, or its second copy of the weights finds no memory (the
+// per-step launches do without it).  fail_alloc: a test's, the allocation that is taken to fail (-1: none).
+int resident_create(Resident &r, const rnnt_config_t &c, const ResidentWeights &w, std::string &err, int fail_alloc = -1);
 void resident_destroy(Resident &r);
 
 struct ResidentBatch {

@@ -932,6 +932,12 @@ struct DeviceSlot {
   }
 };
 
+int create_resident(rnnt_beam *h, int fail_alloc) {
+  const rnnt_config_t &c = h->cfg;
+  const ResidentWeights rw{h->W_hh, h->W_out, h->W_pred, h->n_chunks * 32};
+  return c.use_graph && !c.persistent_kernel && !c.async_enqueue ? resident_create(h->res, c, rw, h->err, fail_alloc) : RNNT_OK;
+}
+
 int decode_max_steps(const rnnt_config_t &c, const Workspace &w, int T) {
   // every utterance has finished after at most T (s + 1) steps (the selection enforces it)
   return T * (c.max_symbols + 1) < w.S_max ? T * (c.max_symbols + 1) : w.S_max;
@@ -1320,10 +1326,6 @@ int rnnt_beam_create(const rnnt_config_t *cfg, const rnnt_weights_t *w, rnnt_bea
   if (!rc) {
     hipError_t e = hipHostMalloc(reinterpret_cast<void **>(&h->h_done), 128, hipHostMallocMapped);
     if (e == hipSuccess) e = hipHostGetDevicePointer(reinterpret_cast<void **>(&h->h_done_dev), h->h_done, 0);
-    if (e == hipSuccess) {
-      const ResidentWeights rw{h->W_hh, h->W_out, h->W_pred, h->n_chunks * 32};
-      rc = c.use_graph && !c.persistent_kernel && !c.async_enqueue ? resident_create(h->res, c, rw, h->err) : RNNT_OK;
-    }
     h->h_out_bytes = out_pack(c.max_B, c.max_beam, h->ws.cap).bytes;
     if (e == hipSuccess) e = hipHostMalloc(reinterpret_cast<void **>(&h->h_out), h->h_out_bytes, hipHostMallocDefault);
     if (e == hipSuccess) e = hipEventCreate(&h->ev_begin);
@@ -1352,10 +1354,11 @@ int rnnt_beam_create(const rnnt_config_t *cfg, const rnnt_weights_t *w, rnnt_bea
         h->pctl = static_cast<PersistCtl *>(q);
       }
     }
-    if (e != hipSuccess && !rc) {
+    if (e != hipSuccess) {
       h->err = std::string("create: ") + hipGetErrorString(e);
       rc = RNNT_E_HIP;
     }
+    if (!rc) rc = create_resident(h, -1);
   }
   if (rc) {
     g_create_error = h->err;
@@ -1571,6 +1574,13 @@ int rnnt_beam_debug_stall_resident(rnnt_beam_t *h, int32_t step) {
   if (!h || step < -1) return RNNT_E_ARG;
   h->stall_step = step;
   return RNNT_OK;
+}
+
+int rnnt_beam_debug_rebuild_resident(rnnt_beam_t *h, int32_t fail_alloc) {
+  if (!h) return RNNT_E_ARG;
+  RB_HIP(h, hipDeviceSynchronize());
+  resident_destroy(h->res);
+  return create_resident(h, fail_alloc);
 }
 
 int rnnt_beam_set_profiling(rnnt_beam_t *h, int32_t on) {

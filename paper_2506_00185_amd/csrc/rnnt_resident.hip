@@ -169,7 +169,7 @@ void resident_destroy(Resident &r) {
   r = Resident{};
 }
 
-int resident_create(Resident &r, const rnnt_config_t &c, const ResidentWeights &w, std::string &err) {
+int resident_create(Resident &r, const rnnt_config_t &c, const ResidentWeights &w, std::string &err, int fail_alloc) {
   r.usable = false;
   // decoders whose contractions split into eight slices of whole rounds and fit the registers (stateless ones: P is not
   // that of a contraction); vocabularies that one wave holds in registers
@@ -180,7 +180,11 @@ int resident_create(Resident &r, const rnnt_config_t &c, const ResidentWeights &
   auto fail = [&](const char *what) {
     err = std::string(what) + ": " + hipGetErrorString(e);
     resident_destroy(r);
-    return e == hipErrorOutOfMemory ? RNNT_E_NOMEM : RNNT_E_HIP;
+    if (e == hipErrorOutOfMemory) {
+      (void)hipGetLastError();  // (handled: no later check is to find it)
+      return RNNT_OK;
+    }
+    return RNNT_E_HIP;
   };
   int dev = 0;
   if ((e = hipGetDevice(&dev)) != hipSuccess) return fail("hipGetDevice");
@@ -192,7 +196,7 @@ int resident_create(Resident &r, const rnnt_config_t &c, const ResidentWeights &
   const size_t rows = (size_t)G * kResMaxNT * kResSlot;
   auto alloc = [&](auto **p, size_t n) {
     void *q = nullptr;
-    e = hipMalloc(&q, n * sizeof(**p));
+    e = fail_alloc == (int)r.allocs.size() ? hipErrorOutOfMemory : hipMalloc(&q, n * sizeof(**p));
     if (e == hipSuccess) {
       r.allocs.push_back(q);
       *p = static_cast<std::remove_reference_t<decltype(*p)>>(q);

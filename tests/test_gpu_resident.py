@@ -140,6 +140,23 @@ def test_resident_loop_is_tried_again_after_launches_that_gave_up():
     assert loops(4 + 1) == ["graph"] * 4 + ["resident"]  # the count had started anew
 
 
+@pytest.mark.parametrize("kw", [{}, dict(prec="bf16"), dict(ST, ctx=1)], ids=["lstm", "bf16", "stateless"])
+def test_decoder_without_memory_for_the_resident_loop_uses_the_per_step_launches(kw):
+    import paper_2506_00185_amd as A
+    c = S.custom_config(B=3, T=9, D=32, H=64, P=64, E=64, V=30, beam=3, s=2, **kw)
+    w = S.make_weights(c, 25)
+    L = S.make_lengths(c, 27)
+    enc = S.make_enc(c, L, 28)
+    dec = A.BeamDecoder(c, w)
+    ref = gpu_decode(dec, enc, L)
+    for alloc, loop in [(i, "graph") for i in range(5)] + [(100, "resident"), (-1, "resident")]:
+        dec.debug_rebuild_resident(alloc)
+        r = gpu_decode(dec, enc, L)
+        assert dec.last_step_loop() == loop
+        for key in KEYS:
+            np.testing.assert_array_equal(r[key], ref[key])
+
+
 @pytest.mark.parametrize("kw", [dict(beam=12), dict(beam=12, prec="bf16", B=24), dict(beam=4, B=8), dict(beam=4, B=8, **ST, ctx=2)],
                          ids=["straddles_two_tiles", "bf16", "one_tile", "stateless"])
 @pytest.mark.parametrize("step", [0, 1, 5])
