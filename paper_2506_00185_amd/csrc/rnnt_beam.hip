@@ -917,18 +917,40 @@ int launch_persistent(rnnt_beam *h, hipStream_t s, const StepPlan &p, int max_st
 }
 
 // The resident loop (one launch that keeps the weights on chip, kernels_resident.h) takes the decodes that would replay a
-// graph, where the batch fits it.  Its blocks wait for each other, so there is one such launch at a time on a device:
-// a decode that finds the device taken by another thread's uses the per-step launches.
+// graph, where the batch fits it.  Its blocks wait for each other, as do those of the single-launch loop, so there is one such
+// launch at a time on a device.  A resident decode holds the device until it is over; one that finds it taken uses the
+// per-step launches.  A single-launch decode, which returns when it is enqueued, leaves an event: the next one runs behind
+// it, and until it has passed the device counts as taken.
 struct DeviceSlot {
-  std::mutex *m = nullptr;
-  bool take(int dev) {
-    static std::mutex slots[kMaxDevices];
-    if (dev < 0 || dev >= kMaxDevices || !slots[dev].try_lock()) return false;
-    m = &slots[dev];
+  struct Device {
+    std::mutex m;
+    hipEvent_t end = nullptr;  // of the last single-launch loop; kept until the process ends
+  };
+  Device *d = nullptr;
+  static Device *device() {
+    static Device devices[kMaxDevices];
+    int dev = -1;
+    return hipGetDevice(&dev) == hipSuccess && dev >= 0 && dev < kMaxDevices ? &devices[dev] : nullptr;
+  }
+  bool take_for_resident() {
+    Device *x = device();
+    if (!x || !x->m.try_lock()) return false;
+    if (x->end && hipEventQuery(x->end) != hipSuccess) {
+      x->m.unlock();
+      return false;
+    }
+    d = x;
     return true;
   }
+  // s: the launch that follows goes there, and then done()
+  hipError_t take_for_single_launch(hipStream_t s) {
+    if (!(d = device())) return hipErrorInvalidDevice;
+    d->m.lock();
+    return d->end ? hipStreamWaitEvent(s, d->end, 0) : hipEventCreateWithFlags(&d->end, hipEventDisableTiming);
+  }
+  hipError_t done(hipStream_t s) { return hipEventRecord(d->end, s); }
   ~DeviceSlot() {
-    if (m) m->unlock();
+    if (d) d->m.unlock();
   }
 };
 
@@ -991,10 +1013,7 @@ int run_decode(rnnt_beam *h, const float *enc, const int32_t *lengths, const Ste
   h->prof_used = 0;
   h->prof_launches.clear();
   DeviceSlot slot;
-  if (resident) {
-    int dev = -1;
-    resident = use_resident(h, p) && hipGetDevice(&dev) == hipSuccess && slot.take(dev);
-  }
+  if (resident) resident = use_resident(h, p) && slot.take_for_resident();
   RB_HIP(h, hipEventRecord(h->ev_begin, s));
   {
     InitArgs a;
@@ -1045,7 +1064,10 @@ int run_decode(rnnt_beam *h, const float *enc, const int32_t *lengths, const Ste
     if ((rc = launch_resident(h, s, p))) return rc;
   } else if (h->last_loop == RNNT_LOOP_SINGLE_LAUNCH) {
     // one launch walks all steps (it starts with the prediction network on the start symbol itself)
+    DeviceSlot single;
+    RB_HIP(h, single.take_for_single_launch(s));
     if ((rc = launch_persistent(h, s, p, max_steps))) return rc;
+    RB_HIP(h, single.done(s));
   } else {
   // prediction network on the start symbol (reads parity 1, writes parity 0), LM on the empty context
   if ((rc = launch_pred(h, s, p, 1, 0))) return rc;

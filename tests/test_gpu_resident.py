@@ -180,3 +180,67 @@ def test_logits_that_do_not_come_end_the_resident_loop_as_a_whole(kw, step):
         r = gpu_decode(dec, enc, L)
         for key in KEYS:
             np.testing.assert_array_equal(r[key], ref[key])
+
+
+def test_resident_loop_does_not_start_beside_a_single_launch_loop():
+    """The single-launch loop's blocks wait for each other too.  One of another handle waits on its stream, behind 40 ms of other
+    work, to begin."""
+    import torch
+    import paper_2506_00185_amd as A
+    c = S.custom_config(B=4, T=9, D=64, H=64, P=64, E=64, V=40, beam=4, s=2)
+    w = S.make_weights(c, 45)
+    L = S.make_lengths(c, 47)
+    enc = S.make_enc(c, L, 48)
+    dec, single = A.BeamDecoder(c, w), A.BeamDecoder(c, w, persistent=True)
+    ref = gpu_decode(dec, enc, L)
+    assert dec.last_step_loop() == "resident"
+    x, n = torch.as_tensor(enc).cuda(), torch.as_tensor(L).cuda()
+    s = torch.cuda.Stream()
+    torch.cuda.synchronize()
+    with torch.cuda.stream(s):
+        torch.cuda._sleep(80_000_000)
+        single.decode(x, n)
+    dec.decode(x, n)
+    r = dec.results()
+    assert dec.last_step_loop() == "graph" and single.last_step_loop() == "single launch"
+    r1 = single.results()
+    for key in ("tokens", "lens", "scores", "n_steps"):
+        np.testing.assert_array_equal(r[key], ref[key])
+        np.testing.assert_array_equal(r1[key], ref[key])
+    gpu_decode(dec, enc, L)
+    assert dec.last_step_loop() == "resident"
+
+
+def test_threads_that_decode_on_streams_of_their_own():
+    """Two handles for the resident loop, one for the single-launch loop and one with a launch per step, each in a thread and on a
+    stream of its own: whatever loop a decode finds free, the results are those of the same decode alone."""
+    import threading
+    import torch
+    import paper_2506_00185_amd as A
+    c = S.custom_config(B=6, T=12, D=64, H=192, P=192, E=64, V=150, beam=4, s=2, blank_bias=3.0)
+    w = S.make_weights(c, 55)
+    L = S.make_lengths(c, 57)
+    enc = S.make_enc(c, L, 58)
+    ref = gpu_decode(A.BeamDecoder(c, w, use_graph=False), enc, L)
+    x, n = torch.as_tensor(enc).cuda(), torch.as_tensor(L).cuda()
+    handles = [A.BeamDecoder(c, w), A.BeamDecoder(c, w), A.BeamDecoder(c, w, persistent=True), A.BeamDecoder(c, w, use_graph=False)]
+    torch.cuda.synchronize()
+    out = [[] for _ in handles]
+
+    def work(i):
+        s = torch.cuda.Stream()
+        for _ in range(12):
+            handles[i].decode(x, n, stream=s)
+            out[i].append((handles[i].results(), handles[i].last_step_loop()))
+
+    threads = [threading.Thread(target=work, args=(i,)) for i in range(len(handles))]
+    for t in threads:
+        t.start()
+    for t in threads:
+        t.join()
+    for i, results in enumerate(out):
+        assert len(results) == 12
+        for r, loop in results:
+            assert loop in (("resident", "graph"), ("resident", "graph"), ("single launch",), ("launches",))[i]
+            for key in ("tokens", "lens", "scores", "n_steps"):
+                np.testing.assert_array_equal(r[key], ref[key])
