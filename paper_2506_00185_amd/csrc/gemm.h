@@ -190,7 +190,10 @@ __global__ __launch_bounds__(256) void k_gemm_tiled(GemmArgs a) {
       for (int r = 0; r < 16; ++r) {
         const int m = m0 + wm0 + 32 * i + 8 * (r >> 2) + 4 * half + (r & 3);
         if (m < a.M) {
-          const float v = acc[i][j][r] + bv;
+          // (one NaN for all of them: the all-ones one of a caller's buffer would keep its bits through every sum, and
+          // arrays of the resident loop mark places that are still empty with it)
+          float v = acc[i][j][r] + bv;
+          v = v == v ? v : __builtin_nanf("");
           a.C[(size_t)m * a.N + n] = v;
           bad |= !isfinite(v);
         }

@@ -211,6 +211,24 @@ def test_resident_loop_does_not_start_beside_a_single_launch_loop():
     assert dec.last_step_loop() == "resident"
 
 
+def test_nan_of_all_ones_in_the_encoder_output():
+    """The bit pattern that marks empty places of the hand-over arrays, as data: the decode ends and reports it, in this loop."""
+    import torch
+    import paper_2506_00185_amd as A
+    c = S.custom_config(B=9, T=10, V=90, beam=4, s=2, **W640)
+    w = S.make_weights(c, 65)
+    L = S.make_lengths(c, 67)
+    enc = S.make_enc(c, L, 68)
+    dec = A.BeamDecoder(c, w)
+    n = torch.as_tensor(L).cuda()
+    x = torch.as_tensor(enc).cuda()
+    x.view(torch.int32)[3, 2, 5] = -1
+    dec.decode(x, n)
+    assert dec.results(check=False)["rc"] == -4 and dec.last_step_loop() == "resident"
+    gpu_decode(dec, enc, L)
+    assert dec.last_step_loop() == "resident"
+
+
 def test_threads_that_decode_on_streams_of_their_own():
     """Two handles for the resident loop, one for the single-launch loop and one with a launch per step, each in a thread and on a
     stream of its own: whatever loop a decode finds free, the results are those of the same decode alone."""
