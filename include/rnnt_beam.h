@@ -88,16 +88,21 @@ typedef struct {
   float prune_margin;        /* AES++ only: a token whose log-probability is more than this below
                                 the best one of its hypothesis is not expanded; INFINITY = off */
   int32_t use_graph;         /* 1: no launch per step.  Decoders whose weights fit the chip (H, for LSTM models also P, multiples of
-                                64 up to 640; V <= 1024; no tdt_all_pairs; fused joint) run the step loop as one launch whose blocks keep the weights
-                                on chip ("resident loop"; batches of up to 48 hypotheses per 32 compute units,
-                                stateless ones 16); all others
-                                replay the per-step kernels as a captured HIP graph (Sec. 2.1, "CUDA Graphs").  0: the
-                                per-step kernels are launched one by one.  The results are the same bit for bit up to 256
-                                hypotheses.  The resident loop needs memory for a second copy of
-                                the weights (without it the per-step launches are replayed) and every one of its blocks on the chip at once: where they
-                                do not find room within 50 ms, or another thread's decode holds the device, the per-step
-                                launches decode the batch (after a launch that gave up, the next 4 decodes of the handle
-                                as well; 8, 16, .. 256 after further ones in a row) */
+                                64 up to 640; V <= 1024; no tdt_all_pairs; fused joint) run the step loop as one launch whose
+                                blocks keep the weights on chip ("resident loop"), in batches of up to 48 hypotheses (stateless
+                                decoders 16) and 16 utterances per 32 compute units; narrow decoders with wide beams, for which
+                                it is slower, and all others replay the per-step kernels as a captured HIP graph (Sec. 2.1,
+                                "CUDA Graphs").  0: the per-step kernels are launched one by one.  The results are the same bit
+                                for bit up to 256 hypotheses.
+                                The resident loop needs memory for a second copy of the weights (without it the per-step
+                                launches are replayed) and every one of its blocks on the chip at once: where they do not find
+                                room within 50 ms, or another thread's decode or a persistent_kernel one holds the device, the
+                                per-step launches decode the batch (after a launch that gave up, the next 4 decodes of the
+                                handle as well; 8, 16, .. 256 after further ones in a row).  While it runs it has every compute
+                                unit to itself, also for one utterance: kernels of other streams wait until the decode is over
+                                (batch 32, beam 4: a matrix product of another stream 7.6 ms, beside the replayed graph
+                                0.2 ms).  A program that needs the compute units shared during a decode sets async_enqueue,
+                                which replays the graph, or use_graph = 0 */
   int32_t joint_path;        /* rnnt_joint_path_t; create fails if MATERIALIZED is asked for a decoder
                                 that cannot take it */
   int32_t lm_rule;           /* how the LM enters a candidate's score (Sec. 2.3): 0 or 4 = Eq. (4), tokens get

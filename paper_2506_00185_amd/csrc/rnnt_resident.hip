@@ -118,6 +118,21 @@ bool assign_tiles(const rnnt_config_t &c, int n_blocks, std::vector<ResTab> &tab
   return true;
 }
 
+// Decoders that fit the loop and gain nothing from it: narrow ones, whose per-step launches are short, with several tiles of slots
+// or wide beams, whose selection takes longer here.  Both sides timed in turn at widths 64 to 640 (time of the per-step
+// launches over the loop's; 640-wide LSTM decoders: 1.07 and more at every shape tried, up to three tiles).
+bool per_step_is_faster(const rnnt_config_t &c, int B, int K, int n_tiles) {
+  const bool bf = c.prec == RNNT_BF16_JOINT;
+  if (c.pred != RNNT_PRED_LSTM)  // 64 wide 0.85 to 1.10, most below 1; bf16 at one utterance: 320 wide 0.88 to 1.03, 576 0.96 to 1.08
+    return K > 8 && (c.H <= 128 || (bf && B == 1 && c.H <= 320));
+  if (c.H == 640 && c.P == 640) return false;
+  // float32, three tiles: 0.79 to 1.14 (95 shapes, mean 0.93), except large vocabularies at beams up to 8 (1.0 to 1.18)
+  if (!bf && n_tiles == 3 && !(c.V > 512 && K <= 8)) return true;
+  // 64 to 320 wide, V = 700 and 1000: 0.85 to 0.98; V = 500: float32 0.92 to 0.96 (beam 16: 1.01 to 1.06), bf16 0.90 to 1.16;
+  // V = 260 and less: 0.99 to 1.22
+  return std::max(c.H, c.P) <= 320 && n_tiles > 1 && K > 8 && c.V > (bf ? 512 : 384);
+}
+
 Plan make_plan(const Resident &r, const rnnt_config_t &c, int B, int K, bool has_lm, bool fold) {
   Plan p;
   // one group per 32 compute units at most (a group of 32 holds the weights of a 640-wide decoder), never more groups
@@ -134,6 +149,7 @@ Plan make_plan(const Resident &r, const rnnt_config_t &c, int B, int K, bool has
   // per-step launches are as fast or faster (float32, 640 wide, us per step here / there: batch 32 beam 4 13.1 / 19.1; two
   // tiles, batch 16 beam 16 34.8 / 33.3; three, batch 32 beam 12 37.3 / 36.0)
   if (c.pred != RNNT_PRED_LSTM && p.NT > 1) return p;
+  if (per_step_is_faster(c, B, K, p.NT)) return p;
   const int most_sel = std::max(1, p.n_blocks / 8);
   p.upc = (p.nu + most_sel - 1) / most_sel;
   if (p.upc > kResMaxSel || p.upc * K * K > 512 || p.upc * K > kResMaxHyps) return p;

@@ -74,6 +74,35 @@ def test_resident_loop_equals_the_per_step_launches(kw):
             np.testing.assert_array_equal(r[key], ref[key])
 
 
+W192 = dict(H=192, P=192, E=64, D=32)
+
+
+@pytest.mark.parametrize("loop,kw", [
+    ("graph", dict(B=32, beam=12, V=512, **W192)), ("graph", dict(B=33, beam=8, V=512, **W192)),      # three tiles, float32
+    ("resident", dict(B=33, beam=8, V=513, **W192)), ("resident", dict(B=33, beam=8, V=90, prec="bf16", **W192)),
+    ("graph", dict(B=9, beam=9, V=385, **W192)), ("resident", dict(B=9, beam=9, V=384, **W192)),      # two tiles, wide beams
+    ("resident", dict(B=9, beam=8, V=385, **W192)), ("resident", dict(B=8, beam=9, V=385, **W192)),
+    ("graph", dict(B=9, beam=9, V=513, prec="bf16", **W192)), ("resident", dict(B=9, beam=9, V=512, prec="bf16", **W192)),
+    ("resident", dict(B=9, beam=9, V=600, **dict(W192, P=384))),
+    ("graph", dict(B=8, beam=9, V=90, **dict(W192, H=128), **ST, ctx=1)), ("resident", dict(B=8, beam=8, V=90, **dict(W192, H=128), **ST, ctx=1)),
+    ("graph", dict(B=1, beam=9, V=90, prec="bf16", **W192, **ST, ctx=1)), ("resident", dict(B=2, beam=9, V=90, prec="bf16", **W192, **ST, ctx=1)),
+    ("resident", dict(B=1, beam=9, V=90, **W192, **ST, ctx=1)),
+])
+def test_loop_that_decodes_a_batch_on_either_side_of_a_rule(loop, kw):
+    import paper_2506_00185_amd as A
+    c = S.custom_config(**dict(dict(T=8, T_min=3, s=2, blank_bias=3.0), **kw))
+    w = S.perturb_biases(S.make_weights(c, 5), 6)
+    L = S.make_lengths(c, 7)
+    enc = S.make_enc(c, L, 8)
+    ref = gpu_decode(A.BeamDecoder(c, w, use_graph=False), enc, L)
+    dec = A.BeamDecoder(c, w)
+    r = gpu_decode(dec, enc, L)
+    assert dec.last_step_loop() == loop
+    if c["B"] * c["beam"] <= 256:
+        for key in KEYS:
+            np.testing.assert_array_equal(r[key], ref[key])
+
+
 @pytest.mark.parametrize("prune,rule,beam,B,more", [("late", 4, 8, 9, {}), ("early", 3, 4, 17, {}), ("late", 3, 11, 4, {}),
                                                     ("late", 4, 6, 10, dict(ST, ctx=2)),
                                                     # up to four hypotheses of more than 512 tokens: two waves per row
