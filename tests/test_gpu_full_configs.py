@@ -1,6 +1,7 @@
 """The five workloads at full size, in the launch configuration the benchmark
-times (graph replay).  The whole batch is decoded on the GPU; the oracle decodes
-a sample of the utterances (they are independent of each other) and the
+times (the resident loop; graph replay where it does not apply).  The whole batch
+is decoded on the GPU, where the resident loop applies by graph replay as well,
+which must give the same bits; the oracle decodes a sample of the utterances (they are independent of each other) and the
 comparison is the same as in the small cases: trees identical up to the first
 near tie, then identical transcripts and scores within tolerance.  A sampled
 utterance whose tree leaves the oracle's at a near tie is not dropped: its own
@@ -46,6 +47,13 @@ def test_workload_at_full_size(oracle, cid, variant, rows, tol, tie):
     dec = A.BeamDecoder(c, w)
     g = gpu_decode(dec, enc, L, lm=glm, lm_weight=c["lm_weight"])
     assert g["rc"] == 0
+    assert dec.last_step_loop() == ("graph" if cid == 5 else "resident")
+    if cid != 5:
+        dec.debug_rebuild_resident(0)
+        g2 = gpu_decode(dec, enc, L, lm=glm, lm_weight=c["lm_weight"])
+        assert dec.last_step_loop() == "graph"
+        for key in ("tokens", "lens", "scores", "n_steps", "parent", "token", "merged"):
+            np.testing.assert_array_equal(g2[key], g[key])
     # properties that hold for every utterance of the batch, sampled or not
     max_adv = max(c["durations"]) if c["durations"] else 1  # frames one step can consume
     assert np.all(g["n_steps"] <= L * (c["s"] + 1)) and np.all(g["n_steps"] * max_adv >= L)

@@ -246,18 +246,23 @@ def test_full_width_model_small_batch(amd, oracle, name, kw):
 def test_full_width_model_wide_batch(amd, oracle, name, kw, prec):
     """From 256 slots up at the real layer widths: more joint blocks than compute units, so the blank and duration
     columns (alone in the last column chunk, V % 32 == 0) are computed by the token chunks' blocks, and the blocks of
-    the recurrent product take four slot tiles each (256 slots) or two (288: the last block of a gate tile has one)."""
+    the recurrent product take four slot tiles each (256 slots) or two (288: the last block of a gate tile has one).
+    In the resident loop, and in the replayed graph that this describes."""
     c = S.custom_config(D=256, H=640, P=640, E=640, V=1024, blank_bias=3.0, prec=prec, **kw)
     w, L, enc = _case(c, 450 + len(name))
     if c["model"] == "tdt":
         w["b_out"][c["V"] + 2] += 2.0
     dec = amd.BeamDecoder(c, w)
-    g = gpu_decode(dec, enc, L)
     o = oracle.decode(c, w, enc, L, log=True)
     tol, tie = (TOL_BF16, TIE_BF16) if prec == "bf16" else (TOL, TIE)
-    full, exempt = compare(g, o, tol, tie, walk=make_walk(oracle, c, w, enc, L, g, tol))
-    assert full + exempt == c["B"]
-    assert full >= c["B"] // 2, (full, exempt)
+    for loop in ("resident", "graph"):
+        if loop == "graph":
+            dec.debug_rebuild_resident(0)
+        g = gpu_decode(dec, enc, L)
+        assert dec.last_step_loop() == loop
+        full, exempt = compare(g, o, tol, tie, walk=make_walk(oracle, c, w, enc, L, g, tol))
+        assert full + exempt == c["B"]
+        assert full >= c["B"] // 2, (full, exempt)
 
 
 def test_odd_shapes(amd, oracle):
@@ -576,8 +581,10 @@ def test_enqueue_pacing_hears_from_every_kind_of_step(amd, capfd, monkeypatch):
     ]
     for i, (c, kw) in enumerate(cases):
         w, L, enc = _case(c, 1200 + i)
-        r = gpu_decode(amd.BeamDecoder(c, w, **kw), enc, L)
-        assert r["n_steps"].max() > 2 * 16
+        dec = amd.BeamDecoder(c, w, **kw)
+        dec.debug_rebuild_resident(0)  # (the resident loop has no chunks)
+        r = gpu_decode(dec, enc, L)
+        assert dec.last_step_loop() == "graph" and r["n_steps"].max() > 2 * 16
         ref = gpu_decode(amd.BeamDecoder(c, w, async_enqueue=True, **kw), enc, L)
         for key in ("tokens", "lens", "scores", "n_steps"):
             np.testing.assert_array_equal(r[key], ref[key])
@@ -616,11 +623,11 @@ def test_single_launch_step_loop_equals_the_per_step_launches(amd, oracle, kw):
     and scores must be identical bit for bit; batches that leave some XCDs without an utterance included."""
     c = S.custom_config(T=22, T_min=6, D=64, H=192, P=192, E=64, V=150, s=3, blank_bias=3.0, **kw)
     w, L, enc = _case(c, 1300 + kw["B"], zero_len=True)
-    ref = gpu_decode(amd.BeamDecoder(c, w), enc, L)
+    ref = gpu_decode(amd.BeamDecoder(c, w, use_graph=False), enc, L)
     dec = amd.BeamDecoder(c, w, persistent=True)
     for _ in range(2):
         r = gpu_decode(dec, enc, L)
-        assert r["rc"] == 0
+        assert r["rc"] == 0 and dec.last_step_loop() == "single launch"
         for key in ("tokens", "lens", "scores", "n_steps", "parent", "token", "merged"):
             np.testing.assert_array_equal(r[key], ref[key])
     o = oracle.decode(c, w, enc, L, log=True)
