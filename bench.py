@@ -169,6 +169,7 @@ def measure(S, A, torch, cid: int, variant: str, steps: int, warmup: int, args, 
     ms = dt / steps * 1e3
     value = audio_s * steps / dt
     n_steps = int(r["n_steps"].max())
+    step_loop = dec.last_step_loop()
     gpu_ms = dec.last_decode_ms()
 
     # same kernels at beam 1 (greedy)
@@ -222,16 +223,25 @@ def measure(S, A, torch, cid: int, variant: str, steps: int, warmup: int, args, 
         roofline["traffic"] = round(tj["fetch_bytes"] + tj["write_bytes"])
         roofline["traffic_source"] = os.path.relpath(tpath, ROOT)
     gpath = os.path.join(ROOT, "profiles", "%s_in_graph.json" % name)
-    # decoders that fit the chip run the resident loop: the launches above are those that it replaces (profiling mode, and
-    # the fallback), and what the timed passes reach is the whole loop's rate
-    resident = not (args.no_graph or args.single_launch or args.async_enqueue or c.get("tdt_pairs")) and c["V"] <= 1024
-    if resident:
-        fl = kernel_flops("k_step_main", c, M, B, T) + kernel_flops("k_pred_proj", c, M, B, T)
-        ach = fl * n_steps / (gpu_ms * 1e-3) / 1e12
-        roofline["resident_loop"] = dict(flops_per_step=fl, us_per_step=round(gpu_ms * 1e3 / max(n_steps, 1), 3),
-                                         achieved=round(ach, 3), unit="TFLOP/s",
-                                         note="the timed passes: one launch for all steps (all hypotheses of all steps "
-                                              "counted, decode time with projection and back-trace)")
+    if step_loop == "resident":
+        # one launch for all steps: what it must multiply (an utterance's hypotheses up to its own last step; slots of finished
+        # utterances beside unfinished ones are work that does not count) over the time of the whole decode.  The launches
+        # above are those that it replaces (profiling mode, and the fallback).
+        rows = float(np.asarray(r["n_steps"], dtype=np.float64).sum()) * K
+        work = (kernel_flops("k_step_main", c, M, B, T) + kernel_flops("k_pred_proj", c, M, B, T)) / M * rows
+        ach = work / (gpu_ms * 1e-3) / 1e12
+        launches = roofline
+        roofline = dict(kernel="k_decode_resident", bound="mfma", achieved=round(ach, 3), peak=PEAK_FP32_MFMA_TFLOPS,
+                        unit="TFLOP/s", frac=round(ach / PEAK_FP32_MFMA_TFLOPS, 5), traffic=None,
+                        avg_us=round(gpu_ms * 1e3, 1), us_per_step=round(gpu_ms * 1e3 / max(n_steps, 1), 3),
+                        timing="HIP events around the whole decode, with encoder projection and back-trace",
+                        flops_per_launch=work, per_step_launches=launches)
+        tpath = os.path.join(ROOT, "profiles", "%s_k_decode_resident_traffic.json" % name)
+        if os.path.exists(tpath):
+            with open(tpath) as f:
+                tj = json.load(f)
+            roofline["traffic"] = round(tj["fetch_bytes"] + tj["write_bytes"])
+            roofline["traffic_source"] = os.path.relpath(tpath, ROOT)
     elif os.path.exists(gpath):
         with open(gpath) as f:
             gj = json.load(f)
@@ -249,12 +259,12 @@ def measure(S, A, torch, cid: int, variant: str, steps: int, warmup: int, args, 
                 **({"lm_rule": args.lm_rule, "lm_prune": args.lm_prune} if c["lm"] else {}),
                 **({"tdt_pairs": True} if c.get("tdt_pairs") else {}),
                 **({"async_enqueue": True} if args.async_enqueue else {}),
-                **({"step_loop": "single launch"} if args.single_launch else {})},
+                "step_loop": step_loop},
         beam_search_steps=n_steps, us_per_beam_step=round(gpu_ms * 1e3 / max(n_steps, 1), 3),
         gpu_ms_per_pass=round(gpu_ms, 4), beam1_ms_per_pass=round(ms_beam1, 4), beam_over_greedy=round(ms / ms_beam1, 4),
         roofline=roofline, kernels=kernels)
     joint = "k_joint_big" if "k_joint_big" in loop else "k_step_main"
-    out["joint_launch_mfma_util"] = loop[joint]["frac_of_bound"]
+    out["joint_launch_mfma_util"] = roofline["frac"] if step_loop == "resident" else loop[joint]["frac_of_bound"]
     if want_cpu:
         import oracle
         n_utt = min(args.cpu_utts, B)
