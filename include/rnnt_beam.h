@@ -115,11 +115,12 @@ typedef struct {
                                 the most likely one that advances).  1: every (symbol, duration) pair is a candidate
                                 of its own, blank only with durations >= 1: Beam x (V + 1) x n_durations candidates
                                 per utterance and step.  Needs max_beam <= 8 */
-  int32_t async_enqueue;     /* 0: rnnt_beam_decode enqueues chunks of 16 steps, one chunk ahead of the device, and
-                                returns once the device has reported that every utterance has finished (the calling
-                                thread is blocked for most of the decode).  1: it enqueues the upper bound of
-                                T (max_symbols + 1) steps at once and returns without waiting; steps after the last
-                                utterance has finished return at once on the device (a few microseconds each) */
+  int32_t async_enqueue;     /* 0: rnnt_beam_decode enqueues the resident loop or, without it, chunks of 16 steps, one chunk ahead
+                                of the device, and returns once the device has reported that every utterance has finished
+                                (the calling thread is blocked for most of the decode).  1: it enqueues the upper bound of
+                                T (max_symbols + 1) steps at once (replayed graphs or launches, never the resident loop) and
+                                returns without waiting; steps after the last utterance has finished return at once on the
+                                device (a few microseconds each) */
   int32_t aes_prefix_search; /* RNNT_AES only: maximum-length prefix search (Sec. 2.2, "AES": probabilities of hypotheses
                                 with shared prefixes are combined; only the longest proper prefix is looked at).  When
                                 two hypotheses expanded in the same frame hold y and y + v, and the expansion of y by v
@@ -184,15 +185,15 @@ int rnnt_lm_create(int32_t order, int64_t n, const int32_t *ngram_tokens, const 
  * (1 + lambda) ln p(blank), tokens as ln p + lambda ln((1 - p(blank)) p_LM)), combined before the
  * beam is cut (late pruning); the config fields lm_rule and lm_early_pruning select Eq. (3) and early
  * pruning.  An LM together with a finite prune_margin is rejected.
- * Work is enqueued on hip_stream (a hipStream_t, NULL = default stream) in chunks of 16 steps, one
- * chunk ahead of the device; the call returns once the device has reported (through a pinned word)
- * that every utterance has finished and the back-trace has been enqueued, i.e. it blocks the calling
- * thread for most of the decode's duration (config field async_enqueue: enqueue everything and return).
- * Steps enqueued after the last utterance finished (under two chunks of them) still run; their kernels return at once.
- * The chunk behind the running one is enqueued when the running one is about 60 % through; the thread spins meanwhile
- * on two words of pinned host memory that the device writes (every utterance finished; a chunk begins).  Environment
- * variable RNNT_BEAM_TRACE_PACING (read at create): a line on stderr whenever that report does not arrive within
- * 200 ms and the thread waits for the stream instead.
+ * Work is enqueued on hip_stream (a hipStream_t, NULL = default stream): the resident loop as one launch (config field
+ * use_graph), other decodes in chunks of 16 steps, one chunk ahead of the device.  The call returns once the device has
+ * reported, through pinned words on which the thread spins, that every utterance has finished; the back-trace has been enqueued
+ * by then.  It blocks the calling thread for most of the decode's duration (config field async_enqueue: enqueue everything and
+ * return).  A resident loop that gave up is replaced by the chunks within the call.
+ * Chunks: steps enqueued after the last utterance finished (under two chunks of them) still run; their kernels return at once.
+ * The chunk behind the running one is enqueued when the running one is about 60 % through.  Environment variable
+ * RNNT_BEAM_TRACE_PACING (read at create): a line on stderr whenever the begin of a chunk is not reported within 200 ms and the
+ * thread waits for the stream instead, and whenever a resident loop gave up.
  * Results stay valid until the next decode.  Graphs captured for a decode hold the LM's device tables: an LM
  * must outlive every decode that uses it, and at most 8 graphs (distinct B, T, beam, algo, LM, LM weight) are
  * kept per handle, the oldest being dropped.
