@@ -25,7 +25,7 @@ struct Resident {
   uint64_t *words = nullptr;
   int *ctl = nullptr;
   ResTab *tab = nullptr;          // who owns what in a group, as uploaded for the last launch:
-  int tab_blocks = 0, tab_sel = 0, tab_lm = -1;
+  int tab_blocks = 0, tab_sel = 0;
   int *h_abort = nullptr, *h_abort_dev = nullptr;  // pinned
   std::vector<void *> allocs;
 };

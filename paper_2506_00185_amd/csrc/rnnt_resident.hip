@@ -278,14 +278,13 @@ hipError_t resident_launch(Resident &r, const rnnt_config_t &c, const ResidentBa
   a.start_limit = short_spin ? 100 : 5000000;  // 50 ms
   *reinterpret_cast<volatile int *>(r.h_abort) = 0;
   hipError_t e = hipSuccess;
-  if (r.tab_blocks != p.n_blocks || r.tab_sel != p.n_sel || r.tab_lm != a.has_lm) {
+  if (r.tab_blocks != p.n_blocks || r.tab_sel != p.n_sel) {
     // (pageable memory: the call returns when it has been read; the last launch that read the table is over, as its
     // decode waited for it)
     e = hipMemcpyAsync(r.tab, p.tab.data(), sizeof(ResTab) * p.tab.size(), hipMemcpyHostToDevice, s);
     if (e != hipSuccess) return e;
     r.tab_blocks = p.n_blocks;
     r.tab_sel = p.n_sel;
-    r.tab_lm = a.has_lm;
   }
   hipLaunchKernelGGL(k_resident_init, dim3(512), dim3(256), 0, s, a);
   const bool plain = c.n_durations == 0 && !b.has_lm && b.algo == RNNT_ALSD;
