@@ -286,7 +286,8 @@ int rnnt_beam_debug_set_spin_limit(rnnt_beam_t *h, int32_t polls);
 
 /* Test hook for the waits inside the resident loop (use_graph): at step `step` the owners of the output layer publish no
  * logits for the last tile of 16 hypotheses that they hold and end; the other blocks' waits give up (after 4096 polls
- * instead of 2^19) and the batch is decoded with per-step launches.  -1 (default): off. */
+ * instead of 2^19) and the batch is decoded with per-step launches.  -1 (default): off.  -2: no such step, but every group
+ * of blocks takes itself to lie on several XCDs and writes its hand-over stores through. */
 int rnnt_beam_debug_stall_resident(rnnt_beam_t *h, int32_t step);
 
 /* Test hook for the resident loop's memory: its second copy of the weights, hand-over arrays and tables are given back and laid

@@ -4,8 +4,8 @@
 // What bounds the per-step launches is not their work but their boundaries: three dependent kernels of 4 to 14 us per
 // step of which each pays 2 to 3 us of launch head and tail, fetches the weights anew (the caches do not survive a
 // kernel boundary) and hands its results over through memory.  Here the utterances are dealt out to groups of blocks
-// (one group per 32 compute units where there are as many utterances; that more, emptier groups beat fewer, fuller ones has not
-// been measured) that decode them independently of each other.  A group holds every weight of
+// (one group per 32 compute units where there are as many utterances, each on an XCD of its own; that more, emptier groups beat
+// fewer, fuller ones has not been measured) that decode them independently of each other.  A group holds every weight of
 // the three contractions once, in registers and LDS: a block owns some 16-row tiles of W_hh (at most 6, with the LSTM
 // cells of their four units each), of the output layer and of the prediction projection.  One step of a group:
 //   cell    words of the last step -> the owners of W_hh tiles update the cells of their units        -> h
@@ -16,7 +16,7 @@
 // Hand-over between blocks: an array that one phase writes and another reads is pre-filled with a bit pattern that no
 // result has (a NaN with all bits set); the reader loads the data itself, device-coherently, until none of it holds the
 // pattern.  No barrier, no flag and no acknowledged store lies between the two (one hop costs 0.6 us; stores, their
-// acknowledgement, a counter and then the loads 2.0 us).  The words of the selection carry the step's number instead.
+// acknowledgement, a counter and then the loads 2.0 us).  The blocks of a group lie on one XCD and hand over through its L2.  The words of the selection carry the step's number instead.
 // A writer puts the pattern back once a word of a later phase proves that every reader is through (see the clear_
 // functions), one or two steps before the place is used again.
 //
@@ -46,7 +46,8 @@ constexpr int kResMaxP = 2;
 constexpr int kResMaxSel = 4;        // utterances per selecting block
 constexpr int kResMaxRounds = 10;    // rounds of 8 k per wave slice: H, P <= 640
 constexpr int kResMaxV = 1024;
-constexpr int kResStepRing = 4;      // ring of h and of the words; pre and logits alternate
+constexpr int kResStepRing = 4;      // ring of the hand-over arrays
+constexpr int kResNotLocal = -2;     // stall_step of a test: the groups take themselves to lie on several XCDs
 constexpr uint32_t kResEmpty = 0xffffffffu;
 constexpr int kResSurvivors = 128;
 constexpr int kResRedBlock = 2048;   // floats of one 16-row tile's partial sums: 8 waves x 64 lanes x 4
@@ -80,18 +81,19 @@ struct ResArgs {
   float *hb, *pb, *zb;               // rings of the hand-over arrays, all groups
   uint64_t *words;
   const ResTab *tab;                 // of the group's blocks behind the selecting ones
-  int *ctl;                          // [0] blocks that have started, [1] abort
+  int *ctl;                          // [0] blocks that have started, [1] abort, [2 + group] the XCDs that its blocks found themselves on
   volatile int *h_abort;             // pinned host word
   SelectArgs sel;
   LmView lm;
   int B, K, T, V, N, Npad, H, P;
-  int n_groups, n_sel, upc;          // groups; per group: selecting blocks, utterances of each
+  int n_groups, stride;              // groups; block i of the launch is of group i % stride (there may be fewer groups)
+  int n_sel, upc;                    // per group: selecting blocks, utterances of each
   int NT, halves, has_lm;            // slot tiles per group
   int rounds_h, rounds_p;            // rounds of 8 k per wave slice over H and over P
   int poll_limit, start_limit;       // polls of a data wait; ticks (10 ns) of the wait for all blocks
   int start_blocks;                  // how many those are
   int fold;                          // the per-step launches would fold the blank and duration columns (see res_fold_mma)
-  int stall_step;                    // a test's: from this step on the last tile of slots gets no logits (-1: never)
+  int stall_step;                    // a test's: from this step on the last tile of slots gets no logits (below 0: never)
 };
 
 // The kernel's arguments, read from the argument segment anew at the begin of every phase: kept in scalar registers over
@@ -149,8 +151,7 @@ struct ResWait {
   }
 };
 
-// Waits until one 8-byte word of every lane is there.  (One load per poll: all blocks of a group poll at once, and with all
-// words of a lane in every poll, 5 KB per wave, the polls alone filled the L2's bandwidth.)
+// Waits until one 8-byte word of every lane is there.
 __device__ __forceinline__ bool res_probe(const uint64_t *p, ResWait &w) {
   for (;;) {
     const uint64_t x[1] = {load_agent(p)};
@@ -158,13 +159,13 @@ __device__ __forceinline__ bool res_probe(const uint64_t *p, ResWait &w) {
     if (!w.again()) return false;
   }
 }
-// N 8-byte words of a lane as soon as all are there (in every lane of the wave), the last one first.  at(i): address of
-// word i; the first n are used (FULL: all N).
+// N 8-byte words of a lane as soon as all are there (in every lane of the wave).  at(i): address of word i; the first n are
+// used (FULL: all N).  (Every poll loads all of them.  With a poll of one word first, a trip to the L2 lay between the arrival of
+// the data and its use: batch 32 / beam 4 9.26 instead of 8.95 ms per decode.)
 template <bool FULL, int N, class AT>
 __device__ __forceinline__ bool res_gather(AT at, int n, uint64_t (&x)[N]) {
   ResWait w;
   for (;;) {
-    if (!res_probe(at(FULL ? N - 1 : n - 1), w)) return false;
 #pragma unroll
     for (int i = 0; i < N; ++i) {
       x[i] = 0;
@@ -190,13 +191,13 @@ struct ResAddr {
   size_t h_ring, p_ring, z_ring, w_ring, h_tile, p_tile;
   int Npad;
   __device__ __forceinline__ float *h(int step, int nt) const { return hb + (step & (kResStepRing - 1)) * h_ring + nt * h_tile; }
-  __device__ __forceinline__ float *p(int step, int nt) const { return pb + (step & 1) * p_ring + nt * p_tile; }
-  __device__ __forceinline__ float *z(int step, int slot) const { return zb + (step & 1) * z_ring + (size_t)slot * Npad; }
+  __device__ __forceinline__ float *p(int step, int nt) const { return pb + (step & (kResStepRing - 1)) * p_ring + nt * p_tile; }
+  __device__ __forceinline__ float *z(int step, int slot) const { return zb + (step & (kResStepRing - 1)) * z_ring + (size_t)slot * Npad; }
   __device__ __forceinline__ uint64_t *w(int step) const { return words + (step & (kResStepRing - 1)) * w_ring; }
 };
 __host__ __device__ inline size_t res_h_floats(const ResArgs &a) { return a.emb_tab ? 0 : (size_t)kResStepRing * a.n_groups * a.NT * a.P * kResSlot; }
-__host__ __device__ inline size_t res_p_floats(const ResArgs &a) { return a.emb_tab ? 0 : (size_t)2 * a.n_groups * a.NT * a.H * kResSlot; }
-__host__ __device__ inline size_t res_z_floats(const ResArgs &a) { return (size_t)2 * a.n_groups * a.NT * kResSlot * a.Npad; }
+__host__ __device__ inline size_t res_p_floats(const ResArgs &a) { return a.emb_tab ? 0 : (size_t)kResStepRing * a.n_groups * a.NT * a.H * kResSlot; }
+__host__ __device__ inline size_t res_z_floats(const ResArgs &a) { return (size_t)kResStepRing * a.n_groups * a.NT * kResSlot * a.Npad; }
 __host__ __device__ inline size_t res_words(const ResArgs &a) { return (size_t)kResStepRing * a.n_groups * a.NT * kResSlot; }
 __device__ __forceinline__ ResAddr res_addr(const ResArgs &a, int g) {
   ResAddr r;
@@ -217,6 +218,7 @@ __device__ __forceinline__ ResAddr res_addr(const ResArgs &a, int g) {
 // what a wave knows about itself and its block
 struct ResBlock {
   int g, nu, nslots;                 // group, utterances and slots of the group
+  bool local;                        // the group's blocks share one XCD (see res_store)
   int nt;                            // slot tiles up to the last one with an unfinished utterance: the others are left out
   const int16_t *order;              // LDS: the group's utterances (indices in the batch), longest first
   int nR, nJ, nP;
@@ -343,13 +345,13 @@ __device__ __forceinline__ void res_p_finish(const ResArgs &a, const ResBlock &k
   if (a.halves) v += res_sum<BF16>(k, l, second);
   float *dst = res_p_dst(ad.p(step, nt), k.ptile, l.kq, l.sl);
   wait_stores_acknowledged();  // (of the pattern that this wave put back into places of the array meanwhile)
-  store_agent(reinterpret_cast<uint64_t *>(dst), pack2(v[0], v[1]));
-  store_agent(reinterpret_cast<uint64_t *>(dst + 2 * kResSlot), pack2(v[2], v[3]));
+  res_store(k.local, reinterpret_cast<uint64_t *>(dst), pack2(v[0], v[1]));
+  res_store(k.local, reinterpret_cast<uint64_t *>(dst + 2 * kResSlot), pack2(v[2], v[3]));
 }
 __device__ __forceinline__ void clear_p(const ResBlock &k, const ResLane &l, const ResAddr &ad, int step, int nt) {
   float *dst = res_p_dst(ad.p(step, nt), k.ptile, l.kq, l.sl);
-  store_agent(reinterpret_cast<uint64_t *>(dst), (uint64_t)~0ull);
-  store_agent(reinterpret_cast<uint64_t *>(dst + 2 * kResSlot), (uint64_t)~0ull);
+  res_store(k.local, reinterpret_cast<uint64_t *>(dst), (uint64_t)~0ull);
+  res_store(k.local, reinterpret_cast<uint64_t *>(dst + 2 * kResSlot), (uint64_t)~0ull);
 }
 // the wave that finishes a tile of the projection: from the last one down, which own no cells
 __device__ __forceinline__ int res_p_wave(int tile_no) { return kResWaves - 1 - tile_no; }
@@ -503,12 +505,12 @@ __device__ __forceinline__ void res_j_finish(const ResBlock &k, const ResLane &l
   const int slot = nt * kResSlot + l.sl, n0 = 16 * tile + 4 * l.kq;
   const floatx4 v = res_sum<BF16>(k, l, block) + bias;
   wait_stores_acknowledged();
-  if (slot < k.nslots) store16_through(ad.z(step, slot) + n0, v);
+  if (slot < k.nslots) res_store16(k.local, ad.z(step, slot) + n0, v);
 }
 __device__ __forceinline__ void clear_z(const ResBlock &k, const ResLane &l, const ResAddr &ad, int step, int nt, int tile) {
   const int slot = nt * kResSlot + l.sl;
   const float e = __uint_as_float(kResEmpty);
-  if (slot < k.nslots) store16_through(ad.z(step, slot) + 16 * tile + 4 * l.kq, floatx4{e, e, e, e});
+  if (slot < k.nslots) res_store16(k.local, ad.z(step, slot) + 16 * tile + 4 * l.kq, floatx4{e, e, e, e});
 }
 
 // Stateless decoders: the wave's slice of pre of its lanes' slots, as res_gather / bf16_gather would have read it, summed up
@@ -726,8 +728,9 @@ __device__ __forceinline__ bool res_j_phase(ResBlock &k, int step, const float (
 }
 
 // the block's own pieces of pre[step] and of the logits of `step`: every word of `step` has been seen, i.e. every selecting
-// block has read its logits, which needed every piece of pre
-// (the wave that writes a place next is the one that clears it, with a wait for its stores in between)
+// block has read its logits, which needed every piece of pre.
+// Who reads a place next (four steps on, see kResStepRing) has seen words that needed what this wave wrote for two steps on,
+// which it stores behind the acknowledgement of these.
 template <bool BF16>
 __device__ __forceinline__ void res_clear_pz(const ResArgs &a, const ResBlock &k, const ResAddr &ad, int step) {
   const ResLane l = res_lane();
@@ -884,7 +887,7 @@ __device__ __forceinline__ void res_worker(ResBlock k, const ResTab &tab, float 
           hn[nt] = hl[at];
           if (word_tok(w) >= 0) hn[nt] = lstm_unit(*reinterpret_cast<const float4 *>(Rl + at * 4), g4[nt], cn[nt]);
           if (nt == 0) wait_stores_acknowledged();
-          store_agent(ad.h(step, nt) + hofs, hn[nt]);
+          res_store(k.local, ad.h(step, nt) + hofs, hn[nt]);
         }
       wave_sync();
 #pragma unroll
@@ -895,13 +898,14 @@ __device__ __forceinline__ void res_worker(ResBlock k, const ResTab &tab, float 
           hl[at] = hn[nt];
         }
     }
+    if constexpr (!ST)
+      if (!res_p_phase<FULL, BF16>(k, step)) return;
+    if (!res_j_phase<FULL, BF16, ST>(k, step, wj)) return;
+    // (under the selection: ahead of the projection the waits for the activations included these stores)
     if (step > 0) {
       const ResArgs &a = res_args();
       res_clear_pz<BF16>(a, k, res_addr(a, k.g), step - 1);
     }
-    if constexpr (!ST)
-      if (!res_p_phase<FULL, BF16>(k, step)) return;
-    if (!res_j_phase<FULL, BF16, ST>(k, step, wj)) return;
     // ---- R
     if constexpr (!ST) if (k.nR > 0) {
       const ResArgs &a = res_args();
@@ -916,7 +920,7 @@ __device__ __forceinline__ void res_worker(ResBlock k, const ResTab &tab, float 
       // 1.3 % slower.)
       if (step > 1 && k.wave < k.nR)
         for (int nt = 0; nt < k.nt; ++nt)
-          store_agent(reinterpret_cast<uint32_t *>(ad.h(step - 2, nt) + res_h_ofs(l, mytile)), kResEmpty);
+          res_store(k.local, reinterpret_cast<uint32_t *>(ad.h(step - 2, nt) + res_h_ofs(l, mytile)), kResEmpty);
 #pragma unroll 1
       for (int nt = 0; nt < k.nt; ++nt) {
         uint64_t x[kResMaxRounds];
@@ -1259,6 +1263,7 @@ __device__ __forceinline__ void res_selector(ResBlock k, int sel, float *lds) {
     rs.T_b = a0.lengths[res_utt(k, u)];
     rs.lm = lm_rows + (size_t)k.wave * K * V;
     rs.finished = rs.T_b == 0;
+    rs.local = k.local;
   }
   __syncthreads();
   int over = res_first_words(a0, k);
@@ -1290,7 +1295,7 @@ __device__ __forceinline__ void res_selector(ResBlock k, int sel, float *lds) {
       rs.words = res_addr(a, k.g).w(step) + u * K;
       rs.step = step;
       if (rs.finished) {
-        if (lane < K) store_agent(rs.words + lane, slot_word(step, 1, u * K + lane, -1, 0));
+        if (lane < K) res_store(k.local, rs.words + lane, slot_word(step, 1, u * K + lane, -1, 0));
       } else {
         const CandView cv{L.cand + k.wave * K * K, L.smax + k.wave * K, L.ssum + k.wave * K, L.zs + k.wave * K * (1 + a.sel.ND), b * K};
         if constexpr (KC == 4) select_utterance<16, 1, 4, false, false, SelectScratchWide, true, PLAIN, false, true>(a.sel, b, scratch[k.wave], cv, &rs);
@@ -1315,7 +1320,11 @@ __global__ __launch_bounds__(kResThreads, 2) void k_decode_resident(ResArgs) {
   const ResArgs &a = res_args();
   if (*reinterpret_cast<const volatile int *>(a.sel.done)) return;
   // every block of the launch must be on the chip before any of them waits for another's data
+  const int g = (int)blockIdx.x % a.stride;  // (workgroup i runs on XCD i % 8)
+  if (g >= a.n_groups) return;
   if (threadIdx.x == 0) {
+    __hip_atomic_fetch_or(a.ctl + 2 + g, 1 << (__builtin_amdgcn_s_getreg((3 << 11) | 20) & 15), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    wait_stores_acknowledged();
     __hip_atomic_fetch_add(a.ctl, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     const long long t0 = wall_clock64();
     int ok = 0;
@@ -1332,12 +1341,11 @@ __global__ __launch_bounds__(kResThreads, 2) void k_decode_resident(ResArgs) {
       }
       __builtin_amdgcn_s_sleep(4);
     }
-    s_ok = ok;
+    s_ok = ok && __popc(load_agent(a.ctl + 2 + g)) == 1 && a.stall_step != kResNotLocal ? 2 : ok;
   }
   ResBlock k;
-  // (workgroup i runs on XCD i % 8: the blocks of a group share as few L2s as they can)
-  k.g = (int)blockIdx.x % a.n_groups;
-  const int rank = (int)blockIdx.x / a.n_groups;
+  k.g = g;
+  const int rank = (int)blockIdx.x / a.stride;
   k.nu = (a.B - k.g + a.n_groups - 1) / a.n_groups;
   // utterances of the group, g + n_groups i, the longest first: the ends of the slots run empty first, and tiles behind
   // the last unfinished utterance are left out of every phase (TDT, 64 utterances of 4 to 20 s, beam 4: 5.90 -> 5.22 ms;
@@ -1356,6 +1364,7 @@ __global__ __launch_bounds__(kResThreads, 2) void k_decode_resident(ResArgs) {
   k.nt = a.NT;
   __syncthreads();
   if (!s_ok) return;
+  k.local = res_uniform(s_ok) == 2;
   k.nslots = k.nu * a.K;
   k.wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   k.phase = 0;

@@ -1593,7 +1593,7 @@ int rnnt_beam_debug_set_spin_limit(rnnt_beam_t *h, int32_t polls) {
 }
 
 int rnnt_beam_debug_stall_resident(rnnt_beam_t *h, int32_t step) {
-  if (!h || step < -1) return RNNT_E_ARG;
+  if (!h || step < -2) return RNNT_E_ARG;
   h->stall_step = step;
   return RNNT_OK;
 }

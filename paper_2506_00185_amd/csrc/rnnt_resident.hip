@@ -61,16 +61,17 @@ __global__ void k_resident_init(ResArgs a) {
   for (size_t i = gid; i < res_p_floats(a) / 4; i += n) reinterpret_cast<uintx4_t *>(a.pb)[i] = e;
   for (size_t i = gid; i < res_z_floats(a) / 4; i += n) reinterpret_cast<uintx4_t *>(a.zb)[i] = e;
   for (size_t i = gid; i < res_words(a); i += n) a.words[i] = 0;
-  if (gid < 2) a.ctl[gid] = 0;
+  if (gid < 64) a.ctl[gid] = 0;
 }
 
 constexpr int kResShortSpin = 1000;  // a test's limit: the launch waits, for a microsecond, for one block more than it has
 
+constexpr int kResMaxGroups = 62;  // words of ctl
 constexpr int kResStallPolls = 4096;  // a test's wait for data that does not come
 
 struct Plan {
   bool ok = false;
-  int n_groups = 0, n_blocks = 0, nu = 0, n_sel = 0, upc = 0, NT = 0;
+  int n_groups = 0, stride = 0, n_blocks = 0, nu = 0, n_sel = 0, upc = 0, NT = 0;
   size_t lds = 0;
   std::vector<ResTab> tab;
 };
@@ -135,12 +136,14 @@ bool per_step_is_faster(const rnnt_config_t &c, int B, int K, int n_tiles) {
 
 Plan make_plan(const Resident &r, const rnnt_config_t &c, int B, int K, bool has_lm, bool fold) {
   Plan p;
-  // one group per 32 compute units at most (a group of 32 holds the weights of a 640-wide decoder), never more groups
-  // than utterances: few utterances get more blocks each
-  int G = 1;
-  while (2 * G <= B && 2 * G * 32 <= r.n_cus) G *= 2;
+  // One group per 32 compute units at most (they hold the weights of a 640-wide decoder), and never more than utterances.
+  // Each group is on one XCD (see res_store); the others stay free when there are fewer utterances.  (One utterance of 125 frames
+  // on all 256 units, with written-through stores between the XCDs: 9.4 ms, on the 32 of one: 8.6; 7 utterances in 4 groups 7.3,
+  // in 7 groups 6.4.)
+  p.stride = std::min(std::max(1, r.n_cus / 32), kResMaxGroups);
+  const int G = std::min(B, p.stride);
   p.n_groups = G;
-  p.n_blocks = r.n_cus / G;
+  p.n_blocks = r.n_cus / p.stride;
   p.nu = (B + G - 1) / G;
   const int slots = p.nu * K;
   p.NT = (slots + kResSlot - 1) / kResSlot;
@@ -222,10 +225,10 @@ int resident_create(Resident &r, const rnnt_config_t &c, const ResidentWeights &
   const int nR = 4 * c.P / 16, nJ = bf ? (N + 31) / 32 : (N + 15) / 16, nP = bf ? c.H / 32 : c.H / 16;
   bool ok = bf ? alloc(&r.WJb, (size_t)nJ * (c.H / 8) * 64) : alloc(&r.WJ, (size_t)nJ * 16 * c.H) && alloc(&r.WJs, (size_t)16 * c.H);
   if (lstm) {
-    ok = ok && alloc(&r.WR, (size_t)nR * 16 * c.P) && alloc(&r.hb, kResStepRing * rows * c.P) && alloc(&r.pb, 2 * rows * c.H);
+    ok = ok && alloc(&r.WR, (size_t)nR * 16 * c.P) && alloc(&r.hb, kResStepRing * rows * c.P) && alloc(&r.pb, kResStepRing * rows * c.H);
     ok = ok && (bf ? alloc(&r.WPb, (size_t)nP * (c.P / 8) * 64) : alloc(&r.WP, (size_t)nP * 16 * c.P));
   }
-  ok = ok && alloc(&r.zb, 2 * rows * w.out_rows) &&
+  ok = ok && alloc(&r.zb, kResStepRing * rows * w.out_rows) &&
        alloc(&r.words, kResStepRing * rows) && alloc(&r.ctl, 64) && alloc(&r.tab, r.n_cus);
   if (!ok) return fail("resident loop: hipMalloc");
   if ((e = hipHostMalloc(reinterpret_cast<void **>(&r.h_abort), 128, hipHostMallocMapped)) != hipSuccess) return fail("hipHostMalloc");
@@ -267,7 +270,7 @@ hipError_t resident_launch(Resident &r, const rnnt_config_t &c, const ResidentBa
   a.sel = b.sel;
   a.lm = b.lm;
   a.B = b.B; a.K = b.K; a.T = b.T; a.V = c.V; a.N = c.V + 1 + c.n_durations; a.Npad = b.Npad; a.H = c.H; a.P = c.P;
-  a.n_groups = p.n_groups; a.n_sel = p.n_sel; a.upc = p.upc;
+  a.n_groups = p.n_groups; a.stride = p.stride; a.n_sel = p.n_sel; a.upc = p.upc;
   a.NT = p.NT; a.halves = b.halves ? 1 : 0; a.has_lm = b.has_lm ? 1 : 0;
   a.rounds_h = c.H / 64; a.rounds_p = c.P / 64;
   a.fold = b.fold ? 1 : 0;
@@ -291,7 +294,7 @@ hipError_t resident_launch(Resident &r, const rnnt_config_t &c, const ResidentBa
   ResKernel k = b.emb_tab ? pick_kernel<true>(c, b.K, plain) : pick_kernel<false>(c, b.K, plain);
   e = hipFuncSetAttribute(reinterpret_cast<const void *>(k), hipFuncAttributeMaxDynamicSharedMemorySize, (int)p.lds);
   if (e != hipSuccess) return e;
-  hipLaunchKernelGGL(k, dim3(p.n_groups * p.n_blocks), dim3(kResThreads), p.lds, s, a);
+  hipLaunchKernelGGL(k, dim3(p.stride * p.n_blocks), dim3(kResThreads), p.lds, s, a);
   return hipGetLastError();
 }
 

@@ -187,6 +187,20 @@ __device__ __forceinline__ void rank_by_counting_n(const double *keys, const int
   }
 }
 
+// Hand-over stores.  Blocks on one XCD share its L2: a plain store leaves the data there, and a device-coherent load finds it
+// there (such a load passes by the L1 but not by the L2: 107 ns, like any other that the L2 answers).  Across XCDs the store has
+// to be written through, which takes longer to be seen and to be acknowledged.  (One word from block to block and back, per
+// direction: 272 ns on one XCD with plain stores, 375 with written-through ones, 440 between two XCDs.)
+template <typename T>
+__device__ __forceinline__ void res_store(bool local, T *p, T v) {
+  if (local) __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WAVEFRONT);
+  else store_agent(p, v);
+}
+__device__ __forceinline__ void res_store16(bool local, float *p, floatx4 v) {
+  if (local) asm volatile("global_store_dwordx4 %0, %1, off" ::"v"(p), "v"(v) : "memory");
+  else store16_through(p, v);
+}
+
 // How the resident loop (kernels_resident.h) calls the selection: the hypotheses' state stays in the scratch from one step
 // to the next (score .. hash, ctx), and what the step decided for each slot leaves as one word (slot_word) that every
 // block of the group waits for.
@@ -196,6 +210,7 @@ struct ResidentSelect {
   int step, T_b;
   const float *lm;      // [K][V] LM scores (log10) of the slots in LDS (early pruning)
   int finished;         // out: the utterance's last step is done
+  bool local;           // see res_store
 };
 // step tag (16 bits, step + 1) | utterance finished (1) | parent slot in the group (6) | token + 1 (21) | frame (20)
 constexpr int kWordMaxFrames = 1 << 20;
@@ -806,7 +821,7 @@ __device__ __forceinline__ void select_utterance(const SelectArgs &a, int b, Scr
   if constexpr (RES) {
     last_step = __ballot(live_new && t_new < T_b) == 0ull || S + 1 >= T_b * (a.max_sym + 1);
     if (lane < K)
-      store_agent(rs->words + lane, slot_word(S, last_step ? 1 : 0, rs->slot0 + (parent >= 0 ? parent : lane), appended, t_new));
+      res_store(rs->local, rs->words + lane, slot_word(S, last_step ? 1 : 0, rs->slot0 + (parent >= 0 ? parent : lane), appended, t_new));
   }
   wave_sync();
 

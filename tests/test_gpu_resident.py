@@ -211,6 +211,23 @@ def test_logits_that_do_not_come_end_the_resident_loop_as_a_whole(kw, step):
             np.testing.assert_array_equal(r[key], ref[key])
 
 
+@pytest.mark.parametrize("kw", [dict(B=5, beam=4), dict(B=17, beam=9, prec="bf16"), dict(B=8, beam=4, **ST, ctx=2)], ids=["lstm", "bf16", "stateless"])
+def test_groups_that_do_not_lie_on_one_xcd(kw):
+    """Their hand-over stores are written through: the same words arrive."""
+    import paper_2506_00185_amd as A
+    c = S.custom_config(**dict(dict(T=17, T_min=3, s=3, V=300, blank_bias=3.0, **W640), **kw))
+    w = S.make_weights(c, 45)
+    L = S.make_lengths(c, 47)
+    enc = S.make_enc(c, L, 48)
+    dec = A.BeamDecoder(c, w)
+    ref = gpu_decode(dec, enc, L)
+    dec.debug_stall_resident(-2)
+    r = gpu_decode(dec, enc, L)
+    assert dec.last_step_loop() == "resident"
+    for key in KEYS:
+        np.testing.assert_array_equal(r[key], ref[key])
+
+
 def test_resident_loop_does_not_start_beside_a_single_launch_loop():
     """The single-launch loop's blocks wait for each other too.  One of another handle waits on its stream, behind 40 ms of other
     work, to begin."""
