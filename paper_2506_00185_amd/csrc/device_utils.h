@@ -59,6 +59,83 @@ __device__ __forceinline__ floatx16 mfma32_bf16_from_f32(float4 a0, float4 a1, f
                                                  0, 0);
 }
 
+// ---- float32 products on the 16-bit matrix cores
+// A float32 x as hi + lo, hi = x rounded to float16, lo = the rest rounded to float16: exact to 2^-24 of x, half a unit in the
+// last place of float32, as long as lo is no subnormal number, which scaling by a power of two takes care of.  A product is then
+// hi hi + (hi lo + lo hi); the term left out, lo lo, is 2^-24 of it at most.  Three float16 matrix instructions replace eight
+// float32 ones of twice the cycles each.  Error of sums of 640 products against 64 bits, relative 2-norm (normal weights, h in
+// (-1, 1)): 1.2e-7, with the float32 matrix instructions 1.7e-7, whose chain rounds after every product (these round once per
+// eight); with the two sums in one accumulator 1.4e-7.
+// How the instructions add up (measured): acc + the eight products of one lane in one rounding, the lanes of a row or column
+// one after the other in the order of their k.  Which of the shapes 32x32x16, 16x16x32 and 16x16x16 takes the k does not matter.
+typedef _Float16 f16x2_t __attribute__((ext_vector_type(2)));
+typedef _Float16 f16x4_t __attribute__((ext_vector_type(4)));
+typedef _Float16 f16x8_t __attribute__((ext_vector_type(8)));
+constexpr float kHidScale = 32768.f;  // of hidden states, whose values lie in [-1, 1]
+// two values -> their two hi and their two lo, each pair in one word
+__device__ __forceinline__ void split_f16(float a, float b, uint32_t &hi, uint32_t &lo) {
+  const floatx2_t v = {a, b};
+  const f16x2_t h = __builtin_convertvector(v, f16x2_t);
+  const floatx2_t r = {a - (float)h[0], b - (float)h[1]};
+  hi = __builtin_bit_cast(uint32_t, h);
+  lo = __builtin_bit_cast(uint32_t, __builtin_convertvector(r, f16x2_t));
+}
+__device__ __forceinline__ floatx16 mfma32_f16(uintx4_t a, uintx4_t b, floatx16 acc) {
+  return __builtin_amdgcn_mfma_f32_32x32x16_f16(__builtin_bit_cast(f16x8_t, a), __builtin_bit_cast(f16x8_t, b), acc, 0, 0, 0);
+}
+__device__ __forceinline__ floatx4 mfma16_f16(uintx4_t a, uintx4_t b, floatx4 acc) {
+  return __builtin_amdgcn_mfma_f32_16x16x32_f16(__builtin_bit_cast(f16x8_t, a), __builtin_bit_cast(f16x8_t, b), acc, 0, 0, 0);
+}
+__device__ __forceinline__ floatx4 mfma16_f16(uintx2_t a, uintx2_t b, floatx4 acc) {
+  return __builtin_amdgcn_mfma_f32_16x16x16f16(__builtin_bit_cast(f16x4_t, a), __builtin_bit_cast(f16x4_t, b), acc, 0, 0, 0);
+}
+// 32x32x16 steps of a split product on N (two or four) consecutive 8-k rounds of the float32 scheme (see mfma32): weights come
+// split and scaled (k_split_rows), hidden states are split here.  The order in `cor` is that of the 16x16x32 instructions of the
+// resident loop, which take four rounds at a time.
+template <int N>
+__device__ __forceinline__ void mfma32_split_hid(const float4 (&a)[N], const float4 (&b)[N], floatx16 &acc, floatx16 &cor) {
+  uintx4_t wh[N / 2], wl[N / 2], xh[N / 2], xl[N / 2];
+#pragma unroll
+  for (int i = 0; i < N; i += 2) {
+    const uintx4_t w0 = __builtin_bit_cast(uintx4_t, a[i]), w1 = __builtin_bit_cast(uintx4_t, a[i + 1]);
+    wh[i / 2] = uintx4_t{w0[0], w0[1], w1[0], w1[1]};
+    wl[i / 2] = uintx4_t{w0[2], w0[3], w1[2], w1[3]};
+    uint32_t h[4], l[4];
+    split_f16(b[i].x * kHidScale, b[i].y * kHidScale, h[0], l[0]);
+    split_f16(b[i].z * kHidScale, b[i].w * kHidScale, h[1], l[1]);
+    split_f16(b[i + 1].x * kHidScale, b[i + 1].y * kHidScale, h[2], l[2]);
+    split_f16(b[i + 1].z * kHidScale, b[i + 1].w * kHidScale, h[3], l[3]);
+    xh[i / 2] = uintx4_t{h[0], h[1], h[2], h[3]};
+    xl[i / 2] = uintx4_t{l[0], l[1], l[2], l[3]};
+  }
+#pragma unroll
+  for (int i = 0; i < N / 2; ++i) acc = mfma32_f16(wh[i], xh[i], acc);
+#pragma unroll
+  for (int i = 0; i < N / 2; ++i) cor = mfma32_f16(wh[i], xl[i], cor);
+#pragma unroll
+  for (int i = 0; i < N / 2; ++i) cor = mfma32_f16(wl[i], xh[i], cor);
+}
+// the same on ITERS rounds
+template <int ITERS>
+__device__ __forceinline__ void mfma32_split_hid_rounds(const float4 (&a)[ITERS], const float4 (&b)[ITERS], floatx16 &acc, floatx16 &cor) {
+  const float4 zero4 = make_float4(0.f, 0.f, 0.f, 0.f);
+#pragma unroll
+  for (int i = 0; i < ITERS; i += 4) {
+    if (ITERS - i > 2) {
+      const bool four = i + 3 < ITERS;
+      const int i3 = four ? i + 3 : i;
+      const float4 w[4] = {a[i], a[i + 1 < ITERS ? i + 1 : i], a[i + 2 < ITERS ? i + 2 : i], four ? a[i3] : zero4};
+      const float4 x[4] = {b[i], b[i + 1 < ITERS ? i + 1 : i], b[i + 2 < ITERS ? i + 2 : i], four ? b[i3] : zero4};
+      mfma32_split_hid<4>(w, x, acc, cor);
+    } else {
+      const bool two = i + 1 < ITERS;
+      const int i1 = two ? i + 1 : i;
+      const float4 w[2] = {a[i], two ? a[i1] : zero4}, x[2] = {b[i], two ? b[i1] : zero4};
+      mfma32_split_hid<2>(w, x, acc, cor);
+    }
+  }
+}
+
 __device__ __forceinline__ double logaddexp_d(double a, double b) {
   if (a == -INFINITY) return b;
   if (b == -INFINITY) return a;

@@ -126,6 +126,35 @@ __device__ __forceinline__ void splitk_mma(SplitKOperands<ITERS> &op, AL a_at, B
   __syncthreads();
 }
 
+// The same for weights that k_split_rows has split and hidden states: sums of the tile, still scaled, to LDS.
+template <int WAVES, int ITERS, class AL, class BL>
+__device__ __forceinline__ void splitk_mma_hid(SplitKOperands<ITERS> &op, AL a_at, BL b_at, int K, float *red) {
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, half = lane >> 5;
+  const float4 zero4 = make_float4(0.f, 0.f, 0.f, 0.f);
+  floatx16 acc = {0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0}, cor = acc;
+  if constexpr (ITERS > 0) {
+    mfma32_split_hid_rounds<ITERS>(op.a, op.b, acc, cor);
+  } else {
+    const int kw = K / WAVES, kbeg = wave * kw + 4 * half, kend = (wave + 1) * kw;
+    for (int k = kbeg; k < kend; k += 32) {
+      float4 w[4], x[4];
+#pragma unroll
+      for (int i = 0; i < 4; ++i) {
+        const bool in = k + 8 * i < kend;
+        const float4 w1 = a_at(in ? k + 8 * i : k), x1 = b_at(in ? k + 8 * i : k);
+        w[i] = in ? w1 : zero4;
+        x[i] = in ? x1 : zero4;
+      }
+      mfma32_split_hid<4>(w, x, acc, cor);
+    }
+  }
+  acc += cor;
+  float *mine = red + (wave * 64 + lane) * kRedStride;
+#pragma unroll
+  for (int r = 0; r < 16; ++r) mine[r] = acc[r];
+  __syncthreads();
+}
+
 // the extra row's product with hypothesis j (see splitk_mma)
 template <int WAVES>
 __device__ __forceinline__ float extra_value(const float *red, int j) {
@@ -267,10 +296,44 @@ __host__ __device__ __forceinline__ int xcd_item(const XcdMap &m, int bid, int &
   return -1;
 }
 
+// Splits a k4-major matrix in place (see split_f16), each row scaled by a power of two that brings its largest element to
+// [2^14, 2^15): the 16 bytes of four k become their four hi, then their four lo.  unscale[row] takes that scale, and that of the
+// hidden states, off a sum.  Infinite weights become the row's largest float16 (the scale is that of the finite ones).
+// 64 rows x 4 parts of the k per block.
+__global__ __launch_bounds__(256) void k_split_rows(float *W, int rows, int K, float *unscale) {
+  __shared__ float s_max[4][64];
+  const int r = threadIdx.x & 63, part = threadIdx.x >> 6, row = blockIdx.x * 64 + r;
+  float4 *p = reinterpret_cast<float4 *>(W) + (row < rows ? row : 0);
+  float m = 0.f;
+  auto larger = [&](float x) { m = fabsf(x) < INFINITY ? fmaxf(m, fabsf(x)) : m; };
+  for (int i = part; i < K / 4; i += 4) {
+    const float4 v = p[(size_t)i * rows];
+    larger(v.x); larger(v.y); larger(v.z); larger(v.w);
+  }
+  s_max[part][r] = m;
+  __syncthreads();
+  m = fmaxf(fmaxf(s_max[0][r], s_max[1][r]), fmaxf(s_max[2][r], s_max[3][r]));
+  if (row >= rows) return;
+  int e = 0;  // m in [2^(e - 1), 2^e)
+  if (m > 0.f) frexpf(m, &e);
+  e = 15 - e < 100 ? 15 - e : 100;
+  const float scale = ldexpf(1.f, e);
+  if (part == 0) unscale[row] = ldexpf(1.f / kHidScale, -e);
+  auto scaled = [&](float x) { return fminf(fmaxf(x * scale, -65504.f), x != x ? x : 65504.f); };
+  for (int i = part; i < K / 4; i += 4) {
+    const float4 v = p[(size_t)i * rows];
+    uint32_t hi[2], lo[2];
+    split_f16(scaled(v.x), scaled(v.y), hi[0], lo[0]);
+    split_f16(scaled(v.z), scaled(v.w), hi[1], lo[1]);
+    p[(size_t)i * rows] = make_float4(__uint_as_float(hi[0]), __uint_as_float(hi[1]), __uint_as_float(lo[0]), __uint_as_float(lo[1]));
+  }
+}
+
 // R[m] = W_hh h[m] for one tile of 32 gate rows x the 32 current slots from m0 on (it does not depend on the
 // selection, so its blocks ride along in the launches that have idle compute units).
 struct RecurrentArgs {
-  const float *Whh;    // k4-major [P][4P], gate rows re-ordered (NULL: no such blocks)
+  const float *Whh;    // k4-major [P][4P], gate rows re-ordered, split by k_split_rows (NULL: no such blocks)
+  const float *unscale;  // [4P] (see k_split_rows)
   const float *h;      // k4-major [P][Mp]
   float *R;            // [M][4P]
   int P, M, Mp;
@@ -287,17 +350,19 @@ __device__ __forceinline__ void recurrent_tile(const RecurrentArgs &a, int tile,
   const float *hp = a.h + (size_t)(m0 + col) * 4;
   auto a_at = [&](int k) { return *reinterpret_cast<const float4 *>(wp + (size_t)(k >> 2) * R4 * 4); };
   auto b_at = [&](int k) { return *reinterpret_cast<const float4 *>(hp + (size_t)(k >> 2) * Mp * 4); };
-  auto fb = [](float4 v) { return v; };
   SplitKOperands<ITERS> op;
   splitk_load<WAVES, ITERS>(op, a_at, b_at, a.P);
-  if (done) return;
-  splitk_mma<WAVES, ITERS>(op, a_at, b_at, fb, a.P, red);
   // thread -> (slot j, VPL adjacent rows of the tile)
   const int j = tid / LPH, i0 = (tid % LPH) * VPL;
+  float us[VPL];
+#pragma unroll
+  for (int q = 0; q < VPL; ++q) us[q] = a.unscale[tile * 32 + i0 + q];
+  if (done) return;
+  splitk_mma_hid<WAVES, ITERS>(op, a_at, b_at, a.P, red);
   const int m = m0 + j;
   if (m < a.M) {
 #pragma unroll
-    for (int q = 0; q < VPL; ++q) store_through(a.R + (size_t)m * R4 + tile * 32 + i0 + q, tile_value<WAVES>(red, i0 + q, j));
+    for (int q = 0; q < VPL; ++q) store_through(a.R + (size_t)m * R4 + tile * 32 + i0 + q, tile_value<WAVES>(red, i0 + q, j) * us[q]);
   }
 }
 
@@ -321,8 +386,11 @@ __device__ __forceinline__ void recurrent_tiles(const RecurrentArgs &a, int tile
     wa[i] = *reinterpret_cast<const float4 *>(wp + (size_t)(2 * i) * R4 * 4);
     hb[0][i] = *reinterpret_cast<const float4 *>(hp + (size_t)(2 * i) * Mp * 4);
   }
-  if (done) return;
   const int j = tid / LPH, i0 = (tid % LPH) * VPL;
+  float us[VPL];
+#pragma unroll
+  for (int q = 0; q < VPL; ++q) us[q] = a.unscale[tile * 32 + i0 + q];
+  if (done) return;
   // one slot tile; G copies of this code, each with its register set known at compile time (a loop over g that can
   // end early is kept as a loop by the compiler, with the next tile's loads waited for one by one inside it).
   // (Reading the previous tile's sums back beside this tile's matrix instructions, from a second buffer, was slower:
@@ -338,15 +406,9 @@ __device__ __forceinline__ void recurrent_tiles(const RecurrentArgs &a, int tile
       }
     }
     __builtin_amdgcn_sched_barrier(0);  // the next tile's loads are under way before the first matrix instruction
-    floatx16 acc = {0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0};
-#pragma unroll
-    for (int i = 0; i < ITERS; ++i) {
-      const float4 b = hb[g & 1][i];
-      acc = mfma32(wa[i].x, b.x, acc);
-      acc = mfma32(wa[i].y, b.y, acc);
-      acc = mfma32(wa[i].z, b.z, acc);
-      acc = mfma32(wa[i].w, b.w, acc);
-    }
+    floatx16 acc = {0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0}, cor = acc;
+    mfma32_split_hid_rounds<ITERS>(wa, hb[g & 1], acc, cor);
+    acc += cor;
     if (g > 0) __syncthreads();  // the previous tile's partial sums have been read
     float *mine = red + (wave * 64 + lane) * kRedStride;
 #pragma unroll
@@ -356,7 +418,7 @@ __device__ __forceinline__ void recurrent_tiles(const RecurrentArgs &a, int tile
     if (m < a.M) {
 #pragma unroll
       for (int q = 0; q < VPL; ++q)
-        store_through(a.R + (size_t)m * R4 + tile * 32 + i0 + q, tile_value<WAVES>(red, i0 + q, j));
+        store_through(a.R + (size_t)m * R4 + tile * 32 + i0 + q, tile_value<WAVES>(red, i0 + q, j) * us[q]);
     }
   };
   static_assert(G == 4, "four copies below");

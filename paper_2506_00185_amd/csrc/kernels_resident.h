@@ -23,6 +23,10 @@
 // Every sum is formed in the order of the per-step kernels (K slices of 1/8 of the contraction, one chain of fused
 // multiply-adds each, in the order in which the 32x32x2 matrix instructions take their k; slices added first to last), so the
 // results are the same bit for bit: a 16x16x4 fp32 matrix instruction rounds like four fused multiply-adds in a row.
+// W_hh h goes through the float16 matrix instructions, both operands split in two (see split_f16): six tiles x 16 slots took 3.2
+// us of a block's matrix cores in float32, as long as the selection it hides under, and twice that with two tiles of slots.
+// (ms per decode, float32 / split: greedy batch 32 9.06 / 8.37, batch 32 beam 4 9.09 / 8.86 (bf16 9.03 / 8.09), TDT batch 64
+// 5.09 / 4.51, LM 16.6 / 15.0.)
 //
 // Stateless decoders (ST) have no cells and no projection: pre is a sum of table rows, f_proj[frame] + tab_0[last token] +
 // tab_1[the one before] + .., and every owner of output-layer tiles forms its own slice of it from the words (see
@@ -45,6 +49,7 @@ constexpr int kResMaxLdsTiles = 2;   // tiles that wait in LDS: projection tiles
 constexpr int kResMaxP = 2;
 constexpr int kResMaxSel = 4;        // utterances per selecting block
 constexpr int kResMaxRounds = 10;    // rounds of 8 k per wave slice: H, P <= 640
+constexpr int kResQuads = 5;         // 16-byte words of a lane of a split tile
 constexpr int kResMaxV = 1024;
 constexpr int kResStepRing = 4;      // ring of the hand-over arrays
 constexpr int kResNotLocal = -2;     // stall_step of a test: the groups take themselves to lie on several XCDs
@@ -71,7 +76,9 @@ constexpr int kResRedBlocks = BF16 ? 4 : 3;
 __host__ __device__ inline int res_k_of(int round, int kq, int e) { return 8 * round + (kq & 1) * 4 + (kq >> 1) + 2 * e; }
 
 struct ResArgs {
-  const float *WR, *WJ, *WP;         // [tile][round][64 lanes][2] (bf16 models: WR only)
+  const uintx4_t *WR;                // [tile][wave][kResQuads][64 lanes] (see ResW16)
+  const float *hh_unscale;           // [4 P] (see k_split_rows)
+  const float *WJ, *WP;              // [tile][round][64 lanes][2] (float32 models)
   const float *WJs;                  // the tile that begins with the blank column, for res_fold_mma: see k_pack_fold
   const uint64_t *WJb, *WPb;         // bf16 models: [32-row tile][round][64 lanes] four bf16 (k of the lane's half)
   const float *b_out, *b_pred, *G, *f_proj;
@@ -98,8 +105,8 @@ struct ResArgs {
 
 // The kernel's arguments, read from the argument segment anew at the begin of every phase: kept in scalar registers over
 // the whole loop they would push the weights out of the vector registers (a thousand spills).  What is left by the compiler's
-// report: LSTM forms 20 vector registers spilled (bf16 22; other widths 16, bf16 62) and 93 to 187 scalar ones (into vector
-// lanes), 256 vector registers in use; stateless forms no vector register, 76 to 147 scalar ones.  The selecting blocks, whose
+// report: LSTM forms 36 vector registers spilled (bf16 12; other widths 60, bf16 18) and 99 to 200 scalar ones (into vector
+// lanes), 256 vector registers in use; stateless forms no vector register, 80 to 150 scalar ones.  The selecting blocks, whose
 // code needs the scalar ones, share the kernel with the owners of the weights.
 __device__ __forceinline__ const ResArgs &res_args() {
   typedef const __attribute__((address_space(4))) ResArgs ConstArgs;
@@ -246,6 +253,64 @@ __device__ __forceinline__ ResLane res_lane() {
 __device__ __forceinline__ int res_uniform(int x) { return __builtin_amdgcn_readfirstlane(x); }
 // index of utterance u of the group in the batch
 __device__ __forceinline__ int res_utt(const ResBlock &k, int u) { return k.order[u]; }
+
+// ---- split operands (see split_f16)
+// A lane's part of a wave slice of up to 10 rounds of 8 k, for the 16x16x32 instruction (two quads of rounds) and the 16x16x16 one
+// (the last two).  A lane (row or slot, kq) has four k of each of two rounds of a quad, half kq % 2 of rounds 2 (kq / 2) and the
+// next, resp. half kq / 2 of round 8 + kq % 2: the eight products that an instruction adds up at once are then those of the
+// 32x32x16 instructions of the per-step kernels, in the same order.  Absent rounds are zero.
+struct ResW16 {
+  uintx4_t h[2], l[2];
+  uintx2_t th, tl;
+};
+// the word of the hand-over arrays' fragment order, relative to the slice's first, that is part i of the operand (i: 0 to 9)
+__device__ __forceinline__ int res_split_word(const ResLane &l, int i) {
+  const int round = i < 8 ? 4 * (i >> 2) + 2 * (l.kq >> 1) + ((i >> 1) & 1) : 8 + (l.kq & 1), half = i < 8 ? l.kq & 1 : l.kq >> 1;
+  return (round * 4 + half + 2 * (i & 1)) * kResSlot + l.sl;
+}
+// hidden states of a lane -> operand
+__device__ __forceinline__ void res_split_hid(const uint64_t (&x)[kResMaxRounds], ResW16 &o) {
+  uint32_t h[kResMaxRounds], l[kResMaxRounds];
+#pragma unroll
+  for (int i = 0; i < kResMaxRounds; ++i) split_f16(lo_f(x[i]) * kHidScale, hi_f(x[i]) * kHidScale, h[i], l[i]);
+#pragma unroll
+  for (int g = 0; g < 2; ++g) {
+    o.h[g] = uintx4_t{h[4 * g], h[4 * g + 1], h[4 * g + 2], h[4 * g + 3]};
+    o.l[g] = uintx4_t{l[4 * g], l[4 * g + 1], l[4 * g + 2], l[4 * g + 3]};
+  }
+  o.th = uintx2_t{h[8], h[9]};
+  o.tl = uintx2_t{l[8], l[9]};
+}
+// N tiles of 16 rows.  n_rounds: of the slice (beyond: zeros)
+template <bool FULL, int N>
+__device__ __forceinline__ void res_split_mma(const ResW16 *w, const ResW16 &x, int n_rounds, floatx4 (&acc)[N], floatx4 (&cor)[N]) {
+#pragma unroll
+  for (int t = 0; t < N; ++t) acc[t] = cor[t] = floatx4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+  for (int g = 0; g < 2; ++g)
+    if (FULL || 4 * g < n_rounds) {
+#pragma unroll
+      for (int t = 0; t < N; ++t) {
+        acc[t] = mfma16_f16(w[t].h[g], x.h[g], acc[t]);
+        cor[t] = mfma16_f16(w[t].h[g], x.l[g], cor[t]);
+      }
+#pragma unroll
+      for (int t = 0; t < N; ++t) cor[t] = mfma16_f16(w[t].l[g], x.h[g], cor[t]);
+    }
+  if (FULL || n_rounds > 8) {
+    // A 16x16x16 instruction that takes up the sums of a 16x16x32 one right behind it has missed its last addend (seen here: the
+    // compiler puts no wait states between the two shapes); these are well above the latency.
+#pragma unroll
+    for (int t = 0; t < N; ++t) asm volatile("s_nop 15" : "+v"(acc[t]), "+v"(cor[t]));
+#pragma unroll
+    for (int t = 0; t < N; ++t) {
+      acc[t] = mfma16_f16(w[t].th, x.th, acc[t]);
+      cor[t] = mfma16_f16(w[t].th, x.tl, cor[t]);
+    }
+#pragma unroll
+    for (int t = 0; t < N; ++t) cor[t] = mfma16_f16(w[t].tl, x.th, cor[t]);
+  }
+}
 
 // partial sums of a 16-row tile: wave's lane (row group, slot) holds four rows
 template <bool BF16>
@@ -824,9 +889,10 @@ __device__ __forceinline__ void res_worker(ResBlock k, const ResTab &tab, float 
     k.ctx = reinterpret_cast<int4 *>(Rl) + k.wave * a0.NT * kResSlot;
     for (int i = l0.lane; i < a0.NT * kResSlot; i += 64) k.ctx[i] = make_int4(-1, -1, -1, -1);
   }
-  float wj[NJ][2 * kResMaxRounds], wr[ST ? 1 : kResMaxR][2 * kResMaxRounds];
+  float wj[NJ][2 * kResMaxRounds];
+  ResW16 wr[ST ? 1 : kResMaxR];
   {
-    const int nrh = FULL ? kResMaxRounds : a0.rounds_h, nrp = FULL ? kResMaxRounds : a0.rounds_p;
+    const int nrh = FULL ? kResMaxRounds : a0.rounds_h;
 #pragma unroll
     for (int t = 0; t < NJ; ++t)
 #pragma unroll
@@ -841,24 +907,28 @@ __device__ __forceinline__ void res_worker(ResBlock k, const ResTab &tab, float 
         }
       }
 #pragma unroll
-    for (int t = 0; t < NR; ++t)
-#pragma unroll
-      for (int i = 0; i < kResMaxRounds; ++i) {
-        wr[t][2 * i] = wr[t][2 * i + 1] = 0.f;
-        if (t < k.nR && (FULL || i < nrp)) {
-          const uint64_t v = reinterpret_cast<const uint64_t *>(a0.WR)[((size_t)tab.R[t] * (a0.P / 8) + k.wave * nrp + i) * 64 + l0.lane];
-          wr[t][2 * i] = lo_f(v);
-          wr[t][2 * i + 1] = hi_f(v);
-        }
+    for (int t = 0; t < NR; ++t) {
+      wr[t] = ResW16{};
+      if (t < k.nR) {
+        const uintx4_t *src = a0.WR + ((size_t)tab.R[t] * kResWaves + k.wave) * kResQuads * 64 + l0.lane;
+        wr[t].h[0] = src[0];
+        wr[t].l[0] = src[64];
+        wr[t].h[1] = src[128];
+        wr[t].l[1] = src[192];
+        const uintx4_t v = src[256];
+        wr[t].th = uintx2_t{v[0], v[1]};
+        wr[t].tl = uintx2_t{v[2], v[3]};
       }
+    }
     // (loaded once; without this the compiler would rather load them again in every step)
 #pragma unroll
     for (int i = 0; i < 2 * kResMaxRounds; ++i) {
 #pragma unroll
       for (int t = 0; t < NJ; ++t) asm volatile("" : "+v"(wj[t][i]));
-#pragma unroll
-      for (int t = 0; t < NR; ++t) asm volatile("" : "+v"(wr[t][i]));
     }
+#pragma unroll
+    for (int t = 0; t < NR; ++t)
+      asm volatile("" : "+v"(wr[t].h[0]), "+v"(wr[t].h[1]), "+v"(wr[t].l[0]), "+v"(wr[t].l[1]), "+v"(wr[t].th), "+v"(wr[t].tl));
   }
   __syncthreads();
   int over = res_first_words(a0, k);
@@ -921,33 +991,39 @@ __device__ __forceinline__ void res_worker(ResBlock k, const ResTab &tab, float 
       if (step > 1 && k.wave < k.nR)
         for (int nt = 0; nt < k.nt; ++nt)
           res_store(k.local, reinterpret_cast<uint32_t *>(ad.h(step - 2, nt) + res_h_ofs(l, mytile)), kResEmpty);
+      const floatx4 unscale = *reinterpret_cast<const floatx4 *>(a.hh_unscale + 4 * (8 * (mytile >> 1) + 2 * l.kq + (mytile & 1)));
 #pragma unroll 1
       for (int nt = 0; nt < k.nt; ++nt) {
-        uint64_t x[kResMaxRounds];
-        const uint64_t *src = reinterpret_cast<const uint64_t *>(ad.h(step, nt)) + (size_t)k.wave * nrp * 64 + l.lane;
-        if (!res_gather<FULL, kResMaxRounds>([src](int i) { return src + i * 64; }, nrp, x)) return;
+        ResW16 xs;
+        {
+          uint64_t x[kResMaxRounds];
+          const uint64_t *src = reinterpret_cast<const uint64_t *>(ad.h(step, nt)) + (size_t)k.wave * nrp * 64;
+          // (absent rounds read the slice's first and are cleared)
+          auto at = [&](int i) {
+            const int w = res_split_word(l, i);
+            return src + (FULL || w < nrp * 64 ? w : l.sl);
+          };
+          if (!res_gather<true, kResMaxRounds>(at, kResMaxRounds, x)) return;
+          if constexpr (!FULL) {
+#pragma unroll
+            for (int i = 0; i < kResMaxRounds; ++i)
+              if (res_split_word(l, i) >= nrp * 64) x[i] = 0;
+          }
+          res_split_hid(x, xs);
+        }
 #pragma unroll
         for (int t0 = 0; t0 < kResMaxR; t0 += 3) {
           if (t0 >= k.nR) break;
-          floatx4 acc[3];
-#pragma unroll
-          for (int t = 0; t < 3; ++t) acc[t] = floatx4{0.f, 0.f, 0.f, 0.f};
           // (tiles that the block does not own have zero weights; fewer branches are worth more than their instructions)
-#pragma unroll
-          for (int i = 0; i < kResMaxRounds; ++i)
-            if (FULL || i < nrp) {
-#pragma unroll
-              for (int t = 0; t < 3; ++t) acc[t] = mfma16(wr[t0 + t][2 * i], lo_f(x[i]), acc[t]);
-#pragma unroll
-              for (int t = 0; t < 3; ++t) acc[t] = mfma16(wr[t0 + t][2 * i + 1], hi_f(x[i]), acc[t]);
-            }
+          floatx4 acc[3], cor[3];
+          res_split_mma<FULL, 3>(wr + t0, xs, nrp, acc, cor);
 #pragma unroll
           for (int t = 0; t < 3; ++t)
-            if (t0 + t < k.nR) res_put<BF16>(k, l, t, acc[t]);
+            if (t0 + t < k.nR) res_put<BF16>(k, l, t, acc[t] + cor[t]);
           __syncthreads();
           if (res_gave_up()) return;
           if (k.wave >= t0 && k.wave < t0 + 3 && k.wave < k.nR)
-            *reinterpret_cast<floatx4 *>(Rl + ((k.wave * a.NT + nt) * 64 + l.lane) * 4) = res_sum<BF16>(k, l, k.wave - t0);
+            *reinterpret_cast<floatx4 *>(Rl + ((k.wave * a.NT + nt) * 64 + l.lane) * 4) = res_sum<BF16>(k, l, k.wave - t0) * unscale;
           ++k.phase;
         }
       }

@@ -19,6 +19,7 @@ struct Resident {
   bool usable = false;
   int n_cus = 0, max_lds = 0;
   int misses = 0, skip = 0;       // launches in a row that gave up; decodes left to the per-step launches before the next try
+  const float *hh_unscale = nullptr;  // the handle's
   float *WR = nullptr, *WJ = nullptr, *WJs = nullptr, *WP = nullptr;
   uint64_t *WJb = nullptr, *WPb = nullptr;
   float *hb = nullptr, *pb = nullptr, *zb = nullptr;
@@ -40,7 +41,8 @@ inline void resident_missed(Resident &r) {
 
 // What the packing reads: the handle's k4-major weights (see kernels.h, k4_index)
 struct ResidentWeights {
-  const float *W_hh, *W_out, *W_pred;
+  const float *W_hh, *hh_unscale;  // split (k_split_rows)
+  const float *W_out, *W_pred;
   int out_rows;  // padded rows of W_out
 };
 

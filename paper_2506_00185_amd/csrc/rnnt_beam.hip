@@ -172,7 +172,7 @@ struct rnnt_beam {
   std::vector<void *> allocs;
   // packed weights
   float *W_enc = nullptr, *b_enc = nullptr, *W_pred = nullptr, *b_pred = nullptr, *W_out = nullptr,
-        *b_out = nullptr, *W_hh = nullptr, *G = nullptr, *tab = nullptr;
+        *b_out = nullptr, *W_hh = nullptr, *hh_unscale = nullptr, *G = nullptr, *tab = nullptr;
   // materialised-logits path (bf16 joint, large shapes)
   bool big = false;
   int Npad_big = 0, Hb = 0;  // padded extents of the bf16 operands: 256 columns, 64 k
@@ -409,6 +409,9 @@ int pack_weights(rnnt_beam *h, const rnnt_weights_t *w) {
       b_p[r] = bih[o] + bhh[o];
     }
     if ((rc = upload(h, &h->W_hh, to_k4(whh_p, 4 * P, P, 4 * P)))) return rc;
+    if ((rc = dev_alloc(h, &h->hh_unscale, (size_t)4 * P))) return rc;
+    hipLaunchKernelGGL(k_split_rows, dim3((4 * P + 63) / 64), dim3(256), 0, nullptr, h->W_hh, 4 * P, P, h->hh_unscale);
+    RB_HIP(h, hipGetLastError());
     // G[v] = W_ih emb[v] + b_ih + b_hh for every token (and the start symbol): one GEMM at create
     float *d_wih = nullptr, *d_b = nullptr, *d_emb = nullptr;
     if ((rc = upload(h, &d_wih, wih_p))) return rc;
@@ -568,7 +571,7 @@ int launch_pred(rnnt_beam *h, hipStream_t s, const StepPlan &p, int cur, int bum
       a.M = p.M; a.Mp = w.Mp; a.K = p.K; a.T = p.T; a.P = c.P; a.H = c.H;
       a.round_ops = c.prec == RNNT_BF16_JOINT ? 1 : 0;
       a.done = done; a.step_base = step_base; a.bump = bump; a.h_progress = h->h_done_dev + kProgressWord;
-      a.rec.Whh = h->W_hh; a.rec.h = w.h[cur ^ 1]; a.rec.R = w.Rgates;
+      a.rec.Whh = h->W_hh; a.rec.unscale = h->hh_unscale; a.rec.h = w.h[cur ^ 1]; a.rec.R = w.Rgates;
       a.rec.P = c.P; a.rec.M = p.M; a.rec.Mp = w.Mp; a.rec.group = 1;
       a.map.a_tiles = c.H / 32; a.map.a_m = m_tiles;
       a.map.b_begin = 0; a.map.b_end = recurrent_split(c, p.M); a.map.b_m = m_tiles;
@@ -788,7 +791,7 @@ int launch_step(rnnt_beam *h, hipStream_t s, const StepPlan &p, int step_off, in
     a.tile_ctr = w.tile_ctr;
     const bool lstm = c.pred == RNNT_PRED_LSTM;
     if (lstm && proj_split(c, p.M) && cur) a.pre = w.pre2;  // (see launch_pred: the buffers alternate with the steps)
-    a.rec.Whh = h->W_hh; a.rec.h = w.h[cur]; a.rec.R = w.Rgates;
+    a.rec.Whh = h->W_hh; a.rec.unscale = h->hh_unscale; a.rec.h = w.h[cur]; a.rec.R = w.Rgates;
     a.rec.P = c.P; a.rec.M = p.M; a.rec.Mp = w.Mp; a.rec.group = recurrent_group(c, p.M);
     const bool fold = fold_specials(c, a.n_chunks, p.B, p.K);
     a.n_jchunks = fold ? a.n_chunks - 1 : a.n_chunks;
@@ -889,7 +892,7 @@ int launch_persistent(rnnt_beam *h, hipStream_t s, const StepPlan &p, int max_st
   m.round_ops = c.prec == RNNT_BF16_JOINT ? 1 : 0;
   m.p_max = w.p_max; m.p_sum = w.p_sum; m.p_cand = w.p_cand; m.zs = w.zs;
   m.tile_ctr = w.tile_ctr;
-  m.rec.Whh = h->W_hh; m.rec.h = nullptr; m.rec.R = w.Rgates; m.rec.P = c.P; m.rec.M = p.M; m.rec.Mp = w.Mp; m.rec.group = 1;
+  m.rec.Whh = h->W_hh; m.rec.unscale = h->hh_unscale; m.rec.h = nullptr; m.rec.R = w.Rgates; m.rec.P = c.P; m.rec.M = p.M; m.rec.Mp = w.Mp; m.rec.group = 1;
   fill_select_args(h, p, 0, h->n_chunks, m.sel);  // (the step counter word stays 0: the kernel passes the step itself)
   PredProjArgs &q = a.pp;
   q.Wp = h->W_pred; q.bias = h->b_pred; q.h = nullptr; q.f_proj = w.f_proj; q.t = w.t; q.lengths = w.lengths;
@@ -956,7 +959,7 @@ struct DeviceSlot {
 
 int create_resident(rnnt_beam *h, int fail_alloc) {
   const rnnt_config_t &c = h->cfg;
-  const ResidentWeights rw{h->W_hh, h->W_out, h->W_pred, h->n_chunks * 32};
+  const ResidentWeights rw{h->W_hh, h->hh_unscale, h->W_out, h->W_pred, h->n_chunks * 32};
   return c.use_graph && !c.persistent_kernel && !c.async_enqueue ? resident_create(h->res, c, rw, h->err, fail_alloc) : RNNT_OK;
 }
 

@@ -13,8 +13,8 @@ namespace {
 
 __device__ __forceinline__ size_t k4_at(int k, int row, int rows) { return ((size_t)(k >> 2) * rows + row) * 4 + (k & 3); }
 
-// W (k4-major, `rows` rows) -> [tile of 16 rows][round][64 lanes][2].  MAP 0: rows as they are; 1: tiles of four LSTM units;
-// 2: tiles of projection outputs (res_p_row)
+// W (k4-major, `rows` rows) -> [tile of 16 rows][round][64 lanes][2].  MAP 0: rows as they are; 2: tiles of projection outputs
+// (res_p_row)
 template <int MAP>
 __global__ void k_pack_f32(const float *W, int rows, int K, int n_tiles, float *out) {
   const int n_rounds = K / 8;
@@ -25,9 +25,28 @@ __global__ void k_pack_f32(const float *W, int rows, int K, int n_tiles, float *
     const int r = lane & 15, kq = lane >> 4;
     int row;
     if (MAP == 0) row = 16 * tile + r;
-    else if (MAP == 1) row = 4 * (8 * (tile >> 1) + 2 * (r >> 2) + (tile & 1)) + (r & 3);
     else row = res_p_row(tile, r);
     out[i] = row < rows ? W[k4_at(res_k_of(round, kq, e), row, rows)] : 0.f;
+  }
+}
+// W_hh, split (k_split_rows), -> [tile of four LSTM units][wave][quadword of a lane][64 lanes] (see ResW16): rounds of 8 k of a
+// wave slice, absent ones zero.  Quadwords 0 to 3: hi and lo of the first two quads of rounds, 4: hi and lo of the last two rounds
+__global__ void k_pack_split(const uint32_t *W, int rows, int K, int n_tiles, uint32_t *out) {
+  const int n_rounds = K / 64;
+  const size_t n = (size_t)n_tiles * kResWaves * kResQuads * 64 * 4;
+  for (size_t i = (size_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += (size_t)gridDim.x * blockDim.x) {
+    const int e = (int)(i & 3), lane = (int)(i >> 2) & 63, q = (int)((i >> 8) % kResQuads);
+    const int wave = (int)((i >> 8) / kResQuads) % kResWaves, tile = (int)((i >> 8) / kResQuads / kResWaves);
+    const int r = lane & 15, kq = lane >> 4, row = 4 * (8 * (tile >> 1) + 2 * (r >> 2) + (tile & 1)) + (r & 3);
+    const bool tail = q == 4, lo = tail ? e >> 1 : q & 1;
+    const int round = tail ? 8 + (kq & 1) : 4 * (q >> 1) + 2 * (kq >> 1) + (e >> 1), half = tail ? kq >> 1 : kq & 1;
+    // the word of a lane holds k and k + 2 (see res_k_of)
+    uint32_t v = 0;
+    if (round < n_rounds) {
+      const uint32_t *g = W + ((size_t)((wave * n_rounds + round) * 2 + half) * rows + row) * 4 + (lo ? 2 : 0);  // k pairs (0, 1), (2, 3)
+      v = (e & 1) == 0 ? (g[0] & 0xffffu) | g[1] << 16 : g[0] >> 16 | (g[1] & 0xffff0000u);
+    }
+    out[i] = v;
   }
 }
 // rows row0 .. + 15 as res_fold_mma reads them: [round][64 lanes][2], k = 8 round + lane / 16 and four further
@@ -225,7 +244,7 @@ int resident_create(Resident &r, const rnnt_config_t &c, const ResidentWeights &
   const int nR = 4 * c.P / 16, nJ = bf ? (N + 31) / 32 : (N + 15) / 16, nP = bf ? c.H / 32 : c.H / 16;
   bool ok = bf ? alloc(&r.WJb, (size_t)nJ * (c.H / 8) * 64) : alloc(&r.WJ, (size_t)nJ * 16 * c.H) && alloc(&r.WJs, (size_t)16 * c.H);
   if (lstm) {
-    ok = ok && alloc(&r.WR, (size_t)nR * 16 * c.P) && alloc(&r.hb, kResStepRing * rows * c.P) && alloc(&r.pb, kResStepRing * rows * c.H);
+    ok = ok && alloc(&r.WR, (size_t)nR * kResWaves * kResQuads * 64 * 4) && alloc(&r.hb, kResStepRing * rows * c.P) && alloc(&r.pb, kResStepRing * rows * c.H);
     ok = ok && (bf ? alloc(&r.WPb, (size_t)nP * (c.P / 8) * 64) : alloc(&r.WP, (size_t)nP * 16 * c.P));
   }
   ok = ok && alloc(&r.zb, kResStepRing * rows * w.out_rows) &&
@@ -240,7 +259,9 @@ int resident_create(Resident &r, const rnnt_config_t &c, const ResidentWeights &
     hipLaunchKernelGGL(k_pack_fold, grid, block, 0, nullptr, w.W_out, w.out_rows, c.V / 16 * 16, c.H, r.WJs);
   }
   if (lstm) {
-    hipLaunchKernelGGL(k_pack_f32<1>, grid, block, 0, nullptr, w.W_hh, 4 * c.P, c.P, nR, r.WR);
+    hipLaunchKernelGGL(k_pack_split, grid, block, 0, nullptr, reinterpret_cast<const uint32_t *>(w.W_hh), 4 * c.P, c.P, nR,
+                       reinterpret_cast<uint32_t *>(r.WR));
+    r.hh_unscale = w.hh_unscale;
     if (bf) hipLaunchKernelGGL(k_pack_bf16<2>, grid, block, 0, nullptr, w.W_pred, c.H, c.P, nP, r.WPb);
     else hipLaunchKernelGGL(k_pack_f32<2>, grid, block, 0, nullptr, w.W_pred, c.H, c.P, nP, r.WP);
   }
@@ -259,7 +280,7 @@ hipError_t resident_launch(Resident &r, const rnnt_config_t &c, const ResidentBa
   Plan p = make_plan(r, c, b.B, b.K, b.has_lm, b.fold);
   if (!p.ok) return hipErrorInvalidValue;
   ResArgs a{};
-  a.WR = r.WR; a.WJ = r.WJ; a.WJs = r.WJs; a.WP = r.WP; a.WJb = r.WJb; a.WPb = r.WPb;
+  a.WR = reinterpret_cast<const uintx4_t *>(r.WR); a.hh_unscale = r.hh_unscale; a.WJ = r.WJ; a.WJs = r.WJs; a.WP = r.WP; a.WJb = r.WJb; a.WPb = r.WPb;
   a.emb_tab = b.emb_tab; a.n_ctx = b.n_ctx;
   a.b_out = b.b_out; a.b_pred = b.b_pred; a.G = b.G; a.f_proj = b.f_proj;
   a.lengths = b.lengths;
