@@ -72,6 +72,14 @@ typedef _Float16 f16x2_t __attribute__((ext_vector_type(2)));
 typedef _Float16 f16x4_t __attribute__((ext_vector_type(4)));
 typedef _Float16 f16x8_t __attribute__((ext_vector_type(8)));
 constexpr float kHidScale = 32768.f;  // of hidden states, whose values lie in [-1, 1]
+// Of values whose size is not known ahead (the joint's activations): m, the largest of a hypothesis in a slice of the k, goes to
+// [2^14, 2^15).  inv takes the scale off the slice's sum again.
+__device__ __forceinline__ float split_scale(float m, float &inv) {
+  uint32_t e = __float_as_uint(m) & 0x7f800000u;
+  e = e > 18u << 23 ? e : 18u << 23;
+  inv = __uint_as_float(e - (14u << 23));
+  return __uint_as_float((268u << 23) - e);
+}
 // two values -> their two hi and their two lo, each pair in one word
 __device__ __forceinline__ void split_f16(float a, float b, uint32_t &hi, uint32_t &lo) {
   const floatx2_t v = {a, b};
@@ -90,10 +98,10 @@ __device__ __forceinline__ floatx4 mfma16_f16(uintx2_t a, uintx2_t b, floatx4 ac
   return __builtin_amdgcn_mfma_f32_16x16x16f16(__builtin_bit_cast(f16x4_t, a), __builtin_bit_cast(f16x4_t, b), acc, 0, 0, 0);
 }
 // 32x32x16 steps of a split product on N (two or four) consecutive 8-k rounds of the float32 scheme (see mfma32): weights come
-// split and scaled (k_split_rows), hidden states are split here.  The order in `cor` is that of the 16x16x32 instructions of the
+// split and scaled (k_split_rows), activations are scaled and split here.  The order in `cor` is that of the 16x16x32 instructions of the
 // resident loop, which take four rounds at a time.
 template <int N>
-__device__ __forceinline__ void mfma32_split_hid(const float4 (&a)[N], const float4 (&b)[N], floatx16 &acc, floatx16 &cor) {
+__device__ __forceinline__ void mfma32_split(const float4 (&a)[N], const float4 (&b)[N], float scale, floatx16 &acc, floatx16 &cor) {
   uintx4_t wh[N / 2], wl[N / 2], xh[N / 2], xl[N / 2];
 #pragma unroll
   for (int i = 0; i < N; i += 2) {
@@ -101,10 +109,10 @@ __device__ __forceinline__ void mfma32_split_hid(const float4 (&a)[N], const flo
     wh[i / 2] = uintx4_t{w0[0], w0[1], w1[0], w1[1]};
     wl[i / 2] = uintx4_t{w0[2], w0[3], w1[2], w1[3]};
     uint32_t h[4], l[4];
-    split_f16(b[i].x * kHidScale, b[i].y * kHidScale, h[0], l[0]);
-    split_f16(b[i].z * kHidScale, b[i].w * kHidScale, h[1], l[1]);
-    split_f16(b[i + 1].x * kHidScale, b[i + 1].y * kHidScale, h[2], l[2]);
-    split_f16(b[i + 1].z * kHidScale, b[i + 1].w * kHidScale, h[3], l[3]);
+    split_f16(b[i].x * scale, b[i].y * scale, h[0], l[0]);
+    split_f16(b[i].z * scale, b[i].w * scale, h[1], l[1]);
+    split_f16(b[i + 1].x * scale, b[i + 1].y * scale, h[2], l[2]);
+    split_f16(b[i + 1].z * scale, b[i + 1].w * scale, h[3], l[3]);
     xh[i / 2] = uintx4_t{h[0], h[1], h[2], h[3]};
     xl[i / 2] = uintx4_t{l[0], l[1], l[2], l[3]};
   }
@@ -117,7 +125,7 @@ __device__ __forceinline__ void mfma32_split_hid(const float4 (&a)[N], const flo
 }
 // the same on ITERS rounds
 template <int ITERS>
-__device__ __forceinline__ void mfma32_split_hid_rounds(const float4 (&a)[ITERS], const float4 (&b)[ITERS], floatx16 &acc, floatx16 &cor) {
+__device__ __forceinline__ void mfma32_split_rounds(const float4 (&a)[ITERS], const float4 (&b)[ITERS], float scale, floatx16 &acc, floatx16 &cor) {
   const float4 zero4 = make_float4(0.f, 0.f, 0.f, 0.f);
 #pragma unroll
   for (int i = 0; i < ITERS; i += 4) {
@@ -126,12 +134,12 @@ __device__ __forceinline__ void mfma32_split_hid_rounds(const float4 (&a)[ITERS]
       const int i3 = four ? i + 3 : i;
       const float4 w[4] = {a[i], a[i + 1 < ITERS ? i + 1 : i], a[i + 2 < ITERS ? i + 2 : i], four ? a[i3] : zero4};
       const float4 x[4] = {b[i], b[i + 1 < ITERS ? i + 1 : i], b[i + 2 < ITERS ? i + 2 : i], four ? b[i3] : zero4};
-      mfma32_split_hid<4>(w, x, acc, cor);
+      mfma32_split<4>(w, x, scale, acc, cor);
     } else {
       const bool two = i + 1 < ITERS;
       const int i1 = two ? i + 1 : i;
       const float4 w[2] = {a[i], two ? a[i1] : zero4}, x[2] = {b[i], two ? b[i1] : zero4};
-      mfma32_split_hid<2>(w, x, acc, cor);
+      mfma32_split<2>(w, x, scale, acc, cor);
     }
   }
 }

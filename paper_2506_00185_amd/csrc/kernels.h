@@ -48,29 +48,32 @@ __device__ __forceinline__ void splitk_load(SplitKOperands<ITERS> &op, AL a_at, 
   }
 }
 
+constexpr int kFormSplit = 0, kFormBf16 = 1, kFormF32 = 2;
+
+// larger of a lane's value and that of the same column in the wave's other half
+__device__ __forceinline__ float max_of_halves(float m) {
+  const auto s = __builtin_amdgcn_permlane32_swap(__float_as_uint(m), __float_as_uint(m), false, false);
+  return fmaxf(__uint_as_float(s[0]), __uint_as_float(s[1]));
+}
+
 // matrix instructions of the wave's K slice, partial tile to LDS, block barrier.
 // fb: applied to each hypothesis-side operand just before use (ReLU).
-// bf16 (uniform over the block): both operands are rounded to bfloat16 (weights handed in are bf16 values already)
-// and two 8-k rounds at a time go through one bf16 matrix instruction, an eighth of the matrix-core time of the
-// eight float32 ones; the accumulation stays float32.
+// form (uniform over the block): kFormBf16: both operands are rounded to bfloat16 (weights handed in are bf16 values already)
+// and two 8-k rounds at a time go through one bf16 matrix instruction; the accumulation stays float32.  kFormSplit: a split
+// product (see split_f16): weights as k_split_rows leaves them, ACT: activations of any size, a scale per hypothesis and
+// slice, else hidden states (whose scale stays in the sums, see k_split_rows).  kFormF32 (recurrent product of bf16-joint models):
+// float32 matrix instructions.
 // xw (ITERS > 0 only): this lane's k values of one more output row; the lane's part of that row's product with its
 // hypothesis goes into the spare float of its slot in red (extra_value() sums the parts).
-template <int WAVES, int ITERS, class AL, class BL, class FB>
+template <int WAVES, int ITERS, bool ACT, class AL, class BL, class FB>
 __device__ __forceinline__ void splitk_mma(SplitKOperands<ITERS> &op, AL a_at, BL b_at, FB fb, int K, float *red,
-                                           int bf16 = 0, const float4 *xw = nullptr) {
+                                           int form, const float4 *xw = nullptr) {
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, half = lane >> 5;
   const int kw = K / WAVES;
   const float4 zero4 = make_float4(0.f, 0.f, 0.f, 0.f);
-  floatx16 acc = {0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0};
+  floatx16 acc = {0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0}, cor = acc;
   if constexpr (ITERS > 0) {
-    if (bf16) {
-#pragma unroll
-      for (int i = 0; i < ITERS; i += 2) {
-        const bool two = i + 1 < ITERS;
-        acc = mfma32_bf16_from_f32(op.a[i], two ? op.a[i + 1 < ITERS ? i + 1 : i] : zero4, fb(op.b[i]),
-                                   two ? fb(op.b[i + 1 < ITERS ? i + 1 : i]) : zero4, acc);
-      }
-    } else {
+    if (!ACT && form == kFormF32) {
 #pragma unroll
       for (int i = 0; i < ITERS; ++i) {
         const float4 b = fb(op.b[i]);
@@ -79,17 +82,30 @@ __device__ __forceinline__ void splitk_mma(SplitKOperands<ITERS> &op, AL a_at, B
         acc = mfma32(op.a[i].z, b.z, acc);
         acc = mfma32(op.a[i].w, b.w, acc);
       }
+    } else if (form == kFormBf16) {
+#pragma unroll
+      for (int i = 0; i < ITERS; i += 2) {
+        const bool two = i + 1 < ITERS;
+        acc = mfma32_bf16_from_f32(op.a[i], two ? op.a[i + 1 < ITERS ? i + 1 : i] : zero4, fb(op.b[i]),
+                                   two ? fb(op.b[i + 1 < ITERS ? i + 1 : i]) : zero4, acc);
+      }
+    } else {
+      float4 b[ITERS];
+      float m = 0.f;
+#pragma unroll
+      for (int i = 0; i < ITERS; ++i) {
+        b[i] = fb(op.b[i]);
+        if (ACT) m = fmaxf(m, fmaxf(fmaxf(b[i].x, b[i].y), fmaxf(b[i].z, b[i].w)));
+      }
+      float inv = 1.f;
+      const float scale = ACT ? split_scale(max_of_halves(m), inv) : kHidScale;
+      mfma32_split_rounds<ITERS>(op.a, b, scale, acc, cor);
+      acc += cor;
+      if (ACT) acc *= inv;
     }
   } else {
     const int kbeg = wave * kw + 4 * half, kend = (wave + 1) * kw;
-    if (bf16) {
-      for (int k = kbeg; k < kend; k += 16) {
-        const bool two = k + 8 < kend;
-        const int k2 = two ? k + 8 : k;
-        const float4 a0 = a_at(k), a1 = a_at(k2), b0 = fb(b_at(k)), b1 = fb(b_at(k2));
-        acc = mfma32_bf16_from_f32(a0, two ? a1 : zero4, b0, two ? b1 : zero4, acc);
-      }
-    } else {
+    if (!ACT && form == kFormF32) {
       for (int k = kbeg; k < kend; k += 8) {
         const float4 a = a_at(k);
         const float4 b = fb(b_at(k));
@@ -98,6 +114,36 @@ __device__ __forceinline__ void splitk_mma(SplitKOperands<ITERS> &op, AL a_at, B
         acc = mfma32(a.z, b.z, acc);
         acc = mfma32(a.w, b.w, acc);
       }
+    } else if (form == kFormBf16) {
+      for (int k = kbeg; k < kend; k += 16) {
+        const bool two = k + 8 < kend;
+        const int k2 = two ? k + 8 : k;
+        const float4 a0 = a_at(k), a1 = a_at(k2), b0 = fb(b_at(k)), b1 = fb(b_at(k2));
+        acc = mfma32_bf16_from_f32(a0, two ? a1 : zero4, b0, two ? b1 : zero4, acc);
+      }
+    } else {
+      float inv = 1.f, scale = kHidScale;
+      if constexpr (ACT) {
+        float m = 0.f;
+        for (int k = kbeg; k < kend; k += 8) {
+          const float4 b = fb(b_at(k));
+          m = fmaxf(m, fmaxf(fmaxf(b.x, b.y), fmaxf(b.z, b.w)));
+        }
+        scale = split_scale(max_of_halves(m), inv);
+      }
+      for (int k = kbeg; k < kend; k += 32) {
+        float4 w[4], x[4];
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+          const bool in = k + 8 * i < kend;
+          const float4 w1 = a_at(in ? k + 8 * i : k), x1 = fb(b_at(in ? k + 8 * i : k));
+          w[i] = in ? w1 : zero4;
+          x[i] = in ? x1 : zero4;
+        }
+        mfma32_split<4>(w, x, scale, acc, cor);
+      }
+      acc += cor;
+      if (ACT) acc *= inv;
     }
   }
   float *mine = red + (wave * 64 + lane) * kRedStride;
@@ -109,7 +155,7 @@ __device__ __forceinline__ void splitk_mma(SplitKOperands<ITERS> &op, AL a_at, B
 #pragma unroll
       for (int i = 0; i < ITERS; ++i) {
         float4 b = fb(op.b[i]);
-        if (bf16) {  // (the weights are bf16 values already)
+        if (form == kFormBf16) {  // (the weights are bf16 values already)
           b.x = __uint_as_float(pack_bf16_rne(b.x, 0.f) << 16);
           b.y = __uint_as_float(pack_bf16_rne(b.y, 0.f) << 16);
           b.z = __uint_as_float(pack_bf16_rne(b.z, 0.f) << 16);
@@ -123,35 +169,6 @@ __device__ __forceinline__ void splitk_mma(SplitKOperands<ITERS> &op, AL a_at, B
       mine[16] = part;
     }
   }
-  __syncthreads();
-}
-
-// The same for weights that k_split_rows has split and hidden states: sums of the tile, still scaled, to LDS.
-template <int WAVES, int ITERS, class AL, class BL>
-__device__ __forceinline__ void splitk_mma_hid(SplitKOperands<ITERS> &op, AL a_at, BL b_at, int K, float *red) {
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, half = lane >> 5;
-  const float4 zero4 = make_float4(0.f, 0.f, 0.f, 0.f);
-  floatx16 acc = {0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0}, cor = acc;
-  if constexpr (ITERS > 0) {
-    mfma32_split_hid_rounds<ITERS>(op.a, op.b, acc, cor);
-  } else {
-    const int kw = K / WAVES, kbeg = wave * kw + 4 * half, kend = (wave + 1) * kw;
-    for (int k = kbeg; k < kend; k += 32) {
-      float4 w[4], x[4];
-#pragma unroll
-      for (int i = 0; i < 4; ++i) {
-        const bool in = k + 8 * i < kend;
-        const float4 w1 = a_at(in ? k + 8 * i : k), x1 = b_at(in ? k + 8 * i : k);
-        w[i] = in ? w1 : zero4;
-        x[i] = in ? x1 : zero4;
-      }
-      mfma32_split_hid<4>(w, x, acc, cor);
-    }
-  }
-  acc += cor;
-  float *mine = red + (wave * 64 + lane) * kRedStride;
-#pragma unroll
-  for (int r = 0; r < 16; ++r) mine[r] = acc[r];
   __syncthreads();
 }
 
@@ -297,10 +314,10 @@ __host__ __device__ __forceinline__ int xcd_item(const XcdMap &m, int bid, int &
 }
 
 // Splits a k4-major matrix in place (see split_f16), each row scaled by a power of two that brings its largest element to
-// [2^14, 2^15): the 16 bytes of four k become their four hi, then their four lo.  unscale[row] takes that scale, and that of the
-// hidden states, off a sum.  Infinite weights become the row's largest float16 (the scale is that of the finite ones).
+// [2^14, 2^15): the 16 bytes of four k become their four hi, then their four lo.  unscale[row] takes that scale, and x_scale, off
+// a sum.  Infinite weights become the row's largest float16 (the scale is that of the finite ones).
 // 64 rows x 4 parts of the k per block.
-__global__ __launch_bounds__(256) void k_split_rows(float *W, int rows, int K, float *unscale) {
+__global__ __launch_bounds__(256) void k_split_rows(float *W, int rows, int K, float x_scale, float *unscale) {
   __shared__ float s_max[4][64];
   const int r = threadIdx.x & 63, part = threadIdx.x >> 6, row = blockIdx.x * 64 + r;
   float4 *p = reinterpret_cast<float4 *>(W) + (row < rows ? row : 0);
@@ -318,7 +335,7 @@ __global__ __launch_bounds__(256) void k_split_rows(float *W, int rows, int K, f
   if (m > 0.f) frexpf(m, &e);
   e = 15 - e < 100 ? 15 - e : 100;
   const float scale = ldexpf(1.f, e);
-  if (part == 0) unscale[row] = ldexpf(1.f / kHidScale, -e);
+  if (part == 0) unscale[row] = ldexpf(1.f / x_scale, -e);
   auto scaled = [&](float x) { return fminf(fmaxf(x * scale, -65504.f), x != x ? x : 65504.f); };
   for (int i = part; i < K / 4; i += 4) {
     const float4 v = p[(size_t)i * rows];
@@ -332,8 +349,8 @@ __global__ __launch_bounds__(256) void k_split_rows(float *W, int rows, int K, f
 // R[m] = W_hh h[m] for one tile of 32 gate rows x the 32 current slots from m0 on (it does not depend on the
 // selection, so its blocks ride along in the launches that have idle compute units).
 struct RecurrentArgs {
-  const float *Whh;    // k4-major [P][4P], gate rows re-ordered, split by k_split_rows (NULL: no such blocks)
-  const float *unscale;  // [4P] (see k_split_rows)
+  const float *Whh;    // k4-major [P][4P], gate rows re-ordered (NULL: no such blocks)
+  const float *unscale;  // [4P] where Whh is split, see k_split_rows, else null (bf16-joint models)
   const float *h;      // k4-major [P][Mp]
   float *R;            // [M][4P]
   int P, M, Mp;
@@ -356,9 +373,9 @@ __device__ __forceinline__ void recurrent_tile(const RecurrentArgs &a, int tile,
   const int j = tid / LPH, i0 = (tid % LPH) * VPL;
   float us[VPL];
 #pragma unroll
-  for (int q = 0; q < VPL; ++q) us[q] = a.unscale[tile * 32 + i0 + q];
+  for (int q = 0; q < VPL; ++q) us[q] = a.unscale ? a.unscale[tile * 32 + i0 + q] : 1.f;
   if (done) return;
-  splitk_mma_hid<WAVES, ITERS>(op, a_at, b_at, a.P, red);
+  splitk_mma<WAVES, ITERS, false>(op, a_at, b_at, [](float4 v) { return v; }, a.P, red, a.unscale ? kFormSplit : kFormF32);
   const int m = m0 + j;
   if (m < a.M) {
 #pragma unroll
@@ -389,7 +406,7 @@ __device__ __forceinline__ void recurrent_tiles(const RecurrentArgs &a, int tile
   const int j = tid / LPH, i0 = (tid % LPH) * VPL;
   float us[VPL];
 #pragma unroll
-  for (int q = 0; q < VPL; ++q) us[q] = a.unscale[tile * 32 + i0 + q];
+  for (int q = 0; q < VPL; ++q) us[q] = a.unscale ? a.unscale[tile * 32 + i0 + q] : 1.f;
   if (done) return;
   // one slot tile; G copies of this code, each with its register set known at compile time (a loop over g that can
   // end early is kept as a loop by the compiler, with the next tile's loads waited for one by one inside it).
@@ -407,8 +424,19 @@ __device__ __forceinline__ void recurrent_tiles(const RecurrentArgs &a, int tile
     }
     __builtin_amdgcn_sched_barrier(0);  // the next tile's loads are under way before the first matrix instruction
     floatx16 acc = {0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0}, cor = acc;
-    mfma32_split_hid_rounds<ITERS>(wa, hb[g & 1], acc, cor);
-    acc += cor;
+    if (a.unscale) {
+      mfma32_split_rounds<ITERS>(wa, hb[g & 1], kHidScale, acc, cor);
+      acc += cor;
+    } else {
+#pragma unroll
+      for (int i = 0; i < ITERS; ++i) {
+        const float4 b = hb[g & 1][i];
+        acc = mfma32(wa[i].x, b.x, acc);
+        acc = mfma32(wa[i].y, b.y, acc);
+        acc = mfma32(wa[i].z, b.z, acc);
+        acc = mfma32(wa[i].w, b.w, acc);
+      }
+    }
     if (g > 0) __syncthreads();  // the previous tile's partial sums have been read
     float *mine = red + (wave * 64 + lane) * kRedStride;
 #pragma unroll
@@ -431,7 +459,8 @@ __device__ __forceinline__ void recurrent_tiles(const RecurrentArgs &a, int tile
 struct MainArgs {
   // ---- joint role
   const float *pre;   // k4-major [H][Mp]: f_proj[b, t_m] + prediction projection of hypothesis m
-  const float *W;     // k4-major [H][n_chunks * 32] output layer, zero rows beyond V + 1 + ND
+  const float *W;     // k4-major [H][n_chunks * 32] output layer, zero rows beyond V + 1 + ND; float32 models: split by k_split_rows
+  const float *W_plain, *w_unscale;  // float32 models: the same not split, and the scales of its rows (else W and null)
   const float *bias;  // [n_chunks * 32]
   const float *lm;    // [M, V] natural-log LM scores or NULL
   float lambda;
@@ -482,18 +511,18 @@ __device__ __forceinline__ void joint_tile(const MainArgs &a, int chunk, int m0,
       if (folds) {  // (uniform over the block) the folded column's weights, requested behind the operands
         float4 xw[ITERS];
         const int kbeg = (tid >> 6) * (a.H / WAVES) + 4 * (lane >> 5);
-        const float *xp = a.W + (size_t)(a.V + fold_c) * 4;
+        const float *xp = a.W_plain + (size_t)(a.V + fold_c) * 4;
 #pragma unroll
         for (int i = 0; i < ITERS; ++i) xw[i] = *reinterpret_cast<const float4 *>(xp + (size_t)((kbeg + 8 * i) >> 2) * Np * 4);
         if (done) return;
-        splitk_mma<WAVES, ITERS>(op, a_at, b_at, fb, a.H, red, round_ops, xw);
+        splitk_mma<WAVES, ITERS, true>(op, a_at, b_at, fb, a.H, red, round_ops, xw);
       } else {
         if (done) return;
-        splitk_mma<WAVES, ITERS>(op, a_at, b_at, fb, a.H, red, round_ops);
+        splitk_mma<WAVES, ITERS, true>(op, a_at, b_at, fb, a.H, red, round_ops);
       }
     } else {
       if (done) return;
-      splitk_mma<WAVES, ITERS>(op, a_at, b_at, fb, a.H, red, round_ops);
+      splitk_mma<WAVES, ITERS, true>(op, a_at, b_at, fb, a.H, red, round_ops);
     }
   }
 
@@ -502,6 +531,9 @@ __device__ __forceinline__ void joint_tile(const MainArgs &a, int chunk, int m0,
   const int m = m0 + j;
   const bool mvalid = j < rows && m < a.M;
   const int nz = 1 + a.ND;
+  float us[VPL];
+#pragma unroll
+  for (int q = 0; q < VPL; ++q) us[q] = a.w_unscale ? a.w_unscale[n0 + i0 + q] : 1.f;
   if (WIDE && folds && mvalid) {
     if (e == 0) store_agent(a.zs + (size_t)m * nz + fold_c, extra_value<WAVES>(red, j) + a.bias[a.V + fold_c]);
     if (fold_c == 0) {  // ... and the empty lists of the chunk that has no block now
@@ -521,7 +553,7 @@ __device__ __forceinline__ void joint_tile(const MainArgs &a, int chunk, int m0,
 #pragma unroll
   for (int q = 0; q < VPL; ++q) {
     const int n = n0 + i0 + q;
-    const float z = tile_value<WAVES>(red, i0 + q, j) + a.bias[n];
+    const float z = tile_value<WAVES>(red, i0 + q, j) * us[q] + a.bias[n];
     zv[q] = z;
     cand[q] = no_cand();
     if (n < a.V) {
@@ -867,6 +899,7 @@ __device__ __forceinline__ void bump_step(int *step_base, int bump, volatile int
 // W_pred: k4-major [P][H]; h: k4-major [P][Mp]; f_proj: row-major [B * T, H].
 struct PredProjArgs {
   const float *Wp, *bias, *h, *f_proj;
+  const float *wp_unscale;  // float32 models: Wp is split, the scales of its rows (else null)
   const int *t, *lengths;
   float *pre;
   int M, Mp, K, T, P, H, round_ops;
@@ -931,11 +964,14 @@ __device__ __forceinline__ void pred_proj_tile(const PredProjArgs &a, int tile, 
       bv[q] = a.bias[o0 + q];
     }
   }
-  splitk_mma<WAVES, ITERS>(op, a_at, b_at, fb, a.P, red, round_ops);
+  float us[VPL];
+#pragma unroll
+  for (int q = 0; q < VPL; ++q) us[q] = a.wp_unscale ? a.wp_unscale[o0 + q] : 1.f;
+  splitk_mma<WAVES, ITERS, false>(op, a_at, b_at, fb, a.P, red, round_ops);
   if (me >= a.M) return;
 #pragma unroll
   for (int q = 0; q < VPL; ++q)
-    store_through(a.pre + k4_index(o0 + q, me, a.Mp), tile_value<WAVES>(red, (tid % LPH) * VPL + q, j) + bv[q] + fv[q]);
+    store_through(a.pre + k4_index(o0 + q, me, a.Mp), tile_value<WAVES>(red, (tid % LPH) * VPL + q, j) * us[q] + bv[q] + fv[q]);
 }
 
 // LM: the launch carries LM rows (an instantiation of its own: the test for them costs the plain launch 0.26 us)
@@ -1004,6 +1040,9 @@ __global__ __launch_bounds__(WAVES * 64) void k_pred_proj_half(PredProjArgs a) {
       bv[q] = a.bias[o0 + q];
     }
   }
+  float us[VPL];
+#pragma unroll
+  for (int q = 0; q < VPL; ++q) us[q] = a.wp_unscale ? a.wp_unscale[o0 + q] : 1.f;
   __builtin_amdgcn_sched_barrier(0);
   // (behind every load of the block, whose waits then do not include these stores; they are on their way while the
   // operands come in and are multiplied)
@@ -1011,13 +1050,13 @@ __global__ __launch_bounds__(WAVES * 64) void k_pred_proj_half(PredProjArgs a) {
        i += 4 * WAVES * 64 * a.map.a_tiles * a.map.a_m)
     store16_through(a.pre_clear + i, floatx4{0.f, 0.f, 0.f, 0.f});
   __builtin_amdgcn_sched_barrier(0);
-  splitk_mma<WAVES, ITERS>(op, a_at, b_at, fb, a.P / 2, red, round_ops);
+  splitk_mma<WAVES, ITERS, false>(op, a_at, b_at, fb, a.P / 2, red, round_ops);
   if (a.bump && tile == 0 && item == 0 && tid == 0) bump_step(a.step_base, a.bump, a.h_progress);
   if (me >= a.M) return;
 #pragma unroll
   for (int q = 0; q < VPL; ++q)
     __hip_atomic_fetch_add(a.pre + k4_index(o0 + q, me, a.Mp),
-                           tile_value<WAVES>(red, (tid % LPH) * VPL + q, j) + bv[q] + fv[q], __ATOMIC_RELAXED,
+                           tile_value<WAVES>(red, (tid % LPH) * VPL + q, j) * us[q] + bv[q] + fv[q], __ATOMIC_RELAXED,
                            __HIP_MEMORY_SCOPE_AGENT);
 }
 

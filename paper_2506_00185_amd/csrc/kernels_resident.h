@@ -20,13 +20,13 @@
 // A writer puts the pattern back once a word of a later phase proves that every reader is through (see the clear_
 // functions), one or two steps before the place is used again.
 //
-// Every sum is formed in the order of the per-step kernels (K slices of 1/8 of the contraction, one chain of fused
-// multiply-adds each, in the order in which the 32x32x2 matrix instructions take their k; slices added first to last), so the
-// results are the same bit for bit: a 16x16x4 fp32 matrix instruction rounds like four fused multiply-adds in a row.
-// W_hh h goes through the float16 matrix instructions, both operands split in two (see split_f16): six tiles x 16 slots took 3.2
-// us of a block's matrix cores in float32, as long as the selection it hides under, and twice that with two tiles of slots.
-// (ms per decode, float32 / split: greedy batch 32 9.06 / 8.37, batch 32 beam 4 9.09 / 8.86 (bf16 9.03 / 8.09), TDT batch 64
-// 5.09 / 4.51, LM 16.6 / 15.0.)
+// Every sum is formed in the order of the per-step kernels (K slices of 1/8 of the contraction, slices added first to last), so the
+// results are the same bit for bit.  Float32 models multiply on the float16 matrix instructions, both operands split in two (see
+// split_f16): in float32, W_hh h took 3.2 us per step and tile of 16 slots, as long as the selection it hides under, and the other
+// two contractions 3 us of the chain.  bf16-joint models keep W_hh h on float32 matrix instructions (a 16x16x4 one rounds like four
+// fused multiply-adds in a row): they round activations to 8 bits, and near ties there follow every last bit of the hidden state.
+// (ms per decode before / after the splits, the gathers and the ends of waves described below: one utterance 8.65 / 6.95, greedy batch
+// 32 9.05 / 7.05, batch 32 beam 4 9.05 / 7.55, TDT batch 64 5.1 / 4.1, LM 16.5 / 13.8.)
 //
 // Stateless decoders (ST) have no cells and no projection: pre is a sum of table rows, f_proj[frame] + tab_0[last token] +
 // tab_1[the one before] + .., and every owner of output-layer tiles forms its own slice of it from the words (see
@@ -36,6 +36,8 @@
 // Every wait is bounded: a wave that waits too long raises the abort word and ends, every other wave sees the word (or
 // its own limit) and ends too, and the host decodes the batch with the per-step launches instead.
 #pragma once
+#include <type_traits>
+
 #include "lm_device.h"
 #include "select.h"
 
@@ -50,6 +52,7 @@ constexpr int kResMaxP = 2;
 constexpr int kResMaxSel = 4;        // utterances per selecting block
 constexpr int kResMaxRounds = 10;    // rounds of 8 k per wave slice: H, P <= 640
 constexpr int kResQuads = 5;         // 16-byte words of a lane of a split tile
+constexpr int kResTileFloats = kResWaves * kResQuads * 64 * 4;  // a split tile
 constexpr int kResMaxV = 1024;
 constexpr int kResStepRing = 4;      // ring of the hand-over arrays
 constexpr int kResNotLocal = -2;     // stall_step of a test: the groups take themselves to lie on several XCDs
@@ -76,9 +79,9 @@ constexpr int kResRedBlocks = BF16 ? 4 : 3;
 __host__ __device__ inline int res_k_of(int round, int kq, int e) { return 8 * round + (kq & 1) * 4 + (kq >> 1) + 2 * e; }
 
 struct ResArgs {
-  const uintx4_t *WR;                // [tile][wave][kResQuads][64 lanes] (see ResW16)
-  const float *hh_unscale;           // [4 P] (see k_split_rows)
-  const float *WJ, *WP;              // [tile][round][64 lanes][2] (float32 models)
+  const uintx4_t *WR, *WJ, *WP;      // float32 models: [tile][wave][kResQuads * 64] (see k_pack_split)
+  const float *WRf;                  // bf16 models: [tile][round][64 lanes][2]
+  const float *hh_unscale, *out_unscale, *pred_unscale;  // of their rows (see k_split_rows)
   const float *WJs;                  // the tile that begins with the blank column, for res_fold_mma: see k_pack_fold
   const uint64_t *WJb, *WPb;         // bf16 models: [32-row tile][round][64 lanes] four bf16 (k of the lane's half)
   const float *b_out, *b_pred, *G, *f_proj;
@@ -105,8 +108,8 @@ struct ResArgs {
 
 // The kernel's arguments, read from the argument segment anew at the begin of every phase: kept in scalar registers over
 // the whole loop they would push the weights out of the vector registers (a thousand spills).  What is left by the compiler's
-// report: LSTM forms 36 vector registers spilled (bf16 12; other widths 60, bf16 18) and 99 to 200 scalar ones (into vector
-// lanes), 256 vector registers in use; stateless forms no vector register, 80 to 150 scalar ones.  The selecting blocks, whose
+// report: LSTM forms 48 vector registers spilled (bf16 8; other widths 60, bf16 4) and 130 to 210 scalar ones (into vector
+// lanes), 256 vector registers in use; stateless forms no vector register, 90 to 130 scalar ones.  The selecting blocks, whose
 // code needs the scalar ones, share the kernel with the owners of the weights.
 __device__ __forceinline__ const ResArgs &res_args() {
   typedef const __attribute__((address_space(4))) ResArgs ConstArgs;
@@ -135,60 +138,73 @@ __device__ __forceinline__ uint64_t pack2(float lo, float hi) {
 // Giving up is a matter of the whole block: a wave whose wait fails leaves a flag in LDS and ends (the barriers no longer
 // count it), and every wave looks at the flag behind each barrier that follows a wait, before it uses or publishes what
 // the others should have left in LDS.  (Reading the flag along with that and looking at it last: 1 to 3 % slower.)
-__device__ __forceinline__ volatile int &res_gave_up_word() {
+// (An LDS address, not a generic pointer: a flat load of the word waited for every store and load that the wave had in flight.)
+typedef __attribute__((address_space(3))) int LdsInt;
+__device__ __forceinline__ LdsInt *res_gave_up_word() {
   __shared__ int word;
-  return word;
+  return (LdsInt *)&word;
 }
-__device__ __forceinline__ bool res_gave_up() { return __builtin_amdgcn_readfirstlane(res_gave_up_word()) != 0; }
-// bounded waiting: true while another poll may follow
+// (Ending the wave where it gives up, rather than by a result handed up through every caller, leaves the compiler no paths on which
+// the awaited words are undefined: those took registers and moves.)
+__device__ __forceinline__ void res_end_if_given_up() {
+  if (__builtin_amdgcn_readfirstlane(__hip_atomic_load(res_gave_up_word(), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP)) != 0) __builtin_amdgcn_endpgm();
+}
+// bounded waiting: between two polls; the wave ends here when it has waited too long, or when another one has
 struct ResWait {
   int n = 0;
-  __device__ __forceinline__ bool again() {
-    if ((++n & 255) == 0) return more();
-    return true;
-  }
-  __device__ __forceinline__ bool more() const {
+  __device__ __forceinline__ void again() {
+    if ((++n & 255) != 0) return;
     const ResArgs &a = res_args();
-    if (n < a.poll_limit && !load_agent(a.ctl + 1)) return true;
+    if (n < a.poll_limit && !load_agent(a.ctl + 1)) return;
     store_agent(a.ctl + 1, 1);
     *a.h_abort = 1;
-    res_gave_up_word() = 1;
+    __hip_atomic_store(res_gave_up_word(), 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
     __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");  // (ahead of the wave's end)
-    return false;
+    __builtin_amdgcn_endpgm();
+  }
+  // between two polls of all words of a wave: from the 32nd on (10 us, which no hand-over takes) the wave leaves gaps, for should the
+  // polls be what holds up the data (see res_gather)
+  __device__ __forceinline__ void again_wide() {
+    if (n >= 32) __builtin_amdgcn_s_sleep(32);
+    again();
   }
 };
 
-// Waits until one 8-byte word of every lane is there.
-__device__ __forceinline__ bool res_probe(const uint64_t *p, ResWait &w) {
-  for (;;) {
-    const uint64_t x[1] = {load_agent(p)};
-    if (__ballot(res_any_empty(x)) == 0ull) return true;
-    if (!w.again()) return false;
-  }
-}
-// N 8-byte words of a lane as soon as all are there (in every lane of the wave).  at(i): address of word i; the first n are
-// used (FULL: all N).  (Every poll loads all of them.  With a poll of one word first, a trip to the L2 lay between the arrival of
-// the data and its use: batch 32 / beam 4 9.26 instead of 8.95 ms per decode.)
-template <bool FULL, int N, class AT>
-__device__ __forceinline__ bool res_gather(AT at, int n, uint64_t (&x)[N]) {
+__device__ __forceinline__ uint64_t res_load(const char *p) { return load_agent(reinterpret_cast<const uint64_t *>(p)); }
+// N 8-byte words of a lane as soon as all are there (in every lane of the wave).  base: the same in all lanes; at(i, o): address of
+// word i, base + one of the lane's offsets + a constant; the first n are used (FULL: all N).  (The offsets are made anew for every
+// poll: an address kept per word would take more registers than the words.)  Every poll loads all of the words: with a poll of one
+// word per tile first, a trip to the L2 lies between the arrival of the data and their use (batch 32 / beam 4 8.09 instead of 7.52 ms
+// per decode).  PROBE: such a poll all the same, where a wave waits for 20 words: the polls of eight such waves kept a compute unit's
+// L1 so busy that its own stores did not get out (bf16 joint, in one build: 280 us per step; with the poll first 11).  probe: offset of
+// one word of every tile whose owner writes into the wave's words, lanes share them out.
+template <bool FULL, int N, bool PROBE = true, int M, class AT>
+__device__ __forceinline__ void res_gather(const char *base, uint32_t probe, const uint32_t (&offs)[M], AT at, int n, uint64_t (&x)[N]) {
   ResWait w;
+  if constexpr (PROBE) {
+    for (;;) {
+      uint32_t o = probe;
+      asm volatile("" : "+v"(o));
+      const uint64_t y[1] = {res_load(base + o)};
+      if (__ballot(res_any_empty(y)) == 0ull) break;
+      w.again();
+    }
+  }
   for (;;) {
+    uint32_t o[M];
+#pragma unroll
+    for (int m = 0; m < M; ++m) {
+      o[m] = offs[m];
+      asm volatile("" : "+v"(o[m]));
+    }
 #pragma unroll
     for (int i = 0; i < N; ++i) {
       x[i] = 0;
-      if (FULL || i < n) x[i] = load_agent(at(i));
+      if (FULL || i < n) x[i] = res_load(at(i, o));
     }
-    if (__ballot(res_any_empty(x)) == 0ull) return true;
-    if (!w.again()) return false;
+    if (__ballot(res_any_empty(x)) == 0ull) return;
+    w.again_wide();
   }
-}
-
-// x[i] for an index that is the same in all lanes but not known at compile time
-__device__ __forceinline__ uint64_t res_pick(const uint64_t (&x)[kResMaxRounds], int i) {
-  uint64_t v = x[0];
-#pragma unroll
-  for (int q = 1; q < kResMaxRounds; ++q) v = i == q ? x[q] : v;
-  return v;
 }
 
 // ---- addresses of the hand-over arrays
@@ -235,6 +251,7 @@ struct ResBlock {
   float *red;                        // LDS: partial sums (two halves that alternate)
   const uint64_t *spec;              // LDS: see res_fold_bf16
   const uint64_t *tiles;             // LDS: weights of up to kResMaxLdsTiles tiles
+  const floatx4 *par;                // LDS: scales and biases of the rows of the block's tiles (see ResPar)
   const int2 *info;                  // LDS: frames of the slot's utterance, its first row of f_proj
   uint64_t *word;                    // LDS: this wave's copy of the last step's words, [slot tile][16]
   int4 *ctx;                         // LDS, stateless decoders: this wave's copy of the slots' last tokens (-1: none)
@@ -263,16 +280,40 @@ struct ResW16 {
   uintx4_t h[2], l[2];
   uintx2_t th, tl;
 };
-// the word of the hand-over arrays' fragment order, relative to the slice's first, that is part i of the operand (i: 0 to 9)
-__device__ __forceinline__ int res_split_word(const ResLane &l, int i) {
-  const int round = i < 8 ? 4 * (i >> 2) + 2 * (l.kq >> 1) + ((i >> 1) & 1) : 8 + (l.kq & 1), half = i < 8 ? l.kq & 1 : l.kq >> 1;
-  return (round * 4 + half + 2 * (i & 1)) * kResSlot + l.sl;
+// Byte offset, relative to the slice's first, of the word of the hand-over arrays' fragment order that is part i (0 to 3) of a lane's
+// operand on a quad of rounds, or part i (0, 1) of its operand on two rounds.
+constexpr int kResRoundBytes = 4 * kResSlot * 8, kResWordBytes = 2 * kResSlot * 8;  // of a round; from a word to the one of k + 1
+__device__ __forceinline__ uint32_t res_quad_base(const ResLane &l) { return (l.kq >> 1) * 2 * kResRoundBytes + ((l.kq & 1) * kResSlot + l.sl) * 8; }
+__device__ __forceinline__ uint32_t res_pair_base(const ResLane &l) { return (l.kq & 1) * kResRoundBytes + ((l.kq >> 1) * kResSlot + l.sl) * 8; }
+__device__ __forceinline__ constexpr uint32_t res_part(int i) { return (i >> 1) * kResRoundBytes + (i & 1) * kResWordBytes; }
+// part i (0 to 9) of ten rounds; pair: that of round 8
+__device__ __forceinline__ constexpr uint32_t res_split_part(int i) { return i < 8 ? (i >> 2) * 4 * kResRoundBytes + res_part(i & 3) : res_part(i & 1); }
+// Words to poll, see res_gather: a tile of W_hh's four units writes half of a round's words (lanes 0 ..: two per round), a tile of the
+// projection two rounds' (one per round, which also serves slices that begin in the middle of a tile).
+__device__ __forceinline__ uint32_t res_probe_h(const ResLane &l, int nr) { return (l.lane < 2 * nr ? l.lane >> 1 : 0) * kResRoundBytes + (l.lane & 1) * kResWordBytes; }
+__device__ __forceinline__ uint32_t res_probe_p(const ResLane &l, int nr) { return (l.lane < nr ? l.lane : 0) * kResRoundBytes; }
+// a slice of nr rounds, as soon as all of it is there
+template <bool FULL, bool PROBE = true>
+__device__ __forceinline__ void res_split_gather(const ResLane &l, const char *src, uint32_t probe, int nr, uint64_t (&x)[kResMaxRounds]) {
+  // (absent rounds read the slice's first and are cleared)
+  const uint32_t offs[2] = {res_quad_base(l), res_pair_base(l) + 8 * kResRoundBytes}, end = nr * kResRoundBytes;
+  auto at = [&](int i, const uint32_t (&o)[2]) {
+    if constexpr (FULL) return src + o[i < 8 ? 0 : 1] + res_split_part(i);
+    const uint32_t w = o[i < 8 ? 0 : 1] + res_split_part(i);
+    return src + (w < end ? w : l.sl * 8);
+  };
+  res_gather<true, kResMaxRounds, PROBE>(src, probe, offs, at, kResMaxRounds, x);
+  if constexpr (!FULL) {
+#pragma unroll
+    for (int i = 0; i < kResMaxRounds; ++i)
+      if (offs[i < 8 ? 0 : 1] + res_split_part(i) >= end) x[i] = 0;
+  }
 }
-// hidden states of a lane -> operand
-__device__ __forceinline__ void res_split_hid(const uint64_t (&x)[kResMaxRounds], ResW16 &o) {
+// words of a lane -> operand
+__device__ __forceinline__ void res_split_act(const uint64_t (&x)[kResMaxRounds], float scale, ResW16 &o) {
   uint32_t h[kResMaxRounds], l[kResMaxRounds];
 #pragma unroll
-  for (int i = 0; i < kResMaxRounds; ++i) split_f16(lo_f(x[i]) * kHidScale, hi_f(x[i]) * kHidScale, h[i], l[i]);
+  for (int i = 0; i < kResMaxRounds; ++i) split_f16(lo_f(x[i]) * scale, hi_f(x[i]) * scale, h[i], l[i]);
 #pragma unroll
   for (int g = 0; g < 2; ++g) {
     o.h[g] = uintx4_t{h[4 * g], h[4 * g + 1], h[4 * g + 2], h[4 * g + 3]};
@@ -281,9 +322,21 @@ __device__ __forceinline__ void res_split_hid(const uint64_t (&x)[kResMaxRounds]
   o.th = uintx2_t{h[8], h[9]};
   o.tl = uintx2_t{l[8], l[9]};
 }
-// N tiles of 16 rows.  n_rounds: of the slice (beyond: zeros)
-template <bool FULL, int N>
-__device__ __forceinline__ void res_split_mma(const ResW16 *w, const ResW16 &x, int n_rounds, floatx4 (&acc)[N], floatx4 (&cor)[N]) {
+// a lane's part of a split tile, p: the wave's
+__device__ __forceinline__ ResW16 res_split_load(const uintx4_t *p, const ResLane &l) {
+  const uintx4_t v = p[4 * 64 + l.lane];
+  return ResW16{{p[l.lane], p[2 * 64 + l.lane]}, {p[64 + l.lane], p[3 * 64 + l.lane]}, uintx2_t{v[0], v[1]}, uintx2_t{v[2], v[3]}};
+}
+// the 20 words as they lie in a tile that is not split (res_fold_mma's)
+__device__ __forceinline__ float res_raw(const ResW16 &w, int i) {
+  return __uint_as_float(i < 16 ? ((i >> 2) & 1 ? w.l[i >> 3][i & 3] : w.h[i >> 3][i & 3]) : i < 18 ? w.th[i & 1] : w.tl[i & 1]);
+}
+// A 16x16x16 instruction that takes up the sums of a 16x16x32 one right behind it has missed the last one's addends (seen here: the
+// compiler puts no wait states between the two shapes); these are well above the latency.
+__device__ __forceinline__ void res_mma_gap(floatx4 &acc, floatx4 &cor) { asm volatile("s_nop 15" : "+v"(acc), "+v"(cor)); }
+// N tiles of 16 rows, from w[T0] on.  n_rounds: of the slice (beyond: zeros)
+template <bool FULL, int T0, int N, int M>
+__device__ __forceinline__ void res_split_mma(const ResW16 (&w)[M], const ResW16 &x, int n_rounds, floatx4 (&acc)[N], floatx4 (&cor)[N]) {
 #pragma unroll
   for (int t = 0; t < N; ++t) acc[t] = cor[t] = floatx4{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
@@ -291,27 +344,31 @@ __device__ __forceinline__ void res_split_mma(const ResW16 *w, const ResW16 &x, 
     if (FULL || 4 * g < n_rounds) {
 #pragma unroll
       for (int t = 0; t < N; ++t) {
-        acc[t] = mfma16_f16(w[t].h[g], x.h[g], acc[t]);
-        cor[t] = mfma16_f16(w[t].h[g], x.l[g], cor[t]);
+        acc[t] = mfma16_f16(w[T0 + t].h[g], x.h[g], acc[t]);
+        cor[t] = mfma16_f16(w[T0 + t].h[g], x.l[g], cor[t]);
       }
 #pragma unroll
-      for (int t = 0; t < N; ++t) cor[t] = mfma16_f16(w[t].l[g], x.h[g], cor[t]);
+      for (int t = 0; t < N; ++t) cor[t] = mfma16_f16(w[T0 + t].l[g], x.h[g], cor[t]);
     }
   if (FULL || n_rounds > 8) {
-    // A 16x16x16 instruction that takes up the sums of a 16x16x32 one right behind it has missed its last addend (seen here: the
-    // compiler puts no wait states between the two shapes); these are well above the latency.
 #pragma unroll
-    for (int t = 0; t < N; ++t) asm volatile("s_nop 15" : "+v"(acc[t]), "+v"(cor[t]));
+    for (int t = 0; t < N; ++t) res_mma_gap(acc[t], cor[t]);
 #pragma unroll
     for (int t = 0; t < N; ++t) {
-      acc[t] = mfma16_f16(w[t].th, x.th, acc[t]);
-      cor[t] = mfma16_f16(w[t].th, x.tl, cor[t]);
+      acc[t] = mfma16_f16(w[T0 + t].th, x.th, acc[t]);
+      cor[t] = mfma16_f16(w[T0 + t].th, x.tl, cor[t]);
     }
 #pragma unroll
-    for (int t = 0; t < N; ++t) cor[t] = mfma16_f16(w[t].tl, x.th, cor[t]);
+    for (int t = 0; t < N; ++t) cor[t] = mfma16_f16(w[T0 + t].tl, x.th, cor[t]);
   }
 }
 
+// Places in ResBlock::par: of each tile four floats per group of four rows, as the lanes that finish it hold them.
+struct ResPar {
+  static constexpr int kScale = 0, kBias = 4;                     // of a projection or output-layer tile
+  static constexpr int kP = 0, kJ = 8 * kResMaxP, kR = kJ + 8 * 4;  // first of the projection's, the output layer's, W_hh's (no bias)
+  static constexpr int kFloats = 4 * (kR + 4 * kResMaxR);
+};
 // partial sums of a 16-row tile: wave's lane (row group, slot) holds four rows
 template <bool BF16>
 __device__ __forceinline__ float *res_red(const ResBlock &k, int block) {
@@ -334,7 +391,7 @@ __device__ __forceinline__ floatx4 res_sum(const ResBlock &k, const ResLane &l, 
 }
 
 // Waits for the words of step `step` and leaves them in the wave's LDS copy; slots beyond the group's are idle (finished).
-// 1: every utterance of the group has finished, 0: not yet, -1: the wait gave up.
+// 1: every utterance of the group has finished, 0: not yet.
 __device__ __forceinline__ int res_words(ResBlock &k, int step) {
   const ResArgs &a = res_args();
   const ResLane l = res_lane();
@@ -353,7 +410,7 @@ __device__ __forceinline__ int res_words(ResBlock &k, int step) {
         missing = word_tag(w) != tag;
       }
       if (__ballot(missing) == 0ull) break;
-      if (!wait.again()) return -1;
+      wait.again();
     }
     if (__ballot(!word_finished(w))) top = nt + 1;
     if (l.kq == 0) k.word[slot] = w;
@@ -398,25 +455,28 @@ __device__ __forceinline__ floatx4 res_p_frame(const ResArgs &a, const ResBlock 
   tt = tt < 0 ? 0 : tt;
   return res_p_pick(l, a.f_proj + ((size_t)in.y + tt) * a.H + 16 * k.ptile + 8 * (l.kq >> 1));
 }
-__device__ __forceinline__ floatx4 res_p_bias(const ResArgs &a, const ResBlock &k, const ResLane &l) {
-  return res_p_pick(l, a.b_pred + 16 * k.ptile + 8 * (l.kq >> 1));
-}
 // sums of the wave's tile -> pre.  first / second: the blocks of its partial sums of the two halves of k (halves: the
 // per-step launches add the bias and the frame's projection to the first half's sum, then the second half's).
 template <bool BF16>
 __device__ __forceinline__ void res_p_finish(const ResArgs &a, const ResBlock &k, const ResLane &l, const ResAddr &ad, int step, int nt, int first,
-                                             int second, floatx4 bias, floatx4 f) {
-  floatx4 v = (res_sum<BF16>(k, l, first) + bias) + f;
-  if (a.halves) v += res_sum<BF16>(k, l, second);
+                                             int second, floatx4 f) {
+  const floatx4 *par = k.par + ResPar::kP + 8 * (kResWaves - 1 - k.wave) + l.kq;
+  floatx4 v = res_sum<BF16>(k, l, first);
+  if constexpr (!BF16) v *= par[ResPar::kScale];
+  v = (v + par[ResPar::kBias]) + f;
+  if (a.halves) {
+    floatx4 s = res_sum<BF16>(k, l, second);
+    if constexpr (!BF16) s *= par[ResPar::kScale];
+    v += s;
+  }
   float *dst = res_p_dst(ad.p(step, nt), k.ptile, l.kq, l.sl);
+  asm volatile("" : "+v"(v));  // (all four before either store: else both sums' operands live on behind the first)
   wait_stores_acknowledged();  // (of the pattern that this wave put back into places of the array meanwhile)
-  res_store(k.local, reinterpret_cast<uint64_t *>(dst), pack2(v[0], v[1]));
-  res_store(k.local, reinterpret_cast<uint64_t *>(dst + 2 * kResSlot), pack2(v[2], v[3]));
+  res_store_pair(k.local, reinterpret_cast<uint64_t *>(dst), kResSlot, pack2(v[0], v[1]), pack2(v[2], v[3]));
 }
 __device__ __forceinline__ void clear_p(const ResBlock &k, const ResLane &l, const ResAddr &ad, int step, int nt) {
   float *dst = res_p_dst(ad.p(step, nt), k.ptile, l.kq, l.sl);
-  res_store(k.local, reinterpret_cast<uint64_t *>(dst), (uint64_t)~0ull);
-  res_store(k.local, reinterpret_cast<uint64_t *>(dst + 2 * kResSlot), (uint64_t)~0ull);
+  res_store_pair(k.local, reinterpret_cast<uint64_t *>(dst), kResSlot, ~0ull, ~0ull);
 }
 // the wave that finishes a tile of the projection: from the last one down, which own no cells
 __device__ __forceinline__ int res_p_wave(int tile_no) { return kResWaves - 1 - tile_no; }
@@ -437,17 +497,47 @@ __device__ __forceinline__ floatx16 mfma_pair_bf16(uint64_t w0, uint64_t w1, uin
   const uintx4_t b = {(uint32_t)x0, (uint32_t)(x0 >> 32), two ? (uint32_t)x1 : 0u, two ? (uint32_t)(x1 >> 32) : 0u};
   return __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8_t, w), __builtin_bit_cast(bf16x8_t, b), acc, 0, 0, 0);
 }
-// lane (column c, half): the two words of a round; columns 16..31 are the next slot tile (or a repeat)
-__device__ __forceinline__ const uint64_t *bf16_src(const ResLane &l, const float *tile0, size_t tile_floats, bool second,
-                                                    int round0) {
+// Lane (column c, half): the two words of a round, quads half and half + 2; columns 16..31 are the next slot tile (or a repeat).
+// Offset from the slice's first word; rounds follow in even strides of kResWordBytes.
+__device__ __forceinline__ uint32_t bf16_src(const ResLane &l, size_t tile_floats, bool second) {
   const int half = l.lane >> 5, c = l.lane & 31;
-  const float *t = tile0 + ((c >> 4) && second ? tile_floats : 0);
-  return reinterpret_cast<const uint64_t *>(t) + (size_t)(round0 * 4 + half) * kResSlot + (c & 15);
+  return ((c >> 4) && second ? (uint32_t)tile_floats * 4 : 0u) + (half * kResSlot + (c & 15)) * 8;
 }
-// words of a round: quads half and half + 2, i.e. two words 2 * 16 apart; rounds 4 * 16 apart: one even stride
-template <bool FULL, int ROUNDS>
-__device__ __forceinline__ bool bf16_gather(const uint64_t *p, int n, uint64_t (&x)[2 * ROUNDS]) {
-  return res_gather<FULL, 2 * ROUNDS>([p](int i) { return p + i * 2 * kResSlot; }, 2 * n, x);
+// Ten rounds of a lane's words: five from first on, five from then on (offsets of the slice's rounds from src; the first n of either
+// are there, the others repeat the first).  With one tile of slots the lanes of the columns beyond it read the words of k + 1 for
+// the others, which halves the loads.
+template <bool FULL>
+__device__ __forceinline__ void bf16_gather(const ResLane &l, const char *src, uint32_t first, uint32_t then, int n_first, int n_then, bool second, size_t tile_floats,
+                                            uint32_t probe, uint64_t (&x)[2 * kResMaxRounds]) {
+  constexpr int R = kResMaxRounds / 2;
+  const uint32_t lane0 = bf16_src(l, tile_floats, second);
+  if (second) {
+    const uint32_t offs[2] = {lane0 + first, lane0 + then};
+    res_gather<true, 2 * kResMaxRounds>(src, probe, offs, [&](int i, const uint32_t (&o)[2]) {
+      const int r = i / 2 % R;
+      return src + o[i / kResMaxRounds] + (FULL || r < (i < kResMaxRounds ? n_first : n_then) ? r * kResRoundBytes : 0) + (i & 1) * kResWordBytes;
+    }, 0, x);
+  } else {
+    const uint32_t odd = (l.lane & 16) ? kResWordBytes : 0;
+    const uint32_t offs[2] = {lane0 + first + odd, lane0 + then + odd};
+    uint64_t y[kResMaxRounds];
+    res_gather<true, kResMaxRounds, false>(src, probe, offs, [&](int i, const uint32_t (&o)[2]) {
+      const int r = i % R;
+      return src + o[i / R] + (FULL || r < (i < R ? n_first : n_then) ? r * kResRoundBytes : 0);
+    }, 0, y);
+#pragma unroll
+    for (int i = 0; i < kResMaxRounds; ++i) {
+      const auto lo = __builtin_amdgcn_permlane16_swap((uint32_t)y[i], (uint32_t)y[i], false, false);
+      const auto hi = __builtin_amdgcn_permlane16_swap((uint32_t)(y[i] >> 32), (uint32_t)(y[i] >> 32), false, false);
+      x[2 * i] = (uint64_t)(uint32_t)hi[0] << 32 | (uint32_t)lo[0];
+      x[2 * i + 1] = (uint64_t)(uint32_t)hi[1] << 32 | (uint32_t)lo[1];
+    }
+  }
+}
+// (words to poll of the second slot tile: lanes from 32 on)
+__device__ __forceinline__ ResLane bf16_probe_lane(const ResLane &l) { return ResLane{l.lane & 31, 0, 0}; }
+__device__ __forceinline__ uint32_t bf16_probe_tile(const ResLane &l, size_t tile_floats, bool second) {
+  return (l.lane >> 5) && second ? (uint32_t)tile_floats * 4 : 0u;
 }
 // 32-row tile's accumulators -> partial sums of its two 16-row tiles (blocks b0, b0 + 1) for columns 16 nt2 .. + 15
 __device__ __forceinline__ void bf16_put(const ResBlock &k, const ResLane &l, int b0, int nt2, const floatx16 &acc) {
@@ -463,8 +553,8 @@ __device__ __forceinline__ void bf16_put(const ResBlock &k, const ResLane &l, in
 }
 
 template <bool FULL, bool BF16>
-__device__ __forceinline__ bool res_p_phase(ResBlock &k, int step) {
-  if (k.nP == 0) return true;
+__device__ __forceinline__ void res_p_phase(ResBlock &k, int step) {
+  if (k.nP == 0) return;
   const ResArgs &a = res_args();
   const ResLane l = res_lane();
   const ResAddr ad = res_addr(a, k.g);
@@ -475,39 +565,61 @@ __device__ __forceinline__ bool res_p_phase(ResBlock &k, int step) {
 #pragma unroll 1
     for (int nt = 0; nt < k.nt; nt += 2) {
       const bool second = nt + 1 < k.nt;
-      floatx4 f[2] = {floatx4{0.f, 0.f, 0.f, 0.f}, floatx4{0.f, 0.f, 0.f, 0.f}}, bias = f[0];
+      floatx4 f[2] = {floatx4{0.f, 0.f, 0.f, 0.f}, floatx4{0.f, 0.f, 0.f, 0.f}};
       if (k.ptile >= 0) {
-        bias = res_p_bias(a, k, l);
         f[0] = res_p_frame(a, k, l, nt);
         if (second) f[1] = res_p_frame(a, k, l, nt + 1);
       }
       const uint64_t *w = k.tiles + l.lane;
       if (second) __syncthreads();  // (both halves of the buffer are written below; one of them has just been read)
-      for (int hf = 0; hf < (halves ? 2 : 1); ++hf) {
-        const int r0 = halves ? hf * (4 * nr) + k.wave * nh : k.wave * nr;
-        uint64_t x[2 * kResMaxRounds];
-        if (!bf16_gather<false, kResMaxRounds>(bf16_src(l, ad.h(step, nt), ad.h_tile, second, r0), nh, x)) return false;
-        floatx16 acc = {0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0};
-#pragma unroll
-        for (int i = 0; i < kResMaxRounds / 2; ++i)
-          if (2 * i < nh) {
-            const bool two = 2 * i + 1 < nh;
-            acc = mfma_pair_bf16(w[(r0 + 2 * i) * 64], w[(r0 + 2 * i + (two ? 1 : 0)) * 64], round_bf16<false>(x + 4 * i),
-                                 round_bf16<false>(x + 4 * i + 2), two, acc);
-          }
+      // words of five rounds of the first half's slice, then of the second's (or of ten of the one slice); absent ones repeat the first
+      const int ra = k.wave * nh, rb = halves ? 4 * nr + ra : nr > 5 ? ra + 5 : ra;
+      uint64_t x[2 * kResMaxRounds];
+      {
+        const int pr = (l.lane & 31) < 2 * nr ? (l.lane & 31) >> 1 : 0;
+        const uint32_t probe = bf16_probe_tile(l, ad.h_tile, second) + (!halves || pr < nh ? ra + pr : rb + pr - nh) * kResRoundBytes + (l.lane & 1) * kResWordBytes;
+        bf16_gather<FULL>(l, reinterpret_cast<const char *>(ad.h(step, nt)), ra * kResRoundBytes, rb * kResRoundBytes, halves ? nh : min(nr, 5),
+                          halves ? nh : max(nr - 5, 0), second, ad.h_tile, probe, x);
+      }
+      auto put = [&](int hf, const floatx16 &acc) {
         bf16_put(k, l, 2 * hf, 0, acc);
         if (second) {  // the other slot tile's sums go to the other half of the buffer
           ++k.phase;
           bf16_put(k, l, 2 * hf, 1, acc);
           --k.phase;
         }
+      };
+      if (halves) {
+#pragma unroll
+        for (int hf = 0; hf < 2; ++hf) {
+          const uint64_t *wh = w + (hf ? rb : ra) * 64;
+          floatx16 acc = {0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0};
+#pragma unroll
+          for (int i = 0; i < 3; ++i)
+            if (2 * i < nh) {
+              const bool two = i < 2 && 2 * i + 1 < nh;
+              const uint64_t *xi = x + kResMaxRounds * hf + 4 * i;
+              acc = mfma_pair_bf16(wh[2 * i * 64], wh[(2 * i + (two ? 1 : 0)) * 64], round_bf16<false>(xi), round_bf16<false>(i < 2 ? xi + 2 : xi), two, acc);
+            }
+          put(hf, acc);
+        }
+      } else {
+        floatx16 acc = {0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0};
+#pragma unroll
+        for (int i = 0; i < kResMaxRounds / 2; ++i)
+          if (2 * i < nr) {
+            const bool two = 2 * i + 1 < nr;
+            acc = mfma_pair_bf16(w[(ra + 2 * i) * 64], w[(ra + 2 * i + (two ? 1 : 0)) * 64], round_bf16<false>(x + 4 * i),
+                                 round_bf16<false>(x + 4 * i + 2), two, acc);
+          }
+        put(0, acc);
       }
       __syncthreads();
-      if (res_gave_up()) return false;
-      if (k.ptile >= 0) res_p_finish<true>(a, k, l, ad, step, nt, k.ptile & 1, 2 + (k.ptile & 1), bias, f[0]);
+      res_end_if_given_up();
+      if (k.ptile >= 0) res_p_finish<true>(a, k, l, ad, step, nt, k.ptile & 1, 2 + (k.ptile & 1), f[0]);
       ++k.phase;
       if (second) {
-        if (k.ptile >= 0) res_p_finish<true>(a, k, l, ad, step, nt + 1, k.ptile & 1, 2 + (k.ptile & 1), bias, f[1]);
+        if (k.ptile >= 0) res_p_finish<true>(a, k, l, ad, step, nt + 1, k.ptile & 1, 2 + (k.ptile & 1), f[1]);
         ++k.phase;
         __syncthreads();  // (both halves of the buffer have just been read)
       }
@@ -515,60 +627,100 @@ __device__ __forceinline__ bool res_p_phase(ResBlock &k, int step) {
   } else {
 #pragma unroll 1
     for (int nt = 0; nt < k.nt; ++nt) {
-      floatx4 f = {0.f, 0.f, 0.f, 0.f}, bias = f;
-      if (k.ptile >= 0) {
-        bias = res_p_bias(a, k, l);
-        f = res_p_frame(a, k, l, nt);
-      }
-      uint64_t x[kResMaxRounds];
-      // rounds i < nr / 2 from the wave's slice of the first half of k, the others from its slice of the second half (or
-      // all of one slice)
-      const uint64_t *src = reinterpret_cast<const uint64_t *>(ad.h(step, nt)) + (size_t)k.wave * nh * 64 + l.lane;
-      const int n1 = FULL ? kResMaxRounds / 2 : nr / 2, jump = halves ? (4 * nr - n1) * 64 : 0;
-      auto at = [&](int i) { return src + i * 64 + (i >= n1 ? jump : 0); };
-      if (!res_gather<FULL, kResMaxRounds>(at, nr, x)) return false;
-      for (int tp = 0; tp < k.nP; ++tp) {
-        const uint64_t *w = k.tiles + (size_t)tp * (a.P * kResSlot / 2) + (size_t)k.wave * nh * 64 + l.lane;
-        if (halves) {
-          floatx4 acc0 = {0.f, 0.f, 0.f, 0.f}, acc1 = acc0;
-#pragma unroll
-          for (int i = 0; i < kResMaxRounds / 2; ++i)
-            if (FULL || i < n1) {
-              const uint64_t u = w[i * 64], v = w[(4 * nr + i) * 64];
-              const uint64_t y = FULL ? x[kResMaxRounds / 2 + i] : res_pick(x, n1 + i);
-              acc0 = mfma16(lo_f(u), lo_f(x[i]), acc0);
-              acc1 = mfma16(lo_f(v), lo_f(y), acc1);
-              acc0 = mfma16(hi_f(u), hi_f(x[i]), acc0);
-              acc1 = mfma16(hi_f(v), hi_f(y), acc1);
-            }
-          res_put<false>(k, l, 0, acc0);
-          res_put<false>(k, l, 1, acc1);
-        } else {
-          floatx4 acc = {0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-          for (int i = 0; i < kResMaxRounds; ++i)
-            if (FULL || i < nr) {
-              const uint64_t u = w[i * 64];
-              acc = mfma16(lo_f(u), lo_f(x[i]), acc);
-              acc = mfma16(hi_f(u), hi_f(x[i]), acc);
-            }
-          res_put<false>(k, l, 0, acc);
-        }
+      floatx4 f = {0.f, 0.f, 0.f, 0.f};
+      if (k.ptile >= 0) f = res_p_frame(a, k, l, nt);
+      const char *src = reinterpret_cast<const char *>(ad.h(step, nt)) + k.wave * nh * kResRoundBytes;
+      const uintx4_t *tiles = reinterpret_cast<const uintx4_t *>(k.tiles) + (size_t)k.wave * kResQuads * 64;
+      // what the wave finishes of tile tp (a copy per tile: their blocks of partial sums alternate)
+      auto finish = [&](int tp) {
         __syncthreads();
-        if (res_gave_up()) return false;
-        if (k.wave == res_p_wave(tp)) res_p_finish<false>(a, k, l, ad, step, nt, 0, 1, bias, f);
+        res_end_if_given_up();
+        if (k.wave == res_p_wave(tp)) res_p_finish<false>(a, k, l, ad, step, nt, 0, 1, f);
         ++k.phase;
+      };
+      if (halves) {
+        // a slice of up to five rounds of either half of k: a quad, and a fifth round that the lanes of even kq hold
+        uint64_t x[12];
+        // (absent rounds: words that are there, cleared below)
+        const uint32_t end = nh * kResRoundBytes, second = 4 * nr * kResRoundBytes;
+        const uint32_t quad = res_quad_base(l), fifth = (FULL || nh > 4) && (l.kq & 1) == 0 ? 4 * kResRoundBytes + res_pair_base(l) : l.sl * 8;
+        const uint32_t offs[4] = {quad, fifth, quad + second, fifth + second};
+        auto at = [&](int i, const uint32_t (&o)[4]) {
+          const int p = i % 6, hf = i / 6;
+          if constexpr (FULL) return src + o[2 * hf + (p >= 4)] + res_part(p & 3);
+          const uint32_t w = o[2 * hf] + res_part(p);
+          return src + (p >= 4 ? o[2 * hf + 1] + res_part(p & 3) : w < end + hf * second ? w : l.sl * 8 + hf * second);
+        };
+        const int pr = l.lane < 2 * nr ? l.lane >> 1 : 0;
+        const uint32_t probe = (pr < nh ? pr : pr - nh + 4 * nr) * kResRoundBytes + (l.lane & 1) * kResWordBytes;
+        res_gather<true, 12, false>(src, probe, offs, at, 12, x);
+        uintx4_t xh[2], xl[2];
+        uintx2_t yh[2], yl[2];
+#pragma unroll
+        for (int hf = 0; hf < 2; ++hf) {
+          uint32_t h[6], lo[6];
+#pragma unroll
+          for (int p = 0; p < 6; ++p) {
+            const bool in = p < 4 ? FULL || quad + res_part(p) < end : (FULL || nh > 4) && (l.kq & 1) == 0;
+            const uint64_t v = in ? x[6 * hf + p] : 0;
+            split_f16(lo_f(v) * kHidScale, hi_f(v) * kHidScale, h[p], lo[p]);
+          }
+          xh[hf] = uintx4_t{h[0], h[1], h[2], h[3]};
+          xl[hf] = uintx4_t{lo[0], lo[1], lo[2], lo[3]};
+          yh[hf] = uintx2_t{h[4], h[5]};
+          yl[hf] = uintx2_t{lo[4], lo[5]};
+        }
+#pragma unroll 1
+        for (int tp = 0; tp < k.nP; ++tp) {
+          const uintx4_t *w = tiles + (size_t)tp * (kResTileFloats / 4);
+#pragma unroll
+          for (int hf = 0; hf < 2; ++hf) {
+            const uintx4_t wh = w[160 * hf + l.lane], wl = w[160 * hf + 64 + l.lane];
+            floatx4 acc = {0.f, 0.f, 0.f, 0.f}, cor = acc;
+            acc = mfma16_f16(wh, xh[hf], acc);
+            cor = mfma16_f16(wh, xl[hf], cor);
+            cor = mfma16_f16(wl, xh[hf], cor);
+            if (FULL || nh > 4) {
+              uintx4_t v = w[160 * hf + 128 + (l.kq >> 1) * 16 + l.sl];
+              if (l.kq & 1) v = uintx4_t{0, 0, 0, 0};
+              const uintx2_t vh = {v[0], v[1]}, vl = {v[2], v[3]};
+              res_mma_gap(acc, cor);
+              acc = mfma16_f16(vh, yh[hf], acc);
+              cor = mfma16_f16(vh, yl[hf], cor);
+              cor = mfma16_f16(vl, yh[hf], cor);
+            }
+            res_put<false>(k, l, hf, acc + cor);
+            __builtin_amdgcn_sched_barrier(0);  // (both halves at once need more registers than there are)
+          }
+          finish(tp);
+        }
+      } else {
+        ResW16 xs;
+        {
+          uint64_t x[kResMaxRounds];
+          res_split_gather<FULL, false>(l, src, res_probe_h(l, nr), nr, x);
+          res_split_act(x, kHidScale, xs);
+        }
+#pragma unroll 1
+        for (int tp = 0; tp < k.nP; ++tp) {
+          const ResW16 w[1] = {res_split_load(tiles + (size_t)tp * (kResTileFloats / 4), l)};
+          floatx4 acc[1], cor[1];
+          res_split_mma<FULL, 0, 1>(w, xs, nr, acc, cor);
+          res_put<false>(k, l, 0, acc[0] + cor[0]);
+          finish(tp);
+        }
       }
     }
   }
-  return true;
 }
 
 // ---- J: z[step] = W_out ReLU(pre[step]) + b_out for the block's tiles
 template <bool BF16>
-__device__ __forceinline__ void res_j_finish(const ResBlock &k, const ResLane &l, const ResAddr &ad, int step, int nt, int tile, floatx4 bias, int block) {
+__device__ __forceinline__ void res_j_finish(const ResBlock &k, const ResLane &l, const ResAddr &ad, int step, int nt, int tile, int par, int block) {
   const int slot = nt * kResSlot + l.sl, n0 = 16 * tile + 4 * l.kq;
-  const floatx4 v = res_sum<BF16>(k, l, block) + bias;
+  floatx4 v = res_sum<BF16>(k, l, block);
+  if constexpr (!BF16) v *= k.par[par + ResPar::kScale + l.kq];
+  v += k.par[par + ResPar::kBias + l.kq];
   wait_stores_acknowledged();
   if (slot < k.nslots) res_store16(k.local, ad.z(step, slot) + n0, v);
 }
@@ -582,7 +734,8 @@ __device__ __forceinline__ void clear_z(const ResBlock &k, const ResLane &l, con
 // in the order of k_stateless_pre.  All rows of a pair of tables are requested before the first is needed: the time is that
 // of one trip to the L2 (each block of a group reads all of the group's rows, at most 16 x (1 + n_ctx) x 2.5 KB; a
 // hand-over of sums formed once would cost a hop more, and the same trip before it).
-template <bool FULL, bool BF16>
+// SPLIT (float32 models): a lane's places of split operands (see ResW16), else those of res_k_of.
+template <bool FULL, bool BF16, bool SPLIT>
 __device__ __forceinline__ void res_stateless_pre(const ResArgs &a, const ResBlock &k, const ResLane &l, int nr,
                                                   uint64_t (&x)[(BF16 ? 2 : 1) * kResMaxRounds]) {
   const int slot = l.sl < k.nslots ? l.sl : 0;  // (places without a slot repeat the first one's rows)
@@ -591,15 +744,21 @@ __device__ __forceinline__ void res_stateless_pre(const ResArgs &a, const ResBlo
   int tt = word_frame(k.word[slot]);
   tt = tt < in.x ? tt : in.x - 1;
   tt = tt < 0 ? 0 : tt;
-  const int k0 = 8 * k.wave * nr + 4 * (BF16 ? l.lane >> 5 : l.kq & 1);
-  float4 v[kResMaxRounds];
-  auto row = [&](float4 (&d)[kResMaxRounds], const float *p) {
+  constexpr int N = SPLIT ? kResMaxRounds / 2 : kResMaxRounds;
+  // (SPLIT: four k of two rounds of either quad, then of the last two rounds)
+  auto round_of = [&](int i) { return !SPLIT ? i : i < 4 ? 4 * (i >> 1) + 2 * (l.kq >> 1) + (i & 1) : 8 + (l.kq & 1); };
+  const int k0 = 8 * k.wave * nr + 4 * (BF16 ? l.lane >> 5 : l.kq & 1), k4 = 8 * k.wave * nr + 4 * (l.kq >> 1);
+  float4 v[N];
+  auto row = [&](float4 (&d)[N], const float *p) {
 #pragma unroll
-    for (int i = 0; i < kResMaxRounds; ++i) d[i] = *reinterpret_cast<const float4 *>(p + k0 + 8 * (FULL || i < nr ? i : 0));
+    for (int i = 0; i < N; ++i) {
+      const int r = round_of(i);
+      d[i] = *reinterpret_cast<const float4 *>(p + (SPLIT && i == 4 ? k4 : k0) + 8 * (FULL || r < nr ? r : 0));
+    }
   };
-  auto add = [&](const float4 (&d)[kResMaxRounds]) {
+  auto add = [&](const float4 (&d)[N]) {
 #pragma unroll
-    for (int i = 0; i < kResMaxRounds; ++i) {
+    for (int i = 0; i < N; ++i) {
       v[i].x += d[i].x; v[i].y += d[i].y; v[i].z += d[i].z; v[i].w += d[i].w;
     }
   };
@@ -608,15 +767,19 @@ __device__ __forceinline__ void res_stateless_pre(const ResArgs &a, const ResBlo
   for (int j = 0; j < a.n_ctx; j += 2) {
     const int j1 = j + 1 < a.n_ctx ? j + 1 : j;
     const int t0 = j == 0 ? c.x : c.z, t1 = j1 == j ? t0 : j == 0 ? c.y : c.w;
-    float4 d0[kResMaxRounds], d1[kResMaxRounds];
+    float4 d0[N], d1[N];
     row(d0, a.emb_tab + ((size_t)j * (a.V + 1) + (t0 < 0 ? a.V : t0)) * a.H);
     row(d1, a.emb_tab + ((size_t)j1 * (a.V + 1) + (t1 < 0 ? a.V : t1)) * a.H);
     add(d0);
     if (j1 > j) add(d1);
   }
 #pragma unroll
-  for (int i = 0; i < kResMaxRounds; ++i) {
-    if constexpr (BF16) {
+  for (int i = 0; i < N; ++i) {
+    if constexpr (SPLIT) {
+      const bool in = FULL || round_of(i) < nr;
+      x[2 * i] = in ? pack2(v[i].x, v[i].z) : 0;
+      x[2 * i + 1] = in ? pack2(v[i].y, v[i].w) : 0;
+    } else if constexpr (BF16) {
       x[2 * i] = pack2(v[i].x, v[i].z);
       x[2 * i + 1] = pack2(v[i].y, v[i].w);
     } else {
@@ -628,18 +791,15 @@ __device__ __forceinline__ void res_stateless_pre(const ResArgs &a, const ResBlo
 // wave slice and half of every eight k a chain of its own, then the halves' sum, then the slices'.
 // Float32: one matrix instruction takes the four k of a half.  x: two k of a round, {0, 4, 1, 5}[kq] and two further; the
 // swaps (rows 2, 3 of the first with rows 0, 1 of the second, then odd rows with even ones) leave k = kq and 4 + kq.  The
-// weights lie that way (k_pack_fold).  other: the block's second tile, in the usual order, between the two chains.
-__device__ __forceinline__ floatx4 res_fold_mma(const float (&w)[2 * kResMaxRounds], const uint64_t (&x)[kResMaxRounds],
-                                                const float (&w_other)[2 * kResMaxRounds], floatx4 &other) {
+// weights lie that way (k_pack_fold).
+__device__ __forceinline__ floatx4 res_fold_mma(const ResW16 &w, const uint64_t (&x)[kResMaxRounds]) {
   floatx4 lo = {0.f, 0.f, 0.f, 0.f}, hi = lo;
 #pragma unroll
   for (int i = 0; i < kResMaxRounds; ++i) {
     const auto s32 = __builtin_amdgcn_permlane32_swap((uint32_t)x[i], (uint32_t)(x[i] >> 32), false, false);
     const auto s16 = __builtin_amdgcn_permlane16_swap(s32[0], s32[1], false, false);
-    other = mfma16(w_other[2 * i], lo_f(x[i]), other);
-    lo = mfma16(w[2 * i], __uint_as_float(s16[0]), lo);
-    other = mfma16(w_other[2 * i + 1], hi_f(x[i]), other);
-    hi = mfma16(w[2 * i + 1], __uint_as_float(s16[1]), hi);
+    lo = mfma16(res_raw(w, 2 * i), __uint_as_float(s16[0]), lo);
+    hi = mfma16(res_raw(w, 2 * i + 1), __uint_as_float(s16[1]), hi);
   }
   return lo + hi;
 }
@@ -680,39 +840,46 @@ __device__ __forceinline__ void res_update_ctx(const ResBlock &k) {
   wave_sync();
 }
 
+// float32: split tiles (the one that is folded as k_pack_fold leaves it); bf16: four k a pair of words, round by round
+template <bool BF16>
+struct ResWJ {
+  std::conditional_t<BF16, float[kResRegJ<true>][2 * kResMaxRounds], ResW16[kResRegJ<false>]> t;
+};
+// W_hh: split (float32 models), or round by round
+template <bool BF16>
+struct ResWR {
+  std::conditional_t<BF16, float[kResMaxR][2 * kResMaxRounds], ResW16[kResMaxR]> t;
+};
 // wj: the tiles that the block keeps in registers; one more may lie in LDS behind the projection's
 template <bool FULL, bool BF16, bool ST>
-__device__ __forceinline__ bool res_j_phase(ResBlock &k, int step, const float (&wj)[kResRegJ<BF16>][2 * kResMaxRounds]) {
-  if (k.nJ == 0) return true;
+__device__ __forceinline__ void res_j_phase(ResBlock &k, int step, const ResWJ<BF16> &wj) {
+  if (k.nJ == 0) return;
   constexpr int NJ = kResRegJ<BF16>;
   const ResArgs &a = res_args();
   const ResLane l = res_lane();
   const ResAddr ad = res_addr(a, k.g);
   const int nr = FULL ? kResMaxRounds : a.rounds_h;
-  floatx4 bias[2];
-#pragma unroll
-  for (int t = 0; t < 2; ++t) {
-    bias[t] = floatx4{0.f, 0.f, 0.f, 0.f};
-    if ((BF16 || t == 0) && k.jtile[t] >= 0) bias[t] = *reinterpret_cast<const floatx4 *>(a.b_out + 16 * k.jtile[t] + 4 * l.kq);
-  }
-  const uint64_t *wx = k.tiles + (size_t)k.nP * (a.P * kResSlot / 2) + (size_t)k.wave * nr * 64 + l.lane;
   if constexpr (BF16) {
+    const uint64_t *wx = k.tiles + (size_t)k.nP * (a.P * kResSlot / 2) + (size_t)k.wave * nr * 64 + l.lane;
 #pragma unroll 1
     for (int nt = 0; nt < k.nt; nt += 2) {
       const bool second = nt + 1 < k.nt;
-      if (step == a.stall_step && nt + 2 >= k.nt) return false;
+      if (step == a.stall_step && nt + 2 >= k.nt) __builtin_amdgcn_endpgm();
       uint64_t x[2 * kResMaxRounds];
-      if constexpr (ST) res_stateless_pre<FULL, true>(a, k, l, nr, x);
-      else if (!bf16_gather<FULL, kResMaxRounds>(bf16_src(l, ad.p(step, nt), ad.p_tile, second, k.wave * nr), nr, x)) return false;
+      if constexpr (ST) res_stateless_pre<FULL, true, false>(a, k, l, nr, x);
+      else {
+        const uint32_t probe = bf16_probe_tile(l, ad.p_tile, second) + res_probe_p(bf16_probe_lane(l), nr);
+        bf16_gather<FULL>(l, reinterpret_cast<const char *>(ad.p(step, nt)) + k.wave * nr * kResRoundBytes, 0, nr > 5 ? 5 * kResRoundBytes : 0, min(nr, 5),
+                          max(nr - 5, 0), second, ad.p_tile, probe, x);
+      }
       uint64_t xb[kResMaxRounds];
 #pragma unroll
       for (int i = 0; i < kResMaxRounds; ++i) xb[i] = round_bf16<true>(x + 2 * i);
       auto put_out = [&](int t) {
         __syncthreads();
-        if (res_gave_up()) return false;
-        if (k.wave < (second ? 4 : 2)) res_j_finish<true>(k, l, ad, step, nt + (k.wave >> 1), k.jtile[t], bias[t], k.wave);
+        res_end_if_given_up();
+        if (k.wave < (second ? 4 : 2)) res_j_finish<true>(k, l, ad, step, nt + (k.wave >> 1), k.jtile[t], ResPar::kJ + 8 * (2 * t + (k.wave & 1)), k.wave);
         ++k.phase;
-        return true;
       };
 #pragma unroll
       for (int t = 0; t < NJ + 1; ++t) {
@@ -720,7 +887,7 @@ __device__ __forceinline__ bool res_j_phase(ResBlock &k, int step, const float (
         if constexpr (FULL)
           if (t == 0 && k.fold) {
             res_fold_bf16(k, l, a.N - a.V, second, xb);
-            if (!put_out(t)) return false;
+            put_out(t);
             continue;
           }
         floatx16 acc = {0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0};
@@ -730,8 +897,8 @@ __device__ __forceinline__ bool res_j_phase(ResBlock &k, int step, const float (
             const bool two = FULL || 2 * i + 1 < nr;
             uint64_t w0, w1;
             if (t < NJ) {
-              w0 = pack2(wj[t < NJ ? t : 0][4 * i], wj[t < NJ ? t : 0][4 * i + 1]);
-              w1 = pack2(wj[t < NJ ? t : 0][4 * i + 2], wj[t < NJ ? t : 0][4 * i + 3]);
+              w0 = pack2(wj.t[t < NJ ? t : 0][4 * i], wj.t[t < NJ ? t : 0][4 * i + 1]);
+              w1 = pack2(wj.t[t < NJ ? t : 0][4 * i + 2], wj.t[t < NJ ? t : 0][4 * i + 3]);
             } else {
               w0 = wx[2 * i * 64];
               w1 = wx[(2 * i + (two ? 1 : 0)) * 64];
@@ -740,56 +907,66 @@ __device__ __forceinline__ bool res_j_phase(ResBlock &k, int step, const float (
           }
         bf16_put(k, l, 0, 0, acc);
         if (second) bf16_put(k, l, 2, 1, acc);
-        if (!put_out(t)) return false;
+        put_out(t);
       }
     }
   } else {
 #pragma unroll 1
     for (int nt = 0; nt < k.nt; ++nt) {
-      if (step == a.stall_step && nt + 1 == k.nt) return false;
-      uint64_t x[kResMaxRounds];
-      const uint64_t *src = reinterpret_cast<const uint64_t *>(ad.p(step, nt)) + (size_t)k.wave * nr * 64 + l.lane;
-      if constexpr (ST) res_stateless_pre<FULL, false>(a, k, l, nr, x);
-      else if (!res_gather<FULL, kResMaxRounds>([src](int i) { return src + i * 64; }, nr, x)) return false;
+      if (step == a.stall_step && nt + 1 == k.nt) __builtin_amdgcn_endpgm();
+      const char *src = reinterpret_cast<const char *>(ad.p(step, nt)) + k.wave * nr * kResRoundBytes;
+      auto relu = [](uint64_t (&x)[kResMaxRounds]) {
 #pragma unroll
-      for (int i = 0; i < kResMaxRounds; ++i) x[i] = pack2(fmaxf(lo_f(x[i]), 0.f), fmaxf(hi_f(x[i]), 0.f));
-      floatx4 acc[NJ];
+        for (int i = 0; i < kResMaxRounds; ++i) x[i] = pack2(fmaxf(lo_f(x[i]), 0.f), fmaxf(hi_f(x[i]), 0.f));
+      };
+      ResW16 xs;
+      float inv;
+      {
+        uint64_t x[kResMaxRounds];
+        if constexpr (ST) res_stateless_pre<FULL, false, true>(a, k, l, nr, x);
+        else res_split_gather<FULL, false>(l, src, res_probe_p(l, nr), nr, x);
+        relu(x);
+        float m = 0.f;
 #pragma unroll
-      for (int t = 0; t < NJ; ++t) acc[t] = floatx4{0.f, 0.f, 0.f, 0.f};
-      if (FULL && k.fold) {
-        static_assert(NJ == 2);
-        acc[0] = res_fold_mma(wj[0], x, wj[1], acc[1]);
-      } else {
-#pragma unroll
-        for (int i = 0; i < kResMaxRounds; ++i)
-          if (FULL || i < nr) {
-#pragma unroll
-            for (int t = 0; t < NJ; ++t) acc[t] = mfma16(wj[t][2 * i], lo_f(x[i]), acc[t]);
-#pragma unroll
-            for (int t = 0; t < NJ; ++t) acc[t] = mfma16(wj[t][2 * i + 1], hi_f(x[i]), acc[t]);
-          }
+        for (int i = 0; i < kResMaxRounds; ++i) m = fmaxf(m, fmaxf(lo_f(x[i]), hi_f(x[i])));
+        const auto s16 = __builtin_amdgcn_permlane16_swap(__float_as_uint(m), __float_as_uint(m), false, false);
+        m = fmaxf(__uint_as_float(s16[0]), __uint_as_float(s16[1]));
+        const auto s32 = __builtin_amdgcn_permlane32_swap(__float_as_uint(m), __float_as_uint(m), false, false);
+        m = fmaxf(__uint_as_float(s32[0]), __uint_as_float(s32[1]));
+        const float scale = split_scale(m, inv);
+        res_split_act(x, scale, xs);
       }
+      if (FULL && k.fold) {
+        uint64_t x[kResMaxRounds];  // (known to be there; other places of it than above)
+        if constexpr (ST) res_stateless_pre<FULL, false, false>(a, k, l, nr, x);
+        else {
 #pragma unroll
-      for (int t = 0; t < NJ; ++t)
-        if (t < k.nJ) res_put<false>(k, l, t, acc[t]);
+          for (int i = 0; i < kResMaxRounds; ++i) x[i] = res_load(src + l.lane * 8 + i * kResRoundBytes);
+        }
+        relu(x);
+        floatx4 c1[1], d1[1];
+        res_split_mma<FULL, 1, 1>(wj.t, xs, nr, c1, d1);
+        res_put<false>(k, l, 0, res_fold_mma(wj.t[0], x));
+        if (1 < k.nJ) res_put<false>(k, l, 1, (c1[0] + d1[0]) * inv);
+      } else {
+        floatx4 acc[NJ], cor[NJ];
+        res_split_mma<FULL, 0, NJ>(wj.t, xs, nr, acc, cor);
+#pragma unroll
+        for (int t = 0; t < NJ; ++t)
+          if (t < k.nJ) res_put<false>(k, l, t, (acc[t] + cor[t]) * inv);
+      }
       if (k.nJ > NJ) {
-        floatx4 c = {0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-        for (int i = 0; i < kResMaxRounds; ++i)
-          if (FULL || i < nr) {
-            const uint64_t u = wx[i * 64];
-            c = mfma16(lo_f(u), lo_f(x[i]), c);
-            c = mfma16(hi_f(u), hi_f(x[i]), c);
-          }
-        res_put<false>(k, l, NJ, c);
+        const ResW16 w[1] = {res_split_load(reinterpret_cast<const uintx4_t *>(k.tiles) + (size_t)k.nP * (kResTileFloats / 4) + (size_t)k.wave * kResQuads * 64, l)};
+        floatx4 c1[1], d1[1];
+        res_split_mma<FULL, 0, 1>(w, xs, nr, c1, d1);
+        res_put<false>(k, l, NJ, (c1[0] + d1[0]) * inv);
       }
       __syncthreads();
-      if (res_gave_up()) return false;
-      if (k.jtile[0] >= 0) res_j_finish<false>(k, l, ad, step, nt, k.jtile[0], bias[0], k.wave);
+      res_end_if_given_up();
+      if (k.jtile[0] >= 0) res_j_finish<false>(k, l, ad, step, nt, k.jtile[0], ResPar::kJ + 8 * k.wave, k.wave);
       ++k.phase;
     }
   }
-  return true;
 }
 
 // the block's own pieces of pre[step] and of the logits of `step`: every word of `step` has been seen, i.e. every selecting
@@ -847,18 +1024,16 @@ __device__ __forceinline__ void res_worker(ResBlock k, const ResTab &tab, float 
   const ResLane l0 = res_lane();
   // weights: projection tiles (and the output-layer tile that finds no registers) to LDS, the others to registers
   {
-    const int n4 = a0.P * kResSlot / 4, h4 = a0.H * kResSlot / 4;
+    const int n4 = BF16 ? a0.P * kResSlot / 4 : kResTileFloats / 4, h4 = BF16 ? a0.H * kResSlot / 4 : kResTileFloats / 4;
     uintx4_t *dst = reinterpret_cast<uintx4_t *>(lds);
     k.tiles = reinterpret_cast<const uint64_t *>(lds);
     for (int tp = 0; tp < k.nP; ++tp) {
-      const uintx4_t *src = (BF16 ? reinterpret_cast<const uintx4_t *>(a0.WPb) : reinterpret_cast<const uintx4_t *>(a0.WP)) +
-                            (size_t)tab.P[tp] * n4;
+      const uintx4_t *src = (BF16 ? reinterpret_cast<const uintx4_t *>(a0.WPb) : a0.WP) + (size_t)tab.P[tp] * n4;
       for (int i = threadIdx.x; i < n4; i += kResThreads) dst[i] = src[i];
       dst += n4;
     }
     if (k.nJ > NJ) {
-      const uintx4_t *src = (BF16 ? reinterpret_cast<const uintx4_t *>(a0.WJb) : reinterpret_cast<const uintx4_t *>(a0.WJ)) +
-                            (size_t)tab.J[NJ] * h4;
+      const uintx4_t *src = (BF16 ? reinterpret_cast<const uintx4_t *>(a0.WJb) : a0.WJ) + (size_t)tab.J[NJ] * h4;
       for (int i = threadIdx.x; i < h4; i += kResThreads) dst[i] = src[i];
       dst += h4;
     }
@@ -876,7 +1051,25 @@ __device__ __forceinline__ void res_worker(ResBlock k, const ResTab &tab, float 
   }
   // LDS of the cells: sums W_hh h of the block's tiles, cell state and hidden state of their units, [tile][slot tile][64]
   float *Rl = k.red + 2 * kResRedBlocks<BF16> * kResRedBlock, *cl = Rl + kResMaxR * a0.NT * 256, *hl = cl + kResMaxR * a0.NT * 64;
-  int2 *info = reinterpret_cast<int2 *>(hl + kResMaxR * a0.NT * 64);
+  float *par = hl + kResMaxR * a0.NT * 64;
+  k.par = reinterpret_cast<const floatx4 *>(par);
+  if (threadIdx.x < 16) {
+    const int i = threadIdx.x;
+    auto tile = [&](int first, int row, const float *unscale, const float *bias) {
+      if (unscale) par[4 * (first + ResPar::kScale) + i] = unscale[row];
+      if (bias) par[4 * (first + ResPar::kBias) + i] = bias[row];
+    };
+    constexpr int W = BF16 ? 2 : 1;  // 16-row tiles of a tile
+    for (int t = 0; t < W * k.nP; ++t)
+      tile(ResPar::kP + 8 * t, res_p_row(W * tab.P[t / W] + t % W, i), a0.pred_unscale, a0.b_pred);
+    for (int t = 0; t < W * k.nJ; ++t) {
+      const int row = 16 * (W * tab.J[t / W] + t % W) + i;
+      tile(ResPar::kJ + 8 * t, row, a0.out_unscale, a0.b_out);
+      if (k.fold && t == 0) par[4 * (ResPar::kJ + ResPar::kScale) + i] = 1.f;  // (folded from weights that are not split)
+    }
+    for (int t = 0; t < k.nR; ++t) tile(ResPar::kR + 4 * t, 4 * (8 * (tab.R[t] >> 1) + 2 * (i >> 2) + (tab.R[t] & 1)) + (i & 3), a0.hh_unscale, nullptr);
+  }
+  int2 *info = reinterpret_cast<int2 *>(par + ResPar::kFloats);
   if constexpr (!ST)
     for (int i = threadIdx.x; i < kResMaxR * a0.NT * (256 + 128); i += kResThreads) Rl[i] = 0.f;
   if (threadIdx.x < a0.NT * kResSlot) {
@@ -889,46 +1082,77 @@ __device__ __forceinline__ void res_worker(ResBlock k, const ResTab &tab, float 
     k.ctx = reinterpret_cast<int4 *>(Rl) + k.wave * a0.NT * kResSlot;
     for (int i = l0.lane; i < a0.NT * kResSlot; i += 64) k.ctx[i] = make_int4(-1, -1, -1, -1);
   }
-  float wj[NJ][2 * kResMaxRounds];
-  ResW16 wr[ST ? 1 : kResMaxR];
+  ResWJ<BF16> wj;
+  ResWR<BF16> wr;
   {
-    const int nrh = FULL ? kResMaxRounds : a0.rounds_h;
+    if constexpr (BF16) {
+      const int nrh = FULL ? kResMaxRounds : a0.rounds_h;
 #pragma unroll
-    for (int t = 0; t < NJ; ++t)
+      for (int t = 0; t < NJ; ++t)
 #pragma unroll
-      for (int i = 0; i < kResMaxRounds; ++i) {
-        wj[t][2 * i] = wj[t][2 * i + 1] = 0.f;
-        if (t < k.nJ && (FULL || i < nrh)) {
-          const bool fold = !BF16 && t == 0 && k.fold;
-          const uint64_t v = ((BF16 ? a0.WJb : reinterpret_cast<const uint64_t *>(fold ? a0.WJs : a0.WJ)) +
-                              ((size_t)(fold ? 0 : tab.J[t]) * (a0.H / 8) + k.wave * nrh) * 64 + l0.lane)[i * 64];
-          wj[t][2 * i] = lo_f(v);
-          wj[t][2 * i + 1] = hi_f(v);
+        for (int i = 0; i < kResMaxRounds; ++i) {
+          wj.t[t][2 * i] = wj.t[t][2 * i + 1] = 0.f;
+          if (t < k.nJ && (FULL || i < nrh)) {
+            const uint64_t v = a0.WJb[((size_t)tab.J[t] * (a0.H / 8) + k.wave * nrh + i) * 64 + l0.lane];
+            wj.t[t][2 * i] = lo_f(v);
+            wj.t[t][2 * i + 1] = hi_f(v);
+          }
         }
+    } else {
+#pragma unroll
+      for (int t = 0; t < NJ; ++t) {
+        wj.t[t] = ResW16{};
+        if (t < k.nJ) wj.t[t] = res_split_load(a0.WJ + ((size_t)tab.J[t] * kResWaves + k.wave) * kResQuads * 64, l0);
       }
+      if (FULL && k.fold) {  // (words 0 to 19 of the lane, see res_raw)
+        uint32_t v[2 * kResMaxRounds];
+#pragma unroll
+        for (int i = 0; i < kResMaxRounds; ++i) {
+          const uint64_t u = reinterpret_cast<const uint64_t *>(a0.WJs)[(k.wave * kResMaxRounds + i) * 64 + l0.lane];
+          v[2 * i] = (uint32_t)u;
+          v[2 * i + 1] = (uint32_t)(u >> 32);
+        }
+        wj.t[0] = ResW16{{{v[0], v[1], v[2], v[3]}, {v[8], v[9], v[10], v[11]}}, {{v[4], v[5], v[6], v[7]}, {v[12], v[13], v[14], v[15]}}, {v[16], v[17]}, {v[18], v[19]}};
+      }
+    }
 #pragma unroll
     for (int t = 0; t < NR; ++t) {
-      wr[t] = ResW16{};
-      if (t < k.nR) {
-        const uintx4_t *src = a0.WR + ((size_t)tab.R[t] * kResWaves + k.wave) * kResQuads * 64 + l0.lane;
-        wr[t].h[0] = src[0];
-        wr[t].l[0] = src[64];
-        wr[t].h[1] = src[128];
-        wr[t].l[1] = src[192];
-        const uintx4_t v = src[256];
-        wr[t].th = uintx2_t{v[0], v[1]};
-        wr[t].tl = uintx2_t{v[2], v[3]};
+      if constexpr (BF16) {
+        const int nrp = FULL ? kResMaxRounds : a0.rounds_p;
+#pragma unroll
+        for (int i = 0; i < kResMaxRounds; ++i) {
+          wr.t[t][2 * i] = wr.t[t][2 * i + 1] = 0.f;
+          if (t < k.nR && (FULL || i < nrp)) {
+            const uint64_t v = reinterpret_cast<const uint64_t *>(a0.WRf)[((size_t)tab.R[t] * (a0.P / 8) + k.wave * nrp + i) * 64 + l0.lane];
+            wr.t[t][2 * i] = lo_f(v);
+            wr.t[t][2 * i + 1] = hi_f(v);
+          }
+        }
+      } else {
+        wr.t[t] = ResW16{};
+        if (t < k.nR) wr.t[t] = res_split_load(a0.WR + ((size_t)tab.R[t] * kResWaves + k.wave) * kResQuads * 64, l0);
       }
     }
     // (loaded once; without this the compiler would rather load them again in every step)
+    auto keep = [](ResW16 &w) { asm volatile("" : "+v"(w.h[0]), "+v"(w.h[1]), "+v"(w.l[0]), "+v"(w.l[1]), "+v"(w.th), "+v"(w.tl)); };
 #pragma unroll
-    for (int i = 0; i < 2 * kResMaxRounds; ++i) {
+    for (int t = 0; t < NJ; ++t) {
+      if constexpr (BF16) {
 #pragma unroll
-      for (int t = 0; t < NJ; ++t) asm volatile("" : "+v"(wj[t][i]));
+        for (int i = 0; i < 2 * kResMaxRounds; ++i) asm volatile("" : "+v"(wj.t[t][i]));
+      } else {
+        keep(wj.t[t]);
+      }
     }
 #pragma unroll
-    for (int t = 0; t < NR; ++t)
-      asm volatile("" : "+v"(wr[t].h[0]), "+v"(wr[t].h[1]), "+v"(wr[t].l[0]), "+v"(wr[t].l[1]), "+v"(wr[t].th), "+v"(wr[t].tl));
+    for (int t = 0; t < NR; ++t) {
+      if constexpr (BF16) {
+#pragma unroll
+        for (int i = 0; i < 2 * kResMaxRounds; ++i) asm volatile("" : "+v"(wr.t[t][i]));
+      } else {
+        keep(wr.t[t]);
+      }
+    }
   }
   __syncthreads();
   int over = res_first_words(a0, k);
@@ -969,8 +1193,8 @@ __device__ __forceinline__ void res_worker(ResBlock k, const ResTab &tab, float 
         }
     }
     if constexpr (!ST)
-      if (!res_p_phase<FULL, BF16>(k, step)) return;
-    if (!res_j_phase<FULL, BF16, ST>(k, step, wj)) return;
+      res_p_phase<FULL, BF16>(k, step);
+    res_j_phase<FULL, BF16, ST>(k, step, wj);
     // (under the selection: ahead of the projection the waits for the activations included these stores)
     if (step > 0) {
       const ResArgs &a = res_args();
@@ -991,41 +1215,55 @@ __device__ __forceinline__ void res_worker(ResBlock k, const ResTab &tab, float 
       if (step > 1 && k.wave < k.nR)
         for (int nt = 0; nt < k.nt; ++nt)
           res_store(k.local, reinterpret_cast<uint32_t *>(ad.h(step - 2, nt) + res_h_ofs(l, mytile)), kResEmpty);
-      const floatx4 unscale = *reinterpret_cast<const floatx4 *>(a.hh_unscale + 4 * (8 * (mytile >> 1) + 2 * l.kq + (mytile & 1)));
 #pragma unroll 1
       for (int nt = 0; nt < k.nt; ++nt) {
         ResW16 xs;
-        {
-          uint64_t x[kResMaxRounds];
-          const uint64_t *src = reinterpret_cast<const uint64_t *>(ad.h(step, nt)) + (size_t)k.wave * nrp * 64;
-          // (absent rounds read the slice's first and are cleared)
-          auto at = [&](int i) {
-            const int w = res_split_word(l, i);
-            return src + (FULL || w < nrp * 64 ? w : l.sl);
-          };
-          if (!res_gather<true, kResMaxRounds>(at, kResMaxRounds, x)) return;
-          if constexpr (!FULL) {
-#pragma unroll
-            for (int i = 0; i < kResMaxRounds; ++i)
-              if (res_split_word(l, i) >= nrp * 64) x[i] = 0;
-          }
-          res_split_hid(x, xs);
+        uint64_t x[kResMaxRounds];
+        const char *src = reinterpret_cast<const char *>(ad.h(step, nt)) + k.wave * nrp * kResRoundBytes;
+        // (nearly always there: the logits needed all of it)
+        if constexpr (BF16) {
+          const uint32_t offs[2] = {(uint32_t)l.lane * 8, (uint32_t)l.lane * 8 + 5 * kResRoundBytes};
+          res_gather<FULL, kResMaxRounds, false>(src, 0, offs, [src](int i, const uint32_t (&o)[2]) { return src + o[i / 5] + i % 5 * kResRoundBytes; }, nrp, x);
+        } else {
+          res_split_gather<FULL, false>(l, src, 0, nrp, x);
+          res_split_act(x, kHidScale, xs);
         }
-#pragma unroll
-        for (int t0 = 0; t0 < kResMaxR; t0 += 3) {
-          if (t0 >= k.nR) break;
+        auto three = [&](auto first) {
+          constexpr int t0 = decltype(first)::value;
+          if (t0 >= k.nR) return;
           // (tiles that the block does not own have zero weights; fewer branches are worth more than their instructions)
           floatx4 acc[3], cor[3];
-          res_split_mma<FULL, 3>(wr + t0, xs, nrp, acc, cor);
+          if constexpr (BF16) {
+#pragma unroll
+            for (int t = 0; t < 3; ++t) acc[t] = cor[t] = floatx4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+            for (int i = 0; i < kResMaxRounds; ++i)
+              if (FULL || i < nrp) {
+#pragma unroll
+                for (int t = 0; t < 3; ++t) acc[t] = mfma16(wr.t[t0 + t][2 * i], lo_f(x[i]), acc[t]);
+#pragma unroll
+                for (int t = 0; t < 3; ++t) acc[t] = mfma16(wr.t[t0 + t][2 * i + 1], hi_f(x[i]), acc[t]);
+              }
+          } else {
+            res_split_mma<FULL, t0, 3>(wr.t, xs, nrp, acc, cor);
+#pragma unroll
+            for (int t = 0; t < 3; ++t) acc[t] += cor[t];
+          }
 #pragma unroll
           for (int t = 0; t < 3; ++t)
-            if (t0 + t < k.nR) res_put<BF16>(k, l, t, acc[t] + cor[t]);
+            if (t0 + t < k.nR) res_put<BF16>(k, l, t, acc[t]);
           __syncthreads();
-          if (res_gave_up()) return;
-          if (k.wave >= t0 && k.wave < t0 + 3 && k.wave < k.nR)
-            *reinterpret_cast<floatx4 *>(Rl + ((k.wave * a.NT + nt) * 64 + l.lane) * 4) = res_sum<BF16>(k, l, k.wave - t0) * unscale;
+          res_end_if_given_up();
+          if (k.wave >= t0 && k.wave < t0 + 3 && k.wave < k.nR) {
+            floatx4 s = res_sum<BF16>(k, l, k.wave - t0);
+            if constexpr (!BF16) s *= k.par[ResPar::kR + 4 * k.wave + l.kq];
+            *reinterpret_cast<floatx4 *>(Rl + ((k.wave * a.NT + nt) * 64 + l.lane) * 4) = s;
+          }
           ++k.phase;
-        }
+        };
+        static_assert(kResMaxR == 6);
+        three(std::integral_constant<int, 0>{});
+        three(std::integral_constant<int, 3>{});
       }
     }
     over = res_words(k, step);
@@ -1087,7 +1325,7 @@ __device__ __forceinline__ void group_sum_n(float (&x)[N]) {
 // (Every load is unconditional, from a clamped address, and nothing branches before the keys are compared: the wave's
 // time is the latency of this chain.)
 template <int NQ, int KC, int PLAIN>
-__device__ __forceinline__ bool res_row(int g, int step, int slot, const float *lmrow, int hyp, int part, int parts, ResSelLds &L) {
+__device__ __forceinline__ void res_row(int g, int step, int slot, const float *lmrow, int hyp, int part, int parts, ResSelLds &L) {
   const ResArgs &a = res_args();
   const int lane = threadIdx.x & 63, V = a.V, nz = a.N - V;
   const int q0 = part * NQ;
@@ -1096,13 +1334,12 @@ __device__ __forceinline__ bool res_row(int g, int step, int slot, const float *
   uint64_t zz[NQ + 1];  // the last: blank and duration logits, one per lane
   const uint32_t *ps = reinterpret_cast<const uint32_t *>(zrow) + V + (lane < nz ? lane : 0);
   ResWait w;
-  if (!res_probe(reinterpret_cast<const uint64_t *>(zrow + min(128 * q0 + 2 * lane, v_last)), w)) return false;
   for (;;) {
 #pragma unroll
     for (int q = 0; q < NQ; ++q) zz[q] = load_agent(reinterpret_cast<const uint64_t *>(zrow + min(128 * (q0 + q) + 2 * lane, v_last)));
     zz[NQ] = load_agent(ps);
     if (__ballot(res_any_empty(zz)) == 0ull) break;
-    if (!w.again()) return false;
+    w.again();
   }
   if (part == 0 && lane < nz) L.zs[hyp * nz + lane] = lo_f(zz[NQ]);
   // a place without a token: -inf
@@ -1175,7 +1412,6 @@ __device__ __forceinline__ bool res_row(int g, int step, int slot, const float *
   }
   if (lane < 8 && total + lane < cap) surv[total + lane] = 0;  // (below every key: the ranking reads in eights)
   if (lane == 0) L.n_surv[hyp][part] = total;
-  return true;
 }
 
 // The row's soft-max statistics from those of its chunks, added up in the order of the per-step kernels (which depends on
@@ -1355,13 +1591,13 @@ __device__ __forceinline__ void res_selector(ResBlock k, int sel, float *lds) {
     // all logits of the step were there)
     if (parts == 2) {
       const int q = k.wave >> 1;
-      if (q < n_rows && !res_row<kResMaxV / 256, KC, PLAIN>(k.g, step, u0 * K + q, late_lm ? lm_rows + (size_t)q * V : nullptr, q, k.wave & 1, 2, L)) return;
+      if (q < n_rows) res_row<kResMaxV / 256, KC, PLAIN>(k.g, step, u0 * K + q, late_lm ? lm_rows + (size_t)q * V : nullptr, q, k.wave & 1, 2, L);
     } else {
       for (int q = k.wave; q < n_rows; q += kResWaves)
-        if (!res_row<kResMaxV / 128, KC, PLAIN>(k.g, step, u0 * K + q, late_lm ? lm_rows + (size_t)q * V : nullptr, q, 0, 1, L)) return;
+        res_row<kResMaxV / 128, KC, PLAIN>(k.g, step, u0 * K + q, late_lm ? lm_rows + (size_t)q * V : nullptr, q, 0, 1, L);
     }
     __syncthreads();
-    if (res_gave_up()) return;
+    res_end_if_given_up();
     for (int q = k.wave; q < n_rows; q += kResWaves)
       res_row_finish<KC, PLAIN>(k.g, step, u0 * K + q, late_lm ? lm_rows + (size_t)q * V : nullptr, q, parts, L);
     __syncthreads();
@@ -1435,7 +1671,7 @@ __global__ __launch_bounds__(kResThreads, 2) void k_decode_resident(ResArgs) {
     }
     s_order[at] = (int16_t)(k.g + a.n_groups * threadIdx.x);
   }
-  if (threadIdx.x == 0) res_gave_up_word() = 0;
+  if (threadIdx.x == 0) *res_gave_up_word() = 0;
   k.order = s_order;
   k.nt = a.NT;
   __syncthreads();

@@ -19,8 +19,9 @@ struct Resident {
   bool usable = false;
   int n_cus = 0, max_lds = 0;
   int misses = 0, skip = 0;       // launches in a row that gave up; decodes left to the per-step launches before the next try
-  const float *hh_unscale = nullptr;  // the handle's
-  float *WR = nullptr, *WJ = nullptr, *WJs = nullptr, *WP = nullptr;
+  const float *hh_unscale = nullptr, *out_unscale = nullptr, *pred_unscale = nullptr;  // the handle's
+  uint32_t *WR = nullptr, *WJ = nullptr, *WP[2] = {nullptr, nullptr};  // see k_pack_split
+  float *WRf = nullptr, *WJs = nullptr;
   uint64_t *WJb = nullptr, *WPb = nullptr;
   float *hb = nullptr, *pb = nullptr, *zb = nullptr;
   uint64_t *words = nullptr;
@@ -41,8 +42,8 @@ inline void resident_missed(Resident &r) {
 
 // What the packing reads: the handle's k4-major weights (see kernels.h, k4_index)
 struct ResidentWeights {
-  const float *W_hh, *hh_unscale;  // split (k_split_rows)
-  const float *W_out, *W_pred;
+  // float32 models: split (k_split_rows), the output layer also as it is
+  const float *W_hh, *hh_unscale, *W_out, *W_out_s, *out_unscale, *W_pred, *pred_unscale;
   int out_rows;  // padded rows of W_out
 };
 

@@ -172,7 +172,7 @@ struct rnnt_beam {
   std::vector<void *> allocs;
   // packed weights
   float *W_enc = nullptr, *b_enc = nullptr, *W_pred = nullptr, *b_pred = nullptr, *W_out = nullptr,
-        *b_out = nullptr, *W_hh = nullptr, *hh_unscale = nullptr, *G = nullptr, *tab = nullptr;
+        *b_out = nullptr, *W_hh = nullptr, *hh_unscale = nullptr, *W_out_s = nullptr, *out_unscale = nullptr, *pred_unscale = nullptr, *G = nullptr, *tab = nullptr;
   // materialised-logits path (bf16 joint, large shapes)
   bool big = false;
   int Npad_big = 0, Hb = 0;  // padded extents of the bf16 operands: 256 columns, 64 k
@@ -332,6 +332,13 @@ std::vector<float> to_k4(const std::vector<float> &src, int rows, int K, int row
   return out;
 }
 
+int split_rows(rnnt_beam *h, float *W, int rows, int K, float x_scale, float **unscale) {
+  if (int rc = dev_alloc(h, unscale, rows)) return rc;
+  hipLaunchKernelGGL(k_split_rows, dim3((rows + 63) / 64), dim3(256), 0, nullptr, W, rows, K, x_scale, *unscale);
+  RB_HIP(h, hipGetLastError());
+  return RNNT_OK;
+}
+
 int pack_weights(rnnt_beam *h, const rnnt_weights_t *w) {
   const rnnt_config_t &c = h->cfg;
   const int H = c.H, P = c.P, D = c.D, E = c.E, V = c.V, N = h->N;
@@ -355,13 +362,18 @@ int pack_weights(rnnt_beam *h, const rnnt_weights_t *w) {
   if ((rc = upload(h, &d_wpred_rm, wpred))) return rc;
   staging.push_back(d_wpred_rm);
   if ((rc = upload(h, &h->W_pred, to_k4(wpred, H, P, H)))) return rc;
+  if (!bf && c.pred == RNNT_PRED_LSTM && (rc = split_rows(h, h->W_pred, H, P, kHidScale, &h->pred_unscale))) return rc;
   if ((rc = download(h, bpred, w->b_pred, H))) return rc;
   if ((rc = upload(h, &h->b_pred, bpred))) return rc;
   // output layer, rows padded with zeros to whole 32-column chunks
   if ((rc = download(h, tmp, w->W_out, (size_t)N * H))) return rc;
   if (bf)
     for (auto &x : tmp) x = host_bf16_round(x);
-  if ((rc = upload(h, &h->W_out, to_k4(tmp, N, H, h->n_chunks * 32)))) return rc;
+  if ((rc = upload(h, &h->W_out, out = to_k4(tmp, N, H, h->n_chunks * 32)))) return rc;
+  if (!bf) {
+    if ((rc = upload(h, &h->W_out_s, out))) return rc;
+    if ((rc = split_rows(h, h->W_out_s, h->n_chunks * 32, H, 1.f, &h->out_unscale))) return rc;
+  }
   if ((rc = download(h, tmp, w->b_out, N))) return rc;
   out.assign((size_t)h->n_chunks * 32, 0.f);
   for (int i = 0; i < N; ++i) out[i] = tmp[i];
@@ -409,9 +421,8 @@ int pack_weights(rnnt_beam *h, const rnnt_weights_t *w) {
       b_p[r] = bih[o] + bhh[o];
     }
     if ((rc = upload(h, &h->W_hh, to_k4(whh_p, 4 * P, P, 4 * P)))) return rc;
-    if ((rc = dev_alloc(h, &h->hh_unscale, (size_t)4 * P))) return rc;
-    hipLaunchKernelGGL(k_split_rows, dim3((4 * P + 63) / 64), dim3(256), 0, nullptr, h->W_hh, 4 * P, P, h->hh_unscale);
-    RB_HIP(h, hipGetLastError());
+    // (not for the bf16 joint: its rounding of the activations turns any other order of the sums into other near ties)
+    if (!bf && (rc = split_rows(h, h->W_hh, 4 * P, P, kHidScale, &h->hh_unscale))) return rc;
     // G[v] = W_ih emb[v] + b_ih + b_hh for every token (and the start symbol): one GEMM at create
     float *d_wih = nullptr, *d_b = nullptr, *d_emb = nullptr;
     if ((rc = upload(h, &d_wih, wih_p))) return rc;
@@ -560,7 +571,7 @@ int launch_pred(rnnt_beam *h, hipStream_t s, const StepPlan &p, int cur, int bum
     }
     {
       PredProjArgs a;
-      a.Wp = h->W_pred; a.bias = h->b_pred; a.h = w.h[cur ^ 1]; a.f_proj = w.f_proj;
+      a.Wp = h->W_pred; a.wp_unscale = h->pred_unscale; a.bias = h->b_pred; a.h = w.h[cur ^ 1]; a.f_proj = w.f_proj;
       a.t = w.t; a.lengths = w.lengths;
       a.pre = w.pre;
       if (proj_split(c, p.M)) {  // (the step at parity cur read buffer cur; this launch writes the next step's)
@@ -777,7 +788,8 @@ int launch_step(rnnt_beam *h, hipStream_t s, const StepPlan &p, int step_off, in
   } else {
     MainArgs a;
     a.pre = w.pre;
-    a.W = h->W_out;
+    a.W = h->W_out_s ? h->W_out_s : h->W_out;
+    a.W_plain = h->W_out; a.w_unscale = h->out_unscale;
     a.bias = h->b_out;
     a.lm = (p.lm && !c.lm_early_pruning) ? w.lm_rows : nullptr;  // early pruning ranks without the LM term
     a.lambda = p.lambda;
@@ -886,7 +898,7 @@ int launch_persistent(rnnt_beam *h, hipStream_t s, const StepPlan &p, int max_st
   const rnnt_config_t &c = h->cfg;
   PersistArgs a{};
   MainArgs &m = a.main;
-  m.pre = w.pre; m.W = h->W_out; m.bias = h->b_out; m.lm = nullptr; m.lambda = 0.f;
+  m.pre = w.pre; m.W = h->W_out_s ? h->W_out_s : h->W_out; m.W_plain = h->W_out; m.w_unscale = h->out_unscale; m.bias = h->b_out; m.lm = nullptr; m.lambda = 0.f;
   m.M = p.M; m.Mp = w.Mp; m.K = p.K; m.H = c.H; m.V = c.V; m.ND = c.n_durations;
   m.n_chunks = m.n_jchunks = h->n_chunks;
   m.round_ops = c.prec == RNNT_BF16_JOINT ? 1 : 0;
@@ -895,7 +907,7 @@ int launch_persistent(rnnt_beam *h, hipStream_t s, const StepPlan &p, int max_st
   m.rec.Whh = h->W_hh; m.rec.unscale = h->hh_unscale; m.rec.h = nullptr; m.rec.R = w.Rgates; m.rec.P = c.P; m.rec.M = p.M; m.rec.Mp = w.Mp; m.rec.group = 1;
   fill_select_args(h, p, 0, h->n_chunks, m.sel);  // (the step counter word stays 0: the kernel passes the step itself)
   PredProjArgs &q = a.pp;
-  q.Wp = h->W_pred; q.bias = h->b_pred; q.h = nullptr; q.f_proj = w.f_proj; q.t = w.t; q.lengths = w.lengths;
+  q.Wp = h->W_pred; q.wp_unscale = h->pred_unscale; q.bias = h->b_pred; q.h = nullptr; q.f_proj = w.f_proj; q.t = w.t; q.lengths = w.lengths;
   q.pre = w.pre;
   q.M = p.M; q.Mp = w.Mp; q.K = p.K; q.T = p.T; q.P = c.P; q.H = c.H; q.round_ops = m.round_ops;
   q.done = w.ctrl + 1; q.step_base = w.ctrl + 2; q.bump = 0;
@@ -959,7 +971,7 @@ struct DeviceSlot {
 
 int create_resident(rnnt_beam *h, int fail_alloc) {
   const rnnt_config_t &c = h->cfg;
-  const ResidentWeights rw{h->W_hh, h->hh_unscale, h->W_out, h->W_pred, h->n_chunks * 32};
+  const ResidentWeights rw{h->W_hh, h->hh_unscale, h->W_out, h->W_out_s, h->out_unscale, h->W_pred, h->pred_unscale, h->n_chunks * 32};
   return c.use_graph && !c.persistent_kernel && !c.async_enqueue ? resident_create(h->res, c, rw, h->err, fail_alloc) : RNNT_OK;
 }
 

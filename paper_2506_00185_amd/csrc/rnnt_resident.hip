@@ -13,40 +13,45 @@ namespace {
 
 __device__ __forceinline__ size_t k4_at(int k, int row, int rows) { return ((size_t)(k >> 2) * rows + row) * 4 + (k & 3); }
 
-// W (k4-major, `rows` rows) -> [tile of 16 rows][round][64 lanes][2].  MAP 0: rows as they are; 2: tiles of projection outputs
-// (res_p_row)
+// W (k4-major, `rows` rows, split by k_split_rows) -> [tile of 16 rows][wave][kResQuads * 64 words of 16 bytes] (see ResW16),
+// rounds of 8 k, absent ones zero.  MAP 0: rows as they are; 1: tiles of four LSTM units; 2: tiles of projection outputs.
+// One slice of k per wave: [quadword of a lane][64 lanes], hi and lo of the first two quads of rounds, then those of the last two
+// rounds.  halves: two slices of up to five rounds, one of either half of k; of each hi and lo of a quad, [64 lanes] each, then the
+// fifth round's [32 lanes]: the lanes of even kq.
 template <int MAP>
-__global__ void k_pack_f32(const float *W, int rows, int K, int n_tiles, float *out) {
-  const int n_rounds = K / 8;
-  const size_t n = (size_t)n_tiles * n_rounds * 128;
-  for (size_t i = (size_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += (size_t)gridDim.x * blockDim.x) {
-    const int e = (int)(i & 1), lane = (int)(i >> 1) & 63;
-    const int round = (int)((i >> 7) % n_rounds), tile = (int)((i >> 7) / n_rounds);
-    const int r = lane & 15, kq = lane >> 4;
-    int row;
-    if (MAP == 0) row = 16 * tile + r;
-    else row = res_p_row(tile, r);
-    out[i] = row < rows ? W[k4_at(res_k_of(round, kq, e), row, rows)] : 0.f;
-  }
-}
-// W_hh, split (k_split_rows), -> [tile of four LSTM units][wave][quadword of a lane][64 lanes] (see ResW16): rounds of 8 k of a
-// wave slice, absent ones zero.  Quadwords 0 to 3: hi and lo of the first two quads of rounds, 4: hi and lo of the last two rounds
-__global__ void k_pack_split(const uint32_t *W, int rows, int K, int n_tiles, uint32_t *out) {
-  const int n_rounds = K / 64;
+__global__ void k_pack_split(const uint32_t *W, int rows, int K, int n_tiles, bool halves, uint32_t *out) {
+  const int n_rounds = halves ? K / 128 : K / 64;
   const size_t n = (size_t)n_tiles * kResWaves * kResQuads * 64 * 4;
   for (size_t i = (size_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += (size_t)gridDim.x * blockDim.x) {
-    const int e = (int)(i & 3), lane = (int)(i >> 2) & 63, q = (int)((i >> 8) % kResQuads);
-    const int wave = (int)((i >> 8) / kResQuads) % kResWaves, tile = (int)((i >> 8) / kResQuads / kResWaves);
-    const int r = lane & 15, kq = lane >> 4, row = 4 * (8 * (tile >> 1) + 2 * (r >> 2) + (tile & 1)) + (r & 3);
-    const bool tail = q == 4, lo = tail ? e >> 1 : q & 1;
-    const int round = tail ? 8 + (kq & 1) : 4 * (q >> 1) + 2 * (kq >> 1) + (e >> 1), half = tail ? kq >> 1 : kq & 1;
+    const int e = (int)(i & 3), wave = (int)((i >> 8) / kResQuads) % kResWaves, tile = (int)((i >> 8) / kResQuads / kResWaves);
+    int at = (int)((i >> 2) % (kResQuads * 64)), slice = wave * n_rounds;
+    if (halves) {
+      slice += at / 160 * 8 * n_rounds;
+      at %= 160;
+    }
+    const int q = at >> 6, most = halves ? 4 : 8;
+    const bool tail = q == (halves ? 2 : 4), lo = tail ? e >> 1 : q & 1;
+    int r = at & 15, kq = (at >> 4) & 3;
+    if (halves && tail) kq = 2 * (kq & 1);
+    const int round = tail ? most + (kq & 1) : 4 * (q >> 1) + 2 * (kq >> 1) + (e >> 1), half = tail ? kq >> 1 : kq & 1;
+    const int row = MAP == 0 ? 16 * tile + r : MAP == 1 ? 4 * (8 * (tile >> 1) + 2 * (r >> 2) + (tile & 1)) + (r & 3) : res_p_row(tile, r);
     // the word of a lane holds k and k + 2 (see res_k_of)
     uint32_t v = 0;
-    if (round < n_rounds) {
-      const uint32_t *g = W + ((size_t)((wave * n_rounds + round) * 2 + half) * rows + row) * 4 + (lo ? 2 : 0);  // k pairs (0, 1), (2, 3)
+    if (round < n_rounds && row < rows) {
+      const uint32_t *g = W + ((size_t)((slice + round) * 2 + half) * rows + row) * 4 + (lo ? 2 : 0);  // k pairs (0, 1), (2, 3)
       v = (e & 1) == 0 ? (g[0] & 0xffffu) | g[1] << 16 : g[0] >> 16 | (g[1] & 0xffff0000u);
     }
     out[i] = v;
+  }
+}
+// W_hh of the bf16-joint models -> [tile of four LSTM units][round][64 lanes][2]
+__global__ void k_pack_units(const float *W, int rows, int K, int n_tiles, float *out) {
+  const int n_rounds = K / 8;
+  const size_t n = (size_t)n_tiles * n_rounds * 128;
+  for (size_t i = (size_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += (size_t)gridDim.x * blockDim.x) {
+    const int e = (int)(i & 1), lane = (int)(i >> 1) & 63, r = lane & 15;
+    const int round = (int)((i >> 7) % n_rounds), tile = (int)((i >> 7) / n_rounds);
+    out[i] = W[k4_at(res_k_of(round, lane >> 4, e), 4 * (8 * (tile >> 1) + 2 * (r >> 2) + (tile & 1)) + (r & 3), rows)];
   }
 }
 // rows row0 .. + 15 as res_fold_mma reads them: [round][64 lanes][2], k = 8 round + lane / 16 and four further
@@ -57,7 +62,7 @@ __global__ void k_pack_fold(const float *W, int rows, int row0, int K, float *ou
     out[i] = row < rows ? W[k4_at(8 * (i >> 7) + 4 * e + (lane >> 4), row, rows)] : 0.f;
   }
 }
-// k_pack_f32 for the bf16 matrix instructions: [tile of 32 rows][round][64 lanes] four bf16 (values are bf16 already)
+// For the bf16 matrix instructions: [tile of 32 rows][round][64 lanes] four bf16 (values are bf16 already)
 template <int MAP>
 __global__ void k_pack_bf16(const float *W, int rows, int K, int n_tiles, uint64_t *out) {
   const int n_rounds = K / 8;
@@ -180,9 +185,9 @@ Plan make_plan(const Resident &r, const rnnt_config_t &c, int B, int K, bool has
   const bool bf = c.prec == RNNT_BF16_JOINT;
   int lds_tiles = 0;
   for (const ResTab &t : p.tab) lds_tiles = std::max(lds_tiles, t.nP + std::max(0, t.nJ - (bf ? kResRegJ<true> : kResRegJ<false>)));
-  const size_t worker = (size_t)lds_tiles * std::max(c.pred == RNNT_PRED_LSTM ? c.P : 0, c.H) * kResSlot * 4 +
+  const size_t worker = (size_t)lds_tiles * (bf ? std::max(c.pred == RNNT_PRED_LSTM ? c.P : 0, c.H) * kResSlot : kResTileFloats) * 4 +
                         (bf && fold ? (size_t)(1 + c.n_durations) * c.H * 2 : 0) + (size_t)2 * (bf ? kResRedBlocks<true> : kResRedBlocks<false>) * kResRedBlock * 4 +
-                        (size_t)kResMaxR * p.NT * (256 + 128) * 4 + (size_t)p.NT * kResSlot * (sizeof(int2) + kResWaves * 8);
+                        (size_t)kResMaxR * p.NT * (256 + 128) * 4 + ResPar::kFloats * 4 + (size_t)p.NT * kResSlot * (sizeof(int2) + kResWaves * 8);
   const size_t sel = (sizeof(ResSelLds) + 15) / 16 * 16 + p.upc * sizeof(SelectScratchWide) +
                      (size_t)p.NT * kResSlot * kResWaves * 8 + (has_lm ? (size_t)p.upc * K * c.V * 4 : 0);
   p.lds = std::max(worker, sel);
@@ -242,10 +247,11 @@ int resident_create(Resident &r, const rnnt_config_t &c, const ResidentWeights &
     return e == hipSuccess;
   };
   const int nR = 4 * c.P / 16, nJ = bf ? (N + 31) / 32 : (N + 15) / 16, nP = bf ? c.H / 32 : c.H / 16;
-  bool ok = bf ? alloc(&r.WJb, (size_t)nJ * (c.H / 8) * 64) : alloc(&r.WJ, (size_t)nJ * 16 * c.H) && alloc(&r.WJs, (size_t)16 * c.H);
+  constexpr size_t kTileWords = kResTileFloats;
+  bool ok = bf ? alloc(&r.WJb, (size_t)nJ * (c.H / 8) * 64) : alloc(&r.WJ, nJ * kTileWords) && alloc(&r.WJs, (size_t)16 * c.H);
   if (lstm) {
-    ok = ok && alloc(&r.WR, (size_t)nR * kResWaves * kResQuads * 64 * 4) && alloc(&r.hb, kResStepRing * rows * c.P) && alloc(&r.pb, kResStepRing * rows * c.H);
-    ok = ok && (bf ? alloc(&r.WPb, (size_t)nP * (c.P / 8) * 64) : alloc(&r.WP, (size_t)nP * 16 * c.P));
+    ok = ok && (bf ? alloc(&r.WRf, (size_t)nR * 16 * c.P) : alloc(&r.WR, nR * kTileWords)) && alloc(&r.hb, kResStepRing * rows * c.P) && alloc(&r.pb, kResStepRing * rows * c.H);
+    ok = ok && (bf ? alloc(&r.WPb, (size_t)nP * (c.P / 8) * 64) : alloc(&r.WP[0], nP * kTileWords) && (c.P % 128 || alloc(&r.WP[1], nP * kTileWords)));
   }
   ok = ok && alloc(&r.zb, kResStepRing * rows * w.out_rows) &&
        alloc(&r.words, kResStepRing * rows) && alloc(&r.ctl, 64) && alloc(&r.tab, r.n_cus);
@@ -255,15 +261,22 @@ int resident_create(Resident &r, const rnnt_config_t &c, const ResidentWeights &
   const dim3 grid(512), block(256);
   if (bf) hipLaunchKernelGGL(k_pack_bf16<0>, grid, block, 0, nullptr, w.W_out, w.out_rows, c.H, nJ, r.WJb);
   else {
-    hipLaunchKernelGGL(k_pack_f32<0>, grid, block, 0, nullptr, w.W_out, w.out_rows, c.H, nJ, r.WJ);
+    hipLaunchKernelGGL(k_pack_split<0>, grid, block, 0, nullptr, reinterpret_cast<const uint32_t *>(w.W_out_s), w.out_rows, c.H, nJ, false, r.WJ);
+    r.out_unscale = w.out_unscale;
     hipLaunchKernelGGL(k_pack_fold, grid, block, 0, nullptr, w.W_out, w.out_rows, c.V / 16 * 16, c.H, r.WJs);
   }
   if (lstm) {
-    hipLaunchKernelGGL(k_pack_split, grid, block, 0, nullptr, reinterpret_cast<const uint32_t *>(w.W_hh), 4 * c.P, c.P, nR,
-                       reinterpret_cast<uint32_t *>(r.WR));
+    if (bf) hipLaunchKernelGGL(k_pack_units, grid, block, 0, nullptr, w.W_hh, 4 * c.P, c.P, nR, r.WRf);
+    else hipLaunchKernelGGL(k_pack_split<1>, grid, block, 0, nullptr, reinterpret_cast<const uint32_t *>(w.W_hh), 4 * c.P, c.P, nR, false, r.WR);
     r.hh_unscale = w.hh_unscale;
     if (bf) hipLaunchKernelGGL(k_pack_bf16<2>, grid, block, 0, nullptr, w.W_pred, c.H, c.P, nP, r.WPb);
-    else hipLaunchKernelGGL(k_pack_f32<2>, grid, block, 0, nullptr, w.W_pred, c.H, c.P, nP, r.WP);
+    else {
+      for (int halves = 0; halves < 2; ++halves)
+        if (r.WP[halves])
+          hipLaunchKernelGGL(k_pack_split<2>, grid, block, 0, nullptr, reinterpret_cast<const uint32_t *>(w.W_pred), c.H, c.P, nP, halves != 0,
+                             r.WP[halves]);
+      r.pred_unscale = w.pred_unscale;
+    }
   }
   if ((e = hipGetLastError()) != hipSuccess || (e = hipDeviceSynchronize()) != hipSuccess) return fail("resident loop: packing");
   r.usable = true;
@@ -280,7 +293,9 @@ hipError_t resident_launch(Resident &r, const rnnt_config_t &c, const ResidentBa
   Plan p = make_plan(r, c, b.B, b.K, b.has_lm, b.fold);
   if (!p.ok) return hipErrorInvalidValue;
   ResArgs a{};
-  a.WR = reinterpret_cast<const uintx4_t *>(r.WR); a.hh_unscale = r.hh_unscale; a.WJ = r.WJ; a.WJs = r.WJs; a.WP = r.WP; a.WJb = r.WJb; a.WPb = r.WPb;
+  a.WR = reinterpret_cast<const uintx4_t *>(r.WR); a.WJ = reinterpret_cast<const uintx4_t *>(r.WJ);
+  a.WP = reinterpret_cast<const uintx4_t *>(r.WP[b.halves ? 1 : 0]);
+  a.hh_unscale = r.hh_unscale; a.out_unscale = r.out_unscale; a.pred_unscale = r.pred_unscale; a.WRf = r.WRf; a.WJs = r.WJs; a.WJb = r.WJb; a.WPb = r.WPb;
   a.emb_tab = b.emb_tab; a.n_ctx = b.n_ctx;
   a.b_out = b.b_out; a.b_pred = b.b_pred; a.G = b.G; a.f_proj = b.f_proj;
   a.lengths = b.lengths;

@@ -196,6 +196,15 @@ __device__ __forceinline__ void res_store(bool local, T *p, T v) {
   if (local) __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WAVEFRONT);
   else store_agent(p, v);
 }
+__device__ __forceinline__ void res_store_pair(bool local, uint64_t *p, int second, uint64_t v0, uint64_t v1) {
+  if (local) {
+    __hip_atomic_store(p, v0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WAVEFRONT);
+    __hip_atomic_store(p + second, v1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WAVEFRONT);
+  } else {
+    store_agent(p, v0);
+    store_agent(p + second, v1);
+  }
+}
 __device__ __forceinline__ void res_store16(bool local, float *p, floatx4 v) {
   if (local) asm volatile("global_store_dwordx4 %0, %1, off" ::"v"(p), "v"(v) : "memory");
   else store16_through(p, v);

@@ -9,7 +9,7 @@ import numpy as np
 import pytest
 
 import synth_inputs as S
-from gpu_common import gpu_decode
+from gpu_common import compare, gpu_decode
 
 pytestmark = pytest.mark.gpu
 
@@ -209,6 +209,35 @@ def test_logits_that_do_not_come_end_the_resident_loop_as_a_whole(kw, step):
         r = gpu_decode(dec, enc, L)
         for key in KEYS:
             np.testing.assert_array_equal(r[key], ref[key])
+
+
+@pytest.mark.parametrize("h,B,beam", [(64, 3, 4), (320, 9, 5), (640, 5, 9), (640, 17, 4)])
+def test_split_products_over_a_wide_range_of_scales(oracle, h, B, beam):
+    """Outputs of the prediction and encoder projections times powers of two from 2^-6 to 2^6, columns of the output layer by their
+    inverses: the same function (ReLU is homogeneous), but rows, columns and activations of sizes far apart, which the split into
+    float16 has to scale.  The tolerance is that of float32 models: a value down to 2^-16 of the largest keeps 24 bits."""
+    import paper_2506_00185_amd as A
+    c = S.custom_config(B=B, T=12, T_min=6, s=3, V=90, beam=beam, blank_bias=3.0, H=h, P=h, E=64, D=64)
+    w = {k: np.array(v) for k, v in S.make_weights(c, 75).items()}
+    L = S.make_lengths(c, 77)
+    enc = S.make_enc(c, L, 78)
+    f = (2.0 ** np.random.default_rng(79).integers(-6, 7, h)).astype(np.float32)
+    for k in ("W_enc", "W_pred"):
+        w[k] = w[k] * f[:, None]
+    for k in ("b_enc", "b_pred"):
+        w[k] = w[k] * f
+    w["W_out"] = w["W_out"] / f[None, :]
+    w["W_hh"][5] = 0.0         # a row without weights
+    w["W_hh"][7] *= 2.0 ** -30
+    dec = A.BeamDecoder(c, w)
+    g = gpu_decode(dec, enc, L)
+    assert dec.last_step_loop() == "resident"
+    o = oracle.decode(c, w, enc, L, log=True)
+    full, exempt = compare(g, o, 1e-3, 1e-4)
+    assert full >= (c["B"] + 1) // 2
+    ref = gpu_decode(A.BeamDecoder(c, w, use_graph=False), enc, L)
+    for key in KEYS:
+        np.testing.assert_array_equal(g[key], ref[key])
 
 
 @pytest.mark.parametrize("kw", [dict(B=5, beam=4), dict(B=17, beam=9, prec="bf16"), dict(B=8, beam=4, **ST, ctx=2)], ids=["lstm", "bf16", "stateless"])
