@@ -676,11 +676,11 @@ __global__ __launch_bounds__(WAVES * 64, TAIL ? 1 : 16 / WAVES) void k_step_main
 
 // stand-alone selection kernels: one wave per utterance, four utterances per block
 __global__ __launch_bounds__(256) void k_select(SelectArgs a) {
-  __shared__ SelectScratchWide scratch[4];
+  __shared__ SelectScratch scratch[4];
   if (*reinterpret_cast<volatile int *>(a.done)) return;
   const int wave = threadIdx.x >> 6;
   const int b = blockIdx.x * 4 + wave;
-  if (b < a.B) select_dispatch<1, SelectScratchWide>(a, b, scratch[wave]);
+  if (b < a.B) select_dispatch<1, SelectScratch>(a, b, scratch[wave]);
 }
 // two utterances per block: the candidate arrays of this form are larger
 __global__ __launch_bounds__(128) void k_select_pairs(SelectArgs a) {
@@ -691,11 +691,11 @@ __global__ __launch_bounds__(128) void k_select_pairs(SelectArgs a) {
   if (b < a.B) select_dispatch<3, SelectScratchPairs>(a, b, scratch[wave]);
 }
 __global__ __launch_bounds__(256) void k_select_wide(SelectArgs a) {
-  __shared__ SelectScratchWide scratch[4];
+  __shared__ SelectScratch scratch[4];
   if (*reinterpret_cast<volatile int *>(a.done)) return;
   const int wave = threadIdx.x >> 6;
   const int b = blockIdx.x * 4 + wave;
-  if (b < a.B) select_dispatch<2, SelectScratchWide>(a, b, scratch[wave]);
+  if (b < a.B) select_dispatch<2, SelectScratch>(a, b, scratch[wave]);
 }
 
 // Beams too wide for the in-kernel forms (9 to 16) on the fused path, where the selection has a launch of its own:
@@ -713,7 +713,7 @@ constexpr int kMergeHeads = 8, kMergeCap = 128;
 
 template <int FORMS>  // 4, or 12 / 16 on a plain RNN-T (see select_dispatch)
 __global__ __launch_bounds__(64 * kMaxBeam) void k_utt_merge_select(MergeSelectArgs a) {
-  __shared__ SelectScratchWide scratch;
+  __shared__ SelectScratch scratch;
   __shared__ uint64_t l_cand[kMaxBeam * kMaxBeam];
   __shared__ float l_max[kMaxBeam], l_sum[kMaxBeam], l_zs[kMaxBeam * 9];
   __shared__ uint64_t surv[kMaxBeam][kMergeCap];
@@ -818,7 +818,7 @@ __global__ __launch_bounds__(64 * kMaxBeam) void k_utt_merge_select(MergeSelectA
     }
   }
   __syncthreads();
-  if (wave == 0) select_dispatch<FORMS, SelectScratchWide>(a.sel, b, scratch, CandView{l_cand, l_max, l_sum, l_zs, b * K});
+  if (wave == 0) select_dispatch<FORMS, SelectScratch>(a.sel, b, scratch, CandView{l_cand, l_max, l_sum, l_zs, b * K});
 }
 
 // ---------------------------------------------------------------------------

@@ -1554,7 +1554,7 @@ __device__ __forceinline__ void res_selector(ResBlock k, int sel, float *lds) {
   const int K = a0.K, V = a0.V, lane = threadIdx.x & 63, upc = a0.upc;
   const bool has_lm = a0.has_lm != 0, late_lm = has_lm && !a0.sel.lm_early;
   ResSelLds &L = *reinterpret_cast<ResSelLds *>(lds);
-  SelectScratchWide *scratch = reinterpret_cast<SelectScratchWide *>(lds + (sizeof(ResSelLds) + 15) / 16 * 4);
+  SelectScratch *scratch = reinterpret_cast<SelectScratch *>(lds + (sizeof(ResSelLds) + 15) / 16 * 4);
   k.word = reinterpret_cast<uint64_t *>(scratch + upc) + k.wave * a0.NT * kResSlot;
   float *lm_rows = reinterpret_cast<float *>(reinterpret_cast<uint64_t *>(scratch + upc) + kResWaves * a0.NT * kResSlot);
   const int u0 = sel * upc, nu = min(upc, k.nu - u0);  // the block's utterances of the group (none: nu <= 0)
@@ -1563,7 +1563,7 @@ __device__ __forceinline__ void res_selector(ResBlock k, int sel, float *lds) {
   ResidentSelect rs{};
   if (k.wave < nu) {  // the wave that selects for utterance u0 + wave
     const int u = u0 + k.wave;
-    SelectScratchWide &s = scratch[k.wave];
+    SelectScratch &s = scratch[k.wave];
     if (lane < K) {
       s.score[lane] = lane == 0 ? 0.0 : -INFINITY;
       s.t[lane] = s.sym[lane] = s.len[lane] = 0;
@@ -1610,9 +1610,9 @@ __device__ __forceinline__ void res_selector(ResBlock k, int sel, float *lds) {
         if (lane < K) res_store(k.local, rs.words + lane, slot_word(step, 1, u * K + lane, -1, 0));
       } else {
         const CandView cv{L.cand + k.wave * K * K, L.smax + k.wave * K, L.ssum + k.wave * K, L.zs + k.wave * K * (1 + a.sel.ND), b * K};
-        if constexpr (KC == 4) select_utterance<16, 1, 4, false, false, SelectScratchWide, true, PLAIN, false, true>(a.sel, b, scratch[k.wave], cv, &rs);
-        else if constexpr (KC == 8) select_utterance<8, 1, 8, false, false, SelectScratchWide, true, PLAIN, false, true>(a.sel, b, scratch[k.wave], cv, &rs);
-        else select_utterance<4, 1, 16, false, false, SelectScratchWide, true, PLAIN, false, true>(a.sel, b, scratch[k.wave], cv, &rs);
+        if constexpr (KC == 4) select_utterance<16, 1, 4, false, false, SelectScratch, true, PLAIN, false, true>(a.sel, b, scratch[k.wave], cv, &rs);
+        else if constexpr (KC == 8) select_utterance<8, 1, 8, false, false, SelectScratch, true, PLAIN, false, true>(a.sel, b, scratch[k.wave], cv, &rs);
+        else select_utterance<4, 1, 16, false, false, SelectScratch, true, PLAIN, false, true>(a.sel, b, scratch[k.wave], cv, &rs);
         rs.finished = __builtin_amdgcn_readfirstlane(rs.finished);
       }
     }

@@ -62,9 +62,8 @@ __device__ __forceinline__ float logaddexp_f(float a, float b) {
 }
 
 // LDS scratch of one wave while it handles one utterance
-template <int CAND, int STAIR = 64>
+template <int CAND>
 struct SelectScratchT {
-  static constexpr int kStair = STAIR;  // candidates the staircase form of the ranking can hold (64 per lane pass)
   double score[kMaxBeam];
   double rc_val[CAND];
   double rc_key[CAND];  // early pruning only: what the candidates are ranked by
@@ -77,17 +76,14 @@ struct SelectScratchT {
   int advt[kMaxBeam], advb[kMaxBeam];
   int rc_flat[CAND];
   int sel_flat[kMaxBeam];
-  // staircase form of the ranking (beams 8 .. 10): per hypothesis the place of blank in its sorted list, its head,
-  // the order of the lists by their heads; then the K (K + 1) / 2 candidates that can still be among the Beam best
-  double head_val[kMaxBeam], st_key[STAIR + 8];
-  int head_flat[kMaxBeam], pos_blank[kMaxBeam], ord[kMaxBeam], st_flat[STAIR + 8], st_src[STAIR];
+  // more than 64 candidates: those that can be among the Beam best (and what the ranking reads beyond them)
+  double top_key[64 + 8];
+  int top_flat[64 + 8], top_src[64];
   int n_t[kMaxBeam], n_sym[kMaxBeam], n_len[kMaxBeam], n_last[kMaxBeam], n_live[kMaxBeam];
   uint32_t n_hash[kMaxBeam];
 };
 // K (K + 1) candidates per utterance: K tokens and blank / stay of every hypothesis
 typedef SelectScratchT<kMaxBeam * (kMaxBeam + 1)> SelectScratch;
-// the same with room for the staircase of beams up to 16 (16 * 17 / 2 = 136 candidates, three per lane)
-typedef SelectScratchT<kMaxBeam * (kMaxBeam + 1), 192> SelectScratchWide;
 // TDT with every (symbol, duration) pair as a candidate: K (K + 1) ND of them, for beams up to 8
 constexpr int kPairsMaxBeam = 8;
 typedef SelectScratchT<kPairsMaxBeam * (kPairsMaxBeam + 1) * 8> SelectScratchPairs;
@@ -142,51 +138,6 @@ __device__ __forceinline__ int rank_by_counting(const double *keys, const int *f
   return rank;
 }
 
-// The same for OWN candidates per lane (lane, lane + 64, ..): one pass over the candidates serves them all.
-template <int OWN>
-__device__ __forceinline__ void rank_by_counting_n(const double *keys, const int *flats, int cnt, const double (&mv)[OWN],
-                                                   const int (&mf)[OWN], int (&rank)[OWN]) {
-  int ge[OWN];
-#pragma unroll
-  for (int o = 0; o < OWN; ++o) ge[o] = 0;
-  for (int c0 = 0; c0 < cnt; c0 += 8) {
-    double cv[8];
-#pragma unroll
-    for (int q = 0; q < 8; ++q) cv[q] = keys[c0 + q];
-#pragma unroll
-    for (int q = 0; q < 8; ++q)
-#pragma unroll
-      for (int o = 0; o < OWN; ++o) ge[o] += (int)(cv[q] >= mv[o]);
-  }
-  int F = 0, tot = 0;
-#pragma unroll
-  for (int o = 0; o < OWN; ++o) {
-    const bool finite = mv[o] > -INFINITY;
-    F += __popcll(__ballot(finite));
-    tot += finite ? ge[o] : 0;
-  }
-  if (wave_sum_i(tot) == F * (F + 1) / 2) {
-#pragma unroll
-    for (int o = 0; o < OWN; ++o) rank[o] = ge[o] - 1;
-    return;
-  }
-#pragma unroll
-  for (int o = 0; o < OWN; ++o) rank[o] = 0;
-  for (int c0 = 0; c0 < cnt; c0 += 8) {
-    double cv[8];
-    int cf[8];
-#pragma unroll
-    for (int q = 0; q < 8; ++q) {
-      cv[q] = keys[c0 + q];
-      cf[q] = flats[c0 + q];
-    }
-#pragma unroll
-    for (int q = 0; q < 8; ++q)
-#pragma unroll
-      for (int o = 0; o < OWN; ++o) rank[o] += comes_before_count(cv[q], cf[q], mv[o], mf[o]);
-  }
-}
-
 // Hand-over stores.  Blocks on one XCD share its L2: a plain store leaves the data there, and a device-coherent load finds it
 // there (such a load passes by the L1 but not by the L2: 107 ns, like any other that the L2 answers).  Across XCDs the store has
 // to be written through, which takes longer to be seen and to be acknowledged.  (One word from block to block and back, per
@@ -208,6 +159,64 @@ __device__ __forceinline__ void res_store_pair(bool local, uint64_t *p, int seco
 __device__ __forceinline__ void res_store16(bool local, float *p, floatx4 v) {
   if (local) asm volatile("global_store_dwordx4 %0, %1, off" ::"v"(p), "v"(v) : "memory");
   else store16_through(p, v);
+}
+
+// The Beam best of more than 64 candidates (beams from 8 on), candidate r * (K + 1) + j of hypothesis r, tokens (best first) and then
+// blank.  The K-th largest of a few candidates is a lower bound of the K-th largest of all: with each hypothesis' two best tokens and
+// its blank (a lane each) few more than K candidates reach it, and those are ranked against each other.  false: more than 64 do.
+// (Ranking the K (K + 1) / 2 candidates that the order of the sorted lists leaves took 4.5 us at beam 12 and 2.0 at beam 8.)
+template <class Scratch>
+__device__ __forceinline__ bool rank_best(Scratch &s, const double *rank_of, int K, int n) {
+  const int lane = threadIdx.x & 63, first = 3 * K;
+  {
+    const int r = (171 * lane) >> 9, j = lane - 3 * r;  // lane / 3
+    const double v = lane < first ? rank_of[r * (K + 1) + (j == 2 ? K : j)] : -INFINITY;
+    s.top_key[lane] = v;
+    wave_sync();
+    int ge = 0;  // of these, not below mine
+    for (int c0 = 0; c0 < first; c0 += 8) {
+      double cv[8];
+#pragma unroll
+      for (int q = 0; q < 8; ++q) cv[q] = s.top_key[c0 + q];
+#pragma unroll
+      for (int q = 0; q < 8; ++q) ge += (int)(cv[q] >= v);
+    }
+    ge = v > -INFINITY && ge >= K ? ge : 64;
+    int least = group_min_i<16>(ge);
+    least = min(min(__builtin_amdgcn_readlane(least, 0), __builtin_amdgcn_readlane(least, 16)),
+                min(__builtin_amdgcn_readlane(least, 32), __builtin_amdgcn_readlane(least, 48)));
+    const double tau = least < 64 ? readlane_d(v, __builtin_ctzll(__ballot(ge == least))) : -INFINITY;
+    wave_sync();
+    int total = 0;
+    for (int c0 = 0; c0 < n; c0 += 64) {
+      const int c = c0 + lane;
+      const double x = rank_of[c < n ? c : 0];
+      const bool in = c < n && x > -INFINITY && x >= tau;
+      const unsigned long long mask = __ballot(in);
+      const int pos = total + __builtin_amdgcn_mbcnt_hi((uint32_t)(mask >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)mask, 0));
+      if (in && pos < 64) {
+        s.top_key[pos] = x;
+        s.top_flat[pos] = s.rc_flat[c];
+        s.top_src[pos] = c;
+      }
+      total += __popcll(mask);
+    }
+    if (total > 64) return false;
+    if (lane < 8) {  // (the ranking reads in eights)
+      s.top_key[total + lane] = -INFINITY;
+      s.top_flat[total + lane] = 0x7fffffff;
+    }
+    wave_sync();
+    const bool mine = lane < total;
+    const double mv = mine ? s.top_key[lane] : -INFINITY;
+    const int mf = mine ? s.top_flat[lane] : 0x7fffffff;
+    const int rank = rank_by_counting(s.top_key, s.top_flat, total, mv, mf);
+    if (mine && rank < K) {
+      s.sel_val[rank] = s.rc_val[s.top_src[lane]];
+      s.sel_flat[rank] = mf;
+    }
+  }
+  return true;
 }
 
 // How the resident loop (kernels_resident.h) calls the selection: the hypotheses' state stays in the scratch from one step
@@ -667,73 +676,8 @@ __device__ __forceinline__ void select_utterance(const SelectArgs &a, int b, Scr
         s.sel_val[rank[q]] = s.rc_val[lane + 64 * q];
         s.sel_flat[rank[q]] = mf[q];
       }
-  } else if (!PAIRS && KMAX > 7 && K * (K + 1) / 2 <= Scratch::kStair) {
-    // More than 64 candidates.  The candidates of one hypothesis are a sorted list: its tokens come
-    // best first (the ranking value grows with the key) and blank / stay has its place among them.  With the lists
-    // ordered by their heads, the entry at place p of the list of order o has at least p + o candidates ahead of it,
-    // so only the K (K + 1) / 2 entries with p + o < K can be among the Beam best, and an entry's rank among those
-    // is its rank among all whenever that is below K.  One to three per lane, and the counting form applies.
-    if (lane < K) {
-      const int base = lane * (K + 1);
-      const double bv = rank_of[base + K];
-      int pos = 0;
-#pragma unroll
-      for (int j = 0; j < KMAX; ++j) {  // (reads past the K tokens stay inside the array and are not counted)
-        const double tv = rank_of[base + j];
-        pos += (int)(j < K) & (int)(tv > -INFINITY) & (int)(tv >= bv);  // (equal values: the token comes first)
-      }
-      s.pos_blank[lane] = pos;
-      s.head_val[lane] = pos == 0 ? bv : rank_of[base];
-      s.head_flat[lane] = pos == 0 ? s.rc_flat[base + K] : s.rc_flat[base];
-    }
-    wave_sync();
-    if (lane < K) {
-      const double hv = s.head_val[lane];
-      const int hf = s.head_flat[lane];
-      int o = 0;
-#pragma unroll
-      for (int r = 0; r < KMAX; ++r) o += (int)(r < K) & comes_before_count(s.head_val[r], s.head_flat[r], hv, hf);
-      s.ord[lane] = o;
-    }
-    wave_sync();
-    const unsigned inv = 65536u / (unsigned)(K + 1) + 1u;  // c / (K + 1) for c < 272 without a division per lane
-    for (int c = lane; c < n; c += 64) {
-      const int r = (int)(((unsigned)c * inv) >> 16), j = c - r * (K + 1);
-      const int pb = s.pos_blank[r], o = s.ord[r];
-      const int p = j == K ? pb : (j < pb ? j : j + 1);
-      if (p + o < K) {
-        const int slot = o * K - o * (o - 1) / 2 + p;
-        s.st_key[slot] = rank_of[c];
-        s.st_flat[slot] = s.rc_flat[c];
-        s.st_src[slot] = c;
-      }
-    }
-    const int nn = K * (K + 1) / 2;
-    if (lane < 8) {  // (as above: the counting loop reads in eights)
-      s.st_key[nn + lane] = -INFINITY;
-      s.st_flat[nn + lane] = 0x7fffffff;
-    }
-    wave_sync();
-    // (candidates a lane owns: as many as the form's widest beam needs and the scratch holds)
-    constexpr int kNeed = (KMAX * (KMAX + 1) / 2 + 63) / 64, kHave = Scratch::kStair / 64;
-    constexpr int OWN = kNeed < kHave ? kNeed : kHave;
-    double mv[OWN];
-    int mf[OWN], rank[OWN];
-#pragma unroll
-    for (int o = 0; o < OWN; ++o) {
-      const int slot = lane + 64 * o;
-      mv[o] = slot < nn ? s.st_key[slot] : -INFINITY;
-      mf[o] = slot < nn ? s.st_flat[slot] : 0x7fffffff;
-      rank[o] = K;
-    }
-    if (OWN == 1 || nn <= 64) rank[0] = rank_by_counting(s.st_key, s.st_flat, nn, mv[0], mf[0]);
-    else rank_by_counting_n<OWN>(s.st_key, s.st_flat, nn, mv, mf, rank);
-#pragma unroll
-    for (int o = 0; o < OWN; ++o)
-      if (mv[o] > -INFINITY && rank[o] < K) {
-        s.sel_val[rank[o]] = s.rc_val[s.st_src[lane + 64 * o]];
-        s.sel_flat[rank[o]] = mf[o];
-      }
+  } else if (!PAIRS && KMAX > 7 && rank_best(s, rank_of, K, n)) {
+    // (beams from 8 on)
   } else {
     double last_v = INFINITY;
     int last_i = -1;
