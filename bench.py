@@ -27,6 +27,7 @@ sys.path.insert(0, ROOT)
 
 PEAK_FP32_MFMA_TFLOPS = 157.3  # MI355X, dense fp32 matrix
 PEAK_BF16_MFMA_TFLOPS = 2500.0
+PEAK_SPLIT_MFMA_TFLOPS = 2500.0 / 3  # float32 products on operands split into two float16: three 16-bit ones for each
 PEAK_HBM_GBS = 8000.0
 
 LOOP_KERNELS = ("k_step_main", "k_select", "k_lstm_pointwise", "k_pred_proj", "k_lm_rows", "k_joint_big", "k_row_select",
@@ -118,8 +119,9 @@ def kernel_bound(name: str, c: dict) -> tuple:
     everything else against HBM."""
     if name == "k_joint_big":
         return "mfma", PEAK_BF16_MFMA_TFLOPS, "TFLOP/s"
-    if name in ("k_step_main", "k_pred_proj"):  # the recurrent product (most of the launch's FLOPs) is float32 always
-        return "mfma", PEAK_FP32_MFMA_TFLOPS, "TFLOP/s"
+    if name in ("k_step_main", "k_pred_proj", "k_decode_resident"):
+        # (the recurrent product, most of the FLOPs, of bf16-joint models multiplies in float32)
+        return "mfma", PEAK_FP32_MFMA_TFLOPS if c["prec"] == "bf16" else PEAK_SPLIT_MFMA_TFLOPS, "TFLOP/s"
     if name.startswith("k_gemm_tiled"):
         return "mfma", PEAK_BF16_MFMA_TFLOPS if c["prec"] == "bf16" else PEAK_FP32_MFMA_TFLOPS, "TFLOP/s"
     return "hbm", PEAK_HBM_GBS, "GB/s"
@@ -209,7 +211,7 @@ def measure(S, A, torch, cid: int, variant: str, steps: int, warmup: int, args, 
     bound, peak, unit = kernel_bound(dom, c)
     work = kernel_flops(dom, c, M, B, T) if bound == "mfma" else kernel_bytes(dom, c, M, B, T, K, n_steps)
     achieved = work / (loop[dom]["avg_us"] * 1e-6) / (1e12 if bound == "mfma" else 1e9)
-    roofline = dict(kernel=dom, bound=bound, achieved=round(achieved, 3), peak=peak, unit=unit,
+    roofline = dict(kernel=dom, bound=bound, achieved=round(achieved, 3), peak=round(peak, 1), unit=unit,
                     frac=round(achieved / peak, 5), traffic=None, avg_us=loop[dom]["avg_us"],
                     timing="HIP events around each plain launch (holds the dispatch latency after the previous command)")
     roofline["flops_per_launch" if bound == "mfma" else "bytes_per_launch"] = work
@@ -231,8 +233,9 @@ def measure(S, A, torch, cid: int, variant: str, steps: int, warmup: int, args, 
         work = (kernel_flops("k_step_main", c, M, B, T) + kernel_flops("k_pred_proj", c, M, B, T)) / M * rows
         ach = work / (gpu_ms * 1e-3) / 1e12
         launches = roofline
-        roofline = dict(kernel="k_decode_resident", bound="mfma", achieved=round(ach, 3), peak=PEAK_FP32_MFMA_TFLOPS,
-                        unit="TFLOP/s", frac=round(ach / PEAK_FP32_MFMA_TFLOPS, 5), traffic=None,
+        bound, peak, unit = kernel_bound("k_decode_resident", c)
+        roofline = dict(kernel="k_decode_resident", bound=bound, achieved=round(ach, 3), peak=round(peak, 1), unit=unit,
+                        frac=round(ach / peak, 5), traffic=None,
                         avg_us=round(gpu_ms * 1e3, 1), us_per_step=round(gpu_ms * 1e3 / max(n_steps, 1), 3),
                         timing="HIP events around the whole decode, with encoder projection and back-trace",
                         flops_per_launch=work, per_step_launches=launches)
