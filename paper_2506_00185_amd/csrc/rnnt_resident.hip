@@ -143,19 +143,21 @@ bool assign_tiles(const rnnt_config_t &c, int n_blocks, std::vector<ResTab> &tab
   return true;
 }
 
-// Decoders that fit the loop and gain nothing from it: narrow ones, whose per-step launches are short, with several tiles of slots
-// or wide beams, whose selection takes longer here.  Both sides timed in turn at widths 64 to 640 (time of the per-step
-// launches over the loop's; 640-wide LSTM decoders: 1.07 and more at every shape tried, up to three tiles).
+// Decoders that stay with the per-step launches although they fit the loop: narrow ones, whose per-step launches are short, with
+// several tiles of slots or wide beams, whose selection takes longer here.  Both sides timed in turn, time of the per-step launches
+// over the loop's.  LSTM decoders wider than 192: 1.01 and more at each of 250 shapes of two and three tiles (256 to 512 wide, V = 29
+// to 1000, beams 5 to 16, LM and TDT among them; means 1.33 in float32, 1.23 with the bf16 joint); 640 wide 1.07 and more.
 bool per_step_is_faster(const rnnt_config_t &c, int B, int K, int n_tiles) {
   const bool bf = c.prec == RNNT_BF16_JOINT;
-  if (c.pred != RNNT_PRED_LSTM)  // 64 wide 0.85 to 1.10, most below 1; bf16 at one utterance: 320 wide 0.88 to 1.03, 576 0.96 to 1.08
+  if (c.pred != RNNT_PRED_LSTM)  // bf16, one utterance, up to 320 wide: 0.96 to 1.20.  Others up to 128 wide: 1.08 to 1.53, not moved yet
     return K > 8 && (c.H <= 128 || (bf && B == 1 && c.H <= 320));
-  if (c.H == 640 && c.P == 640) return false;
-  // float32, three tiles: 0.79 to 1.14 (95 shapes, mean 0.93), except large vocabularies at beams up to 8 (1.0 to 1.18)
-  if (!bf && n_tiles == 3 && !(c.V > 512 && K <= 8)) return true;
-  // 64 to 320 wide, V = 700 and 1000: 0.85 to 0.98; V = 500: float32 0.92 to 0.96 (beam 16: 1.01 to 1.06), bf16 0.90 to 1.16;
-  // V = 260 and less: 0.99 to 1.22
-  return std::max(c.H, c.P) <= 320 && n_tiles > 1 && K > 8 && c.V > (bf ? 512 : 384);
+  if (std::max(c.H, c.P) <= 192) {
+    // float32, three tiles: V = 100 0.94 to 1.01, V = 500 at beams from 9 on 0.88 to 1.01 (at smaller beams 1.13 to 1.22)
+    if (!bf && n_tiles == 3 && !(c.V > 512 && K <= 8)) return true;
+    // two tiles: V = 450 0.97 to 1.84, V > 512 1.00 to 1.34; three, float32, V = 1000: 1.05 to 1.07
+    return n_tiles > 1 && K > 8 && c.V > (bf ? 512 : 384);
+  }
+  return false;
 }
 
 Plan make_plan(const Resident &r, const rnnt_config_t &c, int B, int K, bool has_lm, bool fold) {

@@ -103,6 +103,21 @@ def test_loop_that_decodes_a_batch_on_either_side_of_a_rule(loop, kw):
             np.testing.assert_array_equal(r[key], ref[key])
 
 
+W256 = dict(H=256, P=256, E=64, D=32)
+
+
+@pytest.mark.parametrize("loop,kw", [
+    ("resident", dict(B=25, beam=9, V=512, **W256)), ("resident", dict(B=17, beam=12, V=29, **W256)),     # three tiles, float32
+    ("resident", dict(B=33, beam=8, V=90, **dict(W256, H=512, P=512))), ("resident", dict(B=9, beam=9, V=600, **W256)),
+    ("resident", dict(B=25, beam=10, V=1000, prec="bf16", **dict(W256, H=320, P=320))),
+    ("resident", dict(B=9, beam=9, V=700, **dict(W256, P=192))), ("graph", dict(B=9, beam=9, V=700, **dict(W192, P=128))),
+    ("graph", dict(B=1, beam=9, V=90, prec="bf16", **dict(W256, H=320), **ST, ctx=1)),
+    ("resident", dict(B=1, beam=9, V=90, prec="bf16", **dict(W256, H=384), **ST, ctx=1)),
+])
+def test_loop_of_wide_and_narrow_decoders_with_several_tiles(loop, kw):
+    test_loop_that_decodes_a_batch_on_either_side_of_a_rule(loop, kw)
+
+
 @pytest.mark.parametrize("prune,rule,beam,B,more", [("late", 4, 8, 9, {}), ("early", 3, 4, 17, {}), ("late", 3, 11, 4, {}),
                                                     ("late", 4, 6, 10, dict(ST, ctx=2)),
                                                     # up to four hypotheses of more than 512 tokens: two waves per row
