@@ -48,7 +48,10 @@ __device__ __forceinline__ void splitk_load(SplitKOperands<ITERS> &op, AL a_at, 
   }
 }
 
-constexpr int kFormSplit = 0, kFormBf16 = 1, kFormF32 = 2;
+// how splitk_mma multiplies: float32 or bfloat16 instructions (run time), or a split product (see split_f16) of weights with hidden
+// states, whose scale stays in the sums (see k_split_rows), or with activations of any size, a scale per hypothesis and slice.
+// (A template parameter: the registers of split operands would cost bf16-joint models occupancy, k_pred_proj<8, 10> 122 -> 150.)
+enum class Prod { kPlain, kSplitHidden, kSplitAct };
 
 // larger of a lane's value and that of the same column in the wave's other half
 __device__ __forceinline__ float max_of_halves(float m) {
@@ -58,77 +61,36 @@ __device__ __forceinline__ float max_of_halves(float m) {
 
 // matrix instructions of the wave's K slice, partial tile to LDS, block barrier.
 // fb: applied to each hypothesis-side operand just before use (ReLU).
-// form (uniform over the block): kFormBf16: both operands are rounded to bfloat16 (weights handed in are bf16 values already)
-// and two 8-k rounds at a time go through one bf16 matrix instruction; the accumulation stays float32.  kFormSplit: a split
-// product (see split_f16): weights as k_split_rows leaves them, ACT: activations of any size, a scale per hypothesis and
-// slice, else hidden states (whose scale stays in the sums, see k_split_rows).  kFormF32 (recurrent product of bf16-joint models):
-// float32 matrix instructions.
+// bf16 (uniform over the block; kPlain): both operands are rounded to bfloat16 (weights handed in are bf16 values already)
+// and two 8-k rounds at a time go through one bf16 matrix instruction, an eighth of the matrix-core time of the
+// eight float32 ones; the accumulation stays float32.
 // xw (ITERS > 0 only): this lane's k values of one more output row; the lane's part of that row's product with its
 // hypothesis goes into the spare float of its slot in red (extra_value() sums the parts).
-template <int WAVES, int ITERS, bool ACT, class AL, class BL, class FB>
+template <int WAVES, int ITERS, Prod PROD, class AL, class BL, class FB>
 __device__ __forceinline__ void splitk_mma(SplitKOperands<ITERS> &op, AL a_at, BL b_at, FB fb, int K, float *red,
-                                           int form, const float4 *xw = nullptr) {
+                                           int bf16 = 0, const float4 *xw = nullptr) {
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, half = lane >> 5;
   const int kw = K / WAVES;
   const float4 zero4 = make_float4(0.f, 0.f, 0.f, 0.f);
-  floatx16 acc = {0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0}, cor = acc;
-  if constexpr (ITERS > 0) {
-    if (!ACT && form == kFormF32) {
-#pragma unroll
-      for (int i = 0; i < ITERS; ++i) {
-        const float4 b = fb(op.b[i]);
-        acc = mfma32(op.a[i].x, b.x, acc);
-        acc = mfma32(op.a[i].y, b.y, acc);
-        acc = mfma32(op.a[i].z, b.z, acc);
-        acc = mfma32(op.a[i].w, b.w, acc);
-      }
-    } else if (form == kFormBf16) {
-#pragma unroll
-      for (int i = 0; i < ITERS; i += 2) {
-        const bool two = i + 1 < ITERS;
-        acc = mfma32_bf16_from_f32(op.a[i], two ? op.a[i + 1 < ITERS ? i + 1 : i] : zero4, fb(op.b[i]),
-                                   two ? fb(op.b[i + 1 < ITERS ? i + 1 : i]) : zero4, acc);
-      }
-    } else {
+  floatx16 acc = {0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0};
+  const int kbeg = wave * kw + 4 * half, kend = (wave + 1) * kw;
+  if constexpr (PROD != Prod::kPlain) {
+    constexpr bool ACT = PROD == Prod::kSplitAct;
+    floatx16 cor = acc;
+    float inv = 1.f, scale = kHidScale, m = 0.f;
+    auto larger = [&](float4 b) { m = fmaxf(m, fmaxf(fmaxf(b.x, b.y), fmaxf(b.z, b.w))); };
+    if constexpr (ITERS > 0) {
       float4 b[ITERS];
-      float m = 0.f;
 #pragma unroll
       for (int i = 0; i < ITERS; ++i) {
         b[i] = fb(op.b[i]);
-        if (ACT) m = fmaxf(m, fmaxf(fmaxf(b[i].x, b[i].y), fmaxf(b[i].z, b[i].w)));
+        if (ACT) larger(b[i]);
       }
-      float inv = 1.f;
-      const float scale = ACT ? split_scale(max_of_halves(m), inv) : kHidScale;
+      if (ACT) scale = split_scale(max_of_halves(m), inv);
       mfma32_split_rounds<ITERS>(op.a, b, scale, acc, cor);
-      acc += cor;
-      if (ACT) acc *= inv;
-    }
-  } else {
-    const int kbeg = wave * kw + 4 * half, kend = (wave + 1) * kw;
-    if (!ACT && form == kFormF32) {
-      for (int k = kbeg; k < kend; k += 8) {
-        const float4 a = a_at(k);
-        const float4 b = fb(b_at(k));
-        acc = mfma32(a.x, b.x, acc);
-        acc = mfma32(a.y, b.y, acc);
-        acc = mfma32(a.z, b.z, acc);
-        acc = mfma32(a.w, b.w, acc);
-      }
-    } else if (form == kFormBf16) {
-      for (int k = kbeg; k < kend; k += 16) {
-        const bool two = k + 8 < kend;
-        const int k2 = two ? k + 8 : k;
-        const float4 a0 = a_at(k), a1 = a_at(k2), b0 = fb(b_at(k)), b1 = fb(b_at(k2));
-        acc = mfma32_bf16_from_f32(a0, two ? a1 : zero4, b0, two ? b1 : zero4, acc);
-      }
     } else {
-      float inv = 1.f, scale = kHidScale;
       if constexpr (ACT) {
-        float m = 0.f;
-        for (int k = kbeg; k < kend; k += 8) {
-          const float4 b = fb(b_at(k));
-          m = fmaxf(m, fmaxf(fmaxf(b.x, b.y), fmaxf(b.z, b.w)));
-        }
+        for (int k = kbeg; k < kend; k += 8) larger(fb(b_at(k)));
         scale = split_scale(max_of_halves(m), inv);
       }
       for (int k = kbeg; k < kend; k += 32) {
@@ -142,8 +104,42 @@ __device__ __forceinline__ void splitk_mma(SplitKOperands<ITERS> &op, AL a_at, B
         }
         mfma32_split<4>(w, x, scale, acc, cor);
       }
-      acc += cor;
-      if (ACT) acc *= inv;
+    }
+    acc += cor;
+    if (ACT) acc *= inv;
+  } else if constexpr (ITERS > 0) {
+    if (bf16) {
+#pragma unroll
+      for (int i = 0; i < ITERS; i += 2) {
+        const bool two = i + 1 < ITERS;
+        acc = mfma32_bf16_from_f32(op.a[i], two ? op.a[i + 1 < ITERS ? i + 1 : i] : zero4, fb(op.b[i]),
+                                   two ? fb(op.b[i + 1 < ITERS ? i + 1 : i]) : zero4, acc);
+      }
+    } else {
+#pragma unroll
+      for (int i = 0; i < ITERS; ++i) {
+        const float4 b = fb(op.b[i]);
+        acc = mfma32(op.a[i].x, b.x, acc);
+        acc = mfma32(op.a[i].y, b.y, acc);
+        acc = mfma32(op.a[i].z, b.z, acc);
+        acc = mfma32(op.a[i].w, b.w, acc);
+      }
+    }
+  } else if (bf16) {
+    for (int k = kbeg; k < kend; k += 16) {
+      const bool two = k + 8 < kend;
+      const int k2 = two ? k + 8 : k;
+      const float4 a0 = a_at(k), a1 = a_at(k2), b0 = fb(b_at(k)), b1 = fb(b_at(k2));
+      acc = mfma32_bf16_from_f32(a0, two ? a1 : zero4, b0, two ? b1 : zero4, acc);
+    }
+  } else {
+    for (int k = kbeg; k < kend; k += 8) {
+      const float4 a = a_at(k);
+      const float4 b = fb(b_at(k));
+      acc = mfma32(a.x, b.x, acc);
+      acc = mfma32(a.y, b.y, acc);
+      acc = mfma32(a.z, b.z, acc);
+      acc = mfma32(a.w, b.w, acc);
     }
   }
   float *mine = red + (wave * 64 + lane) * kRedStride;
@@ -155,7 +151,7 @@ __device__ __forceinline__ void splitk_mma(SplitKOperands<ITERS> &op, AL a_at, B
 #pragma unroll
       for (int i = 0; i < ITERS; ++i) {
         float4 b = fb(op.b[i]);
-        if (form == kFormBf16) {  // (the weights are bf16 values already)
+        if (PROD == Prod::kPlain && bf16) {  // (the weights are bf16 values already)
           b.x = __uint_as_float(pack_bf16_rne(b.x, 0.f) << 16);
           b.y = __uint_as_float(pack_bf16_rne(b.y, 0.f) << 16);
           b.z = __uint_as_float(pack_bf16_rne(b.z, 0.f) << 16);
@@ -350,7 +346,7 @@ __global__ __launch_bounds__(256) void k_split_rows(float *W, int rows, int K, f
 // selection, so its blocks ride along in the launches that have idle compute units).
 struct RecurrentArgs {
   const float *Whh;    // k4-major [P][4P], gate rows re-ordered (NULL: no such blocks)
-  const float *unscale;  // [4P] where Whh is split, see k_split_rows, else null (bf16-joint models)
+  const float *unscale;  // SPLIT: [4P] scales of the rows of Whh, see k_split_rows
   const float *h;      // k4-major [P][Mp]
   float *R;            // [M][4P]
   int P, M, Mp;
@@ -358,7 +354,8 @@ struct RecurrentArgs {
 };
 constexpr int kRecGroup = 4;
 
-template <int WAVES, int ITERS>
+// SPLIT: Whh is split (k_split_rows)
+template <int WAVES, int ITERS, bool SPLIT>
 __device__ __forceinline__ void recurrent_tile(const RecurrentArgs &a, int tile, int m0, int done, float *red) {
   constexpr int LPH = 2 * WAVES, VPL = 32 / LPH;
   const int tid = threadIdx.x, lane = tid & 63, col = lane & 31;
@@ -373,9 +370,9 @@ __device__ __forceinline__ void recurrent_tile(const RecurrentArgs &a, int tile,
   const int j = tid / LPH, i0 = (tid % LPH) * VPL;
   float us[VPL];
 #pragma unroll
-  for (int q = 0; q < VPL; ++q) us[q] = a.unscale ? a.unscale[tile * 32 + i0 + q] : 1.f;
+  for (int q = 0; q < VPL; ++q) us[q] = SPLIT ? a.unscale[tile * 32 + i0 + q] : 1.f;
   if (done) return;
-  splitk_mma<WAVES, ITERS, false>(op, a_at, b_at, [](float4 v) { return v; }, a.P, red, a.unscale ? kFormSplit : kFormF32);
+  splitk_mma<WAVES, ITERS, SPLIT ? Prod::kSplitHidden : Prod::kPlain>(op, a_at, b_at, [](float4 v) { return v; }, a.P, red);
   const int m = m0 + j;
   if (m < a.M) {
 #pragma unroll
@@ -386,7 +383,7 @@ __device__ __forceinline__ void recurrent_tile(const RecurrentArgs &a, int tile,
 // The same for up to G slot tiles in a row (item `grp` of the tile's row: slot tiles grp * G ...): the 32 gate rows
 // stay in registers, and the slots of the next tile are requested before the matrix instructions of the current one
 // start, so that a block streams half as much per tile and streams while it multiplies.
-template <int WAVES, int ITERS, int G>
+template <int WAVES, int ITERS, bool SPLIT, int G>
 __device__ __forceinline__ void recurrent_tiles(const RecurrentArgs &a, int tile, int grp, int done, float *red) {
   static_assert(ITERS > 0, "every load of a slice in flight at once");
   constexpr int LPH = 2 * WAVES, VPL = 32 / LPH;
@@ -406,7 +403,7 @@ __device__ __forceinline__ void recurrent_tiles(const RecurrentArgs &a, int tile
   const int j = tid / LPH, i0 = (tid % LPH) * VPL;
   float us[VPL];
 #pragma unroll
-  for (int q = 0; q < VPL; ++q) us[q] = a.unscale ? a.unscale[tile * 32 + i0 + q] : 1.f;
+  for (int q = 0; q < VPL; ++q) us[q] = SPLIT ? a.unscale[tile * 32 + i0 + q] : 1.f;
   if (done) return;
   // one slot tile; G copies of this code, each with its register set known at compile time (a loop over g that can
   // end early is kept as a loop by the compiler, with the next tile's loads waited for one by one inside it).
@@ -423,8 +420,9 @@ __device__ __forceinline__ void recurrent_tiles(const RecurrentArgs &a, int tile
       }
     }
     __builtin_amdgcn_sched_barrier(0);  // the next tile's loads are under way before the first matrix instruction
-    floatx16 acc = {0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0}, cor = acc;
-    if (a.unscale) {
+    floatx16 acc = {0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0};
+    if constexpr (SPLIT) {
+      floatx16 cor = acc;
       mfma32_split_rounds<ITERS>(wa, hb[g & 1], kHidScale, acc, cor);
       acc += cor;
     } else {
@@ -459,8 +457,8 @@ __device__ __forceinline__ void recurrent_tiles(const RecurrentArgs &a, int tile
 struct MainArgs {
   // ---- joint role
   const float *pre;   // k4-major [H][Mp]: f_proj[b, t_m] + prediction projection of hypothesis m
-  const float *W;     // k4-major [H][n_chunks * 32] output layer, zero rows beyond V + 1 + ND; float32 models: split by k_split_rows
-  const float *W_plain, *w_unscale;  // float32 models: the same not split, and the scales of its rows (else W and null)
+  const float *W;     // k4-major [H][n_chunks * 32] output layer, zero rows beyond V + 1 + ND; SPLIT: split by k_split_rows
+  const float *W_plain, *w_unscale;  // the same not split; SPLIT: the scales of its rows
   const float *bias;  // [n_chunks * 32]
   const float *lm;    // [M, V] natural-log LM scores or NULL
   float lambda;
@@ -485,9 +483,10 @@ struct MainArgs {
 // so that the [M, V + 1] logits never reach memory (LPH = 2 * WAVES lanes share a hypothesis, each holds 32 / LPH
 // columns; the best K are found in K rounds of an LPH-lane arg-max).  Lists and statistics are written with
 // device-coherent stores.  red: the block's reduction buffer (WAVES * 64 * kRedStride floats).
-template <int WAVES, int ITERS, bool WIDE = false>
+template <int WAVES, int ITERS, bool SPLIT, bool WIDE = false>
 __device__ __forceinline__ void joint_tile(const MainArgs &a, int chunk, int m0, int rows, int done, float *red) {
   constexpr int LPH = 2 * WAVES, VPL = 32 / LPH;
+  constexpr Prod kProd = SPLIT ? Prod::kSplitAct : Prod::kPlain;
   const int tid = threadIdx.x, lane = tid & 63, col = lane & 31;
   const int n0 = chunk * 32;
   // (shifted by the tile's index: the blocks with a folded column finish last, and the one that completes a tile
@@ -515,14 +514,14 @@ __device__ __forceinline__ void joint_tile(const MainArgs &a, int chunk, int m0,
 #pragma unroll
         for (int i = 0; i < ITERS; ++i) xw[i] = *reinterpret_cast<const float4 *>(xp + (size_t)((kbeg + 8 * i) >> 2) * Np * 4);
         if (done) return;
-        splitk_mma<WAVES, ITERS, true>(op, a_at, b_at, fb, a.H, red, round_ops, xw);
+        splitk_mma<WAVES, ITERS, kProd>(op, a_at, b_at, fb, a.H, red, round_ops, xw);
       } else {
         if (done) return;
-        splitk_mma<WAVES, ITERS, true>(op, a_at, b_at, fb, a.H, red, round_ops);
+        splitk_mma<WAVES, ITERS, kProd>(op, a_at, b_at, fb, a.H, red, round_ops);
       }
     } else {
       if (done) return;
-      splitk_mma<WAVES, ITERS, true>(op, a_at, b_at, fb, a.H, red, round_ops);
+      splitk_mma<WAVES, ITERS, kProd>(op, a_at, b_at, fb, a.H, red, round_ops);
     }
   }
 
@@ -533,7 +532,7 @@ __device__ __forceinline__ void joint_tile(const MainArgs &a, int chunk, int m0,
   const int nz = 1 + a.ND;
   float us[VPL];
 #pragma unroll
-  for (int q = 0; q < VPL; ++q) us[q] = a.w_unscale ? a.w_unscale[n0 + i0 + q] : 1.f;
+  for (int q = 0; q < VPL; ++q) us[q] = SPLIT ? a.w_unscale[n0 + i0 + q] : 1.f;
   if (WIDE && folds && mvalid) {
     if (e == 0) store_agent(a.zs + (size_t)m * nz + fold_c, extra_value<WAVES>(red, j) + a.bias[a.V + fold_c]);
     if (fold_c == 0) {  // ... and the empty lists of the chunk that has no block now
@@ -615,7 +614,8 @@ __device__ __forceinline__ void joint_tile(const MainArgs &a, int chunk, int m0,
 // WIDE: the forms for 256 slots and more (folded blank / duration columns, recurrent blocks of several slot tiles);
 // an instantiation of their own, because their code costs the smaller shapes 0.2 us per launch when it is only there.
 // SEL: the selection forms in the tail (0: every in-kernel form; 5, 6: one form, see select_dispatch).
-template <int WAVES, int ITERS, bool TAIL = true, bool WIDE = false, int SEL = 0>
+// SPLIT: weights split (k_split_rows).
+template <int WAVES, int ITERS, bool SPLIT, bool TAIL = true, bool WIDE = false, int SEL = 0>
 __global__ __launch_bounds__(WAVES * 64, TAIL ? 1 : 16 / WAVES) void k_step_main(MainArgs a) {
   constexpr int kRedFloats = WAVES * 64 * kRedStride;
   constexpr int kScratchFloats = TAIL ? (int)((sizeof(SelectScratch) * WAVES + 3) / 4) : 1;
@@ -631,15 +631,15 @@ __global__ __launch_bounds__(WAVES * 64, TAIL ? 1 : 16 / WAVES) void k_step_main
   if (role == 1) {
     if constexpr (WIDE && ITERS > 0) {
       if (a.rec.group > 1) {
-        recurrent_tiles<WAVES, ITERS, kRecGroup>(a.rec, chunk, ty, done, red);
+        recurrent_tiles<WAVES, ITERS, SPLIT, kRecGroup>(a.rec, chunk, ty, done, red);
         return;
       }
     }
-    recurrent_tile<WAVES, ITERS>(a.rec, chunk, ty * 32, done, red);
+    recurrent_tile<WAVES, ITERS, SPLIT>(a.rec, chunk, ty * 32, done, red);
     return;
   }
 
-  joint_tile<WAVES, ITERS, WIDE>(a, chunk, ty * a.rpt, a.rpt, done, red);
+  joint_tile<WAVES, ITERS, SPLIT, WIDE>(a, chunk, ty * a.rpt, a.rpt, done, red);
   if (done) return;
 
   if constexpr (!TAIL) {
@@ -899,7 +899,7 @@ __device__ __forceinline__ void bump_step(int *step_base, int bump, volatile int
 // W_pred: k4-major [P][H]; h: k4-major [P][Mp]; f_proj: row-major [B * T, H].
 struct PredProjArgs {
   const float *Wp, *bias, *h, *f_proj;
-  const float *wp_unscale;  // float32 models: Wp is split, the scales of its rows (else null)
+  const float *wp_unscale;  // SPLIT: the scales of the rows of Wp
   const int *t, *lengths;
   float *pre;
   int M, Mp, K, T, P, H, round_ops;
@@ -930,7 +930,7 @@ __device__ __forceinline__ bool pred_proj_lm_block(const PredProjArgs &a) {
 }
 
 // One tile of the projection: 32 outputs of H (tile) x the slots [m0, m0 + 32).
-template <int WAVES, int ITERS>
+template <int WAVES, int ITERS, bool SPLIT>
 __device__ __forceinline__ void pred_proj_tile(const PredProjArgs &a, int tile, int m0, int done_flag, float *red) {
   constexpr int LPH = 2 * WAVES, VPL = 32 / LPH;
   const int tid = threadIdx.x, lane = tid & 63, col = lane & 31;
@@ -966,8 +966,8 @@ __device__ __forceinline__ void pred_proj_tile(const PredProjArgs &a, int tile, 
   }
   float us[VPL];
 #pragma unroll
-  for (int q = 0; q < VPL; ++q) us[q] = a.wp_unscale ? a.wp_unscale[o0 + q] : 1.f;
-  splitk_mma<WAVES, ITERS, false>(op, a_at, b_at, fb, a.P, red, round_ops);
+  for (int q = 0; q < VPL; ++q) us[q] = SPLIT ? a.wp_unscale[o0 + q] : 1.f;
+  splitk_mma<WAVES, ITERS, SPLIT ? Prod::kSplitHidden : Prod::kPlain>(op, a_at, b_at, fb, a.P, red, round_ops);
   if (me >= a.M) return;
 #pragma unroll
   for (int q = 0; q < VPL; ++q)
@@ -975,7 +975,7 @@ __device__ __forceinline__ void pred_proj_tile(const PredProjArgs &a, int tile, 
 }
 
 // LM: the launch carries LM rows (an instantiation of its own: the test for them costs the plain launch 0.26 us)
-template <int WAVES, int ITERS, bool LM = false>
+template <int WAVES, int ITERS, bool SPLIT, bool LM = false>
 __global__ __launch_bounds__(WAVES * 64) void k_pred_proj(PredProjArgs a) {
   __shared__ float red[WAVES * 64 * kRedStride];
   if constexpr (LM) {
@@ -986,11 +986,11 @@ __global__ __launch_bounds__(WAVES * 64) void k_pred_proj(PredProjArgs a) {
   if (role < 0) return;
   const int done_flag = *reinterpret_cast<const volatile int *>(a.done);
   if (role == 1) {
-    recurrent_tile<WAVES, ITERS>(a.rec, tile, mtile * 32, done_flag, red);
+    recurrent_tile<WAVES, ITERS, SPLIT>(a.rec, tile, mtile * 32, done_flag, red);
     return;
   }
   if (!done_flag && a.bump && tile == 0 && mtile == 0 && threadIdx.x == 0) bump_step(a.step_base, a.bump, a.h_progress);
-  pred_proj_tile<WAVES, ITERS>(a, tile, mtile * 32, done_flag, red);
+  pred_proj_tile<WAVES, ITERS, SPLIT>(a, tile, mtile * 32, done_flag, red);
 }
 
 // The same projection with the contraction split in two across blocks, for launches that would leave half the
@@ -999,7 +999,7 @@ __global__ __launch_bounds__(WAVES * 64) void k_pred_proj(PredProjArgs a) {
 // on which block comes first.  Half the operands and half the matrix instructions per block: 3.0 instead of 4.8 us.
 // No recurrent tiles ride in this launch (they would set its duration); the main launch takes them all.
 // ITERS = P / 2 / WAVES / 8.
-template <int WAVES, int ITERS, bool LM = false>
+template <int WAVES, int ITERS, bool SPLIT, bool LM = false>
 __global__ __launch_bounds__(WAVES * 64) void k_pred_proj_half(PredProjArgs a) {
   __shared__ float red[WAVES * 64 * kRedStride];
   constexpr int LPH = 2 * WAVES, VPL = 32 / LPH;
@@ -1042,7 +1042,7 @@ __global__ __launch_bounds__(WAVES * 64) void k_pred_proj_half(PredProjArgs a) {
   }
   float us[VPL];
 #pragma unroll
-  for (int q = 0; q < VPL; ++q) us[q] = a.wp_unscale ? a.wp_unscale[o0 + q] : 1.f;
+  for (int q = 0; q < VPL; ++q) us[q] = SPLIT ? a.wp_unscale[o0 + q] : 1.f;
   __builtin_amdgcn_sched_barrier(0);
   // (behind every load of the block, whose waits then do not include these stores; they are on their way while the
   // operands come in and are multiplied)
@@ -1050,7 +1050,7 @@ __global__ __launch_bounds__(WAVES * 64) void k_pred_proj_half(PredProjArgs a) {
        i += 4 * WAVES * 64 * a.map.a_tiles * a.map.a_m)
     store16_through(a.pre_clear + i, floatx4{0.f, 0.f, 0.f, 0.f});
   __builtin_amdgcn_sched_barrier(0);
-  splitk_mma<WAVES, ITERS, false>(op, a_at, b_at, fb, a.P / 2, red, round_ops);
+  splitk_mma<WAVES, ITERS, SPLIT ? Prod::kSplitHidden : Prod::kPlain>(op, a_at, b_at, fb, a.P / 2, red, round_ops);
   if (a.bump && tile == 0 && item == 0 && tid == 0) bump_step(a.step_base, a.bump, a.h_progress);
   if (me >= a.M) return;
 #pragma unroll

@@ -97,7 +97,7 @@ __device__ __forceinline__ void tile_done(int *counter) {
   if (threadIdx.x == 0) __hip_atomic_fetch_add(counter, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 
-template <int WAVES, int ITERS>
+template <int WAVES, int ITERS, bool SPLIT>
 __global__ __launch_bounds__(WAVES * 64, 1) void k_decode_persistent(PersistArgs a) {
   constexpr int kRedFloats = WAVES * 64 * kRedStride;
   constexpr int kScratchFloats = (int)((sizeof(SelectScratch) * WAVES + 3) / 4);
@@ -162,11 +162,11 @@ __global__ __launch_bounds__(WAVES * 64, 1) void k_decode_persistent(PersistArgs
     rec.h = a.h[cur];
     if (rank < n_pp) {
       for (int tile = rank; tile < n_pp; tile += n_blocks) {
-        pred_proj_tile<WAVES, ITERS>(pp, tile, m0, 0, red);
+        pred_proj_tile<WAVES, ITERS, SPLIT>(pp, tile, m0, 0, red);
         tile_done(&grp->pp_done);
       }
     } else if (rec_early < n_rec) {
-      recurrent_tile<WAVES, ITERS>(rec, rec_early, m0, 0, red);
+      recurrent_tile<WAVES, ITERS, SPLIT>(rec, rec_early, m0, 0, red);
       __syncthreads();
     }
     // ---- A: joint tiles need every projection tile
@@ -174,12 +174,12 @@ __global__ __launch_bounds__(WAVES * 64, 1) void k_decode_persistent(PersistArgs
     for (int chunk = rank; chunk < n_chunks; chunk += n_blocks) {
       // (block 0 selects: it takes one tile only, its further ones go to block 1)
       if (rank == 0 && chunk > 0) break;
-      joint_tile<WAVES, ITERS>(a.main, chunk, m0, rows, 0, red);
+      joint_tile<WAVES, ITERS, SPLIT>(a.main, chunk, m0, rows, 0, red);
       tile_done(&grp->joint_done);
     }
     if (rank == 1)
       for (int chunk = n_blocks; chunk < n_chunks; chunk += n_blocks) {  // block 0's further tiles
-        joint_tile<WAVES, ITERS>(a.main, chunk, m0, rows, 0, red);
+        joint_tile<WAVES, ITERS, SPLIT>(a.main, chunk, m0, rows, 0, red);
         tile_done(&grp->joint_done);
       }
     if (rank == 0) {
@@ -197,7 +197,7 @@ __global__ __launch_bounds__(WAVES * 64, 1) void k_decode_persistent(PersistArgs
     } else {
       // the rest of R': tiles n_early .. n_rec - 1 go round the blocks 1 .. n_blocks - 1
       for (int tile = n_early + rank - 1; tile < n_rec; tile += n_blocks - 1) {
-        recurrent_tile<WAVES, ITERS>(rec, tile, m0, 0, red);
+        recurrent_tile<WAVES, ITERS, SPLIT>(rec, tile, m0, 0, red);
         __syncthreads();
       }
     }

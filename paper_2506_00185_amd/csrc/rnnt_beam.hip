@@ -173,6 +173,7 @@ struct rnnt_beam {
   // packed weights
   float *W_enc = nullptr, *b_enc = nullptr, *W_pred = nullptr, *b_pred = nullptr, *W_out = nullptr,
         *b_out = nullptr, *W_hh = nullptr, *hh_unscale = nullptr, *W_out_s = nullptr, *out_unscale = nullptr, *pred_unscale = nullptr, *G = nullptr, *tab = nullptr;
+  bool split = false;   // W_hh, W_pred and W_out_s are split (k_split_rows): float32 models
   // materialised-logits path (bf16 joint, large shapes)
   bool big = false;
   int Npad_big = 0, Hb = 0;  // padded extents of the bf16 operands: 256 columns, 64 k
@@ -343,6 +344,8 @@ int pack_weights(rnnt_beam *h, const rnnt_weights_t *w) {
   const rnnt_config_t &c = h->cfg;
   const int H = c.H, P = c.P, D = c.D, E = c.E, V = c.V, N = h->N;
   const bool bf = c.prec == RNNT_BF16_JOINT;
+  // (not for the bf16 joint: its rounding of the activations turns any other order of the sums into other near ties)
+  h->split = !bf;
   std::vector<float> tmp, out;
   std::vector<void *> staging;  // device buffers needed only until the folded tables have been computed
   int rc;
@@ -362,7 +365,7 @@ int pack_weights(rnnt_beam *h, const rnnt_weights_t *w) {
   if ((rc = upload(h, &d_wpred_rm, wpred))) return rc;
   staging.push_back(d_wpred_rm);
   if ((rc = upload(h, &h->W_pred, to_k4(wpred, H, P, H)))) return rc;
-  if (!bf && c.pred == RNNT_PRED_LSTM && (rc = split_rows(h, h->W_pred, H, P, kHidScale, &h->pred_unscale))) return rc;
+  if (h->split && c.pred == RNNT_PRED_LSTM && (rc = split_rows(h, h->W_pred, H, P, kHidScale, &h->pred_unscale))) return rc;
   if ((rc = download(h, bpred, w->b_pred, H))) return rc;
   if ((rc = upload(h, &h->b_pred, bpred))) return rc;
   // output layer, rows padded with zeros to whole 32-column chunks
@@ -370,7 +373,7 @@ int pack_weights(rnnt_beam *h, const rnnt_weights_t *w) {
   if (bf)
     for (auto &x : tmp) x = host_bf16_round(x);
   if ((rc = upload(h, &h->W_out, out = to_k4(tmp, N, H, h->n_chunks * 32)))) return rc;
-  if (!bf) {
+  if (h->split) {
     if ((rc = upload(h, &h->W_out_s, out))) return rc;
     if ((rc = split_rows(h, h->W_out_s, h->n_chunks * 32, H, 1.f, &h->out_unscale))) return rc;
   }
@@ -421,8 +424,7 @@ int pack_weights(rnnt_beam *h, const rnnt_weights_t *w) {
       b_p[r] = bih[o] + bhh[o];
     }
     if ((rc = upload(h, &h->W_hh, to_k4(whh_p, 4 * P, P, 4 * P)))) return rc;
-    // (not for the bf16 joint: its rounding of the activations turns any other order of the sums into other near ties)
-    if (!bf && (rc = split_rows(h, h->W_hh, 4 * P, P, kHidScale, &h->hh_unscale))) return rc;
+    if (h->split && (rc = split_rows(h, h->W_hh, 4 * P, P, kHidScale, &h->hh_unscale))) return rc;
     // G[v] = W_ih emb[v] + b_ih + b_hh for every token (and the start symbol): one GEMM at create
     float *d_wih = nullptr, *d_b = nullptr, *d_emb = nullptr;
     if ((rc = upload(h, &d_wih, wih_p))) return rc;
@@ -600,25 +602,22 @@ int launch_pred(rnnt_beam *h, hipStream_t s, const StepPlan &p, int cur, int bum
         lds = lm_row_bytes;
       }
       const dim3 grid(n_tiles + a.lmr.M);
-#define RB_PRED(W, I)                                                                                        \
-  do {                                                                                                       \
-    if (a.lmr.M) hipLaunchKernelGGL((k_pred_proj<W, I, true>), grid, dim3(W * 64), lds, s, a);              \
-    else hipLaunchKernelGGL((k_pred_proj<W, I, false>), grid, dim3(W * 64), 0, s, a);                        \
-  } while (0)
-#define RB_PRED_HALF(I)                                                                                      \
-  do {                                                                                                       \
-    if (a.lmr.M) hipLaunchKernelGGL((k_pred_proj_half<8, I, true>), grid, dim3(512), lds, s, a);            \
-    else hipLaunchKernelGGL((k_pred_proj_half<8, I, false>), grid, dim3(512), 0, s, a);                      \
-  } while (0)
-      if (proj_split(c, p.M)) {
-        if (c.P == 640) RB_PRED_HALF(5);
-        else RB_PRED_HALF(0);
-      }
-      else if (c.P == 640) RB_PRED(8, 10);
-      else if (c.P % 64 == 0) RB_PRED(8, 0);
-      else RB_PRED(4, 0);
-#undef RB_PRED_HALF
-#undef RB_PRED
+      auto launch = [&](auto split) {
+        constexpr bool S = decltype(split)::value;
+        auto go = [&](auto lm, auto plain, int waves) {
+          if (a.lmr.M) hipLaunchKernelGGL(lm, grid, dim3(waves * 64), lds, s, a);
+          else hipLaunchKernelGGL(plain, grid, dim3(waves * 64), 0, s, a);
+        };
+        if (proj_split(c, p.M)) {
+          if (c.P == 640) go(k_pred_proj_half<8, 5, S, true>, k_pred_proj_half<8, 5, S, false>, 8);
+          else go(k_pred_proj_half<8, 0, S, true>, k_pred_proj_half<8, 0, S, false>, 8);
+        }
+        else if (c.P == 640) go(k_pred_proj<8, 10, S, true>, k_pred_proj<8, 10, S, false>, 8);
+        else if (c.P % 64 == 0) go(k_pred_proj<8, 0, S, true>, k_pred_proj<8, 0, S, false>, 8);
+        else go(k_pred_proj<4, 0, S, true>, k_pred_proj<4, 0, S, false>, 4);
+      };
+      if (h->split) launch(std::true_type{});
+      else launch(std::false_type{});
     }
   } else if (p.big) {
     StatelessPreBigArgs a;
@@ -696,6 +695,51 @@ void launch_select(rnnt_beam *h, hipStream_t s, const StepPlan &p, const SelectA
     hipLaunchKernelGGL(k_sel, dim3(p.B), dim3(64 * p.K), 0, s, ma);
   } else if (select_needs_wide_forms(p.K, n_chunks)) hipLaunchKernelGGL(k_select_wide, dim3((p.B + 3) / 4), dim3(256), 0, s, sa);
   else hipLaunchKernelGGL(k_select, dim3((p.B + 3) / 4), dim3(256), 0, s, sa);
+}
+
+// k_step_main in the form for the decoder's widths and the selection that follows
+template <bool SPLIT>
+void launch_main(rnnt_beam *h, hipStream_t s, const StepPlan &p, const MainArgs &a, bool fold, bool tail) {
+  const rnnt_config_t &c = h->cfg;
+  const bool lstm = c.pred == RNNT_PRED_LSTM;
+  const dim3 grid(xcd_grid(a.map));
+  const bool wide = fold || a.rec.group > 1;  // (both only with the fully unrolled form below)
+  const bool full = c.H == 640 && (!lstm || c.P == 640);  // the fully unrolled form
+  // one selection form in the kernel where the shape is one of the two common ones (a third of the code)
+  // (11: form 5 for ALSD++ on a plain RNN-T, i.e. without durations and LM)
+  const bool plain = c.n_durations == 0 && !p.lm && p.algo == RNNT_ALSD;
+  const bool plain_aes = c.n_durations == 0 && !p.lm && p.algo == RNNT_AES && !std::isfinite(c.prune_margin) && !c.aes_prefix_search;
+  const int sel_any = !tail ? 0 : (p.K <= 2 && a.n_chunks <= 48 && plain) ? 13
+                                : (p.K > 2 && p.K <= 4 && a.n_chunks <= 48) ? (plain ? 11 : plain_aes ? 15 : 5)
+                                : (p.K > 4 && p.K <= 8 && a.n_chunks <= 40) ? (plain ? 14 : 6) : 0;
+  const int sel = full ? sel_any : 0;
+  // (the kernels for other widths: the ALSD++ forms for a plain RNN-T only)
+  const int sel_gen = (sel_any == 11 || sel_any == 13 || sel_any == 14) ? sel_any : 0;
+  auto go = [&](auto kernel, int waves) { hipLaunchKernelGGL(kernel, grid, dim3(waves * 64), 0, s, a); };
+  auto full_tail = [&](auto w) {
+    constexpr bool WIDE = decltype(w)::value;
+    if (sel == 11) go(k_step_main<8, 10, SPLIT, true, WIDE, 11>, 8);
+    else if (sel == 13) go(k_step_main<8, 10, SPLIT, true, WIDE, 13>, 8);
+    else if (sel == 14) go(k_step_main<8, 10, SPLIT, true, WIDE, 14>, 8);
+    else if (sel == 15) go(k_step_main<8, 10, SPLIT, true, WIDE, 15>, 8);
+    else if (sel == 5) go(k_step_main<8, 10, SPLIT, true, WIDE, 5>, 8);
+    else if (sel == 6) go(k_step_main<8, 10, SPLIT, true, WIDE, 6>, 8);
+    else go(k_step_main<8, 10, SPLIT, true, WIDE, 0>, 8);
+  };
+  auto other_widths = [&](auto w) {
+    constexpr int W = decltype(w)::value;
+    if (sel_gen == 11) go(k_step_main<W, 0, SPLIT, true, false, 11>, W);
+    else if (sel_gen == 13) go(k_step_main<W, 0, SPLIT, true, false, 13>, W);
+    else if (sel_gen == 14) go(k_step_main<W, 0, SPLIT, true, false, 14>, W);
+    else if (tail) go(k_step_main<W, 0, SPLIT, true>, W);
+    else go(k_step_main<W, 0, SPLIT, false>, W);
+  };
+  if (wide && tail) full_tail(std::true_type{});
+  else if (wide) go(k_step_main<8, 10, SPLIT, false, true>, 8);
+  else if (full && tail) full_tail(std::false_type{});
+  else if (full) go(k_step_main<8, 10, SPLIT, false>, 8);
+  else if (c.H % 64 == 0 && (!lstm || c.P % 64 == 0)) other_widths(std::integral_constant<int, 8>{});
+  else other_widths(std::integral_constant<int, 4>{});
 }
 
 // one beam-search step; cur = parity of the prediction-network state it reads
@@ -788,7 +832,7 @@ int launch_step(rnnt_beam *h, hipStream_t s, const StepPlan &p, int step_off, in
   } else {
     MainArgs a;
     a.pre = w.pre;
-    a.W = h->W_out_s ? h->W_out_s : h->W_out;
+    a.W = h->split ? h->W_out_s : h->W_out;
     a.W_plain = h->W_out; a.w_unscale = h->out_unscale;
     a.bias = h->b_out;
     a.lm = (p.lm && !c.lm_early_pruning) ? w.lm_rows : nullptr;  // early pruning ranks without the LM term
@@ -812,58 +856,15 @@ int launch_step(rnnt_beam *h, hipStream_t s, const StepPlan &p, int step_off, in
     a.map.b_end = lstm ? 4 * c.P / 32 : 0;
     a.map.b_m = recurrent_items(c, p.M);
     fill_select_args(h, p, step_off, h->n_chunks, a.sel);
-    const dim3 grid(xcd_grid(a.map));
     // The selection runs in the tail of this kernel for the beams its in-kernel forms take.  (Building the kernel
     // without it lets two blocks share a compute unit, but they also share its operand path: measured slower at
     // every shape, 11.3 vs 10.6 ms at B * beam = 256, beam 4.)
     const bool tail = p.K <= 8 && !c.tdt_all_pairs;
-#define RB_MAIN(W, I)                                                                              \
-  do {                                                                                             \
-    if (tail) hipLaunchKernelGGL((k_step_main<W, I, true>), grid, dim3(W * 64), 0, s, a);         \
-    else hipLaunchKernelGGL((k_step_main<W, I, false>), grid, dim3(W * 64), 0, s, a);             \
-  } while (0)
-    const bool wide = fold || a.rec.group > 1;  // (both only with the fully unrolled form below)
     {
       ScopedKernelTime tm(h, s, KT_JOINT);
-      const bool full = c.H == 640 && (!lstm || c.P == 640);  // the fully unrolled form
-      // one selection form in the kernel where the shape is one of the two common ones (a third of the code)
-      // (11: form 5 for ALSD++ on a plain RNN-T, i.e. without durations and LM)
-      const bool plain = c.n_durations == 0 && !p.lm && p.algo == RNNT_ALSD;
-      const bool plain_aes = c.n_durations == 0 && !p.lm && p.algo == RNNT_AES && !std::isfinite(c.prune_margin) &&
-                             !c.aes_prefix_search;
-      const int sel_any = !tail ? 0 : (p.K <= 2 && a.n_chunks <= 48 && plain) ? 13
-                                    : (p.K > 2 && p.K <= 4 && a.n_chunks <= 48) ? (plain ? 11 : plain_aes ? 15 : 5)
-                                    : (p.K > 4 && p.K <= 8 && a.n_chunks <= 40) ? (plain ? 14 : 6) : 0;
-      const int sel = full ? sel_any : 0;
-      // (the kernels for other widths: the ALSD++ forms for a plain RNN-T only)
-      const int sel_gen = (sel_any == 11 || sel_any == 13 || sel_any == 14) ? sel_any : 0;
-#define RB_MAIN_SEL(WIDE)                                                                                   \
-  do {                                                                                                      \
-    if (sel == 11) hipLaunchKernelGGL((k_step_main<8, 10, true, WIDE, 11>), grid, dim3(512), 0, s, a);      \
-    else if (sel == 13) hipLaunchKernelGGL((k_step_main<8, 10, true, WIDE, 13>), grid, dim3(512), 0, s, a); \
-    else if (sel == 14) hipLaunchKernelGGL((k_step_main<8, 10, true, WIDE, 14>), grid, dim3(512), 0, s, a); \
-    else if (sel == 15) hipLaunchKernelGGL((k_step_main<8, 10, true, WIDE, 15>), grid, dim3(512), 0, s, a); \
-    else if (sel == 5) hipLaunchKernelGGL((k_step_main<8, 10, true, WIDE, 5>), grid, dim3(512), 0, s, a);   \
-    else if (sel == 6) hipLaunchKernelGGL((k_step_main<8, 10, true, WIDE, 6>), grid, dim3(512), 0, s, a);   \
-    else hipLaunchKernelGGL((k_step_main<8, 10, true, WIDE, 0>), grid, dim3(512), 0, s, a);                 \
-  } while (0)
-      if (wide && tail) RB_MAIN_SEL(true);
-      else if (wide) hipLaunchKernelGGL((k_step_main<8, 10, false, true>), grid, dim3(512), 0, s, a);
-      else if (full && tail) RB_MAIN_SEL(false);
-      else if (full) RB_MAIN(8, 10);
-#undef RB_MAIN_SEL
-#define RB_MAIN_GEN(W)                                                                                       \
-  do {                                                                                                       \
-    if (sel_gen == 11) hipLaunchKernelGGL((k_step_main<W, 0, true, false, 11>), grid, dim3(W * 64), 0, s, a); \
-    else if (sel_gen == 13) hipLaunchKernelGGL((k_step_main<W, 0, true, false, 13>), grid, dim3(W * 64), 0, s, a); \
-    else if (sel_gen == 14) hipLaunchKernelGGL((k_step_main<W, 0, true, false, 14>), grid, dim3(W * 64), 0, s, a); \
-    else RB_MAIN(W, 0);                                                                                      \
-  } while (0)
-      else if (c.H % 64 == 0 && (!lstm || c.P % 64 == 0)) RB_MAIN_GEN(8);
-      else RB_MAIN_GEN(4);
-#undef RB_MAIN_GEN
+      if (h->split) launch_main<true>(h, s, p, a, fold, tail);
+      else launch_main<false>(h, s, p, a, fold, tail);
     }
-#undef RB_MAIN
     if (!tail) {
       RB_HIP(h, hipGetLastError());
       ScopedKernelTime tm(h, s, KT_SELECT);
@@ -893,12 +894,18 @@ bool use_persistent(const rnnt_beam *h, const StepPlan &p) {
   return h->n_cus >= 2 * kXccs;
 }
 
+auto persistent_kernel(const rnnt_beam *h) {
+  const bool full = h->cfg.H == 640 && h->cfg.P == 640;
+  if (h->split) return full ? k_decode_persistent<8, 10, true> : k_decode_persistent<8, 0, true>;
+  return full ? k_decode_persistent<8, 10, false> : k_decode_persistent<8, 0, false>;
+}
+
 int launch_persistent(rnnt_beam *h, hipStream_t s, const StepPlan &p, int max_steps) {
   const Workspace &w = *p.ws;
   const rnnt_config_t &c = h->cfg;
   PersistArgs a{};
   MainArgs &m = a.main;
-  m.pre = w.pre; m.W = h->W_out_s ? h->W_out_s : h->W_out; m.W_plain = h->W_out; m.w_unscale = h->out_unscale; m.bias = h->b_out; m.lm = nullptr; m.lambda = 0.f;
+  m.pre = w.pre; m.W = h->split ? h->W_out_s : h->W_out; m.W_plain = h->W_out; m.w_unscale = h->out_unscale; m.bias = h->b_out; m.lm = nullptr; m.lambda = 0.f;
   m.M = p.M; m.Mp = w.Mp; m.K = p.K; m.H = c.H; m.V = c.V; m.ND = c.n_durations;
   m.n_chunks = m.n_jchunks = h->n_chunks;
   m.round_ops = c.prec == RNNT_BF16_JOINT ? 1 : 0;
@@ -925,8 +932,7 @@ int launch_persistent(rnnt_beam *h, hipStream_t s, const StepPlan &p, int max_st
                      (int)(sizeof(PersistCtl) / sizeof(int)));
   const dim3 grid(h->n_cus / kXccs * kXccs);
   ScopedKernelTime tm(h, s, KT_JOINT);
-  if (c.H == 640 && c.P == 640) hipLaunchKernelGGL((k_decode_persistent<8, 10>), grid, dim3(512), 0, s, a);
-  else hipLaunchKernelGGL((k_decode_persistent<8, 0>), grid, dim3(512), 0, s, a);
+  hipLaunchKernelGGL(persistent_kernel(h), grid, dim3(512), 0, s, a);
   RB_HIP(h, hipGetLastError());
   return RNNT_OK;
 }
@@ -1379,10 +1385,7 @@ int rnnt_beam_create(const rnnt_config_t *cfg, const rnnt_weights_t *w, rnnt_bea
       int dev = 0, n_cu = 0, per_cu = 0;
       e = hipGetDevice(&dev);
       if (e == hipSuccess) e = hipDeviceGetAttribute(&n_cu, hipDeviceAttributeMultiprocessorCount, dev);
-      if (e == hipSuccess && c.H == 640 && c.P == 640)
-        e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, k_decode_persistent<8, 10>, 512, 0);
-      else if (e == hipSuccess)
-        e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, k_decode_persistent<8, 0>, 512, 0);
+      if (e == hipSuccess) e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, persistent_kernel(h), 512, 0);
       h->n_cus = (e == hipSuccess && per_cu >= 1) ? n_cu : 0;
       void *q = nullptr;
       if (e == hipSuccess) e = hipMalloc(&q, sizeof(PersistCtl));
