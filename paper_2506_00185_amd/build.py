@@ -11,8 +11,8 @@ CSRC = os.path.join(HERE, "csrc")
 LIB = os.path.join(HERE, "librnnt_beam.so")
 # (source, defines): compiled at the same time, then linked
 UNITS = [("rnnt_beam.hip", []), ("rnnt_lm.hip", []), ("rnnt_resident.hip", [])] + [
-    ("resident_kernels.hip", [f"-DRB_RES_FULL={full}", f"-DRB_RES_BF16={bf16}", f"-DRB_RES_ST={st}"])
-    for st in (0, 1) for full in (1, 0) for bf16 in (0, 1)]
+    ("resident_kernels.hip", [f"-DRB_RES_FULL={full}", f"-DRB_RES_FORM={form}", f"-DRB_RES_ST={st}"])
+    for st in (0, 1) for full in (1, 0) for form in (0, 1, 2)]
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
 FLAGS = ["-O3", "--offload-arch=gfx950", "-fPIC", "-std=c++17", "-Wno-unused-value",
          "-Wno-pass-failed", "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops"]

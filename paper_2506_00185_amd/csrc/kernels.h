@@ -311,14 +311,14 @@ __host__ __device__ __forceinline__ int xcd_item(const XcdMap &m, int bid, int &
 
 // Splits a k4-major matrix in place (see split_f16), each row scaled by a power of two that brings its largest element to
 // [2^14, 2^15): the 16 bytes of four k become their four hi, then their four lo.  unscale[row] takes that scale, and x_scale, off
-// a sum.  Infinite weights become the row's largest float16 (the scale is that of the finite ones).
+// a sum.  For finite weights only: NaN and infinities have no split.
 // 64 rows x 4 parts of the k per block.
 __global__ __launch_bounds__(256) void k_split_rows(float *W, int rows, int K, float x_scale, float *unscale) {
   __shared__ float s_max[4][64];
   const int r = threadIdx.x & 63, part = threadIdx.x >> 6, row = blockIdx.x * 64 + r;
   float4 *p = reinterpret_cast<float4 *>(W) + (row < rows ? row : 0);
   float m = 0.f;
-  auto larger = [&](float x) { m = fabsf(x) < INFINITY ? fmaxf(m, fabsf(x)) : m; };
+  auto larger = [&](float x) { m = fmaxf(m, fabsf(x)); };
   for (int i = part; i < K / 4; i += 4) {
     const float4 v = p[(size_t)i * rows];
     larger(v.x); larger(v.y); larger(v.z); larger(v.w);
@@ -332,12 +332,11 @@ __global__ __launch_bounds__(256) void k_split_rows(float *W, int rows, int K, f
   e = 15 - e < 100 ? 15 - e : 100;
   const float scale = ldexpf(1.f, e);
   if (part == 0) unscale[row] = ldexpf(1.f / x_scale, -e);
-  auto scaled = [&](float x) { return fminf(fmaxf(x * scale, -65504.f), x != x ? x : 65504.f); };
   for (int i = part; i < K / 4; i += 4) {
     const float4 v = p[(size_t)i * rows];
     uint32_t hi[2], lo[2];
-    split_f16(scaled(v.x), scaled(v.y), hi[0], lo[0]);
-    split_f16(scaled(v.z), scaled(v.w), hi[1], lo[1]);
+    split_f16(v.x * scale, v.y * scale, hi[0], lo[0]);
+    split_f16(v.z * scale, v.w * scale, hi[1], lo[1]);
     p[(size_t)i * rows] = make_float4(__uint_as_float(hi[0]), __uint_as_float(hi[1]), __uint_as_float(lo[0]), __uint_as_float(lo[1]));
   }
 }

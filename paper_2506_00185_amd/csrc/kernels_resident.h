@@ -21,8 +21,8 @@
 // functions), one or two steps before the place is used again.
 //
 // Every sum is formed in the order of the per-step kernels (K slices of 1/8 of the contraction, slices added first to last), so the
-// results are the same bit for bit.  Float32 models multiply on the float16 matrix instructions, both operands split in two (see
-// split_f16): in float32, W_hh h took 3.2 us per step and tile of 16 slots, as long as the selection it hides under, and the other
+// results are the same bit for bit.  Float32 models whose weights can be split multiply on the float16 matrix instructions, both
+// operands split in two (see split_f16): in float32, W_hh h took 3.2 us per step and tile of 16 slots, as long as the selection it hides under, and the other
 // two contractions 3 us of the chain.  bf16-joint models keep W_hh h on float32 matrix instructions (a 16x16x4 one rounds like four
 // fused multiply-adds in a row): they round activations to 8 bits, and near ties there follow every last bit of the hidden state.
 // (ms per decode before / after the splits, the gathers and the ends of waves described below: one utterance 8.65 / 6.95, greedy batch
@@ -58,6 +58,9 @@ constexpr int kResStepRing = 4;      // ring of the hand-over arrays
 constexpr int kResNotLocal = -2;     // stall_step of a test: the groups take themselves to lie on several XCDs
 constexpr uint32_t kResEmpty = 0xffffffffu;
 constexpr int kResSurvivors = 128;
+// How a decoder's products are formed: on float32 matrix instructions; W_out and W_pred on bf16 ones (the bf16 joint); on float16 ones
+// from split operands (see split_f16).
+enum ResForm { kResF32, kResBf16, kResSplit };
 constexpr int kResRedBlock = 2048;   // floats of one 16-row tile's partial sums: 8 waves x 64 lanes x 4
 
 // What one block of a group owns (the same table for every group).
@@ -79,11 +82,11 @@ constexpr int kResRedBlocks = BF16 ? 4 : 3;
 __host__ __device__ inline int res_k_of(int round, int kq, int e) { return 8 * round + (kq & 1) * 4 + (kq >> 1) + 2 * e; }
 
 struct ResArgs {
-  const uintx4_t *WR, *WJ, *WP;      // float32 models: [tile][wave][kResQuads * 64] (see k_pack_split)
-  const float *WRf;                  // bf16 models: [tile][round][64 lanes][2]
+  const uintx4_t *WR, *WJ, *WP;      // kResSplit: [tile][wave][kResQuads * 64] (see k_pack_split)
+  const float *WRf, *WJf, *WPf;      // else, [tile][round][64 lanes][2] (kResBf16: W_hh only)
   const float *hh_unscale, *out_unscale, *pred_unscale;  // of their rows (see k_split_rows)
   const float *WJs;                  // the tile that begins with the blank column, for res_fold_mma: see k_pack_fold
-  const uint64_t *WJb, *WPb;         // bf16 models: [32-row tile][round][64 lanes] four bf16 (k of the lane's half)
+  const uint64_t *WJb, *WPb;         // kResBf16: [32-row tile][round][64 lanes] four bf16 (k of the lane's half)
   const float *b_out, *b_pred, *G, *f_proj;
   const float *emb_tab;              // stateless decoders: [n_ctx][V + 1][H], else null
   int n_ctx;
@@ -130,6 +133,14 @@ __device__ __forceinline__ bool res_any_empty(const uint64_t (&x)[N]) {
 #pragma unroll
   for (int i = 0; i < N; ++i) m = max(m, max((uint32_t)x[i], (uint32_t)(x[i] >> 32)));
   return m == kResEmpty;
+}
+// x[i] for an index that is the same in all lanes but not known at compile time
+template <int N>
+__device__ __forceinline__ uint64_t res_pick(const uint64_t (&x)[N], int i) {
+  uint64_t v = x[0];
+#pragma unroll
+  for (int q = 1; q < N; ++q) v = i == q ? x[q] : v;
+  return v;
 }
 __device__ __forceinline__ uint64_t pack2(float lo, float hi) {
   return (uint64_t)__float_as_uint(hi) << 32 | __float_as_uint(lo);
@@ -457,16 +468,16 @@ __device__ __forceinline__ floatx4 res_p_frame(const ResArgs &a, const ResBlock 
 }
 // sums of the wave's tile -> pre.  first / second: the blocks of its partial sums of the two halves of k (halves: the
 // per-step launches add the bias and the frame's projection to the first half's sum, then the second half's).
-template <bool BF16>
+template <int FORM>
 __device__ __forceinline__ void res_p_finish(const ResArgs &a, const ResBlock &k, const ResLane &l, const ResAddr &ad, int step, int nt, int first,
                                              int second, floatx4 f) {
   const floatx4 *par = k.par + ResPar::kP + 8 * (kResWaves - 1 - k.wave) + l.kq;
-  floatx4 v = res_sum<BF16>(k, l, first);
-  if constexpr (!BF16) v *= par[ResPar::kScale];
+  floatx4 v = res_sum<FORM == kResBf16>(k, l, first);
+  if constexpr (FORM == kResSplit) v *= par[ResPar::kScale];
   v = (v + par[ResPar::kBias]) + f;
   if (a.halves) {
-    floatx4 s = res_sum<BF16>(k, l, second);
-    if constexpr (!BF16) s *= par[ResPar::kScale];
+    floatx4 s = res_sum<FORM == kResBf16>(k, l, second);
+    if constexpr (FORM == kResSplit) s *= par[ResPar::kScale];
     v += s;
   }
   float *dst = res_p_dst(ad.p(step, nt), k.ptile, l.kq, l.sl);
@@ -552,7 +563,7 @@ __device__ __forceinline__ void bf16_put(const ResBlock &k, const ResLane &l, in
   }
 }
 
-template <bool FULL, bool BF16>
+template <bool FULL, int FORM>
 __device__ __forceinline__ void res_p_phase(ResBlock &k, int step) {
   if (k.nP == 0) return;
   const ResArgs &a = res_args();
@@ -561,7 +572,7 @@ __device__ __forceinline__ void res_p_phase(ResBlock &k, int step) {
   const int nr = FULL ? kResMaxRounds : a.rounds_p;
   const bool halves = a.halves != 0;
   const int nh = halves ? nr / 2 : nr;  // rounds of a slice: the wave has one in either half of k, or one of the whole
-  if constexpr (BF16) {  // one tile of 32 outputs: two waves finish 16 each
+  if constexpr (FORM == kResBf16) {  // one tile of 32 outputs: two waves finish 16 each
 #pragma unroll 1
     for (int nt = 0; nt < k.nt; nt += 2) {
       const bool second = nt + 1 < k.nt;
@@ -616,10 +627,10 @@ __device__ __forceinline__ void res_p_phase(ResBlock &k, int step) {
       }
       __syncthreads();
       res_end_if_given_up();
-      if (k.ptile >= 0) res_p_finish<true>(a, k, l, ad, step, nt, k.ptile & 1, 2 + (k.ptile & 1), f[0]);
+      if (k.ptile >= 0) res_p_finish<kResBf16>(a, k, l, ad, step, nt, k.ptile & 1, 2 + (k.ptile & 1), f[0]);
       ++k.phase;
       if (second) {
-        if (k.ptile >= 0) res_p_finish<true>(a, k, l, ad, step, nt + 1, k.ptile & 1, 2 + (k.ptile & 1), f[1]);
+        if (k.ptile >= 0) res_p_finish<kResBf16>(a, k, l, ad, step, nt + 1, k.ptile & 1, 2 + (k.ptile & 1), f[1]);
         ++k.phase;
         __syncthreads();  // (both halves of the buffer have just been read)
       }
@@ -630,15 +641,56 @@ __device__ __forceinline__ void res_p_phase(ResBlock &k, int step) {
       floatx4 f = {0.f, 0.f, 0.f, 0.f};
       if (k.ptile >= 0) f = res_p_frame(a, k, l, nt);
       const char *src = reinterpret_cast<const char *>(ad.h(step, nt)) + k.wave * nh * kResRoundBytes;
-      const uintx4_t *tiles = reinterpret_cast<const uintx4_t *>(k.tiles) + (size_t)k.wave * kResQuads * 64;
+      [[maybe_unused]] const uintx4_t *tiles = reinterpret_cast<const uintx4_t *>(k.tiles) + (size_t)k.wave * kResQuads * 64;
       // what the wave finishes of tile tp (a copy per tile: their blocks of partial sums alternate)
       auto finish = [&](int tp) {
         __syncthreads();
         res_end_if_given_up();
-        if (k.wave == res_p_wave(tp)) res_p_finish<false>(a, k, l, ad, step, nt, 0, 1, f);
+        if (k.wave == res_p_wave(tp)) res_p_finish<FORM>(a, k, l, ad, step, nt, 0, 1, f);
         ++k.phase;
       };
-      if (halves) {
+      if constexpr (FORM == kResF32) {
+        uint64_t x[kResMaxRounds];
+        // rounds i < nr / 2 from the wave's slice of the first half of k, the others from its slice of the second half (or
+        // all of one slice)
+        constexpr int R = kResMaxRounds / 2;
+        const int n1 = FULL ? R : nr / 2, jump = halves ? 4 * nr - n1 : 0;
+        const uint32_t offs[2] = {(uint32_t)l.lane * 8, (uint32_t)l.lane * 8 + (R + jump) * kResRoundBytes};
+        auto at = [&](int i, const uint32_t (&o)[2]) {
+          if constexpr (FULL) return src + o[i / R] + i % R * kResRoundBytes;
+          return src + o[0] + (i + (i >= n1 ? jump : 0)) * kResRoundBytes;
+        };
+        res_gather<FULL, kResMaxRounds, false>(src, 0, offs, at, nr, x);
+#pragma unroll 1
+        for (int tp = 0; tp < k.nP; ++tp) {
+          const uint64_t *w = k.tiles + (size_t)tp * (a.P * kResSlot / 2) + (size_t)k.wave * nh * 64 + l.lane;
+          if (halves) {
+            floatx4 acc0 = {0.f, 0.f, 0.f, 0.f}, acc1 = acc0;
+#pragma unroll
+            for (int i = 0; i < R; ++i)
+              if (FULL || i < n1) {
+                const uint64_t u = w[i * 64], v = w[(4 * nr + i) * 64], y = FULL ? x[R + i] : res_pick(x, n1 + i);
+                acc0 = mfma16(lo_f(u), lo_f(x[i]), acc0);
+                acc1 = mfma16(lo_f(v), lo_f(y), acc1);
+                acc0 = mfma16(hi_f(u), hi_f(x[i]), acc0);
+                acc1 = mfma16(hi_f(v), hi_f(y), acc1);
+              }
+            res_put<false>(k, l, 0, acc0);
+            res_put<false>(k, l, 1, acc1);
+          } else {
+            floatx4 acc = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+            for (int i = 0; i < kResMaxRounds; ++i)
+              if (FULL || i < nr) {
+                const uint64_t u = w[i * 64];
+                acc = mfma16(lo_f(u), lo_f(x[i]), acc);
+                acc = mfma16(hi_f(u), hi_f(x[i]), acc);
+              }
+            res_put<false>(k, l, 0, acc);
+          }
+          finish(tp);
+        }
+      } else if (halves) {
         // a slice of up to five rounds of either half of k: a quad, and a fifth round that the lanes of even kq hold
         uint64_t x[12];
         // (absent rounds: words that are there, cleared below)
@@ -715,11 +767,11 @@ __device__ __forceinline__ void res_p_phase(ResBlock &k, int step) {
 }
 
 // ---- J: z[step] = W_out ReLU(pre[step]) + b_out for the block's tiles
-template <bool BF16>
+template <int FORM>
 __device__ __forceinline__ void res_j_finish(const ResBlock &k, const ResLane &l, const ResAddr &ad, int step, int nt, int tile, int par, int block) {
   const int slot = nt * kResSlot + l.sl, n0 = 16 * tile + 4 * l.kq;
-  floatx4 v = res_sum<BF16>(k, l, block);
-  if constexpr (!BF16) v *= k.par[par + ResPar::kScale + l.kq];
+  floatx4 v = res_sum<FORM == kResBf16>(k, l, block);
+  if constexpr (FORM == kResSplit) v *= k.par[par + ResPar::kScale + l.kq];
   v += k.par[par + ResPar::kBias + l.kq];
   wait_stores_acknowledged();
   if (slot < k.nslots) res_store16(k.local, ad.z(step, slot) + n0, v);
@@ -792,14 +844,16 @@ __device__ __forceinline__ void res_stateless_pre(const ResArgs &a, const ResBlo
 // Float32: one matrix instruction takes the four k of a half.  x: two k of a round, {0, 4, 1, 5}[kq] and two further; the
 // swaps (rows 2, 3 of the first with rows 0, 1 of the second, then odd rows with even ones) leave k = kq and 4 + kq.  The
 // weights lie that way (k_pack_fold).
-__device__ __forceinline__ floatx4 res_fold_mma(const ResW16 &w, const uint64_t (&x)[kResMaxRounds]) {
+// w_at(i): word i of the lane's part of the tile.
+template <class W>
+__device__ __forceinline__ floatx4 res_fold_mma(W w_at, const uint64_t (&x)[kResMaxRounds]) {
   floatx4 lo = {0.f, 0.f, 0.f, 0.f}, hi = lo;
 #pragma unroll
   for (int i = 0; i < kResMaxRounds; ++i) {
     const auto s32 = __builtin_amdgcn_permlane32_swap((uint32_t)x[i], (uint32_t)(x[i] >> 32), false, false);
     const auto s16 = __builtin_amdgcn_permlane16_swap(s32[0], s32[1], false, false);
-    lo = mfma16(res_raw(w, 2 * i), __uint_as_float(s16[0]), lo);
-    hi = mfma16(res_raw(w, 2 * i + 1), __uint_as_float(s16[1]), hi);
+    lo = mfma16(w_at(2 * i), __uint_as_float(s16[0]), lo);
+    hi = mfma16(w_at(2 * i + 1), __uint_as_float(s16[1]), hi);
   }
   return lo + hi;
 }
@@ -840,20 +894,21 @@ __device__ __forceinline__ void res_update_ctx(const ResBlock &k) {
   wave_sync();
 }
 
-// float32: split tiles (the one that is folded as k_pack_fold leaves it); bf16: four k a pair of words, round by round
-template <bool BF16>
+// split tiles, or two words a round (kResBf16: they are four k); the one that is folded as k_pack_fold leaves it
+template <int FORM>
 struct ResWJ {
-  std::conditional_t<BF16, float[kResRegJ<true>][2 * kResMaxRounds], ResW16[kResRegJ<false>]> t;
+  std::conditional_t<FORM == kResSplit, ResW16[kResRegJ<false>], float[kResRegJ<FORM == kResBf16>][2 * kResMaxRounds]> t;
 };
-// W_hh: split (float32 models), or round by round
-template <bool BF16>
+// W_hh: split, or round by round
+template <int FORM>
 struct ResWR {
-  std::conditional_t<BF16, float[kResMaxR][2 * kResMaxRounds], ResW16[kResMaxR]> t;
+  std::conditional_t<FORM == kResSplit, ResW16[kResMaxR], float[kResMaxR][2 * kResMaxRounds]> t;
 };
 // wj: the tiles that the block keeps in registers; one more may lie in LDS behind the projection's
-template <bool FULL, bool BF16, bool ST>
-__device__ __forceinline__ void res_j_phase(ResBlock &k, int step, const ResWJ<BF16> &wj) {
+template <bool FULL, int FORM, bool ST>
+__device__ __forceinline__ void res_j_phase(ResBlock &k, int step, const ResWJ<FORM> &wj) {
   if (k.nJ == 0) return;
+  constexpr bool BF16 = FORM == kResBf16;
   constexpr int NJ = kResRegJ<BF16>;
   const ResArgs &a = res_args();
   const ResLane l = res_lane();
@@ -878,7 +933,7 @@ __device__ __forceinline__ void res_j_phase(ResBlock &k, int step, const ResWJ<B
       auto put_out = [&](int t) {
         __syncthreads();
         res_end_if_given_up();
-        if (k.wave < (second ? 4 : 2)) res_j_finish<true>(k, l, ad, step, nt + (k.wave >> 1), k.jtile[t], ResPar::kJ + 8 * (2 * t + (k.wave & 1)), k.wave);
+        if (k.wave < (second ? 4 : 2)) res_j_finish<kResBf16>(k, l, ad, step, nt + (k.wave >> 1), k.jtile[t], ResPar::kJ + 8 * (2 * t + (k.wave & 1)), k.wave);
         ++k.phase;
       };
 #pragma unroll
@@ -919,6 +974,54 @@ __device__ __forceinline__ void res_j_phase(ResBlock &k, int step, const ResWJ<B
 #pragma unroll
         for (int i = 0; i < kResMaxRounds; ++i) x[i] = pack2(fmaxf(lo_f(x[i]), 0.f), fmaxf(hi_f(x[i]), 0.f));
       };
+      auto done = [&] {
+        __syncthreads();
+        res_end_if_given_up();
+        if (k.jtile[0] >= 0) res_j_finish<FORM>(k, l, ad, step, nt, k.jtile[0], ResPar::kJ + 8 * k.wave, k.wave);
+        ++k.phase;
+      };
+      if constexpr (FORM == kResF32) {
+        uint64_t x[kResMaxRounds];
+        if constexpr (ST) res_stateless_pre<FULL, false, false>(a, k, l, nr, x);
+        else {
+          const uint32_t offs[2] = {(uint32_t)l.lane * 8, (uint32_t)l.lane * 8 + 5 * kResRoundBytes};
+          res_gather<FULL, kResMaxRounds, false>(src, 0, offs, [src](int i, const uint32_t (&o)[2]) { return src + o[i / 5] + i % 5 * kResRoundBytes; }, nr, x);
+        }
+        relu(x);
+        floatx4 acc[NJ];
+        // N tiles from the first on
+        auto mma = [&](auto first, auto w_at, auto &c) {
+          constexpr int t0 = decltype(first)::value;
+#pragma unroll
+          for (int t = t0; t < NJ; ++t) c[t] = floatx4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+          for (int i = 0; i < kResMaxRounds; ++i)
+            if (FULL || i < nr) {
+#pragma unroll
+              for (int t = t0; t < NJ; ++t) c[t] = mfma16(w_at(t, 2 * i), lo_f(x[i]), c[t]);
+#pragma unroll
+              for (int t = t0; t < NJ; ++t) c[t] = mfma16(w_at(t, 2 * i + 1), hi_f(x[i]), c[t]);
+            }
+        };
+        auto in_regs = [&](int t, int i) { return wj.t[t][i]; };
+        if (FULL && k.fold) {
+          mma(std::integral_constant<int, 1>{}, in_regs, acc);
+          acc[0] = res_fold_mma([&](int i) { return wj.t[0][i]; }, x);
+        } else {
+          mma(std::integral_constant<int, 0>{}, in_regs, acc);
+        }
+#pragma unroll
+        for (int t = 0; t < NJ; ++t)
+          if (t < k.nJ) res_put<false>(k, l, t, acc[t]);
+        if (k.nJ > NJ) {
+          const uint64_t *w = k.tiles + (size_t)k.nP * (a.P * kResSlot / 2) + (size_t)k.wave * nr * 64 + l.lane;
+          floatx4 c[NJ];
+          mma(std::integral_constant<int, NJ - 1>{}, [&](int, int i) { return i & 1 ? hi_f(w[(i >> 1) * 64]) : lo_f(w[(i >> 1) * 64]); }, c);
+          res_put<false>(k, l, NJ, c[NJ - 1]);
+        }
+        done();
+        continue;
+      } else {
       ResW16 xs;
       float inv;
       {
@@ -946,7 +1049,7 @@ __device__ __forceinline__ void res_j_phase(ResBlock &k, int step, const ResWJ<B
         relu(x);
         floatx4 c1[1], d1[1];
         res_split_mma<FULL, 1, 1>(wj.t, xs, nr, c1, d1);
-        res_put<false>(k, l, 0, res_fold_mma(wj.t[0], x));
+        res_put<false>(k, l, 0, res_fold_mma([&](int i) { return res_raw(wj.t[0], i); }, x));
         if (1 < k.nJ) res_put<false>(k, l, 1, (c1[0] + d1[0]) * inv);
       } else {
         floatx4 acc[NJ], cor[NJ];
@@ -961,10 +1064,8 @@ __device__ __forceinline__ void res_j_phase(ResBlock &k, int step, const ResWJ<B
         res_split_mma<FULL, 0, 1>(w, xs, nr, c1, d1);
         res_put<false>(k, l, NJ, (c1[0] + d1[0]) * inv);
       }
-      __syncthreads();
-      res_end_if_given_up();
-      if (k.jtile[0] >= 0) res_j_finish<false>(k, l, ad, step, nt, k.jtile[0], ResPar::kJ + 8 * k.wave, k.wave);
-      ++k.phase;
+      done();
+      }
     }
   }
 }
@@ -997,8 +1098,9 @@ __device__ __forceinline__ int res_h_ofs(const ResLane &l, int t) {
   return ((t >> 1) * 4 + (t & 1) * 2 + (l.kq >> 1)) * (2 * kResSlot) + l.sl * 2 + (l.kq & 1);
 }
 
-template <bool FULL, bool BF16, bool ST>
+template <bool FULL, int FORM, bool ST>
 __device__ __forceinline__ void res_worker(ResBlock k, const ResTab &tab, float *lds) {
+  constexpr bool BF16 = FORM == kResBf16, SPLIT = FORM == kResSplit;
   constexpr int NJ = kResRegJ<BF16>, NR = ST ? 0 : kResMaxR;
   const ResArgs &a0 = res_args();
   k.nR = res_uniform(tab.nR);
@@ -1024,16 +1126,19 @@ __device__ __forceinline__ void res_worker(ResBlock k, const ResTab &tab, float 
   const ResLane l0 = res_lane();
   // weights: projection tiles (and the output-layer tile that finds no registers) to LDS, the others to registers
   {
-    const int n4 = BF16 ? a0.P * kResSlot / 4 : kResTileFloats / 4, h4 = BF16 ? a0.H * kResSlot / 4 : kResTileFloats / 4;
+    const int n4 = SPLIT ? kResTileFloats / 4 : a0.P * kResSlot / 4, h4 = SPLIT ? kResTileFloats / 4 : a0.H * kResSlot / 4;
+    auto form = [](const uintx4_t *split, const uint64_t *b, const float *f) {
+      return SPLIT ? split : BF16 ? reinterpret_cast<const uintx4_t *>(b) : reinterpret_cast<const uintx4_t *>(f);
+    };
     uintx4_t *dst = reinterpret_cast<uintx4_t *>(lds);
     k.tiles = reinterpret_cast<const uint64_t *>(lds);
     for (int tp = 0; tp < k.nP; ++tp) {
-      const uintx4_t *src = (BF16 ? reinterpret_cast<const uintx4_t *>(a0.WPb) : a0.WP) + (size_t)tab.P[tp] * n4;
+      const uintx4_t *src = form(a0.WP, a0.WPb, a0.WPf) + (size_t)tab.P[tp] * n4;
       for (int i = threadIdx.x; i < n4; i += kResThreads) dst[i] = src[i];
       dst += n4;
     }
     if (k.nJ > NJ) {
-      const uintx4_t *src = (BF16 ? reinterpret_cast<const uintx4_t *>(a0.WJb) : a0.WJ) + (size_t)tab.J[NJ] * h4;
+      const uintx4_t *src = form(a0.WJ, a0.WJb, a0.WJf) + (size_t)tab.J[NJ] * h4;
       for (int i = threadIdx.x; i < h4; i += kResThreads) dst[i] = src[i];
       dst += h4;
     }
@@ -1082,10 +1187,10 @@ __device__ __forceinline__ void res_worker(ResBlock k, const ResTab &tab, float 
     k.ctx = reinterpret_cast<int4 *>(Rl) + k.wave * a0.NT * kResSlot;
     for (int i = l0.lane; i < a0.NT * kResSlot; i += 64) k.ctx[i] = make_int4(-1, -1, -1, -1);
   }
-  ResWJ<BF16> wj;
-  ResWR<BF16> wr;
+  ResWJ<FORM> wj;
+  ResWR<FORM> wr;
   {
-    if constexpr (BF16) {
+    if constexpr (!SPLIT) {
       const int nrh = FULL ? kResMaxRounds : a0.rounds_h;
 #pragma unroll
       for (int t = 0; t < NJ; ++t)
@@ -1093,7 +1198,9 @@ __device__ __forceinline__ void res_worker(ResBlock k, const ResTab &tab, float 
         for (int i = 0; i < kResMaxRounds; ++i) {
           wj.t[t][2 * i] = wj.t[t][2 * i + 1] = 0.f;
           if (t < k.nJ && (FULL || i < nrh)) {
-            const uint64_t v = a0.WJb[((size_t)tab.J[t] * (a0.H / 8) + k.wave * nrh + i) * 64 + l0.lane];
+            const bool fold = !BF16 && t == 0 && k.fold;
+            const uint64_t *w = BF16 ? a0.WJb : reinterpret_cast<const uint64_t *>(fold ? a0.WJs : a0.WJf);
+            const uint64_t v = w[((size_t)(fold ? 0 : tab.J[t]) * (a0.H / 8) + k.wave * nrh + i) * 64 + l0.lane];
             wj.t[t][2 * i] = lo_f(v);
             wj.t[t][2 * i + 1] = hi_f(v);
           }
@@ -1117,7 +1224,7 @@ __device__ __forceinline__ void res_worker(ResBlock k, const ResTab &tab, float 
     }
 #pragma unroll
     for (int t = 0; t < NR; ++t) {
-      if constexpr (BF16) {
+      if constexpr (!SPLIT) {
         const int nrp = FULL ? kResMaxRounds : a0.rounds_p;
 #pragma unroll
         for (int i = 0; i < kResMaxRounds; ++i) {
@@ -1137,7 +1244,7 @@ __device__ __forceinline__ void res_worker(ResBlock k, const ResTab &tab, float 
     auto keep = [](ResW16 &w) { asm volatile("" : "+v"(w.h[0]), "+v"(w.h[1]), "+v"(w.l[0]), "+v"(w.l[1]), "+v"(w.th), "+v"(w.tl)); };
 #pragma unroll
     for (int t = 0; t < NJ; ++t) {
-      if constexpr (BF16) {
+      if constexpr (!SPLIT) {
 #pragma unroll
         for (int i = 0; i < 2 * kResMaxRounds; ++i) asm volatile("" : "+v"(wj.t[t][i]));
       } else {
@@ -1146,7 +1253,7 @@ __device__ __forceinline__ void res_worker(ResBlock k, const ResTab &tab, float 
     }
 #pragma unroll
     for (int t = 0; t < NR; ++t) {
-      if constexpr (BF16) {
+      if constexpr (!SPLIT) {
 #pragma unroll
         for (int i = 0; i < 2 * kResMaxRounds; ++i) asm volatile("" : "+v"(wr.t[t][i]));
       } else {
@@ -1193,8 +1300,8 @@ __device__ __forceinline__ void res_worker(ResBlock k, const ResTab &tab, float 
         }
     }
     if constexpr (!ST)
-      res_p_phase<FULL, BF16>(k, step);
-    res_j_phase<FULL, BF16, ST>(k, step, wj);
+      res_p_phase<FULL, FORM>(k, step);
+    res_j_phase<FULL, FORM, ST>(k, step, wj);
     // (under the selection: ahead of the projection the waits for the activations included these stores)
     if (step > 0) {
       const ResArgs &a = res_args();
@@ -1221,7 +1328,7 @@ __device__ __forceinline__ void res_worker(ResBlock k, const ResTab &tab, float 
         uint64_t x[kResMaxRounds];
         const char *src = reinterpret_cast<const char *>(ad.h(step, nt)) + k.wave * nrp * kResRoundBytes;
         // (nearly always there: the logits needed all of it)
-        if constexpr (BF16) {
+        if constexpr (!SPLIT) {
           const uint32_t offs[2] = {(uint32_t)l.lane * 8, (uint32_t)l.lane * 8 + 5 * kResRoundBytes};
           res_gather<FULL, kResMaxRounds, false>(src, 0, offs, [src](int i, const uint32_t (&o)[2]) { return src + o[i / 5] + i % 5 * kResRoundBytes; }, nrp, x);
         } else {
@@ -1232,10 +1339,10 @@ __device__ __forceinline__ void res_worker(ResBlock k, const ResTab &tab, float 
           constexpr int t0 = decltype(first)::value;
           if (t0 >= k.nR) return;
           // (tiles that the block does not own have zero weights; fewer branches are worth more than their instructions)
-          floatx4 acc[3], cor[3];
-          if constexpr (BF16) {
+          floatx4 acc[3];
+          if constexpr (!SPLIT) {
 #pragma unroll
-            for (int t = 0; t < 3; ++t) acc[t] = cor[t] = floatx4{0.f, 0.f, 0.f, 0.f};
+            for (int t = 0; t < 3; ++t) acc[t] = floatx4{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
             for (int i = 0; i < kResMaxRounds; ++i)
               if (FULL || i < nrp) {
@@ -1245,6 +1352,7 @@ __device__ __forceinline__ void res_worker(ResBlock k, const ResTab &tab, float 
                 for (int t = 0; t < 3; ++t) acc[t] = mfma16(wr.t[t0 + t][2 * i + 1], hi_f(x[i]), acc[t]);
               }
           } else {
+            floatx4 cor[3];
             res_split_mma<FULL, t0, 3>(wr.t, xs, nrp, acc, cor);
 #pragma unroll
             for (int t = 0; t < 3; ++t) acc[t] += cor[t];
@@ -1256,7 +1364,7 @@ __device__ __forceinline__ void res_worker(ResBlock k, const ResTab &tab, float 
           res_end_if_given_up();
           if (k.wave >= t0 && k.wave < t0 + 3 && k.wave < k.nR) {
             floatx4 s = res_sum<BF16>(k, l, k.wave - t0);
-            if constexpr (!BF16) s *= k.par[ResPar::kR + 4 * k.wave + l.kq];
+            if constexpr (SPLIT) s *= k.par[ResPar::kR + 4 * k.wave + l.kq];
             *reinterpret_cast<floatx4 *>(Rl + ((k.wave * a.NT + nt) * 64 + l.lane) * 4) = s;
           }
           ++k.phase;
@@ -1624,7 +1732,7 @@ __device__ __forceinline__ void res_selector(ResBlock k, int sel, float *lds) {
 // FULL: H = P = 640 (loops of known length).  ST: stateless decoder (P does not count).  KC: beams up to 4, 8, 16.  PLAIN: 1 = ALSD++ on a plain RNN-T (see
 // select_utterance), 0 = any.  One block of 8 waves per compute unit (the LDS it asks for is more than half of a unit's).
 // The first n_sel blocks of a group select, the others own the tiles.
-template <bool FULL, bool BF16, bool ST, int KC, int PLAIN>
+template <bool FULL, int FORM, bool ST, int KC, int PLAIN>
 __global__ __launch_bounds__(kResThreads, 2) void k_decode_resident(ResArgs) {
   extern __shared__ __align__(16) float smem[];
   __shared__ int s_ok;
@@ -1684,13 +1792,13 @@ __global__ __launch_bounds__(kResThreads, 2) void k_decode_resident(ResArgs) {
     res_selector<KC, PLAIN>(k, rank, smem);
   } else {
     const ResTab &tab = a.tab[rank - a.n_sel];
-    if (tab.nR + tab.nJ + tab.nP > 0) res_worker<FULL, BF16, ST>(k, tab, smem);
+    if (tab.nR + tab.nJ + tab.nP > 0) res_worker<FULL, FORM, ST>(k, tab, smem);
   }
 }
 
 typedef void (*ResKernel)(ResArgs);
 // each in a translation unit of its own (resident_kernels.hip), so that they build at once
-template <bool FULL, bool BF16, bool ST>
+template <bool FULL, int FORM, bool ST>
 ResKernel resident_kernel(int K, bool plain);
 
 }  // namespace rb

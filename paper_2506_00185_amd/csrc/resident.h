@@ -19,9 +19,10 @@ struct Resident {
   bool usable = false;
   int n_cus = 0, max_lds = 0;
   int misses = 0, skip = 0;       // launches in a row that gave up; decodes left to the per-step launches before the next try
+  int form = 0;                   // ResForm
   const float *hh_unscale = nullptr, *out_unscale = nullptr, *pred_unscale = nullptr;  // the handle's
   uint32_t *WR = nullptr, *WJ = nullptr, *WP[2] = {nullptr, nullptr};  // see k_pack_split
-  float *WRf = nullptr, *WJs = nullptr;
+  float *WRf = nullptr, *WJf = nullptr, *WPf = nullptr, *WJs = nullptr;
   uint64_t *WJb = nullptr, *WPb = nullptr;
   float *hb = nullptr, *pb = nullptr, *zb = nullptr;
   uint64_t *words = nullptr;
@@ -42,7 +43,8 @@ inline void resident_missed(Resident &r) {
 
 // What the packing reads: the handle's k4-major weights (see kernels.h, k4_index)
 struct ResidentWeights {
-  // float32 models: split (k_split_rows), the output layer also as it is
+  // split: W_hh, W_out_s and W_pred are (k_split_rows), the output layer is there as it is as well
+  bool split;
   const float *W_hh, *hh_unscale, *W_out, *W_out_s, *out_unscale, *W_pred, *pred_unscale;
   int out_rows;  // padded rows of W_out
 };

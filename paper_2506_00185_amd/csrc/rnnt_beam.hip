@@ -173,7 +173,7 @@ struct rnnt_beam {
   // packed weights
   float *W_enc = nullptr, *b_enc = nullptr, *W_pred = nullptr, *b_pred = nullptr, *W_out = nullptr,
         *b_out = nullptr, *W_hh = nullptr, *hh_unscale = nullptr, *W_out_s = nullptr, *out_unscale = nullptr, *pred_unscale = nullptr, *G = nullptr, *tab = nullptr;
-  bool split = false;   // W_hh, W_pred and W_out_s are split (k_split_rows): float32 models
+  bool split = false;   // W_hh, W_pred and W_out_s are split (k_split_rows)
   // materialised-logits path (bf16 joint, large shapes)
   bool big = false;
   int Npad_big = 0, Hb = 0;  // padded extents of the bf16 operands: 256 columns, 64 k
@@ -344,8 +344,12 @@ int pack_weights(rnnt_beam *h, const rnnt_weights_t *w) {
   const rnnt_config_t &c = h->cfg;
   const int H = c.H, P = c.P, D = c.D, E = c.E, V = c.V, N = h->N;
   const bool bf = c.prec == RNNT_BF16_JOINT;
-  // (not for the bf16 joint: its rounding of the activations turns any other order of the sums into other near ties)
-  h->split = !bf;
+  // Split products (see split_f16) for float32 models whose weights are finite: NaN and infinities have no split.  (Not for the bf16
+  // joint: its rounding of the activations turns any other order of the sums into other near ties.)
+  bool finite = true;
+  auto look = [&](const std::vector<float> &v) {
+    for (float x : v) finite = finite && std::isfinite(x);
+  };
   std::vector<float> tmp, out;
   std::vector<void *> staging;  // device buffers needed only until the folded tables have been computed
   int rc;
@@ -365,18 +369,16 @@ int pack_weights(rnnt_beam *h, const rnnt_weights_t *w) {
   if ((rc = upload(h, &d_wpred_rm, wpred))) return rc;
   staging.push_back(d_wpred_rm);
   if ((rc = upload(h, &h->W_pred, to_k4(wpred, H, P, H)))) return rc;
-  if (h->split && c.pred == RNNT_PRED_LSTM && (rc = split_rows(h, h->W_pred, H, P, kHidScale, &h->pred_unscale))) return rc;
+  if (c.pred == RNNT_PRED_LSTM) look(wpred);  // (stateless: of the tables only)
   if ((rc = download(h, bpred, w->b_pred, H))) return rc;
   if ((rc = upload(h, &h->b_pred, bpred))) return rc;
   // output layer, rows padded with zeros to whole 32-column chunks
   if ((rc = download(h, tmp, w->W_out, (size_t)N * H))) return rc;
   if (bf)
     for (auto &x : tmp) x = host_bf16_round(x);
-  if ((rc = upload(h, &h->W_out, out = to_k4(tmp, N, H, h->n_chunks * 32)))) return rc;
-  if (h->split) {
-    if ((rc = upload(h, &h->W_out_s, out))) return rc;
-    if ((rc = split_rows(h, h->W_out_s, h->n_chunks * 32, H, 1.f, &h->out_unscale))) return rc;
-  }
+  look(tmp);
+  const std::vector<float> w_out_k4 = to_k4(tmp, N, H, h->n_chunks * 32);
+  if ((rc = upload(h, &h->W_out, w_out_k4))) return rc;
   if ((rc = download(h, tmp, w->b_out, N))) return rc;
   out.assign((size_t)h->n_chunks * 32, 0.f);
   for (int i = 0; i < N; ++i) out[i] = tmp[i];
@@ -424,7 +426,7 @@ int pack_weights(rnnt_beam *h, const rnnt_weights_t *w) {
       b_p[r] = bih[o] + bhh[o];
     }
     if ((rc = upload(h, &h->W_hh, to_k4(whh_p, 4 * P, P, 4 * P)))) return rc;
-    if (h->split && (rc = split_rows(h, h->W_hh, 4 * P, P, kHidScale, &h->hh_unscale))) return rc;
+    look(whh_p);
     // G[v] = W_ih emb[v] + b_ih + b_hh for every token (and the start symbol): one GEMM at create
     float *d_wih = nullptr, *d_b = nullptr, *d_emb = nullptr;
     if ((rc = upload(h, &d_wih, wih_p))) return rc;
@@ -450,6 +452,13 @@ int pack_weights(rnnt_beam *h, const rnnt_weights_t *w) {
       if ((rc = launch_gemm(h, nullptr, d_emb + (size_t)i * (V + 1) * P, d_wpred_rm, i == 0 ? h->b_pred : nullptr,
                             h->tab + (size_t)i * (V + 1) * H, V + 1, H, P, bf ? 1 : 0, nullptr)))
         return rc;
+  }
+  h->split = !bf && finite;
+  if (h->split) {
+    if ((rc = upload(h, &h->W_out_s, w_out_k4))) return rc;
+    if ((rc = split_rows(h, h->W_out_s, h->n_chunks * 32, H, 1.f, &h->out_unscale))) return rc;
+    if (c.pred == RNNT_PRED_LSTM && (rc = split_rows(h, h->W_pred, H, P, kHidScale, &h->pred_unscale))) return rc;
+    if (c.pred == RNNT_PRED_LSTM && (rc = split_rows(h, h->W_hh, 4 * P, P, kHidScale, &h->hh_unscale))) return rc;
   }
   RB_HIP(h, hipDeviceSynchronize());
   // the row-major copies were only the operands of the folding products above
@@ -977,7 +986,7 @@ struct DeviceSlot {
 
 int create_resident(rnnt_beam *h, int fail_alloc) {
   const rnnt_config_t &c = h->cfg;
-  const ResidentWeights rw{h->W_hh, h->hh_unscale, h->W_out, h->W_out_s, h->out_unscale, h->W_pred, h->pred_unscale, h->n_chunks * 32};
+  const ResidentWeights rw{h->split, h->W_hh, h->hh_unscale, h->W_out, h->W_out_s, h->out_unscale, h->W_pred, h->pred_unscale, h->n_chunks * 32};
   return c.use_graph && !c.persistent_kernel && !c.async_enqueue ? resident_create(h->res, c, rw, h->err, fail_alloc) : RNNT_OK;
 }
 

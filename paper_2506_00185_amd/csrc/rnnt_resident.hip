@@ -13,8 +13,14 @@ namespace {
 
 __device__ __forceinline__ size_t k4_at(int k, int row, int rows) { return ((size_t)(k >> 2) * rows + row) * 4 + (k & 3); }
 
+// row r of a 16-row tile.  MAP 0: rows as they are; 1: tiles of four LSTM units; 2: tiles of projection outputs
+template <int MAP>
+__device__ __forceinline__ int res_tile_row(int tile, int r) {
+  return MAP == 0 ? 16 * tile + r : MAP == 1 ? 4 * (8 * (tile >> 1) + 2 * (r >> 2) + (tile & 1)) + (r & 3) : res_p_row(tile, r);
+}
+
 // W (k4-major, `rows` rows, split by k_split_rows) -> [tile of 16 rows][wave][kResQuads * 64 words of 16 bytes] (see ResW16),
-// rounds of 8 k, absent ones zero.  MAP 0: rows as they are; 1: tiles of four LSTM units; 2: tiles of projection outputs.
+// rounds of 8 k, absent ones zero.
 // One slice of k per wave: [quadword of a lane][64 lanes], hi and lo of the first two quads of rounds, then those of the last two
 // rounds.  halves: two slices of up to five rounds, one of either half of k; of each hi and lo of a quad, [64 lanes] each, then the
 // fifth round's [32 lanes]: the lanes of even kq.
@@ -34,7 +40,7 @@ __global__ void k_pack_split(const uint32_t *W, int rows, int K, int n_tiles, bo
     int r = at & 15, kq = (at >> 4) & 3;
     if (halves && tail) kq = 2 * (kq & 1);
     const int round = tail ? most + (kq & 1) : 4 * (q >> 1) + 2 * (kq >> 1) + (e >> 1), half = tail ? kq >> 1 : kq & 1;
-    const int row = MAP == 0 ? 16 * tile + r : MAP == 1 ? 4 * (8 * (tile >> 1) + 2 * (r >> 2) + (tile & 1)) + (r & 3) : res_p_row(tile, r);
+    const int row = res_tile_row<MAP>(tile, r);
     // the word of a lane holds k and k + 2 (see res_k_of)
     uint32_t v = 0;
     if (round < n_rounds && row < rows) {
@@ -44,14 +50,15 @@ __global__ void k_pack_split(const uint32_t *W, int rows, int K, int n_tiles, bo
     out[i] = v;
   }
 }
-// W_hh of the bf16-joint models -> [tile of four LSTM units][round][64 lanes][2]
-__global__ void k_pack_units(const float *W, int rows, int K, int n_tiles, float *out) {
+// W as it is -> [tile of 16 rows][round][64 lanes][2].  MAP: as above
+template <int MAP>
+__global__ void k_pack_f32(const float *W, int rows, int K, int n_tiles, float *out) {
   const int n_rounds = K / 8;
   const size_t n = (size_t)n_tiles * n_rounds * 128;
   for (size_t i = (size_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += (size_t)gridDim.x * blockDim.x) {
-    const int e = (int)(i & 1), lane = (int)(i >> 1) & 63, r = lane & 15;
-    const int round = (int)((i >> 7) % n_rounds), tile = (int)((i >> 7) / n_rounds);
-    out[i] = W[k4_at(res_k_of(round, lane >> 4, e), 4 * (8 * (tile >> 1) + 2 * (r >> 2) + (tile & 1)) + (r & 3), rows)];
+    const int e = (int)(i & 1), lane = (int)(i >> 1) & 63;
+    const int round = (int)((i >> 7) % n_rounds), tile = (int)((i >> 7) / n_rounds), row = res_tile_row<MAP>(tile, lane & 15);
+    out[i] = row < rows ? W[k4_at(res_k_of(round, lane >> 4, e), row, rows)] : 0.f;
   }
 }
 // rows row0 .. + 15 as res_fold_mma reads them: [round][64 lanes][2], k = 8 round + lane / 16 and four further
@@ -187,7 +194,7 @@ Plan make_plan(const Resident &r, const rnnt_config_t &c, int B, int K, bool has
   const bool bf = c.prec == RNNT_BF16_JOINT;
   int lds_tiles = 0;
   for (const ResTab &t : p.tab) lds_tiles = std::max(lds_tiles, t.nP + std::max(0, t.nJ - (bf ? kResRegJ<true> : kResRegJ<false>)));
-  const size_t worker = (size_t)lds_tiles * (bf ? std::max(c.pred == RNNT_PRED_LSTM ? c.P : 0, c.H) * kResSlot : kResTileFloats) * 4 +
+  const size_t worker = (size_t)lds_tiles * (r.form == kResSplit ? kResTileFloats : std::max(c.pred == RNNT_PRED_LSTM ? c.P : 0, c.H) * kResSlot) * 4 +
                         (bf && fold ? (size_t)(1 + c.n_durations) * c.H * 2 : 0) + (size_t)2 * (bf ? kResRedBlocks<true> : kResRedBlocks<false>) * kResRedBlock * 4 +
                         (size_t)kResMaxR * p.NT * (256 + 128) * 4 + ResPar::kFloats * 4 + (size_t)p.NT * kResSlot * (sizeof(int2) + kResWaves * 8);
   const size_t sel = (sizeof(ResSelLds) + 15) / 16 * 16 + p.upc * sizeof(SelectScratch) +
@@ -199,11 +206,14 @@ Plan make_plan(const Resident &r, const rnnt_config_t &c, int B, int K, bool has
   return p;
 }
 
+template <bool FULL, bool ST>
+ResKernel pick_form(int form, int K, bool plain) {
+  return form == kResSplit ? resident_kernel<FULL, kResSplit, ST>(K, plain)
+         : form == kResBf16 ? resident_kernel<FULL, kResBf16, ST>(K, plain) : resident_kernel<FULL, kResF32, ST>(K, plain);
+}
 template <bool ST>
-ResKernel pick_kernel(const rnnt_config_t &c, int K, bool plain) {
-  const bool full = c.H == 640 && (ST || c.P == 640), bf = c.prec == RNNT_BF16_JOINT;
-  if (full) return bf ? resident_kernel<true, true, ST>(K, plain) : resident_kernel<true, false, ST>(K, plain);
-  return bf ? resident_kernel<false, true, ST>(K, plain) : resident_kernel<false, false, ST>(K, plain);
+ResKernel pick_kernel(const rnnt_config_t &c, int form, int K, bool plain) {
+  return c.H == 640 && (ST || c.P == 640) ? pick_form<true, ST>(form, K, plain) : pick_form<false, ST>(form, K, plain);
 }
 
 }  // namespace
@@ -250,10 +260,15 @@ int resident_create(Resident &r, const rnnt_config_t &c, const ResidentWeights &
   };
   const int nR = 4 * c.P / 16, nJ = bf ? (N + 31) / 32 : (N + 15) / 16, nP = bf ? c.H / 32 : c.H / 16;
   constexpr size_t kTileWords = kResTileFloats;
-  bool ok = bf ? alloc(&r.WJb, (size_t)nJ * (c.H / 8) * 64) : alloc(&r.WJ, nJ * kTileWords) && alloc(&r.WJs, (size_t)16 * c.H);
+  const bool split = w.split;
+  r.form = bf ? kResBf16 : split ? kResSplit : kResF32;
+  bool ok = bf ? alloc(&r.WJb, (size_t)nJ * (c.H / 8) * 64)
+               : (split ? alloc(&r.WJ, nJ * kTileWords) : alloc(&r.WJf, (size_t)nJ * 16 * c.H)) && alloc(&r.WJs, (size_t)16 * c.H);
   if (lstm) {
-    ok = ok && (bf ? alloc(&r.WRf, (size_t)nR * 16 * c.P) : alloc(&r.WR, nR * kTileWords)) && alloc(&r.hb, kResStepRing * rows * c.P) && alloc(&r.pb, kResStepRing * rows * c.H);
-    ok = ok && (bf ? alloc(&r.WPb, (size_t)nP * (c.P / 8) * 64) : alloc(&r.WP[0], nP * kTileWords) && (c.P % 128 || alloc(&r.WP[1], nP * kTileWords)));
+    ok = ok && (split ? alloc(&r.WR, nR * kTileWords) : alloc(&r.WRf, (size_t)nR * 16 * c.P)) && alloc(&r.hb, kResStepRing * rows * c.P) && alloc(&r.pb, kResStepRing * rows * c.H);
+    ok = ok && (bf      ? alloc(&r.WPb, (size_t)nP * (c.P / 8) * 64)
+                : split ? alloc(&r.WP[0], nP * kTileWords) && (c.P % 128 || alloc(&r.WP[1], nP * kTileWords))
+                        : alloc(&r.WPf, (size_t)nP * 16 * c.P));
   }
   ok = ok && alloc(&r.zb, kResStepRing * rows * w.out_rows) &&
        alloc(&r.words, kResStepRing * rows) && alloc(&r.ctl, 64) && alloc(&r.tab, r.n_cus);
@@ -263,15 +278,17 @@ int resident_create(Resident &r, const rnnt_config_t &c, const ResidentWeights &
   const dim3 grid(512), block(256);
   if (bf) hipLaunchKernelGGL(k_pack_bf16<0>, grid, block, 0, nullptr, w.W_out, w.out_rows, c.H, nJ, r.WJb);
   else {
-    hipLaunchKernelGGL(k_pack_split<0>, grid, block, 0, nullptr, reinterpret_cast<const uint32_t *>(w.W_out_s), w.out_rows, c.H, nJ, false, r.WJ);
+    if (split) hipLaunchKernelGGL(k_pack_split<0>, grid, block, 0, nullptr, reinterpret_cast<const uint32_t *>(w.W_out_s), w.out_rows, c.H, nJ, false, r.WJ);
+    else hipLaunchKernelGGL(k_pack_f32<0>, grid, block, 0, nullptr, w.W_out, w.out_rows, c.H, nJ, r.WJf);
     r.out_unscale = w.out_unscale;
     hipLaunchKernelGGL(k_pack_fold, grid, block, 0, nullptr, w.W_out, w.out_rows, c.V / 16 * 16, c.H, r.WJs);
   }
   if (lstm) {
-    if (bf) hipLaunchKernelGGL(k_pack_units, grid, block, 0, nullptr, w.W_hh, 4 * c.P, c.P, nR, r.WRf);
+    if (!split) hipLaunchKernelGGL(k_pack_f32<1>, grid, block, 0, nullptr, w.W_hh, 4 * c.P, c.P, nR, r.WRf);
     else hipLaunchKernelGGL(k_pack_split<1>, grid, block, 0, nullptr, reinterpret_cast<const uint32_t *>(w.W_hh), 4 * c.P, c.P, nR, false, r.WR);
     r.hh_unscale = w.hh_unscale;
     if (bf) hipLaunchKernelGGL(k_pack_bf16<2>, grid, block, 0, nullptr, w.W_pred, c.H, c.P, nP, r.WPb);
+    else if (!split) hipLaunchKernelGGL(k_pack_f32<2>, grid, block, 0, nullptr, w.W_pred, c.H, c.P, nP, r.WPf);
     else {
       for (int halves = 0; halves < 2; ++halves)
         if (r.WP[halves])
@@ -297,7 +314,7 @@ hipError_t resident_launch(Resident &r, const rnnt_config_t &c, const ResidentBa
   ResArgs a{};
   a.WR = reinterpret_cast<const uintx4_t *>(r.WR); a.WJ = reinterpret_cast<const uintx4_t *>(r.WJ);
   a.WP = reinterpret_cast<const uintx4_t *>(r.WP[b.halves ? 1 : 0]);
-  a.hh_unscale = r.hh_unscale; a.out_unscale = r.out_unscale; a.pred_unscale = r.pred_unscale; a.WRf = r.WRf; a.WJs = r.WJs; a.WJb = r.WJb; a.WPb = r.WPb;
+  a.hh_unscale = r.hh_unscale; a.out_unscale = r.out_unscale; a.pred_unscale = r.pred_unscale; a.WRf = r.WRf; a.WJf = r.WJf; a.WPf = r.WPf; a.WJs = r.WJs; a.WJb = r.WJb; a.WPb = r.WPb;
   a.emb_tab = b.emb_tab; a.n_ctx = b.n_ctx;
   a.b_out = b.b_out; a.b_pred = b.b_pred; a.G = b.G; a.f_proj = b.f_proj;
   a.lengths = b.lengths;
@@ -329,7 +346,7 @@ hipError_t resident_launch(Resident &r, const rnnt_config_t &c, const ResidentBa
   }
   hipLaunchKernelGGL(k_resident_init, dim3(512), dim3(256), 0, s, a);
   const bool plain = c.n_durations == 0 && !b.has_lm && b.algo == RNNT_ALSD;
-  ResKernel k = b.emb_tab ? pick_kernel<true>(c, b.K, plain) : pick_kernel<false>(c, b.K, plain);
+  ResKernel k = b.emb_tab ? pick_kernel<true>(c, r.form, b.K, plain) : pick_kernel<false>(c, r.form, b.K, plain);
   e = hipFuncSetAttribute(reinterpret_cast<const void *>(k), hipFuncAttributeMaxDynamicSharedMemorySize, (int)p.lds);
   if (e != hipSuccess) return e;
   hipLaunchKernelGGL(k, dim3(p.stride * p.n_blocks), dim3(kResThreads), p.lds, s, a);

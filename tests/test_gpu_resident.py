@@ -255,6 +255,51 @@ def test_split_products_over_a_wide_range_of_scales(oracle, h, B, beam):
         np.testing.assert_array_equal(g[key], ref[key])
 
 
+@pytest.mark.parametrize("loop,kw", [
+    ("resident", dict(B=3, beam=4, V=90, H=64, P=64, E=64)), ("resident", dict(B=9, beam=5, V=90, **dict(W640, H=320, P=448))),
+    ("resident", dict(B=5, beam=4, V=90, **W640, **TDT)),
+    # the per-step launches would fold the blank and duration columns
+    ("resident", dict(B=57, beam=4, V=1024, T=6, **W640, **TDT)),
+    ("launches", dict(B=57, beam=4, V=1024, T=6, **W640, **TDT)), ("launches", dict(B=3, beam=4, V=90, H=96, P=96, E=64)),
+    ("launches", dict(B=9, beam=5, V=90, **dict(W640, H=320, P=448))),
+    ("resident", dict(B=3, beam=4, V=90, **W640, **ST, ctx=2)),
+])
+def test_weights_that_are_not_finite(oracle, loop, kw):
+    """A weight of -inf closes what it leads to (a token, a duration, a unit of the joint, a forget gate) and a token whose row holds a
+    NaN is no candidate: the same as finite weights with biases of -inf or -1e30 there (the oracle's)."""
+    import paper_2506_00185_amd as A
+    c = S.custom_config(**dict(dict(T=12, T_min=3, s=3, blank_bias=3.0, D=64), **kw))
+    w = {k: np.array(v) for k, v in S.make_weights(c, 91).items()}
+    L = S.make_lengths(c, 92)
+    enc = S.make_enc(c, L, 93)
+    V, P, lstm = c["V"], c["P"], c["pred"] == "lstm"
+    on, off, unit, gate = 5, 9, 7, 3   # joint: a unit that is always active, one to be closed; LSTM: a positive unit, a forget gate
+    w["W_enc"][on] = w["W_pred"][on] = 0.0
+    w["b_pred"][on] = 2.0
+    w["W_out"][:, on] = 0.0
+    closed = [V // 2, V - 1] + ([V + 2] if c["durations"] else [])  # two tokens, a duration
+    w["b_out"][closed] = 6.0           # (they would win often)
+    if lstm:
+        w["b_ih"][2 * P + unit] = 20.0  # cell candidate and gates of the unit: its state stays positive
+        w["b_ih"][3 * P + unit] = w["b_ih"][unit] = 5.0
+    ref = {k: v.copy() for k, v in w.items()}
+    w["W_out"][closed, on] = -np.inf
+    if loop == "resident":             # (the per-step launches add NaN logits up)
+        w["W_out"][V // 3, off] = np.nan
+        ref["b_out"][V // 3] = -np.inf
+    ref["b_out"][closed] = -np.inf
+    if lstm:
+        w["W_hh"][P + gate, unit] = w["W_pred"][off, unit] = -np.inf
+        ref["b_ih"][P + gate] = ref["b_pred"][off] = -1e30
+    dec = A.BeamDecoder(c, w, use_graph=loop == "resident")
+    g = gpu_decode(dec, enc, L)
+    assert dec.last_step_loop() == loop
+    o = oracle.decode(c, ref, enc, L, log=True)
+    full, exempt = compare(g, o, 1e-3, 1e-4)
+    assert full >= (c["B"] + 1) // 2
+    assert not np.isin(g["tokens"], closed[:2] + ([V // 3] if loop == "resident" else [])).any()
+
+
 @pytest.mark.parametrize("kw", [dict(B=5, beam=4), dict(B=17, beam=9, prec="bf16"), dict(B=8, beam=4, **ST, ctx=2)], ids=["lstm", "bf16", "stateless"])
 def test_groups_that_do_not_lie_on_one_xcd(kw):
     """Their hand-over stores are written through: the same words arrive."""
