@@ -152,19 +152,22 @@ bool assign_tiles(const rnnt_config_t &c, int n_blocks, std::vector<ResTab> &tab
 
 // Decoders that stay with the per-step launches although they fit the loop: narrow ones, whose per-step launches are short, with
 // several tiles of slots or wide beams, whose selection takes longer here.  Both sides timed in turn, time of the per-step launches
-// over the loop's.  LSTM decoders wider than 192: 1.01 and more at each of 250 shapes of two and three tiles (256 to 512 wide, V = 29
+// over the loop's.  Split decoders (320 wide and more): 1.01 and more at each of 250 shapes of two and three tiles (to 512 wide, V = 29
 // to 1000, beams 5 to 16, LM and TDT among them; means 1.33 in float32, 1.23 with the bf16 joint); 640 wide 1.07 and more.
-bool per_step_is_faster(const rnnt_config_t &c, int B, int K, int n_tiles) {
+bool per_step_is_faster(const Resident &r, const rnnt_config_t &c, int B, int K, int n_tiles) {
   const bool bf = c.prec == RNNT_BF16_JOINT;
-  if (c.pred != RNNT_PRED_LSTM)  // bf16, one utterance, up to 320 wide: 0.96 to 1.20.  Others up to 128 wide: 1.08 to 1.53, not moved yet
+  if (c.pred != RNNT_PRED_LSTM)  // 64 and 128 wide, V = 1000: 0.95 to 1.34 (one utterance below 1.08); bf16, one utterance, 320 wide: 1.07 and 1.12
     return K > 8 && (c.H <= 128 || (bf && B == 1 && c.H <= 320));
+  // float32 instructions, 64 to 256 wide, one tile: 1.23 to 1.98; two tiles, beams up to 8: 1.24 to 1.53
   if (std::max(c.H, c.P) <= 192) {
-    // float32, three tiles: V = 100 0.94 to 1.01, V = 500 at beams from 9 on 0.88 to 1.01 (at smaller beams 1.13 to 1.22)
+    // float32, three tiles: V = 1000 at beams up to 8 1.15 to 1.28, else 0.85 to 1.62
     if (!bf && n_tiles == 3 && !(c.V > 512 && K <= 8)) return true;
-    // two tiles: V = 450 0.97 to 1.84, V > 512 1.00 to 1.34; three, float32, V = 1000: 1.05 to 1.07
+    // two tiles, beams above 8, float32: V = 29 and 260 1.13 to 1.72, V = 500 0.97 to 1.42, V = 1000 1.05 to 1.16 (not moved yet);
+    // bf16: V = 450 0.97 to 1.84, V > 512 1.00 to 1.34
     return n_tiles > 1 && K > 8 && c.V > (bf ? 512 : 384);
   }
-  return false;
+  // 256 wide, three tiles: V up to 500 at beam 4 0.92 to 0.98, else 0.95 to 1.53, most above 1
+  return r.form == kResF32 && n_tiles == 3 && K <= 4 && c.V <= 512;
 }
 
 Plan make_plan(const Resident &r, const rnnt_config_t &c, int B, int K, bool has_lm, bool fold) {
@@ -185,7 +188,7 @@ Plan make_plan(const Resident &r, const rnnt_config_t &c, int B, int K, bool has
   // per-step launches are as fast or faster (float32, 640 wide, us per step here / there: batch 32 beam 4 13.1 / 19.1; two
   // tiles, batch 16 beam 16 34.8 / 33.3; three, batch 32 beam 12 37.3 / 36.0)
   if (c.pred != RNNT_PRED_LSTM && p.NT > 1) return p;
-  if (per_step_is_faster(c, B, K, p.NT)) return p;
+  if (per_step_is_faster(r, c, B, K, p.NT)) return p;
   const int most_sel = std::max(1, p.n_blocks / 8);
   p.upc = (p.nu + most_sel - 1) / most_sel;
   if (p.upc > kResMaxSel || p.upc * K * K > 512 || p.upc * K > kResMaxHyps) return p;

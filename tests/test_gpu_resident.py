@@ -300,6 +300,25 @@ def test_weights_that_are_not_finite(oracle, loop, kw):
     assert not np.isin(g["tokens"], closed[:2] + ([V // 3] if loop == "resident" else [])).any()
 
 
+@pytest.mark.parametrize("h,p,more", [(64, 64, {}), (256, 256, {}), (640, 128, dict(V=700)), (192, 640, dict(B=9)), (256, 64, ST),
+                                      (96, 160, {}), (128, 128, dict(B=10, beam=10, V=500))])
+def test_narrow_decoders_multiply_in_float32(h, p, more):
+    """... as they do with a weight that has no split: a token that a bias has closed anyhow is closed by such a weight too."""
+    import paper_2506_00185_amd as A
+    c = S.custom_config(**dict(dict(B=5, T=12, T_min=6, s=3, V=90, beam=4, blank_bias=3.0, H=h, P=p, E=64, D=64, ctx=2 if more is ST else 0), **more))
+    w = {k: np.array(v) for k, v in S.make_weights(c, 75).items()}
+    w["W_enc"][0] = w["W_pred"][0] = 0.0
+    w["b_pred"][0] = 1.0                        # a unit that is always active
+    w["b_out"][c["V"] - 1] = -1e30
+    ref = {k: np.array(v) for k, v in w.items()}
+    ref["W_out"][c["V"] - 1, 0] = -np.inf
+    L = S.make_lengths(c, 77)
+    enc = S.make_enc(c, L, 78)
+    got, want = [gpu_decode(A.BeamDecoder(c, x), enc, L) for x in (w, ref)]
+    for key in KEYS:
+        np.testing.assert_array_equal(got[key], want[key])
+
+
 @pytest.mark.parametrize("kw", [dict(B=5, beam=4), dict(B=17, beam=9, prec="bf16"), dict(B=8, beam=4, **ST, ctx=2)], ids=["lstm", "bf16", "stateless"])
 def test_groups_that_do_not_lie_on_one_xcd(kw):
     """Their hand-over stores are written through: the same words arrive."""
