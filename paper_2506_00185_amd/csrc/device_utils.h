@@ -60,12 +60,12 @@ __device__ __forceinline__ floatx16 mfma32_bf16_from_f32(float4 a0, float4 a1, f
 }
 
 // ---- float32 products on the 16-bit matrix cores
-// A float32 x as hi + lo, hi = x rounded to float16, lo = the rest rounded to float16: exact to 2^-24 of x, half a unit in the
-// last place of float32, as long as lo is no subnormal number, which scaling by a power of two takes care of.  A product is then
-// hi hi + (hi lo + lo hi); the term left out, lo lo, is 2^-24 of it at most.  Three float16 matrix instructions replace eight
-// float32 ones of twice the cycles each.  Error of sums of 640 products against 64 bits, relative 2-norm (normal weights, h in
-// (-1, 1)): 1.2e-7, with the float32 matrix instructions 1.7e-7, whose chain rounds after every product (these round once per
-// eight); with the two sums in one accumulator 1.4e-7.
+// A float32 x as hi + lo, hi = x rounded to float16, lo = the rest rounded to float16 and kept 2^11 times as large, so that neither is a
+// subnormal number for x down to 2^-28 of the largest that shares its scale: x to 2^-23 of itself (a unit in the last place of float32,
+// for a quarter of all x; the others exactly).  Smaller ones are right to 2^-50 of the largest.  A product is then hi hi + (hi lo + lo hi)
+// 2^-11; the term left out, lo lo, is 2^-22 of it at most.  Three float16 matrix instructions replace eight float32 ones of twice the
+// cycles each.  (Unscaled, lo is a subnormal number below 2^-15 of the largest: with one weight of a row 2^24 times the others the
+// error of their products was 1.3e-5.  The scale takes a multiplication per pair of values, less than 1 % of a decode.)
 // How the instructions add up (measured): acc + the eight products of one lane in one rounding, the lanes of a row or column
 // one after the other in the order of their k.  Which of the shapes 32x32x16, 16x16x32 and 16x16x16 takes the k does not matter.
 typedef _Float16 f16x2_t __attribute__((ext_vector_type(2)));
@@ -73,18 +73,24 @@ typedef _Float16 f16x4_t __attribute__((ext_vector_type(4)));
 typedef _Float16 f16x8_t __attribute__((ext_vector_type(8)));
 constexpr float kHidScale = 32768.f;  // of hidden states, whose values lie in [-1, 1]
 // Of values whose size is not known ahead (the joint's activations): m, the largest of a hypothesis in a slice of the k, goes to
-// [2^14, 2^15).  inv takes the scale off the slice's sum again.
+// [2^14, 2^15) (from 2^-84 on).  inv takes the scale off the slice's sum again, and kActUnscale more, for the largest sums of the largest
+// values to stay finite, which the scale of the weights' rows gives back.
+constexpr float kActUnscale = 1.f / (1 << 25);
 __device__ __forceinline__ float split_scale(float m, float &inv) {
   uint32_t e = __float_as_uint(m) & 0x7f800000u;
-  e = e > 18u << 23 ? e : 18u << 23;
-  inv = __uint_as_float(e - (14u << 23));
+  e = e > 43u << 23 ? e : 43u << 23;
+  inv = __uint_as_float(e - (39u << 23));
   return __uint_as_float((268u << 23) - e);
 }
+constexpr float kLoScale = 2048.f;
+// acc + the sum of the products with a lo in them
+template <class V>
+__device__ __forceinline__ V split_join(V acc, V cor) { return acc + cor * (1.f / kLoScale); }
 // two values -> their two hi and their two lo, each pair in one word
 __device__ __forceinline__ void split_f16(float a, float b, uint32_t &hi, uint32_t &lo) {
   const floatx2_t v = {a, b};
   const f16x2_t h = __builtin_convertvector(v, f16x2_t);
-  const floatx2_t r = {a - (float)h[0], b - (float)h[1]};
+  const floatx2_t r = {(a - (float)h[0]) * kLoScale, (b - (float)h[1]) * kLoScale};
   hi = __builtin_bit_cast(uint32_t, h);
   lo = __builtin_bit_cast(uint32_t, __builtin_convertvector(r, f16x2_t));
 }

@@ -105,7 +105,7 @@ __device__ __forceinline__ void splitk_mma(SplitKOperands<ITERS> &op, AL a_at, B
         mfma32_split<4>(w, x, scale, acc, cor);
       }
     }
-    acc += cor;
+    acc = split_join(acc, cor);
     if (ACT) acc *= inv;
   } else if constexpr (ITERS > 0) {
     if (bf16) {
@@ -311,7 +311,7 @@ __host__ __device__ __forceinline__ int xcd_item(const XcdMap &m, int bid, int &
 
 // Splits a k4-major matrix in place (see split_f16), each row scaled by a power of two that brings its largest element to
 // [2^14, 2^15): the 16 bytes of four k become their four hi, then their four lo.  unscale[row] takes that scale, and x_scale, off
-// a sum.  For finite weights only: NaN and infinities have no split.
+// a sum.  For finite rows whose largest is 0 or not far from 1 (see splittable).
 // 64 rows x 4 parts of the k per block.
 __global__ __launch_bounds__(256) void k_split_rows(float *W, int rows, int K, float x_scale, float *unscale) {
   __shared__ float s_max[4][64];
@@ -329,7 +329,7 @@ __global__ __launch_bounds__(256) void k_split_rows(float *W, int rows, int K, f
   if (row >= rows) return;
   int e = 0;  // m in [2^(e - 1), 2^e)
   if (m > 0.f) frexpf(m, &e);
-  e = 15 - e < 100 ? 15 - e : 100;
+  e = 15 - e;
   const float scale = ldexpf(1.f, e);
   if (part == 0) unscale[row] = ldexpf(1.f / x_scale, -e);
   for (int i = part; i < K / 4; i += 4) {
@@ -423,7 +423,7 @@ __device__ __forceinline__ void recurrent_tiles(const RecurrentArgs &a, int tile
     if constexpr (SPLIT) {
       floatx16 cor = acc;
       mfma32_split_rounds<ITERS>(wa, hb[g & 1], kHidScale, acc, cor);
-      acc += cor;
+      acc = split_join(acc, cor);
     } else {
 #pragma unroll
       for (int i = 0; i < ITERS; ++i) {

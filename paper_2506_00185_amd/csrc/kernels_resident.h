@@ -741,7 +741,7 @@ __device__ __forceinline__ void res_p_phase(ResBlock &k, int step) {
               cor = mfma16_f16(vh, yl[hf], cor);
               cor = mfma16_f16(vl, yh[hf], cor);
             }
-            res_put<false>(k, l, hf, acc + cor);
+            res_put<false>(k, l, hf, split_join(acc, cor));
             __builtin_amdgcn_sched_barrier(0);  // (both halves at once need more registers than there are)
           }
           finish(tp);
@@ -758,7 +758,7 @@ __device__ __forceinline__ void res_p_phase(ResBlock &k, int step) {
           const ResW16 w[1] = {res_split_load(tiles + (size_t)tp * (kResTileFloats / 4), l)};
           floatx4 acc[1], cor[1];
           res_split_mma<FULL, 0, 1>(w, xs, nr, acc, cor);
-          res_put<false>(k, l, 0, acc[0] + cor[0]);
+          res_put<false>(k, l, 0, split_join(acc[0], cor[0]));
           finish(tp);
         }
       }
@@ -1050,19 +1050,19 @@ __device__ __forceinline__ void res_j_phase(ResBlock &k, int step, const ResWJ<F
         floatx4 c1[1], d1[1];
         res_split_mma<FULL, 1, 1>(wj.t, xs, nr, c1, d1);
         res_put<false>(k, l, 0, res_fold_mma([&](int i) { return res_raw(wj.t[0], i); }, x));
-        if (1 < k.nJ) res_put<false>(k, l, 1, (c1[0] + d1[0]) * inv);
+        if (1 < k.nJ) res_put<false>(k, l, 1, split_join(c1[0], d1[0]) * inv);
       } else {
         floatx4 acc[NJ], cor[NJ];
         res_split_mma<FULL, 0, NJ>(wj.t, xs, nr, acc, cor);
 #pragma unroll
         for (int t = 0; t < NJ; ++t)
-          if (t < k.nJ) res_put<false>(k, l, t, (acc[t] + cor[t]) * inv);
+          if (t < k.nJ) res_put<false>(k, l, t, split_join(acc[t], cor[t]) * inv);
       }
       if (k.nJ > NJ) {
         const ResW16 w[1] = {res_split_load(reinterpret_cast<const uintx4_t *>(k.tiles) + (size_t)k.nP * (kResTileFloats / 4) + (size_t)k.wave * kResQuads * 64, l)};
         floatx4 c1[1], d1[1];
         res_split_mma<FULL, 0, 1>(w, xs, nr, c1, d1);
-        res_put<false>(k, l, NJ, (c1[0] + d1[0]) * inv);
+        res_put<false>(k, l, NJ, split_join(c1[0], d1[0]) * inv);
       }
       done();
       }
@@ -1355,7 +1355,7 @@ __device__ __forceinline__ void res_worker(ResBlock k, const ResTab &tab, float 
             floatx4 cor[3];
             res_split_mma<FULL, t0, 3>(wr.t, xs, nrp, acc, cor);
 #pragma unroll
-            for (int t = 0; t < 3; ++t) acc[t] += cor[t];
+            for (int t = 0; t < 3; ++t) acc[t] = split_join(acc[t], cor[t]);
           }
 #pragma unroll
           for (int t = 0; t < 3; ++t)

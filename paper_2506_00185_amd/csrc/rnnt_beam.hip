@@ -340,22 +340,34 @@ int split_rows(rnnt_beam *h, float *W, int rows, int K, float x_scale, float **u
   return RNNT_OK;
 }
 
+// Rows of K weights that k_split_rows can split: NaN and infinities have no split, and scales beyond 2^64 either way would take sums
+// that float32 holds out of its range.
+bool splittable(const std::vector<float> &W, int K) {
+  for (size_t i = 0; i < W.size(); i += K) {
+    float m = 0.f;
+    for (int k = 0; k < K; ++k) {
+      const float x = std::fabs(W[i + k]);
+      if (!(x <= 0x1p64f)) return false;
+      m = std::max(m, x);
+    }
+    if (m > 0.f && m < 0x1p-64f) return false;
+  }
+  return true;
+}
+
 constexpr int kSplitWidth = 320;  // H and P of decoders with split weights
 
 int pack_weights(rnnt_beam *h, const rnnt_weights_t *w) {
   const rnnt_config_t &c = h->cfg;
   const int H = c.H, P = c.P, D = c.D, E = c.E, V = c.V, N = h->N;
   const bool bf = c.prec == RNNT_BF16_JOINT;
-  // Split products (see split_f16) for float32 models whose weights are finite (NaN and infinities have no split) and whose sums are
+  // Split products (see split_f16) for float32 models whose weights have a split and whose sums are
   // long enough: a split operand is off by a unit in its last place now and then, the same way in every step, which fewer
   // roundings of the sum have to make up for.  Error of scores against 64 bits, split over float32 (1600 utterances each, plus or minus
   // 0.02): LSTM decoders 256 wide 1.05, 320 1.02, 384 1.00, 512 0.99, 640 1.01; 64 to 192 wide (380 utterances) 1.02 to 1.09.
   // (Not for the bf16 joint: its rounding of the activations turns any other order of the sums into other near ties.)
   const bool lstm = c.pred == RNNT_PRED_LSTM, wide = std::min(H, lstm ? P : H) >= kSplitWidth;
-  bool finite = true;
-  auto look = [&](const std::vector<float> &v) {
-    for (float x : v) finite = finite && std::isfinite(x);
-  };
+  bool can_split = !bf && wide;
   std::vector<float> tmp, out;
   std::vector<void *> staging;  // device buffers needed only until the folded tables have been computed
   int rc;
@@ -375,14 +387,14 @@ int pack_weights(rnnt_beam *h, const rnnt_weights_t *w) {
   if ((rc = upload(h, &d_wpred_rm, wpred))) return rc;
   staging.push_back(d_wpred_rm);
   if ((rc = upload(h, &h->W_pred, to_k4(wpred, H, P, H)))) return rc;
-  if (lstm) look(wpred);  // (stateless: of the tables only)
+  if (lstm) can_split = can_split && splittable(wpred, P);  // (stateless: of the tables only)
   if ((rc = download(h, bpred, w->b_pred, H))) return rc;
   if ((rc = upload(h, &h->b_pred, bpred))) return rc;
   // output layer, rows padded with zeros to whole 32-column chunks
   if ((rc = download(h, tmp, w->W_out, (size_t)N * H))) return rc;
   if (bf)
     for (auto &x : tmp) x = host_bf16_round(x);
-  look(tmp);
+  can_split = can_split && splittable(tmp, H);
   const std::vector<float> w_out_k4 = to_k4(tmp, N, H, h->n_chunks * 32);
   if ((rc = upload(h, &h->W_out, w_out_k4))) return rc;
   if ((rc = download(h, tmp, w->b_out, N))) return rc;
@@ -432,7 +444,7 @@ int pack_weights(rnnt_beam *h, const rnnt_weights_t *w) {
       b_p[r] = bih[o] + bhh[o];
     }
     if ((rc = upload(h, &h->W_hh, to_k4(whh_p, 4 * P, P, 4 * P)))) return rc;
-    look(whh_p);
+    can_split = can_split && splittable(whh_p, P);
     // G[v] = W_ih emb[v] + b_ih + b_hh for every token (and the start symbol): one GEMM at create
     float *d_wih = nullptr, *d_b = nullptr, *d_emb = nullptr;
     if ((rc = upload(h, &d_wih, wih_p))) return rc;
@@ -459,10 +471,10 @@ int pack_weights(rnnt_beam *h, const rnnt_weights_t *w) {
                             h->tab + (size_t)i * (V + 1) * H, V + 1, H, P, bf ? 1 : 0, nullptr)))
         return rc;
   }
-  h->split = !bf && finite && wide;
+  h->split = can_split;
   if (h->split) {
     if ((rc = upload(h, &h->W_out_s, w_out_k4))) return rc;
-    if ((rc = split_rows(h, h->W_out_s, h->n_chunks * 32, H, 1.f, &h->out_unscale))) return rc;
+    if ((rc = split_rows(h, h->W_out_s, h->n_chunks * 32, H, kActUnscale, &h->out_unscale))) return rc;
     if (lstm && (rc = split_rows(h, h->W_pred, H, P, kHidScale, &h->pred_unscale))) return rc;
     if (lstm && (rc = split_rows(h, h->W_hh, 4 * P, P, kHidScale, &h->hh_unscale))) return rc;
   }

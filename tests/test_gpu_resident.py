@@ -230,7 +230,7 @@ def test_logits_that_do_not_come_end_the_resident_loop_as_a_whole(kw, step):
 def test_split_products_over_a_wide_range_of_scales(oracle, h, B, beam):
     """Outputs of the prediction and encoder projections times powers of two from 2^-6 to 2^6, columns of the output layer by their
     inverses: the same function (ReLU is homogeneous), but rows, columns and activations of sizes far apart, which the split into
-    float16 has to scale.  The tolerance is that of float32 models: a value down to 2^-16 of the largest keeps 24 bits."""
+    float16 has to scale.  The tolerance is that of float32 models: a value down to 2^-28 of the largest keeps 23 bits."""
     import paper_2506_00185_amd as A
     c = S.custom_config(B=B, T=12, T_min=6, s=3, V=90, beam=beam, blank_bias=3.0, H=h, P=h, E=64, D=64)
     w = {k: np.array(v) for k, v in S.make_weights(c, 75).items()}
@@ -298,6 +298,45 @@ def test_weights_that_are_not_finite(oracle, loop, kw):
     full, exempt = compare(g, o, 1e-3, 1e-4)
     assert full >= (c["B"] + 1) // 2
     assert not np.isin(g["tokens"], closed[:2] + ([V // 3] if loop == "resident" else [])).any()
+
+
+@pytest.mark.parametrize("h,B,beam,apart,huge", [(320, 9, 5, 0, 0), (640, 5, 9, 13, 0), (640, 17, 4, 0, 0), (576, 3, 4, 13, 0), (640, 3, 4, 0, 2.0 ** 90),
+                                                 (320, 3, 4, 13, 2.0 ** -100)])
+def test_split_products_of_rows_with_outliers(oracle, h, B, beam, apart, huge):
+    """Units up to 2^26 apart, as above, or in every row of W_out a weight 2^26 times the others on a unit that is never active; in those of
+    W_pred and W_hh too: the same function.  23 bits of every operand remain: the tolerance is that of float32 models.  huge: rows that
+    are not split at all."""
+    import paper_2506_00185_amd as A
+    c = S.custom_config(B=B, T=12, T_min=6, s=3, V=90, beam=beam, blank_bias=3.0, H=h, P=h, E=64, D=64)
+    w = {k: np.array(v) for k, v in S.make_weights(c, 81).items()}
+    L = S.make_lengths(c, 82)
+    enc = S.make_enc(c, L, 83)
+    off, silent, P = 3, 5, h
+    w["b_pred"][off] = -1e9                      # joint: ReLU gives 0
+    w["b_ih"][3 * P + silent] = -1e9             # LSTM: the output gate is shut
+    f = (2.0 ** np.random.default_rng(84).integers(-apart, apart + 1, h)).astype(np.float32)
+    f[off] = 1.0
+    for k in ("W_enc", "W_pred"):
+        w[k] = w[k] * f[:, None]
+    for k in ("b_enc", "b_pred"):
+        w[k] = w[k] * f
+    w["W_out"] = w["W_out"] / f[None, :]
+    ref = {k: np.array(v) for k, v in w.items()}
+    if not apart:
+        w["W_out"][:, off] = np.float32(max(huge, 2.0 ** 26 * np.abs(w["W_out"]).mean()))
+    w["W_pred"][:, silent] *= 2.0 ** 26
+    w["W_hh"][:, silent] = np.float32(2.0 ** 26 * np.abs(w["W_hh"]).mean())
+    if huge and huge < 1.0:
+        w["W_hh"][P + 7] = ref["W_hh"][P + 7] = huge
+    dec = A.BeamDecoder(c, w)
+    g = gpu_decode(dec, enc, L)
+    assert dec.last_step_loop() == "resident"
+    o = oracle.decode(c, ref, enc, L, log=True)
+    full, exempt = compare(g, o, 1e-3, 1e-4)
+    assert full >= (c["B"] + 1) // 2
+    ref = gpu_decode(A.BeamDecoder(c, w, use_graph=False), enc, L)
+    for key in KEYS:
+        np.testing.assert_array_equal(g[key], ref[key])
 
 
 @pytest.mark.parametrize("h,p,more", [(64, 64, {}), (256, 256, {}), (640, 128, dict(V=700)), (192, 640, dict(B=9)), (256, 64, ST),
