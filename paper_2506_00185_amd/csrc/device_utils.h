@@ -63,8 +63,8 @@ __device__ __forceinline__ floatx16 mfma32_bf16_from_f32(float4 a0, float4 a1, f
 // A float32 x as hi + lo, hi = x rounded to float16, lo = the rest rounded to float16 and kept 2^11 times as large, so that neither is a
 // subnormal number for x down to 2^-28 of the largest that shares its scale: x to 2^-23 of itself (a unit in the last place of float32,
 // for a quarter of all x; the others exactly).  Smaller ones are right to 2^-50 of the largest.  A product is then hi hi + (hi lo + lo hi)
-// 2^-11; the term left out, lo lo, is 2^-22 of it at most.  Three float16 matrix instructions replace eight float32 ones of twice the
-// cycles each.  (Unscaled, lo is a subnormal number below 2^-15 of the largest: with one weight of a row 2^24 times the others the
+// 2^-11, to which decoders less than 640 wide add lo lo 2^-22 (see kSplitLoLo).  Three or four float16 matrix instructions replace eight
+// float32 ones of twice the cycles each.  (Unscaled, lo is a subnormal number below 2^-15 of the largest: with one weight of a row 2^24 times the others the
 // error of their products was 1.3e-5.  The scale takes a multiplication per pair of values, less than 1 % of a decode.)
 // How the instructions add up (measured): acc + the eight products of one lane in one rounding, the lanes of a row or column
 // one after the other in the order of their k.  Which of the shapes 32x32x16, 16x16x32 and 16x16x16 takes the k does not matter.
@@ -86,6 +86,18 @@ constexpr float kLoScale = 2048.f;
 // acc + the sum of the products with a lo in them
 template <class V>
 __device__ __forceinline__ V split_join(V acc, V cor) { return acc + cor * (1.f / kLoScale); }
+// Whether and how a decoder's weights are split.  kSplitLoLo: with the products of two lo, up to 2^-22 of a product, which the sums of
+// 640 make up for and those of 320 do not: error of scores with large logits against 64 bits, split over float32 (plus or minus 0.02),
+// 320 wide 1.04 without them and 1.01 with them, 384 0.99 / 0.96, 512 0.99 / 0.97, 640 0.91 / 0.90.  320 wide they cost 1 % of a decode;
+// 640 wide, where they take registers that there are not, 7 %.
+constexpr int kNotSplit = 0, kSplit = 1, kSplitLoLo = 2;
+// lo words without their scale
+template <class V>
+__device__ __forceinline__ V unscaled_lo(V lo) {
+  constexpr int N = sizeof(V) / 2;
+  typedef _Float16 Halves __attribute__((ext_vector_type(N)));
+  return __builtin_bit_cast(V, __builtin_bit_cast(Halves, lo) * (_Float16)(1.f / kLoScale));
+}
 // two values -> their two hi and their two lo, each pair in one word
 __device__ __forceinline__ void split_f16(float a, float b, uint32_t &hi, uint32_t &lo) {
   const floatx2_t v = {a, b};
@@ -106,7 +118,7 @@ __device__ __forceinline__ floatx4 mfma16_f16(uintx2_t a, uintx2_t b, floatx4 ac
 // 32x32x16 steps of a split product on N (two or four) consecutive 8-k rounds of the float32 scheme (see mfma32): weights come
 // split and scaled (k_split_rows), activations are scaled and split here.  The order in `cor` is that of the 16x16x32 instructions of the
 // resident loop, which take four rounds at a time.
-template <int N>
+template <int N, bool LOLO>
 __device__ __forceinline__ void mfma32_split(const float4 (&a)[N], const float4 (&b)[N], float scale, floatx16 &acc, floatx16 &cor) {
   uintx4_t wh[N / 2], wl[N / 2], xh[N / 2], xl[N / 2];
 #pragma unroll
@@ -128,9 +140,13 @@ __device__ __forceinline__ void mfma32_split(const float4 (&a)[N], const float4 
   for (int i = 0; i < N / 2; ++i) cor = mfma32_f16(wh[i], xl[i], cor);
 #pragma unroll
   for (int i = 0; i < N / 2; ++i) cor = mfma32_f16(wl[i], xh[i], cor);
+  if constexpr (LOLO) {
+#pragma unroll
+    for (int i = 0; i < N / 2; ++i) cor = mfma32_f16(wl[i], unscaled_lo(xl[i]), cor);
+  }
 }
 // the same on ITERS rounds
-template <int ITERS>
+template <int ITERS, bool LOLO>
 __device__ __forceinline__ void mfma32_split_rounds(const float4 (&a)[ITERS], const float4 (&b)[ITERS], float scale, floatx16 &acc, floatx16 &cor) {
   const float4 zero4 = make_float4(0.f, 0.f, 0.f, 0.f);
 #pragma unroll
@@ -140,12 +156,12 @@ __device__ __forceinline__ void mfma32_split_rounds(const float4 (&a)[ITERS], co
       const int i3 = four ? i + 3 : i;
       const float4 w[4] = {a[i], a[i + 1 < ITERS ? i + 1 : i], a[i + 2 < ITERS ? i + 2 : i], four ? a[i3] : zero4};
       const float4 x[4] = {b[i], b[i + 1 < ITERS ? i + 1 : i], b[i + 2 < ITERS ? i + 2 : i], four ? b[i3] : zero4};
-      mfma32_split<4>(w, x, scale, acc, cor);
+      mfma32_split<4, LOLO>(w, x, scale, acc, cor);
     } else {
       const bool two = i + 1 < ITERS;
       const int i1 = two ? i + 1 : i;
       const float4 w[2] = {a[i], two ? a[i1] : zero4}, x[2] = {b[i], two ? b[i1] : zero4};
-      mfma32_split<2>(w, x, scale, acc, cor);
+      mfma32_split<2, LOLO>(w, x, scale, acc, cor);
     }
   }
 }

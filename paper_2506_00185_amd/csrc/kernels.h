@@ -66,7 +66,7 @@ __device__ __forceinline__ float max_of_halves(float m) {
 // eight float32 ones; the accumulation stays float32.
 // xw (ITERS > 0 only): this lane's k values of one more output row; the lane's part of that row's product with its
 // hypothesis goes into the spare float of its slot in red (extra_value() sums the parts).
-template <int WAVES, int ITERS, Prod PROD, class AL, class BL, class FB>
+template <int WAVES, int ITERS, Prod PROD, bool LOLO, class AL, class BL, class FB>
 __device__ __forceinline__ void splitk_mma(SplitKOperands<ITERS> &op, AL a_at, BL b_at, FB fb, int K, float *red,
                                            int bf16 = 0, const float4 *xw = nullptr) {
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, half = lane >> 5;
@@ -87,7 +87,7 @@ __device__ __forceinline__ void splitk_mma(SplitKOperands<ITERS> &op, AL a_at, B
         if (ACT) larger(b[i]);
       }
       if (ACT) scale = split_scale(max_of_halves(m), inv);
-      mfma32_split_rounds<ITERS>(op.a, b, scale, acc, cor);
+      mfma32_split_rounds<ITERS, LOLO>(op.a, b, scale, acc, cor);
     } else {
       if constexpr (ACT) {
         for (int k = kbeg; k < kend; k += 8) larger(fb(b_at(k)));
@@ -102,7 +102,7 @@ __device__ __forceinline__ void splitk_mma(SplitKOperands<ITERS> &op, AL a_at, B
           w[i] = in ? w1 : zero4;
           x[i] = in ? x1 : zero4;
         }
-        mfma32_split<4>(w, x, scale, acc, cor);
+        mfma32_split<4, LOLO>(w, x, scale, acc, cor);
       }
     }
     acc = split_join(acc, cor);
@@ -353,8 +353,8 @@ struct RecurrentArgs {
 };
 constexpr int kRecGroup = 4;
 
-// SPLIT: Whh is split (k_split_rows)
-template <int WAVES, int ITERS, bool SPLIT>
+// SPLIT: how Whh is split (k_split_rows)
+template <int WAVES, int ITERS, int SPLIT>
 __device__ __forceinline__ void recurrent_tile(const RecurrentArgs &a, int tile, int m0, int done, float *red) {
   constexpr int LPH = 2 * WAVES, VPL = 32 / LPH;
   const int tid = threadIdx.x, lane = tid & 63, col = lane & 31;
@@ -371,7 +371,7 @@ __device__ __forceinline__ void recurrent_tile(const RecurrentArgs &a, int tile,
 #pragma unroll
   for (int q = 0; q < VPL; ++q) us[q] = SPLIT ? a.unscale[tile * 32 + i0 + q] : 1.f;
   if (done) return;
-  splitk_mma<WAVES, ITERS, SPLIT ? Prod::kSplitHidden : Prod::kPlain>(op, a_at, b_at, [](float4 v) { return v; }, a.P, red);
+  splitk_mma<WAVES, ITERS, SPLIT ? Prod::kSplitHidden : Prod::kPlain, SPLIT == kSplitLoLo>(op, a_at, b_at, [](float4 v) { return v; }, a.P, red);
   const int m = m0 + j;
   if (m < a.M) {
 #pragma unroll
@@ -382,7 +382,7 @@ __device__ __forceinline__ void recurrent_tile(const RecurrentArgs &a, int tile,
 // The same for up to G slot tiles in a row (item `grp` of the tile's row: slot tiles grp * G ...): the 32 gate rows
 // stay in registers, and the slots of the next tile are requested before the matrix instructions of the current one
 // start, so that a block streams half as much per tile and streams while it multiplies.
-template <int WAVES, int ITERS, bool SPLIT, int G>
+template <int WAVES, int ITERS, int SPLIT, int G>
 __device__ __forceinline__ void recurrent_tiles(const RecurrentArgs &a, int tile, int grp, int done, float *red) {
   static_assert(ITERS > 0, "every load of a slice in flight at once");
   constexpr int LPH = 2 * WAVES, VPL = 32 / LPH;
@@ -422,7 +422,7 @@ __device__ __forceinline__ void recurrent_tiles(const RecurrentArgs &a, int tile
     floatx16 acc = {0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0};
     if constexpr (SPLIT) {
       floatx16 cor = acc;
-      mfma32_split_rounds<ITERS>(wa, hb[g & 1], kHidScale, acc, cor);
+      mfma32_split_rounds<ITERS, SPLIT == kSplitLoLo>(wa, hb[g & 1], kHidScale, acc, cor);
       acc = split_join(acc, cor);
     } else {
 #pragma unroll
@@ -482,7 +482,7 @@ struct MainArgs {
 // so that the [M, V + 1] logits never reach memory (LPH = 2 * WAVES lanes share a hypothesis, each holds 32 / LPH
 // columns; the best K are found in K rounds of an LPH-lane arg-max).  Lists and statistics are written with
 // device-coherent stores.  red: the block's reduction buffer (WAVES * 64 * kRedStride floats).
-template <int WAVES, int ITERS, bool SPLIT, bool WIDE = false>
+template <int WAVES, int ITERS, int SPLIT, bool WIDE = false>
 __device__ __forceinline__ void joint_tile(const MainArgs &a, int chunk, int m0, int rows, int done, float *red) {
   constexpr int LPH = 2 * WAVES, VPL = 32 / LPH;
   constexpr Prod kProd = SPLIT ? Prod::kSplitAct : Prod::kPlain;
@@ -513,14 +513,14 @@ __device__ __forceinline__ void joint_tile(const MainArgs &a, int chunk, int m0,
 #pragma unroll
         for (int i = 0; i < ITERS; ++i) xw[i] = *reinterpret_cast<const float4 *>(xp + (size_t)((kbeg + 8 * i) >> 2) * Np * 4);
         if (done) return;
-        splitk_mma<WAVES, ITERS, kProd>(op, a_at, b_at, fb, a.H, red, round_ops, xw);
+        splitk_mma<WAVES, ITERS, kProd, SPLIT == kSplitLoLo>(op, a_at, b_at, fb, a.H, red, round_ops, xw);
       } else {
         if (done) return;
-        splitk_mma<WAVES, ITERS, kProd>(op, a_at, b_at, fb, a.H, red, round_ops);
+        splitk_mma<WAVES, ITERS, kProd, SPLIT == kSplitLoLo>(op, a_at, b_at, fb, a.H, red, round_ops);
       }
     } else {
       if (done) return;
-      splitk_mma<WAVES, ITERS, kProd>(op, a_at, b_at, fb, a.H, red, round_ops);
+      splitk_mma<WAVES, ITERS, kProd, SPLIT == kSplitLoLo>(op, a_at, b_at, fb, a.H, red, round_ops);
     }
   }
 
@@ -613,8 +613,8 @@ __device__ __forceinline__ void joint_tile(const MainArgs &a, int chunk, int m0,
 // WIDE: the forms for 256 slots and more (folded blank / duration columns, recurrent blocks of several slot tiles);
 // an instantiation of their own, because their code costs the smaller shapes 0.2 us per launch when it is only there.
 // SEL: the selection forms in the tail (0: every in-kernel form; 5, 6: one form, see select_dispatch).
-// SPLIT: weights split (k_split_rows).
-template <int WAVES, int ITERS, bool SPLIT, bool TAIL = true, bool WIDE = false, int SEL = 0>
+// SPLIT: how the weights are split (k_split_rows).
+template <int WAVES, int ITERS, int SPLIT, bool TAIL = true, bool WIDE = false, int SEL = 0>
 __global__ __launch_bounds__(WAVES * 64, TAIL ? 1 : 16 / WAVES) void k_step_main(MainArgs a) {
   constexpr int kRedFloats = WAVES * 64 * kRedStride;
   constexpr int kScratchFloats = TAIL ? (int)((sizeof(SelectScratch) * WAVES + 3) / 4) : 1;
@@ -929,7 +929,7 @@ __device__ __forceinline__ bool pred_proj_lm_block(const PredProjArgs &a) {
 }
 
 // One tile of the projection: 32 outputs of H (tile) x the slots [m0, m0 + 32).
-template <int WAVES, int ITERS, bool SPLIT>
+template <int WAVES, int ITERS, int SPLIT>
 __device__ __forceinline__ void pred_proj_tile(const PredProjArgs &a, int tile, int m0, int done_flag, float *red) {
   constexpr int LPH = 2 * WAVES, VPL = 32 / LPH;
   const int tid = threadIdx.x, lane = tid & 63, col = lane & 31;
@@ -966,7 +966,7 @@ __device__ __forceinline__ void pred_proj_tile(const PredProjArgs &a, int tile, 
   float us[VPL];
 #pragma unroll
   for (int q = 0; q < VPL; ++q) us[q] = SPLIT ? a.wp_unscale[o0 + q] : 1.f;
-  splitk_mma<WAVES, ITERS, SPLIT ? Prod::kSplitHidden : Prod::kPlain>(op, a_at, b_at, fb, a.P, red, round_ops);
+  splitk_mma<WAVES, ITERS, SPLIT ? Prod::kSplitHidden : Prod::kPlain, SPLIT == kSplitLoLo>(op, a_at, b_at, fb, a.P, red, round_ops);
   if (me >= a.M) return;
 #pragma unroll
   for (int q = 0; q < VPL; ++q)
@@ -974,7 +974,7 @@ __device__ __forceinline__ void pred_proj_tile(const PredProjArgs &a, int tile, 
 }
 
 // LM: the launch carries LM rows (an instantiation of its own: the test for them costs the plain launch 0.26 us)
-template <int WAVES, int ITERS, bool SPLIT, bool LM = false>
+template <int WAVES, int ITERS, int SPLIT, bool LM = false>
 __global__ __launch_bounds__(WAVES * 64) void k_pred_proj(PredProjArgs a) {
   __shared__ float red[WAVES * 64 * kRedStride];
   if constexpr (LM) {
@@ -998,7 +998,7 @@ __global__ __launch_bounds__(WAVES * 64) void k_pred_proj(PredProjArgs a) {
 // on which block comes first.  Half the operands and half the matrix instructions per block: 3.0 instead of 4.8 us.
 // No recurrent tiles ride in this launch (they would set its duration); the main launch takes them all.
 // ITERS = P / 2 / WAVES / 8.
-template <int WAVES, int ITERS, bool SPLIT, bool LM = false>
+template <int WAVES, int ITERS, int SPLIT, bool LM = false>
 __global__ __launch_bounds__(WAVES * 64) void k_pred_proj_half(PredProjArgs a) {
   __shared__ float red[WAVES * 64 * kRedStride];
   constexpr int LPH = 2 * WAVES, VPL = 32 / LPH;
@@ -1049,7 +1049,7 @@ __global__ __launch_bounds__(WAVES * 64) void k_pred_proj_half(PredProjArgs a) {
        i += 4 * WAVES * 64 * a.map.a_tiles * a.map.a_m)
     store16_through(a.pre_clear + i, floatx4{0.f, 0.f, 0.f, 0.f});
   __builtin_amdgcn_sched_barrier(0);
-  splitk_mma<WAVES, ITERS, SPLIT ? Prod::kSplitHidden : Prod::kPlain>(op, a_at, b_at, fb, a.P / 2, red, round_ops);
+  splitk_mma<WAVES, ITERS, SPLIT ? Prod::kSplitHidden : Prod::kPlain, SPLIT == kSplitLoLo>(op, a_at, b_at, fb, a.P / 2, red, round_ops);
   if (a.bump && tile == 0 && item == 0 && tid == 0) bump_step(a.step_base, a.bump, a.h_progress);
   if (me >= a.M) return;
 #pragma unroll

@@ -97,7 +97,7 @@ __device__ __forceinline__ void tile_done(int *counter) {
   if (threadIdx.x == 0) __hip_atomic_fetch_add(counter, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 
-template <int WAVES, int ITERS, bool SPLIT>
+template <int WAVES, int ITERS, int SPLIT>
 __global__ __launch_bounds__(WAVES * 64, 1) void k_decode_persistent(PersistArgs a) {
   constexpr int kRedFloats = WAVES * 64 * kRedStride;
   constexpr int kScratchFloats = (int)((sizeof(SelectScratch) * WAVES + 3) / 4);

@@ -345,7 +345,7 @@ __device__ __forceinline__ float res_raw(const ResW16 &w, int i) {
 // A 16x16x16 instruction that takes up the sums of a 16x16x32 one right behind it has missed the last one's addends (seen here: the
 // compiler puts no wait states between the two shapes); these are well above the latency.
 __device__ __forceinline__ void res_mma_gap(floatx4 &acc, floatx4 &cor) { asm volatile("s_nop 15" : "+v"(acc), "+v"(cor)); }
-// N tiles of 16 rows, from w[T0] on.  n_rounds: of the slice (beyond: zeros)
+// N tiles of 16 rows, from w[T0] on.  n_rounds: of the slice (beyond: zeros).  Not FULL: kSplitLoLo
 template <bool FULL, int T0, int N, int M>
 __device__ __forceinline__ void res_split_mma(const ResW16 (&w)[M], const ResW16 &x, int n_rounds, floatx4 (&acc)[N], floatx4 (&cor)[N]) {
 #pragma unroll
@@ -360,6 +360,11 @@ __device__ __forceinline__ void res_split_mma(const ResW16 (&w)[M], const ResW16
       }
 #pragma unroll
       for (int t = 0; t < N; ++t) cor[t] = mfma16_f16(w[T0 + t].l[g], x.h[g], cor[t]);
+      if constexpr (!FULL) {
+        const uintx4_t xl = unscaled_lo(x.l[g]);
+#pragma unroll
+        for (int t = 0; t < N; ++t) cor[t] = mfma16_f16(w[T0 + t].l[g], xl, cor[t]);
+      }
     }
   if (FULL || n_rounds > 8) {
 #pragma unroll
@@ -371,6 +376,11 @@ __device__ __forceinline__ void res_split_mma(const ResW16 (&w)[M], const ResW16
     }
 #pragma unroll
     for (int t = 0; t < N; ++t) cor[t] = mfma16_f16(w[T0 + t].tl, x.th, cor[t]);
+    if constexpr (!FULL) {
+      const uintx2_t xl = unscaled_lo(x.tl);
+#pragma unroll
+      for (int t = 0; t < N; ++t) cor[t] = mfma16_f16(w[T0 + t].tl, xl, cor[t]);
+    }
   }
 }
 
@@ -732,6 +742,7 @@ __device__ __forceinline__ void res_p_phase(ResBlock &k, int step) {
             acc = mfma16_f16(wh, xh[hf], acc);
             cor = mfma16_f16(wh, xl[hf], cor);
             cor = mfma16_f16(wl, xh[hf], cor);
+            if constexpr (!FULL) cor = mfma16_f16(wl, unscaled_lo(xl[hf]), cor);
             if (FULL || nh > 4) {
               uintx4_t v = w[160 * hf + 128 + (l.kq >> 1) * 16 + l.sl];
               if (l.kq & 1) v = uintx4_t{0, 0, 0, 0};
@@ -740,6 +751,7 @@ __device__ __forceinline__ void res_p_phase(ResBlock &k, int step) {
               acc = mfma16_f16(vh, yh[hf], acc);
               cor = mfma16_f16(vh, yl[hf], cor);
               cor = mfma16_f16(vl, yh[hf], cor);
+              if constexpr (!FULL) cor = mfma16_f16(vl, unscaled_lo(yl[hf]), cor);
             }
             res_put<false>(k, l, hf, split_join(acc, cor));
             __builtin_amdgcn_sched_barrier(0);  // (both halves at once need more registers than there are)

@@ -173,7 +173,7 @@ struct rnnt_beam {
   // packed weights
   float *W_enc = nullptr, *b_enc = nullptr, *W_pred = nullptr, *b_pred = nullptr, *W_out = nullptr,
         *b_out = nullptr, *W_hh = nullptr, *hh_unscale = nullptr, *W_out_s = nullptr, *out_unscale = nullptr, *pred_unscale = nullptr, *G = nullptr, *tab = nullptr;
-  bool split = false;   // W_hh, W_pred and W_out_s are split (k_split_rows)
+  int split = kNotSplit;  // how W_hh, W_pred and W_out_s are split (k_split_rows)
   // materialised-logits path (bf16 joint, large shapes)
   bool big = false;
   int Npad_big = 0, Hb = 0;  // padded extents of the bf16 operands: 256 columns, 64 k
@@ -364,7 +364,8 @@ int pack_weights(rnnt_beam *h, const rnnt_weights_t *w) {
   // Split products (see split_f16) for float32 models whose weights have a split and whose sums are
   // long enough: a split operand is off by a unit in its last place now and then, the same way in every step, which fewer
   // roundings of the sum have to make up for.  Error of scores against 64 bits, split over float32 (1600 utterances each, plus or minus
-  // 0.02): LSTM decoders 256 wide 1.05, 320 1.02, 384 1.00, 512 0.99, 640 1.01; 64 to 192 wide (380 utterances) 1.02 to 1.09.
+  // 0.02) and without the products of two lo (see kSplitLoLo): LSTM decoders 256 wide 1.05, 320 1.02, 384 1.00, 512 0.99, 640 1.01; 64 to
+  // 192 wide (380 utterances) 1.02 to 1.09.
   // (Not for the bf16 joint: its rounding of the activations turns any other order of the sums into other near ties.)
   const bool lstm = c.pred == RNNT_PRED_LSTM, wide = std::min(H, lstm ? P : H) >= kSplitWidth;
   bool can_split = !bf && wide;
@@ -471,7 +472,7 @@ int pack_weights(rnnt_beam *h, const rnnt_weights_t *w) {
                             h->tab + (size_t)i * (V + 1) * H, V + 1, H, P, bf ? 1 : 0, nullptr)))
         return rc;
   }
-  h->split = can_split;
+  h->split = !can_split ? kNotSplit : H == 640 && (!lstm || P == 640) ? kSplit : kSplitLoLo;
   if (h->split) {
     if ((rc = upload(h, &h->W_out_s, w_out_k4))) return rc;
     if ((rc = split_rows(h, h->W_out_s, h->n_chunks * 32, H, kActUnscale, &h->out_unscale))) return rc;
@@ -630,21 +631,23 @@ int launch_pred(rnnt_beam *h, hipStream_t s, const StepPlan &p, int cur, int bum
       }
       const dim3 grid(n_tiles + a.lmr.M);
       auto launch = [&](auto split) {
-        constexpr bool S = decltype(split)::value;
+        constexpr int S = decltype(split)::value;
         auto go = [&](auto lm, auto plain, int waves) {
           if (a.lmr.M) hipLaunchKernelGGL(lm, grid, dim3(waves * 64), lds, s, a);
           else hipLaunchKernelGGL(plain, grid, dim3(waves * 64), 0, s, a);
         };
-        if (proj_split(c, p.M)) {
-          if (c.P == 640) go(k_pred_proj_half<8, 5, S, true>, k_pred_proj_half<8, 5, S, false>, 8);
-          else go(k_pred_proj_half<8, 0, S, true>, k_pred_proj_half<8, 0, S, false>, 8);
+        if (S == kSplit || c.P == 640) {
+          if (proj_split(c, p.M)) go(k_pred_proj_half<8, 5, S, true>, k_pred_proj_half<8, 5, S, false>, 8);
+          else go(k_pred_proj<8, 10, S, true>, k_pred_proj<8, 10, S, false>, 8);
+        } else if constexpr (S != kSplit) {
+          if (proj_split(c, p.M)) go(k_pred_proj_half<8, 0, S, true>, k_pred_proj_half<8, 0, S, false>, 8);
+          else if (c.P % 64 == 0) go(k_pred_proj<8, 0, S, true>, k_pred_proj<8, 0, S, false>, 8);
+          else go(k_pred_proj<4, 0, S, true>, k_pred_proj<4, 0, S, false>, 4);
         }
-        else if (c.P == 640) go(k_pred_proj<8, 10, S, true>, k_pred_proj<8, 10, S, false>, 8);
-        else if (c.P % 64 == 0) go(k_pred_proj<8, 0, S, true>, k_pred_proj<8, 0, S, false>, 8);
-        else go(k_pred_proj<4, 0, S, true>, k_pred_proj<4, 0, S, false>, 4);
       };
-      if (h->split) launch(std::true_type{});
-      else launch(std::false_type{});
+      if (h->split == kSplit) launch(std::integral_constant<int, kSplit>{});
+      else if (h->split == kSplitLoLo) launch(std::integral_constant<int, kSplitLoLo>{});
+      else launch(std::integral_constant<int, kNotSplit>{});
     }
   } else if (p.big) {
     StatelessPreBigArgs a;
@@ -725,7 +728,7 @@ void launch_select(rnnt_beam *h, hipStream_t s, const StepPlan &p, const SelectA
 }
 
 // k_step_main in the form for the decoder's widths and the selection that follows
-template <bool SPLIT>
+template <int SPLIT>
 void launch_main(rnnt_beam *h, hipStream_t s, const StepPlan &p, const MainArgs &a, bool fold, bool tail) {
   const rnnt_config_t &c = h->cfg;
   const bool lstm = c.pred == RNNT_PRED_LSTM;
@@ -761,12 +764,19 @@ void launch_main(rnnt_beam *h, hipStream_t s, const StepPlan &p, const MainArgs 
     else if (tail) go(k_step_main<W, 0, SPLIT, true>, W);
     else go(k_step_main<W, 0, SPLIT, false>, W);
   };
-  if (wide && tail) full_tail(std::true_type{});
-  else if (wide) go(k_step_main<8, 10, SPLIT, false, true>, 8);
-  else if (full && tail) full_tail(std::false_type{});
-  else if (full) go(k_step_main<8, 10, SPLIT, false>, 8);
-  else if (c.H % 64 == 0 && (!lstm || c.P % 64 == 0)) other_widths(std::integral_constant<int, 8>{});
-  else other_widths(std::integral_constant<int, 4>{});
+  if constexpr (SPLIT != kSplitLoLo) {
+    if (full) {
+      if (wide && tail) full_tail(std::true_type{});
+      else if (wide) go(k_step_main<8, 10, SPLIT, false, true>, 8);
+      else if (tail) full_tail(std::false_type{});
+      else go(k_step_main<8, 10, SPLIT, false>, 8);
+      return;
+    }
+  }
+  if constexpr (SPLIT != kSplit) {
+    if (c.H % 64 == 0 && (!lstm || c.P % 64 == 0)) other_widths(std::integral_constant<int, 8>{});
+    else other_widths(std::integral_constant<int, 4>{});
+  }
 }
 
 // one beam-search step; cur = parity of the prediction-network state it reads
@@ -889,8 +899,9 @@ int launch_step(rnnt_beam *h, hipStream_t s, const StepPlan &p, int step_off, in
     const bool tail = p.K <= 8 && !c.tdt_all_pairs;
     {
       ScopedKernelTime tm(h, s, KT_JOINT);
-      if (h->split) launch_main<true>(h, s, p, a, fold, tail);
-      else launch_main<false>(h, s, p, a, fold, tail);
+      if (h->split == kSplit) launch_main<kSplit>(h, s, p, a, fold, tail);
+      else if (h->split == kSplitLoLo) launch_main<kSplitLoLo>(h, s, p, a, fold, tail);
+      else launch_main<kNotSplit>(h, s, p, a, fold, tail);
     }
     if (!tail) {
       RB_HIP(h, hipGetLastError());
@@ -923,8 +934,8 @@ bool use_persistent(const rnnt_beam *h, const StepPlan &p) {
 
 auto persistent_kernel(const rnnt_beam *h) {
   const bool full = h->cfg.H == 640 && h->cfg.P == 640;
-  if (h->split) return full ? k_decode_persistent<8, 10, true> : k_decode_persistent<8, 0, true>;
-  return full ? k_decode_persistent<8, 10, false> : k_decode_persistent<8, 0, false>;
+  if (h->split) return full ? k_decode_persistent<8, 10, kSplit> : k_decode_persistent<8, 0, kSplitLoLo>;
+  return full ? k_decode_persistent<8, 10, kNotSplit> : k_decode_persistent<8, 0, kNotSplit>;
 }
 
 int launch_persistent(rnnt_beam *h, hipStream_t s, const StepPlan &p, int max_steps) {
@@ -1004,7 +1015,7 @@ struct DeviceSlot {
 
 int create_resident(rnnt_beam *h, int fail_alloc) {
   const rnnt_config_t &c = h->cfg;
-  const ResidentWeights rw{h->split, h->W_hh, h->hh_unscale, h->W_out, h->W_out_s, h->out_unscale, h->W_pred, h->pred_unscale, h->n_chunks * 32};
+  const ResidentWeights rw{h->split != kNotSplit, h->W_hh, h->hh_unscale, h->W_out, h->W_out_s, h->out_unscale, h->W_pred, h->pred_unscale, h->n_chunks * 32};
   return c.use_graph && !c.persistent_kernel && !c.async_enqueue ? resident_create(h->res, c, rw, h->err, fail_alloc) : RNNT_OK;
 }
 

@@ -339,6 +339,36 @@ def test_split_products_of_rows_with_outliers(oracle, h, B, beam, apart, huge):
         np.testing.assert_array_equal(g[key], ref[key])
 
 
+@pytest.mark.parametrize("h,p,more", [(320, 320, {}), (640, 640, {}), (448, 640, {}), (640, 640, dict(ST, ctx=2))])
+def test_error_of_split_products_against_64_bits(oracle, h, p, more):
+    """Scores of decodes with logits of some hundreds, whose errors are those of the products, against the oracle's 64 bits: no larger
+    than with float32 instructions, which the same decoder runs when a token that a bias has closed is closed by a weight without a
+    split.  Bound: 4 standard errors of the ratio of the two (0.02 to 0.03 at 20 decodes of 16 utterances) above 1."""
+    import paper_2506_00185_amd as A
+    square, n = np.zeros(2), 0
+    for seed in range(100, 120):
+        c = S.custom_config(**dict(dict(B=16, T=3, T_min=3, s=2, V=300, beam=8, blank_bias=0.0, H=h, P=p, E=64, D=64), **more))
+        w = {k: np.array(v) for k, v in S.make_weights(c, seed).items()}
+        w["W_out"] = w["W_out"] * 100.0
+        w["W_enc"][0] = w["W_pred"][0] = 0.0
+        w["b_pred"][0] = 1.0                    # a unit that is always active
+        w["b_out"][c["V"] - 1] = -1e30
+        ref = {k: np.array(v) for k, v in w.items()}
+        ref["W_out"][c["V"] - 1, 0] = -np.inf
+        L = S.make_lengths(c, seed + 1)
+        enc = S.make_enc(c, L, seed + 2)
+        o = oracle.decode(c, w, enc, L)
+        lists = [[{tuple(r["tokens"][b, j, :l]): r["scores"][b, j] for j, l in enumerate(r["lens"][b]) if l >= 0} for b in range(c["B"])]
+                 for r in (o, *[gpu_decode(A.BeamDecoder(c, x), enc, L, want_tree=False) for x in (w, ref)])]
+        for want, split, plain in zip(*lists):
+            for k in want.keys() & split.keys() & plain.keys():
+                square += (split[k] - want[k]) ** 2, (plain[k] - want[k]) ** 2
+                n += 1
+    ratio = float(np.sqrt(square[0] / square[1]))
+    print("error, split over float32:", round(ratio, 3), "of", n, "scores")
+    assert n > 1000 and ratio <= 1.1
+
+
 @pytest.mark.parametrize("h,p,more", [(64, 64, {}), (256, 256, {}), (640, 128, dict(V=700)), (192, 640, dict(B=9)), (256, 64, ST),
                                       (96, 160, {}), (128, 128, dict(B=10, beam=10, V=500))])
 def test_narrow_decoders_multiply_in_float32(h, p, more):
