@@ -710,7 +710,7 @@ struct MergeSelectArgs {
 };
 constexpr int kMergeHeads = 8, kMergeCap = 128;
 
-template <int FORMS>  // 4, or 12 / 16 on a plain RNN-T (see select_dispatch)
+template <int KC, int PLAIN>  // see select_one_list
 __global__ __launch_bounds__(64 * kMaxBeam) void k_utt_merge_select(MergeSelectArgs a) {
   __shared__ SelectScratch scratch;
   __shared__ uint64_t l_cand[kMaxBeam * kMaxBeam];
@@ -817,7 +817,7 @@ __global__ __launch_bounds__(64 * kMaxBeam) void k_utt_merge_select(MergeSelectA
     }
   }
   __syncthreads();
-  if (wave == 0) select_dispatch<FORMS, SelectScratch>(a.sel, b, scratch, CandView{l_cand, l_max, l_sum, l_zs, b * K});
+  if (wave == 0) select_one_list<KC, PLAIN>(a.sel, b, scratch, CandView{l_cand, l_max, l_sum, l_zs, b * K});
 }
 
 // ---------------------------------------------------------------------------

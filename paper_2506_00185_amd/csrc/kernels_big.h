@@ -316,7 +316,7 @@ struct RowSelectArgs {
   float *zs;             // [M][1 + ND]
   const int *finished;   // [B]
   const int *done;
-  // TAIL: the block that completes an utterance (counted in utt_ctr) runs its selection and writes the
+  // KC > 0 (see select_one_list): the block that completes an utterance (counted in utt_ctr) runs its selection and writes the
   // activations of its new hypotheses, so that the step needs no further launch
   int *utt_ctr;          // [B], zero between steps
   SelectArgs sel;
@@ -338,7 +338,8 @@ constexpr int kSurvivorCap = 256;
 // Otherwise the whole row is read, 32 values per lane, and the lane maxima play the part of the chunk maxima.
 // Four waves per row rather than one: 32 instead of 128 registers of logits per lane, five waves per SIMD
 // instead of 1.25, so that the arithmetic of one row overlaps with the loads of another.
-template <bool TAIL, bool STATS>
+// KC: 0, or beams that the selection in the tail takes (see RowSelectArgs)
+template <int KC, bool STATS>
 __global__ __launch_bounds__(64 * kRowWaves) void k_row_select(RowSelectArgs a) {
   __shared__ uint64_t surv[kSurvivorCap];
   __shared__ int surv_n;
@@ -524,7 +525,7 @@ __global__ __launch_bounds__(64 * kRowWaves) void k_row_select(RowSelectArgs a) 
         if (lane == 0) store_through(a.zs + (size_t)m * nz + d, v + a.bias_spec[d]);
       }
   }
-  if constexpr (TAIL) {
+  if constexpr (KC > 0) {
     // Every thread waits until its write-through stores (list, statistics, blank / duration logits) have been
     // acknowledged, then the barrier, then one thread counts the row in: the count cannot become visible before
     // anything of the row.  The block that brings the utterance's count to K owns the rest of its step.
@@ -542,7 +543,7 @@ __global__ __launch_bounds__(64 * kRowWaves) void k_row_select(RowSelectArgs a) 
     }
     __syncthreads();
     if (!s_is_last) return;
-    if (wave == 0) select_dispatch<4, SelectScratch>(a.sel, b, scratch);  // (reads the lists with device-coherent loads)
+    if (wave == 0) select_one_list<KC, 0>(a.sel, b, scratch, cand_view(a.sel));  // (reads the lists with device-coherent loads)
     __syncthreads();
     // activations of the utterance's new hypotheses, from the selection's scratch (frame, token history)
     const int T_b = a.pre.lengths[b];
@@ -571,8 +572,8 @@ __global__ __launch_bounds__(64 * kRowWaves) void k_row_select(RowSelectArgs a) 
 // it collected and ranked by counting).
 constexpr int kUttSurvivorCap = 128;
 
-// FORMS: 4, or 12 / 16 for AES++ / ALSD++ on a plain RNN-T (see select_dispatch)
-template <int FORMS>
+// KC, PLAIN: see select_one_list
+template <int KC, int PLAIN>
 __global__ __launch_bounds__(64 * kMaxBeam) void k_utt_select(RowSelectArgs a) {
   __shared__ SelectScratch scratch;
   __shared__ uint64_t l_cand[kMaxBeam * kMaxBeam];
@@ -660,7 +661,7 @@ __global__ __launch_bounds__(64 * kMaxBeam) void k_utt_select(RowSelectArgs a) {
   }
   // blank and duration logits from the bf16 activations: z[V + d] = Wspec[d] . a_m + bias; a lane takes 8 k at a time
   {
-    const int nz = (FORMS == 12 || FORMS == 16) ? 1 : 1 + a.ND;  // (the plain forms: no durations)
+    const int nz = PLAIN ? 1 : 1 + a.ND;  // (the plain forms: no durations)
     float acc[9];
 #pragma unroll
     for (int d = 0; d < 9; ++d) acc[d] = 0.f;
@@ -690,7 +691,7 @@ __global__ __launch_bounds__(64 * kMaxBeam) void k_utt_select(RowSelectArgs a) {
       }
   }
   __syncthreads();
-  if (wave == 0) select_dispatch<FORMS, SelectScratch>(a.sel, b, scratch, CandView{l_cand, l_max, l_sum, l_zs, b * K});
+  if (wave == 0) select_one_list<KC, PLAIN>(a.sel, b, scratch, CandView{l_cand, l_max, l_sum, l_zs, b * K});
   __syncthreads();
   // activations of the utterance's new hypotheses, from the selection's scratch (frame, token history)
   const int T_b = a.pre.lengths[b];

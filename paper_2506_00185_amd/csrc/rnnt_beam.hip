@@ -554,13 +554,21 @@ void fill_stateless_pre_big(rnnt_beam *h, const StepPlan &p, int bump, Stateless
   a.h_progress = h->h_done_dev + kProgressWord;
 }
 
-// One-list selection forms: 16 / 12 for ALSD++ / AES++ (without prune margin and prefix search) on a plain RNN-T
-// (no durations, no LM), else the general 4.
-int plain_forms(const rnnt_beam *h, const StepPlan &p) {
+// Calls f with (beams up to, plain) of select_one_list for this decode.  plain: 1 for ALSD++, 2 for AES++ (without prune margin and
+// prefix search) on an RNN-T without durations and LM.
+template <class F>
+void one_list_form(const rnnt_beam *h, const StepPlan &p, F f) {
   const rnnt_config_t &c = h->cfg;
-  if (c.n_durations != 0 || p.lm) return 4;
-  if (p.algo == RNNT_ALSD) return 16;
-  return (!std::isfinite(c.prune_margin) && !c.aes_prefix_search) ? 12 : 4;
+  auto with = [&](auto plain) {
+    if (p.K <= 4) f(std::integral_constant<int, 4>{}, plain);
+    else if (p.K <= 8) f(std::integral_constant<int, 8>{}, plain);
+    else if (p.K <= 12) f(std::integral_constant<int, 12>{}, plain);
+    else f(std::integral_constant<int, 16>{}, plain);
+  };
+  if (c.n_durations != 0 || p.lm) with(std::integral_constant<int, 0>{});
+  else if (p.algo == RNNT_ALSD) with(std::integral_constant<int, 1>{});
+  else if (!std::isfinite(c.prune_margin) && !c.aes_prefix_search) with(std::integral_constant<int, 2>{});
+  else with(std::integral_constant<int, 0>{});
 }
 
 // fuse_lm: the LM rows of the new hypotheses ride in the projection launch, or in the cell-update launch when
@@ -720,9 +728,10 @@ void launch_select(rnnt_beam *h, hipStream_t s, const StepPlan &p, const SelectA
     ma.sel = sa;
     ma.sel.n_chunks = 1;
     ma.n_lists = n_chunks;
-    const int forms = plain_forms(h, p);
-    auto k_sel = forms == 16 ? k_utt_merge_select<16> : forms == 12 ? k_utt_merge_select<12> : k_utt_merge_select<4>;
-    hipLaunchKernelGGL(k_sel, dim3(p.B), dim3(64 * p.K), 0, s, ma);
+    one_list_form(h, p, [&](auto kc, auto plain) {
+      constexpr int KC = decltype(kc)::value;
+      if constexpr (KC > 8) hipLaunchKernelGGL((k_utt_merge_select<KC, decltype(plain)::value>), dim3(p.B), dim3(64 * p.K), 0, s, ma);
+    });
   } else if (select_needs_wide_forms(p.K, n_chunks)) hipLaunchKernelGGL(k_select_wide, dim3((p.B + 3) / 4), dim3(256), 0, s, sa);
   else hipLaunchKernelGGL(k_select, dim3((p.B + 3) / 4), dim3(256), 0, s, sa);
 }
@@ -844,15 +853,14 @@ int launch_step(rnnt_beam *h, hipStream_t s, const StepPlan &p, int step_off, in
       // without an LM term in the keys the chunk statistics of the contraction say which chunks to read
       const dim3 grid(p.M), block(64 * kRowWaves);
       if (big_tail(h, p)) {
-        if (a.lm) hipLaunchKernelGGL((k_row_select<true, false>), grid, block, 0, s, a);
-        else {  // one block per utterance
-          const int forms = plain_forms(h, p);
-          auto k_sel = forms == 16 ? k_utt_select<16> : forms == 12 ? k_utt_select<12> : k_utt_select<4>;
-          hipLaunchKernelGGL(k_sel, dim3(p.B), dim3(64 * p.K), 0, s, a);
-        }
+        one_list_form(h, p, [&](auto kc, auto plain) {
+          constexpr int KC = decltype(kc)::value, PLAIN = decltype(plain)::value;
+          if (!a.lm) hipLaunchKernelGGL((k_utt_select<KC, PLAIN>), dim3(p.B), dim3(64 * p.K), 0, s, a);  // one block per utterance
+          else if constexpr (PLAIN == 0) hipLaunchKernelGGL((k_row_select<KC, false>), grid, block, 0, s, a);
+        });
       } else {
-        if (a.lm) hipLaunchKernelGGL((k_row_select<false, false>), grid, block, 0, s, a);
-        else hipLaunchKernelGGL((k_row_select<false, true>), grid, block, 0, s, a);
+        if (a.lm) hipLaunchKernelGGL((k_row_select<0, false>), grid, block, 0, s, a);
+        else hipLaunchKernelGGL((k_row_select<0, true>), grid, block, 0, s, a);
       }
     }
     RB_HIP(h, hipGetLastError());

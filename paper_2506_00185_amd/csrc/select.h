@@ -873,24 +873,12 @@ __device__ __forceinline__ void select_utterance(const SelectArgs &a, int b, Scr
 }
 
 // picks the lane-group width and register budget for the beam and list sizes at hand.
-// FORMS: 4 = one list per hypothesis, known at compile time (tail of the row kernel of the materialised-logits path);
-// 0 = beams up to 8 (what the main kernel of a step runs in its tail); 1 = those plus wider beams
+// FORMS: 0 = beams up to 8 (what the main kernel of a step runs in its tail); 1 = those plus wider beams
 // whose hypotheses come with a single list; 2 = wider beams with many lists (several passes, many
 // registers).  The heavy forms are kept out of the kernels that do not need them.
 template <int FORMS, class Scratch = SelectScratch>
 __device__ __forceinline__ void select_dispatch(const SelectArgs &a, int b, Scratch &s, const CandView cv) {
-  if constexpr (FORMS == 12 || FORMS == 16) {  // FORMS == 4 on a plain RNN-T (no durations, no LM): 12 for AES++
-    constexpr int P = FORMS == 12 ? 2 : 1;      // without prune margin and prefix search, 16 for ALSD++
-    if (a.K <= 4) select_utterance<16, 1, 4, false, false, Scratch, true, P>(a, b, s, cv);
-    else if (a.K <= 8) select_utterance<8, 1, 8, false, false, Scratch, true, P>(a, b, s, cv);
-    else if (a.K <= 12) select_utterance<4, 1, 12, false, false, Scratch, true, P>(a, b, s, cv);
-    else select_utterance<4, 1, 16, false, false, Scratch, true, P>(a, b, s, cv);
-  } else if constexpr (FORMS == 4) {  // one list per hypothesis (the materialised-logits path), any beam
-    if (a.K <= 4) select_utterance<16, 1, 4, false, false, Scratch, true>(a, b, s, cv);
-    else if (a.K <= 8) select_utterance<8, 1, 8, false, false, Scratch, true>(a, b, s, cv);
-    else if (a.K <= 12) select_utterance<4, 1, 12, false, false, Scratch, true>(a, b, s, cv);
-    else select_utterance<4, 1, 16, false, false, Scratch, true>(a, b, s, cv);
-  } else if constexpr (FORMS == 3) {  // TDT, every (symbol, duration) pair a candidate, beams up to 8
+  if constexpr (FORMS == 3) {  // TDT, every (symbol, duration) pair a candidate, beams up to 8
     if (a.K <= 4) {
       if (a.n_chunks <= 16 * 3) select_utterance<16, 3, 4, false, true, Scratch>(a, b, s, cv);
       else select_utterance<16, 0, 4, false, true, Scratch>(a, b, s, cv);
@@ -934,6 +922,13 @@ __device__ __forceinline__ void select_dispatch(const SelectArgs &a, int b, Scra
 template <int FORMS, class Scratch = SelectScratch>
 __device__ __forceinline__ void select_dispatch(const SelectArgs &a, int b, Scratch &s) {
   select_dispatch<FORMS, Scratch>(a, b, s, cand_view(a));
+}
+// One list per hypothesis, of beams up to KC (4, 8, 12 or 16: chosen on the host, or narrow beams would pay for the ranking of wide ones:
+// k_utt_select with all four took 149 scalar spills, 197 since the ranking of wide beams finds a bound first).  PLAIN: see
+// select_utterance.
+template <int KC, int PLAIN>
+__device__ __forceinline__ void select_one_list(const SelectArgs &a, int b, SelectScratch &s, const CandView cv) {
+  select_utterance<(KC == 4 ? 16 : KC == 8 ? 8 : 4), 1, KC, false, false, SelectScratch, true, PLAIN>(a, b, s, cv);
 }
 // which stand-alone selection kernel takes a beam of K with n_chunks lists per hypothesis
 __host__ __device__ inline bool select_needs_wide_forms(int K, int n_chunks) { return K > 8 && n_chunks > 4; }
