@@ -163,31 +163,36 @@ __device__ __forceinline__ void res_store16(bool local, float *p, floatx4 v) {
 
 // The Beam best of more than 64 candidates (beams from 8 on), candidate r * (K + 1) + j of hypothesis r, tokens (best first) and then
 // blank.  The K-th largest of a few candidates is a lower bound of the K-th largest of all: with each hypothesis' two best tokens and
-// its blank (a lane each) few more than K candidates reach it, and those are ranked against each other.  false: more than 64 do.
-// (Ranking the K (K + 1) / 2 candidates that the order of the sorted lists leaves took 4.5 us at beam 12 and 2.0 at beam 8.)
+// its blank (a lane each) few more than K candidates reach it, and those are ranked against each other.  Where more than 64 do (wide
+// beams of hypotheses of much the same score), the K-th largest of the first 64 of them is a better bound.  false: many equal ones.
+// (Ranking the K (K + 1) / 2 candidates that the order of the sorted lists leaves took 4.5 us at beam 12 and 2.0 at beam 8.  Without
+// the second bound beams of 16 fell back to K rounds over all: stateless, batch
+// 24, 64 wide, V = 1000 10.19 ms per decode of 40 frames, with it 6.03, with the ranking by the sorted lists 6.59.)
 template <class Scratch>
 __device__ __forceinline__ bool rank_best(Scratch &s, const double *rank_of, int K, int n) {
-  const int lane = threadIdx.x & 63, first = 3 * K;
-  {
-    const int r = (171 * lane) >> 9, j = lane - 3 * r;  // lane / 3
-    const double v = lane < first ? rank_of[r * (K + 1) + (j == 2 ? K : j)] : -INFINITY;
-    s.top_key[lane] = v;
+  const int lane = threadIdx.x & 63;
+  const int r = (171 * lane) >> 9, j = lane - 3 * r;  // lane / 3
+  double v = lane < 3 * K ? rank_of[r * (K + 1) + (j == 2 ? K : j)] : -INFINITY;
+  s.top_key[lane] = v;
+  int total, few = 3 * K;
+#pragma unroll 1
+  for (int pass = 0;; ++pass) {
     wave_sync();
     int ge = 0;  // of these, not below mine
-    for (int c0 = 0; c0 < first; c0 += 8) {
+    for (int c0 = 0; c0 < few; c0 += 8) {
       double cv[8];
 #pragma unroll
       for (int q = 0; q < 8; ++q) cv[q] = s.top_key[c0 + q];
 #pragma unroll
       for (int q = 0; q < 8; ++q) ge += (int)(cv[q] >= v);
     }
-    ge = v > -INFINITY && ge >= K ? ge : 64;
+    ge = v > -INFINITY && ge >= K ? ge : 65;
     int least = group_min_i<16>(ge);
     least = min(min(__builtin_amdgcn_readlane(least, 0), __builtin_amdgcn_readlane(least, 16)),
                 min(__builtin_amdgcn_readlane(least, 32), __builtin_amdgcn_readlane(least, 48)));
-    const double tau = least < 64 ? readlane_d(v, __builtin_ctzll(__ballot(ge == least))) : -INFINITY;
+    const double tau = least < 65 ? readlane_d(v, __builtin_ctzll(__ballot(ge == least))) : -INFINITY;
     wave_sync();
-    int total = 0;
+    total = 0;
     for (int c0 = 0; c0 < n; c0 += 64) {
       const int c = c0 + lane;
       const double x = rank_of[c < n ? c : 0];
@@ -201,20 +206,24 @@ __device__ __forceinline__ bool rank_best(Scratch &s, const double *rank_of, int
       }
       total += __popcll(mask);
     }
-    if (total > 64) return false;
-    if (lane < 8) {  // (the ranking reads in eights)
-      s.top_key[total + lane] = -INFINITY;
-      s.top_flat[total + lane] = 0x7fffffff;
-    }
+    if (total <= 64) break;
+    if (pass == 2) return false;
     wave_sync();
-    const bool mine = lane < total;
-    const double mv = mine ? s.top_key[lane] : -INFINITY;
-    const int mf = mine ? s.top_flat[lane] : 0x7fffffff;
-    const int rank = rank_by_counting(s.top_key, s.top_flat, total, mv, mf);
-    if (mine && rank < K) {
-      s.sel_val[rank] = s.rc_val[s.top_src[lane]];
-      s.sel_flat[rank] = mf;
-    }
+    v = s.top_key[lane];
+    few = 64;
+  }
+  if (lane < 8) {  // (the ranking reads in eights)
+    s.top_key[total + lane] = -INFINITY;
+    s.top_flat[total + lane] = 0x7fffffff;
+  }
+  wave_sync();
+  const bool mine = lane < total;
+  const double mv = mine ? s.top_key[lane] : -INFINITY;
+  const int mf = mine ? s.top_flat[lane] : 0x7fffffff;
+  const int rank = rank_by_counting(s.top_key, s.top_flat, total, mv, mf);
+  if (mine && rank < K) {
+    s.sel_val[rank] = s.rc_val[s.top_src[lane]];
+    s.sel_flat[rank] = mf;
   }
   return true;
 }

@@ -151,6 +151,23 @@ def test_injected_merge_heavy_tables_are_bit_exact(amd, oracle, algo, beam, V, m
     assert np.sum((m >= 0) & (m != slots)) >= 3, "the table does not exercise recombination"
 
 
+@pytest.mark.parametrize("algo", ["alsd", "aes"])
+@pytest.mark.parametrize("beam", [8, 9, 12, 16])
+@pytest.mark.parametrize("spacing", [0.0, 2.0 ** -12, 2.0 ** -6], ids=["equal", "close", "apart"])
+def test_injected_many_candidates_near_the_last_one_kept(amd, oracle, algo, beam, spacing):
+    """Candidates of much the same score: far more than the 64 that are ranked against each other reach a first bound of the Beam
+    best (close), or every bound (equal)."""
+    B, T, C, V = 3, 8, 5, 120
+    c = S.custom_config(B=B, T=T, T_min=3, D=32, H=32, P=32, E=32, V=V, beam=beam, s=3, algo=algo)
+    L = S.make_lengths(c, 17)
+    tok = (-5.0 - spacing * np.random.default_rng(beam).permuted(np.tile(np.arange(V + 1), (B, T, C, 1)), axis=-1)).astype(np.float32)
+    g = gpu_decode_injected(amd.BeamDecoder(c, S.make_weights(c, 1)), tok, None, L)
+    o = oracle.decode(c, None, None, L, injected=(tok, None), log=True)
+    assert np.array_equal(g["n_steps"], o["n_steps"])
+    full, exempt = compare(g, o, tol=1e-9, tie=0.0, exact_tree=True)
+    assert full == B and exempt == 0
+
+
 @pytest.mark.parametrize("T,beam,tree_kib", [(130, 8, 64), (150, 16, 144)])
 def test_injected_long_utterances_walk_the_tree_in_memory(amd, oracle, T, beam, tree_kib):
     """Trees of more than 64 KiB per utterance (steps x beam x 8 bytes), and of more than the back-trace can hold in
