@@ -342,9 +342,18 @@ __device__ __forceinline__ ResW16 res_split_load(const uintx4_t *p, const ResLan
 __device__ __forceinline__ float res_raw(const ResW16 &w, int i) {
   return __uint_as_float(i < 16 ? ((i >> 2) & 1 ? w.l[i >> 3][i & 3] : w.h[i >> 3][i & 3]) : i < 18 ? w.th[i & 1] : w.tl[i & 1]);
 }
-// A 16x16x16 instruction that takes up the sums of a 16x16x32 one right behind it has missed the last one's addends (seen here: the
-// compiler puts no wait states between the two shapes); these are well above the latency.
-__device__ __forceinline__ void res_mma_gap(floatx4 &acc, floatx4 &cor) { asm volatile("s_nop 15" : "+v"(acc), "+v"(cor)); }
+// Between 16x16x32 instructions and 16x16x16 ones on the same accumulators.  Instructions of one shape hand their sums on inside the
+// matrix unit, back to back; from one shape to the other the second missed addends of the first here (the compiler puts no wait states
+// between the two).  In the vector registers, where every instruction finds it, a result of either shape is 8 wait states behind its
+// instruction (the compiler's distance to any other reader, s_nop 7); these are 16, behind the last instruction on any of the
+// accumulators, since all of them pass through the asm.
+__device__ __forceinline__ void res_mma_gap(floatx4 (&a)[1], floatx4 (&b)[1]) { asm volatile("s_nop 15" : "+v"(a[0]), "+v"(b[0])); }
+__device__ __forceinline__ void res_mma_gap(floatx4 (&a)[2], floatx4 (&b)[2]) {
+  asm volatile("s_nop 15" : "+v"(a[0]), "+v"(b[0]), "+v"(a[1]), "+v"(b[1]));
+}
+__device__ __forceinline__ void res_mma_gap(floatx4 (&a)[3], floatx4 (&b)[3]) {
+  asm volatile("s_nop 15" : "+v"(a[0]), "+v"(b[0]), "+v"(a[1]), "+v"(b[1]), "+v"(a[2]), "+v"(b[2]));
+}
 // N tiles of 16 rows, from w[T0] on.  n_rounds: of the slice (beyond: zeros).  Not FULL: kSplitLoLo
 template <bool FULL, int T0, int N, int M>
 __device__ __forceinline__ void res_split_mma(const ResW16 (&w)[M], const ResW16 &x, int n_rounds, floatx4 (&acc)[N], floatx4 (&cor)[N]) {
@@ -367,8 +376,7 @@ __device__ __forceinline__ void res_split_mma(const ResW16 (&w)[M], const ResW16
       }
     }
   if (FULL || n_rounds > 8) {
-#pragma unroll
-    for (int t = 0; t < N; ++t) res_mma_gap(acc[t], cor[t]);
+    res_mma_gap(acc, cor);
 #pragma unroll
     for (int t = 0; t < N; ++t) {
       acc[t] = mfma16_f16(w[T0 + t].th, x.th, acc[t]);
@@ -738,22 +746,22 @@ __device__ __forceinline__ void res_p_phase(ResBlock &k, int step) {
 #pragma unroll
           for (int hf = 0; hf < 2; ++hf) {
             const uintx4_t wh = w[160 * hf + l.lane], wl = w[160 * hf + 64 + l.lane];
-            floatx4 acc = {0.f, 0.f, 0.f, 0.f}, cor = acc;
-            acc = mfma16_f16(wh, xh[hf], acc);
-            cor = mfma16_f16(wh, xl[hf], cor);
-            cor = mfma16_f16(wl, xh[hf], cor);
-            if constexpr (!FULL) cor = mfma16_f16(wl, unscaled_lo(xl[hf]), cor);
+            floatx4 acc[1] = {floatx4{0.f, 0.f, 0.f, 0.f}}, cor[1] = {acc[0]};
+            acc[0] = mfma16_f16(wh, xh[hf], acc[0]);
+            cor[0] = mfma16_f16(wh, xl[hf], cor[0]);
+            cor[0] = mfma16_f16(wl, xh[hf], cor[0]);
+            if constexpr (!FULL) cor[0] = mfma16_f16(wl, unscaled_lo(xl[hf]), cor[0]);
             if (FULL || nh > 4) {
               uintx4_t v = w[160 * hf + 128 + (l.kq >> 1) * 16 + l.sl];
               if (l.kq & 1) v = uintx4_t{0, 0, 0, 0};
               const uintx2_t vh = {v[0], v[1]}, vl = {v[2], v[3]};
               res_mma_gap(acc, cor);
-              acc = mfma16_f16(vh, yh[hf], acc);
-              cor = mfma16_f16(vh, yl[hf], cor);
-              cor = mfma16_f16(vl, yh[hf], cor);
-              if constexpr (!FULL) cor = mfma16_f16(vl, unscaled_lo(yl[hf]), cor);
+              acc[0] = mfma16_f16(vh, yh[hf], acc[0]);
+              cor[0] = mfma16_f16(vh, yl[hf], cor[0]);
+              cor[0] = mfma16_f16(vl, yh[hf], cor[0]);
+              if constexpr (!FULL) cor[0] = mfma16_f16(vl, unscaled_lo(yl[hf]), cor[0]);
             }
-            res_put<false>(k, l, hf, split_join(acc, cor));
+            res_put<false>(k, l, hf, split_join(acc[0], cor[0]));
             __builtin_amdgcn_sched_barrier(0);  // (both halves at once need more registers than there are)
           }
           finish(tp);
