@@ -173,8 +173,8 @@ struct ResWait {
     __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");  // (ahead of the wave's end)
     __builtin_amdgcn_endpgm();
   }
-  // between two polls of all words of a wave: from the 32nd on (10 us, which no hand-over takes) the wave leaves gaps, for should the
-  // polls be what holds up the data (see res_gather)
+  // between two polls of all words of a wave: from the 32nd on (10 us, which no hand-over takes) the wave leaves gaps of 1 us, for
+  // should the polls be what holds up the data (see res_gather)
   __device__ __forceinline__ void again_wide() {
     if (n >= 32) __builtin_amdgcn_s_sleep(32);
     again();
@@ -186,21 +186,10 @@ __device__ __forceinline__ uint64_t res_load(const char *p) { return load_agent(
 // word i, base + one of the lane's offsets + a constant; the first n are used (FULL: all N).  (The offsets are made anew for every
 // poll: an address kept per word would take more registers than the words.)  Every poll loads all of the words: with a poll of one
 // word per tile first, a trip to the L2 lies between the arrival of the data and their use (batch 32 / beam 4 8.09 instead of 7.52 ms
-// per decode).  PROBE: such a poll all the same, where a wave waits for 20 words: the polls of eight such waves kept a compute unit's
-// L1 so busy that its own stores did not get out (bf16 joint, in one build: 280 us per step; with the poll first 11).  probe: offset of
-// one word of every tile whose owner writes into the wave's words, lanes share them out.
-template <bool FULL, int N, bool PROBE = true, int M, class AT>
-__device__ __forceinline__ void res_gather(const char *base, uint32_t probe, const uint32_t (&offs)[M], AT at, int n, uint64_t (&x)[N]) {
+// per decode).
+template <bool FULL, int N, int M, class AT>
+__device__ __forceinline__ void res_gather(const uint32_t (&offs)[M], AT at, int n, uint64_t (&x)[N]) {
   ResWait w;
-  if constexpr (PROBE) {
-    for (;;) {
-      uint32_t o = probe;
-      asm volatile("" : "+v"(o));
-      const uint64_t y[1] = {res_load(base + o)};
-      if (__ballot(res_any_empty(y)) == 0ull) break;
-      w.again();
-    }
-  }
   for (;;) {
     uint32_t o[M];
 #pragma unroll
@@ -215,6 +204,20 @@ __device__ __forceinline__ void res_gather(const char *base, uint32_t probe, con
     }
     if (__ballot(res_any_empty(x)) == 0ull) return;
     w.again_wide();
+  }
+}
+// Waits for one word of every tile whose owner writes into the words that the wave gathers next (base + the lane's offset: lanes share
+// them out).  For waves that gather 20 words a lane (bf16 joint, two tiles of slots): the polls of eight such waves kept a compute unit's
+// memory pipeline so busy that its own stores, which others waited for, did not get out (in one build: 280 us per step; with this poll
+// first 11).  With 12 words and less no build has shown it; the gaps of again_wide would bound it at some 10 us per hand-over.
+__device__ __forceinline__ void res_probe(const char *base, uint32_t offset) {
+  ResWait w;
+  for (;;) {
+    uint32_t o = offset;
+    asm volatile("" : "+v"(o));
+    const uint64_t y[1] = {res_load(base + o)};
+    if (__ballot(res_any_empty(y)) == 0ull) return;
+    w.again();
   }
 }
 
@@ -299,13 +302,9 @@ __device__ __forceinline__ uint32_t res_pair_base(const ResLane &l) { return (l.
 __device__ __forceinline__ constexpr uint32_t res_part(int i) { return (i >> 1) * kResRoundBytes + (i & 1) * kResWordBytes; }
 // part i (0 to 9) of ten rounds; pair: that of round 8
 __device__ __forceinline__ constexpr uint32_t res_split_part(int i) { return i < 8 ? (i >> 2) * 4 * kResRoundBytes + res_part(i & 3) : res_part(i & 1); }
-// Words to poll, see res_gather: a tile of W_hh's four units writes half of a round's words (lanes 0 ..: two per round), a tile of the
-// projection two rounds' (one per round, which also serves slices that begin in the middle of a tile).
-__device__ __forceinline__ uint32_t res_probe_h(const ResLane &l, int nr) { return (l.lane < 2 * nr ? l.lane >> 1 : 0) * kResRoundBytes + (l.lane & 1) * kResWordBytes; }
-__device__ __forceinline__ uint32_t res_probe_p(const ResLane &l, int nr) { return (l.lane < nr ? l.lane : 0) * kResRoundBytes; }
 // a slice of nr rounds, as soon as all of it is there
-template <bool FULL, bool PROBE = true>
-__device__ __forceinline__ void res_split_gather(const ResLane &l, const char *src, uint32_t probe, int nr, uint64_t (&x)[kResMaxRounds]) {
+template <bool FULL>
+__device__ __forceinline__ void res_split_gather(const ResLane &l, const char *src, int nr, uint64_t (&x)[kResMaxRounds]) {
   // (absent rounds read the slice's first and are cleared)
   const uint32_t offs[2] = {res_quad_base(l), res_pair_base(l) + 8 * kResRoundBytes}, end = nr * kResRoundBytes;
   auto at = [&](int i, const uint32_t (&o)[2]) {
@@ -313,7 +312,7 @@ __device__ __forceinline__ void res_split_gather(const ResLane &l, const char *s
     const uint32_t w = o[i < 8 ? 0 : 1] + res_split_part(i);
     return src + (w < end ? w : l.sl * 8);
   };
-  res_gather<true, kResMaxRounds, PROBE>(src, probe, offs, at, kResMaxRounds, x);
+  res_gather<true, kResMaxRounds>(offs, at, kResMaxRounds, x);
   if constexpr (!FULL) {
 #pragma unroll
     for (int i = 0; i < kResMaxRounds; ++i)
@@ -542,7 +541,8 @@ __device__ __forceinline__ void bf16_gather(const ResLane &l, const char *src, u
   const uint32_t lane0 = bf16_src(l, tile_floats, second);
   if (second) {
     const uint32_t offs[2] = {lane0 + first, lane0 + then};
-    res_gather<true, 2 * kResMaxRounds>(src, probe, offs, [&](int i, const uint32_t (&o)[2]) {
+    res_probe(src, probe);
+    res_gather<true, 2 * kResMaxRounds>(offs, [&](int i, const uint32_t (&o)[2]) {
       const int r = i / 2 % R;
       return src + o[i / kResMaxRounds] + (FULL || r < (i < kResMaxRounds ? n_first : n_then) ? r * kResRoundBytes : 0) + (i & 1) * kResWordBytes;
     }, 0, x);
@@ -550,7 +550,7 @@ __device__ __forceinline__ void bf16_gather(const ResLane &l, const char *src, u
     const uint32_t odd = (l.lane & 16) ? kResWordBytes : 0;
     const uint32_t offs[2] = {lane0 + first + odd, lane0 + then + odd};
     uint64_t y[kResMaxRounds];
-    res_gather<true, kResMaxRounds, false>(src, probe, offs, [&](int i, const uint32_t (&o)[2]) {
+    res_gather<true, kResMaxRounds>(offs, [&](int i, const uint32_t (&o)[2]) {
       const int r = i % R;
       return src + o[i / R] + (FULL || r < (i < R ? n_first : n_then) ? r * kResRoundBytes : 0);
     }, 0, y);
@@ -563,8 +563,8 @@ __device__ __forceinline__ void bf16_gather(const ResLane &l, const char *src, u
     }
   }
 }
-// (words to poll of the second slot tile: lanes from 32 on)
-__device__ __forceinline__ ResLane bf16_probe_lane(const ResLane &l) { return ResLane{l.lane & 31, 0, 0}; }
+// Words to probe: a tile of W_hh's four units writes half of a round's words (two per round), a tile of the projection two rounds'
+// (one per round).  Of the second slot tile: lanes from 32 on.
 __device__ __forceinline__ uint32_t bf16_probe_tile(const ResLane &l, size_t tile_floats, bool second) {
   return (l.lane >> 5) && second ? (uint32_t)tile_floats * 4 : 0u;
 }
@@ -678,7 +678,7 @@ __device__ __forceinline__ void res_p_phase(ResBlock &k, int step) {
           if constexpr (FULL) return src + o[i / R] + i % R * kResRoundBytes;
           return src + o[0] + (i + (i >= n1 ? jump : 0)) * kResRoundBytes;
         };
-        res_gather<FULL, kResMaxRounds, false>(src, 0, offs, at, nr, x);
+        res_gather<FULL, kResMaxRounds>(offs, at, nr, x);
 #pragma unroll 1
         for (int tp = 0; tp < k.nP; ++tp) {
           const uint64_t *w = k.tiles + (size_t)tp * (a.P * kResSlot / 2) + (size_t)k.wave * nh * 64 + l.lane;
@@ -721,9 +721,7 @@ __device__ __forceinline__ void res_p_phase(ResBlock &k, int step) {
           const uint32_t w = o[2 * hf] + res_part(p);
           return src + (p >= 4 ? o[2 * hf + 1] + res_part(p & 3) : w < end + hf * second ? w : l.sl * 8 + hf * second);
         };
-        const int pr = l.lane < 2 * nr ? l.lane >> 1 : 0;
-        const uint32_t probe = (pr < nh ? pr : pr - nh + 4 * nr) * kResRoundBytes + (l.lane & 1) * kResWordBytes;
-        res_gather<true, 12, false>(src, probe, offs, at, 12, x);
+        res_gather<true, 12>(offs, at, 12, x);
         uintx4_t xh[2], xl[2];
         uintx2_t yh[2], yl[2];
 #pragma unroll
@@ -770,7 +768,7 @@ __device__ __forceinline__ void res_p_phase(ResBlock &k, int step) {
         ResW16 xs;
         {
           uint64_t x[kResMaxRounds];
-          res_split_gather<FULL, false>(l, src, res_probe_h(l, nr), nr, x);
+          res_split_gather<FULL>(l, src, nr, x);
           res_split_act(x, kHidScale, xs);
         }
 #pragma unroll 1
@@ -943,7 +941,7 @@ __device__ __forceinline__ void res_j_phase(ResBlock &k, int step, const ResWJ<F
       uint64_t x[2 * kResMaxRounds];
       if constexpr (ST) res_stateless_pre<FULL, true, false>(a, k, l, nr, x);
       else {
-        const uint32_t probe = bf16_probe_tile(l, ad.p_tile, second) + res_probe_p(bf16_probe_lane(l), nr);
+        const uint32_t probe = bf16_probe_tile(l, ad.p_tile, second) + ((l.lane & 31) < nr ? l.lane & 31 : 0) * kResRoundBytes;
         bf16_gather<FULL>(l, reinterpret_cast<const char *>(ad.p(step, nt)) + k.wave * nr * kResRoundBytes, 0, nr > 5 ? 5 * kResRoundBytes : 0, min(nr, 5),
                           max(nr - 5, 0), second, ad.p_tile, probe, x);
       }
@@ -1005,7 +1003,7 @@ __device__ __forceinline__ void res_j_phase(ResBlock &k, int step, const ResWJ<F
         if constexpr (ST) res_stateless_pre<FULL, false, false>(a, k, l, nr, x);
         else {
           const uint32_t offs[2] = {(uint32_t)l.lane * 8, (uint32_t)l.lane * 8 + 5 * kResRoundBytes};
-          res_gather<FULL, kResMaxRounds, false>(src, 0, offs, [src](int i, const uint32_t (&o)[2]) { return src + o[i / 5] + i % 5 * kResRoundBytes; }, nr, x);
+          res_gather<FULL, kResMaxRounds>(offs, [src](int i, const uint32_t (&o)[2]) { return src + o[i / 5] + i % 5 * kResRoundBytes; }, nr, x);
         }
         relu(x);
         floatx4 acc[NJ];
@@ -1047,7 +1045,7 @@ __device__ __forceinline__ void res_j_phase(ResBlock &k, int step, const ResWJ<F
       {
         uint64_t x[kResMaxRounds];
         if constexpr (ST) res_stateless_pre<FULL, false, true>(a, k, l, nr, x);
-        else res_split_gather<FULL, false>(l, src, res_probe_p(l, nr), nr, x);
+        else res_split_gather<FULL>(l, src, nr, x);
         relu(x);
         float m = 0.f;
 #pragma unroll
@@ -1350,9 +1348,9 @@ __device__ __forceinline__ void res_worker(ResBlock k, const ResTab &tab, float 
         // (nearly always there: the logits needed all of it)
         if constexpr (!SPLIT) {
           const uint32_t offs[2] = {(uint32_t)l.lane * 8, (uint32_t)l.lane * 8 + 5 * kResRoundBytes};
-          res_gather<FULL, kResMaxRounds, false>(src, 0, offs, [src](int i, const uint32_t (&o)[2]) { return src + o[i / 5] + i % 5 * kResRoundBytes; }, nrp, x);
+          res_gather<FULL, kResMaxRounds>(offs, [src](int i, const uint32_t (&o)[2]) { return src + o[i / 5] + i % 5 * kResRoundBytes; }, nrp, x);
         } else {
-          res_split_gather<FULL, false>(l, src, 0, nrp, x);
+          res_split_gather<FULL>(l, src, nrp, x);
           res_split_act(x, kHidScale, xs);
         }
         auto three = [&](auto first) {
