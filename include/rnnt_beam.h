@@ -290,6 +290,10 @@ int rnnt_beam_debug_set_spin_limit(rnnt_beam_t *h, int32_t polls);
  * of blocks takes itself to lie on several XCDs and writes its hand-over stores through. */
 int rnnt_beam_debug_stall_resident(rnnt_beam_t *h, int32_t step);
 
+/* For tests: the groups of blocks of the handle's last resident launch (0: none yet), and how many of them found themselves on one
+ * XCD and handed over through its L2.  Synchronises. */
+int rnnt_beam_debug_resident_groups(rnnt_beam_t *h, int32_t *groups, int32_t *local);
+
 /* Test hook for the resident loop's memory: its second copy of the weights, hand-over arrays and tables are given back and laid
  * out anew, with allocation number `fail_alloc` (0, 1, ..) taken to fail.  The handle then decodes without that loop, as it
  * does where create finds no memory for them.  -1: none fails. */

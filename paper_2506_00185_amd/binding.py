@@ -18,7 +18,8 @@ EXPORTS = ["rnnt_beam_create", "rnnt_lm_create", "rnnt_beam_decode", "rnnt_beam_
            "rnnt_beam_decode_injected", "rnnt_beam_dump_tree", "rnnt_beam_debug_encproj", "rnnt_lm_debug_query",
            "rnnt_beam_last_decode_ms", "rnnt_beam_set_profiling", "rnnt_beam_kernel_times", "rnnt_beam_last_error",
            "rnnt_beam_destroy", "rnnt_lm_destroy", "rnnt_beam_debug_block_map", "rnnt_beam_decode_static", "rnnt_beam_debug_set_spin_limit",
-           "rnnt_beam_last_step_loop", "rnnt_beam_debug_stall_resident", "rnnt_beam_debug_rebuild_resident"]
+           "rnnt_beam_last_step_loop", "rnnt_beam_debug_stall_resident", "rnnt_beam_debug_rebuild_resident",
+           "rnnt_beam_debug_resident_groups"]
 
 
 class RnntBeamError(RuntimeError):
@@ -279,6 +280,12 @@ class BeamDecoder:
 
     def debug_stall_resident(self, step: int):
         _check(load_library().rnnt_beam_debug_stall_resident(self.handle, C.c_int32(step)), self.handle)
+
+    def debug_resident_groups(self):
+        """(groups of the last resident launch, those that handed over through the L2 of one XCD)"""
+        groups, local = C.c_int32(), C.c_int32()
+        _check(load_library().rnnt_beam_debug_resident_groups(self.handle, C.byref(groups), C.byref(local)), self.handle)
+        return groups.value, local.value
 
     def debug_rebuild_resident(self, fail_alloc: int = -1):
         _check(load_library().rnnt_beam_debug_rebuild_resident(self.handle, C.c_int32(fail_alloc)), self.handle)

@@ -94,7 +94,8 @@ struct ResArgs {
   float *hb, *pb, *zb;               // rings of the hand-over arrays, all groups
   uint64_t *words;
   const ResTab *tab;                 // of the group's blocks behind the selecting ones
-  int *ctl;                          // [0] blocks that have started, [1] abort, [2 + group] the XCDs that its blocks found themselves on
+  int *ctl;                          // [0] blocks that have started, [1] abort, [2 + group] the XCDs that its blocks found themselves on,
+                                     // [64 + group] 1: on one, and their hand-over stores stay in its L2
   volatile int *h_abort;             // pinned host word
   SelectArgs sel;
   LmView lm;
@@ -1780,6 +1781,7 @@ __global__ __launch_bounds__(kResThreads, 2) void k_decode_resident(ResArgs) {
       __builtin_amdgcn_s_sleep(4);
     }
     s_ok = ok && __popc(load_agent(a.ctl + 2 + g)) == 1 && a.stall_step != kResNotLocal ? 2 : ok;
+    if (s_ok == 2 && (int)blockIdx.x < a.stride) store_agent(a.ctl + 64 + g, 1);
   }
   ResBlock k;
   k.g = g;

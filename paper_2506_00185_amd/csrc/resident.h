@@ -29,6 +29,7 @@ struct Resident {
   int *ctl = nullptr;
   ResTab *tab = nullptr;          // who owns what in a group, as uploaded for the last launch:
   int tab_blocks = 0, tab_sel = 0;
+  int n_groups = 0;               // of the last launch
   int *h_abort = nullptr, *h_abort_dev = nullptr;  // pinned
   std::vector<void *> allocs;
 };
@@ -70,6 +71,8 @@ struct ResidentBatch {
 };
 // whether a batch of this shape can run as one resident launch
 bool resident_fits(const Resident &r, const rnnt_config_t &c, int B, int K, int T, int max_steps, bool has_lm, bool fold);
+// groups of the last launch, and how many of them handed over through the L2 of one XCD; waits for the device
+hipError_t resident_local_groups(const Resident &r, int *groups, int *local);
 hipError_t resident_launch(Resident &r, const rnnt_config_t &c, const ResidentBatch &b, hipStream_t s);
 
 }  // namespace rb

@@ -1662,6 +1662,13 @@ int rnnt_beam_debug_stall_resident(rnnt_beam_t *h, int32_t step) {
   return RNNT_OK;
 }
 
+int rnnt_beam_debug_resident_groups(rnnt_beam_t *h, int32_t *groups, int32_t *local) {
+  if (!h || !groups || !local) return RNNT_E_ARG;
+  RB_HIP(h, hipDeviceSynchronize());
+  RB_HIP(h, resident_local_groups(h->res, groups, local));
+  return RNNT_OK;
+}
+
 int rnnt_beam_debug_rebuild_resident(rnnt_beam_t *h, int32_t fail_alloc) {
   if (!h) return RNNT_E_ARG;
   RB_HIP(h, hipDeviceSynchronize());

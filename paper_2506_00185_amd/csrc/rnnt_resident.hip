@@ -84,6 +84,8 @@ __global__ void k_pack_bf16(const float *W, int rows, int K, int n_tiles, uint64
   }
 }
 
+constexpr int kResMaxGroups = 62, kResCtlWords = 128;  // (two words of ctl per group)
+
 // pre-fill of the hand-over arrays, zero words and counters
 __global__ void k_resident_init(ResArgs a) {
   const size_t gid = (size_t)blockIdx.x * blockDim.x + threadIdx.x, n = (size_t)gridDim.x * blockDim.x;
@@ -92,12 +94,11 @@ __global__ void k_resident_init(ResArgs a) {
   for (size_t i = gid; i < res_p_floats(a) / 4; i += n) reinterpret_cast<uintx4_t *>(a.pb)[i] = e;
   for (size_t i = gid; i < res_z_floats(a) / 4; i += n) reinterpret_cast<uintx4_t *>(a.zb)[i] = e;
   for (size_t i = gid; i < res_words(a); i += n) a.words[i] = 0;
-  if (gid < 64) a.ctl[gid] = 0;
+  if (gid < kResCtlWords) a.ctl[gid] = 0;
 }
 
 constexpr int kResShortSpin = 1000;  // a test's limit: the launch waits, for a microsecond, for one block more than it has
 
-constexpr int kResMaxGroups = 62;  // words of ctl
 constexpr int kResStallPolls = 4096;  // a test's wait for data that does not come
 
 struct Plan {
@@ -274,7 +275,7 @@ int resident_create(Resident &r, const rnnt_config_t &c, const ResidentWeights &
                         : alloc(&r.WPf, (size_t)nP * 16 * c.P));
   }
   ok = ok && alloc(&r.zb, kResStepRing * rows * w.out_rows) &&
-       alloc(&r.words, kResStepRing * rows) && alloc(&r.ctl, 64) && alloc(&r.tab, r.n_cus);
+       alloc(&r.words, kResStepRing * rows) && alloc(&r.ctl, kResCtlWords) && alloc(&r.tab, r.n_cus);
   if (!ok) return fail("resident loop: hipMalloc");
   if ((e = hipHostMalloc(reinterpret_cast<void **>(&r.h_abort), 128, hipHostMallocMapped)) != hipSuccess) return fail("hipHostMalloc");
   if ((e = hipHostGetDevicePointer(reinterpret_cast<void **>(&r.h_abort_dev), r.h_abort, 0)) != hipSuccess) return fail("pinned word");
@@ -335,6 +336,7 @@ hipError_t resident_launch(Resident &r, const rnnt_config_t &c, const ResidentBa
   a.stall_step = b.stall_step;
   a.poll_limit = std::min(b.stall_step < 0 ? 1 << 19 : kResStallPolls, b.spin_limit);
   const bool short_spin = b.spin_limit < kResShortSpin;
+  r.n_groups = p.n_groups;
   a.start_blocks = p.n_groups * p.n_blocks + (short_spin ? 1 : 0);
   a.start_limit = short_spin ? 100 : 5000000;  // 50 ms
   *reinterpret_cast<volatile int *>(r.h_abort) = 0;
@@ -354,6 +356,16 @@ hipError_t resident_launch(Resident &r, const rnnt_config_t &c, const ResidentBa
   if (e != hipSuccess) return e;
   hipLaunchKernelGGL(k, dim3(p.stride * p.n_blocks), dim3(kResThreads), p.lds, s, a);
   return hipGetLastError();
+}
+
+hipError_t resident_local_groups(const Resident &r, int *groups, int *local) {
+  int words[kResCtlWords];
+  *groups = r.n_groups;
+  *local = 0;
+  if (r.n_groups == 0) return hipSuccess;
+  const hipError_t e = hipMemcpy(words, r.ctl, sizeof words, hipMemcpyDeviceToHost);
+  for (int g = 0; e == hipSuccess && g < r.n_groups; ++g) *local += words[64 + g] == 1;
+  return e;
 }
 
 }  // namespace rb

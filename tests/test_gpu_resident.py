@@ -398,9 +398,12 @@ def test_groups_that_do_not_lie_on_one_xcd(kw):
     enc = S.make_enc(c, L, 48)
     dec = A.BeamDecoder(c, w)
     ref = gpu_decode(dec, enc, L)
+    groups, local = dec.debug_resident_groups()
+    assert groups == local == min(c["B"], 8)  # (the other decode hands over through the L2)
     dec.debug_stall_resident(-2)
     r = gpu_decode(dec, enc, L)
     assert dec.last_step_loop() == "resident"
+    assert dec.debug_resident_groups() == (groups, 0)
     for key in KEYS:
         np.testing.assert_array_equal(r[key], ref[key])
 
