@@ -94,8 +94,7 @@ struct ResArgs {
   float *hb, *pb, *zb;               // rings of the hand-over arrays, all groups
   uint64_t *words;
   const ResTab *tab;                 // of the group's blocks behind the selecting ones
-  int *ctl;                          // [0] blocks that have started, [1] abort, [2 + group] the XCDs that its blocks found themselves on,
-                                     // [64 + group] 1: on one, and their hand-over stores stay in its L2
+  int *ctl;                          // [0] blocks that have started, [1] abort, [2 + group] the XCDs that its blocks found themselves on
   volatile int *h_abort;             // pinned host word
   SelectArgs sel;
   LmView lm;
@@ -109,6 +108,9 @@ struct ResArgs {
   int fold;                          // the per-step launches would fold the blank and duration columns (see res_fold_mma)
   int stall_step;                    // a test's: from this step on the last tile of slots gets no logits (below 0: never)
 };
+
+// whether the blocks of a group, which found themselves on these XCDs, hand over through one XCD's L2 (see res_store)
+__host__ __device__ inline bool res_on_one_xcd(int xcds, int stall_step) { return xcds != 0 && (xcds & (xcds - 1)) == 0 && stall_step != kResNotLocal; }
 
 // The kernel's arguments, read from the argument segment anew at the begin of every phase: kept in scalar registers over
 // the whole loop they would push the weights out of the vector registers (a thousand spills).  What is left by the compiler's
@@ -1780,8 +1782,7 @@ __global__ __launch_bounds__(kResThreads, 2) void k_decode_resident(ResArgs) {
       }
       __builtin_amdgcn_s_sleep(4);
     }
-    s_ok = ok && __popc(load_agent(a.ctl + 2 + g)) == 1 && a.stall_step != kResNotLocal ? 2 : ok;
-    if (s_ok == 2 && (int)blockIdx.x < a.stride) store_agent(a.ctl + 64 + g, 1);
+    s_ok = ok && res_on_one_xcd(load_agent(a.ctl + 2 + g), a.stall_step) ? 2 : ok;
   }
   ResBlock k;
   k.g = g;

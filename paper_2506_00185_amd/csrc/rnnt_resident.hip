@@ -84,7 +84,7 @@ __global__ void k_pack_bf16(const float *W, int rows, int K, int n_tiles, uint64
   }
 }
 
-constexpr int kResMaxGroups = 62, kResCtlWords = 128;  // (two words of ctl per group)
+constexpr int kResCtlWords = 64, kResMaxGroups = kResCtlWords - 2;
 
 // pre-fill of the hand-over arrays, zero words and counters
 __global__ void k_resident_init(ResArgs a) {
@@ -337,6 +337,7 @@ hipError_t resident_launch(Resident &r, const rnnt_config_t &c, const ResidentBa
   a.poll_limit = std::min(b.stall_step < 0 ? 1 << 19 : kResStallPolls, b.spin_limit);
   const bool short_spin = b.spin_limit < kResShortSpin;
   r.n_groups = p.n_groups;
+  r.last_stall_step = b.stall_step;
   a.start_blocks = p.n_groups * p.n_blocks + (short_spin ? 1 : 0);
   a.start_limit = short_spin ? 100 : 5000000;  // 50 ms
   *reinterpret_cast<volatile int *>(r.h_abort) = 0;
@@ -364,7 +365,7 @@ hipError_t resident_local_groups(const Resident &r, int *groups, int *local) {
   *local = 0;
   if (r.n_groups == 0) return hipSuccess;
   const hipError_t e = hipMemcpy(words, r.ctl, sizeof words, hipMemcpyDeviceToHost);
-  for (int g = 0; e == hipSuccess && g < r.n_groups; ++g) *local += words[64 + g] == 1;
+  for (int g = 0; e == hipSuccess && g < r.n_groups; ++g) *local += res_on_one_xcd(words[2 + g], r.last_stall_step);
   return e;
 }
 
