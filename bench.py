@@ -27,7 +27,7 @@ sys.path.insert(0, ROOT)
 
 PEAK_FP32_MFMA_TFLOPS = 157.3  # MI355X, dense fp32 matrix
 PEAK_BF16_MFMA_TFLOPS = 2500.0
-PEAK_SPLIT_MFMA_TFLOPS = 2500.0 / 3  # float32 products on operands split into two float16: three 16-bit ones for each
+PEAK_SPLIT_MFMA_TFLOPS = 2500.0 / 3  # float32 products on operands split into two float16: three 16-bit ones for each (320 wide and more)
 PEAK_HBM_GBS = 8000.0
 
 LOOP_KERNELS = ("k_step_main", "k_select", "k_lstm_pointwise", "k_pred_proj", "k_lm_rows", "k_joint_big", "k_row_select",
@@ -121,7 +121,7 @@ def kernel_bound(name: str, c: dict) -> tuple:
         return "mfma", PEAK_BF16_MFMA_TFLOPS, "TFLOP/s"
     if name in ("k_step_main", "k_pred_proj", "k_decode_resident"):
         # (the recurrent product, most of the FLOPs, of bf16-joint models multiplies in float32)
-        return "mfma", PEAK_FP32_MFMA_TFLOPS if c["prec"] == "bf16" else PEAK_SPLIT_MFMA_TFLOPS, "TFLOP/s"
+        return "mfma", PEAK_FP32_MFMA_TFLOPS if c["prec"] == "bf16" or min(c["H"], c["P"]) < 320 else PEAK_SPLIT_MFMA_TFLOPS, "TFLOP/s"
     if name.startswith("k_gemm_tiled"):
         return "mfma", PEAK_BF16_MFMA_TFLOPS if c["prec"] == "bf16" else PEAK_FP32_MFMA_TFLOPS, "TFLOP/s"
     return "hbm", PEAK_HBM_GBS, "GB/s"

@@ -16,13 +16,14 @@
 // Hand-over between blocks: an array that one phase writes and another reads is pre-filled with a bit pattern that no
 // result has (a NaN with all bits set); the reader loads the data itself, device-coherently, until none of it holds the
 // pattern.  No barrier, no flag and no acknowledged store lies between the two (one hop costs 0.6 us; stores, their
-// acknowledgement, a counter and then the loads 2.0 us).  The blocks of a group lie on one XCD and hand over through its L2.  The words of the selection carry the step's number instead.
+// acknowledgement, a counter and then the loads 2.0 us).  Where the blocks of a group find themselves on one XCD they hand over through
+// its L2, else their stores are written through.  The words of the selection carry the step's number instead.
 // A writer puts the pattern back once a word of a later phase proves that every reader is through (see the clear_
 // functions), one or two steps before the place is used again.
 //
 // Every sum is formed in the order of the per-step kernels (K slices of 1/8 of the contraction, slices added first to last), so the
-// results are the same bit for bit.  Float32 models whose weights can be split multiply on the float16 matrix instructions, both
-// operands split in two (see split_f16): in float32, W_hh h took 3.2 us per step and tile of 16 slots, as long as the selection it hides under, and the other
+// results are the same bit for bit.  Float32 models from 320 wide on whose weights can be split multiply on the float16 matrix
+// instructions, both operands split in two (see split_f16): in float32, W_hh h took 3.2 us per step and tile of 16 slots, as long as the selection it hides under, and the other
 // two contractions 3 us of the chain.  bf16-joint models keep W_hh h on float32 matrix instructions (a 16x16x4 one rounds like four
 // fused multiply-adds in a row): they round activations to 8 bits, and near ties there follow every last bit of the hidden state.
 // (ms per decode before / after the splits, the gathers and the ends of waves described below: one utterance 8.65 / 6.95, greedy batch
@@ -114,9 +115,9 @@ __host__ __device__ inline bool res_on_one_xcd(int xcds, int stall_step) { retur
 
 // The kernel's arguments, read from the argument segment anew at the begin of every phase: kept in scalar registers over
 // the whole loop they would push the weights out of the vector registers (a thousand spills).  What is left by the compiler's
-// report: LSTM forms 48 vector registers spilled (bf16 8; other widths 60, bf16 4) and 130 to 210 scalar ones (into vector
-// lanes), 256 vector registers in use; stateless forms no vector register, 90 to 130 scalar ones.  The selecting blocks, whose
-// code needs the scalar ones, share the kernel with the owners of the weights.
+// report: LSTM forms 48 vector registers spilled 640 wide and 120 at other widths where the weights are split, 4 to 10 in the other forms,
+// and 120 to 260 scalar ones (into vector lanes), 256 vector registers in use; stateless forms no vector register, 90 to 150 scalar
+// ones.  The selecting blocks, whose code needs the scalar ones, share the kernel with the owners of the weights.
 __device__ __forceinline__ const ResArgs &res_args() {
   typedef const __attribute__((address_space(4))) ResArgs ConstArgs;
   ConstArgs *p = (ConstArgs *)__builtin_amdgcn_kernarg_segment_ptr();

@@ -152,22 +152,23 @@ bool assign_tiles(const rnnt_config_t &c, int n_blocks, std::vector<ResTab> &tab
 }
 
 // Decoders that stay with the per-step launches although they fit the loop: narrow ones, whose per-step launches are short, with
-// several tiles of slots or wide beams, whose selection takes longer here.  Both sides timed in turn, time of the per-step launches
-// over the loop's.  Split decoders (320 wide and more): 1.01 and more at each of 250 shapes of two and three tiles (to 512 wide, V = 29
+// several tiles of slots or wide beams, whose selection takes longer here.  Both sides timed, time of the per-step launches over the
+// loop's.  Split decoders (320 wide and more): 1.01 and more at each of 250 shapes of two and three tiles (to 512 wide, V = 29
 // to 1000, beams 5 to 16, LM and TDT among them; means 1.33 in float32, 1.23 with the bf16 joint); 640 wide 1.07 and more.
+// Not split, 64 to 256 wide: one tile 1.23 to 1.94, two tiles at beams up to 8 1.24 to 1.52.
 bool per_step_is_faster(const Resident &r, const rnnt_config_t &c, int B, int K, int n_tiles) {
   const bool bf = c.prec == RNNT_BF16_JOINT;
-  if (c.pred != RNNT_PRED_LSTM)  // 64 and 128 wide, V = 1000: 0.95 to 1.34 (one utterance below 1.08); bf16, one utterance, 320 wide: 1.07 and 1.12
-    return K > 8 && (c.H <= 128 || (bf && B == 1 && c.H <= 320));
-  // float32 instructions, 64 to 256 wide, one tile: 1.23 to 1.98; two tiles, beams up to 8: 1.24 to 1.53
+  // 64 and 128 wide, V = 1000: one utterance 0.95 to 1.08, eight 1.01 to 1.15; 320 wide, bf16, one utterance 1.09 and 1.11 (these two not
+  // moved yet)
+  if (c.pred != RNNT_PRED_LSTM) return K > 8 && (c.H <= 128 || (bf && B == 1 && c.H <= 320));
   if (std::max(c.H, c.P) <= 192) {
-    // float32, three tiles: V = 1000 at beams up to 8 1.15 to 1.28, else 0.85 to 1.62
+    // float32, three tiles: V = 1000 at beams up to 8 1.17 to 1.26; else 0.85 to 1.50, V = 260 at beams above 4 and V = 29 above 1
     if (!bf && n_tiles == 3 && !(c.V > 512 && K <= 8)) return true;
-    // two tiles, beams above 8, float32: V = 29 and 260 1.13 to 1.72, V = 500 0.97 to 1.42, V = 1000 1.05 to 1.16 (not moved yet);
+    // two tiles, beams above 8, float32: V = 29 and 260 1.12 to 1.65, V = 500 0.98 to 1.27, V = 1000 1.04 to 1.13 (not moved yet);
     // bf16: V = 450 0.97 to 1.84, V > 512 1.00 to 1.34
     return n_tiles > 1 && K > 8 && c.V > (bf ? 512 : 384);
   }
-  // 256 wide, three tiles: V up to 500 at beam 4 0.92 to 0.98, else 0.95 to 1.53, most above 1
+  // 256 wide, three tiles: V up to 500 at beam 4 0.93 to 0.99, else 0.94 to 1.40
   return r.form == kResF32 && n_tiles == 3 && K <= 4 && c.V <= 512;
 }
 
@@ -185,9 +186,8 @@ Plan make_plan(const Resident &r, const rnnt_config_t &c, int B, int K, bool has
   const int slots = p.nu * K;
   p.NT = (slots + kResSlot - 1) / kResSlot;
   if (p.NT > kResMaxNT) return p;
-  // Stateless decoders have no recurrent product to hide under the selection: with more than one tile of slots per group the
-  // per-step launches are as fast or faster (float32, 640 wide, us per step here / there: batch 32 beam 4 13.1 / 19.1; two
-  // tiles, batch 16 beam 16 34.8 / 33.3; three, batch 32 beam 12 37.3 / 36.0)
+  // Stateless decoders: one tile of slots, whose last tokens the owners of output-layer tiles keep.  (With more, float32, 640 wide, us per
+  // step here / there, before hand-overs stayed in the L2: two tiles, batch 16 beam 16 34.8 / 33.3; three, batch 32 beam 12 37.3 / 36.0.)
   if (c.pred != RNNT_PRED_LSTM && p.NT > 1) return p;
   if (per_step_is_faster(r, c, B, K, p.NT)) return p;
   const int most_sel = std::max(1, p.n_blocks / 8);
