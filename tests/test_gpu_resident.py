@@ -51,6 +51,9 @@ CASES = [
     dict(B=57, beam=4, V=1024, prec="bf16", **W640, **TDT),
     dict(B=64, beam=2, V=1024, **W640, **ST, ctx=2),
     dict(B=57, beam=1, V=1024, prec="bf16", **W640, **ST, ctx=1, **TDT),
+    # split products of unequal widths, one of them 640
+    dict(B=9, beam=4, V=90, H=384, P=640, E=64, D=32), dict(B=5, beam=8, V=700, H=640, P=320, E=64, D=32, **TDT),
+    dict(B=17, beam=9, V=300, H=512, P=384, E=64, D=32), dict(B=8, beam=8, V=513, H=320, P=64, E=64, D=32, **ST, ctx=2),
 ]
 
 
@@ -339,13 +342,17 @@ def test_split_products_of_rows_with_outliers(oracle, h, B, beam, apart, huge):
         np.testing.assert_array_equal(g[key], ref[key])
 
 
-@pytest.mark.parametrize("h,p,more", [(320, 320, {}), (640, 640, {}), (448, 640, {}), (640, 640, dict(ST, ctx=2))])
+@pytest.mark.parametrize("h,p,more", [(320, 320, {}), (640, 640, {}), (448, 640, {}), (640, 640, dict(ST, ctx=2)),
+                                      # per-step launches: four waves a block, halves of k
+                                      (352, 352, {}), (384, 384, dict(use_graph=False))])
 def test_error_of_split_products_against_64_bits(oracle, h, p, more):
     """Scores of decodes with logits of some hundreds, whose errors are those of the products, against the oracle's 64 bits: no larger
     than with float32 instructions, which the same decoder runs when a token that a bias has closed is closed by a weight without a
     split.  Bound: 4 standard errors of the ratio of the two (0.02 to 0.03 at 20 decodes of 16 utterances) above 1."""
     import paper_2506_00185_amd as A
     square, n = np.zeros(2), 0
+    more = dict(more)
+    use_graph = more.pop("use_graph", True)
     for seed in range(100, 120):
         c = S.custom_config(**dict(dict(B=16, T=3, T_min=3, s=2, V=300, beam=8, blank_bias=0.0, H=h, P=p, E=64, D=64), **more))
         w = {k: np.array(v) for k, v in S.make_weights(c, seed).items()}
@@ -359,7 +366,7 @@ def test_error_of_split_products_against_64_bits(oracle, h, p, more):
         enc = S.make_enc(c, L, seed + 2)
         o = oracle.decode(c, w, enc, L)
         lists = [[{tuple(r["tokens"][b, j, :l]): r["scores"][b, j] for j, l in enumerate(r["lens"][b]) if l >= 0} for b in range(c["B"])]
-                 for r in (o, *[gpu_decode(A.BeamDecoder(c, x), enc, L, want_tree=False) for x in (w, ref)])]
+                 for r in (o, *[gpu_decode(A.BeamDecoder(c, x, use_graph=use_graph), enc, L, want_tree=False) for x in (w, ref)])]
         for want, split, plain in zip(*lists):
             for k in want.keys() & split.keys() & plain.keys():
                 square += (split[k] - want[k]) ** 2, (plain[k] - want[k]) ** 2
