@@ -58,7 +58,6 @@ constexpr int kResMaxV = 1024;
 constexpr int kResStepRing = 4;      // ring of the hand-over arrays
 constexpr int kResNotLocal = -2;     // stall_step of a test: the groups take themselves to lie on several XCDs
 constexpr uint32_t kResEmpty = 0xffffffffu;
-constexpr int kResSurvivors = 128;
 // How a decoder's products are formed: on float32 matrix instructions; W_out and W_pred on bf16 ones (the bf16 joint); on float16 ones
 // from split operands (see split_f16).
 enum ResForm { kResF32, kResBf16, kResSplit };
@@ -185,6 +184,40 @@ struct ResWait {
   }
 };
 
+// Hand-over stores.  Blocks on one XCD share its L2: a plain store leaves the data there, and a device-coherent load finds it
+// there (such a load passes by the L1 but not by the L2: 107 ns, like any other that the L2 answers).  Across XCDs the store has
+// to be written through, which takes longer to be seen and to be acknowledged.  (One word from block to block and back, per
+// direction: 272 ns on one XCD with plain stores, 375 with written-through ones, 440 between two XCDs.)
+template <typename T>
+__device__ __forceinline__ void res_store(bool local, T *p, T v) {
+  if (local) __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WAVEFRONT);
+  else store_agent(p, v);
+}
+__device__ __forceinline__ void res_store_pair(bool local, uint64_t *p, int second, uint64_t v0, uint64_t v1) {
+  if (local) {
+    __hip_atomic_store(p, v0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WAVEFRONT);
+    __hip_atomic_store(p + second, v1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WAVEFRONT);
+  } else {
+    store_agent(p, v0);
+    store_agent(p + second, v1);
+  }
+}
+__device__ __forceinline__ void res_store16(bool local, float *p, floatx4 v) {
+  if (local) asm volatile("global_store_dwordx4 %0, %1, off" ::"v"(p), "v"(v) : "memory");
+  else store16_through(p, v);
+}
+
+// What a step decided for a slot: step tag (16 bits, step + 1) | utterance finished (1) | parent slot in the group (6) | token + 1 (21) | frame (20)
+constexpr int kWordMaxFrames = 1 << 20;
+__device__ __forceinline__ uint64_t slot_word(int step, int fin, int src, int tok, int t) {
+  return (uint64_t)((step + 1) & 0xffff) | (uint64_t)fin << 16 | (uint64_t)src << 17 | (uint64_t)(tok + 1) << 23 |
+         (uint64_t)t << 44;
+}
+__device__ __forceinline__ int word_tag(uint64_t w) { return (int)(w & 0xffff); }
+__device__ __forceinline__ int word_finished(uint64_t w) { return (int)(w >> 16) & 1; }
+__device__ __forceinline__ int word_src(uint64_t w) { return (int)(w >> 17) & 63; }
+__device__ __forceinline__ int word_tok(uint64_t w) { return ((int)(w >> 23) & 0x1fffff) - 1; }
+__device__ __forceinline__ int word_frame(uint64_t w) { return (int)(w >> 44); }
 __device__ __forceinline__ uint64_t res_load(const char *p) { return load_agent(reinterpret_cast<const uint64_t *>(p)); }
 // N 8-byte words of a lane as soon as all are there (in every lane of the wave).  base: the same in all lanes; at(i, o): address of
 // word i, base + one of the lane's offsets + a constant; the first n are used (FULL: all N).  (The offsets are made anew for every
@@ -1406,34 +1439,82 @@ __device__ __forceinline__ void res_worker(ResBlock k, const ResTab &tab, float 
 // ---------------------------------------------------------------------------
 // selecting blocks
 // ---------------------------------------------------------------------------
+// One step of an utterance: its rows of logits are read by all waves of the block, which leave statistics of every chunk of 32 columns
+// in LDS, and the keys themselves (res_row); one wave then takes the Beam best of all candidates of the utterance at once
+// (res_select).  It turns the largest key of every set of chunks into the score that it would have as a candidate: the K-th largest of
+// these is a lower bound of the K-th largest of all candidates, a close one, and only the chunks that reach it, few more than K,
+// are looked at again.  (With the K best of every row first, ranked among the dozens of keys that reach a bound of the row alone, and
+// then the ranking of K (K + 1) candidates, the time from the last logit to the words was, at beam 4 / 8 / 12, 4.4 / 7.0 / 9.0 us, here
+// 2.8 / 5.7 / 6.3; ms per decode: one utterance, beam 4, 7.09 -> 6.13, batch 32 beam 4 7.62 -> 6.61, batch 16 beam 12 15.4 -> 12.4, batch
+// 32 beam 8 with LM 13.4 -> 12.7, stateless batch 8 3.35 -> 2.89.)
 constexpr int kResMaxHyps = 24;  // hypotheses of a selecting block
-struct ResSelLds {  // LDS of the selection beside the scratch of its utterances
-  uint64_t cand[512];                                   // K lists of K per utterance (upc * K * K <= 512)
-  float smax[kResMaxHyps], ssum[kResMaxHyps], zs[kResMaxHyps * 9];
-  uint64_t surv[kResMaxHyps][kResSurvivors];
-  float2 cst[kResMaxHyps][32];                          // (maximum, sum of exponentials) of every chunk of 32 columns
-  int n_surv[kResMaxHyps][2];
+// floats of a row of keys in LDS (those behind the vocabulary are -inf)
+__host__ __device__ inline int res_row_floats(int V) { return V <= 128 ? 128 : V <= 512 ? 512 : kResMaxV; }
+// An utterance's hypotheses (score to ctx: kept from step to step) and what a step of its selection needs.
+constexpr int kResTop = 64;      // candidates that are ranked
+struct ResUtt {
+  double score[kMaxBeam];
+  int4 state[kMaxBeam];            // frame, symbols in the frame, length, last token
+  uint32_t hash[kMaxBeam];
+  int kind[kMaxBeam];              // 0: empty, 1: waits or has finished, 2: expanded, 3: the same, with blank alone
+  int ctx[kMaxBeam][kCtxMax];
+  // of a hypothesis' candidates (see res_select): score = (score of the hypothesis + key) + tok_base + lm_const
+  double tok_base[kMaxBeam], lm_const[kMaxBeam], lse[kMaxBeam], margin[kMaxBeam], delta[kMaxBeam], blank_key[kMaxBeam], blank[kMaxBeam];
+  int adv[kMaxBeam];               // frames that a token (low half) and that blank advances
+  float set[64];
+  int chunk[16 * 32 + 16];         // hypothesis * 32 + chunk of those that reach the bound
+  double top_key[kResTop + 8], top_val[kResTop];
+  int top_flat[kResTop + 8];
+  // new slots (see recombine)
+  double n_score[kMaxBeam];
+  int n_t[kMaxBeam], n_sym[kMaxBeam], n_len[kMaxBeam], n_last[kMaxBeam], n_live[kMaxBeam];
+  uint32_t n_hash[kMaxBeam];
+  int n_parent[kMaxBeam], n_code[kMaxBeam];
+};
+struct ResSelLds {  // LDS of the selection beside its utterances' and the rows of keys
+  float zs[kResMaxHyps * 9];
+  float2 cst[kResMaxHyps][32];     // (maximum, sum of exponentials) of every chunk of 32 columns
+  float kmax[kResMaxHyps][32];     // largest key of every chunk, where keys are not the logits
   LmCtxRec rec[kResWaves][kCtxMax + 1];
 };
 
-// x[i] = max (or sum) of x[i] and the lane that CTRL names, for N values at once: one instruction each plus the wait
-// states of the first (the compiler's form takes five per value)
-#define RB_RES_DPP(NAME, OP)                                                                                       \
-  template <int CTRL, int N>                                                                                       \
-  __device__ __forceinline__ void NAME(float (&x)[N]) {                                                            \
-    _Pragma("unroll") for (int i = 0; i < N; ++i) {                                                                \
-      float y;                                                                                                     \
-      if constexpr (CTRL == kDppXor1) asm("s_nop 1\n\t" OP " %0, %1, %1 quad_perm:[1,0,3,2] row_mask:0xf bank_mask:0xf" : "=v"(y) : "v"(x[i])); \
-      else if constexpr (CTRL == kDppXor2) asm("s_nop 1\n\t" OP " %0, %1, %1 quad_perm:[2,3,0,1] row_mask:0xf bank_mask:0xf" : "=v"(y) : "v"(x[i])); \
-      else if constexpr (CTRL == kDppHalfMirror) asm("s_nop 1\n\t" OP " %0, %1, %1 row_half_mirror row_mask:0xf bank_mask:0xf" : "=v"(y) : "v"(x[i])); \
-      else asm("s_nop 1\n\t" OP " %0, %1, %1 row_mirror row_mask:0xf bank_mask:0xf" : "=v"(y) : "v"(x[i]));      \
-      x[i] = y;                                                                                                    \
-    }                                                                                                              \
+// floats ahead of the rows of keys
+__host__ __device__ inline size_t res_sel_floats(int upc, int NT) {
+  return (sizeof(ResSelLds) + 15) / 16 * 4 + (upc * sizeof(ResUtt) + (size_t)NT * kResSlot * kResWaves * 8 + 15) / 16 * 4;
+}
+
+// x[i] = max (or sum) of x[i] and the lane that CTRL names, for N values at once: one instruction each plus the wait states of the
+// first of four (the compiler's form takes five per value; it does not know of the wait states between these and a DPP instruction of
+// its own: none may follow on the results)
+#define RB_RES_DPP1(OP, DPP) asm("s_nop 1\n\t" OP " %0, %0, %0 " DPP " row_mask:0xf bank_mask:0xf" : "+v"(x[i]))
+#define RB_RES_DPP4(OP, DPP)                                                                             \
+  asm("s_nop 1\n\t" OP " %0, %0, %0 " DPP " row_mask:0xf bank_mask:0xf\n\t" OP " %1, %1, %1 " DPP        \
+      " row_mask:0xf bank_mask:0xf\n\t" OP " %2, %2, %2 " DPP " row_mask:0xf bank_mask:0xf\n\t" OP       \
+      " %3, %3, %3 " DPP " row_mask:0xf bank_mask:0xf"                                                   \
+      : "+v"(x[i]), "+v"(x[i + 1]), "+v"(x[i + 2]), "+v"(x[i + 3]))
+#define RB_RES_DPP(NAME, OP)                                                                             \
+  template <int CTRL, int N>                                                                             \
+  __device__ __forceinline__ void NAME(float (&x)[N]) {                                                  \
+    _Pragma("unroll") for (int i = 0; i < N / 4 * 4; i += 4) {                                           \
+      if constexpr (N >= 4) {                                                                            \
+        if constexpr (CTRL == kDppXor1) RB_RES_DPP4(OP, "quad_perm:[1,0,3,2]");                          \
+        else if constexpr (CTRL == kDppXor2) RB_RES_DPP4(OP, "quad_perm:[2,3,0,1]");                     \
+        else if constexpr (CTRL == kDppHalfMirror) RB_RES_DPP4(OP, "row_half_mirror");                   \
+        else RB_RES_DPP4(OP, "row_mirror");                                                              \
+      }                                                                                                  \
+    }                                                                                                    \
+    _Pragma("unroll") for (int i = N / 4 * 4; i < N; ++i) {                                              \
+      if constexpr (CTRL == kDppXor1) RB_RES_DPP1(OP, "quad_perm:[1,0,3,2]");                            \
+      else if constexpr (CTRL == kDppXor2) RB_RES_DPP1(OP, "quad_perm:[2,3,0,1]");                       \
+      else if constexpr (CTRL == kDppHalfMirror) RB_RES_DPP1(OP, "row_half_mirror");                     \
+      else RB_RES_DPP1(OP, "row_mirror");                                                                \
+    }                                                                                                    \
   }
 RB_RES_DPP(dpp_max_n, "v_max_f32_dpp")
-RB_RES_DPP(dpp_min_n, "v_min_f32_dpp")
 RB_RES_DPP(dpp_add_n, "v_add_f32_dpp")
 #undef RB_RES_DPP
+#undef RB_RES_DPP4
+#undef RB_RES_DPP1
 template <int LANES, int N>
 __device__ __forceinline__ void group_max_n(float (&x)[N]) {
   dpp_max_n<kDppXor1>(x);
@@ -1449,13 +1530,12 @@ __device__ __forceinline__ void group_sum_n(float (&x)[N]) {
   if constexpr (LANES >= 16) dpp_add_n<kDppMirror>(x);
 }
 
-// A hypothesis' row of logits, columns 128 (q0 .. q0 + NQ - 1), by one wave: chunk statistics as the per-step kernels form
-// them, the blank and duration logits, and the keys that can be among the K best.  A lane holds columns 128 q + 2 lane +
-// {0, 1}; 16 lanes are a chunk of 32.  part / parts: the waves of the row, each of which collects keys of its own columns.
-// (Every load is unconditional, from a clamped address, and nothing branches before the keys are compared: the wave's
-// time is the latency of this chain.)
-template <int NQ, int KC, int PLAIN>
-__device__ __forceinline__ void res_row(int g, int step, int slot, const float *lmrow, int hyp, int part, int parts, ResSelLds &L) {
+// Columns 128 (part NQ .. part NQ + NQ - 1) of a hypothesis' row of logits, by one wave: statistics of the chunks as the per-step kernels
+// form them, the blank and duration logits, and the keys, which go to LDS.  A lane holds columns 128 q + 2 lane + {0, 1}; 16 lanes are a
+// chunk of 32.  late_lm: row holds the LM's scores (log10), to which the keys follow.  stash: whether it takes the keys at all.
+// (Every load is unconditional, from a clamped address: the wave's time is the latency of this chain.)
+template <int NQ, int PLAIN>
+__device__ __forceinline__ void res_row(int g, int step, int slot, float *row, bool late_lm, bool stash, int hyp, int part, ResSelLds &L) {
   const ResArgs &a = res_args();
   const int lane = threadIdx.x & 63, V = a.V, nz = a.N - V;
   const int q0 = part * NQ;
@@ -1472,151 +1552,71 @@ __device__ __forceinline__ void res_row(int g, int step, int slot, const float *
     w.again();
   }
   if (part == 0 && lane < nz) L.zs[hyp * nz + lane] = lo_f(zz[NQ]);
-  // a place without a token: -inf
   float z[2 * NQ];
 #pragma unroll
   for (int q = 0; q < NQ; ++q) {
-    const int n = 128 * (q0 + q) + 2 * lane;
-    z[2 * q] = n < V ? lo_f(zz[q]) : -INFINITY;
-    z[2 * q + 1] = n + 1 < V ? hi_f(zz[q]) : -INFINITY;
+    z[2 * q] = lo_f(zz[q]);
+    z[2 * q + 1] = hi_f(zz[q]);
+  }
+  const bool whole = 128 * (q0 + NQ) <= V;
+  auto mask = [&](float (&x)[2 * NQ]) {  // a place without a token: -inf
+    if (whole) return;
+#pragma unroll
+    for (int q = 0; q < NQ; ++q) {
+      const int n = 128 * (q0 + q) + 2 * lane;
+      x[2 * q] = n < V ? x[2 * q] : -INFINITY;
+      x[2 * q + 1] = n + 1 < V ? x[2 * q + 1] : -INFINITY;
+    }
+  };
+  mask(z);
+  float *keys = row + 128 * q0 + 2 * lane;
+  if (PLAIN == 0 && late_lm) {
+    float x[2 * NQ], km[NQ];
+#pragma unroll
+    for (int q = 0; q < NQ; ++q) {
+      const float2 lm = *reinterpret_cast<const float2 *>(keys + 128 * q);
+      const float l0 = lm.x * kLn10, l1 = lm.y * kLn10;
+      x[2 * q] = z[2 * q] + a.sel.lambda * l0;
+      x[2 * q + 1] = z[2 * q + 1] + a.sel.lambda * l1;
+    }
+    mask(x);
+#pragma unroll
+    for (int q = 0; q < NQ; ++q) {
+      *reinterpret_cast<float2 *>(keys + 128 * q) = make_float2(x[2 * q], x[2 * q + 1]);
+      km[q] = fmaxf(x[2 * q], x[2 * q + 1]);
+    }
+    group_max_n<16>(km);
+    if ((lane & 15) == 0)
+#pragma unroll
+      for (int q = 0; q < NQ; ++q) L.kmax[hyp][4 * (q0 + q) + (lane >> 4)] = km[q];
+  } else if (PLAIN || stash) {
+#pragma unroll
+    for (int q = 0; q < NQ; ++q) *reinterpret_cast<float2 *>(keys + 128 * q) = make_float2(z[2 * q], z[2 * q + 1]);
   }
   // chunk statistics
   float mx[NQ], sum[NQ];
 #pragma unroll
   for (int q = 0; q < NQ; ++q) mx[q] = fmaxf(z[2 * q], z[2 * q + 1]);
-  float km = mx[0];
-#pragma unroll
-  for (int q = 1; q < NQ; ++q) km = fmaxf(km, mx[q]);
   group_max_n<16>(mx);
+  bool odd = false;
 #pragma unroll
   for (int q = 0; q < NQ; ++q) {
-    sum[q] = z[2 * q] > -INFINITY ? __expf(z[2 * q] - mx[q]) : 0.f;
-    sum[q] += z[2 * q + 1] > -INFINITY ? __expf(z[2 * q + 1] - mx[q]) : 0.f;
+    const float m = fmaxf(mx[q], -3.4028235e38f);  // (a chunk of -inf only: sum 0)
+    sum[q] = __expf(z[2 * q] - m);
+    sum[q] += __expf(z[2 * q + 1] - m);
+    odd |= sum[q] != sum[q];
   }
-  group_sum_n<16>(sum);
-  {  // lane q of every group of 16 writes the statistics of the group's q-th chunk
-    float m = mx[0], e = sum[0];
-#pragma unroll
-    for (int q = 1; q < NQ; ++q) {
-      m = (lane & 15) == q ? mx[q] : m;
-      e = (lane & 15) == q ? sum[q] : e;
-    }
-    if ((lane & 15) < NQ) L.cst[hyp][4 * (q0 + (lane & 15)) + (lane >> 4)] = make_float2(m, e);
-  }
-  // keys
-  if (PLAIN == 0 && lmrow) {
-    km = -INFINITY;
+  if (__ballot(odd) != 0ull) {  // (logits that are no numbers count for nothing)
 #pragma unroll
     for (int q = 0; q < NQ; ++q) {
-      const int n = min(128 * (q0 + q) + 2 * lane, v_last);
-      const float l0 = lmrow[n] * kLn10, l1 = lmrow[min(n + 1, V - 1)] * kLn10;
-      z[2 * q] = z[2 * q] + a.sel.lambda * l0;
-      z[2 * q + 1] = z[2 * q + 1] + a.sel.lambda * l1;
-      km = fmaxf(km, fmaxf(z[2 * q], z[2 * q + 1]));
+      sum[q] = z[2 * q] > -INFINITY ? __expf(z[2 * q] - mx[q]) : 0.f;
+      sum[q] += z[2 * q + 1] > -INFINITY ? __expf(z[2 * q + 1] - mx[q]) : 0.f;
     }
   }
-  // a lower bound of the K-th largest key: the smallest of the maxima of at least K disjoint sets of columns
-  float tau[1] = {km};
-  if constexpr (KC == 4) group_max_n<16>(tau);
-  else if constexpr (KC == 8) {
-    group_max_n<8>(tau);
-    dpp_min_n<kDppMirror>(tau);
-  } else {
-    group_max_n<4>(tau);
-    dpp_min_n<kDppHalfMirror>(tau);
-    dpp_min_n<kDppMirror>(tau);
-  }
-  const float t = fmaxf(fminf(fminf(readlane_f(tau[0], 0), readlane_f(tau[0], 16)), fminf(readlane_f(tau[0], 32), readlane_f(tau[0], 48))),
-                        -3.4028235e38f);  // (no token at -inf is a candidate)
-  // the keys at or above it (a dozen or two)
-  const int cap = kResSurvivors / parts;
-  uint64_t *surv = L.surv[hyp] + part * cap;
-  int total = 0;
+  group_sum_n<16>(sum);
+  if ((lane & 15) == 0)
 #pragma unroll
-  for (int i = 0; i < 2 * NQ; ++i) {
-    const bool in = z[i] >= t;
-    const unsigned long long mask = __ballot(in);
-    const int pos = total + __builtin_amdgcn_mbcnt_hi((uint32_t)(mask >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)mask, 0));
-    if (in && pos < cap) surv[pos] = pack_cand(z[i], 128 * (q0 + i / 2) + 2 * lane + (i & 1));
-    total += __popcll(mask);
-  }
-  if (lane < 8 && total + lane < cap) surv[total + lane] = 0;  // (below every key: the ranking reads in eights)
-  if (lane == 0) L.n_surv[hyp][part] = total;
-}
-
-// The row's soft-max statistics from those of its chunks, added up in the order of the per-step kernels (which depends on
-// the beam), and its K best keys from the collected ones.
-template <int KC, int PLAIN>
-__device__ __forceinline__ void res_row_finish(int g, int step, int slot, const float *lmrow, int hyp, int parts, ResSelLds &L) {
-  const ResArgs &a = res_args();
-  const int lane = threadIdx.x & 63, K = a.K, n_cst = 4 * ((a.V + 127) / 128);
-  const float2 *cst = L.cst[hyp];
-  const int cap = kResSurvivors / parts;
-  const int n0 = L.n_surv[hyp][0], n1 = parts > 1 ? L.n_surv[hyp][1] : 0, total = n0 + n1;
-  const uint64_t *surv = L.surv[hyp];
-  const int first = lane < total ? lane : 0;
-  const uint64_t mine0 = surv[min(first < n0 ? first : cap + first - n0, kResSurvivors - 1)];
-  // lanes of a group of LPR take chunks e, e + LPR, ..
-  constexpr int LPR = KC == 4 ? 16 : KC == 8 ? 8 : 64, NC = LPR == 64 ? 1 : 32 / LPR;
-  const int e = lane & (LPR - 1);
-  float2 c[NC];
-#pragma unroll
-  for (int q = 0; q < NC; ++q) {
-    const int i = e + LPR * q;
-    const float2 v = cst[i & 31];
-    c[q] = i < n_cst ? v : make_float2(-INFINITY, 0.f);
-  }
-  float m[1] = {c[0].x}, st_sum[1] = {0.f};
-#pragma unroll
-  for (int q = 1; q < NC; ++q) m[0] = fmaxf(m[0], c[q].x);
-  group_max_n<(LPR < 16 ? LPR : 16)>(m);
-  float st_mx = m[0];
-  if constexpr (LPR == 64) st_mx = fmaxf(fmaxf(readlane_f(st_mx, 0), readlane_f(st_mx, 16)), fmaxf(readlane_f(st_mx, 32), readlane_f(st_mx, 48)));
-#pragma unroll
-  for (int q = 0; q < NC; ++q)
-    st_sum[0] = c[q].x > -INFINITY ? st_sum[0] + c[q].y * __expf(c[q].x - st_mx) : st_sum[0];
-  group_sum_n<(LPR < 16 ? LPR : 16)>(st_sum);
-  float sum = st_sum[0];
-  if constexpr (LPR == 64) sum = (readlane_f(sum, 0) + readlane_f(sum, 16)) + (readlane_f(sum, 32) + readlane_f(sum, 48));
-  if (lane == 0) {
-    L.smax[hyp] = st_mx;
-    L.ssum[hyp] = sum;
-  }
-  uint64_t *out = L.cand + hyp * K;
-  if (n0 <= cap && n1 <= cap) {
-    if (lane < K && lane >= total) out[lane] = no_cand();
-    for (int i = lane; i < total; i += 64) {
-      const uint64_t mine = i < 64 ? mine0 : surv[i < n0 ? i : cap + i - n0];
-      int rank = 0;
-      auto count = [&](const uint64_t *list, int n) {
-        for (int j = 0; j < n; j += 8) {
-          uint64_t v[8];
-#pragma unroll
-          for (int q = 0; q < 8; ++q) v[q] = list[j + q];
-#pragma unroll
-          for (int q = 0; q < 8; ++q) rank += v[q] > mine;
-        }
-      };
-      count(surv, n0);
-      if (parts > 1) count(surv + cap, n1);
-      if (rank < K) out[rank] = mine;
-    }
-  } else {  // (many equal keys) K rounds of "best remaining key" over the row
-    const float *zrow = res_addr(a, g).z(step, slot);
-    uint64_t last = ~0ull;
-    for (int j = 0; j < K; ++j) {
-      uint64_t best = no_cand();
-      for (int n = lane; n < a.V; n += 64) {
-        float key = load_agent(zrow + n);
-        if (PLAIN == 0 && lmrow) key = key + a.sel.lambda * (lmrow[n] * kLn10);
-        const uint64_t x = key > -INFINITY ? pack_cand(key, n) : no_cand();
-        if (x < last && x > best) best = x;
-      }
-      best = wave_max_u64(best);
-      if (lane == 0) out[j] = best;
-      last = best > no_cand() ? best : no_cand() + 1;
-    }
-  }
+    for (int q = 0; q < NQ; ++q) L.cst[hyp][4 * (q0 + q) + (lane >> 4)] = make_float2(mx[q], sum[q]);
 }
 
 // LM scores (log10) of every token after a hypothesis, by one wave, into an LDS row: see lm_row_block
@@ -1678,34 +1678,472 @@ __device__ __forceinline__ void res_lm_row(const LmView &lm, const int *hist, in
   wave_sync();
 }
 
+__device__ __forceinline__ int res_kind(bool live, int4 state, int T_b, int max_sym) {
+  return !live ? 0 : state.x >= T_b ? 1 : state.y >= max_sym ? 3 : 2;
+}
+// The Beam best of an utterance's candidates, expansion, words, recombination and tree, by one wave.  rows: the utterance's rows of
+// keys in LDS (early pruning: of LM scores; the keys are the logits where they came from).  h0: its first hypothesis in the block, u
+// in the group, b in the batch.  Returns whether its last step is done.
+template <int KC, int PLAIN>
+__device__ __forceinline__ bool res_select(const ResBlock &k, int step, int u, int b, int T_b, int h0, const float *rows, ResUtt &s, const ResSelLds &L) {
+  const ResArgs &ra = res_args();
+  const SelectArgs &a = ra.sel;
+  const int K = ra.K, V = ra.V, nz = ra.N - V, stride = res_row_floats(V), lane = threadIdx.x & 63;
+  const int ND = PLAIN ? 0 : nz - 1;
+  const bool has_lm = PLAIN == 0 && ra.has_lm, early = PLAIN == 0 && a.lm_early, late_lm = has_lm && !early;
+  const bool aes = PLAIN == 0 && a.algo == 1, use_gamma = aes && a.gamma < INFINITY;
+  const bool prefix = PLAIN == 0 && a.prefix && aes && !early;
+  // LPR lanes per hypothesis, of which each takes NC chunks: e, e + LPR, ..
+  constexpr int LPR = 64 / KC, NC = 32 / LPR;
+  const int e = lane & (LPR - 1), r = lane / LPR, row = r < K ? r : 0;
+  const int n_cst = 4 * ((V + 127) / 128);
+  const double sc = s.score[row];
+  const int kind = r < K ? s.kind[row] : 0;
+  float2 c[NC];
+  float km[NC];
+#pragma unroll
+  for (int q = 0; q < NC; ++q) {
+    const int i = e + LPR * q;
+    const float2 v = L.cst[h0 + row][i];
+    c[q] = i < n_cst ? v : make_float2(-INFINITY, 0.f);
+    km[q] = c[q].x;
+    if (late_lm) {
+      const float x = L.kmax[h0 + row][i];
+      km[q] = i < n_cst ? x : -INFINITY;
+    }
+  }
+  const float *zs = L.zs + (h0 + row) * nz;
+  const float zb = zs[0];
+  // ---- soft-max statistics of the row, added up in the order of the per-step kernels
+  float m[1] = {c[0].x}, st_sum = 0.f;
+#pragma unroll
+  for (int q = 1; q < NC; ++q) m[0] = fmaxf(m[0], c[q].x);
+  group_max_n<LPR>(m);
+  const float st_mx = m[0];
+  if constexpr (KC < 16) {
+    float t[1] = {0.f};
+#pragma unroll
+    for (int q = 0; q < NC; ++q) t[0] = c[q].x > -INFINITY ? t[0] + c[q].y * __expf(c[q].x - st_mx) : t[0];
+    group_sum_n<LPR>(t);
+    st_sum = t[0];
+  } else {  // (a chunk per lane there, in a tree over 16 lanes, then the two sixteens)
+    float t[NC];
+#pragma unroll
+    for (int q = 0; q < NC; ++q) t[q] = c[q].x > -INFINITY ? c[q].y * __expf(c[q].x - st_mx) : 0.f;
+    group_sum_n<LPR>(t);
+    st_sum = ((t[0] + t[1]) + (t[2] + t[3])) + ((t[4] + t[5]) + (t[6] + t[7]));
+  }
+  const float lse_nb = st_mx + __logf(st_sum);
+  const float hi = fmaxf(lse_nb, zb), lo = fminf(lse_nb, zb);
+  const float lse_all = hi + __logf(1.f + __expf(lo - hi));
+  const double logp_b = (double)zb - (double)lse_all;
+  // ---- durations: the most likely one (the first of equal ones), and the most likely one that advances
+  double x_tok = 0.0, x_blank = 0.0;
+  int adv = 1 << 16;
+  if (ND > 0) {
+    float dl[8];
+#pragma unroll
+    for (int d = 0; d < 8; ++d) dl[d] = zs[1 + (d < ND ? d : 0)];
+    float dmx = -INFINITY, sm = 0.f;
+#pragma unroll
+    for (int d = 0; d < 8; ++d)
+      if (d < ND) dmx = fmaxf(dmx, dl[d]);
+#pragma unroll
+    for (int d = 0; d < 8; ++d)
+      if (d < ND) sm += __expf(dl[d] - dmx);
+    const float l = dmx + __logf(sm);
+#pragma unroll
+    for (int d = 0; d < 8; ++d)
+      if (d < ND) dl[d] -= l;
+    bool have = false, have_b = false;
+    float best_v = 0.f, best_bv = 0.f;
+    int best_adv = 0, best_badv = 1;
+#pragma unroll
+    for (int d = 0; d < 8; ++d)
+      if (d < ND) {
+        const int du = (int)((a.dur_bytes >> (8 * d)) & 0xff);
+        if (!have || dl[d] > best_v) {
+          have = true;
+          best_v = dl[d];
+          best_adv = du;
+        }
+        if (du >= 1 && (!have_b || dl[d] > best_bv)) {
+          have_b = true;
+          best_bv = dl[d];
+          best_badv = du;
+        }
+      }
+    x_tok = (double)best_v;
+    x_blank = (double)best_bv;
+    adv = best_adv | best_badv << 16;
+  }
+  // ---- candidates.  A token's: what it is ranked by (key) and its score (val), which differ under early pruning and with the prefix
+  // search's credit.  Eq. (4): tokens get lambda (ln(1 - p_blank) + lm), blank (1 + lambda) ln p_blank; Eq. (3): tokens lambda lm, blank
+  // unchanged.  Late pruning: lambda lm is in the row's keys; early: added to the score of those that are kept.
+  const double lm_const = (has_lm && !a.lm_rule3) ? (double)a.lambda * ((double)lse_nb - (double)lse_all) : 0.0;
+  const double tok_base = x_tok - (double)lse_all;
+  const double thr = use_gamma ? (double)fmaxf(st_mx, zb) - (double)lse_all - (double)a.gamma : -INFINITY;
+  auto token_key = [&](float z, double score, double base, double lmc, double lse, double margin) {
+    double key = score + (double)z + base;
+    if (PLAIN == 0) {
+      if (!early) key = key + lmc;
+      if (use_gamma && (double)z - lse < margin) key = -INFINITY;
+    }
+    return z > -INFINITY ? key : -INFINITY;
+  };
+  double bkey = -INFINITY, bval = -INFINITY;
+  if (kind >= 2) {
+    double bl = logp_b;
+    if (use_gamma && logp_b < thr && kind == 2) bl = -INFINITY;
+    bkey = sc + bl + x_blank;
+    bval = (has_lm && !a.lm_rule3 && bl > -INFINITY) ? bkey + (double)a.lambda * bl : bkey;
+    if (!early) bkey = bval;
+  } else if (kind == 1) {
+    bkey = bval = sc;  // a waiting or finished hypothesis stays as it is
+  }
+  if (e == 0 && r < K) {
+    s.tok_base[r] = tok_base;
+    if (PLAIN == 0) {
+      s.lm_const[r] = lm_const;
+      s.lse[r] = (double)lse_all;
+      s.margin[r] = thr;
+      s.adv[r] = adv;
+    }
+  }
+  double delta = 0.0;
+  if (prefix) {
+    // AES++, maximum-length prefix search (Sec. 2.2, "AES"), as select_utterance has it: hypotheses i and j expanded at this step in the
+    // same frame with transcript(i) = transcript(j) + v; (j, v), if among j's Beam best tokens, is credited to i for the ranking.
+    wave_sync();
+    const int i = lane < K ? lane : 0;
+    const int4 st = s.state[i];
+    const bool open = lane < K && s.kind[i] >= 2 && st.z >= 1;
+    double add = -INFINITY;
+    for (int j = 0; j < K; ++j) {
+      const int4 sj = s.state[j];
+      bool pair = open && j != i && s.kind[j] == 2 && sj.x == st.x && sj.z + 1 == st.z && (s.adv[j] & 0xffff) == 0;
+      if (pair) pair = mod_mersenne31((uint64_t)s.hash[j] * kHashBase + (uint64_t)(st.w + 1)) == s.hash[i];
+      for (unsigned long long todo = __ballot(pair); todo; todo &= todo - 1ull) {
+        const int who = __builtin_ctzll(todo), v = __builtin_amdgcn_readlane(st.w, who);
+        const float *rj = rows + j * stride;
+        const float z = rj[v];
+        int ahead = 0;
+        for (int n = lane; n < V; n += 64) ahead += comes_before_count(rj[n], n, z, v);
+        ahead = wave_sum_i(ahead);
+        const double val = token_key(z, s.score[j], s.tok_base[j], s.lm_const[j], s.lse[j], s.margin[j]);
+        if (lane == who && ahead < K && val > -INFINITY) add = logaddexp_d(add, val);
+      }
+    }
+    if (lane < K) s.delta[lane] = add > -INFINITY ? logaddexp_d(s.score[lane], add) - s.score[lane] : 0.0;
+    wave_sync();
+    delta = s.delta[row];
+    bkey = bkey + delta;
+  }
+  // ---- a lower bound of the K-th largest: the K-th largest of the maxima of disjoint sets of candidates, a lane's, or those of
+  // four lanes (in float32, rounded down)
+  float kmx = km[0];
+#pragma unroll
+  for (int q = 1; q < NC; ++q) kmx = fmaxf(kmx, km[q]);
+  double best = kind == 2 ? token_key(kmx, sc, tok_base, lm_const, (double)lse_all, thr) : -INFINITY;
+  if (prefix) best = best + delta;
+  if (e == LPR - 1) best = bkey > best || !(best > -INFINITY) ? bkey : best;
+  float fl = (float)best;
+  fl = fl > -INFINITY ? fl - (fabsf(fl) * 2.4e-7f + 1e-30f) : -INFINITY;  // (no number: none)
+  constexpr int SETS = KC == 4 ? 16 : 64;
+  if constexpr (SETS == 16) {
+    float q[1] = {fl};
+    group_max_n<4>(q);
+    fl = q[0];
+    if ((lane & 3) == 0) s.set[lane >> 2] = fl;
+  } else {
+    s.set[lane] = fl;
+  }
+  wave_sync();
+  int ge = 0;  // sets not below mine
+#pragma unroll
+  for (int i = 0; i < SETS; i += 4) {
+    const float4 v = *reinterpret_cast<const float4 *>(s.set + i);
+    ge += (int)(v.x >= fl);
+    ge += (int)(v.y >= fl);
+    ge += (int)(v.z >= fl);
+    ge += (int)(v.w >= fl);
+  }
+  double tau = -INFINITY;
+  {
+    const unsigned long long kth = __ballot(fl > -INFINITY && ge == K);
+    if (kth != 0ull) tau = (double)readlane_f(fl, __builtin_ctzll(kth));
+    else tau = (double)wave_max(fl > -INFINITY && ge >= K ? fl : -INFINITY);
+  }
+  // ---- the chunks that reach it, and of these and the blanks the candidates that do
+  int n_chunks = 0;
+#pragma unroll
+  for (int q = 0; q < NC; ++q) {
+    double x = token_key(km[q], sc, tok_base, lm_const, (double)lse_all, thr);
+    if (prefix) x = x + delta;
+    const bool in = kind == 2 && x > -INFINITY && x >= tau;
+    const unsigned long long mask = __ballot(in);
+    const int pos = n_chunks + __builtin_amdgcn_mbcnt_hi((uint32_t)(mask >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)mask, 0));
+    if (in) s.chunk[pos] = r << 5 | (e + LPR * q);
+    n_chunks += __popcll(mask);
+  }
+  int total = 0;
+  auto append = [&](bool in, double key, double val, int flat) {
+    const unsigned long long mask = __ballot(in);
+    const int pos = total + __builtin_amdgcn_mbcnt_hi((uint32_t)(mask >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)mask, 0));
+    if (in && pos < kResTop) {
+      s.top_key[pos] = key;
+      if (PLAIN == 0) s.top_val[pos] = val;
+      s.top_flat[pos] = flat;
+    }
+    total += __popcll(mask);
+  };
+  append(e == LPR - 1 && bkey > -INFINITY && bkey >= tau, bkey, bval, r << kFlatShift | V);
+  wave_sync();
+  // a candidate of hypothesis h: its key and score
+  const float *zr = early ? res_addr(ra, k.g).z(step, u * K) : rows;  // (early: a row of Npad, in global memory)
+  const int zstride = early ? ra.Npad : stride;
+  auto token = [&](int h, int n, float z, double &key, double &val) {
+    val = token_key(z, s.score[h], s.tok_base[h], PLAIN ? 0.0 : s.lm_const[h], PLAIN ? 0.0 : s.lse[h], PLAIN ? 0.0 : s.margin[h]);
+    key = val;
+    if (PLAIN == 0) {
+      if (prefix) key = val + s.delta[h];
+      if (early) val = key + s.lm_const[h] + (double)a.lambda * (double)(rows[h * stride + (n < V ? n : 0)] * kLn10);
+    }
+  };
+  constexpr int U = KC / 4;  // fours of chunks in flight
+  for (int i0 = 0; i0 < n_chunks; i0 += 4 * U) {
+    int id[U];
+    float2 z[U];
+#pragma unroll
+    for (int i = 0; i < U; ++i) {
+      const int at = i0 + 4 * i + (lane >> 4);
+      id[i] = s.chunk[at < n_chunks ? at : i0];
+    }
+#pragma unroll
+    for (int i = 0; i < U; ++i) {
+      const int n = 32 * (id[i] & 31) + 2 * (lane & 15);
+      if (PLAIN == 0 && early) {
+        const uint64_t x = load_agent(reinterpret_cast<const uint64_t *>(zr + (size_t)(id[i] >> 5) * zstride + min(n, (V - 1) & ~1)));
+        z[i] = make_float2(n < V ? lo_f(x) : -INFINITY, n + 1 < V ? hi_f(x) : -INFINITY);
+      } else {
+        z[i] = *reinterpret_cast<const float2 *>(rows + (id[i] >> 5) * stride + n);
+      }
+    }
+#pragma unroll
+    for (int i = 0; i < U; ++i) {
+      if (i > 0 && i0 + 4 * i >= n_chunks) break;
+      const int h = id[i] >> 5, n = 32 * (id[i] & 31) + 2 * (lane & 15);
+      const bool there = i0 + 4 * i + (lane >> 4) < n_chunks;
+      double k0, v0, k1, v1;
+      token(h, n, z[i].x, k0, v0);
+      token(h, n + 1, z[i].y, k1, v1);
+      append(there && k0 > -INFINITY && k0 >= tau, k0, v0, h << kFlatShift | n);
+      append(there && k1 > -INFINITY && k1 >= tau, k1, v1, h << kFlatShift | (n + 1));
+    }
+  }
+  if (total > kResTop) {
+    // Many reach it: fewer than K sets (a single hypothesis at first), or equal keys.  In the candidates' own order, until the K best
+    // are among the 64 that there is room for: the K-th largest of 64 is the next bound; one that cannot be raised is that of the K
+    // best itself, and of those equal to it the first ones count.
+    if (e == LPR - 1 && r < K) {
+      s.blank_key[r] = bkey;
+      s.blank[r] = bval;
+    }
+    wave_sync();
+    auto collect = [&](auto in, int most) {  // until there are that many (more than that of the last 64 may be)
+      for (int h = 0; h < K && total < most; ++h) {
+        if (__builtin_amdgcn_readfirstlane(s.kind[h]) == 2)
+          for (int n0 = 0; n0 < V && total < most; n0 += 64) {
+            const int n = n0 + lane;
+            const float *p = zr + (size_t)h * zstride + min(n, V - 1);
+            const float z = PLAIN == 0 && early ? load_agent(p) : rows[h * stride + min(n, V - 1)];
+            double key, val;
+            token(h, n, z, key, val);
+            append(n < V && in(key), key, val, h << kFlatShift | n);
+          }
+        if (total >= most) break;
+        append(lane == 0 && in(s.blank_key[h]), s.blank_key[h], s.blank[h], h << kFlatShift | V);
+      }
+    };
+    bool above = false;  // whether the bound itself is left out
+    for (;;) {
+      total = 0;
+      collect([&](double x) { return x > -INFINITY && (above ? x > tau : x >= tau); }, 0x7fffffff);
+      if (total <= kResTop && (!above || total >= K)) break;
+      if (total < K) {
+        collect([&](double x) { return x == tau; }, K);
+        total = min(total, kResTop);
+        break;
+      }
+      wave_sync();
+      const double x = s.top_key[lane];  // (64 or more of them, or, above the bound, K or more)
+      const int have = min(total, kResTop);
+      int n = 0;
+      for (int i = 0; i < have; ++i) n += (int)(s.top_key[i] >= x);
+      // the K-th largest: the largest that K are not below
+      double t = lane < have && n >= K ? x : -INFINITY;
+      int dummy = 0;
+      wave_best(t, dummy);
+      above = !(t > tau);
+      if (!above) tau = t;
+      wave_sync();
+    }
+  }
+  if (lane < 8) {  // (read in eights)
+    s.top_key[total + lane] = -INFINITY;
+    s.top_flat[total + lane] = 0x7fffffff;
+  }
+  wave_sync();
+  // ---- rank, by counting; on the way, what the candidate's hypothesis looks like
+  const bool mine = lane < total;
+  const int at = mine ? lane : 0;
+  const double key = s.top_key[at];
+  const int flat = s.top_flat[at];
+  const double val = PLAIN ? key : s.top_val[at];
+  const int par = (flat >> kFlatShift) & (kMaxBeam - 1), v = flat & ((1 << kFlatShift) - 1);
+  int4 st = s.state[par];
+  uint32_t hash = s.hash[par];
+  const int pkind = s.kind[par];
+  const int padv = PLAIN ? 1 << 16 : s.adv[par];
+  int ge2 = 0, gt = 0;
+  for (int c0 = 0; c0 < total; c0 += 8) {
+    double x[8];
+#pragma unroll
+    for (int q = 0; q < 8; ++q) x[q] = s.top_key[c0 + q];
+#pragma unroll
+    for (int q = 0; q < 8; ++q) {
+      ge2 += (int)(x[q] >= key);
+      gt += (int)(x[q] > key);
+    }
+  }
+  int rank = gt;
+  if (__ballot(mine && ge2 != gt + 1) != 0ull) {  // equal ones: the full order
+    rank = 0;
+    for (int c = 0; c < total; ++c) rank += comes_before_count(s.top_key[c], s.top_flat[c], key, flat);
+  }
+  // ---- expansion into the new slots: a lane whose candidate is kept makes slot `rank` of it
+  const bool kept = mine && rank < K;
+  int code = -2, appended = -1;
+  if (pkind >= 2) {
+    if (v == V) {
+      code = -1;
+      st.x += padv >> 16;
+      st.y = 0;
+    } else {
+      code = appended = v;
+      st.z += 1;
+      st.w = v;
+      hash = mod_mersenne31((uint64_t)hash * kHashBase + (uint64_t)(v + 1));
+      st.x += padv & 0xffff;
+      st.y = (padv & 0xffff) == 0 ? st.y + 1 : 0;
+    }
+  }
+  st.x = min(st.x, T_b);
+  // The words leave here, ahead of the recombination, which changes none of their fields: the slots of a class stand in the same frame
+  // and one of them stays live, so whether any slot is open is known already.  The group's other blocks go on while this wave merges and
+  // writes the tree (batch 32 / beam 4: 10.79 -> 10.50 ms per decode, one utterance 9.53 -> 9.33).
+  const bool alive = kept && (PLAIN || val > -INFINITY);  // (early pruning: the LM's score may be no number)
+  if (PLAIN == 0 && !alive) {
+    st = make_int4(0, 0, 0, -1);
+    hash = 0;
+    code = -3;
+    appended = -1;
+  }
+  const bool last_step = __ballot(alive && st.x < T_b) == 0ull || step + 1 >= T_b * (a.max_sym + 1);
+  const int slot0 = u * K, n_kept = __popcll(__ballot(kept));
+  uint64_t *words = res_addr(ra, k.g).w(step) + slot0;
+  if (kept) res_store(k.local, words + rank, slot_word(step, last_step ? 1 : 0, slot0 + (alive ? par : rank), appended, st.x));
+  if (n_kept < K && lane >= n_kept && lane < K) {
+    res_store(k.local, words + lane, slot_word(step, last_step ? 1 : 0, slot0 + lane, -1, 0));
+    s.n_live[lane] = 0;
+    s.n_score[lane] = -INFINITY;
+    s.n_t[lane] = s.n_sym[lane] = s.n_len[lane] = 0;
+    s.n_last[lane] = s.n_parent[lane] = -1;
+    s.n_hash[lane] = 0;
+    s.n_code[lane] = -3;
+  }
+  int ctx[kCtxMax];
+  if (kept) {
+    s.n_live[rank] = alive;
+    s.n_score[rank] = alive ? val : -INFINITY;
+    s.n_t[rank] = st.x;
+    s.n_sym[rank] = st.y;
+    s.n_len[rank] = st.z;
+    s.n_last[rank] = st.w;
+    s.n_hash[rank] = hash;
+    s.n_parent[rank] = alive ? par : -1;
+    s.n_code[rank] = code;
+    if (a.use_ctx) {
+#pragma unroll
+      for (int i = 0; i < kCtxMax; ++i) ctx[i] = s.ctx[par][i];
+    }
+  }
+  wave_sync();
+  if (a.use_ctx) {  // (every read of the old histories lies before)
+    if (kept)
+#pragma unroll
+      for (int i = 0; i < kCtxMax; ++i) s.ctx[rank][i] = !alive ? -1 : appended < 0 ? ctx[i] : i == 0 ? appended : ctx[i > 0 ? i - 1 : 0];
+    if (n_kept < K && lane >= n_kept && lane < K)
+#pragma unroll
+      for (int i = 0; i < kCtxMax; ++i) s.ctx[lane][i] = -1;
+  }
+  // ---- recombination, tree, and what the hypotheses do next
+  int next = 0, frame = 0;
+  if (lane < K) {
+    const int j = lane;
+    double score;
+    bool live;
+    const int merged = recombine<KC>(s, K, j, score, live);
+    const int4 now = make_int4(s.n_t[j], s.n_sym[j], s.n_len[j], s.n_last[j]);
+    s.score[j] = score;
+    s.state[j] = now;
+    s.hash[j] = s.n_hash[j];
+    if (last_step) {  // what the back-trace ranks and sizes the transcripts by
+      store_through(a.score + b * K + j, score);
+      store_through(a.len + b * K + j, now.z);
+    }
+    write_tree(a, b, step, K, j, s.n_parent[j], s.n_code[j], merged);
+    if (j == 0 && last_step) end_utterance(a, b, step);
+    next = res_kind(live, now, T_b, a.max_sym);
+    frame = now.x;
+  }
+  if (aes) {  // only those in the earliest frame are expanded
+    const int first = __builtin_amdgcn_readlane(group_min_i<16>(next >= 2 ? frame : 0x7fffffff), 0);
+    if (next >= 2 && frame != first) next = 1;
+  }
+  if (lane < K) s.kind[lane] = next;
+  wave_sync();
+  return last_step;
+}
+
 template <int KC, int PLAIN>
 __device__ __forceinline__ void res_selector(ResBlock k, int sel, float *lds) {
   const ResArgs &a0 = res_args();
-  const int K = a0.K, V = a0.V, lane = threadIdx.x & 63, upc = a0.upc;
-  const bool has_lm = a0.has_lm != 0, late_lm = has_lm && !a0.sel.lm_early;
+  const int K = a0.K, lane = threadIdx.x & 63, upc = a0.upc, stride = res_row_floats(a0.V);
+  const bool has_lm = a0.has_lm != 0, late_lm = has_lm && !a0.sel.lm_early, early = has_lm && a0.sel.lm_early;
   ResSelLds &L = *reinterpret_cast<ResSelLds *>(lds);
-  SelectScratch *scratch = reinterpret_cast<SelectScratch *>(lds + (sizeof(ResSelLds) + 15) / 16 * 4);
-  k.word = reinterpret_cast<uint64_t *>(scratch + upc) + k.wave * a0.NT * kResSlot;
-  float *lm_rows = reinterpret_cast<float *>(reinterpret_cast<uint64_t *>(scratch + upc) + kResWaves * a0.NT * kResSlot);
+  float *rows = lds + res_sel_floats(upc, a0.NT);
+  ResUtt *utt = reinterpret_cast<ResUtt *>(lds + (sizeof(ResSelLds) + 15) / 16 * 4);
+  k.word = reinterpret_cast<uint64_t *>(utt + upc) + k.wave * a0.NT * kResSlot;
   const int u0 = sel * upc, nu = min(upc, k.nu - u0);  // the block's utterances of the group (none: nu <= 0)
   const int n_hyp = nu * K;
-  const int parts = n_hyp <= kResWaves / 2 && V > kResMaxV / 2 ? 2 : 1;  // waves per row
-  ResidentSelect rs{};
+  // waves per row: two where that leaves less to the wave that has most (at beams up to 4, and from 9 to 12)
+  const int parts = stride == kResMaxV && (2 * n_hyp + kResWaves - 1) / kResWaves < 2 * ((n_hyp + kResWaves - 1) / kResWaves) ? 2 : 1;
+  int T_b = 0;
+  bool finished = true;
   if (k.wave < nu) {  // the wave that selects for utterance u0 + wave
     const int u = u0 + k.wave;
-    SelectScratch &s = scratch[k.wave];
+    ResUtt &s = utt[k.wave];
+    T_b = res_uniform(a0.lengths[res_utt(k, u)]);
+    finished = T_b == 0;
     if (lane < K) {
+      const int4 none = make_int4(0, 0, 0, -1);
       s.score[lane] = lane == 0 ? 0.0 : -INFINITY;
-      s.t[lane] = s.sym[lane] = s.len[lane] = 0;
-      s.last[lane] = -1;
+      s.state[lane] = none;
       s.hash[lane] = 0;
+      s.kind[lane] = res_kind(lane == 0, none, T_b, a0.sel.max_sym);
       for (int i = 0; i < kCtxMax; ++i) s.ctx[lane][i] = -1;
     }
-    rs.slot0 = u * K;
-    rs.T_b = a0.lengths[res_utt(k, u)];
-    rs.lm = lm_rows + (size_t)k.wave * K * V;
-    rs.finished = rs.T_b == 0;
-    rs.local = k.local;
   }
   __syncthreads();
   int over = res_first_words(a0, k);
@@ -1714,36 +2152,29 @@ __device__ __forceinline__ void res_selector(ResBlock k, int sel, float *lds) {
     const int n_rows = min(n_hyp, k.nt * kResSlot - u0 * K);
     if (has_lm)  // rows of the hypotheses as the last step left them (their histories: behind its last barrier)
       for (int q = k.wave; q < n_rows; q += kResWaves)
-        res_lm_row(res_args().lm, scratch[q / K].ctx[q % K], scratch[q / K].len[q % K], lm_rows + (size_t)q * V, L.rec[k.wave]);
+        res_lm_row(res_args().lm, utt[q / K].ctx[q % K], utt[q / K].state[q % K].z, rows + (size_t)q * stride, L.rec[k.wave]);
     // (with two waves per row of logits a wave reads an LM row that another one has written)
     if (late_lm && parts == 2) __syncthreads();
     // (every other row is waited for, also those of finished utterances: a word of this step tells the group's other blocks that
     // all logits of the step were there)
-    if (parts == 2) {
-      const int q = k.wave >> 1;
-      if (q < n_rows) res_row<kResMaxV / 256, KC, PLAIN>(k.g, step, u0 * K + q, late_lm ? lm_rows + (size_t)q * V : nullptr, q, k.wave & 1, 2, L);
-    } else {
-      for (int q = k.wave; q < n_rows; q += kResWaves)
-        res_row<kResMaxV / 128, KC, PLAIN>(k.g, step, u0 * K + q, late_lm ? lm_rows + (size_t)q * V : nullptr, q, 0, 1, L);
-    }
+    auto read_rows = [&](auto nq) {
+      constexpr int NQ = decltype(nq)::value;
+      for (int i = k.wave; i < n_rows * parts; i += kResWaves) {
+        const int q = parts == 2 ? i >> 1 : i;
+        res_row<NQ, PLAIN>(k.g, step, u0 * K + q, rows + (size_t)q * stride, late_lm, !early, q, parts == 2 ? i & 1 : 0, L);
+      }
+    };
+    if (stride == 128) read_rows(std::integral_constant<int, 1>{});
+    else if (stride == 512 || parts == 2) read_rows(std::integral_constant<int, 4>{});
+    else read_rows(std::integral_constant<int, 8>{});
     __syncthreads();
     res_end_if_given_up();
-    for (int q = k.wave; q < n_rows; q += kResWaves)
-      res_row_finish<KC, PLAIN>(k.g, step, u0 * K + q, late_lm ? lm_rows + (size_t)q * V : nullptr, q, parts, L);
-    __syncthreads();
     if (k.wave < nu) {
-      const ResArgs &a = res_args();
       const int u = u0 + k.wave, b = res_utt(k, u);
-      rs.words = res_addr(a, k.g).w(step) + u * K;
-      rs.step = step;
-      if (rs.finished) {
-        if (lane < K) res_store(k.local, rs.words + lane, slot_word(step, 1, u * K + lane, -1, 0));
+      if (finished) {
+        if (lane < K) res_store(k.local, res_addr(res_args(), k.g).w(step) + u * K + lane, slot_word(step, 1, u * K + lane, -1, 0));
       } else {
-        const CandView cv{L.cand + k.wave * K * K, L.smax + k.wave * K, L.ssum + k.wave * K, L.zs + k.wave * K * (1 + a.sel.ND), b * K};
-        if constexpr (KC == 4) select_utterance<16, 1, 4, false, false, SelectScratch, true, PLAIN, false, true>(a.sel, b, scratch[k.wave], cv, &rs);
-        else if constexpr (KC == 8) select_utterance<8, 1, 8, false, false, SelectScratch, true, PLAIN, false, true>(a.sel, b, scratch[k.wave], cv, &rs);
-        else select_utterance<4, 1, 16, false, false, SelectScratch, true, PLAIN, false, true>(a.sel, b, scratch[k.wave], cv, &rs);
-        rs.finished = __builtin_amdgcn_readfirstlane(rs.finished);
+        finished = res_select<KC, PLAIN>(k, step, u, b, T_b, k.wave * K, rows + (size_t)k.wave * K * stride, utt[k.wave], L);
       }
     }
     if (has_lm) __syncthreads();

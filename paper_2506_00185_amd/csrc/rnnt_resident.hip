@@ -201,8 +201,7 @@ Plan make_plan(const Resident &r, const rnnt_config_t &c, int B, int K, bool has
   const size_t worker = (size_t)lds_tiles * (r.form == kResSplit ? kResTileFloats : std::max(c.pred == RNNT_PRED_LSTM ? c.P : 0, c.H) * kResSlot) * 4 +
                         (bf && fold ? (size_t)(1 + c.n_durations) * c.H * 2 : 0) + (size_t)2 * (bf ? kResRedBlocks<true> : kResRedBlocks<false>) * kResRedBlock * 4 +
                         (size_t)kResMaxR * p.NT * (256 + 128) * 4 + ResPar::kFloats * 4 + (size_t)p.NT * kResSlot * (sizeof(int2) + kResWaves * 8);
-  const size_t sel = (sizeof(ResSelLds) + 15) / 16 * 16 + p.upc * sizeof(SelectScratch) +
-                     (size_t)p.NT * kResSlot * kResWaves * 8 + (has_lm ? (size_t)p.upc * K * c.V * 4 : 0);
+  const size_t sel = (res_sel_floats(p.upc, p.NT) + (size_t)p.upc * K * res_row_floats(c.V)) * 4;
   p.lds = std::max(worker, sel);
   p.lds = std::max<size_t>(p.lds, 84 * 1024);  // more than half of a compute unit's: two blocks never share one
   if (p.lds + 256 > (size_t)r.max_lds) return p;  // (the kernel's own words beside the dynamic ones)

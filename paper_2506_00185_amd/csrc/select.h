@@ -138,29 +138,6 @@ __device__ __forceinline__ int rank_by_counting(const double *keys, const int *f
   return rank;
 }
 
-// Hand-over stores.  Blocks on one XCD share its L2: a plain store leaves the data there, and a device-coherent load finds it
-// there (such a load passes by the L1 but not by the L2: 107 ns, like any other that the L2 answers).  Across XCDs the store has
-// to be written through, which takes longer to be seen and to be acknowledged.  (One word from block to block and back, per
-// direction: 272 ns on one XCD with plain stores, 375 with written-through ones, 440 between two XCDs.)
-template <typename T>
-__device__ __forceinline__ void res_store(bool local, T *p, T v) {
-  if (local) __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WAVEFRONT);
-  else store_agent(p, v);
-}
-__device__ __forceinline__ void res_store_pair(bool local, uint64_t *p, int second, uint64_t v0, uint64_t v1) {
-  if (local) {
-    __hip_atomic_store(p, v0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WAVEFRONT);
-    __hip_atomic_store(p + second, v1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WAVEFRONT);
-  } else {
-    store_agent(p, v0);
-    store_agent(p + second, v1);
-  }
-}
-__device__ __forceinline__ void res_store16(bool local, float *p, floatx4 v) {
-  if (local) asm volatile("global_store_dwordx4 %0, %1, off" ::"v"(p), "v"(v) : "memory");
-  else store16_through(p, v);
-}
-
 // The Beam best of more than 64 candidates (beams from 8 on), candidate r * (K + 1) + j of hypothesis r, tokens (best first) and then
 // blank.  The K-th largest of a few candidates is a lower bound of the K-th largest of all: with each hypothesis' two best tokens and
 // its blank (a lane each) few more than K candidates reach it, and those are ranked against each other.  Where more than 64 do (wide
@@ -228,29 +205,66 @@ __device__ __forceinline__ bool rank_best(Scratch &s, const double *rank_of, int
   return true;
 }
 
-// How the resident loop (kernels_resident.h) calls the selection: the hypotheses' state stays in the scratch from one step
-// to the next (score .. hash, ctx), and what the step decided for each slot leaves as one word (slot_word) that every
-// block of the group waits for.
-struct ResidentSelect {
-  uint64_t *words;      // of the utterance's K slots, written with device-coherent stores
-  int slot0;            // the utterance's first slot in its group
-  int step, T_b;
-  const float *lm;      // [K][V] LM scores (log10) of the slots in LDS (early pruning)
-  int finished;         // out: the utterance's last step is done
-  bool local;           // see res_store
-};
-// step tag (16 bits, step + 1) | utterance finished (1) | parent slot in the group (6) | token + 1 (21) | frame (20)
-constexpr int kWordMaxFrames = 1 << 20;
-__device__ __forceinline__ uint64_t slot_word(int step, int fin, int src, int tok, int t) {
-  return (uint64_t)((step + 1) & 0xffff) | (uint64_t)fin << 16 | (uint64_t)src << 17 | (uint64_t)(tok + 1) << 23 |
-         (uint64_t)t << 44;
-}
-__device__ __forceinline__ int word_tag(uint64_t w) { return (int)(w & 0xffff); }
-__device__ __forceinline__ int word_finished(uint64_t w) { return (int)(w >> 16) & 1; }
-__device__ __forceinline__ int word_src(uint64_t w) { return (int)(w >> 17) & 63; }
-__device__ __forceinline__ int word_tok(uint64_t w) { return ((int)(w >> 23) & 0x1fffff) - 1; }
-__device__ __forceinline__ int word_frame(uint64_t w) { return (int)(w >> 44); }
 constexpr float kLn10 = 2.302585092994046f;
+
+// Recombination: equal (hash, length, last token, frame, symbols in frame).  Slot j of the K new ones: which slot it is merged into
+// (-1: it holds nothing), its score behind that and whether it stays.
+template <int KMAX, class Scratch>
+__device__ __forceinline__ int recombine(const Scratch &s, int K, int j, double &score, bool &live) {
+  int merged = -1;
+  score = s.n_score[j];
+  live = s.n_live[j] != 0;
+  if (live) {
+    // which slots hold the same (hash, length, last token, frame, symbols in frame): all keys are read without
+    // branches in between, so that the LDS reads go out together
+    const uint32_t mh = s.n_hash[j];
+    const int ml = s.n_len[j], mla = s.n_last[j], mt = s.n_t[j], ms = s.n_sym[j];
+    // (the hashes first, read without branches in between; the other fields only of the few slots whose hash is equal)
+    uint32_t same_hash = 0;
+#pragma unroll
+    for (int i = 0; i < KMAX; ++i) {
+      const bool e = (i < K) & (s.n_live[i] != 0) & (s.n_hash[i] == mh);
+      same_hash |= (uint32_t)e << i;
+    }
+    uint32_t same = 1u << j;
+    for (uint32_t r = same_hash & ~(1u << j); r; r &= r - 1u) {
+      const int i = __builtin_ctz(r);
+      const bool e = (s.n_len[i] == ml) & (s.n_last[i] == mla) & (s.n_t[i] == mt) & (s.n_sym[i] == ms);
+      same |= (uint32_t)e << i;
+    }
+    const uint32_t lower = same & ((1u << j) - 1u);
+    if (lower == 0) {  // the lowest slot of its class keeps the log-sum, added up in slot order
+      merged = j;
+      for (uint32_t higher = same & ~((2u << j) - 1u); higher; higher &= higher - 1u)
+        score = logaddexp_d(score, s.n_score[__builtin_ctz(higher)]);
+    } else {
+      merged = __builtin_ctz(lower);
+      live = false;
+      score = -INFINITY;
+    }
+  }
+  return merged;
+}
+__device__ __forceinline__ void write_tree(const SelectArgs &a, int b, int S, int K, int j, int parent, int code, int merged) {
+  if (S < a.S_max) {
+    const size_t ti = ((size_t)b * a.S_max + S) * K + j;
+    store_through(a.tree_parent + ti, parent);
+    store_through(a.tree_token + ti, code);
+    store_through(a.tree_merged + ti, merged);
+  }
+}
+// (one lane) utterance b's last step was S
+__device__ __forceinline__ void end_utterance(const SelectArgs &a, int b, int S) {
+  store_through(a.finished + b, 1);
+  store_through(a.utt_steps + b, S + 1);
+  __threadfence();
+  const int old = atomicAdd(a.n_finished, 1);
+  if (old + 1 == a.B) {
+    *reinterpret_cast<volatile int *>(a.done) = 1;
+    __threadfence_system();
+    *a.h_done = 1;
+  }
+}
 
 // One beam-search step of utterance b by one wave: the K best tokens and blank of every
 // hypothesis (LPR lanes per hypothesis, all hypotheses at once), the Beam best of those,
@@ -264,11 +278,9 @@ constexpr float kLn10 = 2.302585092994046f;
 // durations >= 1) instead of one duration per symbol; candidate (k, j, d) sits at ((k (K + 1) + j) ND + d.
 // ONE: every hypothesis comes with exactly one list (n_chunks == 1, NCH == 1), known at compile time: the merge
 // of list heads and its registers drop out.
-// RES: called by the resident loop (see ResidentSelect).
 template <int LPR, int NCH, int KMAX, bool MULTI = false, bool PAIRS = false, class Scratch = SelectScratch,
-          bool ONE = false, int PLAIN = 0, bool DYNDUR = false, bool RES = false>
-__device__ __forceinline__ void select_utterance(const SelectArgs &a, int b, Scratch &s, const CandView cv,
-                                                 ResidentSelect *rs = nullptr) {
+          bool ONE = false, int PLAIN = 0, bool DYNDUR = false>
+__device__ __forceinline__ void select_utterance(const SelectArgs &a, int b, Scratch &s, const CandView cv) {
   const int K = a.K, V = a.V, lane = threadIdx.x & 63;
   // PLAIN (the caller has checked): 1 = ALSD++, 2 = AES++ without prune margin and prefix search, both without
   // durations and LM: the code of the other cases drops out
@@ -280,25 +292,20 @@ __device__ __forceinline__ void select_utterance(const SelectArgs &a, int b, Scr
   const int m_base = b * K;
   const int nz = 1 + a_ND;
   // ---- every load of the prologue is requested before anything waits on one of them
-  const int fin = RES ? 0 : load_agent(a.finished + b);  // (a wave-uniform word that changes: never through the scalar cache)
-  const int S = RES ? rs->step : *a.step_base + a.step_off;
-  const int T_b = RES ? rs->T_b : a.lengths[b];
+  const int fin = load_agent(a.finished + b);  // (a wave-uniform word that changes: never through the scalar cache)
+  const int S = *a.step_base + a.step_off;
+  const int T_b = a.lengths[b];
   double my_score = -INFINITY;
   int my_t = 0, my_sym = 0, my_len = 0, my_last = -1;
   uint32_t my_hash = 0;
   if (lane < K) {
-    if constexpr (RES) {
-      my_score = s.score[lane];
-      my_t = s.t[lane];
-    } else {
-      const int m = m_base + lane;
-      my_score = a.score[m];
-      my_t = a.t[m];
-      my_sym = a.sym[m];
-      my_len = a.len[m];
-      my_last = a.last[m];
-      my_hash = a.hash[m];
-    }
+    const int m = m_base + lane;
+    my_score = a.score[m];
+    my_t = a.t[m];
+    my_sym = a.sym[m];
+    my_len = a.len[m];
+    my_last = a.last[m];
+    my_hash = a.hash[m];
   }
   // LPR lanes per hypothesis, 64 / LPR hypotheses at once; a beam wider than that takes several passes
   // over the per-hypothesis part (lists -> K best tokens -> candidate scores in LDS)
@@ -557,7 +564,7 @@ __device__ __forceinline__ void select_utterance(const SelectArgs &a, int b, Scr
               key = sc + (double)wk + tok_base;
               val = key + lm_const;
               if (early)
-                val += (double)a.lambda * (double)(RES ? rs->lm[rk * V + wi] * kLn10 : a.lm_rows[(size_t)(m_base + rk) * V + wi]);
+                val += (double)a.lambda * (double)a.lm_rows[(size_t)(m_base + rk) * V + wi];
             }
           }
           put(j, wi < V ? wi : V - 1, key, val);
@@ -581,7 +588,7 @@ __device__ __forceinline__ void select_utterance(const SelectArgs &a, int b, Scr
     wave_sync();
   };
   auto per_utterance = [&]() -> bool {  // false: the utterance had finished before this step
-    if (!RES && a.use_ctx)
+    if (a.use_ctx)
       for (int i = lane; i < K * kCtxMax; i += 64) s.ctx[i / kCtxMax][i % kCtxMax] = a.ctx[m_base * kCtxMax + i];
     if (fin) {  // a finished utterance is frozen; its slots tell the prediction step to copy
       if (lane < K) {
@@ -591,14 +598,12 @@ __device__ __forceinline__ void select_utterance(const SelectArgs &a, int b, Scr
       return false;
     }
     if (lane < K) {
-      if constexpr (!RES) {
-        s.score[lane] = my_score;
-        s.t[lane] = my_t;
-        s.sym[lane] = my_sym;
-        s.len[lane] = my_len;
-        s.last[lane] = my_last;
-        s.hash[lane] = my_hash;
-      }
+      s.score[lane] = my_score;
+      s.t[lane] = my_t;
+      s.sym[lane] = my_sym;
+      s.len[lane] = my_len;
+      s.last[lane] = my_last;
+      s.hash[lane] = my_hash;
       s.sel_val[lane] = -INFINITY;
       s.sel_flat[lane] = -1;
     }
@@ -718,8 +723,6 @@ __device__ __forceinline__ void select_utterance(const SelectArgs &a, int b, Scr
   // ---- expansion into the new slots
   int code = -3, parent = -1, appended = -1;
   int ctx_new[kCtxMax];
-  int t_new = 0;
-  bool live_new = false;
   if (lane < K) {
     const int j = lane;
     const double val = s.sel_val[j];
@@ -764,8 +767,6 @@ __device__ __forceinline__ void select_utterance(const SelectArgs &a, int b, Scr
         ctx_new[0] = v;
       }
       if (t > T_b) t = T_b;
-      t_new = t;
-      live_new = true;
       s.n_live[j] = 1;
       s.n_score[j] = val;
       s.n_t[j] = t;
@@ -775,74 +776,16 @@ __device__ __forceinline__ void select_utterance(const SelectArgs &a, int b, Scr
       s.n_hash[j] = hash;
     }
   }
-  // Resident loop: the words leave here, ahead of the recombination, which changes none of their fields: the slots of a
-  // class stand in the same frame and one of them stays live, so whether any slot is open is known already.  The group's
-  // other blocks go on while this wave merges and writes the tree (batch 32 / beam 4: 10.79
-  // -> 10.50 ms per decode, one utterance 9.53 -> 9.33).
-  bool last_step = false;
-  if constexpr (RES) {
-    last_step = __ballot(live_new && t_new < T_b) == 0ull || S + 1 >= T_b * (a.max_sym + 1);
-    if (lane < K)
-      res_store(rs->local, rs->words + lane, slot_word(S, last_step ? 1 : 0, rs->slot0 + (parent >= 0 ? parent : lane), appended, t_new));
-  }
   wave_sync();
 
-  // ---- recombination: equal (hash, length, last token, frame, symbols in frame)
   if (lane < K) {
     const int j = lane;
-    int merged = -1;
-    double score = s.n_score[j];
-    bool live = s.n_live[j] != 0;
-    if (live) {
-      // which slots hold the same (hash, length, last token, frame, symbols in frame): all keys are read without
-      // branches in between, so that the LDS reads go out together
-      const uint32_t mh = s.n_hash[j];
-      const int ml = s.n_len[j], mla = s.n_last[j], mt = s.n_t[j], ms = s.n_sym[j];
-      // (the hashes first, read without branches in between; the other fields only of the few slots whose hash is equal)
-      uint32_t same_hash = 0;
-#pragma unroll
-      for (int i = 0; i < KMAX; ++i) {
-        const bool e = (i < K) & (s.n_live[i] != 0) & (s.n_hash[i] == mh);
-        same_hash |= (uint32_t)e << i;
-      }
-      uint32_t same = 1u << j;
-      for (uint32_t r = same_hash & ~(1u << j); r; r &= r - 1u) {
-        const int i = __builtin_ctz(r);
-        const bool e = (s.n_len[i] == ml) & (s.n_last[i] == mla) & (s.n_t[i] == mt) & (s.n_sym[i] == ms);
-        same |= (uint32_t)e << i;
-      }
-      const uint32_t lower = same & ((1u << j) - 1u);
-      if (lower == 0) {  // the lowest slot of its class keeps the log-sum, added up in slot order
-        merged = j;
-        for (uint32_t higher = same & ~((2u << j) - 1u); higher; higher &= higher - 1u)
-          score = logaddexp_d(score, s.n_score[__builtin_ctz(higher)]);
-      } else {
-        merged = __builtin_ctz(lower);
-        live = false;
-        score = -INFINITY;
-      }
-    }
+    double score;
+    bool live;
+    const int merged = recombine<KMAX>(s, K, j, score, live);
     const int m = m_base + j;
     // finished when no surviving slot has frames left
-    if constexpr (!RES) last_step = __ballot(live && s.n_t[j] < T_b) == 0ull || S + 1 >= T_b * (a.max_sym + 1);
-    if constexpr (RES) {
-      // (every read of the old state lies before the last wave_sync; the same words are re-read by this wave only)
-      s.score[j] = score;
-      s.t[j] = s.n_t[j];
-      s.sym[j] = s.n_sym[j];
-      s.len[j] = s.n_len[j];
-      s.last[j] = s.n_last[j];
-      s.hash[j] = s.n_hash[j];
-      if (a.use_ctx) {
-#pragma unroll
-        for (int i = 0; i < kCtxMax; ++i) s.ctx[j][i] = ctx_new[i];
-      }
-      if (last_step) {  // what the back-trace ranks and sizes the transcripts by
-        store_through(a.score + m, score);
-        store_through(a.len + m, s.n_len[j]);
-      }
-      rs->finished = last_step;
-    } else {
+    const bool last_step = __ballot(live && s.n_t[j] < T_b) == 0ull || S + 1 >= T_b * (a.max_sym + 1);
     // written through (see store_through): nothing of a step's results waits in an L2 for the kernel's end
     store_through(a.score + m, score);
     store_through(a.t + m, s.n_t[j]);
@@ -859,24 +802,8 @@ __device__ __forceinline__ void select_utterance(const SelectArgs &a, int b, Scr
     }
     store_through(a.src_row + m, parent >= 0 ? m_base + parent : m);
     store_through(a.tok + m, appended);
-    }
-    if (S < a.S_max) {
-      const size_t ti = ((size_t)b * a.S_max + S) * K + j;
-      store_through(a.tree_parent + ti, parent);
-      store_through(a.tree_token + ti, code);
-      store_through(a.tree_merged + ti, merged);
-    }
-    if (j == 0 && last_step) {
-      store_through(a.finished + b, 1);
-      store_through(a.utt_steps + b, S + 1);
-      __threadfence();
-      const int old = atomicAdd(a.n_finished, 1);
-      if (old + 1 == a.B) {
-        *reinterpret_cast<volatile int *>(a.done) = 1;
-        __threadfence_system();
-        *a.h_done = 1;
-      }
-    }
+    write_tree(a, b, S, K, j, parent, code, merged);
+    if (j == 0 && last_step) end_utterance(a, b, S);
   }
   wave_sync();
 }
