@@ -398,10 +398,21 @@ __device__ __forceinline__ void wave_best(double &v, int &i) {
 }
 
 // ---- arithmetic of the LSTM cell
-__device__ __forceinline__ float sigmoid_f(float x) { return 1.f / (1.f + __expf(-x)); }
+// n / d for d from 1 on, n from 0 to 1: the steps of the correctly rounded division without what it does for operands that need scaling
+// (which goes through the one condition register and so keeps divisions from overlapping); up to 2^125, quotients beyond count as
+// of 2^125.
+__device__ __forceinline__ float div_unit_f(float n, float d) {
+  d = d > 0x1p125f ? 0x1p125f : d;  // (no number stays none)
+  float r = __builtin_amdgcn_rcpf(d);
+  r = fmaf(fmaf(-d, r, 1.f), r, r);
+  float q = n * r;
+  q = fmaf(fmaf(-d, q, n), r, q);
+  return fmaf(fmaf(-d, q, n), r, q);
+}
+__device__ __forceinline__ float sigmoid_f(float x) { return div_unit_f(1.f, 1.f + __expf(-x)); }
 __device__ __forceinline__ float tanh_f(float x) {
   const float e = __expf(-2.f * fabsf(x));
-  const float r = (1.f - e) / (1.f + e);
+  const float r = div_unit_f(1.f - e, 1.f + e);
   return x < 0.f ? -r : r;
 }
 // gates (i, f, g, o) = recurrent part r4 + token part g4; c: the unit's old cell state in, the new one out; returns h

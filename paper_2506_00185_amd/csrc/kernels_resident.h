@@ -273,11 +273,12 @@ __host__ __device__ inline size_t res_h_floats(const ResArgs &a) { return a.emb_
 __host__ __device__ inline size_t res_p_floats(const ResArgs &a) { return a.emb_tab ? 0 : (size_t)kResStepRing * a.n_groups * a.NT * a.H * kResSlot; }
 __host__ __device__ inline size_t res_z_floats(const ResArgs &a) { return (size_t)kResStepRing * a.n_groups * a.NT * kResSlot * a.Npad; }
 __host__ __device__ inline size_t res_words(const ResArgs &a) { return (size_t)kResStepRing * a.n_groups * a.NT * kResSlot; }
+template <bool FULL = false>
 __device__ __forceinline__ ResAddr res_addr(const ResArgs &a, int g) {
   ResAddr r;
   r.Npad = a.Npad;
-  r.h_tile = (size_t)a.P * kResSlot;
-  r.p_tile = (size_t)a.H * kResSlot;
+  r.h_tile = (size_t)(FULL ? 8 * 8 * kResMaxRounds : a.P) * kResSlot;
+  r.p_tile = (size_t)(FULL ? 8 * 8 * kResMaxRounds : a.H) * kResSlot;
   r.h_ring = (size_t)a.n_groups * a.NT * r.h_tile;
   r.p_ring = (size_t)a.n_groups * a.NT * r.p_tile;
   r.z_ring = (size_t)a.n_groups * a.NT * kResSlot * a.Npad;
@@ -297,7 +298,8 @@ struct ResBlock {
   const int16_t *order;              // LDS: the group's utterances (indices in the batch), longest first
   int nR, nJ, nP;
   int wave;
-  int fold;                          // the first output-layer tile holds the blank and duration columns, and they are folded
+  int fold;                          // 1, 2: the first output-layer tile holds the blank and duration columns, and they are folded (2: blank
+                                     // alone, see res_fold_one)
   int ptile, jtile[2];               // the tile of 16 outputs / columns whose sums this wave finishes (-1: none)
   float *red;                        // LDS: partial sums (two halves that alternate)
   const uint64_t *spec;              // LDS: see res_fold_bf16
@@ -912,6 +914,30 @@ __device__ __forceinline__ floatx4 res_fold_mma(W w_at, const uint64_t (&x)[kRes
   }
   return lo + hi;
 }
+// Blank alone, and operands that lie as those of the split products do: a lane has the four k of a half of one round after the other,
+// rounds 2 (kq / 2) and the next of either quad (half kq % 2), then round 8 + kq % 2 (half kq / 2), so that a chain of fused multiply-adds
+// goes from lane to lane of a slot with them.  (With matrix instructions, for the sake of one of 16 columns, and the operands read anew
+// in the places that these take: 1.9 us per tile of slots instead of 0.7, which all of the group waited for: batch 32 / beam 8 with
+// LM 18.8 / 15.8 us per step.)
+__device__ __forceinline__ void res_fold_one(const ResBlock &k, const ResLane &l, const ResW16 &w, const uint64_t (&x)[kResMaxRounds]) {
+  auto swap32 = [](float v, int i) { return __uint_as_float(__builtin_amdgcn_permlane32_swap(__float_as_uint(v), __float_as_uint(v), false, false)[i]); };
+  auto swap16 = [](float v, int i) { return __uint_as_float(__builtin_amdgcn_permlane16_swap(__float_as_uint(v), __float_as_uint(v), false, false)[i]); };
+  auto round = [&](float acc, int p) {  // parts p, p + 1: k 0 and 2, k 1 and 3
+    acc = fmaf(res_raw(w, 2 * p), lo_f(x[p]), acc);
+    acc = fmaf(res_raw(w, 2 * p + 2), lo_f(x[p + 1]), acc);
+    acc = fmaf(res_raw(w, 2 * p + 1), hi_f(x[p]), acc);
+    return fmaf(res_raw(w, 2 * p + 3), hi_f(x[p + 1]), acc);
+  };
+  float v = round(round(0.f, 0), 2);                     // rounds 0, 1 in the lower half of the wave ..
+  v = round(round(swap32(v, 0), 0), 2);                  // .. 2, 3 in the upper one
+  v = round(round(swap32(v, 1), 4), 6);
+  v = round(round(swap32(v, 0), 4), 6);
+  const float lower = swap32(v, 1), upper = swap16(v, 1);
+  v = round(l.lane < 32 ? lower : upper, 8);             // round 8 in the first and third 16 lanes,
+  v = round(swap16(v, 0), 8);                            // 9 in the second and fourth
+  v = swap32(v, 0) + swap32(v, 1);
+  if (l.kq == 1) res_red<false>(k, 0)[(k.wave * 64 + l.sl) * 4] = v;
+}
 // bf16 operands: the lane (column, half) has the half's k in order, and the chain is one of fused multiply-adds.  The weights
 // lie in LDS (k.spec), [column][round of all slices][half] four bf16.  (The other columns of the tile are beyond the last one.)
 __device__ __forceinline__ void res_fold_bf16(const ResBlock &k, const ResLane &l, int n_cols, bool second,
@@ -1079,8 +1105,9 @@ __device__ __forceinline__ void res_j_phase(ResBlock &k, int step, const ResWJ<F
       } else {
       ResW16 xs;
       float inv;
+      uint64_t xr[kResMaxRounds];
       {
-        uint64_t x[kResMaxRounds];
+        uint64_t (&x)[kResMaxRounds] = xr;
         if constexpr (ST) res_stateless_pre<FULL, false, true>(a, k, l, nr, x);
         else res_split_gather<FULL>(l, src, nr, x);
         relu(x);
@@ -1094,7 +1121,12 @@ __device__ __forceinline__ void res_j_phase(ResBlock &k, int step, const ResWJ<F
         const float scale = split_scale(m, inv);
         res_split_act(x, scale, xs);
       }
-      if (FULL && k.fold) {
+      if (FULL && k.fold == 2) {
+        floatx4 c1[1], d1[1];
+        res_split_mma<FULL, 1, 1>(wj.t, xs, nr, c1, d1);
+        res_fold_one(k, l, wj.t[0], xr);
+        if (1 < k.nJ) res_put<false>(k, l, 1, split_join(c1[0], d1[0]) * inv);
+      } else if (FULL && k.fold) {
         uint64_t x[kResMaxRounds];  // (known to be there; other places of it than above)
         if constexpr (ST) res_stateless_pre<FULL, false, false>(a, k, l, nr, x);
         else {
@@ -1153,6 +1185,57 @@ __device__ __forceinline__ int res_h_ofs(const ResLane &l, int t) {
   return ((t >> 1) * 4 + (t & 1) * 2 + (l.kq >> 1)) * (2 * kResSlot) + l.sl * 2 + (l.kq & 1);
 }
 
+// The cells of the wave's tile for N tiles of slots.  (All of them at once, without a branch per slot or tile and with divisions that
+// share no condition register: one after the other the five divisions of a cell alone, each a chain of ten instructions, took 0.25 us
+// per tile of slots.)
+template <bool FULL, int N>
+__device__ __forceinline__ void res_cells(const ResBlock &k, int step, int mytile, const float *Rl, float *cl, float *hl) {
+  const ResArgs &a = res_args();
+  const ResLane l = res_lane();
+  const ResAddr ad = res_addr<FULL>(a, k.g);
+  const int P = FULL ? 8 * 8 * kResMaxRounds : a.P, V = a.V, NT = a.NT;
+  const float *G = a.G + 4 * (8 * (mytile >> 1) + (mytile & 1));
+  const int hofs = res_h_ofs(l, mytile);
+  float4 g4[N], r4[N];
+  float c[N], h[N];
+  int at[N];
+  uint64_t w[N];
+#pragma unroll
+  for (int nt = 0; nt < N; ++nt) w[nt] = k.word[nt * kResSlot + l.sl];
+#pragma unroll
+  for (int nt = 0; nt < N; ++nt) {
+    const int tok = word_tok(w[nt]);
+    g4[nt] = *reinterpret_cast<const float4 *>(G + ((uint32_t)(tok < 0 ? V : tok) * (uint32_t)(4 * P) + 8 * l.kq));
+    const int src = word_src(w[nt]);
+    at[nt] = (k.wave * NT + (src >> 4)) * 64 + l.kq * 16 + (src & 15);
+  }
+#pragma unroll
+  for (int nt = 0; nt < N; ++nt) {
+    r4[nt] = *reinterpret_cast<const float4 *>(Rl + at[nt] * 4);
+    c[nt] = cl[at[nt]];
+    h[nt] = hl[at[nt]];
+  }
+#pragma unroll
+  for (int nt = 0; nt < N; ++nt) {
+    float c1 = c[nt];
+    const float h1 = lstm_unit(r4[nt], g4[nt], c1);
+    const bool on = word_tok(w[nt]) >= 0;
+    c[nt] = on ? c1 : c[nt];
+    h[nt] = on ? h1 : h[nt];
+  }
+  wait_stores_acknowledged();
+#pragma unroll
+  for (int nt = 0; nt < N; ++nt)
+    res_store(k.local, ad.h(step, nt) + hofs, h[nt]);
+  wave_sync();
+#pragma unroll
+  for (int nt = 0; nt < N; ++nt) {
+    const int to = (k.wave * NT + nt) * 64 + l.lane;
+    cl[to] = c[nt];
+    hl[to] = h[nt];
+  }
+}
+
 template <bool FULL, int FORM, bool ST>
 __device__ __forceinline__ void res_worker(ResBlock k, const ResTab &tab, float *lds) {
   constexpr bool BF16 = FORM == kResBf16, SPLIT = FORM == kResSplit;
@@ -1161,7 +1244,7 @@ __device__ __forceinline__ void res_worker(ResBlock k, const ResTab &tab, float 
   k.nR = res_uniform(tab.nR);
   k.nJ = res_uniform(tab.nJ);
   k.nP = res_uniform(tab.nP);
-  k.fold = res_uniform(FULL && a0.fold && k.nJ > 0 && tab.J[0] == a0.V / (BF16 ? 32 : 16));
+  k.fold = res_uniform(FULL && a0.fold && k.nJ > 0 && tab.J[0] == a0.V / (BF16 ? 32 : 16) ? (SPLIT && a0.N - a0.V == 1 ? 2 : 1) : 0);
   // which tile's sums this wave finishes, and the tile whose cells it updates
   int pt = -1, jt0 = -1, jt1 = -1;
   if constexpr (BF16) {  // two waves per 32-row tile (output layer: two more for the second slot tile)
@@ -1270,9 +1353,15 @@ __device__ __forceinline__ void res_worker(ResBlock k, const ResTab &tab, float 
         uint32_t v[2 * kResMaxRounds];
 #pragma unroll
         for (int i = 0; i < kResMaxRounds; ++i) {
-          const uint64_t u = reinterpret_cast<const uint64_t *>(a0.WJs)[(k.wave * kResMaxRounds + i) * 64 + l0.lane];
-          v[2 * i] = (uint32_t)u;
-          v[2 * i + 1] = (uint32_t)(u >> 32);
+          const uint32_t *ws = reinterpret_cast<const uint32_t *>(a0.WJs) + (size_t)k.wave * kResMaxRounds * 128;
+          if (k.fold == 2) {  // blank's weights at the k of the lane's parts (k of a round: see k_pack_fold)
+            const int round = i < 8 ? 4 * (i >> 2) + 2 * (l0.kq >> 1) + ((i & 3) >> 1) : 8 + (l0.kq & 1), half = i < 8 ? l0.kq & 1 : l0.kq >> 1;
+            v[2 * i] = ws[round * 128 + (i & 1) * 32 + half];
+            v[2 * i + 1] = ws[round * 128 + ((i & 1) + 2) * 32 + half];
+          } else {
+            v[2 * i] = ws[(i * 64 + l0.lane) * 2];
+            v[2 * i + 1] = ws[(i * 64 + l0.lane) * 2 + 1];
+          }
         }
         wj.t[0] = ResW16{{{v[0], v[1], v[2], v[3]}, {v[8], v[9], v[10], v[11]}}, {{v[4], v[5], v[6], v[7]}, {v[12], v[13], v[14], v[15]}}, {v[16], v[17]}, {v[18], v[19]}};
       }
@@ -1321,38 +1410,9 @@ __device__ __forceinline__ void res_worker(ResBlock k, const ResTab &tab, float 
   for (int step = 0; over == 0; ++step) {
     // ---- cells
     if (!ST && k.wave < k.nR) {
-      const ResArgs &a = res_args();
-      const ResLane l = res_lane();
-      const ResAddr ad = res_addr(a, k.g);
-      const int unit = 8 * (mytile >> 1) + 2 * l.kq + (mytile & 1);
-      const int hofs = res_h_ofs(l, mytile);
-      float4 g4[kResMaxNT];
-#pragma unroll
-      for (int nt = 0; nt < kResMaxNT; ++nt)
-        if (nt < k.nt) {
-          const int tok = word_tok(k.word[nt * kResSlot + l.sl]);
-          g4[nt] = *reinterpret_cast<const float4 *>(a.G + (size_t)(tok < 0 ? a.V : tok) * 4 * a.P + 4 * unit);
-        }
-      float cn[kResMaxNT], hn[kResMaxNT];
-#pragma unroll
-      for (int nt = 0; nt < kResMaxNT; ++nt)
-        if (nt < k.nt) {
-          const uint64_t w = k.word[nt * kResSlot + l.sl];
-          const int src = word_src(w), at = (k.wave * a.NT + (src >> 4)) * 64 + l.kq * 16 + (src & 15);
-          cn[nt] = cl[at];
-          hn[nt] = hl[at];
-          if (word_tok(w) >= 0) hn[nt] = lstm_unit(*reinterpret_cast<const float4 *>(Rl + at * 4), g4[nt], cn[nt]);
-          if (nt == 0) wait_stores_acknowledged();
-          res_store(k.local, ad.h(step, nt) + hofs, hn[nt]);
-        }
-      wave_sync();
-#pragma unroll
-      for (int nt = 0; nt < kResMaxNT; ++nt)
-        if (nt < k.nt) {
-          const int at = (k.wave * a.NT + nt) * 64 + l.lane;
-          cl[at] = cn[nt];
-          hl[at] = hn[nt];
-        }
+      if (k.nt == 1) res_cells<FULL, 1>(k, step, mytile, Rl, cl, hl);
+      else if (k.nt == 2) res_cells<FULL, 2>(k, step, mytile, Rl, cl, hl);
+      else res_cells<FULL, 3>(k, step, mytile, Rl, cl, hl);
     }
     if constexpr (!ST)
       res_p_phase<FULL, FORM>(k, step);
