@@ -106,6 +106,11 @@ __device__ __forceinline__ void split_f16(float a, float b, uint32_t &hi, uint32
   hi = __builtin_bit_cast(uint32_t, h);
   lo = __builtin_bit_cast(uint32_t, __builtin_convertvector(r, f16x2_t));
 }
+// one value -> hi | lo << 16
+__device__ __forceinline__ uint32_t split_f16(float a) {
+  const _Float16 h = (_Float16)a, l = (_Float16)((a - (float)h) * kLoScale);
+  return (uint32_t)__builtin_bit_cast(uint16_t, h) | (uint32_t)__builtin_bit_cast(uint16_t, l) << 16;
+}
 __device__ __forceinline__ floatx16 mfma32_f16(uintx4_t a, uintx4_t b, floatx16 acc) {
   return __builtin_amdgcn_mfma_f32_32x32x16_f16(__builtin_bit_cast(f16x8_t, a), __builtin_bit_cast(f16x8_t, b), acc, 0, 0, 0);
 }
@@ -399,20 +404,20 @@ __device__ __forceinline__ void wave_best(double &v, int &i) {
 
 // ---- arithmetic of the LSTM cell
 // n / d for d from 1 on, n from 0 to 1: the steps of the correctly rounded division without what it does for operands that need scaling
-// (which goes through the one condition register and so keeps divisions from overlapping); up to 2^125, quotients beyond count as
-// of 2^125.
+// (which goes through the one condition register and so keeps divisions from overlapping).  FIXUP: d may be infinite.
+template <bool FIXUP>
 __device__ __forceinline__ float div_unit_f(float n, float d) {
-  d = d > 0x1p125f ? 0x1p125f : d;  // (no number stays none)
   float r = __builtin_amdgcn_rcpf(d);
   r = fmaf(fmaf(-d, r, 1.f), r, r);
   float q = n * r;
   q = fmaf(fmaf(-d, q, n), r, q);
-  return fmaf(fmaf(-d, q, n), r, q);
+  q = fmaf(fmaf(-d, q, n), r, q);
+  return FIXUP ? __builtin_amdgcn_div_fixupf(q, d, n) : q;
 }
-__device__ __forceinline__ float sigmoid_f(float x) { return div_unit_f(1.f, 1.f + __expf(-x)); }
+__device__ __forceinline__ float sigmoid_f(float x) { return div_unit_f<true>(1.f, 1.f + __expf(-x)); }
 __device__ __forceinline__ float tanh_f(float x) {
   const float e = __expf(-2.f * fabsf(x));
-  const float r = div_unit_f(1.f - e, 1.f + e);
+  const float r = div_unit_f<false>(1.f - e, 1.f + e);
   return x < 0.f ? -r : r;
 }
 // gates (i, f, g, o) = recurrent part r4 + token part g4; c: the unit's old cell state in, the new one out; returns h

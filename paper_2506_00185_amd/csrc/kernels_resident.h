@@ -71,7 +71,8 @@ struct ResTab {
 // output-layer tiles a block keeps in registers (a tile is 16 rows; 32 with the bf16 matrix instructions)
 template <bool BF16>
 constexpr int kResRegJ = BF16 ? 1 : 2;
-// 16-row tiles whose partial sums one half of the buffer holds
+// 16-row tiles whose partial sums one half of the buffer holds, at least (with split operands four where LDS has room: both halves of k
+// of two projection tiles)
 template <bool BF16>
 constexpr int kResRedBlocks = BF16 ? 4 : 3;
 
@@ -102,6 +103,7 @@ struct ResArgs {
   int n_groups, stride;              // groups; block i of the launch is of group i % stride (there may be fewer groups)
   int n_sel, upc;                    // per group: selecting blocks, utterances of each
   int NT, halves, has_lm;            // slot tiles per group
+  int red_blocks;                    // see kResRedBlocks
   int rounds_h, rounds_p;            // rounds of 8 k per wave slice over H and over P
   int poll_limit, start_limit;       // polls of a data wait; ticks (10 ns) of the wait for all blocks
   int start_blocks;                  // how many those are
@@ -301,7 +303,8 @@ struct ResBlock {
   int fold;                          // 1, 2: the first output-layer tile holds the blank and duration columns, and they are folded (2: blank
                                      // alone, see res_fold_one)
   int ptile, jtile[2];               // the tile of 16 outputs / columns whose sums this wave finishes (-1: none)
-  float *red;                        // LDS: partial sums (two halves that alternate)
+  float *red;                        // LDS: partial sums (two halves that alternate, of so many 16-row tiles)
+  int red_blocks;
   const uint64_t *spec;              // LDS: see res_fold_bf16
   const uint64_t *tiles;             // LDS: weights of up to kResMaxLdsTiles tiles
   const floatx4 *par;                // LDS: scales and biases of the rows of the block's tiles (see ResPar)
@@ -338,24 +341,33 @@ struct ResW16 {
 constexpr int kResRoundBytes = 4 * kResSlot * 8, kResWordBytes = 2 * kResSlot * 8;  // of a round; from a word to the one of k + 1
 __device__ __forceinline__ uint32_t res_quad_base(const ResLane &l) { return (l.kq >> 1) * 2 * kResRoundBytes + ((l.kq & 1) * kResSlot + l.sl) * 8; }
 __device__ __forceinline__ uint32_t res_pair_base(const ResLane &l) { return (l.kq & 1) * kResRoundBytes + ((l.kq >> 1) * kResSlot + l.sl) * 8; }
-__device__ __forceinline__ constexpr uint32_t res_part(int i) { return (i >> 1) * kResRoundBytes + (i & 1) * kResWordBytes; }
+// Hidden states come split already (a cell's lane does it once, where each reader did it for all of its slice: 100 instructions of each
+// wave in the chain h -> pre, and as many under the selection).  A word there holds the hi, or the lo, of the four k of a half of a round,
+// {0, 2, 1, 3}: of a round hi of the halves, then lo, so that the words of a quad are the lane's operand as they come.
+template <bool SPLIT>
+__device__ __forceinline__ constexpr uint32_t res_part(int i) {
+  return SPLIT ? (i & 1) * kResRoundBytes + (i >> 1) * kResWordBytes : (i >> 1) * kResRoundBytes + (i & 1) * kResWordBytes;
+}
 // part i (0 to 9) of ten rounds; pair: that of round 8
-__device__ __forceinline__ constexpr uint32_t res_split_part(int i) { return i < 8 ? (i >> 2) * 4 * kResRoundBytes + res_part(i & 3) : res_part(i & 1); }
+template <bool SPLIT>
+__device__ __forceinline__ constexpr uint32_t res_split_part(int i) {
+  return i < 8 ? (i >> 2) * 4 * kResRoundBytes + res_part<SPLIT>(i & 3) : (i & 1) * kResWordBytes;
+}
 // a slice of nr rounds, as soon as all of it is there
-template <bool FULL>
+template <bool FULL, bool SPLIT>
 __device__ __forceinline__ void res_split_gather(const ResLane &l, const char *src, int nr, uint64_t (&x)[kResMaxRounds]) {
   // (absent rounds read the slice's first and are cleared)
   const uint32_t offs[2] = {res_quad_base(l), res_pair_base(l) + 8 * kResRoundBytes}, end = nr * kResRoundBytes;
   auto at = [&](int i, const uint32_t (&o)[2]) {
-    if constexpr (FULL) return src + o[i < 8 ? 0 : 1] + res_split_part(i);
-    const uint32_t w = o[i < 8 ? 0 : 1] + res_split_part(i);
+    if constexpr (FULL) return src + o[i < 8 ? 0 : 1] + res_split_part<SPLIT>(i);
+    const uint32_t w = o[i < 8 ? 0 : 1] + res_split_part<SPLIT>(i);
     return src + (w < end ? w : l.sl * 8);
   };
   res_gather<true, kResMaxRounds>(offs, at, kResMaxRounds, x);
   if constexpr (!FULL) {
 #pragma unroll
     for (int i = 0; i < kResMaxRounds; ++i)
-      if (offs[i < 8 ? 0 : 1] + res_split_part(i) >= end) x[i] = 0;
+      if (offs[i < 8 ? 0 : 1] + res_split_part<SPLIT>(i) >= end) x[i] = 0;
   }
 }
 // words of a lane -> operand
@@ -370,6 +382,12 @@ __device__ __forceinline__ void res_split_act(const uint64_t (&x)[kResMaxRounds]
   }
   o.th = uintx2_t{h[8], h[9]};
   o.tl = uintx2_t{l[8], l[9]};
+}
+// words that are split already -> operand
+__device__ __forceinline__ uintx4_t res_quad(uint64_t a, uint64_t b) { return uintx4_t{(uint32_t)a, (uint32_t)(a >> 32), (uint32_t)b, (uint32_t)(b >> 32)}; }
+__device__ __forceinline__ uintx2_t res_pair(uint64_t a) { return uintx2_t{(uint32_t)a, (uint32_t)(a >> 32)}; }
+__device__ __forceinline__ ResW16 res_split_words(const uint64_t (&x)[kResMaxRounds]) {
+  return ResW16{{res_quad(x[0], x[1]), res_quad(x[4], x[5])}, {res_quad(x[2], x[3]), res_quad(x[6], x[7])}, res_pair(x[8]), res_pair(x[9])};
 }
 // a lane's part of a split tile, p: the wave's
 __device__ __forceinline__ ResW16 res_split_load(const uintx4_t *p, const ResLane &l) {
@@ -439,7 +457,7 @@ struct ResPar {
 // partial sums of a 16-row tile: wave's lane (row group, slot) holds four rows
 template <bool BF16>
 __device__ __forceinline__ float *res_red(const ResBlock &k, int block) {
-  return k.red + ((k.phase & 1) * kResRedBlocks<BF16> + block) * kResRedBlock;
+  return k.red + ((k.phase & 1) * k.red_blocks + block) * kResRedBlock;
 }
 template <bool BF16>
 __device__ __forceinline__ void res_put(const ResBlock &k, const ResLane &l, int block, floatx4 v) {
@@ -536,6 +554,8 @@ __device__ __forceinline__ void res_p_finish(const ResArgs &a, const ResBlock &k
     if constexpr (FORM == kResSplit) s *= par[ResPar::kScale];
     v += s;
   }
+#pragma unroll
+  for (int i = 0; i < 4; ++i) v[i] = fmaxf(v[i], 0.f);  // (once here, not by every reader; not a number: 0)
   float *dst = res_p_dst(ad.p(step, nt), k.ptile, l.kq, l.sl);
   asm volatile("" : "+v"(v));  // (all four before either store: else both sums' operands live on behind the first)
   wait_stores_acknowledged();  // (of the pattern that this wave put back into places of the array meanwhile)
@@ -747,76 +767,85 @@ __device__ __forceinline__ void res_p_phase(ResBlock &k, int step) {
           }
           finish(tp);
         }
-      } else if (halves) {
-        // a slice of up to five rounds of either half of k: a quad, and a fifth round that the lanes of even kq hold
-        uint64_t x[12];
-        // (absent rounds: words that are there, cleared below)
-        const uint32_t end = nh * kResRoundBytes, second = 4 * nr * kResRoundBytes;
-        const uint32_t quad = res_quad_base(l), fifth = (FULL || nh > 4) && (l.kq & 1) == 0 ? 4 * kResRoundBytes + res_pair_base(l) : l.sl * 8;
-        const uint32_t offs[4] = {quad, fifth, quad + second, fifth + second};
-        auto at = [&](int i, const uint32_t (&o)[4]) {
-          const int p = i % 6, hf = i / 6;
-          if constexpr (FULL) return src + o[2 * hf + (p >= 4)] + res_part(p & 3);
-          const uint32_t w = o[2 * hf] + res_part(p);
-          return src + (p >= 4 ? o[2 * hf + 1] + res_part(p & 3) : w < end + hf * second ? w : l.sl * 8 + hf * second);
-        };
-        res_gather<true, 12>(offs, at, 12, x);
-        uintx4_t xh[2], xl[2];
-        uintx2_t yh[2], yl[2];
-#pragma unroll
-        for (int hf = 0; hf < 2; ++hf) {
-          uint32_t h[6], lo[6];
-#pragma unroll
-          for (int p = 0; p < 6; ++p) {
-            const bool in = p < 4 ? FULL || quad + res_part(p) < end : (FULL || nh > 4) && (l.kq & 1) == 0;
-            const uint64_t v = in ? x[6 * hf + p] : 0;
-            split_f16(lo_f(v) * kHidScale, hi_f(v) * kHidScale, h[p], lo[p]);
-          }
-          xh[hf] = uintx4_t{h[0], h[1], h[2], h[3]};
-          xl[hf] = uintx4_t{lo[0], lo[1], lo[2], lo[3]};
-          yh[hf] = uintx2_t{h[4], h[5]};
-          yl[hf] = uintx2_t{lo[4], lo[5]};
-        }
-#pragma unroll 1
-        for (int tp = 0; tp < k.nP; ++tp) {
-          const uintx4_t *w = tiles + (size_t)tp * (kResTileFloats / 4);
-#pragma unroll
-          for (int hf = 0; hf < 2; ++hf) {
-            const uintx4_t wh = w[160 * hf + l.lane], wl = w[160 * hf + 64 + l.lane];
-            floatx4 acc[1] = {floatx4{0.f, 0.f, 0.f, 0.f}}, cor[1] = {acc[0]};
-            acc[0] = mfma16_f16(wh, xh[hf], acc[0]);
-            cor[0] = mfma16_f16(wh, xl[hf], cor[0]);
-            cor[0] = mfma16_f16(wl, xh[hf], cor[0]);
-            if constexpr (!FULL) cor[0] = mfma16_f16(wl, unscaled_lo(xl[hf]), cor[0]);
-            if (FULL || nh > 4) {
-              uintx4_t v = w[160 * hf + 128 + (l.kq >> 1) * 16 + l.sl];
-              if (l.kq & 1) v = uintx4_t{0, 0, 0, 0};
-              const uintx2_t vh = {v[0], v[1]}, vl = {v[2], v[3]};
-              res_mma_gap(acc, cor);
-              acc[0] = mfma16_f16(vh, yh[hf], acc[0]);
-              cor[0] = mfma16_f16(vh, yl[hf], cor[0]);
-              cor[0] = mfma16_f16(vl, yh[hf], cor[0]);
-              if constexpr (!FULL) cor[0] = mfma16_f16(vl, unscaled_lo(yl[hf]), cor[0]);
-            }
-            res_put<false>(k, l, hf, split_join(acc[0], cor[0]));
-            __builtin_amdgcn_sched_barrier(0);  // (both halves at once need more registers than there are)
-          }
-          finish(tp);
-        }
       } else {
-        ResW16 xs;
-        {
-          uint64_t x[kResMaxRounds];
-          res_split_gather<FULL>(l, src, nr, x);
-          res_split_act(x, kHidScale, xs);
-        }
+        // One pass over all tiles, one barrier, where their partial sums find room; else a pass per tile
+        const bool together = k.nP == 1 || !halves || k.red_blocks >= 4;
+        auto all_tiles = [&](auto tile_mma) {
+          if (together) {
+#pragma unroll
+            for (int tp = 0; tp < kResMaxP; ++tp)
+              if (tp < k.nP) tile_mma(tp, halves ? 2 * tp : tp);
+            __syncthreads();
+            res_end_if_given_up();
+            const int mine = kResWaves - 1 - k.wave, first = halves ? 2 * mine : mine;
+            if (k.ptile >= 0) res_p_finish<FORM>(a, k, l, ad, step, nt, first, first + 1, f);
+            ++k.phase;
+          } else {
 #pragma unroll 1
-        for (int tp = 0; tp < k.nP; ++tp) {
-          const ResW16 w[1] = {res_split_load(tiles + (size_t)tp * (kResTileFloats / 4), l)};
-          floatx4 acc[1], cor[1];
-          res_split_mma<FULL, 0, 1>(w, xs, nr, acc, cor);
-          res_put<false>(k, l, 0, split_join(acc[0], cor[0]));
-          finish(tp);
+            for (int tp = 0; tp < k.nP; ++tp) {
+              tile_mma(tp, 0);
+              finish(tp);
+            }
+          }
+        };
+        if (halves) {
+          // a slice of up to five rounds of either half of k: a quad, and a fifth round that the lanes of even kq hold
+          uint64_t x[12];
+          // (absent rounds: words that are there, cleared below)
+          const uint32_t end = nh * kResRoundBytes, second = 4 * nr * kResRoundBytes;
+          const uint32_t quad = res_quad_base(l), fifth = (FULL || nh > 4) && (l.kq & 1) == 0 ? 4 * kResRoundBytes + res_pair_base(l) : l.sl * 8;
+          const uint32_t offs[4] = {quad, fifth, quad + second, fifth + second};
+          auto at = [&](int i, const uint32_t (&o)[4]) {
+            const int p = i % 6, hf = i / 6;
+            const uint32_t part = p < 4 ? res_part<true>(p) : (p & 1) * kResWordBytes;
+            if constexpr (FULL) return src + o[2 * hf + (p >= 4)] + part;
+            const uint32_t w = o[2 * hf] + part;
+            return src + (p >= 4 ? o[2 * hf + 1] + part : w < end + hf * second ? w : l.sl * 8 + hf * second);
+          };
+          res_gather<true, 12>(offs, at, 12, x);
+#pragma unroll
+          for (int i = 0; i < 12; ++i) {
+            const int p = i % 6;
+            const bool in = p < 4 ? FULL || quad + res_part<true>(p) < end : (FULL || nh > 4) && (l.kq & 1) == 0;
+            x[i] = in ? x[i] : 0;
+          }
+          all_tiles([&](int tp, int block) {
+            const uintx4_t *w = tiles + (size_t)tp * (kResTileFloats / 4);
+#pragma unroll
+            for (int hf = 0; hf < 2; ++hf) {
+              const uintx4_t xh = res_quad(x[6 * hf], x[6 * hf + 1]), xl = res_quad(x[6 * hf + 2], x[6 * hf + 3]);
+              const uintx4_t wh = w[160 * hf + l.lane], wl = w[160 * hf + 64 + l.lane];
+              floatx4 acc[1] = {floatx4{0.f, 0.f, 0.f, 0.f}}, cor[1] = {acc[0]};
+              acc[0] = mfma16_f16(wh, xh, acc[0]);
+              cor[0] = mfma16_f16(wh, xl, cor[0]);
+              cor[0] = mfma16_f16(wl, xh, cor[0]);
+              if constexpr (!FULL) cor[0] = mfma16_f16(wl, unscaled_lo(xl), cor[0]);
+              if (FULL || nh > 4) {
+                const uintx2_t yh = res_pair(x[6 * hf + 4]), yl = res_pair(x[6 * hf + 5]);
+                const uintx4_t v = w[160 * hf + 128 + (l.kq >> 1) * 16 + l.sl];  // (the lanes of odd kq: against zeros)
+                const uintx2_t vh = {v[0], v[1]}, vl = {v[2], v[3]};
+                res_mma_gap(acc, cor);
+                acc[0] = mfma16_f16(vh, yh, acc[0]);
+                cor[0] = mfma16_f16(vh, yl, cor[0]);
+                cor[0] = mfma16_f16(vl, yh, cor[0]);
+                if constexpr (!FULL) cor[0] = mfma16_f16(vl, unscaled_lo(yl), cor[0]);
+              }
+              res_put<false>(k, l, block + hf, split_join(acc[0], cor[0]));
+            }
+          });
+        } else {
+          ResW16 xs;
+          {
+            uint64_t x[kResMaxRounds];
+            res_split_gather<FULL, true>(l, src, nr, x);
+            xs = res_split_words(x);
+          }
+          all_tiles([&](int tp, int block) {
+            const ResW16 w[1] = {res_split_load(tiles + (size_t)tp * (kResTileFloats / 4), l)};
+            floatx4 acc[1], cor[1];
+            res_split_mma<FULL, 0, 1>(w, xs, nr, acc, cor);
+            res_put<false>(k, l, block, split_join(acc[0], cor[0]));
+          });
         }
       }
     }
@@ -1010,7 +1039,7 @@ __device__ __forceinline__ void res_j_phase(ResBlock &k, int step, const ResWJ<F
       }
       uint64_t xb[kResMaxRounds];
 #pragma unroll
-      for (int i = 0; i < kResMaxRounds; ++i) xb[i] = round_bf16<true>(x + 2 * i);
+      for (int i = 0; i < kResMaxRounds; ++i) xb[i] = round_bf16<ST>(x + 2 * i);
       auto put_out = [&](int t) {
         __syncthreads();
         res_end_if_given_up();
@@ -1051,7 +1080,7 @@ __device__ __forceinline__ void res_j_phase(ResBlock &k, int step, const ResWJ<F
     for (int nt = 0; nt < k.nt; ++nt) {
       if (step == a.stall_step && nt + 1 == k.nt) __builtin_amdgcn_endpgm();
       const char *src = reinterpret_cast<const char *>(ad.p(step, nt)) + k.wave * nr * kResRoundBytes;
-      auto relu = [](uint64_t (&x)[kResMaxRounds]) {
+      [[maybe_unused]] auto relu = [](uint64_t (&x)[kResMaxRounds]) {
 #pragma unroll
         for (int i = 0; i < kResMaxRounds; ++i) x[i] = pack2(fmaxf(lo_f(x[i]), 0.f), fmaxf(hi_f(x[i]), 0.f));
       };
@@ -1068,7 +1097,7 @@ __device__ __forceinline__ void res_j_phase(ResBlock &k, int step, const ResWJ<F
           const uint32_t offs[2] = {(uint32_t)l.lane * 8, (uint32_t)l.lane * 8 + 5 * kResRoundBytes};
           res_gather<FULL, kResMaxRounds>(offs, [src](int i, const uint32_t (&o)[2]) { return src + o[i / 5] + i % 5 * kResRoundBytes; }, nr, x);
         }
-        relu(x);
+        if constexpr (ST) relu(x);
         floatx4 acc[NJ];
         // N tiles from the first on
         auto mma = [&](auto first, auto w_at, auto &c) {
@@ -1109,16 +1138,15 @@ __device__ __forceinline__ void res_j_phase(ResBlock &k, int step, const ResWJ<F
       {
         uint64_t (&x)[kResMaxRounds] = xr;
         if constexpr (ST) res_stateless_pre<FULL, false, true>(a, k, l, nr, x);
-        else res_split_gather<FULL>(l, src, nr, x);
-        relu(x);
-        float m = 0.f;
+        else res_split_gather<FULL, false>(l, src, nr, x);
+        if constexpr (ST) relu(x);
+        uint32_t m = 0;  // (of values from 0 on, whose bits are in order)
 #pragma unroll
-        for (int i = 0; i < kResMaxRounds; ++i) m = fmaxf(m, fmaxf(lo_f(x[i]), hi_f(x[i])));
-        const auto s16 = __builtin_amdgcn_permlane16_swap(__float_as_uint(m), __float_as_uint(m), false, false);
-        m = fmaxf(__uint_as_float(s16[0]), __uint_as_float(s16[1]));
-        const auto s32 = __builtin_amdgcn_permlane32_swap(__float_as_uint(m), __float_as_uint(m), false, false);
-        m = fmaxf(__uint_as_float(s32[0]), __uint_as_float(s32[1]));
-        const float scale = split_scale(m, inv);
+        for (int i = 0; i < kResMaxRounds; ++i) m = max(m, max((uint32_t)x[i], (uint32_t)(x[i] >> 32)));
+        const auto s16 = __builtin_amdgcn_permlane16_swap(m, m, false, false);
+        m = max(s16[0], s16[1]);
+        const auto s32 = __builtin_amdgcn_permlane32_swap(m, m, false, false);
+        const float scale = split_scale(__uint_as_float(max(s32[0], s32[1])), inv);
         res_split_act(x, scale, xs);
       }
       if (FULL && k.fold == 2) {
@@ -1133,7 +1161,7 @@ __device__ __forceinline__ void res_j_phase(ResBlock &k, int step, const ResWJ<F
 #pragma unroll
           for (int i = 0; i < kResMaxRounds; ++i) x[i] = res_load(src + l.lane * 8 + i * kResRoundBytes);
         }
-        relu(x);
+        if constexpr (ST) relu(x);
         floatx4 c1[1], d1[1];
         res_split_mma<FULL, 1, 1>(wj.t, xs, nr, c1, d1);
         res_put<false>(k, l, 0, res_fold_mma([&](int i) { return res_raw(wj.t[0], i); }, x));
@@ -1180,22 +1208,24 @@ __device__ __forceinline__ void res_clear_pz(const ResArgs &a, const ResBlock &k
 // ---------------------------------------------------------------------------
 // blocks that own tiles
 // ---------------------------------------------------------------------------
-// place of the lane's unit of W_hh tile t in the fragment order of h
+// place of the lane's unit of W_hh tile t in the fragment order of h (split: of the hi, or the lo, of the two units of a pair of lanes)
+template <int FORM>
 __device__ __forceinline__ int res_h_ofs(const ResLane &l, int t) {
+  if constexpr (FORM == kResSplit) return ((t >> 1) * 4 + (l.kq & 1) * 2 + (l.kq >> 1)) * (2 * kResSlot) + l.sl * 2 + (t & 1);
   return ((t >> 1) * 4 + (t & 1) * 2 + (l.kq >> 1)) * (2 * kResSlot) + l.sl * 2 + (l.kq & 1);
 }
 
 // The cells of the wave's tile for N tiles of slots.  (All of them at once, without a branch per slot or tile and with divisions that
 // share no condition register: one after the other the five divisions of a cell alone, each a chain of ten instructions, took 0.25 us
 // per tile of slots.)
-template <bool FULL, int N>
+template <bool FULL, int FORM, int N>
 __device__ __forceinline__ void res_cells(const ResBlock &k, int step, int mytile, const float *Rl, float *cl, float *hl) {
   const ResArgs &a = res_args();
   const ResLane l = res_lane();
   const ResAddr ad = res_addr<FULL>(a, k.g);
   const int P = FULL ? 8 * 8 * kResMaxRounds : a.P, V = a.V, NT = a.NT;
   const float *G = a.G + 4 * (8 * (mytile >> 1) + (mytile & 1));
-  const int hofs = res_h_ofs(l, mytile);
+  const int hofs = res_h_ofs<FORM>(l, mytile);
   float4 g4[N], r4[N];
   float c[N], h[N];
   int at[N];
@@ -1223,10 +1253,20 @@ __device__ __forceinline__ void res_cells(const ResBlock &k, int step, int mytil
     c[nt] = on ? c1 : c[nt];
     h[nt] = on ? h1 : h[nt];
   }
+  uint32_t out[N];
+#pragma unroll
+  for (int nt = 0; nt < N; ++nt) {
+    out[nt] = __float_as_uint(h[nt]);
+    if constexpr (FORM == kResSplit) {
+      const uint32_t v = split_f16(h[nt] * kHidScale);
+      const auto s = __builtin_amdgcn_permlane16_swap(v, v, false, false);  // of the lanes of even, of odd kq
+      out[nt] = __builtin_amdgcn_perm(s[1], s[0], (l.kq & 1) ? 0x07060302u : 0x05040100u);
+    }
+  }
   wait_stores_acknowledged();
 #pragma unroll
   for (int nt = 0; nt < N; ++nt)
-    res_store(k.local, ad.h(step, nt) + hofs, h[nt]);
+    res_store(k.local, reinterpret_cast<uint32_t *>(ad.h(step, nt) + hofs), out[nt]);
   wave_sync();
 #pragma unroll
   for (int nt = 0; nt < N; ++nt) {
@@ -1293,7 +1333,8 @@ __device__ __forceinline__ void res_worker(ResBlock k, const ResTab &tab, float 
     k.red = reinterpret_cast<float *>(dst);
   }
   // LDS of the cells: sums W_hh h of the block's tiles, cell state and hidden state of their units, [tile][slot tile][64]
-  float *Rl = k.red + 2 * kResRedBlocks<BF16> * kResRedBlock, *cl = Rl + kResMaxR * a0.NT * 256, *hl = cl + kResMaxR * a0.NT * 64;
+  k.red_blocks = res_uniform(a0.red_blocks);
+  float *Rl = k.red + 2 * k.red_blocks * kResRedBlock, *cl = Rl + kResMaxR * a0.NT * 256, *hl = cl + kResMaxR * a0.NT * 64;
   float *par = hl + kResMaxR * a0.NT * 64;
   k.par = reinterpret_cast<const floatx4 *>(par);
   if (threadIdx.x < 16) {
@@ -1410,9 +1451,9 @@ __device__ __forceinline__ void res_worker(ResBlock k, const ResTab &tab, float 
   for (int step = 0; over == 0; ++step) {
     // ---- cells
     if (!ST && k.wave < k.nR) {
-      if (k.nt == 1) res_cells<FULL, 1>(k, step, mytile, Rl, cl, hl);
-      else if (k.nt == 2) res_cells<FULL, 2>(k, step, mytile, Rl, cl, hl);
-      else res_cells<FULL, 3>(k, step, mytile, Rl, cl, hl);
+      if (k.nt == 1) res_cells<FULL, FORM, 1>(k, step, mytile, Rl, cl, hl);
+      else if (k.nt == 2) res_cells<FULL, FORM, 2>(k, step, mytile, Rl, cl, hl);
+      else res_cells<FULL, FORM, 3>(k, step, mytile, Rl, cl, hl);
     }
     if constexpr (!ST)
       res_p_phase<FULL, FORM>(k, step);
@@ -1436,7 +1477,7 @@ __device__ __forceinline__ void res_worker(ResBlock k, const ResTab &tab, float 
       // 1.3 % slower.)
       if (step > 1 && k.wave < k.nR)
         for (int nt = 0; nt < k.nt; ++nt)
-          res_store(k.local, reinterpret_cast<uint32_t *>(ad.h(step - 2, nt) + res_h_ofs(l, mytile)), kResEmpty);
+          res_store(k.local, reinterpret_cast<uint32_t *>(ad.h(step - 2, nt) + res_h_ofs<FORM>(l, mytile)), kResEmpty);
 #pragma unroll 1
       for (int nt = 0; nt < k.nt; ++nt) {
         ResW16 xs;
@@ -1447,8 +1488,8 @@ __device__ __forceinline__ void res_worker(ResBlock k, const ResTab &tab, float 
           const uint32_t offs[2] = {(uint32_t)l.lane * 8, (uint32_t)l.lane * 8 + 5 * kResRoundBytes};
           res_gather<FULL, kResMaxRounds>(offs, [src](int i, const uint32_t (&o)[2]) { return src + o[i / 5] + i % 5 * kResRoundBytes; }, nrp, x);
         } else {
-          res_split_gather<FULL>(l, src, nrp, x);
-          res_split_act(x, kHidScale, xs);
+          res_split_gather<FULL, true>(l, src, nrp, x);
+          xs = res_split_words(x);
         }
         auto three = [&](auto first) {
           constexpr int t0 = decltype(first)::value;

@@ -101,9 +101,11 @@ constexpr int kResShortSpin = 1000;  // a test's limit: the launch waits, for a 
 
 constexpr int kResStallPolls = 4096;  // a test's wait for data that does not come
 
+constexpr size_t kResOwnLds = 256;  // the kernel's own words beside the dynamic ones, at most
+
 struct Plan {
   bool ok = false;
-  int n_groups = 0, stride = 0, n_blocks = 0, nu = 0, n_sel = 0, upc = 0, NT = 0;
+  int n_groups = 0, stride = 0, n_blocks = 0, nu = 0, n_sel = 0, upc = 0, NT = 0, red_blocks = 0;
   size_t lds = 0;
   std::vector<ResTab> tab;
 };
@@ -198,13 +200,19 @@ Plan make_plan(const Resident &r, const rnnt_config_t &c, int B, int K, bool has
   const bool bf = c.prec == RNNT_BF16_JOINT;
   int lds_tiles = 0;
   for (const ResTab &t : p.tab) lds_tiles = std::max(lds_tiles, t.nP + std::max(0, t.nJ - (bf ? kResRegJ<true> : kResRegJ<false>)));
-  const size_t worker = (size_t)lds_tiles * (r.form == kResSplit ? kResTileFloats : std::max(c.pred == RNNT_PRED_LSTM ? c.P : 0, c.H) * kResSlot) * 4 +
-                        (bf && fold ? (size_t)(1 + c.n_durations) * c.H * 2 : 0) + (size_t)2 * (bf ? kResRedBlocks<true> : kResRedBlocks<false>) * kResRedBlock * 4 +
-                        (size_t)kResMaxR * p.NT * (256 + 128) * 4 + ResPar::kFloats * 4 + (size_t)p.NT * kResSlot * (sizeof(int2) + kResWaves * 8);
+  auto worker_lds = [&](int red_blocks) {
+    return (size_t)lds_tiles * (r.form == kResSplit ? kResTileFloats : std::max(c.pred == RNNT_PRED_LSTM ? c.P : 0, c.H) * kResSlot) * 4 +
+           (bf && fold ? (size_t)(1 + c.n_durations) * c.H * 2 : 0) + (size_t)2 * red_blocks * kResRedBlock * 4 +
+           (size_t)kResMaxR * p.NT * (256 + 128) * 4 + ResPar::kFloats * 4 + (size_t)p.NT * kResSlot * (sizeof(int2) + kResWaves * 8);
+  };
+  // (640 wide: with one tile of slots)
+  p.red_blocks = bf ? kResRedBlocks<true> : kResRedBlocks<false>;
+  if (r.form == kResSplit && worker_lds(4) + kResOwnLds <= (size_t)r.max_lds) p.red_blocks = 4;
+  const size_t worker = worker_lds(p.red_blocks);
   const size_t sel = (res_sel_floats(p.upc, p.NT) + (size_t)p.upc * K * res_row_floats(c.V)) * 4;
   p.lds = std::max(worker, sel);
   p.lds = std::max<size_t>(p.lds, 84 * 1024);  // more than half of a compute unit's: two blocks never share one
-  if (p.lds + 256 > (size_t)r.max_lds) return p;  // (the kernel's own words beside the dynamic ones)
+  if (p.lds + kResOwnLds > (size_t)r.max_lds) return p;
   p.ok = true;
   return p;
 }
@@ -329,7 +337,7 @@ hipError_t resident_launch(Resident &r, const rnnt_config_t &c, const ResidentBa
   a.lm = b.lm;
   a.B = b.B; a.K = b.K; a.T = b.T; a.V = c.V; a.N = c.V + 1 + c.n_durations; a.Npad = b.Npad; a.H = c.H; a.P = c.P;
   a.n_groups = p.n_groups; a.stride = p.stride; a.n_sel = p.n_sel; a.upc = p.upc;
-  a.NT = p.NT; a.halves = b.halves ? 1 : 0; a.has_lm = b.has_lm ? 1 : 0;
+  a.NT = p.NT; a.red_blocks = p.red_blocks; a.halves = b.halves ? 1 : 0; a.has_lm = b.has_lm ? 1 : 0;
   a.rounds_h = c.H / 64; a.rounds_p = c.P / 64;
   a.fold = b.fold ? 1 : 0;
   a.stall_step = b.stall_step;
