@@ -56,6 +56,9 @@ constexpr int kResQuads = 5;         // 16-byte words of a lane of a split tile
 constexpr int kResTileFloats = kResWaves * kResQuads * 64 * 4;  // a split tile
 constexpr int kResMaxV = 1024;
 constexpr int kResStepRing = 4;      // ring of the hand-over arrays
+// The words of a step are written in several places, of which a block polls one: the waves of a group, up to 240 of them, that poll one
+// line of the L2 hold each other up.
+constexpr int kResWordCopies = 4, kResWordPlace = 64;  // and the distance of the places, at least a group's slots
 constexpr int kResNotLocal = -2;     // stall_step of a test: the groups take themselves to lie on several XCDs
 constexpr uint32_t kResEmpty = 0xffffffffu;
 // How a decoder's products are formed: on float32 matrix instructions; W_out and W_pred on bf16 ones (the bf16 joint); on float16 ones
@@ -274,7 +277,7 @@ struct ResAddr {
 __host__ __device__ inline size_t res_h_floats(const ResArgs &a) { return a.emb_tab ? 0 : (size_t)kResStepRing * a.n_groups * a.NT * a.P * kResSlot; }
 __host__ __device__ inline size_t res_p_floats(const ResArgs &a) { return a.emb_tab ? 0 : (size_t)kResStepRing * a.n_groups * a.NT * a.H * kResSlot; }
 __host__ __device__ inline size_t res_z_floats(const ResArgs &a) { return (size_t)kResStepRing * a.n_groups * a.NT * kResSlot * a.Npad; }
-__host__ __device__ inline size_t res_words(const ResArgs &a) { return (size_t)kResStepRing * a.n_groups * a.NT * kResSlot; }
+__host__ __device__ inline size_t res_words(const ResArgs &a) { return (size_t)kResStepRing * a.n_groups * kResWordCopies * kResWordPlace; }
 template <bool FULL = false>
 __device__ __forceinline__ ResAddr res_addr(const ResArgs &a, int g) {
   ResAddr r;
@@ -284,17 +287,18 @@ __device__ __forceinline__ ResAddr res_addr(const ResArgs &a, int g) {
   r.h_ring = (size_t)a.n_groups * a.NT * r.h_tile;
   r.p_ring = (size_t)a.n_groups * a.NT * r.p_tile;
   r.z_ring = (size_t)a.n_groups * a.NT * kResSlot * a.Npad;
-  r.w_ring = (size_t)a.n_groups * a.NT * kResSlot;
+  r.w_ring = (size_t)a.n_groups * kResWordCopies * kResWordPlace;
   r.hb = a.hb + (size_t)g * a.NT * r.h_tile;
   r.pb = a.pb + (size_t)g * a.NT * r.p_tile;
   r.zb = a.zb + (size_t)g * a.NT * kResSlot * a.Npad;
-  r.words = a.words + (size_t)g * a.NT * kResSlot;
+  r.words = a.words + (size_t)g * kResWordCopies * kResWordPlace;
   return r;
 }
 
 // what a wave knows about itself and its block
 struct ResBlock {
   int g, nu, nslots;                 // group, utterances and slots of the group
+  int place;                         // of the words that this block polls (see kResWordCopies)
   bool local;                        // the group's blocks share one XCD (see res_store)
   int nt;                            // slot tiles up to the last one with an unfinished utterance: the others are left out
   const int16_t *order;              // LDS: the group's utterances (indices in the batch), longest first
@@ -480,7 +484,7 @@ __device__ __forceinline__ floatx4 res_sum(const ResBlock &k, const ResLane &l, 
 __device__ __forceinline__ int res_words(ResBlock &k, int step) {
   const ResArgs &a = res_args();
   const ResLane l = res_lane();
-  const uint64_t *p = res_addr(a, k.g).w(step) + l.sl;
+  const uint64_t *p = res_addr(a, k.g).w(step) + k.place + l.sl;
   const int tag = (step + 1) & 0xffff;
   int top = 0;
 #pragma unroll 1
@@ -1551,16 +1555,20 @@ __device__ __forceinline__ void res_worker(ResBlock k, const ResTab &tab, float 
 constexpr int kResMaxHyps = 24;  // hypotheses of a selecting block
 // floats of a row of keys in LDS (those behind the vocabulary are -inf)
 __host__ __device__ inline int res_row_floats(int V) { return V <= 128 ? 128 : V <= 512 ? 512 : kResMaxV; }
-// An utterance's hypotheses (score to ctx: kept from step to step) and what a step of its selection needs.
 constexpr int kResTop = 64;      // candidates that are ranked
+// An utterance's hypotheses (up to ctx: kept from step to step) and what a step of its selection needs.
+// a hypothesis' tokens as candidates: (score + key) + base + lm (see res_select)
+struct __align__(16) ResRow {
+  double score, base, lm, pad;
+};
 struct ResUtt {
-  double score[kMaxBeam];
+  ResRow row[kMaxBeam];            // (of these, score is kept)
   int4 state[kMaxBeam];            // frame, symbols in the frame, length, last token
   uint32_t hash[kMaxBeam];
   int kind[kMaxBeam];              // 0: empty, 1: waits or has finished, 2: expanded, 3: the same, with blank alone
   int ctx[kMaxBeam][kCtxMax];
-  // of a hypothesis' candidates (see res_select): score = (score of the hypothesis + key) + tok_base + lm_const
-  double tok_base[kMaxBeam], lm_const[kMaxBeam], lse[kMaxBeam], margin[kMaxBeam], delta[kMaxBeam], blank_key[kMaxBeam], blank[kMaxBeam];
+  // of a step
+  double lm_const[kMaxBeam], lse[kMaxBeam], margin[kMaxBeam], delta[kMaxBeam], blank_key[kMaxBeam], blank[kMaxBeam];
   int adv[kMaxBeam];               // frames that a token (low half) and that blank advances
   float set[64];
   int chunk[16 * 32 + 16];         // hypothesis * 32 + chunk of those that reach the bound
@@ -1779,6 +1787,14 @@ __device__ __forceinline__ void res_lm_row(const LmView &lm, const int *hist, in
   wave_sync();
 }
 
+// a word, in all of its places
+__device__ __forceinline__ void res_put_word(bool local, uint64_t *p, uint64_t w) {
+#pragma unroll
+  for (int i = 0; i < kResWordCopies; ++i) {
+    if (local) __hip_atomic_store(p + i * kResWordPlace, w, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WAVEFRONT);
+    else store_agent(p + i * kResWordPlace, w);
+  }
+}
 __device__ __forceinline__ int res_kind(bool live, int4 state, int T_b, int max_sym) {
   return !live ? 0 : state.x >= T_b ? 1 : state.y >= max_sym ? 3 : 2;
 }
@@ -1790,6 +1806,7 @@ __device__ __forceinline__ bool res_select(const ResBlock &k, int step, int u, i
   const ResArgs &ra = res_args();
   const SelectArgs &a = ra.sel;
   const int K = ra.K, V = ra.V, nz = ra.N - V, stride = res_row_floats(V), lane = threadIdx.x & 63;
+  constexpr float kLeast = -3.4028235e38f;  // (no token at -inf is a candidate)
   const int ND = PLAIN ? 0 : nz - 1;
   const bool has_lm = PLAIN == 0 && ra.has_lm, early = PLAIN == 0 && a.lm_early, late_lm = has_lm && !early;
   const bool aes = PLAIN == 0 && a.algo == 1, use_gamma = aes && a.gamma < INFINITY;
@@ -1798,7 +1815,7 @@ __device__ __forceinline__ bool res_select(const ResBlock &k, int step, int u, i
   constexpr int LPR = 64 / KC, NC = 32 / LPR;
   const int e = lane & (LPR - 1), r = lane / LPR, row = r < K ? r : 0;
   const int n_cst = 4 * ((V + 127) / 128);
-  const double sc = s.score[row];
+  const double sc = s.row[row].score;
   const int kind = r < K ? s.kind[row] : 0;
   float2 c[NC];
   float km[NC];
@@ -1808,9 +1825,9 @@ __device__ __forceinline__ bool res_select(const ResBlock &k, int step, int u, i
     const float2 v = L.cst[h0 + row][i];
     c[q] = i < n_cst ? v : make_float2(-INFINITY, 0.f);
     km[q] = c[q].x;
-    if (late_lm) {
+    if constexpr (PLAIN == 0) {
       const float x = L.kmax[h0 + row][i];
-      km[q] = i < n_cst ? x : -INFINITY;
+      km[q] = !late_lm ? km[q] : i < n_cst ? x : -INFINITY;
     }
   }
   const float *zs = L.zs + (h0 + row) * nz;
@@ -1883,14 +1900,12 @@ __device__ __forceinline__ bool res_select(const ResBlock &k, int step, int u, i
   // unchanged.  Late pruning: lambda lm is in the row's keys; early: added to the score of those that are kept.
   const double lm_const = (has_lm && !a.lm_rule3) ? (double)a.lambda * ((double)lse_nb - (double)lse_all) : 0.0;
   const double tok_base = x_tok - (double)lse_all;
+  const double lm_key = early ? 0.0 : lm_const;
   const double thr = use_gamma ? (double)fmaxf(st_mx, zb) - (double)lse_all - (double)a.gamma : -INFINITY;
-  auto token_key = [&](float z, double score, double base, double lmc, double lse, double margin) {
+  auto token_key = [&](float z, double score, double base, double lm) {
     double key = score + (double)z + base;
-    if (PLAIN == 0) {
-      if (!early) key = key + lmc;
-      if (use_gamma && (double)z - lse < margin) key = -INFINITY;
-    }
-    return z > -INFINITY ? key : -INFINITY;
+    if (PLAIN == 0) key = key + lm;
+    return z >= kLeast ? key : -INFINITY;
   };
   double bkey = -INFINITY, bval = -INFINITY;
   if (kind >= 2) {
@@ -1903,12 +1918,15 @@ __device__ __forceinline__ bool res_select(const ResBlock &k, int step, int u, i
     bkey = bval = sc;  // a waiting or finished hypothesis stays as it is
   }
   if (e == 0 && r < K) {
-    s.tok_base[r] = tok_base;
+    s.row[r].base = tok_base;
     if (PLAIN == 0) {
-      s.lm_const[r] = lm_const;
-      s.lse[r] = (double)lse_all;
-      s.margin[r] = thr;
+      s.row[r].lm = lm_key;
       s.adv[r] = adv;
+      if (early) s.lm_const[r] = lm_const;
+      if (use_gamma) {
+        s.lse[r] = (double)lse_all;
+        s.margin[r] = thr;
+      }
     }
   }
   double delta = 0.0;
@@ -1931,11 +1949,13 @@ __device__ __forceinline__ bool res_select(const ResBlock &k, int step, int u, i
         int ahead = 0;
         for (int n = lane; n < V; n += 64) ahead += comes_before_count(rj[n], n, z, v);
         ahead = wave_sum_i(ahead);
-        const double val = token_key(z, s.score[j], s.tok_base[j], s.lm_const[j], s.lse[j], s.margin[j]);
+        const ResRow rw = s.row[j];
+        double val = token_key(z, rw.score, rw.base, rw.lm);
+        if (use_gamma && (double)z - s.lse[j] < s.margin[j]) val = -INFINITY;
         if (lane == who && ahead < K && val > -INFINITY) add = logaddexp_d(add, val);
       }
     }
-    if (lane < K) s.delta[lane] = add > -INFINITY ? logaddexp_d(s.score[lane], add) - s.score[lane] : 0.0;
+    if (lane < K) s.delta[lane] = add > -INFINITY ? logaddexp_d(s.row[lane].score, add) - s.row[lane].score : 0.0;
     wave_sync();
     delta = s.delta[row];
     bkey = bkey + delta;
@@ -1945,7 +1965,8 @@ __device__ __forceinline__ bool res_select(const ResBlock &k, int step, int u, i
   float kmx = km[0];
 #pragma unroll
   for (int q = 1; q < NC; ++q) kmx = fmaxf(kmx, km[q]);
-  double best = kind == 2 ? token_key(kmx, sc, tok_base, lm_const, (double)lse_all, thr) : -INFINITY;
+  double best = kind == 2 ? token_key(kmx, sc, tok_base, lm_key) : -INFINITY;
+  if (use_gamma && (double)kmx - (double)lse_all < thr) best = -INFINITY;
   if (prefix) best = best + delta;
   if (e == LPR - 1) best = bkey > best || !(best > -INFINITY) ? bkey : best;
   float fl = (float)best;
@@ -1961,13 +1982,17 @@ __device__ __forceinline__ bool res_select(const ResBlock &k, int step, int u, i
   }
   wave_sync();
   int ge = 0;  // sets not below mine
+  {
+    int n[4] = {0, 0, 0, 0};
 #pragma unroll
-  for (int i = 0; i < SETS; i += 4) {
-    const float4 v = *reinterpret_cast<const float4 *>(s.set + i);
-    ge += (int)(v.x >= fl);
-    ge += (int)(v.y >= fl);
-    ge += (int)(v.z >= fl);
-    ge += (int)(v.w >= fl);
+    for (int i = 0; i < SETS; i += 4) {
+      const float4 v = *reinterpret_cast<const float4 *>(s.set + i);
+      n[0] += (int)(v.x >= fl);
+      n[1] += (int)(v.y >= fl);
+      n[2] += (int)(v.z >= fl);
+      n[3] += (int)(v.w >= fl);
+    }
+    ge = (n[0] + n[1]) + (n[2] + n[3]);
   }
   double tau = -INFINITY;
   {
@@ -1976,12 +2001,20 @@ __device__ __forceinline__ bool res_select(const ResBlock &k, int step, int u, i
     else tau = (double)wave_max(fl > -INFINITY && ge >= K ? fl : -INFINITY);
   }
   // ---- the chunks that reach it, and of these and the blanks the candidates that do
+  // (chunks by the key that reaches it, in float32, with room for the rounding of all of this)
+  float reach;
+  {
+    double x = tau;
+    if (prefix) x = x - delta;
+    if (PLAIN == 0) x = x - lm_key;
+    reach = (float)((x - tok_base) - sc);
+    reach -= fabsf(reach) * 2.4e-7f + (fabsf((float)sc) + fabsf((float)tau)) * 1e-14f + 1e-6f;
+    reach = tau > -INFINITY ? fmaxf(reach, kLeast) : kLeast;
+  }
   int n_chunks = 0;
 #pragma unroll
   for (int q = 0; q < NC; ++q) {
-    double x = token_key(km[q], sc, tok_base, lm_const, (double)lse_all, thr);
-    if (prefix) x = x + delta;
-    const bool in = kind == 2 && x > -INFINITY && x >= tau;
+    const bool in = kind == 2 && km[q] >= reach;
     const unsigned long long mask = __ballot(in);
     const int pos = n_chunks + __builtin_amdgcn_mbcnt_hi((uint32_t)(mask >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)mask, 0));
     if (in) s.chunk[pos] = r << 5 | (e + LPR * q);
@@ -2004,7 +2037,9 @@ __device__ __forceinline__ bool res_select(const ResBlock &k, int step, int u, i
   const float *zr = early ? res_addr(ra, k.g).z(step, u * K) : rows;  // (early: a row of Npad, in global memory)
   const int zstride = early ? ra.Npad : stride;
   auto token = [&](int h, int n, float z, double &key, double &val) {
-    val = token_key(z, s.score[h], s.tok_base[h], PLAIN ? 0.0 : s.lm_const[h], PLAIN ? 0.0 : s.lse[h], PLAIN ? 0.0 : s.margin[h]);
+    const ResRow &rw = s.row[h];
+    val = token_key(z, rw.score, rw.base, PLAIN ? 0.0 : rw.lm);
+    if (use_gamma && (double)z - s.lse[h] < s.margin[h]) val = -INFINITY;
     key = val;
     if (PLAIN == 0) {
       if (prefix) key = val + s.delta[h];
@@ -2153,9 +2188,9 @@ __device__ __forceinline__ bool res_select(const ResBlock &k, int step, int u, i
   const bool last_step = __ballot(alive && st.x < T_b) == 0ull || step + 1 >= T_b * (a.max_sym + 1);
   const int slot0 = u * K, n_kept = __popcll(__ballot(kept));
   uint64_t *words = res_addr(ra, k.g).w(step) + slot0;
-  if (kept) res_store(k.local, words + rank, slot_word(step, last_step ? 1 : 0, slot0 + (alive ? par : rank), appended, st.x));
+  if (kept) res_put_word(k.local, words + rank, slot_word(step, last_step ? 1 : 0, slot0 + (alive ? par : rank), appended, st.x));
   if (n_kept < K && lane >= n_kept && lane < K) {
-    res_store(k.local, words + lane, slot_word(step, last_step ? 1 : 0, slot0 + lane, -1, 0));
+    res_put_word(k.local, words + lane, slot_word(step, last_step ? 1 : 0, slot0 + lane, -1, 0));
     s.n_live[lane] = 0;
     s.n_score[lane] = -INFINITY;
     s.n_t[lane] = s.n_sym[lane] = s.n_len[lane] = 0;
@@ -2196,7 +2231,7 @@ __device__ __forceinline__ bool res_select(const ResBlock &k, int step, int u, i
     bool live;
     const int merged = recombine<KC>(s, K, j, score, live);
     const int4 now = make_int4(s.n_t[j], s.n_sym[j], s.n_len[j], s.n_last[j]);
-    s.score[j] = score;
+    s.row[j].score = score;
     s.state[j] = now;
     s.hash[j] = s.n_hash[j];
     if (last_step) {  // what the back-trace ranks and sizes the transcripts by
@@ -2239,7 +2274,7 @@ __device__ __forceinline__ void res_selector(ResBlock k, int sel, float *lds) {
     finished = T_b == 0;
     if (lane < K) {
       const int4 none = make_int4(0, 0, 0, -1);
-      s.score[lane] = lane == 0 ? 0.0 : -INFINITY;
+      s.row[lane].score = lane == 0 ? 0.0 : -INFINITY;
       s.state[lane] = none;
       s.hash[lane] = 0;
       s.kind[lane] = res_kind(lane == 0, none, T_b, a0.sel.max_sym);
@@ -2273,7 +2308,7 @@ __device__ __forceinline__ void res_selector(ResBlock k, int sel, float *lds) {
     if (k.wave < nu) {
       const int u = u0 + k.wave, b = res_utt(k, u);
       if (finished) {
-        if (lane < K) res_store(k.local, res_addr(res_args(), k.g).w(step) + u * K + lane, slot_word(step, 1, u * K + lane, -1, 0));
+        if (lane < K) res_put_word(k.local, res_addr(res_args(), k.g).w(step) + u * K + lane, slot_word(step, 1, u * K + lane, -1, 0));
       } else {
         finished = res_select<KC, PLAIN>(k, step, u, b, T_b, k.wave * K, rows + (size_t)k.wave * K * stride, utt[k.wave], L);
       }
@@ -2320,6 +2355,7 @@ __global__ __launch_bounds__(kResThreads, 2) void k_decode_resident(ResArgs) {
   ResBlock k;
   k.g = g;
   const int rank = (int)blockIdx.x / a.stride;
+  k.place = rank % kResWordCopies * kResWordPlace;
   k.nu = (a.B - k.g + a.n_groups - 1) / a.n_groups;
   // utterances of the group, g + n_groups i, the longest first: the ends of the slots run empty first, and tiles behind
   // the last unfinished utterance are left out of every phase (TDT, 64 utterances of 4 to 20 s, beam 4: 5.90 -> 5.22 ms;

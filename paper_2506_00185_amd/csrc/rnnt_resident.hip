@@ -282,7 +282,7 @@ int resident_create(Resident &r, const rnnt_config_t &c, const ResidentWeights &
                         : alloc(&r.WPf, (size_t)nP * 16 * c.P));
   }
   ok = ok && alloc(&r.zb, kResStepRing * rows * w.out_rows) &&
-       alloc(&r.words, kResStepRing * rows) && alloc(&r.ctl, kResCtlWords) && alloc(&r.tab, r.n_cus);
+       alloc(&r.words, (size_t)kResStepRing * G * kResWordCopies * kResWordPlace) && alloc(&r.ctl, kResCtlWords) && alloc(&r.tab, r.n_cus);
   if (!ok) return fail("resident loop: hipMalloc");
   if ((e = hipHostMalloc(reinterpret_cast<void **>(&r.h_abort), 128, hipHostMallocMapped)) != hipSuccess) return fail("hipHostMalloc");
   if ((e = hipHostGetDevicePointer(reinterpret_cast<void **>(&r.h_abort_dev), r.h_abort, 0)) != hipSuccess) return fail("pinned word");
