@@ -304,8 +304,8 @@ struct ResBlock {
   const int16_t *order;              // LDS: the group's utterances (indices in the batch), longest first
   int nR, nJ, nP;
   int wave;
-  int fold;                          // 1, 2: the first output-layer tile holds the blank and duration columns, and they are folded (2: blank
-                                     // alone, see res_fold_one)
+  int fold;                          // the first output-layer tile holds the blank and duration columns, and they are folded (split
+                                     // operands: it is one of them, see res_fold_one)
   int ptile, jtile[2];               // the tile of 16 outputs / columns whose sums this wave finishes (-1: none)
   float *red;                        // LDS: partial sums (two halves that alternate, of so many 16-row tiles)
   int red_blocks;
@@ -857,18 +857,38 @@ __device__ __forceinline__ void res_p_phase(ResBlock &k, int step) {
 }
 
 // ---- J: z[step] = W_out ReLU(pre[step]) + b_out for the block's tiles
+// Folded columns of split operands are dealt one by one, as "tiles" from V / 16 on: the column of such a one
+__device__ __forceinline__ int res_column(int tile) {
+  const int V = res_args().V;
+  return V + tile - V / 16;
+}
 template <int FORM>
 __device__ __forceinline__ void res_j_finish(const ResBlock &k, const ResLane &l, const ResAddr &ad, int step, int nt, int tile, int par, int block) {
   const int slot = nt * kResSlot + l.sl, n0 = 16 * tile + 4 * l.kq;
+  if (FORM == kResSplit && k.fold && k.wave == 0) {  // (a column alone: see res_fold_one)
+    const float *r = res_red<false>(k, block) + l.sl * 4;
+    float v = 0.f;
+#pragma unroll
+    for (int w = 0; w < kResWaves; ++w) v += r[w * 256];
+    v += reinterpret_cast<const float *>(k.par + par + ResPar::kBias)[0];
+    wait_stores_acknowledged();
+    if (slot < k.nslots && l.kq == 0) res_store(k.local, ad.z(step, slot) + res_column(tile), v);
+    return;
+  }
   floatx4 v = res_sum<FORM == kResBf16>(k, l, block);
   if constexpr (FORM == kResSplit) v *= k.par[par + ResPar::kScale + l.kq];
   v += k.par[par + ResPar::kBias + l.kq];
   wait_stores_acknowledged();
   if (slot < k.nslots) res_store16(k.local, ad.z(step, slot) + n0, v);
 }
+template <int FORM>
 __device__ __forceinline__ void clear_z(const ResBlock &k, const ResLane &l, const ResAddr &ad, int step, int nt, int tile) {
   const int slot = nt * kResSlot + l.sl;
   const float e = __uint_as_float(kResEmpty);
+  if (FORM == kResSplit && k.fold && k.wave == 0) {
+    if (slot < k.nslots && l.kq == 0) res_store(k.local, ad.z(step, slot) + res_column(tile), e);
+    return;
+  }
   if (slot < k.nslots) res_store16(k.local, ad.z(step, slot) + 16 * tile + 4 * l.kq, floatx4{e, e, e, e});
 }
 
@@ -947,11 +967,11 @@ __device__ __forceinline__ floatx4 res_fold_mma(W w_at, const uint64_t (&x)[kRes
   }
   return lo + hi;
 }
-// Blank alone, and operands that lie as those of the split products do: a lane has the four k of a half of one round after the other,
-// rounds 2 (kq / 2) and the next of either quad (half kq % 2), then round 8 + kq % 2 (half kq / 2), so that a chain of fused multiply-adds
-// goes from lane to lane of a slot with them.  (With matrix instructions, for the sake of one of 16 columns, and the operands read anew
-// in the places that these take: 1.9 us per tile of slots instead of 0.7, which all of the group waited for: batch 32 / beam 8 with
-// LM 18.8 / 15.8 us per step.)
+// Split operands: one of the columns per block.  The operands lie as those of the split products do: a lane has the four k of a half of
+// one round after the other, rounds 2 (kq / 2) and the next of either quad (half kq % 2), then round 8 + kq % 2 (half kq / 2), so that a
+// chain of fused multiply-adds goes from lane to lane of a slot with them.  (All columns by one block, with matrix instructions and the
+// operands read anew in the places that these take: 1.9 us per tile of slots instead of 0.7, which all of the group waited for: batch 32 /
+// beam 8 with LM 18.8 / 15.8 us per step, TDT batch 64 16.5 / 14.1.)
 __device__ __forceinline__ void res_fold_one(const ResBlock &k, const ResLane &l, const ResW16 &w, const uint64_t (&x)[kResMaxRounds]) {
   auto swap32 = [](float v, int i) { return __uint_as_float(__builtin_amdgcn_permlane32_swap(__float_as_uint(v), __float_as_uint(v), false, false)[i]); };
   auto swap16 = [](float v, int i) { return __uint_as_float(__builtin_amdgcn_permlane16_swap(__float_as_uint(v), __float_as_uint(v), false, false)[i]); };
@@ -1153,22 +1173,10 @@ __device__ __forceinline__ void res_j_phase(ResBlock &k, int step, const ResWJ<F
         const float scale = split_scale(__uint_as_float(max(s32[0], s32[1])), inv);
         res_split_act(x, scale, xs);
       }
-      if (FULL && k.fold == 2) {
+      if (FULL && k.fold) {
         floatx4 c1[1], d1[1];
         res_split_mma<FULL, 1, 1>(wj.t, xs, nr, c1, d1);
         res_fold_one(k, l, wj.t[0], xr);
-        if (1 < k.nJ) res_put<false>(k, l, 1, split_join(c1[0], d1[0]) * inv);
-      } else if (FULL && k.fold) {
-        uint64_t x[kResMaxRounds];  // (known to be there; other places of it than above)
-        if constexpr (ST) res_stateless_pre<FULL, false, false>(a, k, l, nr, x);
-        else {
-#pragma unroll
-          for (int i = 0; i < kResMaxRounds; ++i) x[i] = res_load(src + l.lane * 8 + i * kResRoundBytes);
-        }
-        if constexpr (ST) relu(x);
-        floatx4 c1[1], d1[1];
-        res_split_mma<FULL, 1, 1>(wj.t, xs, nr, c1, d1);
-        res_put<false>(k, l, 0, res_fold_mma([&](int i) { return res_raw(wj.t[0], i); }, x));
         if (1 < k.nJ) res_put<false>(k, l, 1, split_join(c1[0], d1[0]) * inv);
       } else {
         floatx4 acc[NJ], cor[NJ];
@@ -1193,18 +1201,18 @@ __device__ __forceinline__ void res_j_phase(ResBlock &k, int step, const ResWJ<F
 // block has read its logits, which needed every piece of pre.
 // Who reads a place next (four steps on, see kResStepRing) has seen words that needed what this wave wrote for two steps on,
 // which it stores behind the acknowledgement of these.
-template <bool BF16>
+template <int FORM>
 __device__ __forceinline__ void res_clear_pz(const ResArgs &a, const ResBlock &k, const ResAddr &ad, int step) {
   const ResLane l = res_lane();
   for (int nt = 0; nt < k.nt; ++nt) {
     if (k.ptile >= 0) clear_p(k, l, ad, step, nt);
-    if constexpr (BF16) {
+    if constexpr (FORM == kResBf16) {
       if (k.wave >> 1 == (nt & 1)) {
-        if (k.jtile[0] >= 0) clear_z(k, l, ad, step, nt, k.jtile[0]);
-        if (k.jtile[1] >= 0) clear_z(k, l, ad, step, nt, k.jtile[1]);
+        if (k.jtile[0] >= 0) clear_z<FORM>(k, l, ad, step, nt, k.jtile[0]);
+        if (k.jtile[1] >= 0) clear_z<FORM>(k, l, ad, step, nt, k.jtile[1]);
       }
     } else {
-      if (k.jtile[0] >= 0) clear_z(k, l, ad, step, nt, k.jtile[0]);
+      if (k.jtile[0] >= 0) clear_z<FORM>(k, l, ad, step, nt, k.jtile[0]);
     }
   }
 }
@@ -1288,7 +1296,7 @@ __device__ __forceinline__ void res_worker(ResBlock k, const ResTab &tab, float 
   k.nR = res_uniform(tab.nR);
   k.nJ = res_uniform(tab.nJ);
   k.nP = res_uniform(tab.nP);
-  k.fold = res_uniform(FULL && a0.fold && k.nJ > 0 && tab.J[0] == a0.V / (BF16 ? 32 : 16) ? (SPLIT && a0.N - a0.V == 1 ? 2 : 1) : 0);
+  k.fold = res_uniform(FULL && a0.fold && k.nJ > 0 && tab.J[0] >= a0.V / (BF16 ? 32 : 16));
   // which tile's sums this wave finishes, and the tile whose cells it updates
   int pt = -1, jt0 = -1, jt1 = -1;
   if constexpr (BF16) {  // two waves per 32-row tile (output layer: two more for the second slot tile)
@@ -1352,6 +1360,10 @@ __device__ __forceinline__ void res_worker(ResBlock k, const ResTab &tab, float 
       tile(ResPar::kP + 8 * t, res_p_row(W * tab.P[t / W] + t % W, i), a0.pred_unscale, a0.b_pred);
     for (int t = 0; t < W * k.nJ; ++t) {
       const int row = 16 * (W * tab.J[t / W] + t % W) + i;
+      if (SPLIT && k.fold && t == 0) {  // (one column, of weights that are not split)
+        if (i == 0) par[4 * (ResPar::kJ + ResPar::kBias)] = a0.b_out[a0.V + tab.J[0] - a0.V / 16];
+        continue;
+      }
       tile(ResPar::kJ + 8 * t, row, a0.out_unscale, a0.b_out);
       if (k.fold && t == 0) par[4 * (ResPar::kJ + ResPar::kScale) + i] = 1.f;  // (folded from weights that are not split)
     }
@@ -1392,21 +1404,17 @@ __device__ __forceinline__ void res_worker(ResBlock k, const ResTab &tab, float 
 #pragma unroll
       for (int t = 0; t < NJ; ++t) {
         wj.t[t] = ResW16{};
-        if (t < k.nJ) wj.t[t] = res_split_load(a0.WJ + ((size_t)tab.J[t] * kResWaves + k.wave) * kResQuads * 64, l0);
+        if (t < k.nJ && !(t == 0 && k.fold)) wj.t[t] = res_split_load(a0.WJ + ((size_t)tab.J[t] * kResWaves + k.wave) * kResQuads * 64, l0);
       }
-      if (FULL && k.fold) {  // (words 0 to 19 of the lane, see res_raw)
+      if (FULL && k.fold) {  // (words 0 to 19 of the lane, see res_raw: weights of part i of x at 2 i and 2 i + 1)
         uint32_t v[2 * kResMaxRounds];
 #pragma unroll
         for (int i = 0; i < kResMaxRounds; ++i) {
-          const uint32_t *ws = reinterpret_cast<const uint32_t *>(a0.WJs) + (size_t)k.wave * kResMaxRounds * 128;
-          if (k.fold == 2) {  // blank's weights at the k of the lane's parts (k of a round: see k_pack_fold)
-            const int round = i < 8 ? 4 * (i >> 2) + 2 * (l0.kq >> 1) + ((i & 3) >> 1) : 8 + (l0.kq & 1), half = i < 8 ? l0.kq & 1 : l0.kq >> 1;
-            v[2 * i] = ws[round * 128 + (i & 1) * 32 + half];
-            v[2 * i + 1] = ws[round * 128 + ((i & 1) + 2) * 32 + half];
-          } else {
-            v[2 * i] = ws[(i * 64 + l0.lane) * 2];
-            v[2 * i + 1] = ws[(i * 64 + l0.lane) * 2 + 1];
-          }
+          const uint32_t *ws = reinterpret_cast<const uint32_t *>(a0.WJs) + (size_t)k.wave * kResMaxRounds * 128 + 2 * (tab.J[0] - a0.V / 16);
+          // the column's weights at the k of the lane's parts (k of a round: see k_pack_fold)
+          const int round = i < 8 ? 4 * (i >> 2) + 2 * (l0.kq >> 1) + ((i & 3) >> 1) : 8 + (l0.kq & 1), half = i < 8 ? l0.kq & 1 : l0.kq >> 1;
+          v[2 * i] = ws[round * 128 + (i & 1) * 32 + half];
+          v[2 * i + 1] = ws[round * 128 + ((i & 1) + 2) * 32 + half];
         }
         wj.t[0] = ResW16{{{v[0], v[1], v[2], v[3]}, {v[8], v[9], v[10], v[11]}}, {{v[4], v[5], v[6], v[7]}, {v[12], v[13], v[14], v[15]}}, {v[16], v[17]}, {v[18], v[19]}};
       }
@@ -1465,7 +1473,7 @@ __device__ __forceinline__ void res_worker(ResBlock k, const ResTab &tab, float 
     // (under the selection: ahead of the projection the waits for the activations included these stores)
     if (step > 0) {
       const ResArgs &a = res_args();
-      res_clear_pz<BF16>(a, k, res_addr(a, k.g), step - 1);
+      res_clear_pz<FORM>(a, k, res_addr(a, k.g), step - 1);
     }
     // ---- R
     if constexpr (!ST) if (k.nR > 0) {

@@ -29,6 +29,7 @@ struct Resident {
   int *ctl = nullptr;
   ResTab *tab = nullptr;          // who owns what in a group, as uploaded for the last launch:
   int tab_blocks = 0, tab_sel = 0;
+  bool tab_columns = false;
   int n_groups = 0, last_stall_step = -1;  // of the last launch
   int *h_abort = nullptr, *h_abort_dev = nullptr;  // pinned
   std::vector<void *> allocs;

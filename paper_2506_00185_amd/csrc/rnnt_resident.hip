@@ -103,8 +103,13 @@ constexpr int kResStallPolls = 4096;  // a test's wait for data that does not co
 
 constexpr size_t kResOwnLds = 256;  // the kernel's own words beside the dynamic ones, at most
 
+// kernels whose loops have known lengths (FULL)
+bool whole_width(const rnnt_config_t &c) {
+  return c.H == 8 * 8 * kResMaxRounds && (c.pred != RNNT_PRED_LSTM || c.P == 8 * 8 * kResMaxRounds);
+}
+
 struct Plan {
-  bool ok = false;
+  bool ok = false, columns = false;
   int n_groups = 0, stride = 0, n_blocks = 0, nu = 0, n_sel = 0, upc = 0, NT = 0, red_blocks = 0;
   size_t lds = 0;
   std::vector<ResTab> tab;
@@ -113,11 +118,13 @@ struct Plan {
 // Who owns what among the n_blocks blocks of a group that do not select.  Every tile goes to the block that has least of
 // its kind (the phases of a step follow each other, so what counts is the largest number per block and kind), then least of
 // all.  False: they do not fit.
-bool assign_tiles(const rnnt_config_t &c, int n_blocks, std::vector<ResTab> &tab) {
+// columns: the blank and duration columns are dealt one by one (see res_fold_one).
+bool assign_tiles(const rnnt_config_t &c, int n_blocks, bool columns, std::vector<ResTab> &tab) {
   const bool bf = c.prec == RNNT_BF16_JOINT;
   const int N = c.V + 1 + c.n_durations;
   const bool lstm = c.pred == RNNT_PRED_LSTM;
-  const int nR = lstm ? 4 * c.P / 16 : 0, nJ = bf ? (N + 31) / 32 : (N + 15) / 16, nP = !lstm ? 0 : bf ? c.H / 32 : c.H / 16;
+  const int nR = lstm ? 4 * c.P / 16 : 0, nJ = columns ? c.V / 16 + N - c.V : bf ? (N + 31) / 32 : (N + 15) / 16;
+  const int nP = !lstm ? 0 : bf ? c.H / 32 : c.H / 16;
   const int reg_j = bf ? kResRegJ<true> : kResRegJ<false>, max_p = bf ? 1 : kResMaxP;
   tab.assign(n_blocks, ResTab{});
   auto total = [&](const ResTab &t) { return t.nR + t.nJ + t.nP; };
@@ -136,12 +143,13 @@ bool assign_tiles(const rnnt_config_t &c, int n_blocks, std::vector<ResTab> &tab
     if (!put(t, [](const ResTab &x) { return (int)x.nR; }, [](const ResTab &x) { return x.nR < kResMaxR; },
              [](ResTab &x, int tile) { x.R[x.nR++] = (int16_t)tile; }))
       return false;
-  // (the tile with the blank column is dealt first, as its block reads it from its first place where it is folded, and counts
-  // as two: it has two chains of sums then)
-  const int blank_tile = c.V / (bf ? 32 : 16);
+  // (the tile with the blank column, or the columns, are dealt first, as a block reads them from its first place where they are
+  // folded, and count as two tiles)
+  const int blank_tile = c.V / (bf ? 32 : 16), n_first = columns ? N - c.V : 1;
+  auto special = [&](const ResTab &x) { return x.nJ > 0 && x.J[0] >= blank_tile && x.J[0] < blank_tile + n_first; };
   for (int i = 0; i < nJ; ++i) {
-    const int t = i == 0 ? blank_tile : i <= blank_tile ? i - 1 : i;
-    if (!put(t, [&](const ResTab &x) { return x.nJ + (x.nJ > 0 && x.J[0] == blank_tile); }, [&](const ResTab &x) { return x.nJ < reg_j + 1; },
+    const int t = i < n_first ? blank_tile + i : i - n_first < blank_tile ? i - n_first : i;
+    if (!put(t, [&](const ResTab &x) { return x.nJ + special(x); }, [&](const ResTab &x) { return i < n_first ? x.nJ == 0 : x.nJ < reg_j + 1; },
              [](ResTab &x, int tile) { x.J[x.nJ++] = (int16_t)tile; }))
       return false;
   }
@@ -196,8 +204,9 @@ Plan make_plan(const Resident &r, const rnnt_config_t &c, int B, int K, bool has
   p.upc = (p.nu + most_sel - 1) / most_sel;
   if (p.upc > kResMaxSel || p.upc * K * K > 512 || p.upc * K > kResMaxHyps) return p;
   p.n_sel = (p.nu + p.upc - 1) / p.upc;
-  if (!assign_tiles(c, p.n_blocks - p.n_sel, p.tab)) return p;
   const bool bf = c.prec == RNNT_BF16_JOINT;
+  p.columns = fold && r.form == kResSplit && whole_width(c);
+  if (!assign_tiles(c, p.n_blocks - p.n_sel, p.columns, p.tab)) return p;
   int lds_tiles = 0;
   for (const ResTab &t : p.tab) lds_tiles = std::max(lds_tiles, t.nP + std::max(0, t.nJ - (bf ? kResRegJ<true> : kResRegJ<false>)));
   auto worker_lds = [&](int red_blocks) {
@@ -224,7 +233,7 @@ ResKernel pick_form(int form, int K, bool plain) {
 }
 template <bool ST>
 ResKernel pick_kernel(const rnnt_config_t &c, int form, int K, bool plain) {
-  return c.H == 640 && (ST || c.P == 640) ? pick_form<true, ST>(form, K, plain) : pick_form<false, ST>(form, K, plain);
+  return whole_width(c) ? pick_form<true, ST>(form, K, plain) : pick_form<false, ST>(form, K, plain);
 }
 
 }  // namespace
@@ -349,13 +358,14 @@ hipError_t resident_launch(Resident &r, const rnnt_config_t &c, const ResidentBa
   a.start_limit = short_spin ? 100 : 5000000;  // 50 ms
   *reinterpret_cast<volatile int *>(r.h_abort) = 0;
   hipError_t e = hipSuccess;
-  if (r.tab_blocks != p.n_blocks || r.tab_sel != p.n_sel) {
+  if (r.tab_blocks != p.n_blocks || r.tab_sel != p.n_sel || r.tab_columns != p.columns) {
     // (pageable memory: the call returns when it has been read; the last launch that read the table is over, as its
     // decode waited for it)
     e = hipMemcpyAsync(r.tab, p.tab.data(), sizeof(ResTab) * p.tab.size(), hipMemcpyHostToDevice, s);
     if (e != hipSuccess) return e;
     r.tab_blocks = p.n_blocks;
     r.tab_sel = p.n_sel;
+    r.tab_columns = p.columns;
   }
   hipLaunchKernelGGL(k_resident_init, dim3(512), dim3(256), 0, s, a);
   const bool plain = c.n_durations == 0 && !b.has_lm && b.algo == RNNT_ALSD;
