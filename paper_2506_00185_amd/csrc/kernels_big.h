@@ -563,6 +563,274 @@ __global__ __launch_bounds__(64 * kRowWaves) void k_row_select(RowSelectArgs a) 
   }
 }
 
+// The selection and the next activations of ONE utterance in one block from the chunk statistics of the contraction, for keys without an LM
+// term; wave w takes hypothesis w.  Like res_select: every wave turns the largest logits of sets of its row's chunks into the scores that they
+// would have as candidates; the K-th largest of all rows' is a lower bound of the utterance's K-th largest, and only the chunks that reach
+// it, few more than K in all, are read (32 logits each).  One wave ranks what they hold and expands it; the others go on to the
+// activations while it merges and writes the tree.  What bounds it is latency: three trips to memory (statistics and state, chunks, table
+// rows) and the barriers between.  (K best of every row first, from the K-th largest of the row's own maxima, then the selection from K lists:
+// k_utt_select; stateless batch 128, beam 10, V = 8192: 27.3 -> 24.3 ms per decode.)
+struct UttFew {
+  double score[kMaxBeam], base[kMaxBeam], lse[kMaxBeam], margin[kMaxBeam], blank[kMaxBeam];
+  int4 state[kMaxBeam];
+  uint32_t hash[kMaxBeam];
+  int kind[kMaxBeam], adv[kMaxBeam];
+  int ctx[kMaxBeam][kCtxMax], n_ctx[kMaxBeam][kCtxMax];
+  float set[64], row_set[kMaxBeam][32], row_bound[kMaxBeam];
+  double top_key[kTop + 8];
+  int top_flat[kTop + 8], top_n;
+  uint16_t chunk[kMaxBeam][256];
+  double n_score[kMaxBeam];
+  int n_t[kMaxBeam], n_sym[kMaxBeam], n_len[kMaxBeam], n_last[kMaxBeam], n_live[kMaxBeam];
+  uint32_t n_hash[kMaxBeam];
+  int n_parent[kMaxBeam], n_code[kMaxBeam];
+};
+// KC: beams up to 4, 8, 12 or 16; PLAIN: see select_one_list
+template <int KC, int PLAIN>
+__global__ __launch_bounds__(64 * kMaxBeam) void k_utt_few(RowSelectArgs a) {
+  __shared__ UttFew s;
+  const SelectArgs &sel = a.sel;
+  const int K = a.K, V = a.V, b = blockIdx.x, m0 = b * K;
+  const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);  // wave < K
+  const int m = m0 + wave, ND = PLAIN ? 0 : a.ND, nz = 1 + ND;
+  const bool aes = PLAIN ? PLAIN == 2 : sel.algo == 1, use_gamma = PLAIN == 0 && aes && sel.gamma < INFINITY;
+  const float *zrow = a.Z + (size_t)m * a.Npad;
+  const int n_stat = a.Npad >> 5;  // <= 256: four chunks per lane
+  const float kLog2e = 1.4426950408889634f;
+  // ---- every load of the prologue before anything waits for one of them
+  const int over = *reinterpret_cast<const volatile int *>(a.done) | a.finished[b];
+  const int S = *sel.step_base + sel.step_off, T_b = sel.lengths[b];
+  float cm[4], cs[4];
+#pragma unroll
+  for (int q = 0; q < 4; ++q) {
+    const int c = lane + 64 * q;
+    const uint64_t st = a.cstat[(size_t)m * n_stat + (c < n_stat ? c : 0)];
+    cm[q] = c < n_stat ? __uint_as_float((uint32_t)st) : -INFINITY;
+    cs[q] = c < n_stat ? __uint_as_float((uint32_t)(st >> 32)) : 0.f;
+  }
+  double my_score = -INFINITY;
+  int4 my_state = make_int4(0, 0, 0, -1);
+  uint32_t my_hash = 0;
+  if (lane < K) {
+    my_score = sel.score[m0 + lane];
+    my_state = make_int4(sel.t[m0 + lane], sel.sym[m0 + lane], sel.len[m0 + lane], sel.last[m0 + lane]);
+    my_hash = sel.hash[m0 + lane];
+  }
+  int my_ctx = -1;
+  if (sel.use_ctx && lane < kCtxMax) my_ctx = sel.ctx[m * kCtxMax + lane];
+  // blank and duration logits from the bf16 activations: z[V + d] = Wspec[d] . a_m + bias; a lane takes 8 k at a time
+  float dl[8], zb;
+  {
+    float acc[9];
+#pragma unroll
+    for (int d = 0; d < 9; ++d) acc[d] = 0.f;
+    for (int g = lane; g < (a.H >> 3); g += 64) {
+      const uint4 u = *reinterpret_cast<const uint4 *>(a.Ab + ((size_t)g * a.Mp + m) * 8);
+      const uint32_t w[4] = {u.x, u.y, u.z, u.w};
+      float x[8];
+#pragma unroll
+      for (int i = 0; i < 4; ++i) {
+        x[2 * i] = __uint_as_float(w[i] << 16);
+        x[2 * i + 1] = __uint_as_float(w[i] & 0xffff0000u);
+      }
+#pragma unroll
+      for (int d = 0; d < 9; ++d)
+        if (d < nz) {
+          const float4 p = *reinterpret_cast<const float4 *>(a.Wspec + (size_t)d * a.H + 8 * g);
+          const float4 q = *reinterpret_cast<const float4 *>(a.Wspec + (size_t)d * a.H + 8 * g + 4);
+          acc[d] += (x[0] * p.x + x[1] * p.y) + (x[2] * p.z + x[3] * p.w) + (x[4] * q.x + x[5] * q.y) +
+                    (x[6] * q.z + x[7] * q.w);
+        }
+    }
+    zb = wave_sum(acc[0]) + a.bias_spec[0];
+#pragma unroll
+    for (int d = 0; d < 8; ++d) dl[d] = d < ND ? wave_sum(acc[d + 1]) + a.bias_spec[d + 1 < nz ? d + 1 : 0] : 0.f;
+  }
+  if (over) return;
+  // ---- soft-max statistics of the row
+  const float lmx = fmaxf(fmaxf(cm[0], cm[1]), fmaxf(cm[2], cm[3]));
+  const float mx = wave_max(lmx);
+  float sum = 0.f;
+#pragma unroll
+  for (int q = 0; q < 4; ++q) sum += cm[q] > -INFINITY ? cs[q] * exp2f((cm[q] - mx) * kLog2e) : 0.f;
+  sum = wave_sum(sum);
+  const float lse_nb = mx + __logf(mx > -INFINITY ? sum : 0.f);
+  const float hi = fmaxf(lse_nb, zb), lo = fminf(lse_nb, zb);
+  const float lse_all = hi + __logf(1.f + __expf(lo - hi));
+  const double logp_b = (double)zb - (double)lse_all;
+  double x_tok = 0.0, x_blank = 0.0;
+  int adv = 1 << 16;
+  if (ND > 0) adv = best_durations(dl, ND, sel.dur_bytes, x_tok, x_blank);
+  // ---- what the hypotheses do (AES++: only those in the earliest frame are expanded)
+  int my_kind = hyp_kind(my_score > -INFINITY, my_state, T_b, sel.max_sym);
+  if (aes) {
+    const int first = __builtin_amdgcn_readlane(group_min_i<16>(my_kind >= 2 ? my_state.x : 0x7fffffff), 0);
+    if (my_kind >= 2 && my_state.x != first) my_kind = 1;
+  }
+  const int kind = __builtin_amdgcn_readlane(my_kind, wave);
+  const double sc = readlane_d(my_score, wave);
+  // ---- candidates: a token's score is (sc + logit) + base
+  const double base = x_tok - (double)lse_all;
+  const double thr = use_gamma ? (double)fmaxf(mx, zb) - (double)lse_all - (double)sel.gamma : -INFINITY;
+  auto token = [&](float z, double score, double tok_base, double lse, double margin) {
+    const double key = score + (double)z + tok_base;
+    return z >= kLeastKey && !(use_gamma && (double)z - lse < margin) ? key : -INFINITY;
+  };
+  double blank = -INFINITY;
+  if (kind >= 2) blank = sc + (use_gamma && logp_b < thr && kind == 2 ? -INFINITY : logp_b) + x_blank;
+  else if (kind == 1) blank = sc;  // a waiting or finished hypothesis stays as it is
+  if (wave == 0 && lane < K) {
+    s.score[lane] = my_score;
+    s.state[lane] = my_state;
+    s.hash[lane] = my_hash;
+    s.kind[lane] = my_kind;
+  }
+  if (lane == 0) {
+    s.base[wave] = base;
+    s.blank[wave] = blank;
+    s.adv[wave] = adv;
+    if (use_gamma) {
+      s.lse[wave] = (double)lse_all;
+      s.margin[wave] = thr;
+    }
+  }
+  if (lane < kCtxMax) s.ctx[wave][lane] = my_ctx;
+  if (tid == 0) s.top_n = 0;
+  // ---- the bound: sets of LANES lanes' chunks
+  constexpr int LANES = KC == 4 ? 4 : KC == 8 ? 8 : 16, ROW = 64 / LANES;
+  double best = kind == 2 ? token(lmx, sc, base, (double)lse_all, thr) : -INFINITY;
+  if (lane == 63) best = blank > best || !(best > -INFINITY) ? blank : best;
+  const float mine = score_floor(best), group = group_max<LANES>(mine);
+  if ((lane & (LANES - 1)) == 0) s.set[wave * ROW + lane / LANES] = group;
+  if (wave == 0 && lane >= K * ROW) s.set[lane] = -INFINITY;
+  // (and where few hypotheses are expanded, at first and while the others of AES++ wait, the K-th largest of a row's own sets, the largest of
+  // the rows': the sets of all rows may be fewer than K, or say little of the one row that has candidates)
+  constexpr int OWN = KC <= 8 ? 16 : 32;
+  float own = fmaxf(mine, dpp_f<kDppXor1>(mine));
+  if constexpr (OWN == 16) own = fmaxf(own, dpp_f<kDppXor2>(own));
+  if ((lane & (64 / OWN - 1)) == 0) s.row_set[wave][lane / (64 / OWN)] = own;
+  wave_sync();
+  const float row_bound = kth_largest<OWN>(s.row_set[wave], own, K);
+  if (lane == 0) s.row_bound[wave] = row_bound;
+  __syncthreads();
+  const float rows = lane < K ? s.row_bound[lane] : -INFINITY;
+  const float bound = fmaxf(kth_largest<64>(s.set, s.set[lane], K), wave_max(rows));
+  const double tau = (double)bound;
+  // ---- the candidates that reach it
+  auto append = [&](bool in, double key, int flat) {
+    if (in) {
+      const int pos = atomicAdd(&s.top_n, 1);
+      if (pos < kTop) {
+        s.top_key[pos] = key;
+        s.top_flat[pos] = flat;
+      }
+    }
+  };
+  if (kind == 2) {
+    const float reach = key_reach(tau, sc, base, 0.0);
+    int nq = 0;
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+      const bool in = cm[q] >= reach;
+      const unsigned long long mask = __ballot(in);
+      const int pos = nq + __builtin_amdgcn_mbcnt_hi((uint32_t)(mask >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)mask, 0));
+      if (in) s.chunk[wave][pos] = (uint16_t)(lane + 64 * q);
+      nq += __popcll(mask);
+    }
+    wave_sync();
+    for (int i = lane >> 3; i < nq; i += 8) {  // eight lanes read the 128 bytes of a chunk
+      const int n = 32 * (int)s.chunk[wave][i] + 4 * (lane & 7);
+      const floatx4 z = *reinterpret_cast<const floatx4 *>(zrow + n);
+#pragma unroll
+      for (int e = 0; e < 4; ++e) {
+        const double key = token(z[e], sc, base, (double)lse_all, thr);
+        append(key > -INFINITY && key >= tau, key, wave << kFlatShift | (n + e));
+      }
+    }
+  }
+  append(lane == 63 && blank > -INFINITY && blank >= tau, blank, wave << kFlatShift | V);
+  __syncthreads();
+  // ---- rank, expansion
+  NewSlot x;
+  bool last_step = false;
+  if (wave == 0) {
+    int total = s.top_n;
+    if (total > kTop) {
+      auto collect = [&](auto in, int most) {
+        auto put = [&](bool ok, double key, int flat) {
+          const unsigned long long mask = __ballot(ok);
+          const int pos = total + __builtin_amdgcn_mbcnt_hi((uint32_t)(mask >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)mask, 0));
+          if (ok && pos < kTop) {
+            s.top_key[pos] = key;
+            s.top_flat[pos] = flat;
+          }
+          total += __popcll(mask);
+        };
+        for (int h = 0; h < K && total < most; ++h) {
+          if (__builtin_amdgcn_readfirstlane(s.kind[h]) == 2)
+            for (int n0 = 0; n0 < V && total < most; n0 += 64) {
+              const int n = n0 + lane;
+              const float z = a.Z[(size_t)(m0 + h) * a.Npad + min(n, V - 1)];
+              const double key = token(z, s.score[h], s.base[h], use_gamma ? s.lse[h] : 0.0, use_gamma ? s.margin[h] : 0.0);
+              put(n < V && in(key), key, h << kFlatShift | n);
+            }
+          if (total >= most) break;
+          put(lane == 0 && in(s.blank[h]), s.blank[h], h << kFlatShift | V);
+        }
+      };
+      narrow_top(s.top_key, K, tau, total, collect);
+    }
+    x = rank_and_expand<true, PLAIN != 0>(s, total, K, V, T_b);
+    last_step = __ballot(x.alive && x.state.x < T_b) == 0ull || S + 1 >= T_b * (sel.max_sym + 1);
+    const int n_kept = __popcll(__ballot(x.kept));
+    put_new_slots(s, x, n_kept, K);
+    if (x.kept)
+#pragma unroll
+      for (int i = 0; i < kCtxMax; ++i) s.n_ctx[x.rank][i] = x.appended < 0 ? s.ctx[x.parent][i] : i == 0 ? x.appended : s.ctx[x.parent][i > 0 ? i - 1 : 0];
+    if (n_kept < K && lane >= n_kept && lane < K)
+#pragma unroll
+      for (int i = 0; i < kCtxMax; ++i) s.n_ctx[lane][i] = -1;
+  }
+  __syncthreads();
+  // ---- activations of the new hypotheses by the other waves (two items per thread and round, so that the loads of both are in flight
+  // together), recombination, state and tree by the first
+  if (wave > 0 || K == 1) {
+    const int H8 = a.pre.H >> 3, nthr = K == 1 ? 64 : 64 * (K - 1);
+    for (int it = K == 1 ? tid : tid - 64; it < K * H8; it += 2 * nthr) {
+      const int it2 = it + nthr;
+      const bool two = it2 < K * H8;
+      const int j = it / H8, o8 = it % H8, j2 = two ? it2 / H8 : j, o82 = two ? it2 % H8 : o8;
+      int tt = s.n_t[j], tt2 = s.n_t[j2];
+      tt = tt < T_b ? tt : T_b - 1;
+      tt = tt < 0 ? 0 : tt;
+      tt2 = tt2 < T_b ? tt2 : T_b - 1;
+      tt2 = tt2 < 0 ? 0 : tt2;
+      stateless_pre_big_pair(a.pre, m0 + j, tt, s.n_ctx[j], o8, m0 + j2, tt2, s.n_ctx[j2], o82, b, two);
+    }
+  }
+  if (wave == 0 && lane < K) {
+    const int j = lane, at = m0 + j;
+    double score;
+    bool live;
+    const int merged = recombine<KC>(s, K, j, score, live), parent = s.n_parent[j], code = s.n_code[j];
+    // (written through: see store_through)
+    store_through(sel.score + at, score);
+    store_through(sel.t + at, s.n_t[j]);
+    store_through(sel.sym + at, s.n_sym[j]);
+    store_through(sel.len + at, s.n_len[j]);
+    store_through(sel.last + at, s.n_last[j]);
+    store_through(sel.hash + at, s.n_hash[j]);
+    if (sel.use_ctx) {
+#pragma unroll
+      for (int i = 0; i < kCtxMax; ++i) store_through(sel.ctx + at * kCtxMax + i, s.n_ctx[j][i]);
+    }
+    store_through(sel.src_row + at, parent >= 0 ? m0 + parent : at);
+    store_through(sel.tok + at, code >= 0 ? code : -1);
+    write_tree(sel, b, S, K, j, parent, code, merged);
+    if (j == 0 && last_step) end_utterance(sel, b, S);
+  }
+}
+
 // The row scan, the selection and the next activations of ONE utterance in one block: wave w takes hypothesis w of
 // the utterance (K <= 16 waves).  For keys without an LM term, from the chunk statistics of the contraction.  Nothing
 // is handed from block to block: the K lists, the soft-max statistics and the blank / duration logits stay in LDS, a
@@ -572,8 +840,9 @@ __global__ __launch_bounds__(64 * kRowWaves) void k_row_select(RowSelectArgs a) 
 // it collected and ranked by counting).
 constexpr int kUttSurvivorCap = 128;
 
-// KC, PLAIN: see select_one_list
-template <int KC, int PLAIN>
+// (Where k_utt_few does not do: with the prefix search, which wants each row's K best, and with early pruning.)
+// KC: see select_one_list
+template <int KC>
 __global__ __launch_bounds__(64 * kMaxBeam) void k_utt_select(RowSelectArgs a) {
   __shared__ SelectScratch scratch;
   __shared__ uint64_t l_cand[kMaxBeam * kMaxBeam];
@@ -661,7 +930,7 @@ __global__ __launch_bounds__(64 * kMaxBeam) void k_utt_select(RowSelectArgs a) {
   }
   // blank and duration logits from the bf16 activations: z[V + d] = Wspec[d] . a_m + bias; a lane takes 8 k at a time
   {
-    const int nz = PLAIN ? 1 : 1 + a.ND;  // (the plain forms: no durations)
+    const int nz = 1 + a.ND;
     float acc[9];
 #pragma unroll
     for (int d = 0; d < 9; ++d) acc[d] = 0.f;
@@ -691,7 +960,7 @@ __global__ __launch_bounds__(64 * kMaxBeam) void k_utt_select(RowSelectArgs a) {
       }
   }
   __syncthreads();
-  if (wave == 0) select_one_list<KC, PLAIN>(a.sel, b, scratch, CandView{l_cand, l_max, l_sum, l_zs, b * K});
+  if (wave == 0) select_one_list<KC, 0>(a.sel, b, scratch, CandView{l_cand, l_max, l_sum, l_zs, b * K});
   __syncthreads();
   // activations of the utterance's new hypotheses, from the selection's scratch (frame, token history)
   const int T_b = a.pre.lengths[b];

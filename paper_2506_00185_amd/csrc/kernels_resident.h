@@ -1563,7 +1563,6 @@ __device__ __forceinline__ void res_worker(ResBlock k, const ResTab &tab, float 
 constexpr int kResMaxHyps = 24;  // hypotheses of a selecting block
 // floats of a row of keys in LDS (those behind the vocabulary are -inf)
 __host__ __device__ inline int res_row_floats(int V) { return V <= 128 ? 128 : V <= 512 ? 512 : kResMaxV; }
-constexpr int kResTop = 64;      // candidates that are ranked
 // An utterance's hypotheses (up to ctx: kept from step to step) and what a step of its selection needs.
 // a hypothesis' tokens as candidates: (score + key) + base + lm (see res_select)
 struct __align__(16) ResRow {
@@ -1580,8 +1579,8 @@ struct ResUtt {
   int adv[kMaxBeam];               // frames that a token (low half) and that blank advances
   float set[64];
   int chunk[16 * 32 + 16];         // hypothesis * 32 + chunk of those that reach the bound
-  double top_key[kResTop + 8], top_val[kResTop];
-  int top_flat[kResTop + 8];
+  double top_key[kTop + 8], top_val[kTop];
+  int top_flat[kTop + 8];
   // new slots (see recombine)
   double n_score[kMaxBeam];
   int n_t[kMaxBeam], n_sym[kMaxBeam], n_len[kMaxBeam], n_last[kMaxBeam], n_live[kMaxBeam];
@@ -1803,9 +1802,6 @@ __device__ __forceinline__ void res_put_word(bool local, uint64_t *p, uint64_t w
     else store_agent(p + i * kResWordPlace, w);
   }
 }
-__device__ __forceinline__ int res_kind(bool live, int4 state, int T_b, int max_sym) {
-  return !live ? 0 : state.x >= T_b ? 1 : state.y >= max_sym ? 3 : 2;
-}
 // The Beam best of an utterance's candidates, expansion, words, recombination and tree, by one wave.  rows: the utterance's rows of
 // keys in LDS (early pruning: of LM scores; the keys are the logits where they came from).  h0: its first hypothesis in the block, u
 // in the group, b in the batch.  Returns whether its last step is done.
@@ -1814,7 +1810,6 @@ __device__ __forceinline__ bool res_select(const ResBlock &k, int step, int u, i
   const ResArgs &ra = res_args();
   const SelectArgs &a = ra.sel;
   const int K = ra.K, V = ra.V, nz = ra.N - V, stride = res_row_floats(V), lane = threadIdx.x & 63;
-  constexpr float kLeast = -3.4028235e38f;  // (no token at -inf is a candidate)
   const int ND = PLAIN ? 0 : nz - 1;
   const bool has_lm = PLAIN == 0 && ra.has_lm, early = PLAIN == 0 && a.lm_early, late_lm = has_lm && !early;
   const bool aes = PLAIN == 0 && a.algo == 1, use_gamma = aes && a.gamma < INFINITY;
@@ -1863,45 +1858,13 @@ __device__ __forceinline__ bool res_select(const ResBlock &k, int step, int u, i
   const float hi = fmaxf(lse_nb, zb), lo = fminf(lse_nb, zb);
   const float lse_all = hi + __logf(1.f + __expf(lo - hi));
   const double logp_b = (double)zb - (double)lse_all;
-  // ---- durations: the most likely one (the first of equal ones), and the most likely one that advances
   double x_tok = 0.0, x_blank = 0.0;
   int adv = 1 << 16;
   if (ND > 0) {
     float dl[8];
 #pragma unroll
     for (int d = 0; d < 8; ++d) dl[d] = zs[1 + (d < ND ? d : 0)];
-    float dmx = -INFINITY, sm = 0.f;
-#pragma unroll
-    for (int d = 0; d < 8; ++d)
-      if (d < ND) dmx = fmaxf(dmx, dl[d]);
-#pragma unroll
-    for (int d = 0; d < 8; ++d)
-      if (d < ND) sm += __expf(dl[d] - dmx);
-    const float l = dmx + __logf(sm);
-#pragma unroll
-    for (int d = 0; d < 8; ++d)
-      if (d < ND) dl[d] -= l;
-    bool have = false, have_b = false;
-    float best_v = 0.f, best_bv = 0.f;
-    int best_adv = 0, best_badv = 1;
-#pragma unroll
-    for (int d = 0; d < 8; ++d)
-      if (d < ND) {
-        const int du = (int)((a.dur_bytes >> (8 * d)) & 0xff);
-        if (!have || dl[d] > best_v) {
-          have = true;
-          best_v = dl[d];
-          best_adv = du;
-        }
-        if (du >= 1 && (!have_b || dl[d] > best_bv)) {
-          have_b = true;
-          best_bv = dl[d];
-          best_badv = du;
-        }
-      }
-    x_tok = (double)best_v;
-    x_blank = (double)best_bv;
-    adv = best_adv | best_badv << 16;
+    adv = best_durations(dl, ND, a.dur_bytes, x_tok, x_blank);
   }
   // ---- candidates.  A token's: what it is ranked by (key) and its score (val), which differ under early pruning and with the prefix
   // search's credit.  Eq. (4): tokens get lambda (ln(1 - p_blank) + lm), blank (1 + lambda) ln p_blank; Eq. (3): tokens lambda lm, blank
@@ -1913,7 +1876,7 @@ __device__ __forceinline__ bool res_select(const ResBlock &k, int step, int u, i
   auto token_key = [&](float z, double score, double base, double lm) {
     double key = score + (double)z + base;
     if (PLAIN == 0) key = key + lm;
-    return z >= kLeast ? key : -INFINITY;
+    return z >= kLeastKey ? key : -INFINITY;
   };
   double bkey = -INFINITY, bval = -INFINITY;
   if (kind >= 2) {
@@ -1977,8 +1940,7 @@ __device__ __forceinline__ bool res_select(const ResBlock &k, int step, int u, i
   if (use_gamma && (double)kmx - (double)lse_all < thr) best = -INFINITY;
   if (prefix) best = best + delta;
   if (e == LPR - 1) best = bkey > best || !(best > -INFINITY) ? bkey : best;
-  float fl = (float)best;
-  fl = fl > -INFINITY ? fl - (fabsf(fl) * 2.4e-7f + 1e-30f) : -INFINITY;  // (no number: none)
+  float fl = score_floor(best);
   constexpr int SETS = KC == 4 ? 16 : 64;
   if constexpr (SETS == 16) {
     float q[1] = {fl};
@@ -1989,36 +1951,28 @@ __device__ __forceinline__ bool res_select(const ResBlock &k, int step, int u, i
     s.set[lane] = fl;
   }
   wave_sync();
-  int ge = 0;  // sets not below mine
-  {
-    int n[4] = {0, 0, 0, 0};
-#pragma unroll
-    for (int i = 0; i < SETS; i += 4) {
-      const float4 v = *reinterpret_cast<const float4 *>(s.set + i);
-      n[0] += (int)(v.x >= fl);
-      n[1] += (int)(v.y >= fl);
-      n[2] += (int)(v.z >= fl);
-      n[3] += (int)(v.w >= fl);
+  double tau = (double)kth_largest<SETS>(s.set, fl, K);
+  // Where few hypotheses are expanded (at first, and while the others of AES++ wait) these sets may be fewer than K, or say little of the
+  // one row that has candidates: there the K-th largest of a row's chunks as well, the largest of the rows'.
+  if constexpr (KC > 4) {
+    const int open = __popcll(__ballot(kind == 2 && e == 0));
+    if (open * LPR < K + 4) {
+      for (unsigned long long todo = __ballot(kind == 2 && e == 0); todo; todo &= todo - 1ull) {
+        const int first = __builtin_ctzll(todo), h = first / LPR, i = lane & 31;
+        const float z = late_lm ? L.kmax[h0 + h][i] : L.cst[h0 + h][i].x;
+        double x = token_key(i < n_cst ? z : -INFINITY, readlane_d(sc, first), readlane_d(tok_base, first), readlane_d(lm_key, first));
+        if (use_gamma && (double)z - readlane_d((double)lse_all, first) < readlane_d(thr, first)) x = -INFINITY;
+        if (prefix) x = x + readlane_d(delta, first);
+        const float f = score_floor(x);
+        wave_sync();
+        if (lane < 32) s.set[lane] = f;
+        wave_sync();
+        tau = fmax(tau, (double)kth_largest<32>(s.set, f, K));
+      }
     }
-    ge = (n[0] + n[1]) + (n[2] + n[3]);
-  }
-  double tau = -INFINITY;
-  {
-    const unsigned long long kth = __ballot(fl > -INFINITY && ge == K);
-    if (kth != 0ull) tau = (double)readlane_f(fl, __builtin_ctzll(kth));
-    else tau = (double)wave_max(fl > -INFINITY && ge >= K ? fl : -INFINITY);
   }
   // ---- the chunks that reach it, and of these and the blanks the candidates that do
-  // (chunks by the key that reaches it, in float32, with room for the rounding of all of this)
-  float reach;
-  {
-    double x = tau;
-    if (prefix) x = x - delta;
-    if (PLAIN == 0) x = x - lm_key;
-    reach = (float)((x - tok_base) - sc);
-    reach -= fabsf(reach) * 2.4e-7f + (fabsf((float)sc) + fabsf((float)tau)) * 1e-14f + 1e-6f;
-    reach = tau > -INFINITY ? fmaxf(reach, kLeast) : kLeast;
-  }
+  const float reach = key_reach(tau, sc, tok_base, PLAIN ? 0.0 : prefix ? delta + lm_key : lm_key);
   int n_chunks = 0;
 #pragma unroll
   for (int q = 0; q < NC; ++q) {
@@ -2032,7 +1986,7 @@ __device__ __forceinline__ bool res_select(const ResBlock &k, int step, int u, i
   auto append = [&](bool in, double key, double val, int flat) {
     const unsigned long long mask = __ballot(in);
     const int pos = total + __builtin_amdgcn_mbcnt_hi((uint32_t)(mask >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)mask, 0));
-    if (in && pos < kResTop) {
+    if (in && pos < kTop) {
       s.top_key[pos] = key;
       if (PLAIN == 0) s.top_val[pos] = val;
       s.top_flat[pos] = flat;
@@ -2085,10 +2039,7 @@ __device__ __forceinline__ bool res_select(const ResBlock &k, int step, int u, i
       append(there && k1 > -INFINITY && k1 >= tau, k1, v1, h << kFlatShift | (n + 1));
     }
   }
-  if (total > kResTop) {
-    // Many reach it: fewer than K sets (a single hypothesis at first), or equal keys.  In the candidates' own order, until the K best
-    // are among the 64 that there is room for: the K-th largest of 64 is the next bound; one that cannot be raised is that of the K
-    // best itself, and of those equal to it the first ones count.
+  if (total > kTop) {
     if (e == LPR - 1 && r < K) {
       s.blank_key[r] = bkey;
       s.blank[r] = bval;
@@ -2109,124 +2060,29 @@ __device__ __forceinline__ bool res_select(const ResBlock &k, int step, int u, i
         append(lane == 0 && in(s.blank_key[h]), s.blank_key[h], s.blank[h], h << kFlatShift | V);
       }
     };
-    bool above = false;  // whether the bound itself is left out
-    for (;;) {
-      total = 0;
-      collect([&](double x) { return x > -INFINITY && (above ? x > tau : x >= tau); }, 0x7fffffff);
-      if (total <= kResTop && (!above || total >= K)) break;
-      if (total < K) {
-        collect([&](double x) { return x == tau; }, K);
-        total = min(total, kResTop);
-        break;
-      }
-      wave_sync();
-      const double x = s.top_key[lane];  // (64 or more of them, or, above the bound, K or more)
-      const int have = min(total, kResTop);
-      int n = 0;
-      for (int i = 0; i < have; ++i) n += (int)(s.top_key[i] >= x);
-      // the K-th largest: the largest that K are not below
-      double t = lane < have && n >= K ? x : -INFINITY;
-      int dummy = 0;
-      wave_best(t, dummy);
-      above = !(t > tau);
-      if (!above) tau = t;
-      wave_sync();
-    }
+    narrow_top(s.top_key, K, tau, total, collect);
   }
-  if (lane < 8) {  // (read in eights)
-    s.top_key[total + lane] = -INFINITY;
-    s.top_flat[total + lane] = 0x7fffffff;
-  }
-  wave_sync();
-  // ---- rank, by counting; on the way, what the candidate's hypothesis looks like
-  const bool mine = lane < total;
-  const int at = mine ? lane : 0;
-  const double key = s.top_key[at];
-  const int flat = s.top_flat[at];
-  const double val = PLAIN ? key : s.top_val[at];
-  const int par = (flat >> kFlatShift) & (kMaxBeam - 1), v = flat & ((1 << kFlatShift) - 1);
-  int4 st = s.state[par];
-  uint32_t hash = s.hash[par];
-  const int pkind = s.kind[par];
-  const int padv = PLAIN ? 1 << 16 : s.adv[par];
-  int ge2 = 0, gt = 0;
-  for (int c0 = 0; c0 < total; c0 += 8) {
-    double x[8];
-#pragma unroll
-    for (int q = 0; q < 8; ++q) x[q] = s.top_key[c0 + q];
-#pragma unroll
-    for (int q = 0; q < 8; ++q) {
-      ge2 += (int)(x[q] >= key);
-      gt += (int)(x[q] > key);
-    }
-  }
-  int rank = gt;
-  if (__ballot(mine && ge2 != gt + 1) != 0ull) {  // equal ones: the full order
-    rank = 0;
-    for (int c = 0; c < total; ++c) rank += comes_before_count(s.top_key[c], s.top_flat[c], key, flat);
-  }
-  // ---- expansion into the new slots: a lane whose candidate is kept makes slot `rank` of it
-  const bool kept = mine && rank < K;
-  int code = -2, appended = -1;
-  if (pkind >= 2) {
-    if (v == V) {
-      code = -1;
-      st.x += padv >> 16;
-      st.y = 0;
-    } else {
-      code = appended = v;
-      st.z += 1;
-      st.w = v;
-      hash = mod_mersenne31((uint64_t)hash * kHashBase + (uint64_t)(v + 1));
-      st.x += padv & 0xffff;
-      st.y = (padv & 0xffff) == 0 ? st.y + 1 : 0;
-    }
-  }
-  st.x = min(st.x, T_b);
+  // ---- rank and expansion: a lane whose candidate is kept makes slot `rank` of it
+  const NewSlot x = rank_and_expand<PLAIN != 0, PLAIN != 0>(s, total, K, V, T_b);
   // The words leave here, ahead of the recombination, which changes none of their fields: the slots of a class stand in the same frame
   // and one of them stays live, so whether any slot is open is known already.  The group's other blocks go on while this wave merges and
   // writes the tree (batch 32 / beam 4: 10.79 -> 10.50 ms per decode, one utterance 9.53 -> 9.33).
-  const bool alive = kept && (PLAIN || val > -INFINITY);  // (early pruning: the LM's score may be no number)
-  if (PLAIN == 0 && !alive) {
-    st = make_int4(0, 0, 0, -1);
-    hash = 0;
-    code = -3;
-    appended = -1;
-  }
-  const bool last_step = __ballot(alive && st.x < T_b) == 0ull || step + 1 >= T_b * (a.max_sym + 1);
-  const int slot0 = u * K, n_kept = __popcll(__ballot(kept));
+  const bool last_step = __ballot(x.alive && x.state.x < T_b) == 0ull || step + 1 >= T_b * (a.max_sym + 1);
+  const int slot0 = u * K, n_kept = __popcll(__ballot(x.kept));
   uint64_t *words = res_addr(ra, k.g).w(step) + slot0;
-  if (kept) res_put_word(k.local, words + rank, slot_word(step, last_step ? 1 : 0, slot0 + (alive ? par : rank), appended, st.x));
-  if (n_kept < K && lane >= n_kept && lane < K) {
-    res_put_word(k.local, words + lane, slot_word(step, last_step ? 1 : 0, slot0 + lane, -1, 0));
-    s.n_live[lane] = 0;
-    s.n_score[lane] = -INFINITY;
-    s.n_t[lane] = s.n_sym[lane] = s.n_len[lane] = 0;
-    s.n_last[lane] = s.n_parent[lane] = -1;
-    s.n_hash[lane] = 0;
-    s.n_code[lane] = -3;
-  }
+  if (x.kept) res_put_word(k.local, words + x.rank, slot_word(step, last_step ? 1 : 0, slot0 + (x.alive ? x.parent : x.rank), x.appended, x.state.x));
+  if (n_kept < K && lane >= n_kept && lane < K) res_put_word(k.local, words + lane, slot_word(step, last_step ? 1 : 0, slot0 + lane, -1, 0));
+  put_new_slots(s, x, n_kept, K);
   int ctx[kCtxMax];
-  if (kept) {
-    s.n_live[rank] = alive;
-    s.n_score[rank] = alive ? val : -INFINITY;
-    s.n_t[rank] = st.x;
-    s.n_sym[rank] = st.y;
-    s.n_len[rank] = st.z;
-    s.n_last[rank] = st.w;
-    s.n_hash[rank] = hash;
-    s.n_parent[rank] = alive ? par : -1;
-    s.n_code[rank] = code;
-    if (a.use_ctx) {
+  if (a.use_ctx && x.kept) {
 #pragma unroll
-      for (int i = 0; i < kCtxMax; ++i) ctx[i] = s.ctx[par][i];
-    }
+    for (int i = 0; i < kCtxMax; ++i) ctx[i] = s.ctx[x.parent][i];
   }
   wave_sync();
   if (a.use_ctx) {  // (every read of the old histories lies before)
-    if (kept)
+    if (x.kept)
 #pragma unroll
-      for (int i = 0; i < kCtxMax; ++i) s.ctx[rank][i] = !alive ? -1 : appended < 0 ? ctx[i] : i == 0 ? appended : ctx[i > 0 ? i - 1 : 0];
+      for (int i = 0; i < kCtxMax; ++i) s.ctx[x.rank][i] = !x.alive ? -1 : x.appended < 0 ? ctx[i] : i == 0 ? x.appended : ctx[i > 0 ? i - 1 : 0];
     if (n_kept < K && lane >= n_kept && lane < K)
 #pragma unroll
       for (int i = 0; i < kCtxMax; ++i) s.ctx[lane][i] = -1;
@@ -2248,7 +2104,7 @@ __device__ __forceinline__ bool res_select(const ResBlock &k, int step, int u, i
     }
     write_tree(a, b, step, K, j, s.n_parent[j], s.n_code[j], merged);
     if (j == 0 && last_step) end_utterance(a, b, step);
-    next = res_kind(live, now, T_b, a.max_sym);
+    next = hyp_kind(live, now, T_b, a.max_sym);
     frame = now.x;
   }
   if (aes) {  // only those in the earliest frame are expanded
@@ -2285,7 +2141,7 @@ __device__ __forceinline__ void res_selector(ResBlock k, int sel, float *lds) {
       s.row[lane].score = lane == 0 ? 0.0 : -INFINITY;
       s.state[lane] = none;
       s.hash[lane] = 0;
-      s.kind[lane] = res_kind(lane == 0, none, T_b, a0.sel.max_sym);
+      s.kind[lane] = hyp_kind(lane == 0, none, T_b, a0.sel.max_sym);
       for (int i = 0; i < kCtxMax; ++i) s.ctx[lane][i] = -1;
     }
   }

@@ -855,7 +855,11 @@ int launch_step(rnnt_beam *h, hipStream_t s, const StepPlan &p, int step_off, in
       if (big_tail(h, p)) {
         one_list_form(h, p, [&](auto kc, auto plain) {
           constexpr int KC = decltype(kc)::value, PLAIN = decltype(plain)::value;
-          if (!a.lm) hipLaunchKernelGGL((k_utt_select<KC, PLAIN>), dim3(p.B), dim3(64 * p.K), 0, s, a);  // one block per utterance
+          const dim3 utts(p.B), waves(64 * p.K);  // one block per utterance
+          const bool prefix = a.sel.prefix && p.algo == RNNT_AES;
+          if (!a.lm && !prefix && !a.sel.lm_early) hipLaunchKernelGGL((k_utt_few<KC, PLAIN>), utts, waves, 0, s, a);
+          else if constexpr (PLAIN != 0) return;  // (neither is of the plain forms)
+          else if (!a.lm) hipLaunchKernelGGL((k_utt_select<KC>), utts, waves, 0, s, a);
           else if constexpr (PLAIN == 0) hipLaunchKernelGGL((k_row_select<KC, false>), grid, block, 0, s, a);
         });
       } else {

@@ -266,6 +266,211 @@ __device__ __forceinline__ void end_utterance(const SelectArgs &a, int b, int S)
   }
 }
 
+// ---- the Beam best of the few candidates of an utterance that reach a lower bound of the K-th largest, in LDS (see res_select and
+// k_utt_few): top_key[0 .. kTop - 1] what they are ranked by, top_val their scores (where they differ), top_flat (hypothesis << kFlatShift | token);
+// state, hash, kind, adv of the hypotheses; n_* of the new slots.
+constexpr int kTop = 64;  // candidates that are ranked (and eight more are read)
+// what a hypothesis does at a step.  0: empty, 1: waits or has finished, 2: expanded, 3: the same, with blank alone.  state: frame, symbols in
+// the frame, length, last token
+__device__ __forceinline__ int hyp_kind(bool live, int4 state, int T_b, int max_sym) {
+  return !live ? 0 : state.x >= T_b ? 1 : state.y >= max_sym ? 3 : 2;
+}
+// A score as a float that is not above it (no number: -inf).  The K-th largest of such is below the K-th largest score.
+__device__ __forceinline__ float score_floor(double x) {
+  const float f = (float)x;
+  return f > -INFINITY ? f - (fabsf(f) * 2.4e-7f + 1e-30f) : -INFINITY;
+}
+// K-th largest of SETS values in LDS, one of which each lane holds as well (with fewer sets, some do).  -inf where there are fewer than K.
+template <int SETS>
+__device__ __forceinline__ float kth_largest(const float *set, float mine, int K) {
+  int n[4] = {0, 0, 0, 0};  // not below mine
+#pragma unroll
+  for (int i = 0; i < SETS; i += 4) {
+    const float4 v = *reinterpret_cast<const float4 *>(set + i);
+    n[0] += (int)(v.x >= mine);
+    n[1] += (int)(v.y >= mine);
+    n[2] += (int)(v.z >= mine);
+    n[3] += (int)(v.w >= mine);
+  }
+  const int ge = (n[0] + n[1]) + (n[2] + n[3]);
+  const unsigned long long kth = __ballot(mine > -INFINITY && ge == K);
+  if (kth != 0ull) return readlane_f(mine, __builtin_ctzll(kth));
+  return wave_max(mine > -INFINITY && ge >= K ? mine : -INFINITY);
+}
+// A bound of keys that a hypothesis' candidates reach which reach tau, (score + key) + base + extra, in float32 and with room for the rounding
+// of all of this (no token at -inf is a candidate)
+constexpr float kLeastKey = -3.4028235e38f;
+__device__ __forceinline__ float key_reach(double tau, double score, double base, double extra) {
+  float reach = (float)(((tau - extra) - base) - score);
+  reach -= fabsf(reach) * 2.4e-7f + (fabsf((float)score) + fabsf((float)tau)) * 1e-14f + 1e-6f;
+  return tau > -INFINITY ? fmaxf(reach, kLeastKey) : kLeastKey;
+}
+// Many candidates reach the bound: there were fewer than K sets (a single hypothesis at first), or keys are equal.  collect(in, most)
+// appends those for which in(key), in the candidates' own order, until there are `most` (more than that of the last 64 may be), and counts
+// them in total.  The K-th largest of the first kTop is the next bound; one that cannot be raised is that of the K best itself, and of those
+// equal to it the first ones count.
+template <class Collect>
+__device__ __forceinline__ void narrow_top(const double *top_key, int K, double tau, int &total, Collect collect) {
+  const int lane = threadIdx.x & 63;
+  bool above = false;  // whether the bound itself is left out
+  for (;;) {
+    total = 0;
+    collect([&](double x) { return x > -INFINITY && (above ? x > tau : x >= tau); }, 0x7fffffff);
+    if (total <= kTop && (!above || total >= K)) break;
+    if (total < K) {
+      collect([&](double x) { return x == tau; }, K);
+      total = min(total, kTop);
+      break;
+    }
+    wave_sync();
+    const int have = min(total, kTop);  // (kTop of them, or, above the bound, K or more)
+    const double x = top_key[lane];
+    int n = 0;
+    for (int i = 0; i < have; ++i) n += (int)(top_key[i] >= x);
+    // the K-th largest: the largest that K are not below
+    double t = lane < have && n >= K ? x : -INFINITY;
+    int dummy = 0;
+    wave_best(t, dummy);
+    above = !(t > tau);
+    if (!above) tau = t;
+    wave_sync();
+  }
+}
+// The candidate of a lane (of the first `total`): its place among all, and the slot that it becomes if that is below K.
+struct NewSlot {
+  bool kept, alive;  // alive: as most kept ones (early pruning: the LM's score may be no number)
+  int rank, parent, code, appended;  // code: for the tree
+  int4 state;
+  uint32_t hash;
+  double val;
+};
+// SAME: keys are the scores.  NO_DUR: no durations (adv is not read)
+template <bool SAME, bool NO_DUR, class S>
+__device__ __forceinline__ NewSlot rank_and_expand(S &s, int total, int K, int V, int T_b) {
+  const int lane = threadIdx.x & 63;
+  if (lane < 8) {  // (read in eights)
+    s.top_key[total + lane] = -INFINITY;
+    s.top_flat[total + lane] = 0x7fffffff;
+  }
+  wave_sync();
+  const bool mine = lane < total;
+  const int at = mine ? lane : 0;
+  const double key = s.top_key[at];
+  const int flat = s.top_flat[at];
+  NewSlot x;
+  if constexpr (SAME) x.val = key; else x.val = s.top_val[at];
+  x.parent = (flat >> kFlatShift) & (kMaxBeam - 1);
+  const int v = flat & ((1 << kFlatShift) - 1);
+  x.state = s.state[x.parent];
+  x.hash = s.hash[x.parent];
+  const int kind = s.kind[x.parent];
+  const int adv = NO_DUR ? 1 << 16 : s.adv[x.parent];
+  int ge = 0, gt = 0;
+  for (int c0 = 0; c0 < total; c0 += 8) {
+    double y[8];
+#pragma unroll
+    for (int q = 0; q < 8; ++q) y[q] = s.top_key[c0 + q];
+#pragma unroll
+    for (int q = 0; q < 8; ++q) {
+      ge += (int)(y[q] >= key);
+      gt += (int)(y[q] > key);
+    }
+  }
+  x.rank = gt;
+  if (__ballot(mine && ge != gt + 1) != 0ull) {  // equal ones: the full order
+    x.rank = 0;
+    for (int c = 0; c < total; ++c) x.rank += comes_before_count(s.top_key[c], s.top_flat[c], key, flat);
+  }
+  x.kept = mine && x.rank < K;
+  x.code = -2;
+  x.appended = -1;
+  if (kind >= 2) {
+    if (v == V) {
+      x.code = -1;
+      x.state.x += adv >> 16;
+      x.state.y = 0;
+    } else {
+      x.code = x.appended = v;
+      x.state.z += 1;
+      x.state.w = v;
+      x.hash = mod_mersenne31((uint64_t)x.hash * kHashBase + (uint64_t)(v + 1));
+      x.state.x += adv & 0xffff;
+      x.state.y = (adv & 0xffff) == 0 ? x.state.y + 1 : 0;
+    }
+  }
+  x.state.x = min(x.state.x, T_b);
+  x.alive = x.kept && (SAME || x.val > -INFINITY);
+  if (!SAME && !x.alive) {
+    x.state = make_int4(0, 0, 0, -1);
+    x.hash = 0;
+    x.code = -3;
+    x.appended = -1;
+  }
+  return x;
+}
+// the new slots, for recombine; those behind the n_kept candidates are empty
+template <class S>
+__device__ __forceinline__ void put_new_slots(S &s, const NewSlot &x, int n_kept, int K) {
+  const int lane = threadIdx.x & 63;
+  if (x.kept) {
+    const int j = x.rank;
+    s.n_live[j] = x.alive;
+    s.n_score[j] = x.alive ? x.val : -INFINITY;
+    s.n_t[j] = x.state.x;
+    s.n_sym[j] = x.state.y;
+    s.n_len[j] = x.state.z;
+    s.n_last[j] = x.state.w;
+    s.n_hash[j] = x.hash;
+    s.n_parent[j] = x.alive ? x.parent : -1;
+    s.n_code[j] = x.code;
+  }
+  if (n_kept < K && lane >= n_kept && lane < K) {
+    s.n_live[lane] = 0;
+    s.n_score[lane] = -INFINITY;
+    s.n_t[lane] = s.n_sym[lane] = s.n_len[lane] = 0;
+    s.n_last[lane] = s.n_parent[lane] = -1;
+    s.n_hash[lane] = 0;
+    s.n_code[lane] = -3;
+  }
+}
+// TDT: scores of the most likely duration (the first of equal ones) and of the most likely one that advances, from the logits of ND
+// durations; frames that a token (low half) and that blank advances with them.  (Every index is a compile-time constant: see
+// select_utterance.)
+__device__ __forceinline__ int best_durations(float (&dl)[8], int ND, uint64_t dur_bytes, double &x_tok, double &x_blank) {
+  float dmx = -INFINITY, sm = 0.f;
+#pragma unroll
+  for (int d = 0; d < 8; ++d)
+    if (d < ND) dmx = fmaxf(dmx, dl[d]);
+#pragma unroll
+  for (int d = 0; d < 8; ++d)
+    if (d < ND) sm += __expf(dl[d] - dmx);
+  const float l = dmx + __logf(sm);
+#pragma unroll
+  for (int d = 0; d < 8; ++d)
+    if (d < ND) dl[d] -= l;
+  bool have = false, have_b = false;
+  float best_v = 0.f, best_bv = 0.f;
+  int best_adv = 0, best_badv = 1;
+#pragma unroll
+  for (int d = 0; d < 8; ++d)
+    if (d < ND) {
+      const int du = (int)((dur_bytes >> (8 * d)) & 0xff);
+      if (!have || dl[d] > best_v) {
+        have = true;
+        best_v = dl[d];
+        best_adv = du;
+      }
+      if (du >= 1 && (!have_b || dl[d] > best_bv)) {
+        have_b = true;
+        best_bv = dl[d];
+        best_badv = du;
+      }
+    }
+  x_tok = (double)best_v;
+  x_blank = (double)best_bv;
+  return best_adv | best_badv << 16;
+}
+
 // One beam-search step of utterance b by one wave: the K best tokens and blank of every
 // hypothesis (LPR lanes per hypothesis, all hypotheses at once), the Beam best of those,
 // expansion, tree write, recombination, end-of-utterance detection.
