@@ -782,7 +782,11 @@ __device__ __forceinline__ void res_p_phase(ResBlock &k, int step) {
             __syncthreads();
             res_end_if_given_up();
             const int mine = kResWaves - 1 - k.wave, first = halves ? 2 * mine : mine;
-            if (k.ptile >= 0) res_p_finish<FORM>(a, k, l, ad, step, nt, first, first + 1, f);
+            if (k.ptile >= 0) {
+              __builtin_amdgcn_s_setprio(2);
+              res_p_finish<FORM>(a, k, l, ad, step, nt, first, first + 1, f);
+              __builtin_amdgcn_s_setprio(0);
+            }
             ++k.phase;
           } else {
 #pragma unroll 1
@@ -1111,7 +1115,11 @@ __device__ __forceinline__ void res_j_phase(ResBlock &k, int step, const ResWJ<F
       auto done = [&] {
         __syncthreads();
         res_end_if_given_up();
-        if (k.jtile[0] >= 0) res_j_finish<FORM>(k, l, ad, step, nt, k.jtile[0], ResPar::kJ + 8 * k.wave, k.wave);
+        if (k.jtile[0] >= 0) {
+          __builtin_amdgcn_s_setprio(2);
+          res_j_finish<FORM>(k, l, ad, step, nt, k.jtile[0], ResPar::kJ + 8 * k.wave, k.wave);
+          __builtin_amdgcn_s_setprio(0);
+        }
         ++k.phase;
       };
       if constexpr (FORM == kResF32) {
@@ -1463,9 +1471,12 @@ __device__ __forceinline__ void res_worker(ResBlock k, const ResTab &tab, float 
   for (int step = 0; over == 0; ++step) {
     // ---- cells
     if (!ST && k.wave < k.nR) {
+      // (the later ones of the two waves that have cells on a SIMD would get what the earlier leave)
+      if (k.wave >= kResWaves / 2) __builtin_amdgcn_s_setprio(2);
       if (k.nt == 1) res_cells<FULL, FORM, 1>(k, step, mytile, Rl, cl, hl);
       else if (k.nt == 2) res_cells<FULL, FORM, 2>(k, step, mytile, Rl, cl, hl);
       else res_cells<FULL, FORM, 3>(k, step, mytile, Rl, cl, hl);
+      __builtin_amdgcn_s_setprio(0);
     }
     if constexpr (!ST)
       res_p_phase<FULL, FORM>(k, step);
@@ -1931,8 +1942,8 @@ __device__ __forceinline__ bool res_select(const ResBlock &k, int step, int u, i
     delta = s.delta[row];
     bkey = bkey + delta;
   }
-  // ---- a lower bound of the K-th largest: the K-th largest of the maxima of disjoint sets of candidates, a lane's, or those of
-  // four lanes (in float32, rounded down)
+  // ---- a lower bound of the K-th largest: the K-th largest of the maxima of disjoint sets of candidates, those of one, two or four
+  // lanes (in float32, rounded down)
   float kmx = km[0];
 #pragma unroll
   for (int q = 1; q < NC; ++q) kmx = fmaxf(kmx, km[q]);
@@ -1941,22 +1952,21 @@ __device__ __forceinline__ bool res_select(const ResBlock &k, int step, int u, i
   if (prefix) best = best + delta;
   if (e == LPR - 1) best = bkey > best || !(best > -INFINITY) ? bkey : best;
   float fl = score_floor(best);
-  constexpr int SETS = KC == 4 ? 16 : 64;
-  if constexpr (SETS == 16) {
+  constexpr int SETS = KC == 4 ? 16 : KC == 8 ? 32 : 64, LANES = 64 / SETS;
+  if constexpr (LANES > 1) {
     float q[1] = {fl};
-    group_max_n<4>(q);
+    dpp_max_n<kDppXor1>(q);
+    if constexpr (LANES == 4) dpp_max_n<kDppXor2>(q);
     fl = q[0];
-    if ((lane & 3) == 0) s.set[lane >> 2] = fl;
-  } else {
-    s.set[lane] = fl;
   }
+  if ((lane & (LANES - 1)) == 0) s.set[lane / LANES] = fl;
   wave_sync();
   double tau = (double)kth_largest<SETS>(s.set, fl, K);
   // Where few hypotheses are expanded (at first, and while the others of AES++ wait) these sets may be fewer than K, or say little of the
   // one row that has candidates: there the K-th largest of a row's chunks as well, the largest of the rows'.
   if constexpr (KC > 4) {
     const int open = __popcll(__ballot(kind == 2 && e == 0));
-    if (open * LPR < K + 4) {
+    if (open * (LPR / LANES) < K + 4) {
       for (unsigned long long todo = __ballot(kind == 2 && e == 0); todo; todo &= todo - 1ull) {
         const int first = __builtin_ctzll(todo), h = first / LPR, i = lane & 31;
         const float z = late_lm ? L.kmax[h0 + h][i] : L.cst[h0 + h][i].x;
