@@ -768,11 +768,16 @@ __global__ __launch_bounds__(64 * kMaxBeam) void k_utt_few(RowSelectArgs a) {
         };
         for (int h = 0; h < K && total < most; ++h) {
           if (__builtin_amdgcn_readfirstlane(s.kind[h]) == 2)
-            for (int n0 = 0; n0 < V && total < most; n0 += 64) {
-              const int n = n0 + lane;
-              const float z = a.Z[(size_t)(m0 + h) * a.Npad + min(n, V - 1)];
-              const double key = token(z, s.score[h], s.base[h], use_gamma ? s.lse[h] : 0.0, use_gamma ? s.margin[h] : 0.0);
-              put(n < V && in(key), key, h << kFlatShift | n);
+            for (int n0 = 0; n0 < V && total < most; n0 += 8 * 64) {
+              float z[8];
+#pragma unroll
+              for (int q = 0; q < 8; ++q) z[q] = a.Z[(size_t)(m0 + h) * a.Npad + min(n0 + 64 * q + lane, V - 1)];
+#pragma unroll
+              for (int q = 0; q < 8; ++q) {
+                const int n = n0 + 64 * q + lane;
+                const double key = token(z[q], s.score[h], s.base[h], use_gamma ? s.lse[h] : 0.0, use_gamma ? s.margin[h] : 0.0);
+                if (total < most) put(n < V && in(key), key, h << kFlatShift | n);
+              }
             }
           if (total >= most) break;
           put(lane == 0 && in(s.blank[h]), s.blank[h], h << kFlatShift | V);

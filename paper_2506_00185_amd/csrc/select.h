@@ -306,8 +306,8 @@ __device__ __forceinline__ float key_reach(double tau, double score, double base
   return tau > -INFINITY ? fmaxf(reach, kLeastKey) : kLeastKey;
 }
 // Many candidates reach the bound: there were fewer than K sets (a single hypothesis at first), or keys are equal.  collect(in, most)
-// appends those for which in(key), in the candidates' own order, until there are `most` (more than that of the last 64 may be), and counts
-// them in total.  The K-th largest of the first kTop is the next bound; one that cannot be raised is that of the K best itself, and of those
+// appends those for which in(key), in the candidates' own order, until there are `most` (more than that of the last 64 may be), and
+// counts them in total.  The K-th largest of the first kTop is the next bound; one that cannot be raised is that of the K best itself, and of those
 // equal to it the first ones count.
 template <class Collect>
 __device__ __forceinline__ void narrow_top(const double *top_key, int K, double tau, int &total, Collect collect) {
@@ -315,7 +315,7 @@ __device__ __forceinline__ void narrow_top(const double *top_key, int K, double 
   bool above = false;  // whether the bound itself is left out
   for (;;) {
     total = 0;
-    collect([&](double x) { return x > -INFINITY && (above ? x > tau : x >= tau); }, 0x7fffffff);
+    collect([&](double x) { return x > -INFINITY && (above ? x > tau : x >= tau); }, kTop + 1);
     if (total <= kTop && (!above || total >= K)) break;
     if (total < K) {
       collect([&](double x) { return x == tau; }, K);

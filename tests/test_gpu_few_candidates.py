@@ -1,0 +1,80 @@
+"""The selection from a lower bound of the K-th best candidate (resident loop, and k_utt_few behind materialised logits) where the bound is
+no help: equal logits, of all tokens or of all but a few, whose candidates all reach it.  Then the first of equal ones count, in the
+order of (hypothesis, token).  And the edges of the row kernel's beams and vocabularies."""
+from __future__ import annotations
+
+import numpy as np
+import pytest
+
+import synth_inputs as S
+from gpu_common import compare, gpu_decode, make_walk
+from test_gpu_resident import KEYS, ST, TDT
+
+pytestmark = pytest.mark.gpu
+W64 = dict(H=64, P=64, E=64, D=32)
+W640 = dict(H=640, P=640, E=640, D=64)
+
+
+def _equal_logits(c, above):
+    """Weights whose tokens all have the same logit, `above` of them (spread over the vocabulary) a higher one."""
+    w = S.make_weights(c, 5)
+    w["W_out"][: c["V"] + 1] = 0
+    w["b_out"][: c["V"]] = 0.5
+    if above:
+        w["b_out"][np.linspace(0, c["V"] - 1, above).astype(int)] = 1.25
+    w["b_out"][c["V"]] = 1.0
+    return w
+
+
+@pytest.mark.parametrize("above", [0, 3, 70])
+@pytest.mark.parametrize("kw", [
+    dict(beam=1, V=129, **W64), dict(beam=4, V=1024, **W640), dict(beam=5, V=90, algo="aes", gamma=2.3, **W64, **TDT),
+    dict(beam=8, V=513, algo="aes", **W640), dict(beam=9, V=300, algo="aes", **W640), dict(beam=16, V=1024, **W640),
+    dict(beam=8, V=700, prec="bf16", algo="aes", **W64, **ST, ctx=2),
+], ids=lambda kw: f"k{kw['beam']}_v{kw['V']}_h{kw['H']}_{kw.get('algo', 'alsd')}")
+def test_equal_logits_in_the_resident_loop(kw, above):
+    import paper_2506_00185_amd as A
+    c = S.custom_config(**dict(dict(B=3, T=7, T_min=3, s=3, blank_bias=0.0), **kw))
+    w, L = _equal_logits(c, above), S.make_lengths(c, 7)
+    enc = S.make_enc(c, L, 8)
+    ref = gpu_decode(A.BeamDecoder(c, w, use_graph=False), enc, L)
+    dec = A.BeamDecoder(c, w)
+    r = gpu_decode(dec, enc, L)
+    assert dec.last_step_loop() == "resident"
+    for key in KEYS:
+        np.testing.assert_array_equal(r[key], ref[key])
+
+
+# Scores of the walk: float32 log-probabilities of some 20 steps, each right to 2^-22 of a value below 10 (soft-max statistics in float32);
+# operands are bfloat16 but zero, so that their rounding does not come in.
+@pytest.mark.parametrize("above", [0, 3, 70])
+@pytest.mark.parametrize("beam,V,algo", [(1, 700, "alsd"), (4, 97, "aes"), (10, 1030, "aes"), (16, 1030, "alsd")])
+def test_equal_logits_behind_materialised_ones(oracle, beam, V, algo, above):
+    import paper_2506_00185_amd as A
+    c = S.custom_config(B=3, T=6, T_min=3, V=V, beam=beam, algo=algo, s=2, prec="bf16", blank_bias=0.0, **W64, **ST, ctx=2)
+    w, L = _equal_logits(c, above), S.make_lengths(c, 7)
+    enc = S.make_enc(c, L, 8)
+    g = gpu_decode(A.BeamDecoder(c, w, joint_path="materialized"), enc, L)
+    o = oracle.decode(c, w, enc, L, log=True)
+    tol = 20 * 10 * 2.0 ** -22
+    full, exempt = compare(g, o, tol, tol, walk=make_walk(oracle, c, w, enc, L, g, tol))
+    assert full + exempt == c["B"]
+
+
+@pytest.mark.parametrize("kw", [
+    dict(beam=1, V=8192), dict(beam=8, V=40, algo="aes", gamma=2.3, **TDT), dict(beam=9, V=8191, algo="aes"),
+    dict(beam=13, V=33, algo="aes", gamma=1.0), dict(beam=12, V=8192, algo="aes", **TDT),
+    dict(beam=7, V=600, algo="aes", aes_prefix=True), dict(beam=7, V=600, aes_prefix=True),  # (k_utt_select; ALSD++ has no prefix search)
+], ids=lambda kw: f"k{kw['beam']}_v{kw['V']}_{kw.get('algo', 'alsd')}_{kw.get('model', 'rnnt')}")
+def test_materialised_logits_at_the_edges(oracle, kw):
+    """Bars of the bf16 variant at 160 wide: see test_gpu_parity."""
+    import paper_2506_00185_amd as A
+    from test_gpu_parity import TIE_BF16, TOL_BF16
+    c = S.custom_config(**dict(dict(B=3, T=8, T_min=1, s=2, prec="bf16", blank_bias=3.0, H=160, P=96, E=96, D=64, **ST, ctx=2), **kw))
+    w = S.perturb_biases(S.make_weights(c, 5), 6)
+    L = S.make_lengths(c, 7)
+    enc = S.make_enc(c, L, 8)
+    g = gpu_decode(A.BeamDecoder(c, w, joint_path="materialized"), enc, L)
+    o = oracle.decode(c, w, enc, L, log=True)
+    full, exempt = compare(g, o, TOL_BF16, TIE_BF16, walk=make_walk(oracle, c, w, enc, L, g, TOL_BF16))
+    assert full + exempt == c["B"]
