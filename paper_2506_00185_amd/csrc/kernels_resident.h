@@ -315,6 +315,8 @@ struct ResBlock {
   const int2 *info;                  // LDS: frames of the slot's utterance, its first row of f_proj
   uint64_t *word;                    // LDS: this wave's copy of the last step's words, [slot tile][16]
   int4 *ctx;                         // LDS, stateless decoders: this wave's copy of the slots' last tokens (-1: none)
+  float *pre;                        // LDS, stateless decoders: the waves' slices of pre
+  int quads_inv;                     // 2^16 over the quads of k of a slice, rounded up (numbers below 320 are divided by up to 20)
   int phase;                         // which half of the partial sums
 };
 // A lane's place in the wave.  (Computed anew where it is needed rather than kept: the weights leave no registers to
@@ -573,14 +575,8 @@ __device__ __forceinline__ void clear_p(const ResBlock &k, const ResLane &l, con
 __device__ __forceinline__ int res_p_wave(int tile_no) { return kResWaves - 1 - tile_no; }
 
 // A round of activations (lane: slot column, half of k) rounded to bf16, the four k in order
-template <bool RELU>
 __device__ __forceinline__ uint64_t round_bf16(const uint64_t *x) {
-  float v[4] = {lo_f(x[0]), lo_f(x[1]), hi_f(x[0]), hi_f(x[1])};
-  if constexpr (RELU) {
-#pragma unroll
-    for (int i = 0; i < 4; ++i) v[i] = fmaxf(v[i], 0.f);
-  }
-  return (uint64_t)pack_bf16_rne(v[2], v[3]) << 32 | pack_bf16_rne(v[0], v[1]);
+  return (uint64_t)pack_bf16_rne(hi_f(x[0]), hi_f(x[1])) << 32 | pack_bf16_rne(lo_f(x[0]), lo_f(x[1]));
 }
 // bf16 matrix instruction (32 x 32 x 16) on two rounds
 __device__ __forceinline__ floatx16 mfma_pair_bf16(uint64_t w0, uint64_t w1, uint64_t x0, uint64_t x1, bool two, floatx16 acc) {
@@ -691,7 +687,7 @@ __device__ __forceinline__ void res_p_phase(ResBlock &k, int step) {
             if (2 * i < nh) {
               const bool two = i < 2 && 2 * i + 1 < nh;
               const uint64_t *xi = x + kResMaxRounds * hf + 4 * i;
-              acc = mfma_pair_bf16(wh[2 * i * 64], wh[(2 * i + (two ? 1 : 0)) * 64], round_bf16<false>(xi), round_bf16<false>(i < 2 ? xi + 2 : xi), two, acc);
+              acc = mfma_pair_bf16(wh[2 * i * 64], wh[(2 * i + (two ? 1 : 0)) * 64], round_bf16(xi), round_bf16(i < 2 ? xi + 2 : xi), two, acc);
             }
           put(hf, acc);
         }
@@ -701,8 +697,8 @@ __device__ __forceinline__ void res_p_phase(ResBlock &k, int step) {
         for (int i = 0; i < kResMaxRounds / 2; ++i)
           if (2 * i < nr) {
             const bool two = 2 * i + 1 < nr;
-            acc = mfma_pair_bf16(w[(ra + 2 * i) * 64], w[(ra + 2 * i + (two ? 1 : 0)) * 64], round_bf16<false>(x + 4 * i),
-                                 round_bf16<false>(x + 4 * i + 2), two, acc);
+            acc = mfma_pair_bf16(w[(ra + 2 * i) * 64], w[(ra + 2 * i + (two ? 1 : 0)) * 64], round_bf16(x + 4 * i),
+                                 round_bf16(x + 4 * i + 2), two, acc);
           }
         put(0, acc);
       }
@@ -896,60 +892,91 @@ __device__ __forceinline__ void clear_z(const ResBlock &k, const ResLane &l, con
   if (slot < k.nslots) res_store16(k.local, ad.z(step, slot) + 16 * tile + 4 * l.kq, floatx4{e, e, e, e});
 }
 
-// Stateless decoders: the wave's slice of pre of its lanes' slots, as res_gather / bf16_gather would have read it, summed up
-// in the order of k_stateless_pre.  All rows of a pair of tables are requested before the first is needed: the time is that
-// of one trip to the L2 (each block of a group reads all of the group's rows, at most 16 x (1 + n_ctx) x 2.5 KB; a
-// hand-over of sums formed once would cost a hop more, and the same trip before it).
-// SPLIT (float32 models): a lane's places of split operands (see ResW16), else those of res_k_of.
+// Stateless decoders: the wave's slice of pre of the group's slots, summed up in the order of k_stateless_pre, and from LDS a lane's words of
+// it as res_gather / bf16_gather would have read them.  All rows of a pair of tables are requested before the first is needed: the
+// time is that of one trip to the L2 (each block of a group reads all of the group's rows, at most 16 x (1 + n_ctx) x 2.5 KB; a
+// hand-over of sums formed once would cost a hop more, and the same trip before it).  A lane takes four k of a slot, consecutive lanes
+// consecutive ones, and the operands are read from LDS: each lane loading what its operands are made of, 30 times 16 bytes, most of it what
+// other lanes, or lanes without a slot, load as well, was bound by the 64 bytes a cycle that a compute unit's L1 hands over (1.6 to 2.3 us;
+// batch 8, beam 4, bf16 joint: 2.94 -> 2.62 ms per decode).
+// SPLIT (float32 models): a lane's places of split operands (see ResW16), else those of res_k_of.  BF16: ReLU and rounding are done.
+constexpr int kResPreSlot = 8 * kResMaxRounds + 4;  // floats of a slot in LDS (bf16: half of them)
 template <bool FULL, bool BF16, bool SPLIT>
-__device__ __forceinline__ void res_stateless_pre(const ResArgs &a, const ResBlock &k, const ResLane &l, int nr,
-                                                  uint64_t (&x)[(BF16 ? 2 : 1) * kResMaxRounds]) {
-  const int slot = l.sl < k.nslots ? l.sl : 0;  // (places without a slot repeat the first one's rows)
-  const int2 in = k.info[slot];
-  const int4 c = k.ctx[slot];
-  int tt = word_frame(k.word[slot]);
-  tt = tt < in.x ? tt : in.x - 1;
-  tt = tt < 0 ? 0 : tt;
-  constexpr int N = SPLIT ? kResMaxRounds / 2 : kResMaxRounds;
-  // (SPLIT: four k of two rounds of either quad, then of the last two rounds)
-  auto round_of = [&](int i) { return !SPLIT ? i : i < 4 ? 4 * (i >> 1) + 2 * (l.kq >> 1) + (i & 1) : 8 + (l.kq & 1); };
-  const int k0 = 8 * k.wave * nr + 4 * (BF16 ? l.lane >> 5 : l.kq & 1), k4 = 8 * k.wave * nr + 4 * (l.kq >> 1);
+__device__ __forceinline__ void res_stateless_pre(const ResArgs &a, const ResBlock &k, const ResLane &l, int nr, uint64_t (&x)[kResMaxRounds]) {
+  constexpr int N = kResSlot * 2 * kResMaxRounds / 64;  // quads of k of a lane
+  const int quads = FULL ? 2 * kResMaxRounds : 2 * nr, total = k.nslots * quads;
   float4 v[N];
-  auto row = [&](float4 (&d)[N], const float *p) {
+  const float *f[N];
+  int4 c[N];
+  int at[N];
 #pragma unroll
-    for (int i = 0; i < N; ++i) {
-      const int r = round_of(i);
-      d[i] = *reinterpret_cast<const float4 *>(p + (SPLIT && i == 4 ? k4 : k0) + 8 * (FULL || r < nr ? r : 0));
-    }
-  };
-  auto add = [&](const float4 (&d)[N]) {
-#pragma unroll
-    for (int i = 0; i < N; ++i) {
-      v[i].x += d[i].x; v[i].y += d[i].y; v[i].z += d[i].z; v[i].w += d[i].w;
-    }
-  };
-  row(v, a.f_proj + ((size_t)in.y + tt) * a.H);
+  for (int i = 0; i < N; ++i) {
+    const int q = l.lane + 64 * i < total ? l.lane + 64 * i : 0, slot = FULL ? q / quads : q * k.quads_inv >> 16, quad = q - slot * quads;
+    const int2 in = k.info[slot];
+    c[i] = k.ctx[slot];
+    int tt = word_frame(k.word[slot]);
+    tt = tt < in.x ? tt : in.x - 1;
+    tt = tt < 0 ? 0 : tt;
+    at[i] = slot * kResPreSlot + 4 * quad;
+    f[i] = a.f_proj + ((size_t)in.y + tt) * a.H + 8 * k.wave * nr + 4 * quad;
+    v[i] = make_float4(0.f, 0.f, 0.f, 0.f);
+    if (64 * i < total) v[i] = *reinterpret_cast<const float4 *>(f[i]);
+  }
 #pragma unroll 1
   for (int j = 0; j < a.n_ctx; j += 2) {
     const int j1 = j + 1 < a.n_ctx ? j + 1 : j;
-    const int t0 = j == 0 ? c.x : c.z, t1 = j1 == j ? t0 : j == 0 ? c.y : c.w;
     float4 d0[N], d1[N];
-    row(d0, a.emb_tab + ((size_t)j * (a.V + 1) + (t0 < 0 ? a.V : t0)) * a.H);
-    row(d1, a.emb_tab + ((size_t)j1 * (a.V + 1) + (t1 < 0 ? a.V : t1)) * a.H);
+#pragma unroll
+    for (int i = 0; i < N; ++i) {
+      const int col = 8 * k.wave * nr + (at[i] % kResPreSlot), t0 = j == 0 ? c[i].x : c[i].z, t1 = j1 == j ? t0 : j == 0 ? c[i].y : c[i].w;
+      d0[i] = d1[i] = make_float4(0.f, 0.f, 0.f, 0.f);
+      if (64 * i < total) {
+        d0[i] = *reinterpret_cast<const float4 *>(a.emb_tab + ((size_t)j * (a.V + 1) + (t0 < 0 ? a.V : t0)) * a.H + col);
+        d1[i] = *reinterpret_cast<const float4 *>(a.emb_tab + ((size_t)j1 * (a.V + 1) + (t1 < 0 ? a.V : t1)) * a.H + col);
+      }
+    }
+    auto add = [&](const float4 (&d)[N]) {
+#pragma unroll
+      for (int i = 0; i < N; ++i) {
+        v[i].x += d[i].x; v[i].y += d[i].y; v[i].z += d[i].z; v[i].w += d[i].w;
+      }
+    };
     add(d0);
     if (j1 > j) add(d1);
   }
+  float *mine = k.pre + k.wave * kResSlot * kResPreSlot / (BF16 ? 2 : 1);
+  wave_sync();
 #pragma unroll
-  for (int i = 0; i < N; ++i) {
-    if constexpr (SPLIT) {
-      const bool in = FULL || round_of(i) < nr;
-      x[2 * i] = in ? pack2(v[i].x, v[i].z) : 0;
-      x[2 * i + 1] = in ? pack2(v[i].y, v[i].w) : 0;
-    } else if constexpr (BF16) {
-      x[2 * i] = pack2(v[i].x, v[i].z);
-      x[2 * i + 1] = pack2(v[i].y, v[i].w);
-    } else {
-      x[i] = l.kq >> 1 ? pack2(v[i].y, v[i].w) : pack2(v[i].x, v[i].z);
+  for (int i = 0; i < N; ++i)
+    if (l.lane + 64 * i < total) {
+      if constexpr (BF16) {
+        *reinterpret_cast<uint64_t *>(mine + at[i] / 2) = (uint64_t)pack_bf16_rne(fmaxf(v[i].z, 0.f), fmaxf(v[i].w, 0.f)) << 32 |
+                                                          pack_bf16_rne(fmaxf(v[i].x, 0.f), fmaxf(v[i].y, 0.f));
+      } else {
+        *reinterpret_cast<float4 *>(mine + at[i]) = v[i];
+      }
+    }
+  wave_sync();
+  const int slot = l.sl < k.nslots ? l.sl : 0;  // (places without a slot repeat the first one)
+  if constexpr (BF16) {
+    const uint64_t *r = reinterpret_cast<const uint64_t *>(mine) + slot * (kResPreSlot / 4) + (l.lane >> 5);
+#pragma unroll
+    for (int i = 0; i < kResMaxRounds; ++i) x[i] = FULL || i < nr ? r[2 * i] : 0;
+  } else if constexpr (SPLIT) {
+    // (four k of two rounds of either quad, then of the last two rounds)
+#pragma unroll
+    for (int i = 0; i < kResMaxRounds / 2; ++i) {
+      const int round = i < 4 ? 4 * (i >> 1) + 2 * (l.kq >> 1) + (i & 1) : 8 + (l.kq & 1), half = i < 4 ? l.kq & 1 : l.kq >> 1;
+      const bool in = FULL || round < nr;
+      const float4 d = *reinterpret_cast<const float4 *>(mine + slot * kResPreSlot + 4 * (in ? 2 * round + half : 0));
+      x[2 * i] = in ? pack2(d.x, d.z) : 0;
+      x[2 * i + 1] = in ? pack2(d.y, d.w) : 0;
+    }
+  } else {
+#pragma unroll
+    for (int i = 0; i < kResMaxRounds; ++i) {
+      const float4 d = *reinterpret_cast<const float4 *>(mine + slot * kResPreSlot + 4 * (FULL || i < nr ? 2 * i + (l.kq & 1) : 0));
+      x[i] = l.kq >> 1 ? pack2(d.y, d.w) : pack2(d.x, d.z);
     }
   }
 }
@@ -1058,16 +1085,17 @@ __device__ __forceinline__ void res_j_phase(ResBlock &k, int step, const ResWJ<F
     for (int nt = 0; nt < k.nt; nt += 2) {
       const bool second = nt + 1 < k.nt;
       if (step == a.stall_step && nt + 2 >= k.nt) __builtin_amdgcn_endpgm();
-      uint64_t x[2 * kResMaxRounds];
-      if constexpr (ST) res_stateless_pre<FULL, true, false>(a, k, l, nr, x);
+      uint64_t x[2 * kResMaxRounds], xb[kResMaxRounds];
+      if constexpr (ST) res_stateless_pre<FULL, true, false>(a, k, l, nr, xb);
       else {
         const uint32_t probe = bf16_probe_tile(l, ad.p_tile, second) + ((l.lane & 31) < nr ? l.lane & 31 : 0) * kResRoundBytes;
         bf16_gather<FULL>(l, reinterpret_cast<const char *>(ad.p(step, nt)) + k.wave * nr * kResRoundBytes, 0, nr > 5 ? 5 * kResRoundBytes : 0, min(nr, 5),
                           max(nr - 5, 0), second, ad.p_tile, probe, x);
       }
-      uint64_t xb[kResMaxRounds];
+      if constexpr (!ST) {
 #pragma unroll
-      for (int i = 0; i < kResMaxRounds; ++i) xb[i] = round_bf16<ST>(x + 2 * i);
+        for (int i = 0; i < kResMaxRounds; ++i) xb[i] = round_bf16(x + 2 * i);
+      }
       auto put_out = [&](int t) {
         __syncthreads();
         res_end_if_given_up();
@@ -1389,6 +1417,8 @@ __device__ __forceinline__ void res_worker(ResBlock k, const ResTab &tab, float 
   if constexpr (ST) {  // (in the place of the cells' LDS: 8 waves x NT x 16 x 16 bytes of 6 x NT x 1536)
     k.ctx = reinterpret_cast<int4 *>(Rl) + k.wave * a0.NT * kResSlot;
     for (int i = l0.lane; i < a0.NT * kResSlot; i += 64) k.ctx[i] = make_int4(-1, -1, -1, -1);
+    k.quads_inv = res_uniform(65535 / (2 * a0.rounds_h) + 1);
+    k.pre = reinterpret_cast<float *>(info + a0.NT * kResSlot) + kResWaves * a0.NT * kResSlot * 2;
   }
   ResWJ<FORM> wj;
   ResWR<FORM> wr;

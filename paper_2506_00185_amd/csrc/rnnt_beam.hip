@@ -61,7 +61,7 @@ enum {
 };
 const char *kKernelNames[KT_COUNT] = {"k_gemm_tiled(enc_proj)", "k_init",      "k_step_main", "k_select",    "k_lm_rows",
                                       "k_lstm_pointwise",    "k_pred_proj", "k_backtrace", "k_joint_big", "k_row_select",
-                                      "k_stateless_pre",     "k_utt_select"};
+                                      "k_stateless_pre",     "k_utt_few"};
 
 // Device memory a decode works in beyond its inputs and outputs, laid out for given maxima.  The handle owns one
 // (a single allocation made at create); the allocation-free entry point lays one out in the static array.

@@ -212,7 +212,8 @@ Plan make_plan(const Resident &r, const rnnt_config_t &c, int B, int K, bool has
   auto worker_lds = [&](int red_blocks) {
     return (size_t)lds_tiles * (r.form == kResSplit ? kResTileFloats : std::max(c.pred == RNNT_PRED_LSTM ? c.P : 0, c.H) * kResSlot) * 4 +
            (bf && fold ? (size_t)(1 + c.n_durations) * c.H * 2 : 0) + (size_t)2 * red_blocks * kResRedBlock * 4 +
-           (size_t)kResMaxR * p.NT * (256 + 128) * 4 + ResPar::kFloats * 4 + (size_t)p.NT * kResSlot * (sizeof(int2) + kResWaves * 8);
+           (size_t)kResMaxR * p.NT * (256 + 128) * 4 + ResPar::kFloats * 4 + (size_t)p.NT * kResSlot * (sizeof(int2) + kResWaves * 8) +
+           (c.pred == RNNT_PRED_LSTM ? 0 : (size_t)kResWaves * kResSlot * kResPreSlot * (bf ? 2 : 4));
   };
   // (640 wide: with one tile of slots)
   p.red_blocks = bf ? kResRedBlocks<true> : kResRedBlocks<false>;
