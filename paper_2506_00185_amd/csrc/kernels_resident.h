@@ -11,11 +11,11 @@
 //   cell    words of the last step -> the owners of W_hh tiles update the cells of their units        -> h
 //   P       h    -> the owners of projection tiles: pre = f_proj[frame] + W_pred h + b_pred           -> pre
 //   J       pre  -> the owners of output-layer tiles: z = W_out ReLU(pre) + b_out                     -> logits
-//   select  z    -> one block per utterance (a wave per hypothesis): top Beam, tree, recombination    -> words
+//   select  z    -> one block per utterance (a wave per hypothesis): the Beam best of all, tree, ..   -> words
 //   R       h    -> the owners of W_hh tiles: W_hh h for the next cell update, under the selection
 // Hand-over between blocks: an array that one phase writes and another reads is pre-filled with a bit pattern that no
 // result has (a NaN with all bits set); the reader loads the data itself, device-coherently, until none of it holds the
-// pattern.  No barrier, no flag and no acknowledged store lies between the two (one hop costs 0.6 us; stores, their
+// pattern.  No barrier, no flag and no acknowledged store lies between the two (one hop costs 0.5 us; stores, their
 // acknowledgement, a counter and then the loads 2.0 us).  Where the blocks of a group find themselves on one XCD they hand over through
 // its L2, else their stores are written through.  The words of the selection carry the step's number instead.
 // A writer puts the pattern back once a word of a later phase proves that every reader is through (see the clear_
@@ -23,7 +23,7 @@
 //
 // Every sum is formed in the order of the per-step kernels (K slices of 1/8 of the contraction, slices added first to last), so the
 // results are the same bit for bit.  Float32 models from 320 wide on whose weights can be split multiply on the float16 matrix
-// instructions, both operands split in two (see split_f16): in float32, W_hh h took 3.2 us per step and tile of 16 slots, as long as the selection it hides under, and the other
+// instructions, both operands split in two (see split_f16): in float32, W_hh h took 3.2 us per step and tile of 16 slots, longer than the selection it hides under (2.9), and the other
 // two contractions 3 us of the chain.  bf16-joint models keep W_hh h on float32 matrix instructions (a 16x16x4 one rounds like four
 // fused multiply-adds in a row): they round activations to 8 bits, and near ties there follow every last bit of the hidden state.
 // (ms per decode before / after the splits, the gathers and the ends of waves described below: one utterance 8.65 / 6.95, greedy batch
@@ -32,7 +32,7 @@
 // Stateless decoders (ST) have no cells and no projection: pre is a sum of table rows, f_proj[frame] + tab_0[last token] +
 // tab_1[the one before] + .., and every owner of output-layer tiles forms its own slice of it from the words (see
 // res_stateless_pre), so that a step is two hops (words -> z -> words).  The owners keep the slots' last tokens themselves.
-// (batch 8, beam 4, bf16 joint, 640 wide, V = 1024: 5.46 ms per decode with the per-step launches, 3.62 here.)
+// (batch 8, beam 4, bf16 joint, 640 wide, V = 1024: 5.46 ms per decode with the per-step launches, 2.62 here.)
 //
 // Every wait is bounded: a wave that waits too long raises the abort word and ends, every other wave sees the word (or
 // its own limit) and ends too, and the host decodes the batch with the per-step launches instead.
@@ -119,9 +119,8 @@ __host__ __device__ inline bool res_on_one_xcd(int xcds, int stall_step) { retur
 
 // The kernel's arguments, read from the argument segment anew at the begin of every phase: kept in scalar registers over
 // the whole loop they would push the weights out of the vector registers (a thousand spills).  What is left by the compiler's
-// report: LSTM forms 48 vector registers spilled 640 wide and 120 at other widths where the weights are split, 4 to 10 in the other forms,
-// and 120 to 260 scalar ones (into vector lanes), 256 vector registers in use; stateless forms no vector register, 90 to 150 scalar
-// ones.  The selecting blocks, whose code needs the scalar ones, share the kernel with the owners of the weights.
+// report: LSTM forms no vector register spilled but 60 to 70 where the weights are split and less than 640 wide, and 100 to 200 scalar
+// ones (into vector lanes), 244 to 256 vector registers in use; stateless forms no vector register, 70 to 105 scalar ones.  The selecting blocks, whose code needs the scalar ones, share the kernel with the owners of the weights.
 __device__ __forceinline__ const ResArgs &res_args() {
   typedef const __attribute__((address_space(4))) ResArgs ConstArgs;
   ConstArgs *p = (ConstArgs *)__builtin_amdgcn_kernarg_segment_ptr();
