@@ -201,13 +201,21 @@ Plan make_plan(const Resident &r, const rnnt_config_t &c, int B, int K, bool has
   // step here / there, before hand-overs stayed in the L2: two tiles, batch 16 beam 16 34.8 / 33.3; three, batch 32 beam 12 37.3 / 36.0.)
   if (c.pred != RNNT_PRED_LSTM && p.NT > 1) return p;
   if (per_step_is_faster(r, c, B, K, p.NT)) return p;
-  const int most_sel = std::max(1, p.n_blocks / 8);
+  const bool bf = c.prec == RNNT_BF16_JOINT;
+  p.columns = fold && r.form == kResSplit && whole_width(c);
+  int most_sel = std::max(1, p.n_blocks / 8);
   p.upc = (p.nu + most_sel - 1) / most_sel;
   if (p.upc > kResMaxSel || p.upc * K * K > 512 || p.upc * K > kResMaxHyps) return p;
   p.n_sel = (p.nu + p.upc - 1) / p.upc;
-  const bool bf = c.prec == RNNT_BF16_JOINT;
-  p.columns = fold && r.form == kResSplit && whole_width(c);
-  if (!assign_tiles(c, p.n_blocks - p.n_sel, p.columns, p.tab)) return p;
+  while (!assign_tiles(c, p.n_blocks - p.n_sel, p.columns, p.tab)) {
+    // Columns dealt one by one take more places than the tile that they lie in: with eight durations and V = 1024 one more than 28
+    // blocks have (64 + 9 of the output layer, 40 of the projection, 4 in each).  Then fewer blocks select, for more utterances each
+    // (ms per decode of 100 frames, here / by the per-step launches: batch 32 beam 8 1.50 / 3.46, beam 12 1.94 / 5.23, batch 113 beam 2 1.54 / 3.56).
+    if (!p.columns || --most_sel == 0) return p;
+    p.upc = (p.nu + most_sel - 1) / most_sel;
+    if (p.upc > kResWaves || p.upc * K > kResMaxHyps) return p;  // (a wave per utterance)
+    p.n_sel = (p.nu + p.upc - 1) / p.upc;
+  }
   int lds_tiles = 0;
   for (const ResTab &t : p.tab) lds_tiles = std::max(lds_tiles, t.nP + std::max(0, t.nJ - (bf ? kResRegJ<true> : kResRegJ<false>)));
   auto worker_lds = [&](int red_blocks) {

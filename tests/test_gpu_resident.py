@@ -495,3 +495,22 @@ def test_threads_that_decode_on_streams_of_their_own():
             assert loop in (("resident", "graph"), ("resident", "graph"), ("single launch",), ("launches",))[i]
             for key in ("tokens", "lens", "scores", "n_steps"):
                 np.testing.assert_array_equal(r[key], ref[key])
+
+
+@pytest.mark.parametrize("B,beam", [(32, 12), (29, 8), (57, 1), (113, 2)])
+def test_folded_columns_that_take_a_tile_more_than_there_is_room_for(B, beam):
+    """Eight durations and the largest vocabulary: nine columns beside 64 tiles of tokens and 40 of the projection.  Fewer blocks of a
+    group select then (three or two instead of four, for up to five utterances each), and the loop decodes the batch all the same."""
+    import paper_2506_00185_amd as A
+    c = S.custom_config(B=B, beam=beam, V=1024, T=17, T_min=3, s=2, model="tdt", durations=(0, 1, 2, 3, 4, 5, 6, 7), blank_bias=3.0, **W640)
+    w = S.perturb_biases(S.make_weights(c, 5), 6)
+    L = S.make_lengths(c, 7)
+    L[1] = 0
+    enc = S.make_enc(c, L, 8)
+    ref = gpu_decode(A.BeamDecoder(c, w, use_graph=False), enc, L)
+    dec = A.BeamDecoder(c, w)
+    for _ in range(2):
+        r = gpu_decode(dec, enc, L)
+        assert dec.last_step_loop() == "resident"
+        for key in KEYS:
+            np.testing.assert_array_equal(r[key], ref[key])
