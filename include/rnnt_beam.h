@@ -269,9 +269,12 @@ int rnnt_beam_dump_tree(rnnt_beam_t *h, int32_t *parent, int32_t *token, int32_t
  *   rnnt_beam_debug_lm      : LM scores (natural log) of every token after each of n contexts;
  *                             ctx_tokens host [n, order-1], most recent token first, -1 = none;
  *                             out host [n, V].
+ *   rnnt_beam_debug_gates   : 1 / (1 + e) and (1 - e) / (1 + e) of n device values as the LSTM cell divides, to device
+ *                             arrays: its sigmoid(x) for e = exp(-x), its tanh(|x|) for e = exp(-2 |x|) (e up to 1).
  */
 int rnnt_beam_debug_encproj(rnnt_beam_t *h, float *out, int64_t n_floats);
 int rnnt_lm_debug_query(const rnnt_lm_t *lm, const int32_t *ctx_tokens, int32_t n, float *out);
+int rnnt_beam_debug_gates(const float *e, int64_t n, float *sigmoid, float *tanh);
 
 /*
  * Test hook for host logic, needs no GPU: the block -> work item mapping of the per-step launches.  A launch has

@@ -19,7 +19,7 @@ EXPORTS = ["rnnt_beam_create", "rnnt_lm_create", "rnnt_beam_decode", "rnnt_beam_
            "rnnt_beam_last_decode_ms", "rnnt_beam_set_profiling", "rnnt_beam_kernel_times", "rnnt_beam_last_error",
            "rnnt_beam_destroy", "rnnt_lm_destroy", "rnnt_beam_debug_block_map", "rnnt_beam_decode_static", "rnnt_beam_debug_set_spin_limit",
            "rnnt_beam_last_step_loop", "rnnt_beam_debug_stall_resident", "rnnt_beam_debug_rebuild_resident",
-           "rnnt_beam_debug_resident_groups"]
+           "rnnt_beam_debug_resident_groups", "rnnt_beam_debug_gates"]
 
 
 class RnntBeamError(RuntimeError):
@@ -36,6 +36,16 @@ def block_map(a_tiles, a_m, b_begin, b_end, b_m):
     lib.rnnt_beam_debug_block_map(a_tiles, a_m, b_begin, b_end, b_m, role.ctypes.data_as(C.c_void_p),
                                   nt.ctypes.data_as(C.c_void_p), mt.ctypes.data_as(C.c_void_p), n)
     return n, role, nt, mt
+
+
+def debug_gates(e):
+    """rnnt_beam_debug_gates: (1 / (1 + e), (1 - e) / (1 + e)) of a device float32 tensor."""
+    e = e.contiguous()
+    sig, tanh = (_torch().empty_like(e) for _ in range(2))
+    _torch().cuda.synchronize()
+    _check(load_library().rnnt_beam_debug_gates(C.c_void_p(e.data_ptr()), C.c_int64(e.numel()), C.c_void_p(sig.data_ptr()),
+                                                C.c_void_p(tanh.data_ptr())))
+    return sig, tanh
 
 
 class _Config(C.Structure):

@@ -403,8 +403,10 @@ __device__ __forceinline__ void wave_best(double &v, int &i) {
 }
 
 // ---- arithmetic of the LSTM cell
-// n / d for d from 1 on, n from 0 to 1: the steps of the correctly rounded division without what it does for operands that need scaling
-// (which goes through the one condition register and so keeps divisions from overlapping).  FIXUP: d may be infinite.
+// n / d by Newton's iteration on the reciprocal and two corrections of the quotient by its residual (Markstein, IBM Journal of Research
+// and Development 34, 1990), for n from 0 to 1 and d from 1/4 to below 2^126, whose reciprocal is normal: the correctly rounded quotient, a
+// subnormal one too.  The compiler's division scales its operands for the others, by way of the one condition register, which keeps
+// divisions from overlapping.  FIXUP: d may be infinite.
 template <bool FIXUP>
 __device__ __forceinline__ float div_unit_f(float n, float d) {
   float r = __builtin_amdgcn_rcpf(d);
@@ -414,10 +416,14 @@ __device__ __forceinline__ float div_unit_f(float n, float d) {
   q = fmaf(fmaf(-d, q, n), r, q);
   return FIXUP ? __builtin_amdgcn_div_fixupf(q, d, n) : q;
 }
-__device__ __forceinline__ float sigmoid_f(float x) { return div_unit_f<true>(1.f, 1.f + __expf(-x)); }
+// 1 / (1 + e) for e from 0 to infinity: numerator and denominator are quarters (the rounding of 1 + e is the same), since 1 + e may be
+// beyond 2^126 and its reciprocal, flushed to zero, would make the quotient 0 there instead of some 2^-127
+__device__ __forceinline__ float sigmoid_of(float e) { return div_unit_f<true>(0.25f, fmaf(e, 0.25f, 0.25f)); }
+// (1 - e) / (1 + e) for e from 0 to 1
+__device__ __forceinline__ float tanh_of(float e) { return div_unit_f<false>(1.f - e, 1.f + e); }
+__device__ __forceinline__ float sigmoid_f(float x) { return sigmoid_of(__expf(-x)); }
 __device__ __forceinline__ float tanh_f(float x) {
-  const float e = __expf(-2.f * fabsf(x));
-  const float r = div_unit_f<false>(1.f - e, 1.f + e);
+  const float r = tanh_of(__expf(-2.f * fabsf(x)));
   return x < 0.f ? -r : r;
 }
 // gates (i, f, g, o) = recurrent part r4 + token part g4; c: the unit's old cell state in, the new one out; returns h

@@ -886,6 +886,14 @@ __global__ __launch_bounds__(256) void k_lstm_pointwise(const float *__restrict_
   lstm_cell(R, G, h_cur, c_cur, h_nxt, c_nxt, src_row[m], tok[m], m, u, Mp, P, done_flag);
 }
 
+// (a test's: the divisions of the LSTM cell over their whole range)
+__global__ __launch_bounds__(256) void k_gates(const float *e, int64_t n, float *sigmoid, float *tanh) {
+  for (int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x; i < n; i += (int64_t)gridDim.x * 256) {
+    sigmoid[i] = sigmoid_of(e[i]);
+    tanh[i] = tanh_of(e[i]);
+  }
+}
+
 // Advances the step counter at the boundary of two chunks of steps (one thread of one launch per chunk) and tells
 // the enqueueing host thread, through a word of pinned host memory, that the next chunk begins.
 __device__ __forceinline__ void bump_step(int *step_base, int bump, volatile int *h_progress) {

@@ -1625,6 +1625,12 @@ int rnnt_beam_debug_encproj(rnnt_beam_t *h, float *out, int64_t n_floats) {
   return RNNT_OK;
 }
 
+int rnnt_beam_debug_gates(const float *e, int64_t n, float *sigmoid, float *tanh) {
+  if (!e || !sigmoid || !tanh || n < 1) return RNNT_E_ARG;
+  hipLaunchKernelGGL(k_gates, dim3(512), dim3(256), 0, nullptr, e, n, sigmoid, tanh);
+  return hipGetLastError() == hipSuccess && hipDeviceSynchronize() == hipSuccess ? RNNT_OK : RNNT_E_HIP;
+}
+
 int rnnt_beam_debug_block_map(int32_t a_tiles, int32_t a_m, int32_t b_begin, int32_t b_end, int32_t b_m, int32_t *role,
                               int32_t *ntile, int32_t *mtile, int32_t cap) {
   if (a_tiles < 0 || a_m < 0 || b_begin < 0 || b_end < b_begin || b_m < 0) return RNNT_E_ARG;
