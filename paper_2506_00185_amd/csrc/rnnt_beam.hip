@@ -57,11 +57,11 @@ struct KernelTimer {
 
 enum {
   KT_ENCPROJ = 0, KT_INIT, KT_JOINT, KT_SELECT, KT_LM, KT_LSTM, KT_PREDPROJ, KT_BACKTRACE, KT_JOINTBIG, KT_ROWSELECT,
-  KT_STATELESS, KT_UTTSELECT, KT_COUNT
+  KT_STATELESS, KT_UTTFEW, KT_UTTSELECT, KT_COUNT
 };
 const char *kKernelNames[KT_COUNT] = {"k_gemm_tiled(enc_proj)", "k_init",      "k_step_main", "k_select",    "k_lm_rows",
                                       "k_lstm_pointwise",    "k_pred_proj", "k_backtrace", "k_joint_big", "k_row_select",
-                                      "k_stateless_pre",     "k_utt_few"};
+                                      "k_stateless_pre",     "k_utt_few",   "k_utt_select"};
 
 // Device memory a decode works in beyond its inputs and outputs, laid out for given maxima.  The handle owns one
 // (a single allocation made at create); the allocation-free entry point lays one out in the static array.
@@ -849,17 +849,18 @@ int launch_step(rnnt_beam *h, hipStream_t s, const StepPlan &p, int step_off, in
       a.utt_ctr = w.tile_ctr;
       fill_select_args(h, p, step_off, 1, a.sel);
       fill_stateless_pre_big(h, p, 0, a.pre);
-      ScopedKernelTime tm(h, s, (big_tail(h, p) && !a.lm) ? KT_UTTSELECT : KT_ROWSELECT);
+      // one block per utterance: without an LM term in the keys; with the prefix search and with early pruning from K lists
+      const bool utt = big_tail(h, p) && !a.lm, lists = (a.sel.prefix && p.algo == RNNT_AES) || a.sel.lm_early;
+      ScopedKernelTime tm(h, s, !utt ? KT_ROWSELECT : lists ? KT_UTTSELECT : KT_UTTFEW);
       // without an LM term in the keys the chunk statistics of the contraction say which chunks to read
       const dim3 grid(p.M), block(64 * kRowWaves);
       if (big_tail(h, p)) {
         one_list_form(h, p, [&](auto kc, auto plain) {
           constexpr int KC = decltype(kc)::value, PLAIN = decltype(plain)::value;
-          const dim3 utts(p.B), waves(64 * p.K);  // one block per utterance
-          const bool prefix = a.sel.prefix && p.algo == RNNT_AES;
-          if (!a.lm && !prefix && !a.sel.lm_early) hipLaunchKernelGGL((k_utt_few<KC, PLAIN>), utts, waves, 0, s, a);
+          const dim3 utts(p.B), waves(64 * p.K);
+          if (utt && !lists) hipLaunchKernelGGL((k_utt_few<KC, PLAIN>), utts, waves, 0, s, a);
           else if constexpr (PLAIN != 0) return;  // (neither is of the plain forms)
-          else if (!a.lm) hipLaunchKernelGGL((k_utt_select<KC>), utts, waves, 0, s, a);
+          else if (utt) hipLaunchKernelGGL((k_utt_select<KC>), utts, waves, 0, s, a);
           else if constexpr (PLAIN == 0) hipLaunchKernelGGL((k_row_select<KC, false>), grid, block, 0, s, a);
         });
       } else {

@@ -78,3 +78,19 @@ def test_materialised_logits_at_the_edges(oracle, kw):
     o = oracle.decode(c, w, enc, L, log=True)
     full, exempt = compare(g, o, TOL_BF16, TIE_BF16, walk=make_walk(oracle, c, w, enc, L, g, TOL_BF16))
     assert full + exempt == c["B"]
+
+
+@pytest.mark.parametrize("kernel,kw,prune", [
+    ("k_utt_few", dict(algo="aes"), None), ("k_utt_select", dict(algo="aes", aes_prefix=True), None), ("k_utt_few", dict(aes_prefix=True), None),
+    ("k_utt_select", dict(), "early"), ("k_row_select", dict(), "late"),
+])
+def test_profile_names_the_kernel_that_ran(kernel, kw, prune):
+    import paper_2506_00185_amd as A
+    c = S.custom_config(**dict(dict(B=2, T=4, V=300, beam=4, s=2, prec="bf16", blank_bias=3.0, **W64, **ST, ctx=2), **kw))
+    w, L = S.make_weights(c, 5), S.make_lengths(c, 7)
+    lm = A.NGramLM(S.make_lm(V=300, order=2, n_target=900, zipf_s=1.1, seed=5)) if prune else None
+    dec = A.BeamDecoder(c, w, joint_path="materialized", lm_prune=prune or "late")
+    dec.set_profiling(True)
+    gpu_decode(dec, S.make_enc(c, L, 8), L, lm=lm, lm_weight=0.3 if lm else 0.0)
+    times = dec.kernel_times()
+    assert {n for n in ("k_utt_few", "k_utt_select", "k_row_select") if times.get(n, (0, 0))[1]} == {kernel}
