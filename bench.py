@@ -97,11 +97,16 @@ def kernel_bytes(name: str, c: dict, M: int, B: int, T: int, K: int, steps: int)
     if name == "k_select":                # stand-alone selection from one list per hypothesis
         return M * (8.0 * K + 8.0 + 4.0 * (1 + nd)) + state + tree
     if name in ("k_row_select", "k_utt_select", "k_utt_few"):
-        # without an LM: the chunk statistics (8 bytes per 32 columns) and about 2 K chunks of 128 bytes per row;
-        # with one: one read of the float32 logits and of the LM rows.  Then the tail: selection and activations
+        # without an LM term in the keys: the chunk statistics (8 bytes per 32 columns) and chunks of 128 bytes, about 2 K of
+        # a row, k_utt_few of an utterance; with one: one read of the float32 logits and of the LM rows.  Blank and
+        # duration logits: from the bf16 activations.  Then the selection and the new activations.
         Npad = (V + 255) // 256 * 256
-        scan = 4.0 * M * Npad + lm if c["lm"] else M * (8.0 * Npad / 32 + 2 * K * 128.0)
-        return scan + M * (8.0 * K + 8.0 + 4.0 * (1 + nd)) + state + tree + M * H * (4.0 * (1 + c["ctx"]) + 2.0)
+        stats, chunks = 8.0 * M * Npad / 32, 2 * K * 128.0 * (M / K if name == "k_utt_few" else M)
+        special = 2.0 * M * H + 4.0 * (1 + nd) * H
+        scan = 4.0 * M * Npad + lm if c["lm"] else stats + chunks
+        # (a block per hypothesis: lists, statistics and those logits go through memory, from block to block)
+        lists = M * (8.0 * K + 8.0 + 4.0 * (1 + nd)) if name == "k_row_select" else 0.0
+        return scan + special + lists + state + tree + M * H * (4.0 * (1 + c["ctx"]) + 2.0)
     if name == "k_stateless_pre":
         return M * H * (4.0 * (1 + c["ctx"]) + (2.0 if uses_materialized_path(c, M) else 4.0))
     if name == "k_joint_big":
