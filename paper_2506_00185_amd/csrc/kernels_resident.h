@@ -11,7 +11,8 @@
 //   cell    words of the last step -> the owners of W_hh tiles update the cells of their units        -> h
 //   P       h    -> the owners of projection tiles: pre = f_proj[frame] + W_pred h + b_pred           -> pre
 //   J       pre  -> the owners of output-layer tiles: z = W_out ReLU(pre) + b_out                     -> logits
-//   select  z    -> one block per utterance (a wave per hypothesis): the Beam best of all, tree, ..   -> words
+//   select  z    -> one to four utterances per block (its waves share out the rows of logits, one per utterance selects): the Beam best
+//           of all, tree, ..   -> words
 //   R       h    -> the owners of W_hh tiles: W_hh h for the next cell update, under the selection
 // Hand-over between blocks: an array that one phase writes and another reads is pre-filled with a bit pattern that no
 // result has (a NaN with all bits set); the reader loads the data itself, device-coherently, until none of it holds the
@@ -50,7 +51,7 @@ constexpr int kResMaxNT = 3;         // slot tiles per group
 constexpr int kResMaxR = 6;          // W_hh tiles per block
 constexpr int kResMaxLdsTiles = 2;   // tiles that wait in LDS: projection tiles and the output-layer tile beyond those in registers
 constexpr int kResMaxP = 2;
-constexpr int kResMaxSel = 4;        // utterances per selecting block
+constexpr int kResMaxSel = 4;        // utterances per selecting block (more where the others find no room, see make_plan)
 constexpr int kResMaxRounds = 10;    // rounds of 8 k per wave slice: H, P <= 640
 constexpr int kResQuads = 5;         // 16-byte words of a lane of a split tile
 constexpr int kResTileFloats = kResWaves * kResQuads * 64 * 4;  // a split tile

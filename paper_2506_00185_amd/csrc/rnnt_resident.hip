@@ -205,7 +205,7 @@ Plan make_plan(const Resident &r, const rnnt_config_t &c, int B, int K, bool has
   p.columns = fold && r.form == kResSplit && whole_width(c);
   int most_sel = std::max(1, p.n_blocks / 8);
   p.upc = (p.nu + most_sel - 1) / most_sel;
-  if (p.upc > kResMaxSel || p.upc * K * K > 512 || p.upc * K > kResMaxHyps) return p;
+  if (p.upc > kResMaxSel || p.upc * K > kResMaxHyps) return p;
   p.n_sel = (p.nu + p.upc - 1) / p.upc;
   while (!assign_tiles(c, p.n_blocks - p.n_sel, p.columns, p.tab)) {
     // Columns dealt one by one take more places than the tile that they lie in: with eight durations and V = 1024 one more than 28
