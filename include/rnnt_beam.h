@@ -95,8 +95,8 @@ typedef struct {
   int32_t use_graph;         /* 1: no launch per step.  Decoders whose weights fit the chip (H, for LSTM models also P, multiples of
                                 64 up to 640; V <= 1024; no tdt_all_pairs; fused joint) run the step loop as one launch whose
                                 blocks keep the weights on chip ("resident loop"), in batches of up to 48 hypotheses (stateless
-                                decoders 16) and 16 utterances per 32 compute units; narrow decoders with wide beams, for which
-                                it is slower, and all others replay the per-step kernels as a captured HIP graph (Sec. 2.1,
+                                decoders 16) and 16 utterances per 32 compute units; some narrow decoders with wide beams or
+                                many utterances, and all others, replay the per-step kernels as a captured HIP graph (Sec. 2.1,
                                 "CUDA Graphs").  0: the per-step kernels are launched one by one.  The results are the same bit
                                 for bit up to 256 hypotheses.
                                 The resident loop needs memory for a second copy of the weights (without it the per-step

@@ -162,24 +162,27 @@ bool assign_tiles(const rnnt_config_t &c, int n_blocks, bool columns, std::vecto
 }
 
 // Decoders that stay with the per-step launches although they fit the loop: narrow ones, whose per-step launches are short, with
-// several tiles of slots or wide beams, whose selection takes longer here.  Both sides timed, time of the per-step launches over the
-// loop's.  Split decoders (320 wide and more): 1.01 and more at each of 250 shapes of two and three tiles (to 512 wide, V = 29
+// several tiles of slots or wide beams.  Both sides timed, time of the per-step launches over the loop's.  The lines were drawn while the
+// loop's selection took each row's Beam best first; what is given first at each of them is from then.  With the selection of the Beam
+// best of all at once the loop is the faster one behind each of them as well, 1.02 to 3.3 times at 273 shapes (V = 29 to 1000, beams 3 to 16),
+// as given after "since": they hold back decodes that could take it.
+// Not held back, then: split decoders (320 wide and more) 1.01 and more at each of 250 shapes of two and three tiles (to 512 wide, V = 29
 // to 1000, beams 5 to 16, LM and TDT among them; means 1.33 in float32, 1.23 with the bf16 joint); 640 wide 1.07 and more.
-// Not split, 64 to 256 wide: one tile 1.23 to 1.94, two tiles at beams up to 8 1.24 to 1.52.  (Taken before the selection was for the
-// Beam best of all at once, which makes the loop 1.2 to 1.7 times as fast: the lines could be moved further, none back.)
-bool per_step_is_faster(const Resident &r, const rnnt_config_t &c, int B, int K, int n_tiles) {
+// Not split, 64 to 256 wide: one tile 1.23 to 1.94, two tiles at beams up to 8 1.24 to 1.52.
+bool stays_with_launches(const Resident &r, const rnnt_config_t &c, int B, int K, int n_tiles) {
   const bool bf = c.prec == RNNT_BF16_JOINT;
-  // 64 and 128 wide, V = 1000: one utterance 0.95 to 1.08, eight 1.01 to 1.15; 320 wide, bf16, one utterance 1.09 and 1.11 (these two not
-  // moved yet)
+  // 64 and 128 wide, V = 1000: one utterance 0.95 to 1.08, eight 1.01 to 1.15; 320 wide, bf16, one utterance 1.09 and 1.11.  Since: 1.53 to
+  // 3.3
   if (c.pred != RNNT_PRED_LSTM) return K > 8 && (c.H <= 128 || (bf && B == 1 && c.H <= 320));
   if (std::max(c.H, c.P) <= 192) {
-    // float32, three tiles: V = 1000 at beams up to 8 1.17 to 1.26; else 0.85 to 1.50, V = 260 at beams above 4 and V = 29 above 1
+    // float32, three tiles: V = 1000 at beams up to 8 1.17 to 1.26; else 0.85 to 1.50, V = 260 at beams above 4 and V = 29 above 1.  Since:
+    // 1.08 to 2.25
     if (!bf && n_tiles == 3 && !(c.V > 512 && K <= 8)) return true;
-    // two tiles, beams above 8, float32: V = 29 and 260 1.12 to 1.65, V = 500 0.98 to 1.27, V = 1000 1.04 to 1.13 (not moved yet);
-    // bf16: V = 450 0.97 to 1.84, V > 512 1.00 to 1.34
+    // two tiles, beams above 8, float32: V = 29 and 260 1.12 to 1.65, V = 500 0.98 to 1.27, V = 1000 1.04 to 1.13;
+    // bf16: V = 450 0.97 to 1.84, V > 512 1.00 to 1.34.  Since: float32 1.54 to 2.85, bf16 1.46 to 1.86
     return n_tiles > 1 && K > 8 && c.V > (bf ? 512 : 384);
   }
-  // 256 wide, three tiles: V up to 500 at beam 4 0.93 to 0.99, else 0.94 to 1.40
+  // 256 wide, three tiles: V up to 500 at beam 4 0.93 to 0.99, else 0.94 to 1.40.  Since, beams up to 4: 1.02 to 1.18
   return r.form == kResF32 && n_tiles == 3 && K <= 4 && c.V <= 512;
 }
 
@@ -197,10 +200,11 @@ Plan make_plan(const Resident &r, const rnnt_config_t &c, int B, int K, bool has
   const int slots = p.nu * K;
   p.NT = (slots + kResSlot - 1) / kResSlot;
   if (p.NT > kResMaxNT) return p;
-  // Stateless decoders: one tile of slots, whose last tokens the owners of output-layer tiles keep.  (With more, float32, 640 wide, us per
-  // step here / there, before hand-overs stayed in the L2: two tiles, batch 16 beam 16 34.8 / 33.3; three, batch 32 beam 12 37.3 / 36.0.)
+  // Stateless decoders: one tile of slots, whose last tokens the owners of output-layer tiles keep.  (A form for more, float32, 640 wide, us
+  // per step here / there, before hand-overs stayed in the L2: two tiles, batch 16 beam 16 34.8 / 33.3; three, batch 32 beam 12 37.3 / 36.0.
+  // It has not been tried since.)
   if (c.pred != RNNT_PRED_LSTM && p.NT > 1) return p;
-  if (per_step_is_faster(r, c, B, K, p.NT)) return p;
+  if (stays_with_launches(r, c, B, K, p.NT)) return p;
   const bool bf = c.prec == RNNT_BF16_JOINT;
   p.columns = fold && r.form == kResSplit && whole_width(c);
   int most_sel = std::max(1, p.n_blocks / 8);
