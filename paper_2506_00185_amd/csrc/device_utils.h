@@ -406,21 +406,22 @@ __device__ __forceinline__ void wave_best(double &v, int &i) {
 // n / d by Newton's iteration on the reciprocal and two corrections of the quotient by its residual (Markstein, IBM Journal of Research
 // and Development 34, 1990), for n from 0 to 1 and d from 1/4 to below 2^126, whose reciprocal is normal: the correctly rounded quotient, a
 // subnormal one too.  The compiler's division scales its operands for the others, by way of the one condition register, which keeps
-// divisions from overlapping.  FIXUP: d may be infinite.
+// divisions from overlapping.  FIXUP: d may be infinite.  (It comes negated: a residual is then one instruction with n as a literal, where the
+// other sign would take a move of n to a register first; one utterance 0.7 % slower.)
 template <bool FIXUP>
-__device__ __forceinline__ float div_unit_f(float n, float d) {
-  float r = __builtin_amdgcn_rcpf(d);
-  r = fmaf(fmaf(-d, r, 1.f), r, r);
+__device__ __forceinline__ float div_unit_f(float n, float minus_d) {
+  float r = __builtin_amdgcn_rcpf(-minus_d);
+  r = fmaf(fmaf(minus_d, r, 1.f), r, r);
   float q = n * r;
-  q = fmaf(fmaf(-d, q, n), r, q);
-  q = fmaf(fmaf(-d, q, n), r, q);
-  return FIXUP ? __builtin_amdgcn_div_fixupf(q, d, n) : q;
+  q = fmaf(fmaf(minus_d, q, n), r, q);
+  q = fmaf(fmaf(minus_d, q, n), r, q);
+  return FIXUP ? __builtin_amdgcn_div_fixupf(q, -minus_d, 1.f) : q;  // (any n that is a number does)
 }
 // 1 / (1 + e) for e from 0 to infinity: numerator and denominator are quarters (the rounding of 1 + e is the same), since 1 + e may be
 // beyond 2^126 and its reciprocal, flushed to zero, would make the quotient 0 there instead of some 2^-127
-__device__ __forceinline__ float sigmoid_of(float e) { return div_unit_f<true>(0.25f, fmaf(e, 0.25f, 0.25f)); }
+__device__ __forceinline__ float sigmoid_of(float e) { return div_unit_f<true>(0.25f, fmaf(e, -0.25f, -0.25f)); }
 // (1 - e) / (1 + e) for e from 0 to 1
-__device__ __forceinline__ float tanh_of(float e) { return div_unit_f<false>(1.f - e, 1.f + e); }
+__device__ __forceinline__ float tanh_of(float e) { return div_unit_f<false>(1.f - e, -1.f - e); }
 __device__ __forceinline__ float sigmoid_f(float x) { return sigmoid_of(__expf(-x)); }
 __device__ __forceinline__ float tanh_f(float x) {
   const float r = tanh_of(__expf(-2.f * fabsf(x)));
